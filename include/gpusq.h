@@ -201,14 +201,26 @@ gpusq_status gpusq_spgemm_int8(const int8_t* Xq, const void* Wpacked, const floa
  * calibrated scale before every quantised layer] folded into the GEMM: X [M][K] fp16 is turned into the codes
  * Xq = clamp(rint(X / act_scale[0]), -127, 127) on its way to the matrix instructions (the code rule of
  * gpusq_quantize_int8 with scale_is_input != 0; bit-identical to calling that first), so a layer with a static scale is
- * one launch instead of two.  Only the latency kernel, through whose registers X passes, can do this: a problem that
- * gpusq_spgemm_plan assigns to a tile kernel (kernel >= 2) returns GPUSQ_ERR_UNSUPPORTED and is served by
+ * one launch instead of two.  Only the kernels for small problems, through whose registers X passes, can do this: a problem
+ * that gpusq_spgemm_plan assigns to a tile kernel (kernel >= 2) returns GPUSQ_ERR_UNSUPPORTED and is served by
  * gpusq_quantize_int8 + gpusq_spgemm_int8.  Every workgroup quantises the rows of its own tile, so the saving is that
- * of a launch (a few microseconds) against extra work per K step: it pays for short K (up to about 384).
+ * of a launch (a few microseconds) against extra work per K step; gpusq_linear_int8 takes whichever is the faster.
  * All other arguments as for gpusq_spgemm_int8. */
 gpusq_status gpusq_spgemm_int8_xf16(const void* X, const void* Wpacked, const float* act_scale, const float* w_scale,
                                     const float* bias, void* Y, gpusq_dtype out_dt, const float* out_scale,
                                     int64_t M, int64_t N, int64_t K, int epilogue, void* stream);
+
+/* The whole INT8 layer at inference [Sec. 2.2, 3.4]: quantise X [M][K] (x_dt = GPUSQ_F32 or GPUSQ_F16) per tensor, then the
+ * product of gpusq_spgemm_int8 on the codes.  Results, the codes in Xq [M][K] and the scale in act_scale[0] included, are
+ * bit-identical to gpusq_quantize_int8(GPUSQ_PER_TENSOR) followed by gpusq_spgemm_int8; scale_is_input and workspace as for
+ * the former, all other arguments as for the latter.  For few rows of fp16 the two are one kernel, and for small X (or a
+ * given scale) the layer is a single launch. */
+gpusq_status gpusq_linear_int8(const void* X, gpusq_dtype x_dt, const void* Wpacked, float* act_scale, int scale_is_input,
+                               const float* w_scale, const float* bias, void* Y, gpusq_dtype out_dt, const float* out_scale, int8_t* Xq,
+                               void* workspace, int64_t M, int64_t N, int64_t K, int epilogue, void* stream);
+/* How many launches that call takes on a device with `cus` compute units (cus <= 0: the current device): 1 or 2 where the GEMM
+ * quantises fp16 activations itself, else 2 (scale_is_input != 0) or 3; 0 for invalid sizes or types.  Host-side. */
+int gpusq_linear_int8_launches(gpusq_dtype x_dt, int64_t M, int64_t N, int64_t K, int epilogue, int scale_is_input, int cus);
 
 /* ---- patch embedding [Sec. 3.3: the patch-embedding layer is a convolution with C input channels, D_embed output
  * channels and kernel size = stride = P on images N x C x H x W, each P x P patch becoming one token; 2:4 sparsity is
@@ -237,20 +249,22 @@ gpusq_status gpusq_patch_embed16_fp16(const void* img, const void* Wpacked, cons
 
 /* ---- host-side introspection (no GPU work, no device access when cus > 0): how gpusq_spgemm_fp16 / gpusq_spgemm_int8
  * (dt = GPUSQ_F16 / GPUSQ_I8 = the operand type) decompose a problem on a device with `cus` compute units (cus <= 0: the
- * current device).  out[0] = kernel (0: small kernel, 64 x 64 tiles; 1: small kernel, 128 x 128 tiles, any K % 16 == 0;
+ * current device).  out[0] = kernel (0: one of the kernels for small problems, 64 x 64 tiles or, for few rows,
+ * 64 channels x 16 or 32 rows with K split over the wavefronts of a workgroup; 1: small kernel, 128 x 128 tiles, any K % 16 == 0;
  * 2: tile kernel with one workgroup per CU, tiles of 256 channels x up to 256 rows; 3: tile kernel with two workgroups per
  * CU, tiles of 256 channels x up to 128 rows, the template the dense twins are built from); for the tile kernels out[1] =
  * rows per tile unit u, out[2] = 256-channel blocks, out[3] = full_tm (a full tile has u * full_tm rows), out[4] = row
  * chunks covered by full tiles, out[5] = tail_tm (the remaining rows are cut into tiles of u * tail_tm rows), out[6] =
  * tiles in all, out[7] = workgroups launched.  Same argument checks as the GEMM calls (sizes only).
  * The query describes gpusq_spgemm_fp16 / gpusq_spgemm_int8 only: the fused patch-embedding calls
- * (gpusq_patch_embed16_*) always run on tile kernel 2, whatever this query reports for a GEMM of the same sizes. */
+ * (gpusq_patch_embed16_*) run on the kernel for few rows or on tile kernel 2, whatever this query reports for a GEMM of the same
+ * sizes. */
 gpusq_status gpusq_spgemm_plan(gpusq_dtype dt, int64_t M, int64_t N, int64_t K, int epilogue, int cus, int32_t out[8]);
 
-/* Testing aid: kernel = 0, 1, 2 or 3 makes the sparse GEMM entry points (and gpusq_spgemm_plan's out[0]) take that kernel
- * for every problem it can run (the tile kernels need K * element size % 128 == 0), so that every kernel can be checked on
+/* Testing aid: kernel = 0 (64 x 64 tiles), 1, 2, 3 or 4 (few rows, shown as 0 by gpusq_spgemm_plan) makes the sparse GEMM entry
+ * points (and gpusq_spgemm_plan's out[0]) take that kernel for every problem it can run (the tile kernels need K * element size % 128 == 0), so that every kernel can be checked on
  * the same shapes; 0 and 1 also keep the dense twins on their small kernel; any other value gives the choice back to the
- * size rules.  Returns the previous setting (-1 = none).  Process-wide; the environment variable GPUSQ_FORCE_KERNEL (0..3)
+ * size rules.  Returns the previous setting (-1 = none).  Process-wide; the environment variable GPUSQ_FORCE_KERNEL (0..4)
  * gives the initial setting and is read once, when the library is loaded.  Not meant for production callers. */
 int gpusq_force_kernel(int kernel);
 

@@ -322,6 +322,31 @@ gpusq_status gpusq_spgemm_int8_xf16(const void* X, const void* Wpacked, const fl
   return launch_spgemm(true, a, (hipStream_t)stream);
 }
 
+gpusq_status gpusq_linear_int8(const void* X, gpusq_dtype x_dt, const void* Wpacked, float* act_scale, int scale_is_input,
+                               const float* w_scale, const float* bias, void* Y, gpusq_dtype out_dt, const float* out_scale, int8_t* Xq,
+                               void* workspace, int64_t M, int64_t N, int64_t K, int epilogue, void* stream) {
+  gpusq_status st = check_gemm(X, Wpacked, bias, Y, M, N, K, epilogue);
+  if (st != GPUSQ_OK) return st;
+  if (!Xq || !act_scale || (!scale_is_input && !workspace)) return GPUSQ_ERR_NULL;
+  if (x_dt != GPUSQ_F32 && x_dt != GPUSQ_F16) return GPUSQ_ERR_UNSUPPORTED;
+  if (!aligned16(Xq) || (workspace && !aligned16(workspace))) return GPUSQ_ERR_ALIGN;
+  st = check_int8_extras(act_scale, w_scale, out_dt, out_scale);
+  if (st != GPUSQ_OK) return st;
+  GemmArgs a{X, Wpacked, act_scale, w_scale, bias, out_scale, Y, (int)M, (int)N, (int)K, epilogue, (int)out_dt};
+  return launch_linear_int8(a, x_dt, Xq, act_scale, scale_is_input, workspace, (hipStream_t)stream);
+}
+
+int gpusq_linear_int8_launches(gpusq_dtype x_dt, int64_t M, int64_t N, int64_t K, int epilogue, int scale_is_input, int cus) {
+  if (M <= 0 || M > INT32_MAX || check_nk(N, K) != GPUSQ_OK || K % 16 != 0 || N % 4 != 0) return 0;
+  if (x_dt != GPUSQ_F32 && x_dt != GPUSQ_F16) return 0;
+  GemmArgs a{};
+  a.M = (int)M;
+  a.N = (int)N;
+  a.K = (int)K;
+  a.epilogue = epilogue;
+  return linear_int8_launches(a, x_dt, scale_is_input, cus);
+}
+
 gpusq_status gpusq_gemm_fp16_dense(const void* X, const void* W, const float* bias, void* Y, int64_t M, int64_t N,
                                    int64_t K, int epilogue, void* stream) {
   gpusq_status st = check_gemm(X, W, bias, Y, M, N, K, epilogue);

@@ -46,6 +46,8 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // row in one store; fragments 2 and 3 give the next 32 channels the same way.
 __host__ __device__ inline int packed_row_to_channel(int t, int r) { return 32 * (t >> 1) + 8 * (r >> 2) + 4 * (t & 1) + (r & 3); }
 
+__device__ __forceinline__ float scale_reciprocal(float s) { return __fdiv_rn(1.0f, s); }
+
 // Integer code of x under the scale s: clamp(rint(x / s), -127, 127) with the IEEE fp32 division of the definition
 // (not a reciprocal multiply) and round-half-even, NaN -> 0, so that the code is decided exactly as a plain CPU
 // evaluation of the formula decides it -- but without paying for a division per element.  r = fl(1 / s) (correctly
@@ -115,7 +117,95 @@ __device__ __forceinline__ int quantize_code(float x, float s, float r, float qm
   quantize_codes<1>(xs, s, r, q, qmax);
   return q[0];
 }
-__device__ __forceinline__ float scale_reciprocal(float s) { return __fdiv_rn(1.0f, s); }
+
+// The same codes for fp16 input with less arithmetic: one fused multiply-add per value, x * r + 1.5 * 2^23 (the exact product,
+// rounded once, half to even, to a whole number), whose low byte is the code.  Whether that decides every code as
+// rint(x / s) does depends on s alone and is checked once per scale and workgroup: both are monotone in x, so they agree on
+// every fp16 x if they agree on the two fp16 neighbours of each code boundary (c + 0.5) * s, 254 values, one per thread; any
+// other x lies at least one fp16 spacing, 2^-11 of it, from every boundary, thousands of times the rounding errors of either.
+// Where they disagree, the workgroup refines every product to the correctly rounded quotient first (t = x r, then t + r times
+// the exact remainder x - t s: Markstein's division with a correctly rounded reciprocal), which takes three more operations.
+// A scale outside 2^-100 .. 2^100 (denormal, 0, infinite, NaN) needs neither: every quotient is then far beyond the largest
+// code or rounds to 0, or is NaN, and so is the product.
+struct Fp16Quantiser {
+  typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+  typedef int i4 __attribute__((ext_vector_type(4)));
+  float s, r;
+  bool refine;  // set by the caller from the threads' votes
+
+  // The check of thread `tid` of a workgroup of 256 or more: true if it found a disagreement.
+  __device__ __forceinline__ bool prepare(float scale, int tid) {
+    s = scale;
+    r = scale_reciprocal(scale);
+    if (!(scale >= 0x1p-100f && scale <= 0x1p100f) || tid >= 254) return false;
+    const float boundary = ((float)(tid >> 1) + 0.5f) * scale;
+    const h2 down = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(boundary, 0.0f));
+    const unsigned short bits = (unsigned short)(__builtin_bit_cast(unsigned short, down[0]) + (tid & 1));
+    if (bits >= 0x7C00) return false;  // no fp16 number there; infinity is clamped either way
+    const float x = (float)__builtin_bit_cast(_Float16, bits);
+    const float fast = __fmaf_rn(x, r, 12582912.0f) - 12582912.0f, exact = rintf(__fdiv_rn(x, scale));
+    return fminf(fast, 127.0f) != fminf(exact, 127.0f);
+  }
+  // Codes of 8 values as bytes.  CLAMP: values may exceed 127 s (a given scale; with the scale of the data's own range no
+  // quotient reaches 127.5).  The code of a NaN is 0.
+  template <bool CLAMP>
+  __device__ __forceinline__ void codes(i4 raw, unsigned& lo, unsigned& hi) const {
+    const h8 x = __builtin_bit_cast(h8, raw);
+    const h2 sum = (h2{x[0], x[1]} + h2{x[2], x[3]}) + (h2{x[4], x[5]} + h2{x[6], x[7]});
+    float y[8];
+    if (refine) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float t = (float)x[j] * r;
+        y[j] = __builtin_fmaf(__builtin_fmaf(-t, s, (float)x[j]), r, t) + 12582912.0f;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) y[j] = __builtin_fmaf((float)x[j], r, 12582912.0f);
+    }
+    const _Float16 all = sum[0] + sum[1];
+    // a NaN (or infinities of both signs, which lose nothing here), or a scale so small that 0 * r is one
+    if (__builtin_amdgcn_ballot_w64(!(all == all)) != 0 || !(r <= 3.4028234663852886e38f)) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) y[j] = y[j] == y[j] ? y[j] : 12582912.0f;
+    }
+    if constexpr (CLAMP) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) y[j] = __builtin_amdgcn_fmed3f(y[j], 12582912.0f - 127.0f, 12582912.0f + 127.0f);
+    }
+    unsigned b[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) b[j] = __float_as_uint(y[j]);
+    const unsigned p01 = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), p23 = __builtin_amdgcn_perm(b[3], b[2], 0x04000c0cu);
+    const unsigned p45 = __builtin_amdgcn_perm(b[5], b[4], 0x0c0c0400u), p67 = __builtin_amdgcn_perm(b[7], b[6], 0x04000c0cu);
+    lo = p01 | p23;
+    hi = p45 | p67;
+  }
+};
+
+// Largest magnitude (NaN aside) of this thread's share of n fp16 values, n % 8 == 0: 16-byte loads, eight of them in flight.
+__device__ __forceinline__ float range_of_fp16(const uint8_t* X, int64_t n, int tid, int threads) {
+  typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+  typedef unsigned u4 __attribute__((ext_vector_type(4)));
+  const u4* x = (const u4*)X;
+  const int64_t vecs = n / 8;
+  h8 m = h8(0);
+  for (int64_t i = tid; i < vecs; i += 8 * (int64_t)threads) {
+    u4 v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int64_t at = i + j * (int64_t)threads;
+      v[j] = x[at < vecs ? at : vecs - 1];
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) m = __builtin_elementwise_max(m, __builtin_bit_cast(h8, v[j] & 0x7fff7fffu));
+  }
+  float amax = 0.0f;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) amax = fmaxf(amax, (float)m[j]);
+  return amax;
+}
 
 // Selection rule inside one group of 4 [Sec. 3.1: two of every four contiguous elements are zero; the rule is this
 // library's reading]: element i is kept iff fewer than two elements beat it, where j beats i when |w_j| > |w_i|, or
@@ -153,12 +243,28 @@ struct GemmArgs {
   // patch (py, px) of image b, column (c*P + i)*P + j its pixel (py*P + i, px*P + j) of channel c; M = B*(H/P)*(W/P),
   // K = C*P*P.  The tile kernel then fetches its X slabs from the image directly (no flattened-patch buffer).
   int patch_P = 0, patch_C = 0, patch_H = 0, patch_W = 0;
-  // INT8 path, small kernel only: X holds fp16 activations, quantised inside the kernel with the static act_scale
+  // INT8 path, small kernels only: X holds fp16 activations, quantised inside the kernel with the static act_scale
   int x_f16 = 0;
+  // ... or, in the kernel for few rows, with the scale of X's own range: that of the `npartial` partial maxima a range pass
+  // left behind, or of all of X, read by every workgroup; the scale goes to scale_out, the codes to xq_out (if not NULL)
+  int range_mode = 0, npartial = 0;
+  const float* partial = nullptr;
+  float* scale_out = nullptr;
+  int8_t* xq_out = nullptr;
 };
+enum { kRangeGiven = 0, kRangePartials = 1, kRangeHere = 2 };
 
 gpusq_status launch_spgemm(bool is_i8, const GemmArgs& a, hipStream_t s);
 gpusq_status launch_dense(bool is_i8, const GemmArgs& a, hipStream_t s);
+// the sparse GEMM for few rows (fewrows.hip)
+bool fewrows_supports(const GemmArgs& a);
+bool fewrows_folds_quantiser(int64_t M, int64_t N, int64_t K, int resident);
+gpusq_status launch_fewrows(bool is_i8, const GemmArgs& a, int resident, hipStream_t s);
+// quantise (dt of X, workspace as for launch_quantize) and multiply: one, two or three launches
+gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, void* workspace, hipStream_t s);
+int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int cus);
+// the range pass of the per-tensor quantiser alone; returns the number of partial maxima it leaves in the workspace
+int launch_amax(const void* X, gpusq_dtype dt, int64_t n, void* workspace, hipStream_t s);
 int forced_kernel();                // -1 when none is forced
 int set_forced_kernel(int kernel);  // testing aid, see gpusq_force_kernel; returns the previous value
 gpusq_status plan_spgemm(bool is_i8, int64_t M, int64_t N, int64_t K, int epilogue, int cus, int32_t* out);

@@ -337,6 +337,19 @@ __global__ void __launch_bounds__(256) quantize_tensor_kernel(const T* __restric
 }
 
 template <typename T>
+static int launch_amax_typed(const T* X, int64_t n, float* partial, hipStream_t s) {
+  const int64_t want = ceil_div(n, 256 * 8 * 2);
+  const int blocks = (int)(want < kAmaxMaxBlocks ? want : kAmaxMaxBlocks);
+  tensor_amax_kernel<T><<<(unsigned)blocks, 256, 0, s>>>(X, n, partial);
+  return blocks;
+}
+
+int launch_amax(const void* X, gpusq_dtype dt, int64_t n, void* workspace, hipStream_t s) {
+  return dt == GPUSQ_F32 ? launch_amax_typed((const float*)X, n, (float*)workspace, s)
+                         : launch_amax_typed((const _Float16*)X, n, (float*)workspace, s);
+}
+
+template <typename T>
 static gpusq_status quantize_typed(const T* X, int8_t* Xq, float* scale, int mode, int scale_is_input, int64_t rows,
                                    int64_t cols, void* workspace, hipStream_t s) {
   if (mode == GPUSQ_PER_ROW) {
@@ -348,10 +361,10 @@ static gpusq_status quantize_typed(const T* X, int8_t* Xq, float* scale, int mod
   // ... up to 2048 workgroups (every workgroup of the quantising pass first reduces the partial maxima: with 8192 of them the
   // pass took 1.5 us longer on 12608 x 768 activations, with 1024 or fewer the large tensors slow down)
   const unsigned blocks_q = (unsigned)(want < 2048 ? want : 2048);
-  const unsigned blocks_a = (unsigned)(want < kAmaxMaxBlocks ? want : kAmaxMaxBlocks);
+  int blocks_a = 0;
   const float* partial = nullptr;
   if (!scale_is_input) {
-    tensor_amax_kernel<T><<<blocks_a, 256, 0, s>>>(X, n, (float*)workspace);
+    blocks_a = launch_amax_typed<T>(X, n, (float*)workspace, s);
     partial = (const float*)workspace;
   }
   quantize_tensor_kernel<T><<<blocks_q, 256, 0, s>>>(X, Xq, scale, partial, (int)blocks_a, n);

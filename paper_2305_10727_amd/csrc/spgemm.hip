@@ -153,36 +153,16 @@ __device__ __forceinline__ void tile_x_offsets(uint32_t (&xoff)[4], int64_t m0, 
   }
 }
 
-// The same for the patch-embedding mode with P = 16: the 16-byte chunk kc of row m = (b, py, px) of the X operand is, for
-// int8, the 16 pixels of row py*16 + kc % 16 of patch column px in channel kc / 16 (for fp16, with 2 chunks per patch row:
-// row (kc / 2) % 16, channel kc / 32, half kc % 2).  A K step of 8 chunks stays inside one channel, so a lane's address
-// splits into a per-lane part that does not depend on the step (returned here, relative to the image batch: the patch's
-// first pixel plus the lane's logical chunk inside a step) and a wavefront-uniform part per step (patch_step_offset).
+// The same for the patch-embedding mode with P = 16 (see patch_chunk_offset).
 template <bool IS_I8>
 __device__ __forceinline__ void patch_x_offsets(uint32_t (&xoff)[4], int64_t m0, const GemmArgs& a, int wave, int lane) {
-  constexpr int ES = IS_I8 ? 1 : 2;
-  const int px_n = a.patch_W / 16, py_n = a.patch_H / 16;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int r = 8 * (wave + i * 8) + (lane >> 3);
     const int ch = (lane & 7) ^ ((r >> 1) & 7);  // logical chunk of the step this lane fetches (see tile_x_offsets)
-    // (32-bit unsigned arithmetic: M < 2^31, and 64-bit divisions here cost the K loop, into which the tile change is
-    // inlined, scores of registers)
-    uint32_t m = (uint32_t)m0 + (uint32_t)r;
-    m = m < (uint32_t)a.M ? m : (uint32_t)a.M - 1u;  // rows past the end re-read the last row
-    const uint32_t prow = m / (uint32_t)px_n, px = m - prow * (uint32_t)px_n;
-    const uint32_t b = prow / (uint32_t)py_n, py = prow - b * (uint32_t)py_n;
-    const int64_t pixel = (((int64_t)b * a.patch_C) * a.patch_H + py * 16) * a.patch_W + px * 16;  // first pixel of the patch, channel 0
-    const int row_in_step = IS_I8 ? ch : (ch >> 1), half = IS_I8 ? 0 : (ch & 1);
-    xoff[i] = (uint32_t)((pixel + (int64_t)row_in_step * a.patch_W) * ES + half * 16);
+    const uint32_t m = (uint32_t)m0 + (uint32_t)r;
+    xoff[i] = patch_chunk_offset<IS_I8>(a, m < (uint32_t)a.M ? m : (uint32_t)a.M - 1u, ch);  // rows past the end re-read the last row
   }
-}
-// Byte offset (wavefront-uniform) that K step ks adds: channel ks / S, first patch row (ks % S) * (16 / S), where a channel
-// takes S = 2 (int8) or 4 (fp16) steps.
-template <bool IS_I8>
-__device__ __forceinline__ int64_t patch_step_offset(const GemmArgs& a, int ks) {
-  constexpr int ES = IS_I8 ? 1 : 2, S = IS_I8 ? 2 : 4;
-  return ((int64_t)(ks / S) * a.patch_H * a.patch_W + (int64_t)(ks % S) * (16 / S) * a.patch_W) * ES;
 }
 
 // Per-lane byte offsets of the B operand inside an X slab: lane l reads row wm*16*tm + 16*mt + l%16, the 16-byte
@@ -755,12 +735,12 @@ static int num_cus() {
 // library is loaded, so that no launch pays for an environment lookup.
 static int initial_forced_kernel() {
   const char* f = getenv("GPUSQ_FORCE_KERNEL");
-  return (f && f[0] >= '0' && f[0] <= '3' && f[1] == 0) ? f[0] - '0' : -1;
+  return (f && f[0] >= '0' && f[0] <= '4' && f[1] == 0) ? f[0] - '0' : -1;
 }
 static std::atomic<int> g_forced_kernel{initial_forced_kernel()};
 int forced_kernel() { return g_forced_kernel.load(std::memory_order_relaxed); }
 int set_forced_kernel(int kernel) {
-  return g_forced_kernel.exchange(kernel >= 0 && kernel <= 3 ? kernel : -1);
+  return g_forced_kernel.exchange(kernel >= 0 && kernel <= 4 ? kernel : -1);
 }
 
 // Estimated run time (microseconds, fitted to traces and timings of the kernel on MI355X) of one tile of 64*tm rows: a
@@ -839,14 +819,24 @@ static TilePlan make_plan(int M, int N, int resident, int ksteps, bool gelu) {
 // With few rows (one image: M = 197) the tile kernel has too few tiles for the chip and the small kernel is about
 // twice as fast; from a few thousand rows on the tile kernel wins.  fused_patches: the patch gather exists in the tile
 // kernel only, so that mode keeps the plain size rule.
+// Few rows: up to 3 rounds of the 64-channel x 32-row tiles of the kernel with K split over its wavefronts (fp16: 6, its K
+// has twice the steps).  Around that line it is level with the 64 x 64 tiles (int8, 788 x 768 -> 2304, 3.5 rounds: 7.3 us
+// against 6.9; fp16, 788 x 1024 -> 4096, 6.3 rounds: 12.9 us against 17.6 and the tile kernel's 13.7).
+static bool few_rows(bool is_i8, int64_t M, int64_t N, int resident) {
+  return ceil_div(M, 32) * ceil_div(N, kRowBlock) <= (is_i8 ? 3 : 6) * (int64_t)resident;
+}
 static int kernel_choice(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu, int resident, bool fused_patches = false) {
   const int64_t k_bytes = K * (is_i8 ? 1 : 2);
   const int64_t ksteps = ceil_div(k_bytes, kStepBytes);
   const int64_t wgs64 = ceil_div(M, 64) * ceil_div(N, 64);
   // Testing aid: a forced kernel overrides the choice (2 only where the tile kernel can run the problem).
   if (const int c = g_forced_kernel.load(std::memory_order_relaxed); c >= 0) {
-    if (c < 2 || k_bytes % kStepBytes == 0) return c;
+    if (c < 2 || c == 4 || k_bytes % kStepBytes == 0) return c;
   }
+  // (the fused patch gather is refused up to 256 K outputs; beyond, it takes the kernel a GEMM of its sizes would, so that both
+  // add up in the same order)
+  if (fused_patches && M * N <= (int64_t)256 * 1024) return 0;
+  if (few_rows(is_i8, M, N, resident)) return 4;
   if (M * N <= (int64_t)256 * 1024) return 0;
   if (k_bytes % kStepBytes != 0) return wgs64 <= 2 * resident ? 0 : 1;
   if (fused_patches) return 2;
@@ -873,8 +863,8 @@ gpusq_status plan_spgemm(bool is_i8, int64_t M, int64_t N, int64_t K, int epilog
   const int resident = cus > 0 ? cus : num_cus();
   const int choice = kernel_choice(is_i8, M, N, K, (epilogue & GPUSQ_EPI_GELU) != 0, resident);
   for (int i = 0; i < 8; ++i) out[i] = 0;
-  out[0] = choice;
-  if (choice < 2) return GPUSQ_OK;
+  out[0] = choice == 4 ? 0 : choice;  // (both kernels for small problems are reported as 0)
+  if (choice < 2 || choice == 4) return GPUSQ_OK;
   const int ksteps = (int)(K * (is_i8 ? 1 : 2) / kStepBytes);
   const bool gelu = (epilogue & GPUSQ_EPI_GELU) != 0;
   const TilePlan p = choice == 2 ? make_plan((int)M, (int)N, resident, ksteps, gelu) : make_tile2_plan((int)M, (int)N, 2 * resident, ksteps, gelu, false);
@@ -926,11 +916,11 @@ static gpusq_status launch_typed(const GemmArgs& a, hipStream_t s) {
   const int resident = num_cus();
   const Decision& dec = decide(IS_I8, a.M, a.N, a.K, gelu, resident, a.patch_P != 0);
   const int choice = dec.choice;
-  // the fused patch gather exists in the tile kernel only, for 16 x 16 patches, fp16 output, no GELU
-  if (a.patch_P != 0 && choice == 3) return GPUSQ_ERR_UNSUPPORTED;
-  if (a.patch_P != 0 && (choice != 2 || a.patch_P != 16 || a.out_dt != GPUSQ_F16 || gelu)) return GPUSQ_ERR_UNSUPPORTED;
+  // the fused patch gather exists in the tile kernel and in the one for few rows, for 16 x 16 patches, fp16 output, no GELU
+  if (a.patch_P != 0 && ((choice != 2 && choice != 4) || a.patch_P != 16 || a.out_dt != GPUSQ_F16 || gelu)) return GPUSQ_ERR_UNSUPPORTED;
   // quantising fp16 activations on the way in exists in the small kernel only (X passes through its registers)
-  if (a.x_f16 && (!IS_I8 || choice >= 2)) return GPUSQ_ERR_UNSUPPORTED;
+  if (a.x_f16 && (!IS_I8 || choice == 2 || choice == 3)) return GPUSQ_ERR_UNSUPPORTED;
+  if (choice == 4) return fewrows_supports(a) ? launch_fewrows(IS_I8, a, resident, s) : launch_small<IS_I8, 4, 1, 1, 4>(a, s);
   if (choice == 3) {
     if (!tile2_supports(IS_I8, false, a)) return GPUSQ_ERR_UNSUPPORTED;
     return launch_tile2(IS_I8, false, a, dec.plan, tile2_grid_of(dec.plan, 2 * resident), s);
@@ -967,6 +957,49 @@ static gpusq_status launch_typed(const GemmArgs& a, hipStream_t s) {
       spgemm_tile_kernel<false, 0, GPUSQ_F16><<<grid, 512, 0, s>>>(a, plan);
   }
   return check_launch();
+}
+
+// Quantise X and multiply.  Where the problem goes to the kernel for few rows, X is fp16 and its K is not too long, that
+// kernel quantises: with a given scale, or a range of X small enough for every workgroup to find for itself, in the one
+// launch, else behind the range pass.  Otherwise the quantiser's one or two launches and the GEMM's.
+// A range of 128 KB read by every workgroup costs what the range pass does: 75 KB (197 x 192) 5.8 against 6.7 us, 133 KB (64 x
+// 1040) 8.2 against 8.6, 151 KB (394 x 192) 8.4 against 7.1.
+constexpr int64_t kRangeHereBytes = 128 * 1024;
+
+// 1 + the launches in front of the GEMM's own; `folds`: the GEMM quantises
+static int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int resident, bool& folds) {
+  folds = dt == GPUSQ_F16 && decide(true, a.M, a.N, a.K, (a.epilogue & GPUSQ_EPI_GELU) != 0, resident, false).choice == 4 &&
+          fewrows_supports(a) && fewrows_folds_quantiser(a.M, a.N, a.K, resident);
+  if (!folds) return scale_is_input ? 2 : 3;
+  return scale_is_input || (int64_t)a.M * a.K * 2 <= kRangeHereBytes ? 1 : 2;
+}
+
+int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int cus) {
+  bool folds;
+  return linear_int8_launches(a, dt, scale_is_input, cus > 0 ? cus : num_cus(), folds);
+}
+
+gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, void* workspace, hipStream_t s) {
+  bool folds;
+  const int launches = linear_int8_launches(a, dt, scale_is_input, num_cus(), folds);
+  a.act_scale = scale;
+  if (folds) {
+    a.x_f16 = 1;
+    a.xq_out = Xq;
+    if (!scale_is_input) {
+      a.scale_out = scale;
+      a.range_mode = launches == 1 ? kRangeHere : kRangePartials;
+      if (launches == 2) {
+        a.npartial = launch_amax(a.X, dt, (int64_t)a.M * a.K, workspace, s);
+        a.partial = (const float*)workspace;
+      }
+    }
+    return launch_fewrows(true, a, num_cus(), s);
+  }
+  const gpusq_status st = launch_quantize(a.X, dt, Xq, scale, GPUSQ_PER_TENSOR, scale_is_input, a.M, a.K, workspace, s);
+  if (st != GPUSQ_OK) return st;
+  a.X = Xq;
+  return launch_typed<true>(a, s);
 }
 
 gpusq_status launch_spgemm(bool is_i8, const GemmArgs& a, hipStream_t s) {

@@ -21,12 +21,13 @@ struct AccT { typedef v4f type; };
 template <>
 struct AccT<true> { typedef v4i type; };
 
-template <bool IS_I8>
+// HALF (fp16 only): which half of the index word holds the positions (8 kept values x 2 bits; the instruction's ABID field).
+template <bool IS_I8, int HALF = 0>
 __device__ __forceinline__ typename AccT<IS_I8>::type smfmac(v4i a, v8i b, typename AccT<IS_I8>::type c, int idx) {
   if constexpr (IS_I8)
     return __builtin_amdgcn_smfmac_i32_16x16x128_i8(a, b, c, idx, 0, 0);
   else
-    return __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v16h, b), c, idx, 0, 0);
+    return __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v16h, b), c, idx, 0, HALF);
 }
 
 // The list of tiles of one launch.  The first `full_tiles` tiles have 64*full_tm rows (n fastest); the rows behind the
@@ -124,6 +125,31 @@ __device__ __forceinline__ void load_index_half(int (&ai)[kTileTN], int half, co
       ai[4 * half + 2 * j + 1] = (int)((unsigned)x[j] >> 16);
     }
   }
+}
+
+// Patch-embedding mode with P = 16 (GemmArgs::patch_P): the 16-byte chunk kc of row m = (b, py, px) of the X operand is, for
+// int8, the 16 pixels of row py*16 + kc % 16 of patch column px in channel kc / 16 (for fp16, with 2 chunks per patch row: row
+// (kc / 2) % 16, channel kc / 32, half kc % 2).  A K step of 8 chunks stays inside one channel, so an address splits into a
+// part that does not depend on the step (chunk `ch` of a step for row m, in bytes from the first image) and a
+// wavefront-uniform part per step (patch_step_offset).
+// (32-bit unsigned arithmetic: M < 2^31, and 64-bit divisions cost the tile kernel's K loop, into which the tile change is
+// inlined, scores of registers)
+template <bool IS_I8>
+__device__ __forceinline__ uint32_t patch_chunk_offset(const GemmArgs& a, uint32_t m, int ch) {
+  constexpr int ES = IS_I8 ? 1 : 2;
+  const uint32_t px_n = (uint32_t)a.patch_W / 16u, py_n = (uint32_t)a.patch_H / 16u;
+  const uint32_t prow = m / px_n, px = m - prow * px_n;
+  const uint32_t b = prow / py_n, py = prow - b * py_n;
+  const int64_t pixel = (((int64_t)b * a.patch_C) * a.patch_H + py * 16) * a.patch_W + px * 16;  // first pixel of the patch, channel 0
+  const int row_in_step = IS_I8 ? ch : (ch >> 1), half = IS_I8 ? 0 : (ch & 1);
+  return (uint32_t)((pixel + (int64_t)row_in_step * a.patch_W) * ES + half * 16);
+}
+// Byte offset (wavefront-uniform) that K step ks adds: channel ks / S, first patch row (ks % S) * (16 / S), where a channel
+// takes S = 2 (int8) or 4 (fp16) steps.
+template <bool IS_I8>
+__device__ __forceinline__ int64_t patch_step_offset(const GemmArgs& a, int ks) {
+  constexpr int ES = IS_I8 ? 1 : 2, S = IS_I8 ? 2 : 4;
+  return ((int64_t)(ks / S) * a.patch_H * a.patch_W + (int64_t)(ks % S) * (16 / S) * a.patch_W) * ES;
 }
 
 // Epilogue of one wavefront of the tile kernel for every output type and any N % 4 == 0: 128 channels x 16*tm_active rows

@@ -26,7 +26,7 @@ EXPORTS = [
     "gpusq_spgemm_int8", "gpusq_spgemm_int8_xf16", "gpusq_spgemm_plan", "gpusq_im2col_patches", "gpusq_patch_embed16_int8", "gpusq_patch_embed16_fp16", "gpusq_gemm_fp16_dense", "gpusq_gemm_int8_dense",
     "gpusq_prune_4to8_pairs", "gpusq_quantize_rows_int4", "gpusq_compress_int4", "gpusq_decompress_int4",
     "gpusq_int4_to_sparse_int8", "gpusq_prune_n_of_m", "gpusq_force_kernel",
-    "gpusq_quantize_tensor_int8_noalloc",
+    "gpusq_quantize_tensor_int8_noalloc", "gpusq_linear_int8", "gpusq_linear_int8_launches",
 ]
 
 
@@ -74,6 +74,10 @@ def lib():
         L.gpusq_spgemm_int8.argtypes = [vp, vp, vp, vp, vp, vp, ci, vp, i64, i64, i64, ci, vp]
         L.gpusq_spgemm_int8_xf16.argtypes = [vp, vp, vp, vp, vp, vp, ci, vp, i64, i64, i64, ci, vp]
         L.gpusq_spgemm_int8_xf16.restype = ci
+        L.gpusq_linear_int8.argtypes = [vp, ci, vp, vp, ci, vp, vp, vp, ci, vp, vp, vp, i64, i64, i64, ci, vp]
+        L.gpusq_linear_int8.restype = ci
+        L.gpusq_linear_int8_launches.argtypes = [ci, i64, i64, i64, ci, ci, ci]
+        L.gpusq_linear_int8_launches.restype = ci
         L.gpusq_gemm_fp16_dense.argtypes = [vp, vp, vp, vp, i64, i64, i64, ci, vp]
         L.gpusq_gemm_int8_dense.argtypes = [vp, vp, vp, vp, vp, vp, ci, vp, i64, i64, i64, ci, vp]
         L.gpusq_im2col_patches.argtypes = [vp, vp, ci, i64, i64, i64, i64, i64, i64, vp]

@@ -85,12 +85,9 @@ class SparseLinear:
         return self.Y
 
     def takes_fp16_input(self):
-        """True when the INT8 GEMM of this layer should quantise fp16 activations itself (static scale): the problem
-        goes to the latency kernel, the only one that can, K is short and the rows are few (one round of workgroups).  Every workgroup quantises the X rows of its
-        own tile, K step by K step, which costs it about 0.5 us per step; the launch this saves is worth 2.5-3 us
-        (measured per block at batch 1: K = 192 29 -> 25 us, K = 384 30 -> 29 us, K = 768 34 -> 43 us)."""
-        return (self.precision == "int8" and self.K <= 384 and self.M <= 256 and
-                G.spgemm_plan(torch.int8, self.M, self.N, self.K, self.epilogue)["kernel"] < 2)
+        """True when the INT8 GEMM of this layer should quantise fp16 activations itself (static scale): few rows and a K that
+        is not too long, as the library's one-call layer decides it (one launch instead of two)."""
+        return self.precision == "int8" and G.lib().gpusq_linear_int8_launches(G.F16, self.M, self.N, self.K, self.epilogue, 1, 0) == 1
 
     def gemm_from_f16(self, X, bias, out_scale=None):
         """INT8 path with a static act_scale: quantise + GEMM in one launch (see takes_fp16_input)"""
@@ -113,8 +110,11 @@ class SparseLinear:
         return self.Y
 
     def forward(self, X, bias, out_scale=None):
-        if self.precision == "int8":
-            self.quantize_activations(X)
+        if self.precision == "int8":  # quantise and multiply in one call: one to three launches
+            G._check(G.lib().gpusq_linear_int8(_p(X), G._TORCH_DT[X.dtype], _p(self.packed), _p(self.act_scale), 0, _p(self.w_scale), _p(bias),
+                                               _p(self.Y), G._TORCH_DT[self.out_dtype], _p(out_scale), _p(self.Xq), _p(self.workspace),
+                                               self.M, self.N, self.K, self.epilogue, G._stream()), "gpusq_linear_int8")
+            return self.Y
         return self.gemm(X, bias, out_scale)
 
     def full_path(self, W, X, bias, out_scale=None):
