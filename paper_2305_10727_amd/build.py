@@ -2,11 +2,14 @@
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgpusq.so")
 SOURCES = ["api.hip", "prep.hip", "int4.hip", "spgemm.hip", "fewrows.hip", "tile2.hip", "dense.hip"]
+# Python's side of the binding: a host-only extension module beside the library (no GPU code, so the host compiler)
+FASTCALL = os.path.join(HERE, "_fastcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off",
     # packed-fp32 instructions are kept out of the generated code on the test machines
@@ -28,8 +31,8 @@ def _run(cmd, verbose):
 
 
 def build(verbose=False):
-    """Compile every HIP source (one hipcc process each, side by side) and link paper_2305_10727_amd/libgpusq.so;
-    always recompiles; raises on failure.  The objects live in a temporary directory, not in the tree."""
+    """Compile every HIP source (one hipcc process each, side by side) and link paper_2305_10727_amd/libgpusq.so, and the
+    extension module that calls it; always recompiles; raises on failure.  The objects live in a temporary directory, not in the tree."""
     import concurrent.futures
     import tempfile
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -37,6 +40,8 @@ def build(verbose=False):
     with tempfile.TemporaryDirectory(prefix="gpusq_build_") as tmp:
         objs = [os.path.join(tmp, s.replace(".hip", ".o")) for s in SOURCES]
         cmds = [[hipcc, *compile_flags, "-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objs)]
+        cmds.append(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
+                     os.path.join(CSRC, "fastcall.cpp"), "-o", FASTCALL])
         with concurrent.futures.ThreadPoolExecutor(max_workers=min(len(cmds), os.cpu_count() or 1)) as pool:
             for f in [pool.submit(_run, c, verbose) for c in cmds]:
                 f.result()

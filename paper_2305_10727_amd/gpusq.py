@@ -1,5 +1,7 @@
-"""Thin ctypes binding over libgpusq.so (include/gpusq.h).  Argument marshalling only: every step of the path runs
-in the library's HIP kernels.  PyTorch supplies device memory (`torch.empty`) and the current HIP stream.
+"""Thin binding over libgpusq.so (include/gpusq.h).  Argument marshalling only: every step of the path runs in the library's
+HIP kernels.  PyTorch supplies device memory (`torch.empty`) and the current HIP stream.  The calls that launch kernels go
+through the extension module _fastcall (csrc/fastcall.cpp), which converts arguments at a fraction of ctypes' cost; `lib()`
+is the ctypes handle on the same library for everything else.
 
 There is no fallback: if the library has not been built, or no GPU tensor is passed, the calls raise.
 """
@@ -38,6 +40,57 @@ class GpusqError(RuntimeError):
             msg += " [hip error %d]" % lib().gpusq_last_hip_error()
         super().__init__("%s: %s" % (where, msg))
 
+
+# C parameters of the calls that launch kernels (fastcall.cpp: p pointer, t checked tensor, i integer, s the stream)
+_SIGNATURES = {
+    "gpusq_prune_2to4": "tttiiis", "gpusq_cast_f16": "ttis", "gpusq_quantize_int8": "tittiiiits",
+    "gpusq_quantize_tensor_int8_noalloc": "tittiiis", "gpusq_compress": "ttttiiis", "gpusq_check_2to4": "titiis",
+    "gpusq_decompress": "tttiiis", "gpusq_pack": "tttiiis", "gpusq_prepare_weights": "tittttttiis",
+    "gpusq_spgemm_fp16": "ttttiiiis", "gpusq_spgemm_int8": "ttttttitiiiis", "gpusq_spgemm_int8_xf16": "ttttttitiiiis",
+    "gpusq_linear_int8": "tittitttitttiiiis",
+    "gpusq_im2col_patches": "ttiiiiiiis", "gpusq_patch_embed16_int8": "ttttttiiiiiis", "gpusq_patch_embed16_fp16": "ttttiiiiiis",
+    "gpusq_gemm_fp16_dense": "ttttiiiis", "gpusq_gemm_int8_dense": "ttttttitiiiis", "gpusq_prune_4to8_pairs": "tttiiis",
+    "gpusq_quantize_rows_int4": "tittiiis", "gpusq_compress_int4": "ttttiis", "gpusq_decompress_int4": "tttiis",
+    "gpusq_int4_to_sparse_int8": "tttttiis", "gpusq_prune_n_of_m": "ttiiiis",
+}
+
+
+class _Calls:
+    """The library's launching calls as attributes, built on first use: calls.gpusq_pack(values, meta, packed, dt, N, K) takes
+    tensors (or None), checks them (device, contiguity) and raises GpusqError for a status other than OK.  check=False: for
+    callers that own the tensors they pass."""
+
+    def __init__(self, check):
+        self._check = check
+
+    def __getattr__(self, name):
+        if name not in _SIGNATURES:
+            raise AttributeError(name)
+        L = lib()
+        from . import _fastcall
+        _fastcall.setup(torch._C._cuda_getDevice, _stream_of, _raise)
+        for n, sig in _SIGNATURES.items():
+            assert len(sig) == len(getattr(L, n).argtypes), n
+            address = ctypes.cast(getattr(L, n), ctypes.c_void_p).value
+            setattr(self, n, _fastcall.FastCall(n, address, sig if self._check else sig.replace("t", "p"), n == "gpusq_check_2to4"))
+        return self.__dict__[name]
+
+
+calls, calls_unchecked = _Calls(True), _Calls(False)
+
+
+def _raise(status, where):
+    raise GpusqError(status, where)
+
+
+def _stream_of(device):
+    return torch.cuda.current_stream(device).cuda_stream
+
+
+# torch's current stream as a raw hipStream_t.  The public route (torch.cuda.current_stream().cuda_stream) builds a Stream
+# object per call and takes about 2.7 us, as long as the launch itself; torch's own raw accessor takes a tenth of that.  It is
+# looked up once; without it the public route is used.
+_stream_of = getattr(torch._C, "_cuda_getCurrentRawStream", _stream_of)
 
 _lib = None
 
@@ -109,16 +162,8 @@ def _ptr(t):
     return ctypes.c_void_p(t.data_ptr())
 
 
-# torch's current stream as a raw hipStream_t.  The public route (torch.cuda.current_stream().cuda_stream) builds a Stream
-# object per call and takes about 2.7 us, a third of the host time of a launch through this binding; torch's own raw
-# accessor takes a tenth of that.  It is looked up once; without it the public route is used.
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-
-
 def _stream():
-    if _raw_stream is not None:
-        return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_stream_of(torch.cuda.current_device()))
 
 
 def _check(status, where):
@@ -139,14 +184,14 @@ def prune_2to4(W, out=None, want_mask=False):
     N, K = W.shape
     out = torch.empty_like(W) if out is None else out
     mask = torch.empty((N, max(K // 4, 1)), dtype=torch.uint8, device=W.device) if want_mask else None
-    _check(lib().gpusq_prune_2to4(_ptr(W), _ptr(out), _ptr(mask), _TORCH_DT[W.dtype], N, K, _stream()), "gpusq_prune_2to4")
+    calls.gpusq_prune_2to4(W, out, mask, _TORCH_DT[W.dtype], N, K)
     return (out, mask) if want_mask else out
 
 
 def cast_f16(X, out=None):
     """gpusq_cast_f16: fp32 tensor -> fp16 tensor of the same shape (round-to-nearest-even)."""
     out = torch.empty(X.shape, dtype=torch.float16, device=X.device) if out is None else out
-    _check(lib().gpusq_cast_f16(_ptr(X), _ptr(out), X.numel(), _stream()), "gpusq_cast_f16")
+    calls.gpusq_cast_f16(X, out, X.numel())
     return out
 
 
@@ -160,8 +205,7 @@ def quantize_int8(X, mode, scale=None):
         scale = torch.empty(rows if mode == PER_ROW else 1, dtype=torch.float32, device=X.device)
     ws_bytes = lib().gpusq_quantize_workspace_bytes(mode, rows, cols)
     ws = torch.empty(max(ws_bytes, 16), dtype=torch.uint8, device=X.device)
-    _check(lib().gpusq_quantize_int8(_ptr(X), _TORCH_DT[X.dtype], _ptr(Xq), _ptr(scale), mode, int(given), rows, cols,
-                                     _ptr(ws), _stream()), "gpusq_quantize_int8")
+    calls.gpusq_quantize_int8(X, _TORCH_DT[X.dtype], Xq, scale, mode, int(given), rows, cols, ws)
     return Xq, scale
 
 
@@ -169,8 +213,7 @@ def quantize_tensor_int8_noalloc(X, Xq, scale, scale_is_input=False):
     """gpusq_quantize_tensor_int8_noalloc: per-tensor codes into the caller's Xq [rows, cols] int8 and scale [1] fp32;
     nothing is allocated, here or in the library."""
     rows, cols = X.shape
-    _check(lib().gpusq_quantize_tensor_int8_noalloc(_ptr(X), _TORCH_DT[X.dtype], _ptr(Xq), _ptr(scale), int(bool(scale_is_input)),
-                                                    rows, cols, _stream()), "gpusq_quantize_tensor_int8_noalloc")
+    calls.gpusq_quantize_tensor_int8_noalloc(X, _TORCH_DT[X.dtype], Xq, scale, int(bool(scale_is_input)), rows, cols)
     return Xq, scale
 
 
@@ -180,8 +223,7 @@ def compress(W, want_violations=False):
     values = torch.empty((N, max(K // 2, 1)), dtype=W.dtype, device=W.device)
     meta = torch.empty((N, max(meta_row_bytes(K), 1)), dtype=torch.uint8, device=W.device)
     viol = torch.empty(1, dtype=torch.int32, device=W.device) if want_violations else None
-    _check(lib().gpusq_compress(_ptr(W), _ptr(values), _ptr(meta), _ptr(viol), _TORCH_DT[W.dtype], N, K, _stream()),
-           "gpusq_compress")
+    calls.gpusq_compress(W, values, meta, viol, _TORCH_DT[W.dtype], N, K)
     return (values, meta, viol) if want_violations else (values, meta)
 
 
@@ -192,7 +234,7 @@ def check_2to4(W):
     """gpusq_check_2to4: W [N,K] fp32/fp16/int8 -> (is_2to4, groups with more than two non-zeros); waits for the stream"""
     N, K = W.shape
     viol = torch.empty(1, dtype=torch.int32, device=W.device)
-    st = lib().gpusq_check_2to4(_ptr(W), _TORCH_DT[W.dtype], _ptr(viol), N, K, _stream())
+    st = calls.gpusq_check_2to4(W, _TORCH_DT[W.dtype], viol, N, K)
     if st not in (0, ERR_NOT_2TO4):
         _check(st, "gpusq_check_2to4")
     return st == 0, int(viol.item())
@@ -201,8 +243,7 @@ def check_2to4(W):
 def decompress(values, meta, K):
     N = values.shape[0]
     W = torch.empty((N, K), dtype=values.dtype, device=values.device)
-    _check(lib().gpusq_decompress(_ptr(values), _ptr(meta), _ptr(W), _TORCH_DT[values.dtype], N, K, _stream()),
-           "gpusq_decompress")
+    calls.gpusq_decompress(values, meta, W, _TORCH_DT[values.dtype], N, K)
     return W
 
 
@@ -210,7 +251,7 @@ def prune_n_of_m(W, n, m):
     """gpusq_prune_n_of_m: W [N,K] fp32 -> copy with the n largest magnitudes of every m contiguous elements kept"""
     N, K = W.shape
     out = torch.empty_like(W)
-    _check(lib().gpusq_prune_n_of_m(_ptr(W), _ptr(out), n, m, N, K, _stream()), "gpusq_prune_n_of_m")
+    calls.gpusq_prune_n_of_m(W, out, n, m, N, K)
     return out
 
 
@@ -219,8 +260,7 @@ def prune_4to8_pairs(W, want_mask=False, one_per_group=False):
     N, K = W.shape
     out = torch.empty_like(W)
     mask = torch.empty((N, K // 8), dtype=torch.uint8, device=W.device) if want_mask else None
-    _check(lib().gpusq_prune_4to8_pairs(_ptr(W), _ptr(out), _ptr(mask), int(one_per_group), N, K, _stream()),
-           "gpusq_prune_4to8_pairs")
+    calls.gpusq_prune_4to8_pairs(W, out, mask, int(one_per_group), N, K)
     return (out, mask) if want_mask else out
 
 
@@ -230,8 +270,7 @@ def int4_to_sparse_int8(values4, meta4, K, want_mismatches=False):
     values8 = torch.empty((N, K // 2), dtype=torch.int8, device=values4.device)
     meta8 = torch.empty((N, K // 8), dtype=torch.uint8, device=values4.device)
     bad = torch.empty(1, dtype=torch.int32, device=values4.device) if want_mismatches else None
-    _check(lib().gpusq_int4_to_sparse_int8(_ptr(values4), _ptr(meta4), _ptr(values8), _ptr(meta8), _ptr(bad), N, K, _stream()),
-           "gpusq_int4_to_sparse_int8")
+    calls.gpusq_int4_to_sparse_int8(values4, meta4, values8, meta8, bad, N, K)
     return (values8, meta8, bad) if want_mismatches else (values8, meta8)
 
 
@@ -242,8 +281,7 @@ def quantize_rows_int4(X, scale=None):
     given = scale is not None
     if not given:
         scale = torch.empty(rows, dtype=torch.float32, device=X.device)
-    _check(lib().gpusq_quantize_rows_int4(_ptr(X), _TORCH_DT[X.dtype], _ptr(Xq), _ptr(scale), int(given), rows, cols, _stream()),
-           "gpusq_quantize_rows_int4")
+    calls.gpusq_quantize_rows_int4(X, _TORCH_DT[X.dtype], Xq, scale, int(given), rows, cols)
     return Xq, scale
 
 
@@ -253,14 +291,14 @@ def compress_int4(Wq, want_violations=False):
     values = torch.empty((N, K // 4), dtype=torch.uint8, device=Wq.device)
     meta = torch.empty((N, (K // 8 + 1) // 2), dtype=torch.uint8, device=Wq.device)
     viol = torch.empty(1, dtype=torch.int32, device=Wq.device) if want_violations else None
-    _check(lib().gpusq_compress_int4(_ptr(Wq), _ptr(values), _ptr(meta), _ptr(viol), N, K, _stream()), "gpusq_compress_int4")
+    calls.gpusq_compress_int4(Wq, values, meta, viol, N, K)
     return (values, meta, viol) if want_violations else (values, meta)
 
 
 def decompress_int4(values, meta, K):
     N = values.shape[0]
     W = torch.empty((N, K), dtype=torch.int8, device=values.device)
-    _check(lib().gpusq_decompress_int4(_ptr(values), _ptr(meta), _ptr(W), N, K, _stream()), "gpusq_decompress_int4")
+    calls.gpusq_decompress_int4(values, meta, W, N, K)
     return W
 
 
@@ -270,7 +308,7 @@ def im2col_patches(img, P, K_pad=None):
     K = C * P * P
     K_pad = K if K_pad is None else K_pad
     X = torch.empty((B * (H // P) * (W // P), K_pad), dtype=img.dtype, device=img.device)
-    _check(lib().gpusq_im2col_patches(_ptr(img), _ptr(X), _TORCH_DT[img.dtype], B, C, H, W, P, K_pad, _stream()), "gpusq_im2col_patches")
+    calls.gpusq_im2col_patches(img, X, _TORCH_DT[img.dtype], B, C, H, W, P, K_pad)
     return X
 
 
@@ -280,11 +318,9 @@ def patch_embed16(img, packed, D, act_scale=None, w_scale=None, bias=None):
     Y = torch.empty((B * (H // 16) * (W // 16), D), dtype=torch.float16, device=img.device)
     epi = EPI_BIAS if bias is not None else 0
     if img.dtype == torch.int8:
-        st = lib().gpusq_patch_embed16_int8(_ptr(img), _ptr(packed), _ptr(act_scale), _ptr(w_scale), _ptr(bias), _ptr(Y), B, C, H, W, D,
-                                            epi, _stream())
+        calls.gpusq_patch_embed16_int8(img, packed, act_scale, w_scale, bias, Y, B, C, H, W, D, epi)
     else:
-        st = lib().gpusq_patch_embed16_fp16(_ptr(img), _ptr(packed), _ptr(bias), _ptr(Y), B, C, H, W, D, epi, _stream())
-    _check(st, "gpusq_patch_embed16")
+        calls.gpusq_patch_embed16_fp16(img, packed, bias, Y, B, C, H, W, D, epi)
     return Y
 
 
@@ -313,7 +349,7 @@ def pack(values, meta, K):
     if nbytes == 0:
         raise GpusqError(ERR_SHAPE, "gpusq_packed_bytes")
     packed = torch.empty(nbytes, dtype=torch.uint8, device=values.device)
-    _check(lib().gpusq_pack(_ptr(values), _ptr(meta), _ptr(packed), _TORCH_DT[values.dtype], N, K, _stream()), "gpusq_pack")
+    calls.gpusq_pack(values, meta, packed, _TORCH_DT[values.dtype], N, K)
     return packed
 
 
@@ -330,8 +366,7 @@ def prepare_weights(W, dtype, want_intermediates=False):
         Wl = torch.empty((N, K), dtype=dtype, device=W.device)
         values = torch.empty((N, K // 2), dtype=dtype, device=W.device)
         meta = torch.empty((N, meta_row_bytes(K)), dtype=torch.uint8, device=W.device)
-    _check(lib().gpusq_prepare_weights(_ptr(W), dt, _ptr(Wp), _ptr(Wl), _ptr(w_scale), _ptr(values), _ptr(meta), _ptr(packed),
-                                       N, K, _stream()), "gpusq_prepare_weights")
+    calls.gpusq_prepare_weights(W, dt, Wp, Wl, w_scale, values, meta, packed, N, K)
     out = dict(packed=packed, w_scale=w_scale)
     if want_intermediates:
         out.update(W_pruned=Wp, W_low=Wl, values=values, meta=meta)
@@ -345,8 +380,7 @@ def _epi(bias, gelu):
 def spgemm_fp16(X, Wpacked, N, bias=None, gelu=False, out=None):
     M, K = X.shape
     Y = torch.empty((M, N), dtype=torch.float16, device=X.device) if out is None else out
-    _check(lib().gpusq_spgemm_fp16(_ptr(X), _ptr(Wpacked), _ptr(bias), _ptr(Y), M, N, K, _epi(bias, gelu), _stream()),
-           "gpusq_spgemm_fp16")
+    calls.gpusq_spgemm_fp16(X, Wpacked, bias, Y, M, N, K, _epi(bias, gelu))
     return Y
 
 
@@ -354,9 +388,7 @@ def spgemm_int8(Xq, Wpacked, N, act_scale=None, w_scale=None, bias=None, gelu=Fa
                 out_scale=None, out=None):
     M, K = Xq.shape
     Y = torch.empty((M, N), dtype=out_dtype, device=Xq.device) if out is None else out
-    _check(lib().gpusq_spgemm_int8(_ptr(Xq), _ptr(Wpacked), _ptr(act_scale), _ptr(w_scale), _ptr(bias), _ptr(Y),
-                                   _TORCH_DT[out_dtype], _ptr(out_scale), M, N, K, _epi(bias, gelu), _stream()),
-           "gpusq_spgemm_int8")
+    calls.gpusq_spgemm_int8(Xq, Wpacked, act_scale, w_scale, bias, Y, _TORCH_DT[out_dtype], out_scale, M, N, K, _epi(bias, gelu))
     return Y
 
 
@@ -366,9 +398,7 @@ def spgemm_int8_xf16(X, Wpacked, N, act_scale, w_scale, bias=None, gelu=False, o
     ERR_UNSUPPORTED for problems that spgemm_plan assigns to the tile kernel)"""
     M, K = X.shape
     Y = torch.empty((M, N), dtype=out_dtype, device=X.device) if out is None else out
-    _check(lib().gpusq_spgemm_int8_xf16(_ptr(X), _ptr(Wpacked), _ptr(act_scale), _ptr(w_scale), _ptr(bias), _ptr(Y),
-                                        _TORCH_DT[out_dtype], _ptr(out_scale), M, N, K, _epi(bias, gelu), _stream()),
-           "gpusq_spgemm_int8_xf16")
+    calls.gpusq_spgemm_int8_xf16(X, Wpacked, act_scale, w_scale, bias, Y, _TORCH_DT[out_dtype], out_scale, M, N, K, _epi(bias, gelu))
     return Y
 
 
@@ -376,8 +406,7 @@ def gemm_fp16_dense(X, W, bias=None, gelu=False, out=None):
     M, K = X.shape
     N = W.shape[0]
     Y = torch.empty((M, N), dtype=torch.float16, device=X.device) if out is None else out
-    _check(lib().gpusq_gemm_fp16_dense(_ptr(X), _ptr(W), _ptr(bias), _ptr(Y), M, N, K, _epi(bias, gelu), _stream()),
-           "gpusq_gemm_fp16_dense")
+    calls.gpusq_gemm_fp16_dense(X, W, bias, Y, M, N, K, _epi(bias, gelu))
     return Y
 
 
@@ -386,7 +415,5 @@ def gemm_int8_dense(Xq, Wq, act_scale=None, w_scale=None, bias=None, gelu=False,
     M, K = Xq.shape
     N = Wq.shape[0]
     Y = torch.empty((M, N), dtype=out_dtype, device=Xq.device) if out is None else out
-    _check(lib().gpusq_gemm_int8_dense(_ptr(Xq), _ptr(Wq), _ptr(act_scale), _ptr(w_scale), _ptr(bias), _ptr(Y),
-                                       _TORCH_DT[out_dtype], _ptr(out_scale), M, N, K, _epi(bias, gelu), _stream()),
-           "gpusq_gemm_int8_dense")
+    calls.gpusq_gemm_int8_dense(Xq, Wq, act_scale, w_scale, bias, Y, _TORCH_DT[out_dtype], out_scale, M, N, K, _epi(bias, gelu))
     return Y

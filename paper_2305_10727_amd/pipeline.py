@@ -1,12 +1,14 @@
 """One linear layer's full path with preallocated device buffers: prune -> quantise -> compress -> pack (weight
-side), quantise activations, sparse GEMM with fused epilogue.  Every step is one call into libgpusq through ctypes;
-this class only owns the buffers and passes pointers (PyTorch = device memory + current stream).
+side), quantise activations, sparse GEMM with fused epilogue.  Every step is one call into libgpusq; this class only owns
+the buffers and passes pointers (PyTorch = device memory + current stream).
 """
 import ctypes
 
 import torch
 
 from . import gpusq as G
+
+_call = G.calls_unchecked
 
 
 def _p(t):
@@ -46,42 +48,36 @@ class SparseLinear:
         """fused=True: one launch (gpusq_prepare_weights); fused=False: the four separate calls.
         intermediates=False (fused only): the pruned fp32 weights, the masked low-precision weights, the canonical values
         and metadata stay in the kernel's registers; only what the sparse GEMM reads (packed operand, scales) is written."""
-        L, s = G.lib(), G._stream()
         N, K = self.N, self.K
         if fused and K * 4 <= 64 * 1024:
-            keep = (lambda t: _p(t)) if intermediates else (lambda t: None)
-            G._check(L.gpusq_prepare_weights(_p(W), G.I8 if self.precision == "int8" else G.F16, keep(self.W_pruned),
-                                             keep(self.W_low), _p(self.w_scale) if self.precision == "int8" else None,
-                                             keep(self.values), keep(self.meta), _p(self.packed), N, K, s), "gpusq_prepare_weights")
+            keep = (lambda t: t) if intermediates else (lambda t: None)
+            _call.gpusq_prepare_weights(W, G.I8 if self.precision == "int8" else G.F16, keep(self.W_pruned), keep(self.W_low),
+                                        self.w_scale if self.precision == "int8" else None, keep(self.values), keep(self.meta),
+                                        self.packed, N, K)
             return
-        G._check(L.gpusq_prune_2to4(_p(W), _p(self.W_pruned), None, G.F32, N, K, s), "gpusq_prune_2to4")
+        _call.gpusq_prune_2to4(W, self.W_pruned, None, G.F32, N, K)
         if self.precision == "int8":
-            G._check(L.gpusq_quantize_int8(_p(self.W_pruned), G.F32, _p(self.W_low), _p(self.w_scale), G.PER_ROW, 0, N, K,
-                                           None, s), "gpusq_quantize_int8")
+            _call.gpusq_quantize_int8(self.W_pruned, G.F32, self.W_low, self.w_scale, G.PER_ROW, 0, N, K, None)
             dt = G.I8
         else:
-            G._check(L.gpusq_cast_f16(_p(self.W_pruned), _p(self.W_low), N * K, s), "gpusq_cast_f16")
+            _call.gpusq_cast_f16(self.W_pruned, self.W_low, N * K)
             dt = G.F16
-        G._check(L.gpusq_compress(_p(self.W_low), _p(self.values), _p(self.meta), None, dt, N, K, s), "gpusq_compress")
-        G._check(L.gpusq_pack(_p(self.values), _p(self.meta), _p(self.packed), dt, N, K, s), "gpusq_pack")
+        _call.gpusq_compress(self.W_low, self.values, self.meta, None, dt, N, K)
+        _call.gpusq_pack(self.values, self.meta, self.packed, dt, N, K)
 
     # ---- activation side + GEMM (a4, a5, a6) --------------------------------------------------------------------
     def quantize_activations(self, X, static=False):
         """static=True: act_scale already holds a calibrated scale and is used as it is (one launch, no range pass)"""
-        G._check(G.lib().gpusq_quantize_int8(_p(X), G._TORCH_DT[X.dtype], _p(self.Xq), _p(self.act_scale), G.PER_TENSOR,
-                                             1 if static else 0, self.M, self.K, _p(self.workspace), G._stream()),
-                 "gpusq_quantize_int8")
+        _call.gpusq_quantize_int8(X, G._TORCH_DT[X.dtype], self.Xq, self.act_scale, G.PER_TENSOR, 1 if static else 0, self.M,
+                                  self.K, self.workspace)
 
     def gemm(self, X, bias, out_scale=None):
-        L, s = G.lib(), G._stream()
         M, N, K = self.M, self.N, self.K
         if self.precision == "int8":
-            G._check(L.gpusq_spgemm_int8(_p(self.Xq), _p(self.packed), _p(self.act_scale), _p(self.w_scale), _p(bias),
-                                         _p(self.Y), G._TORCH_DT[self.out_dtype], _p(out_scale), M, N, K, self.epilogue, s),
-                     "gpusq_spgemm_int8")
+            _call.gpusq_spgemm_int8(self.Xq, self.packed, self.act_scale, self.w_scale, bias, self.Y, G._TORCH_DT[self.out_dtype],
+                                    out_scale, M, N, K, self.epilogue)
         else:
-            G._check(L.gpusq_spgemm_fp16(_p(X), _p(self.packed), _p(bias), _p(self.Y), M, N, K, self.epilogue, s),
-                     "gpusq_spgemm_fp16")
+            _call.gpusq_spgemm_fp16(X, self.packed, bias, self.Y, M, N, K, self.epilogue)
         return self.Y
 
     def takes_fp16_input(self):
@@ -91,29 +87,25 @@ class SparseLinear:
 
     def gemm_from_f16(self, X, bias, out_scale=None):
         """INT8 path with a static act_scale: quantise + GEMM in one launch (see takes_fp16_input)"""
-        G._check(G.lib().gpusq_spgemm_int8_xf16(_p(X), _p(self.packed), _p(self.act_scale), _p(self.w_scale), _p(bias), _p(self.Y),
-                                                G._TORCH_DT[self.out_dtype], _p(out_scale), self.M, self.N, self.K, self.epilogue,
-                                                G._stream()), "gpusq_spgemm_int8_xf16")
+        _call.gpusq_spgemm_int8_xf16(X, self.packed, self.act_scale, self.w_scale, bias, self.Y, G._TORCH_DT[self.out_dtype],
+                                     out_scale, self.M, self.N, self.K, self.epilogue)
         return self.Y
 
     def gemm_dense(self, X, bias, out_scale=None):
         """the dense twin on the same masked weights"""
-        L, s = G.lib(), G._stream()
         M, N, K = self.M, self.N, self.K
         if self.precision == "int8":
-            G._check(L.gpusq_gemm_int8_dense(_p(self.Xq), _p(self.W_low), _p(self.act_scale), _p(self.w_scale), _p(bias),
-                                             _p(self.Y), G._TORCH_DT[self.out_dtype], _p(out_scale), M, N, K, self.epilogue,
-                                             s), "gpusq_gemm_int8_dense")
+            _call.gpusq_gemm_int8_dense(self.Xq, self.W_low, self.act_scale, self.w_scale, bias, self.Y,
+                                        G._TORCH_DT[self.out_dtype], out_scale, M, N, K, self.epilogue)
         else:
-            G._check(L.gpusq_gemm_fp16_dense(_p(X), _p(self.W_low), _p(bias), _p(self.Y), M, N, K, self.epilogue, s),
-                     "gpusq_gemm_fp16_dense")
+            _call.gpusq_gemm_fp16_dense(X, self.W_low, bias, self.Y, M, N, K, self.epilogue)
         return self.Y
 
     def forward(self, X, bias, out_scale=None):
         if self.precision == "int8":  # quantise and multiply in one call: one to three launches
-            G._check(G.lib().gpusq_linear_int8(_p(X), G._TORCH_DT[X.dtype], _p(self.packed), _p(self.act_scale), 0, _p(self.w_scale), _p(bias),
-                                               _p(self.Y), G._TORCH_DT[self.out_dtype], _p(out_scale), _p(self.Xq), _p(self.workspace),
-                                               self.M, self.N, self.K, self.epilogue, G._stream()), "gpusq_linear_int8")
+            _call.gpusq_linear_int8(X, G._TORCH_DT[X.dtype], self.packed, self.act_scale, 0, self.w_scale, bias, self.Y,
+                                    G._TORCH_DT[self.out_dtype], out_scale, self.Xq, self.workspace, self.M, self.N, self.K,
+                                    self.epilogue)
             return self.Y
         return self.gemm(X, bias, out_scale)
 
@@ -158,24 +150,21 @@ class SparsePatchEmbed:
 
     def forward(self, img, bias):
         """img [B,C,H,W] fp16 (or fp32 on the int8 path)"""
-        L, s = G.lib(), G._stream()
         B, C, H, W = self.shape
         if self.precision == "int8":
-            G._check(L.gpusq_quantize_int8(_p(img), G._TORCH_DT[img.dtype], _p(self.img_q), _p(self.linear.act_scale), G.PER_TENSOR, 0,
-                                           1, B * C * H * W, _p(self.workspace), s), "gpusq_quantize_int8")
+            _call.gpusq_quantize_int8(img, G._TORCH_DT[img.dtype], self.img_q, self.linear.act_scale, G.PER_TENSOR, 0, 1,
+                                      B * C * H * W, self.workspace)
             src, dt = self.img_q, G.I8
         else:
             src, dt = img, G.F16
         if self.fused:
             lin, epi = self.linear, self.linear.epilogue & G.EPI_BIAS
             if self.precision == "int8":
-                G._check(L.gpusq_patch_embed16_int8(_p(src), _p(lin.packed), _p(lin.act_scale), _p(lin.w_scale), _p(bias), _p(lin.Y),
-                                                    B, C, H, W, self.D, epi, s), "gpusq_patch_embed16_int8")
+                _call.gpusq_patch_embed16_int8(src, lin.packed, lin.act_scale, lin.w_scale, bias, lin.Y, B, C, H, W, self.D, epi)
             else:
-                G._check(L.gpusq_patch_embed16_fp16(_p(src), _p(lin.packed), _p(bias), _p(lin.Y), B, C, H, W, self.D, epi, s),
-                         "gpusq_patch_embed16_fp16")
+                _call.gpusq_patch_embed16_fp16(src, lin.packed, bias, lin.Y, B, C, H, W, self.D, epi)
             return lin.Y
-        G._check(L.gpusq_im2col_patches(_p(src), _p(self.X), dt, B, C, H, W, self.P, self.K_pad, s), "gpusq_im2col_patches")
+        _call.gpusq_im2col_patches(src, self.X, dt, B, C, H, W, self.P, self.K_pad)
         if self.precision == "int8":
             self.linear.Xq = self.X
         return self.linear.gemm(self.X, bias)
