@@ -173,7 +173,7 @@ gpusq_status gpusq_pack(const void* values, const uint8_t* meta, void* packed, g
  *   W [N][K] fp32 (input);  packed: gpusq_packed_bytes(dt, N, K) bytes (required);  w_scale [N] (required for I8).
  *   Optional outputs (NULL to skip): W_pruned [N][K] fp32, W_low [N][K] of dt (the masked low-precision weights, the
  *   dense twins' operand), values [N][K/2] of dt, meta [N][ceil(K/8)].
- *   K is limited to 16384 (GPUSQ_ERR_UNSUPPORTED beyond): one fp32 row is staged in LDS. */
+ *   K is limited to 16384 (GPUSQ_ERR_UNSUPPORTED beyond). */
 gpusq_status gpusq_prepare_weights(const float* W, gpusq_dtype dt, float* W_pruned, void* W_low, float* w_scale,
                                    void* values, uint8_t* meta, void* packed, int64_t N, int64_t K, void* stream);
 

@@ -134,6 +134,25 @@ __global__ void __launch_bounds__(256) decompress_int4_kernel(const uint8_t* __r
 // INT4 storage -> the INT8 2:4 compressed form (values [N][K/2], one metadata byte per chunk = two groups of 4), for rows
 // in which no group of 4 holds two non-zero sub-chunks (what pruning with one_per_group produces).  A group keeps its
 // non-zero sub-chunk (the first one if it has none); a group with two non-zero sub-chunks keeps the second and is counted.
+__device__ __forceinline__ void sparse_chunk(unsigned v, unsigned nib, unsigned& vals, unsigned& meta, int& bad) {
+  const unsigned p0 = nib & 3u, p1 = nib >> 2;
+  auto byte_of = [](unsigned nibble) { return (unsigned)((int)(nibble << 28) >> 28) & 0xFFu; };
+  const uint64_t first = byte_of(v & 0xFu) | (byte_of((v >> 4) & 0xFu) << 8);
+  const uint64_t second = byte_of((v >> 8) & 0xFu) | (byte_of((v >> 12) & 0xFu) << 8);
+  const uint64_t chunk = (first << (16 * p0)) | (second << (16 * p1));  // the 8 dense codes, one byte each
+  vals = 0;
+  meta = 0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const unsigned group = (unsigned)(chunk >> (32 * h));
+    const unsigned pair0 = group & 0xFFFFu, pair1 = group >> 16;
+    bad += (int)(pair0 != 0 && pair1 != 0);
+    const unsigned local = pair1 != 0 ? 1u : 0u;
+    vals |= (local ? pair1 : pair0) << (16 * h);
+    meta |= ((2 * local) | ((2 * local + 1) << 2)) << (4 * h);
+  }
+}
+
 __global__ void __launch_bounds__(256) int4_to_sparse_int8_kernel(const uint8_t* __restrict__ values4, const uint8_t* __restrict__ meta4,
                                                                   int8_t* __restrict__ values8, uint8_t* __restrict__ meta8,
                                                                   int32_t* __restrict__ mismatches, int64_t N, int64_t K) {
@@ -144,24 +163,32 @@ __global__ void __launch_bounds__(256) int4_to_sparse_int8_kernel(const uint8_t*
   if (id < N * chunks_per_row) {
     const int64_t n = id / chunks_per_row, c = id % chunks_per_row;
     const unsigned nib = (meta4[n * mrb4 + (c >> 1)] >> (4 * (c & 1))) & 0xFu;
-    const unsigned p0 = nib & 3u, p1 = nib >> 2;
-    const unsigned v = *(const uint16_t*)(values4 + n * (K / 4) + 2 * c);
-    auto byte_of = [](unsigned nibble) { return (unsigned)((int)(nibble << 28) >> 28) & 0xFFu; };
-    const uint64_t first = byte_of(v & 0xFu) | (byte_of((v >> 4) & 0xFu) << 8);
-    const uint64_t second = byte_of((v >> 8) & 0xFu) | (byte_of((v >> 12) & 0xFu) << 8);
-    const uint64_t chunk = (first << (16 * p0)) | (second << (16 * p1));  // the 8 dense codes, one byte each
-    unsigned vals = 0, meta = 0;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const unsigned group = (unsigned)(chunk >> (32 * h));
-      const unsigned pair0 = group & 0xFFFFu, pair1 = group >> 16;
-      bad += (int)(pair0 != 0 && pair1 != 0);
-      const unsigned local = pair1 != 0 ? 1u : 0u;
-      vals |= (local ? pair1 : pair0) << (16 * h);
-      meta |= ((2 * local) | ((2 * local + 1) << 2)) << (4 * h);
-    }
+    unsigned vals, meta;
+    sparse_chunk(*(const uint16_t*)(values4 + n * (K / 4) + 2 * c), nib, vals, meta, bad);
     *(uint32_t*)(values8 + n * (K / 2) + 4 * c) = vals;
     meta8[n * chunks_per_row + c] = (uint8_t)meta;
+  }
+  if (mismatches) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) bad += __shfl_xor(bad, o, 64);
+    if ((threadIdx.x & 63) == 0 && bad) atomicAdd(mismatches, bad);
+  }
+}
+
+// The same for a flat run of an even number of chunks (no row of indices ends inside a byte): two chunks per thread and no
+// division by the row length (5120 x 1280: 4.2 -> 3.4 us).
+__global__ void __launch_bounds__(256) int4_to_sparse_int8_flat_kernel(const uint32_t* __restrict__ values4, const uint8_t* __restrict__ meta4,
+                                                                       uint2* __restrict__ values8, uint16_t* __restrict__ meta8,
+                                                                       int32_t* __restrict__ mismatches, int64_t pairs) {
+  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int bad = 0;
+  if (id < pairs) {
+    const unsigned v = values4[id], ix = meta4[id];
+    unsigned o[2], m[2];
+    sparse_chunk(v & 0xFFFFu, ix & 0xFu, o[0], m[0], bad);
+    sparse_chunk(v >> 16, ix >> 4, o[1], m[1], bad);
+    values8[id] = uint2{o[0], o[1]};
+    meta8[id] = (uint16_t)(m[0] | (m[1] << 8));
   }
   if (mismatches) {
 #pragma unroll
@@ -173,7 +200,11 @@ __global__ void __launch_bounds__(256) int4_to_sparse_int8_kernel(const uint8_t*
 gpusq_status launch_int4_to_sparse_int8(const uint8_t* values4, const uint8_t* meta4, int8_t* values8, uint8_t* meta8,
                                         int32_t* mismatches, int64_t N, int64_t K, hipStream_t s) {
   if (mismatches) clear_i32_kernel<<<1, 1, 0, s>>>(mismatches);
-  int4_to_sparse_int8_kernel<<<(unsigned)ceil_div(N * (K / 8), 256), 256, 0, s>>>(values4, meta4, values8, meta8, mismatches, N, K);
+  if (K % 16 == 0)
+    int4_to_sparse_int8_flat_kernel<<<(unsigned)ceil_div(N * (K / 16), 256), 256, 0, s>>>((const uint32_t*)values4, meta4, (uint2*)values8,
+                                                                                        (uint16_t*)meta8, mismatches, N * (K / 16));
+  else
+    int4_to_sparse_int8_kernel<<<(unsigned)ceil_div(N * (K / 8), 256), 256, 0, s>>>(values4, meta4, values8, meta8, mismatches, N, K);
   return check_launch();
 }
 

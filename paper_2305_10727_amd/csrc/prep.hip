@@ -229,15 +229,75 @@ __device__ __forceinline__ float wave_max(float v) {
 }
 
 // One wavefront per row (= per output channel), 4 rows per workgroup.
-template <typename T>
+// Rows of whole 16-byte vectors (VEC elements): a batch of kRowBatch vectors per lane is requested before the first is used,
+// and a row of one batch stays in registers between the range and the codes; a longer one is read again.
+// A load per loop turn, and two turns over the row, took a trip to memory each: 5120 x 1280 fp32 12.6 us, 9.1 so.
+// kRowBatch: 8, or 20 for the rows that then stay in registers (up to 5120 fp32 elements).
+template <typename T, int kRowBatch>
 __global__ void __launch_bounds__(256) quantize_rows_kernel(const T* __restrict__ X, int8_t* __restrict__ Q,
                                                             float* __restrict__ scale, int scale_is_input,
                                                             int64_t rows, int64_t cols, float qmax) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  typedef T vec_t __attribute__((ext_vector_type(VEC)));
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
   const T* x = X + row * cols;
+  int8_t* q = Q + row * cols;
   float s;
+  if (cols % VEC == 0) {
+    const int64_t vecs = cols / VEC;
+    vec_t v[kRowBatch];
+    auto load = [&](int64_t base) {
+#pragma unroll
+      for (int j = 0; j < kRowBatch; ++j) {
+        const int64_t i = base + j * 64 + lane;
+        v[j] = i < vecs ? *(const vec_t*)(x + i * VEC) : vec_t(0);
+      }
+    };
+    load(0);
+    if (scale_is_input) {
+      s = scale[row];
+    } else {
+      float amax = 0.0f;
+      for (int64_t base = 0;;) {
+#pragma unroll
+        for (int j = 0; j < kRowBatch; ++j)
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) amax = fmaxf(amax, fabsf((float)v[j][e]));
+        base += kRowBatch * 64;
+        if (base >= vecs) break;
+        load(base);
+      }
+      amax = wave_max(amax);
+      s = (amax == 0.0f) ? 1.0f : __fdiv_rn(amax, qmax);
+      if (lane == 0) scale[row] = s;
+      if (vecs > kRowBatch * 64) load(0);
+    }
+    const float rs = scale_reciprocal(s);
+    for (int64_t base = 0;;) {
+#pragma unroll
+      for (int j = 0; j < kRowBatch; ++j) {
+        const int64_t i = base + j * 64 + lane;
+        if (base + j * 64 >= vecs) break;  // wavefront-uniform
+        float xs[VEC];
+        int qc[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) xs[e] = (float)v[j][e];
+        quantize_codes<VEC>(xs, s, rs, qc, qmax);
+        if (i < vecs) {
+#pragma unroll
+          for (int e = 0; e < VEC; e += 4)
+            *(uint32_t*)(q + i * VEC + e) = (uint32_t)(qc[e] & 0xFF) | ((uint32_t)(qc[e + 1] & 0xFF) << 8) | ((uint32_t)(qc[e + 2] & 0xFF) << 16) |
+                                            ((uint32_t)(qc[e + 3] & 0xFF) << 24);
+        }
+      }
+      base += kRowBatch * 64;
+      if (base >= vecs) break;
+      load(base);
+    }
+    return;
+  }
   if (scale_is_input) {
     s = scale[row];
   } else {
@@ -248,18 +308,19 @@ __global__ void __launch_bounds__(256) quantize_rows_kernel(const T* __restrict_
     if (lane == 0) scale[row] = s;
   }
   const float rs = scale_reciprocal(s);
-  int8_t* q = Q + row * cols;
-  if ((cols & 3) == 0) {
-    for (int64_t c = (int64_t)lane * 4; c < cols; c += 256) {
-      const float xs[4] = {load_as_f32(x, c), load_as_f32(x, c + 1), load_as_f32(x, c + 2), load_as_f32(x, c + 3)};
-      int qc[4];
-      quantize_codes<4>(xs, s, rs, qc, qmax);
-      *(uint32_t*)(q + c) = (uint32_t)(qc[0] & 0xFF) | ((uint32_t)(qc[1] & 0xFF) << 8) | ((uint32_t)(qc[2] & 0xFF) << 16) |
-                            ((uint32_t)(qc[3] & 0xFF) << 24);
-    }
-  } else {
-    for (int64_t c = lane; c < cols; c += 64) q[c] = (int8_t)quantize_code(load_as_f32(x, c), s, rs, qmax);
-  }
+  for (int64_t c = lane; c < cols; c += 64) q[c] = (int8_t)quantize_code(load_as_f32(x, c), s, rs, qmax);
+}
+
+template <typename T>
+static gpusq_status launch_quantize_rows(const T* X, int8_t* Xq, float* scale, int scale_is_input, int64_t rows, int64_t cols, float qmax,
+                                         hipStream_t s) {
+  const unsigned blocks = (unsigned)ceil_div(rows, 4);
+  const int64_t vecs = cols * (int64_t)sizeof(T) / 16;
+  if (vecs > 8 * 64 && vecs <= 20 * 64)
+    quantize_rows_kernel<T, 20><<<blocks, 256, 0, s>>>(X, Xq, scale, scale_is_input, rows, cols, qmax);
+  else
+    quantize_rows_kernel<T, 8><<<blocks, 256, 0, s>>>(X, Xq, scale, scale_is_input, rows, cols, qmax);
+  return check_launch();
 }
 
 __global__ void fill_u32_kernel(uint32_t* p, uint32_t v) { *p = v; }
@@ -353,8 +414,7 @@ template <typename T>
 static gpusq_status quantize_typed(const T* X, int8_t* Xq, float* scale, int mode, int scale_is_input, int64_t rows,
                                    int64_t cols, void* workspace, hipStream_t s) {
   if (mode == GPUSQ_PER_ROW) {
-    quantize_rows_kernel<T><<<(unsigned)ceil_div(rows, 4), 256, 0, s>>>(X, Xq, scale, scale_is_input, rows, cols, 127.0f);
-    return check_launch();
+    return launch_quantize_rows(X, Xq, scale, scale_is_input, rows, cols, 127.0f, s);
   }
   const int64_t n = rows * cols;
   const int64_t want = ceil_div(n, 256 * 8 * 2);  // two 8-element vectors per thread ...
@@ -426,12 +486,8 @@ gpusq_status launch_quantize_tensor_static(const void* X, gpusq_dtype dt, int8_t
 // The same per-row quantiser with the 4-bit range: codes -7..7 in int8 containers, scale = max|row| / 7.
 gpusq_status launch_quantize_rows_int4(const void* X, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, int64_t rows,
                                        int64_t cols, hipStream_t s) {
-  const unsigned blocks = (unsigned)ceil_div(rows, 4);
-  if (dt == GPUSQ_F32)
-    quantize_rows_kernel<float><<<blocks, 256, 0, s>>>((const float*)X, Xq, scale, scale_is_input, rows, cols, 7.0f);
-  else
-    quantize_rows_kernel<_Float16><<<blocks, 256, 0, s>>>((const _Float16*)X, Xq, scale, scale_is_input, rows, cols, 7.0f);
-  return check_launch();
+  if (dt == GPUSQ_F32) return launch_quantize_rows((const float*)X, Xq, scale, scale_is_input, rows, cols, 7.0f, s);
+  return launch_quantize_rows((const _Float16*)X, Xq, scale, scale_is_input, rows, cols, 7.0f, s);
 }
 
 // ------------------------------------------------------------------------------------------------------------ compress
@@ -578,9 +634,11 @@ gpusq_status launch_decompress(const void* values, const uint8_t* meta, void* W,
 // wants, per lane, the kept values of that range in order (16 bytes) and their 2-bit positions in order starting at
 // bit 0 of the index register.  Both are contiguous byte runs of the canonical arrays:
 // values[n][k0/2 .. k0/2 + kept) and meta[n][k0/8 ..).  Rows >= N and K beyond the row end are zero-filled.
-template <bool IS_I8>
+// WHOLE: K is a multiple of a lane's range (32 int8, 16 fp16 elements), so a run is one 16-byte and one 4-byte (2-byte) load;
+// byte by byte the 5120 x 1280 int8 operand took 11.6 us.
+template <bool IS_I8, bool WHOLE>
 __global__ void __launch_bounds__(256) pack_kernel(const uint8_t* __restrict__ values, const uint8_t* __restrict__ meta,
-                                                   uint8_t* __restrict__ packed, int64_t N, int64_t K, int64_t ksteps,
+                                                   uint8_t* __restrict__ packed, int64_t N, int64_t K, int ksteps,
                                                    int64_t total_lanes) {
   constexpr int E = step_elems(IS_I8);  // dense elements per step
   constexpr int ES = IS_I8 ? 1 : 2;     // element size
@@ -591,10 +649,29 @@ __global__ void __launch_bounds__(256) pack_kernel(const uint8_t* __restrict__ v
   const int lane = (int)(id & 63);
   const int f = (int)((id >> 6) & 15);
   const int64_t tile = id >> 10;
-  const int64_t ks = tile % ksteps, nb = tile / ksteps;
+  const int64_t nb = (unsigned)tile / (unsigned)ksteps, ks = (unsigned)tile - (unsigned)nb * (unsigned)ksteps;  // (fewer than 2^32 tiles)
   const int64_t n = nb * kTileRows + (f >> 2) * kRowBlock + packed_row_to_channel(f & 3, lane & 15);
   const int64_t k0 = ks * E + (int64_t)(lane >> 4) * KL;  // first dense element of this lane
   const int64_t mrb = (K / 4 + 1) / 2;
+  uint8_t* t = packed + tile * tile_bytes(IS_I8);
+  uint8_t* ip = t + index_offset(IS_I8, f, lane);
+  if (WHOLE) {  // every lane's run lies inside a row or past its end, and is aligned
+    uint4 vv = uint4{0, 0, 0, 0};
+    uint32_t ix = 0;
+    if (n < N && k0 < K) {
+      vv = *(const uint4*)(values + (n * (K / 2) + k0 / 2) * ES);
+      if constexpr (IS_I8)
+        ix = *(const uint32_t*)(meta + n * (K / 8) + k0 / 8);
+      else
+        ix = *(const uint16_t*)(meta + n * (K / 8) + k0 / 8);
+    }
+    *(uint4*)(t + f * kFragValueBytes + lane * 16) = vv;
+    if constexpr (IS_I8)
+      *(uint32_t*)ip = ix;
+    else
+      *(uint16_t*)ip = (uint16_t)ix;
+    return;
+  }
   uint8_t v[16];
   uint8_t ix[IB];
 #pragma unroll
@@ -608,14 +685,12 @@ __global__ void __launch_bounds__(256) pack_kernel(const uint8_t* __restrict__ v
     // padding (rows >= N, K beyond the row end) carries zero values; its positions are irrelevant
     ix[i] = (n < N && byte < mrb) ? meta[n * mrb + byte] : (uint8_t)0;
   }
-  uint8_t* t = packed + tile * tile_bytes(IS_I8);
   uint4 vv;
   vv.x = v[0] | (v[1] << 8) | (v[2] << 16) | ((uint32_t)v[3] << 24);
   vv.y = v[4] | (v[5] << 8) | (v[6] << 16) | ((uint32_t)v[7] << 24);
   vv.z = v[8] | (v[9] << 8) | (v[10] << 16) | ((uint32_t)v[11] << 24);
   vv.w = v[12] | (v[13] << 8) | (v[14] << 16) | ((uint32_t)v[15] << 24);
   *(uint4*)(t + f * kFragValueBytes + lane * 16) = vv;
-  uint8_t* ip = t + index_offset(IS_I8, f, lane);
   if constexpr (IS_I8)
     *(uint32_t*)ip = ix[0] | (ix[1] << 8) | (ix[2] << 16) | ((uint32_t)ix[3] << 24);
   else
@@ -629,196 +704,192 @@ gpusq_status launch_pack(const void* values, const uint8_t* meta, void* packed, 
   const int64_t tiles = ceil_div(N, kTileRows) * ksteps;
   const int64_t total_lanes = tiles * 16 * 64;
   const unsigned blocks = (unsigned)ceil_div(total_lanes, 256);
-  if (is_i8)
-    pack_kernel<true><<<blocks, 256, 0, s>>>((const uint8_t*)values, meta, (uint8_t*)packed, N, K, ksteps, total_lanes);
-  else
-    pack_kernel<false><<<blocks, 256, 0, s>>>((const uint8_t*)values, meta, (uint8_t*)packed, N, K, ksteps, total_lanes);
+  const bool whole = K % (step_elems(is_i8) / 4) == 0;
+#define GPUSQ_PACK(I8, WH) pack_kernel<I8, WH><<<blocks, 256, 0, s>>>((const uint8_t*)values, meta, (uint8_t*)packed, N, K, (int)ksteps, total_lanes)
+  if (is_i8 && whole) GPUSQ_PACK(true, true);
+  else if (is_i8) GPUSQ_PACK(true, false);
+  else if (whole) GPUSQ_PACK(false, true);
+  else GPUSQ_PACK(false, false);
+#undef GPUSQ_PACK
   return check_launch();
 }
 
 // ------------------------------------------------------------------------------------------------------------ fused
 // prune -> (INT8: per-output-channel quantise | FP16: round) -> compress -> pack for one weight matrix in one launch.
-// One workgroup per output channel.  Phase 1 streams the fp32 row into LDS and reduces max|w| (pruning never removes
-// the row maximum, so this is also the maximum of the pruned row).  Phase 2 gives each thread one "lane unit" of the
-// packed format: the 32 (INT8) or 16 (FP16) consecutive dense elements whose kept values fill one lane's 16 value
-// bytes and 4 (2) index bytes; the thread prunes its groups of 4, quantises or rounds them, applies the compression
-// rule to the low-precision group, and writes the unit to every requested output.  All arithmetic is the same
-// sequence of operations as the separate kernels above, so the results are bit-identical to running them in turn.
-// A workgroup handles `rows_per_block` (1, 2, 4 or 8) consecutive channels with 256 / rows_per_block threads each, so
-// that short rows (K = 768 has only 24 lane units) still keep most of the workgroup busy.
-template <bool IS_I8>
+// One wavefront per output channel, one lane per group of 4: a lane prunes its group, quantises or rounds it, applies the
+// compression rule to the low-precision group and writes its two kept values and its positions to every requested output.
+// All arithmetic is the same sequence of operations as the separate kernels above, so the results are bit-identical to running
+// them in turn.  (Pruning never removes the row maximum, so the maximum of the row is that of the pruned row.)
+// What bounds it is latency: the row, its maximum, the codes.  So a row's groups are requested in batches of kPrepBatch per
+// lane, all before the first is used, and a row of one batch stays in registers (a longer one is read twice, the second time
+// from the L2); the maximum takes wavefront shuffles.  Rows of more than 2048 elements are dealt out over WPR = 4 wavefronts
+// (768 x 3072: with one wavefront per row the chip has fewer wavefronts than SIMDs).  A workgroup takes 4 (WPR = 4: 1) rows of
+// a fragment, and the workgroups whose packed lanes share 128-byte lines run on one XCD.  The rows of the packed
+// tiles past N and the K range past the row end are written (zero) by the wavefronts that own them.
+// With a thread per 32 elements, LDS for the rows and one load in flight per thread, int8: 3072 x 768 9.8 us, 6.0 so; 768 x
+// 3072 10.0, 6.1 so; 5120 x 1280 17.3, 12.2 so.  Workgroups of 256 threads: with 512 and 1024 the 1280 x 5120 take 16 and 20
+// us instead of 13 (their last round is thin), and WPR = 4 at K = 768 12 instead of 6 (one row per workgroup).
+constexpr int kPrepBatch = 8;
+template <bool IS_I8, int WPR>
 __global__ void __launch_bounds__(256) prepare_weights_kernel(const float* __restrict__ W, float* __restrict__ Wp,
                                                               uint8_t* __restrict__ Wlow, float* __restrict__ w_scale,
                                                               uint8_t* __restrict__ values, uint8_t* __restrict__ meta,
-                                                              uint8_t* __restrict__ packed, int64_t N, int64_t K, int64_t ksteps,
-                                                              int rows_per_block) {
-  extern __shared__ float rows_lds[];  // rows_per_block rows of K floats
-  __shared__ float red[256];
-  constexpr int E = step_elems(IS_I8), ES = IS_I8 ? 1 : 2, KL = E / 4, IB = IS_I8 ? 4 : 2;
-  const int tpr = 256 / rows_per_block;         // threads per row
-  const int lr = (int)threadIdx.x / tpr;        // local row
-  const int tr = (int)threadIdx.x % tpr;        // thread within the row
-  const int64_t n = (int64_t)blockIdx.x * rows_per_block + lr;
-  const bool live = n < N;
-  float* row = rows_lds + (int64_t)lr * K;
-  float amax = 0.0f;
-  if (live) {
-    const float* w = W + n * K;
-    for (int64_t k = (int64_t)tr * 4; k < K; k += (int64_t)tpr * 4) {
-      const float4 v = *(const float4*)(w + k);
-      *(float4*)(row + k) = v;
-      amax = fmaxf(fmaxf(amax, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
+                                                              uint8_t* __restrict__ packed, int64_t N, int64_t K, int ksteps) {
+  constexpr int GS = step_elems(IS_I8) / 4;   // groups per K step
+  constexpr int GU = GS / 4;                  // groups per packed lane
+  constexpr int GB = 16 / GU;                 // bytes of kept values per group
+  constexpr int B = kPrepBatch;
+  constexpr int ROWS = 4 / WPR, STRIDE = 64 * WPR;  // rows of a workgroup; groups between a lane's consecutive ones
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // Workgroup id (64-channel block, fragment t of it, ROWS of its 16 rows), the last varying fastest; the ids that share a
+  // line (8 rows) go to workgroups 8 apart, which the dispatcher places on one XCD.
+  constexpr int SHARE = 8 / ROWS;
+  int id = (int)blockIdx.x;
+  id = (id & ~(8 * SHARE - 1)) | ((id & 7) * SHARE) | ((id >> 3) & (SHARE - 1));
+  constexpr int PER_FRAG = 16 / ROWS;
+  const int blk = id / (4 * PER_FRAG), t = (id / PER_FRAG) & 3, r = ROWS * (id % PER_FRAG) + wave / WPR;
+  const int64_t n = (int64_t)blk * kRowBlock + packed_row_to_channel(t, r);
+  const bool live = n < N;  // wavefront-uniform
+  const int groups = live ? (int)(K / 4) : 0, padded = ksteps * GS;
+  const int start = (wave % WPR) * 64;  // this wavefront's first group
+  const float4* row = (const float4*)(W + (live ? n : 0) * K);
+  float4 v[B];
+  auto load = [&](int base) {
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      const int g = base + j * STRIDE + lane;
+      v[j] = g < groups ? row[g] : float4{0.0f, 0.0f, 0.0f, 0.0f};
     }
-  }
+  };
+  load(start);
   float s = 1.0f;
-  if constexpr (IS_I8) {  // max over the row's threads (any order gives the same maximum), through LDS
-    red[threadIdx.x] = amax;
-    __syncthreads();  // also publishes the rows
-    for (int h = tpr >> 1; h > 0; h >>= 1) {
-      if (tr < h) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + h]);
-      __syncthreads();
+  if constexpr (IS_I8) {
+    float amax = 0.0f;
+    for (int base = start;;) {
+#pragma unroll
+      for (int j = 0; j < B; ++j) amax = fmaxf(fmaxf(amax, fmaxf(fabsf(v[j].x), fabsf(v[j].y))), fmaxf(fabsf(v[j].z), fabsf(v[j].w)));
+      base += B * STRIDE;
+      if (base >= groups) break;
+      load(base);
     }
-    amax = red[lr * tpr];
+    amax = wave_max(amax);
+    if constexpr (WPR > 1) {
+      __shared__ float part[ROWS * WPR];
+      if (lane == 0) part[wave] = amax;
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < WPR; ++w) amax = fmaxf(amax, part[wave / WPR * WPR + w]);
+    }
     s = (amax == 0.0f) ? 1.0f : __fdiv_rn(amax, 127.0f);
-    if (live && tr == 0) w_scale[n] = s;
-  } else {
-    __syncthreads();
+    if (live && start == 0 && lane == 0) w_scale[n] = s;
+    if (start + B * STRIDE < groups) load(start);
   }
-  if (!live) return;
   const float rs = scale_reciprocal(s);
   const int64_t mrb = (K / 4 + 1) / 2;
-  const int64_t units = (K + KL - 1) / KL;
-  // packed position of this channel: tile nb, fragment f, row r of the fragment
-  const int64_t nb = n / kTileRows;
-  const int in_tile = (int)(n % kTileRows), blk = in_tile / kRowBlock, c64 = in_tile % kRowBlock;
-  // inverse of packed_row_to_channel: c64 = 32*(t/2) + 8*(r/4) + 4*(t%2) + r%4
-  const int t = 2 * (c64 >> 5) + ((c64 >> 2) & 1), r = 4 * ((c64 >> 3) & 3) + (c64 & 3);
-  const int f = blk * 4 + t;
-  for (int64_t u = tr; u < units; u += tpr) {
-    const int64_t k0 = u * KL;
-    uint8_t vbytes[16];
-    uint8_t ibytes[IB];
+  const int f = (blk & 3) * 4 + t;  // fragment of the packed tile
+  uint8_t* column = packed + (n / kTileRows) * ksteps * tile_bytes(IS_I8);
+  for (int base = start; base < padded;) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) vbytes[i] = 0;
-#pragma unroll
-    for (int i = 0; i < IB; ++i) ibytes[i] = 0;
-#pragma unroll
-    for (int g = 0; g < KL / 4; ++g) {
-      const int64_t k = k0 + 4 * g;
-      if (k < K) {
-        const float4 x = *(const float4*)(row + k);
-        const unsigned m = keep_mask_of_4(__float_as_uint(x.x) & 0x7FFFFFFFu, __float_as_uint(x.y) & 0x7FFFFFFFu,
-                                          __float_as_uint(x.z) & 0x7FFFFFFFu, __float_as_uint(x.w) & 0x7FFFFFFFu);
-        float4 p;
-        p.x = (m & 1u) ? x.x : 0.0f; p.y = (m & 2u) ? x.y : 0.0f; p.z = (m & 4u) ? x.z : 0.0f; p.w = (m & 8u) ? x.w : 0.0f;
-        if (Wp) *(float4*)(Wp + n * K + k) = p;
-        unsigned nib;
-        if constexpr (IS_I8) {
-          const float ps[4] = {p.x, p.y, p.z, p.w};
-          int qc[4];
-          quantize_codes<4>(ps, s, rs, qc);
-          const int q0 = qc[0], q1 = qc[1], q2 = qc[2], q3 = qc[3];
-          if (Wlow) *(uint32_t*)(Wlow + n * K + k) = (uint32_t)(q0 & 0xFF) | ((uint32_t)(q1 & 0xFF) << 8) | ((uint32_t)(q2 & 0xFF) << 16) | ((uint32_t)(q3 & 0xFF) << 24);
-          const unsigned mq = keep_mask_of_4((unsigned)abs(q0), (unsigned)abs(q1), (unsigned)abs(q2), (unsigned)abs(q3));
-          nib = nibble_of_mask(mq);
-          const unsigned p0 = nib & 3u, p1 = nib >> 2;
-          vbytes[2 * g] = (uint8_t)(p0 == 0 ? q0 : (p0 == 1 ? q1 : q2));
-          vbytes[2 * g + 1] = (uint8_t)(p1 == 1 ? q1 : (p1 == 2 ? q2 : q3));
-        } else {
-          const _Float16 h0 = (_Float16)p.x, h1 = (_Float16)p.y, h2 = (_Float16)p.z, h3 = (_Float16)p.w;
-          const unsigned b0 = __builtin_bit_cast(unsigned short, h0), b1 = __builtin_bit_cast(unsigned short, h1);
-          const unsigned b2 = __builtin_bit_cast(unsigned short, h2), b3 = __builtin_bit_cast(unsigned short, h3);
-          if (Wlow) *(uint2*)(Wlow + (n * K + k) * 2) = uint2{b0 | (b1 << 16), b2 | (b3 << 16)};
-          const unsigned mq = keep_mask_of_4(b0 & 0x7FFFu, b1 & 0x7FFFu, b2 & 0x7FFFu, b3 & 0x7FFFu);
-          nib = nibble_of_mask(mq);
-          const unsigned p0 = nib & 3u, p1 = nib >> 2;
-          const unsigned v0 = p0 == 0 ? b0 : (p0 == 1 ? b1 : b2), v1 = p1 == 1 ? b1 : (p1 == 2 ? b2 : b3);
-          vbytes[4 * g] = (uint8_t)v0; vbytes[4 * g + 1] = (uint8_t)(v0 >> 8);
-          vbytes[4 * g + 2] = (uint8_t)v1; vbytes[4 * g + 3] = (uint8_t)(v1 >> 8);
-        }
-        ibytes[g >> 1] |= (uint8_t)(nib << (4 * (g & 1)));
-      }
-    }
-    uint4 vv;
-    vv.x = vbytes[0] | (vbytes[1] << 8) | (vbytes[2] << 16) | ((uint32_t)vbytes[3] << 24);
-    vv.y = vbytes[4] | (vbytes[5] << 8) | (vbytes[6] << 16) | ((uint32_t)vbytes[7] << 24);
-    vv.z = vbytes[8] | (vbytes[9] << 8) | (vbytes[10] << 16) | ((uint32_t)vbytes[11] << 24);
-    vv.w = vbytes[12] | (vbytes[13] << 8) | (vbytes[14] << 16) | ((uint32_t)vbytes[15] << 24);
-    const bool whole = k0 + KL <= K;
-    if (values) {
-      uint8_t* dst = values + (n * (K / 2) + k0 / 2) * ES;
-      if (whole && ((K / 2) * ES) % 16 == 0) {  // rows of the values array are 16-byte aligned
-        *(uint4*)dst = vv;
+    for (int j = 0; j < B; ++j) {
+      if (base + j * STRIDE >= padded) break;  // wavefront-uniform
+      const int g = base + j * STRIDE + lane;
+      const float4 x = v[j];
+      // the selection rule of keep_mask_of_4 on lane masks: element i is dropped iff two or more of the others beat it, where
+      // of a pair the second beats the first iff it is larger (six comparisons, the rest is scalar logic)
+      const unsigned k0 = __float_as_uint(x.x) & 0x7FFFFFFFu, k1 = __float_as_uint(x.y) & 0x7FFFFFFFu;
+      const unsigned k2 = __float_as_uint(x.z) & 0x7FFFFFFFu, k3 = __float_as_uint(x.w) & 0x7FFFFFFFu;
+      const bool c01 = k1 > k0, c02 = k2 > k0, c03 = k3 > k0, c12 = k2 > k1, c13 = k3 > k1, c23 = k3 > k2;
+      auto two_of = [](bool p, bool q, bool r) { return (p & q) | (r & (p | q)); };
+      const bool keep0 = !two_of(c01, c02, c03), keep1 = !two_of(!c01, c12, c13), keep2 = !two_of(!c02, !c12, c23);
+      const bool keep3 = !two_of(!c03, !c13, !c23);
+      unsigned p0 = keep0 ? 0u : (keep1 ? 1u : 2u), p1 = keep3 ? 3u : (keep2 ? 2u : 1u);
+      const float first = keep0 ? x.x : (keep1 ? x.y : x.z), second = keep3 ? x.w : (keep2 ? x.z : x.y);
+      const bool in_row = g < groups;
+      if (Wp && in_row) *(float4*)(Wp + n * K + 4 * g) = float4{keep0 ? x.x : 0.0f, keep1 ? x.y : 0.0f, keep2 ? x.z : 0.0f, keep3 ? x.w : 0.0f};
+      // the two kept values in low precision; the positions recorded are those of the rule applied to the low-precision group,
+      // which differ only where a kept value became zero (then zeros are kept from the lowest index on)
+      unsigned kept;
+      bool zero;
+      if constexpr (IS_I8) {
+        const float xs[2] = {first, second};
+        int q[2];
+        quantize_codes<2>(xs, s, rs, q);
+        kept = (unsigned)(q[0] & 0xFF) | ((unsigned)(q[1] & 0xFF) << 8);
+        zero = q[0] == 0 || q[1] == 0;
       } else {
-        const int64_t nbytes = whole ? 16 : ((K - k0) / 2) * ES;
-        for (int64_t i = 0; i < nbytes; ++i) dst[i] = vbytes[i];
+        const unsigned h0 = __builtin_bit_cast(unsigned short, (_Float16)first), h1 = __builtin_bit_cast(unsigned short, (_Float16)second);
+        kept = h0 | (h1 << 16);
+        zero = (h0 & 0x7FFFu) == 0 || (h1 & 0x7FFFu) == 0;
+      }
+      if (Wlow && in_row) {
+        if constexpr (IS_I8)
+          *(uint32_t*)(Wlow + n * K + 4 * g) = ((kept & 0xFFu) << (8 * p0)) | ((kept >> 8) << (8 * p1));
+        else
+          *(uint64_t*)(Wlow + (n * K + 4 * g) * 2) = ((uint64_t)(kept & 0xFFFFu) << (16 * p0)) | ((uint64_t)(kept >> 16) << (16 * p1));
+      }
+      if (__builtin_amdgcn_ballot_w64(zero) != 0) {
+        constexpr int BITS = IS_I8 ? 8 : 16;
+        constexpr unsigned ONE = (1u << BITS) - 1u, MAGNITUDE = IS_I8 ? 0xFFu : 0x7FFFu;
+        const uint64_t group = ((uint64_t)(kept & ONE) << (BITS * p0)) | ((uint64_t)(kept >> BITS) << (BITS * p1));
+        unsigned nz = 0;  // the non-zero elements of the low-precision group: at most two, and they come first
+#pragma unroll
+        for (int i = 0; i < 4; ++i) nz |= (unsigned)(((unsigned)(group >> (BITS * i)) & MAGNITUDE) != 0) << i;
+        const unsigned nib = nibble_of_mask(keep_mask_of_4(nz & 1u, (nz >> 1) & 1u, (nz >> 2) & 1u, (nz >> 3) & 1u));
+        p0 = nib & 3u;
+        p1 = nib >> 2;
+        kept = ((unsigned)(group >> (BITS * p0)) & ONE) | (((unsigned)(group >> (BITS * p1)) & ONE) << BITS);
+      }
+      const unsigned nib = in_row ? p0 | (p1 << 2) : 0u;
+      // the positions of a packed lane's GU groups, the first group's in the low nibble: exchanged inside its 4 (8) lanes
+      // (quad_perm 1,0,3,2 = 0xB1, quad_perm 2,3,0,1 = 0x4E, row_half_mirror = 0x141)
+      unsigned ix = nib << (4 * (lane & (GU - 1)));
+      ix |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)ix, 0xB1, 0xF, 0xF, true);
+      ix |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)ix, 0x4E, 0xF, 0xF, true);
+      if constexpr (GU == 8) ix |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)ix, 0x141, 0xF, 0xF, true);
+      if (in_row) {
+        if (values) {
+          if constexpr (IS_I8)
+            *(uint16_t*)(values + n * (K / 2) + 2 * g) = (uint16_t)kept;
+          else
+            *(uint32_t*)(values + (n * (K / 2) + 2 * g) * 2) = kept;
+        }
+        if (meta && (g & 1) == 0) meta[n * mrb + (g >> 1)] = (uint8_t)(ix >> (4 * (lane & (GU - 1))));
+      }
+      if (g < padded) {
+        const int ks = g / GS, q4 = (g & (GS - 1)) / GU, in_lane = g & (GU - 1);
+        uint8_t* tp = column + (int64_t)ks * tile_bytes(IS_I8);
+        uint8_t* vp = tp + f * kFragValueBytes + (r + 16 * q4) * 16 + in_lane * GB;
+        if constexpr (IS_I8)
+          *(uint16_t*)vp = (uint16_t)kept;
+        else
+          *(uint32_t*)vp = kept;
+        if (in_lane == 0) {
+          uint8_t* ip = tp + index_offset(IS_I8, f, r + 16 * q4);
+          if constexpr (IS_I8)
+            *(uint32_t*)ip = ix;
+          else
+            *(uint16_t*)ip = (uint16_t)ix;
+        }
       }
     }
-    if (meta) {
-      uint8_t* dst = meta + n * mrb + k0 / 8;
-      const int64_t nbytes = whole ? IB : (mrb - k0 / 8);
-      for (int64_t i = 0; i < nbytes; ++i) dst[i] = ibytes[i];
-    }
-    const int64_t ks = k0 / E;
-    const int lane = r + 16 * (int)((k0 % E) / KL);
-    uint8_t* tp = packed + (nb * ksteps + ks) * tile_bytes(IS_I8);
-    *(uint4*)(tp + f * kFragValueBytes + lane * 16) = vv;
-    uint8_t* ip = tp + index_offset(IS_I8, f, lane);
-    if constexpr (IS_I8)
-      *(uint32_t*)ip = ibytes[0] | (ibytes[1] << 8) | (ibytes[2] << 16) | ((uint32_t)ibytes[3] << 24);
-    else
-      *(uint16_t*)ip = (uint16_t)(ibytes[0] | (ibytes[1] << 8));
+    base += B * STRIDE;
+    if (base < padded) load(base);
   }
-}
-
-// zero-fills the part of the packed buffer that no real channel / K range writes (rows >= N, K beyond the row end)
-template <bool IS_I8>
-__global__ void __launch_bounds__(256) clear_packed_padding_kernel(uint8_t* __restrict__ packed, int64_t N, int64_t K, int64_t ksteps,
-                                                                   int64_t total_lanes) {
-  constexpr int E = step_elems(IS_I8), KL = E / 4;
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= total_lanes) return;
-  const int lane = (int)(id & 63);
-  const int f = (int)((id >> 6) & 15);
-  const int64_t tile = id >> 10;
-  const int64_t ks = tile % ksteps, nb = tile / ksteps;
-  const int64_t n = nb * kTileRows + (f >> 2) * kRowBlock + packed_row_to_channel(f & 3, lane & 15);
-  const int64_t k0 = ks * E + (int64_t)(lane >> 4) * KL;
-  if (n < N && k0 < K) return;  // written by prepare_weights_kernel
-  uint8_t* t = packed + tile * tile_bytes(IS_I8);
-  *(uint4*)(t + f * kFragValueBytes + lane * 16) = uint4{0, 0, 0, 0};
-  uint8_t* ip = t + index_offset(IS_I8, f, lane);
-  if constexpr (IS_I8)
-    *(uint32_t*)ip = 0u;
-  else
-    *(uint16_t*)ip = (uint16_t)0;
 }
 
 gpusq_status launch_prepare_weights(const float* W, gpusq_dtype dt, float* Wp, void* Wlow, float* w_scale, void* values,
                                     uint8_t* meta, void* packed, int64_t N, int64_t K, hipStream_t s) {
   const bool is_i8 = dt == GPUSQ_I8;
-  const int64_t ksteps = ceil_div(K, step_elems(is_i8));
-  // as many rows per workgroup as keep every row's threads busy (one thread per 32-byte lane unit) within 64 KB of LDS
-  const int64_t units = ceil_div(K, step_elems(is_i8) / 4);
-  int rpb = 1;
-  while (rpb < 8 && 256 / (rpb * 2) >= units && (size_t)K * sizeof(float) * (rpb * 2) <= 64 * 1024) rpb *= 2;
-  const size_t lds = (size_t)K * sizeof(float) * rpb;
-  const unsigned grid = (unsigned)ceil_div(N, rpb);
-  const bool padded = (N % kTileRows) != 0 || (K % step_elems(is_i8)) != 0;
-  if (padded) {
-    const int64_t total_lanes = ceil_div(N, kTileRows) * ksteps * 16 * 64;
-    const unsigned blocks = (unsigned)ceil_div(total_lanes, 256);
-    if (is_i8)
-      clear_packed_padding_kernel<true><<<blocks, 256, 0, s>>>((uint8_t*)packed, N, K, ksteps, total_lanes);
-    else
-      clear_packed_padding_kernel<false><<<blocks, 256, 0, s>>>((uint8_t*)packed, N, K, ksteps, total_lanes);
-  }
-  if (is_i8)
-    prepare_weights_kernel<true><<<grid, 256, lds, s>>>(W, Wp, (uint8_t*)Wlow, w_scale, (uint8_t*)values, meta, (uint8_t*)packed, N, K,
-                                                        ksteps, rpb);
-  else
-    prepare_weights_kernel<false><<<grid, 256, lds, s>>>(W, Wp, (uint8_t*)Wlow, w_scale, (uint8_t*)values, meta, (uint8_t*)packed, N, K,
-                                                         ksteps, rpb);
+  const int ksteps = (int)ceil_div(K, step_elems(is_i8));
+  const unsigned tiles = (unsigned)ceil_div(N, kTileRows);  // the padding rows of the last tile have their workgroups as well
+#define GPUSQ_PREPARE(I8, WPR, ROWS)                                                                                                  \
+  prepare_weights_kernel<I8, WPR><<<tiles * (kTileRows / ROWS), 64 * WPR * ROWS, 0, s>>>(W, Wp, (uint8_t*)Wlow, w_scale, (uint8_t*)values, \
+                                                                                          meta, (uint8_t*)packed, N, K, ksteps)
+  if (is_i8 && K > 2048) GPUSQ_PREPARE(true, 4, 1);
+  else if (is_i8) GPUSQ_PREPARE(true, 1, 4);
+  else if (K > 2048) GPUSQ_PREPARE(false, 4, 1);
+  else GPUSQ_PREPARE(false, 1, 4);
+#undef GPUSQ_PREPARE
   return check_launch();
 }
 
