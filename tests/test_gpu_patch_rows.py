@@ -1,0 +1,21 @@
+"""Flattened patches at the edges of the strip kernel: pieces of 1, 2, 4 and 8 bytes, rows of X of more 16-byte chunks than a
+workgroup has threads, strips and planes that are not whole 16-byte vectors, and channels that do not fit into LDS together
+(the kernel per channel)."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import dev, g, host  # noqa: F401
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,C,H,W,P,K_pad", [(2, 3, 20, 40, 5, 80), (3, 1, 36, 12, 3, 16), (1, 2, 28, 42, 14, 4112), (2, 3, 42, 56, 14, 592),
+                                             (1, 90, 28, 28, 14, 17648), (5, 3, 24, 40, 8, 208), (2, 3, 12, 20, 2, 16), (1, 3, 98, 14, 14, 640)])
+@pytest.mark.parametrize("dtype", [np.float16, np.int8])
+def test_patch_rows(g, B, C, H, W, P, K_pad, dtype):
+    rng = np.random.default_rng(B * 1000 + W)
+    img = rng.integers(-100, 100, (B, C, H, W)).astype(dtype)
+    exp = np.zeros((B * (H // P) * (W // P), K_pad), dtype)
+    exp[:, : C * P * P] = img.reshape(B, C, H // P, P, W // P, P).transpose(0, 2, 4, 1, 3, 5).reshape(-1, C * P * P)
+    assert np.array_equal(host(g.im2col_patches(dev(img), P, K_pad)), exp)
