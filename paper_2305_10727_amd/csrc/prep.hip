@@ -402,18 +402,6 @@ __global__ void fill_u32_kernel(uint32_t* p, uint32_t v) { *p = v; }
 
 constexpr int kAmaxMaxBlocks = 1024;  // per-block partial maxima kept in the caller's workspace (4 KB)
 
-// 8 consecutive elements as fp32, one 16-byte (fp16) or two 16-byte (fp32) loads
-__device__ __forceinline__ void load8(const float* p, float (&v)[8]) {
-  const float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
-  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-}
-__device__ __forceinline__ void load8(const _Float16* p, float (&v)[8]) {
-  typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-  const h8 a = *(const h8*)p;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) v[j] = (float)a[j];
-}
-
 __device__ __forceinline__ float block_max(float v) {
   __shared__ float part[4];
   v = wave_max(v);
@@ -423,30 +411,55 @@ __device__ __forceinline__ float block_max(float v) {
   return fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
 }
 
-// per-tensor max |x|, first pass: every workgroup streams its share with 16-byte loads and leaves one partial
-// maximum in the workspace; the quantising pass folds the partials (no atomics, nothing to clear beforehand)
+// Per-tensor max |x|, first pass: every workgroup streams its share with 16-byte loads, two per thread in flight, and leaves one
+// partial maximum in the workspace; the quantising pass folds the partials (no atomics, nothing to clear beforehand).
+__device__ __forceinline__ float range_of_vec(const float4& v) { return fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))); }
+
 template <typename T>
 __global__ void __launch_bounds__(256) tensor_amax_kernel(const T* __restrict__ X, int64_t n, float* __restrict__ partial) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+  typedef unsigned u4 __attribute__((ext_vector_type(4)));
+  const int64_t vecs = n / VEC;
   float amax = 0.0f;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x * 8;
-  for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 8; i < n; i += stride) {
-    if (i + 8 <= n) {
-      float v[8];
-      load8(X + i, v);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) amax = fmaxf(amax, fabsf(v[j]));
+  h8 m = h8(0);
+  const int64_t stride = (int64_t)gridDim.x * 512;
+  for (int64_t i = (int64_t)blockIdx.x * 512 + threadIdx.x; i < vecs; i += stride) {
+    const u4 a = ((const u4*)X)[i], b = ((const u4*)X)[i + 256 < vecs ? i + 256 : i];
+    if constexpr (VEC == 8) {
+      m = __builtin_elementwise_max(m, __builtin_bit_cast(h8, a & 0x7fff7fffu));
+      m = __builtin_elementwise_max(m, __builtin_bit_cast(h8, b & 0x7fff7fffu));
     } else {
-      for (int64_t j = i; j < n; ++j) amax = fmaxf(amax, fabsf(load_as_f32(X, j)));
+      amax = fmaxf(amax, fmaxf(range_of_vec(__builtin_bit_cast(float4, a)), range_of_vec(__builtin_bit_cast(float4, b))));
     }
   }
+  if constexpr (VEC == 8) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) amax = fmaxf(amax, (float)m[j]);
+  }
+  if (blockIdx.x == 0 && vecs * VEC + threadIdx.x < n) amax = fmaxf(amax, fabsf(load_as_f32(X, vecs * VEC + threadIdx.x)));
   amax = block_max(amax);
   if (threadIdx.x == 0) partial[blockIdx.x] = amax;
 }
 
-template <typename T>
+// The codes: consecutive lanes read consecutive 16-byte vectors, U per thread in flight.
+// (Stored with the non-temporal hint the two passes take 60 us instead of 69 on 25216 x 3072 fp16, but the GEMM behind them
+// then finds its codes in HBM instead of the memory-side cache and loses more: 65792 x 1280 -> 5120 both together 394 -> 419.)
+template <typename T, int U>
 __global__ void __launch_bounds__(256) quantize_tensor_kernel(const T* __restrict__ X, int8_t* __restrict__ Q,
                                                               float* __restrict__ scale, const float* __restrict__ partial,
                                                               int npartial, int64_t n) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  typedef int i4 __attribute__((ext_vector_type(4)));
+  const int64_t vecs = n / VEC, stride = (int64_t)gridDim.x * 256 * U;
+  int64_t at = (int64_t)blockIdx.x * 256 * U + threadIdx.x;
+  i4 v[U];
+  auto load = [&](int64_t i) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i + 256 * u < vecs) v[u] = ((const i4*)X)[i + 256 * u];
+  };
+  load(at);
   float s;
   if (partial) {
     float amax = 0.0f;
@@ -458,18 +471,48 @@ __global__ void __launch_bounds__(256) quantize_tensor_kernel(const T* __restric
     s = scale[0];
   }
   const float rs = scale_reciprocal(s);
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x * 8;
-  for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 8; i < n; i += stride) {
-    if (i + 8 <= n) {
-      float v[8];
-      load8(X + i, v);
-      unsigned lo, hi;
-      quantize_bytes8(v, s, rs, lo, hi);  // the same codes as quantize_codes with about half the arithmetic
-      *(uint2*)(Q + i) = uint2{lo, hi};
+  Fp16Quantiser qz;
+  if constexpr (VEC == 8) {
+    __shared__ int inexact[4];
+    const bool bad = __builtin_amdgcn_ballot_w64(qz.prepare(s, threadIdx.x)) != 0;
+    if ((threadIdx.x & 63) == 0) inexact[threadIdx.x >> 6] = bad;
+    __syncthreads();
+    qz.refine = __builtin_amdgcn_readfirstlane(inexact[0] | inexact[1] | inexact[2] | inexact[3]) != 0;
+  }
+  while (at < vecs) {
+    unsigned q[U][2];
+    if constexpr (VEC == 8) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (partial)  // uniform
+          qz.codes<false>(v[u], q[u][0], q[u][1]);
+        else
+          qz.codes<true>(v[u], q[u][0], q[u][1]);
+      }
     } else {
-      for (int64_t j = i; j < n; ++j) Q[j] = (int8_t)quantize_code(load_as_f32(X, j), s, rs);
+#pragma unroll
+      for (int u = 0; u < U; u += 2) {
+        const float4 a = __builtin_bit_cast(float4, v[u]), b = __builtin_bit_cast(float4, v[u + 1]);
+        const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        quantize_bytes8(x, s, rs, q[u][0], q[u + 1][0]);
+      }
+    }
+    const int64_t here = at;
+    at += stride;
+    if (at < vecs) load(at);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = here + 256 * u;
+      if (i < vecs) {
+        if constexpr (VEC == 8)
+          ((uint2*)Q)[i] = uint2{q[u][0], q[u][1]};
+        else
+          ((uint32_t*)Q)[i] = q[u][0];
+      }
     }
   }
+  if (blockIdx.x == 0 && vecs * VEC + threadIdx.x < n)
+    Q[vecs * VEC + threadIdx.x] = (int8_t)quantize_code(load_as_f32(X, vecs * VEC + threadIdx.x), s, rs);
 }
 
 template <typename T>
@@ -492,7 +535,7 @@ static gpusq_status quantize_typed(const T* X, int8_t* Xq, float* scale, int mod
     return launch_quantize_rows(X, Xq, scale, scale_is_input, rows, cols, 127.0f, s);
   }
   const int64_t n = rows * cols;
-  const int64_t want = ceil_div(n, 256 * 8 * 2);  // two 8-element vectors per thread ...
+  const int64_t want = ceil_div(n * (int64_t)sizeof(T), 16 * 256 * 2);  // two 16-byte vectors per thread ...
   // ... up to 2048 workgroups (every workgroup of the quantising pass first reduces the partial maxima: with 8192 of them the
   // pass took 1.5 us longer on 12608 x 768 activations, with 1024 or fewer the large tensors slow down)
   const unsigned blocks_q = (unsigned)(want < 2048 ? want : 2048);
@@ -502,7 +545,12 @@ static gpusq_status quantize_typed(const T* X, int8_t* Xq, float* scale, int mod
     blocks_a = launch_amax_typed<T>(X, n, (float*)workspace, s);
     partial = (const float*)workspace;
   }
-  quantize_tensor_kernel<T><<<blocks_q, 256, 0, s>>>(X, Xq, scale, partial, (int)blocks_a, n);
+  // (large tensors take 4 vectors in flight: 25216 x 3072 fp32, both passes, 131 -> 123 us; 12608 x 768 fp16 would lose half a
+  // microsecond of 12)
+  if (n * (int64_t)sizeof(T) > ((int64_t)48 << 20))
+    quantize_tensor_kernel<T, 4><<<blocks_q, 256, 0, s>>>(X, Xq, scale, partial, blocks_a, n);
+  else
+    quantize_tensor_kernel<T, 2><<<blocks_q, 256, 0, s>>>(X, Xq, scale, partial, blocks_a, n);
   return check_launch();
 }
 
