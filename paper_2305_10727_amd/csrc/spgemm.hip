@@ -14,11 +14,9 @@
 //   B (8 VGPRs): lane l, byte i -> column l%16, K index 64*(i/16) + 16*(l/16) + i%16 (two half-K operands back to back);
 //   D (4 VGPRs): lane l, register r -> row 4*(l/16)+r, column l%16.
 //
-// Two kernels:
-//   spgemm_tile_kernel  tiles of 256 channels x up to 256 rows, operands brought into a three-stage LDS ring by direct
-//                       global->LDS copies (no staging registers), one persistent workgroup of 8 wavefronts per CU.
-//                       Needs K*elemsize % 128 == 0.
-//   spgemm_small_kernel 64 x 64 / 128 x 128 tiles through registers; any K % 16 == 0; used for small or ragged-K problems.
+// Here: spgemm_small_kernel (64 x 64 / 128 x 128 tiles through registers; any K % 16 == 0; used for small or ragged-K problems)
+// and the choice between it, the kernel for few rows (fewrows.hip) and the two tile kernels (tile1.h, tile2.hip), which bring
+// operands into an LDS ring by direct global->LDS copies and need K * element size % 128 == 0.
 #include <atomic>
 #include <cstdlib>
 #include <type_traits>
@@ -76,408 +74,6 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs& a, const typename 
       if (m < a.M) store_8<IS_I8, OUT>(a, m, n, v, raw);
     }
   }
-}
-
-// ------------------------------------------------------------------------------------------------ tile kernel
-// One persistent workgroup of 8 wavefronts per CU on tiles of 256 channels x 64*tm rows (tm <= 4): 2 wavefronts along n x
-// 4 along m, 128 channels x 16*tm rows and 128 accumulator registers each.  All wavefronts run the K loop of a tile,
-// then all run its epilogue.  With two wavefronts per SIMD in the same phase, a SIMD always has a second wavefront to
-// issue from while one waits (for LDS data in the K loop, for a free issue slot in the epilogue: a lone wavefront issues
-// a vector instruction only every 6-8 clocks), and the weight tile is brought into the CU once per 256 rows: 52 KB per K
-// step through the vector-memory path, which at 48-64 bytes per clock and CU is the narrowest pipe of the K loop.
-//
-// LDS: a ring of three stages (X slab 32 KB, kept values 16 KB, index words 4/2 KB).  K steps are numbered g = 0, 1, ...
-// over the workgroup's whole sequence of tiles; step g lives in stage g % 3.  One workgroup barrier per K step, in front
-// of fragment kBarrierFrag: by then a wavefront has issued, and waits for, the last LDS read of the step's stage, and
-// it waits for its own copies of step g+1 (the vector-memory counter retires in order, so "at most the copies of step
-// g+2 outstanding" means step g+1 has landed).  Behind the barrier stage g+1 is complete and is read ahead (the head of
-// the next step: its B operand, its first three A fragments, half of its index words), and stage g is free: the copies
-// of step g+3 are requested there, two whole steps before they are needed, also across tile boundaries (the next
-// tile's first steps land during the epilogue).  Every wavefront executes exactly one barrier per step of every tile
-// of the workgroup, plus one at start-up.
-constexpr int kTileTM = 4, kTileWM = 4, kRing = 3;
-static_assert(kTileWM * 16 == kTileUnitRows, "tile heights are multiples of one slab per wavefront");
-constexpr int kXSlabBytes = kTileWM * kTileTM * 16 * kStepBytes;  // 32 KB: 256 rows x 128 bytes, 16-byte chunks XOR-swizzled per row
-constexpr int kBarrierFrag = 5;
-constexpr int kCopies = 7;  // copy instructions per wavefront and K step: 4 X blocks, 2 fragments, 1 KB of index words
-
-// s_waitcnt immediates (gfx9 encoding: vmcnt [3:0] and [15:14], expcnt [6:4], lgkmcnt [11:8]), all with lgkmcnt(0)
-constexpr int kWaitVm0 = 0x0070;    // vmcnt(0)
-constexpr int kWaitVm7 = 0x0077;    // vmcnt(kCopies)
-constexpr int kWaitVm14 = 0x007E;   // vmcnt(2 * kCopies)
-constexpr int kWaitVm15 = 0x007F;   // vmcnt(kCopies + 8)
-constexpr int kWaitVm23 = 0x4077;   // vmcnt(kCopies + 16)
-static_assert(kCopies == 7, "the wait immediates encode 7, 14, 7 + 8 and 7 + 16");
-static_assert(kBarrierFrag + 3 == kTileTN, "slot plan of tile_step");
-
-// Copy I (0..6) of one wavefront's share (an eighth) of the copies that bring one K step of a tile into an LDS stage:
-// I = 0..3 are 1 KB blocks of the X slab (block j = wave + 8I holds rows 8j..8j+7), I = 4, 5 fragments of kept values,
-// I = 6 1 KB of index words.  Each copy moves 64 lanes x 16 bytes from a wavefront-uniform 64-bit base in scalar
-// registers plus a 32-bit per-lane offset that is fixed for the whole tile, to 1 KB of consecutive LDS at a scalar
-// base plus a constant: per copy the K loop spends one scalar instruction and one wait state besides the copy itself
-// (the K loop is bound by instruction issue, scalar instructions and branches first of all).
-//   lds_wave = LDS address of the stage + wave * 1024, lds_idx = that of the index block this wavefront copies;
-//   Xks = the X rows of the tile at this K step, Wwave = the packed tile of this K step + wave * 1024;
-//   loff = lane * 16, loff8k = loff + 8192, ioff = loff + the index block's offset relative to Wwave.
-// Always exactly kCopies instructions per step, whatever the tile (a short tile copies rows it does not use; there are
-// only 4 KB / 2 KB of index words, so some wavefronts repeat a block), so that the waits can count instructions.
-template <int I>
-__device__ __forceinline__ void issue_step_copy(uint32_t lds_wave, uint32_t lds_idx, const uint8_t* Xks, const uint8_t* Wwave,
-                                                const uint32_t (&xoff)[4], uint32_t loff, uint32_t loff8k, uint32_t ioff) {
-  if constexpr (I < 4)
-    copy16_to_lds_at<8192 * I>(Xks, xoff[I < 4 ? I : 0], lds_wave);
-  else if constexpr (I == 4)
-    copy16_to_lds_at<kXSlabBytes>(Wwave, loff, lds_wave);
-  else if constexpr (I == 5)
-    copy16_to_lds_at<kXSlabBytes + 8192>(Wwave, loff8k, lds_wave);
-  else
-    copy16_to_lds_at<0>(Wwave, ioff, lds_idx);
-}
-
-// Per-lane byte offsets, relative to the tile's first row, of the four X blocks a wavefront copies per K step: lane l
-// fetches row 8j + l/8 of block j, chunk (l%8) ^ ((row >> 1) & 7).  The X slab is stored row-major with the 16-byte
-// chunk c of row r at chunk position c ^ ((r >> 1) & 7), so that the 16 rows a quarter-wavefront reads at the same K
-// offset fall in 16 different 16-byte bank groups; the swizzle is applied by choosing which global chunk each lane
-// fetches.  Rows past the end of X, and rows past the end of a tile shorter than 256 rows (`rows` = its height), re-read
-// the last row they may: their results are never stored, and a short tile then draws no rows from memory that it does
-// not use (the number of copies stays the same, the waits count them).
-__device__ __forceinline__ void tile_x_offsets(uint32_t (&xoff)[4], int64_t m0, int M, int rows, int64_t k_bytes, int wave, int lane) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int r = 8 * (wave + i * 8) + (lane >> 3);
-    const int c = (lane & 7) ^ ((r >> 1) & 7);
-    int64_t last = (int64_t)M - 1 - m0;  // >= 0: a tile starts inside X
-    last = last < rows - 1 ? last : rows - 1;
-    const int64_t rr = r < last ? r : last;
-    xoff[i] = (uint32_t)(rr * k_bytes + c * 16);
-  }
-}
-
-// The same for the patch-embedding mode with P = 16 (see patch_chunk_offset).
-template <bool IS_I8>
-__device__ __forceinline__ void patch_x_offsets(uint32_t (&xoff)[4], int64_t m0, const GemmArgs& a, int wave, int lane) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int r = 8 * (wave + i * 8) + (lane >> 3);
-    const int ch = (lane & 7) ^ ((r >> 1) & 7);  // logical chunk of the step this lane fetches (see tile_x_offsets)
-    const uint32_t m = (uint32_t)m0 + (uint32_t)r;
-    xoff[i] = patch_chunk_offset<IS_I8>(a, m < (uint32_t)a.M ? m : (uint32_t)a.M - 1u, ch);  // rows past the end re-read the last row
-  }
-}
-
-// Per-lane byte offsets of the B operand inside an X slab: lane l reads row wm*16*tm + 16*mt + l%16, the 16-byte
-// chunks l/16 and 4 + l/16 of it (at their swizzled positions).
-struct BOffsets {
-  uint32_t lo, hi;
-};
-__device__ __forceinline__ BOffsets b_offsets(int wm, int tm, int lane) {
-  const int sw = (lane & 15) >> 1, q = lane >> 4;
-  const uint32_t row = (uint32_t)(wm * tm * 16 + (lane & 15)) * kStepBytes;
-  return BOffsets{row + (uint32_t)((q ^ sw) * 16), row + (uint32_t)(((4 + q) ^ sw) * 16)};
-}
-
-// What a wavefront holds in registers when a K step begins: the four B slabs of the step, its A fragments 0..2
-// (fragment f lives in av[f % 4]) and the index words of fragments 0..3; read from the stage whose X slab is at `xslab`
-// and whose weight tile is at `wtile`.
-template <bool IS_I8>
-__device__ __forceinline__ void load_step_head(v8i (&b)[kTileTM], v4i (&av)[4], int (&ai)[kTileTN], const uint8_t* xslab,
-                                               const uint8_t* wtile, const BOffsets& bo, uint32_t a_off, uint32_t i_off) {
-#pragma unroll
-  for (int mt = 0; mt < kTileTM; ++mt) {
-    const v4i lo = *(const v4i*)(xslab + bo.lo + mt * 16 * kStepBytes), hi = *(const v4i*)(xslab + bo.hi + mt * 16 * kStepBytes);
-    b[mt] = v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-  }
-  load_index_half<IS_I8>(ai, 0, wtile + i_off);
-#pragma unroll
-  for (int f = 0; f < 3; ++f) av[f] = *(const v4i*)(wtile + a_off + f * kFragValueBytes);
-}
-
-// One K step of a wavefront (128 n x 64 m), software-pipelined by hand across steps.  When the step begins its B
-// operand `b`, its A fragments 0..2 and the index words of fragments 0..3 are in registers.  Per fragment the step
-// issues the LDS read of the fragment three ahead, then the four matrix instructions of the fragment; in front of
-// fragment kBarrierFrag the wait and the barrier (see the kernel); behind it, one per matrix instruction, the reads
-// of the next step's head from `next` into `bn`, `av`, `ai` and the wavefront's kCopies copy requests.  So every other
-// instruction is issued in the shadow of a matrix instruction.
-// The step has no conditional parts: what the K loop can sustain is set by the instructions a wavefront must issue per
-// step (measured: a compare-and-branch pair between two matrix instructions costs more than the matrix instruction), so
-// the last step of a tile reads ahead like any other (the next tile reloads those registers) and the steps at the end of
-// a workgroup's sequence request copies like any other (the cursor then stays on the last step: they land in a free
-// stage and are never read).
-// wait_mode (wavefront-uniform): what may stay outstanding at the barrier besides one step of copies: 1 = nothing,
-// 2 = 16 output stores, 3 = 8 output stores; 0 = nothing at all may stay outstanding.
-// behind_barrier(): called once, right behind the barrier and before the step's copy requests.
-template <bool IS_I8, int TMA, class Hook>
-__device__ __forceinline__ void tile_step(int wait_mode, const uint8_t* stage, const uint8_t* next, const BOffsets& bo,
-                                          typename AccT<IS_I8>::type (&acc)[kTileTN][kTileTM], const v8i (&b)[kTileTM],
-                                          v8i (&bn)[kTileTM], v4i (&av)[4], int (&ai)[kTileTN], uint32_t a_off, uint32_t i_off,
-                                          uint32_t req_lds_wave, uint32_t req_lds_idx, const uint8_t* req_x, const uint8_t* req_w,
-                                          const uint32_t (&xoff)[4], uint32_t loff, uint32_t loff8k, uint32_t ioff,
-                                          Hook&& behind_barrier) {
-  const uint8_t* abase = stage + kXSlabBytes + a_off;
-  const uint8_t* ibase = stage + kXSlabBytes + i_off;
-  const uint8_t* abase_n = next + kXSlabBytes + a_off;
-  const uint8_t* ibase_n = next + kXSlabBytes + i_off;
-  constexpr int kSlots = (kTileTN - kBarrierFrag) * TMA;  // matrix instructions behind the barrier
-  static_assert(kSlots >= 2 * TMA + 1, "slot plan of tile_step");
-#pragma unroll
-  for (int tn = 0; tn < kTileTN; ++tn) {
-#pragma unroll
-    for (int mt = 0; mt < TMA; ++mt) {
-      if (tn == kBarrierFrag && mt == 0) {
-        __builtin_amdgcn_sched_barrier(0);  // the compiler must not move the wait above the matrix instructions before it
-        if (wait_mode == 1)
-          __builtin_amdgcn_s_waitcnt(kWaitVm7);
-        else if (wait_mode == 2)
-          __builtin_amdgcn_s_waitcnt(kWaitVm23);
-        else if (wait_mode == 3)
-          __builtin_amdgcn_s_waitcnt(kWaitVm15);
-        else
-          __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");  // no LDS read moves above the barrier
-        behind_barrier();
-      }
-      if (mt == 0) {
-        const int f = tn + 3;  // f >= kTileTN exactly when tn >= kBarrierFrag: the next stage, behind the barrier
-        if (f < kTileTN)
-          av[f & 3] = *(const v4i*)(abase + f * kFragValueBytes);
-        else
-          av[f & 3] = *(const v4i*)(abase_n + (f - kTileTN) * kFragValueBytes);
-      }
-      if (tn == 0 && mt == (TMA > 2 ? 2 : TMA - 1)) load_index_half<IS_I8>(ai, 1, ibase);
-      if (tn >= kBarrierFrag) {
-        const int slot = (tn - kBarrierFrag) * TMA + mt;  // 0..kSlots-1
-        if (slot < 2 * TMA) {
-          const v4i piece = *(const v4i*)(next + ((slot & 1) ? bo.hi : bo.lo) + (slot >> 1) * 16 * kStepBytes);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) bn[slot >> 1][4 * (slot & 1) + j] = piece[j];
-        }
-        if (slot == 2 * TMA) load_index_half<IS_I8>(ai, 0, ibase_n);
-        // copy c goes out in slot c (12 slots) or is spread evenly over fewer slots
-        auto at = [&](int c) { return slot == (kSlots >= kCopies ? c : c * kSlots / kCopies); };
-        if (at(0)) issue_step_copy<0>(req_lds_wave, req_lds_idx, req_x, req_w, xoff, loff, loff8k, ioff);
-        if (at(1)) issue_step_copy<1>(req_lds_wave, req_lds_idx, req_x, req_w, xoff, loff, loff8k, ioff);
-        if (at(2)) issue_step_copy<2>(req_lds_wave, req_lds_idx, req_x, req_w, xoff, loff, loff8k, ioff);
-        if (at(3)) issue_step_copy<3>(req_lds_wave, req_lds_idx, req_x, req_w, xoff, loff, loff8k, ioff);
-        if (at(4)) issue_step_copy<4>(req_lds_wave, req_lds_idx, req_x, req_w, xoff, loff, loff8k, ioff);
-        if (at(5)) issue_step_copy<5>(req_lds_wave, req_lds_idx, req_x, req_w, xoff, loff, loff8k, ioff);
-        if (at(6)) issue_step_copy<6>(req_lds_wave, req_lds_idx, req_x, req_w, xoff, loff, loff8k, ioff);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      acc[tn][mt] = smfmac<IS_I8>(av[tn & 3], b[mt], acc[tn][mt], ai[tn]);
-    }
-  }
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// PATCH: the X operand is gathered from an image batch (patch embedding with P = 16, see patch_x_offsets).
-template <bool IS_I8, int GELU, int OUT, bool PATCH = false>
-__global__ void __launch_bounds__(512, 1) spgemm_tile_kernel(const GemmArgs a, const TilePlan plan) {
-  typedef typename AccT<IS_I8>::type acc_t;
-  constexpr int ES = IS_I8 ? 1 : 2;
-  constexpr int STAGE = kXSlabBytes + tile_bytes(IS_I8);
-  constexpr bool RAW = IS_I8 && OUT == GPUSQ_I32;
-  __shared__ __attribute__((aligned(1024))) uint8_t ring[kRing * STAGE];
-  // per tile parity and 128-channel half: 128 weight scales, 128 biases (with the int8 ring: 160 KB in all, the CU's LDS)
-  __shared__ __attribute__((aligned(1024))) float prm[2][2][256];
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wn = wave & 1, wm = wave >> 1;
-  const int64_t k_bytes = (int64_t)a.K * ES;
-  const int ksteps = (int)(k_bytes / kStepBytes);
-  const uint8_t* Xg = (const uint8_t*)a.X;
-  const uint8_t* Wg = (const uint8_t*)a.W;
-  const int64_t w_col_bytes = (int64_t)ksteps * tile_bytes(IS_I8);
-  const int xcd = (int)(blockIdx.x & 7), wgs_per_xcd = (int)(gridDim.x >> 3), wl = (int)(blockIdx.x >> 3);
-  int f0, nf, t0;
-  const int items = xcd_items(plan, xcd, f0, nf, t0);
-  const int my_items = wl < items ? (items - wl + wgs_per_xcd - 1) / wgs_per_xcd : 0;
-  if (my_items == 0) return;  // the whole workgroup leaves before any barrier
-  auto tile_of = [&](int i) {
-    const int it = wl + i * wgs_per_xcd;
-    return decode_tile(plan, it < nf ? f0 + it : t0 + it - nf);
-  };
-  const bool has_bias = !RAW && (a.epilogue & GPUSQ_EPI_BIAS) != 0;
-  const float s_a = (IS_I8 && !RAW) ? a.act_scale[0] : 1.0f;
-  const float s_out = OUT == GPUSQ_I8 ? a.out_scale[0] : 1.0f, r_out = scale_reciprocal(s_out);  // read once: a load in the epilogue would wait for the copies in flight
-  if (!has_bias && wm == 0) {  // the bias halves stay zero for the whole launch (visible after the first barrier)
-#pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      prm[par][wn][128 + lane] = 0.0f;
-      prm[par][wn][192 + lane] = 0.0f;
-    }
-  }
-  const uint32_t ring_lds = lds_address(ring), prm_lds = lds_address(prm[0][wn]);
-  // The 128 channels [n0, n0 + 128) of epilogue constants of this wavefront's half of a tile, into the constants array
-  // of the given parity; requested by the first wavefront of the half.  n0 < 0: nothing (there is no such tile).
-  auto request_constants = [&](int n0, int parity) {
-    if constexpr (!RAW) {
-      if (wm == 0 && n0 >= 0) {
-        const uint32_t dst = prm_lds + (uint32_t)parity * (uint32_t)sizeof(prm[0]);
-        int lane_now = lane;
-        asm volatile("" : "+v"(lane_now));  // computed here, per tile: nothing lane-dependent is carried (or spilled) across the K loop
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          int n = n0 + i * 64 + lane_now;
-          n = n < a.N ? n : a.N - 1;  // channels past the end are never stored
-          if constexpr (IS_I8) copy4_to_lds(a.w_scale, (uint32_t)n * 4u, dst + (uint32_t)i * 256u);
-          if (has_bias) copy4_to_lds(a.bias, (uint32_t)n * 4u, dst + 512u + (uint32_t)i * 256u);
-        }
-      }
-    }
-  };
-  const uint32_t loff = (uint32_t)lane * 16u;
-  const uint32_t a_off = (uint32_t)(wn * kTileTN * kFragValueBytes + lane * 16);
-  const uint32_t i_off = (uint32_t)index_offset(IS_I8, wn * kTileTN, lane);
-
-  // lane offsets of the copies of kept values and index words, relative to the packed tile of a K step + wave * 1024
-  const uint32_t loff8k = loff + 8192u;
-  const int idx_block = IS_I8 ? (wave & 3) : (wave & 1);  // the 1 KB of index words this wavefront copies
-  const uint32_t ioff = loff + (uint32_t)(kTileValueBytes + idx_block * 1024 - wave * 1024);
-  const uint32_t wave_lds = (uint32_t)wave * 1024u, idx_lds = (uint32_t)(kXSlabBytes + kTileValueBytes + idx_block * 1024);
-
-  // Cursor of the copy requests: the next K step to request, as (tile, step), with its source addresses (pf_w includes
-  // wave * 1024).  At the end of the workgroup's sequence it stays on the last step: the requests go on (the waits
-  // count a fixed number of copies per step) and re-fetch that step into a stage that nothing reads any more.
-  int pf_item = 0, pf_ks = 0;
-  const uint8_t *pf_x = Xg, *pf_w = Wg;
-  uint32_t pf_xoff[4] = {0, 0, 0, 0};
-  auto seek = [&](int item) {
-    pf_item = item;
-    pf_ks = 0;
-    const Tile t = tile_of(item);
-    int lane_now = lane;
-    asm volatile("" : "+v"(lane_now));  // (computed here, per tile)
-    if constexpr (PATCH) {
-      patch_x_offsets<IS_I8>(pf_xoff, t.m0, a, wave, lane_now);
-      pf_x = Xg;
-    } else {
-      tile_x_offsets(pf_xoff, t.m0, a.M, kTileUnitRows * t.tm, k_bytes, wave, lane_now);
-      pf_x = Xg + t.m0 * k_bytes;
-    }
-    pf_w = Wg + t.n_blk * w_col_bytes + wave_lds;
-  };
-  auto advance = [&]() {
-    if (pf_ks + 1 < ksteps) {
-      ++pf_ks;
-      if constexpr (PATCH)
-        pf_x = Xg + patch_step_offset<IS_I8>(a, pf_ks);
-      else
-        pf_x += kStepBytes;
-      pf_w += tile_bytes(IS_I8);
-    } else if (pf_item + 1 < my_items) {
-      seek(pf_item + 1);
-    }
-  };
-  auto request_step = [&](uint32_t stage_lds) {
-    issue_step_copy<0>(stage_lds + wave_lds, stage_lds + idx_lds, pf_x, pf_w, pf_xoff, loff, loff8k, ioff);
-    issue_step_copy<1>(stage_lds + wave_lds, stage_lds + idx_lds, pf_x, pf_w, pf_xoff, loff, loff8k, ioff);
-    issue_step_copy<2>(stage_lds + wave_lds, stage_lds + idx_lds, pf_x, pf_w, pf_xoff, loff, loff8k, ioff);
-    issue_step_copy<3>(stage_lds + wave_lds, stage_lds + idx_lds, pf_x, pf_w, pf_xoff, loff, loff8k, ioff);
-    issue_step_copy<4>(stage_lds + wave_lds, stage_lds + idx_lds, pf_x, pf_w, pf_xoff, loff, loff8k, ioff);
-    issue_step_copy<5>(stage_lds + wave_lds, stage_lds + idx_lds, pf_x, pf_w, pf_xoff, loff, loff8k, ioff);
-    issue_step_copy<6>(stage_lds + wave_lds, stage_lds + idx_lds, pf_x, pf_w, pf_xoff, loff, loff8k, ioff);
-  };
-
-  acc_t acc[kTileTN][kTileTM];
-  v8i b0[kTileTM], b1[kTileTM];  // B operands of the current and the next K step (roles alternate)
-  v4i av[4];                     // A fragments in flight
-  int ai[kTileTN];               // index words
-
-  // the constants of the first tile, then the first three K steps of the sequence
-  request_constants(tile_of(0).n_blk * kTileBN + wn * (kTileTN * 16), 0);
-  seek(0);
-  for (int g = 0; g < kRing; ++g) {
-    request_step(ring_lds + (uint32_t)g * STAGE);
-    advance();
-  }
-  __builtin_amdgcn_s_waitcnt(kWaitVm14);  // the constants and step 0 have landed
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-
-  int slot_off = 0;        // byte offset of the current K step's ring stage
-  int first2_mode = 1;     // wait mode of a tile's first two steps (output stores of the previous tile still in the queue)
-  for (int item = 0; item < my_items; ++item) {
-    const Tile t = tile_of(item);
-    int lane_now = lane;
-    asm volatile("" : "+v"(lane_now));  // the offsets are computed here, per tile, not once per kernel and kept (or spilled)
-    const BOffsets bo = b_offsets(wm, t.tm, lane_now);
-    const int next_n0 = item + 1 < my_items ? tile_of(item + 1).n_blk * kTileBN + wn * (kTileTN * 16) : -1;
-#pragma unroll
-    for (int i = 0; i < kTileTN; ++i)
-#pragma unroll
-      for (int j = 0; j < kTileTM; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
-    // the stage of the tile's first step has landed: start-up barrier, or the barrier in the previous tile's last step
-    load_step_head<IS_I8>(b0, av, ai, ring + slot_off, ring + slot_off + kXSlabBytes, bo, a_off, i_off);
-    auto step = [&](auto tma, int ks, const v8i (&b)[kTileTM], v8i (&bn)[kTileTM]) {
-      const int next_off = slot_off + STAGE == kRing * STAGE ? 0 : slot_off + STAGE;
-      // Outstanding at the barrier of step g, oldest first: the copies of step g+1, then those of step g+2, which may
-      // stay in flight.  In the first two steps of a tile the output stores of the previous tile's epilogue sit in the
-      // queue behind the copies waited for, so they may stay in flight too: the stores drain to memory while the K loop
-      // goes on.  The third barrier of a tile then waits for copies that were requested after those stores.  (Only two
-      // counts are exploited, the 16 and 8 stores of a wavefront whose 128 x 64 outputs all lie inside Y; any other
-      // count waits for the stores as well, which is only stricter.)
-      const int wait_mode = ks < 2 ? first2_mode : 1;
-      tile_step<IS_I8, decltype(tma)::value>(wait_mode, ring + slot_off, ring + next_off, bo, acc, b, bn, av, ai, a_off, i_off,
-                       ring_lds + (uint32_t)slot_off + wave_lds, ring_lds + (uint32_t)slot_off + idx_lds, pf_x, pf_w, pf_xoff, loff,
-                       loff8k, ioff, [&]() {
-                         // The next tile's constants go into the other constants array, which was last read in the
-                         // previous tile's epilogue (every wavefront has left it: it passed this tile's barriers).  They
-                         // are older than this step's copy requests and than this tile's output stores, so the wait in
-                         // front of the next tile's first barrier covers them and that barrier publishes them.
-                         if (ks + 1 == ksteps) request_constants(next_n0, (item + 1) & 1);
-                       });
-      advance();
-      slot_off = next_off;
-    };
-    // A tile of fewer than 4 slabs per wavefront runs a K loop with the matrix instructions of its own slabs only (the
-    // other accumulators stay zero and are never stored); the copies stay the same, so that the waits count the same
-    // in every tile.
-    auto k_loop = [&](auto tma) {
-      for (int ks = 0; ks < ksteps; ks += 2) {
-        step(tma, ks, b0, b1);
-        if (ks + 1 < ksteps) step(tma, ks + 1, b1, b0);
-      }
-    };
-    if (t.tm == 4)
-      k_loop(std::integral_constant<int, 4>{});
-    else if (t.tm == 3)
-      k_loop(std::integral_constant<int, 3>{});
-    else if (t.tm == 2)
-      k_loop(std::integral_constant<int, 2>{});
-    else
-      k_loop(std::integral_constant<int, 1>{});
-    const int n_wave = t.n_blk * kTileBN + wn * (kTileTN * 16);
-    const int64_t m_wave = t.m0 + wm * t.tm * 16;
-    const int64_t rows = (int64_t)a.M - m_wave;
-    const int chans = a.N - n_wave;
-    // The epilogue, and the number of store instructions this wavefront issues in it (a count that is too high would let
-    // the next tile's copies go unwaited, one that is too low only waits for stores as well).
-    int stores_pending;
-    const bool lines = OUT == GPUSQ_F16 ? (a.N & 7) == 0 : (OUT == GPUSQ_I8 ? (a.N & 15) == 0 : true);
-    if (lines) {
-      if (t.tm == kTileTM && rows >= kTileTM * 16 && chans >= kTileTN * 16)
-        line_epilogue<IS_I8, GELU, OUT, false, kTileTM>(a, acc, prm[item & 1][wn], s_a, s_out, r_out, n_wave, m_wave, lane, kTileTM);
-      else
-        line_epilogue<IS_I8, GELU, OUT, true, kTileTM>(a, acc, prm[item & 1][wn], s_a, s_out, r_out, n_wave, m_wave, lane, t.tm);
-      // per line of the wavefront's 128 channels with a channel inside N (fp16: 64 channels, int32: 32, int8: all 128):
-      // one store per slab with a row inside M among its first 8 rows and one for its last 8 rows
-      int n = 0;
-      for (int mt = 0; mt < t.tm; ++mt) n += (16 * mt < rows) + (16 * mt + 8 < rows);
-      const int per_line = OUT == GPUSQ_F16 ? kRowBlock : (OUT == GPUSQ_I8 ? 128 : 32);
-      stores_pending = n * (chans <= 0 ? 0 : (chans >= 128 ? 128 / per_line : (chans + per_line - 1) / per_line));
-    } else {
-      batch_epilogue<IS_I8, GELU, OUT, kTileTM>(a, acc, prm[item & 1][wn], s_a, n_wave, m_wave, lane, t.tm);
-      // one (two for 2 x 16 bytes of int32) per batch of 32 channels x 16 rows with a row inside M and a channel inside N;
-      // with N % 8 != 0 the number depends on the lanes and is not used
-      const int mts = rows <= 0 ? 0 : (rows >= t.tm * 16 ? t.tm : (int)((rows + 15) >> 4));
-      const int gs = chans <= 0 ? 0 : (chans >= 128 ? 4 : (chans + 31) >> 5);
-      stores_pending = (a.N & 7) ? 0 : mts * gs * (OUT == GPUSQ_I32 ? 2 : 1);
-    }
-    first2_mode = stores_pending >= 16 ? 2 : (stores_pending >= 8 ? 3 : 1);
-  }
-  __builtin_amdgcn_s_waitcnt(kWaitVm0);  // the copies requested past the end of the sequence land before the LDS is given up
 }
 
 // ------------------------------------------------------------------------------------------------ small / generic kernel
@@ -776,7 +372,10 @@ static double plan_makespan(const TilePlan& p, int grid, int ksteps, bool gelu, 
 
 static int grid_for(const TilePlan& p, int resident) { return (int)ceil_div(p.total < resident ? p.total : resident, 8) * 8; }
 
-// Candidates: full tiles of 64, 128, 192 or 256 rows, either over all of M, or for as many whole rounds over the resident
+constexpr int kTileTM = 4;  // 64-row units of the highest tile
+
+// The plan in units of 64 rows by which the kernel is chosen (even_plan is what runs).  Candidates: full tiles of 64, 128, 192 or 256
+// rows, either over all of M, or for as many whole rounds over the resident
 // workgroups as the problem has with the remaining rows in tail tiles of 64..64*full_tm rows; the one whose busiest
 // workgroup finishes first wins.
 static TilePlan make_plan(int M, int N, int resident, int ksteps, bool gelu) {
@@ -808,6 +407,59 @@ static TilePlan make_plan(int M, int N, int resident, int ksteps, bool gelu) {
       for (int ttm = ftm; ttm >= 1; --ttm) consider(ftm, full_chunks, ttm);
     }
   }
+  return best;
+}
+
+// The plan the tile kernel with one workgroup per CU runs (tile1.h).  For each number of rounds over the CUs from the fewest
+// (tiles of at most 8 units of 32 rows) on: as many chunks as fill them.  Where the rows are a few more than whole rounds of the
+// highest tiles: those, and the rest in tail chunks.  The shortest estimate wins (microseconds, fitted to timings of every plan of
+// sixteen layers' sizes on MI355X): a K step of u units takes 0.24 + 0.113 u and no less than 0.41, so rows spread over more
+// rounds cost 0.24 per K step and round.  A tail tile's K steps are those of a lone workgroup, and part of its time vanishes
+// in the 5 % by which the workgroups' ends differ anyway (65792 x 5120 -> 1280: 6 even rounds 291 us, 5 and a tail 269).
+static EvenPlan even_plan(int64_t M, int64_t N, int resident, int ksteps, bool gelu) {
+  constexpr int kTallest = 8, kTail = 6;  // (a tail tile is one that the loop for tiles of 7 and 8 units can run)
+  const int tiles_n = (int)ceil_div(N, kTileBN);
+  const int64_t units = ceil_div(M, 32);
+  const double epi_unit = gelu ? 0.5 : 0.3;
+  auto round_cost = [&](double u) {
+    const double step = 0.24 + 0.113 * u;
+    return ksteps * (step > 0.41 ? step : 0.41) + 0.3 + epi_unit * u;
+  };
+  EvenPlan best{};
+  double best_cost = -1;
+  auto consider = [&](int64_t main_units, int64_t chunks, int64_t tail_units, double cost) {
+    if (best_cost >= 0 && cost >= best_cost) return;
+    best_cost = cost;
+    best.tiles_n = tiles_n;
+    best.chunks = (int)chunks;
+    best.units = (int)(main_units / chunks);
+    best.higher = (int)(main_units % chunks);
+    best.tail_units = kTail;
+    best.tail_chunks = (int)ceil_div(tail_units, kTail);
+  };
+  const int64_t least = ceil_div(ceil_div(units, kTallest) * tiles_n, resident);
+  for (int64_t rounds = least; rounds <= least + 2; ++rounds) {
+    int64_t chunks = rounds * resident / tiles_n;  // (>= units / kTallest)
+    if (chunks > units) chunks = units;
+    const int64_t r = ceil_div(chunks * tiles_n, resident);
+    // what the workgroup with the most higher tiles has
+    const int64_t most = r * (units / chunks) + ceil_div((units % chunks) * tiles_n, resident);
+    consider(units, chunks, 0, r * round_cost((double)most / r));
+  }
+  const int64_t whole = (least - 1) * resident / tiles_n;  // chunks of the highest tiles that fill the rounds but the last
+  const int64_t rest = units - whole * kTallest;
+  if (least >= 4 && whole > 0 && rest > 0 && ceil_div(rest, kTail) * tiles_n <= resident) {
+    const double all = (least - 1) * round_cost(kTallest), tail = ksteps * 0.5 + 0.3 + epi_unit * kTail - 0.05 * all;
+    consider(whole * kTallest, whole, rest, all + (tail > 0 ? tail : 0));
+  }
+  const int64_t total = even_total(best);
+  best.grid8 = (int)ceil_div(total < resident ? total : resident, 8);  // one workgroup per CU, never more workgroups than tiles
+  best.rounds = (int)(total / (8 * best.grid8));
+  best.last_round = (int)(total % (8 * best.grid8));
+  int log2 = 1;
+  while (((int64_t)1 << log2) < tiles_n) ++log2;
+  best.shift = log2 - 1;
+  best.inv = tiles_n > 1 ? (uint32_t)(((uint64_t)1 << (31 + log2)) / tiles_n + ((((uint64_t)1 << (31 + log2)) % tiles_n) != 0)) : 0u;
   return best;
 }
 
@@ -886,7 +538,8 @@ struct Decision {
   int forced;  // the forced kernel when the decision was taken, -1 for none
   int64_t M, N, K;
   int resident, choice;
-  TilePlan plan;  // valid when choice == 2
+  TilePlan plan;  // valid when choice == 3
+  EvenPlan even;  // valid when choice == 2
 };
 static const Decision& decide(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu, int resident, bool patches) {
   constexpr int kSlots = 16;
@@ -902,9 +555,9 @@ static const Decision& decide(bool is_i8, int64_t M, int64_t N, int64_t K, bool 
   Decision& d = cache[next];
   next = (next + 1) % kSlots;
   if (used < kSlots) ++used;
-  d = Decision{is_i8, gelu, patches, forced, M, N, K, resident, kernel_choice(is_i8, M, N, K, gelu, resident, patches), TilePlan{}};
+  d = Decision{is_i8, gelu, patches, forced, M, N, K, resident, kernel_choice(is_i8, M, N, K, gelu, resident, patches), TilePlan{}, EvenPlan{}};
   const int64_t k_bytes = K * (is_i8 ? 1 : 2);
-  if (d.choice == 2) d.plan = make_plan((int)M, (int)N, resident, (int)(k_bytes / kStepBytes), gelu);
+  if (d.choice == 2) d.even = even_plan(M, N, resident, (int)(k_bytes / kStepBytes), gelu);
   if (d.choice == 3) d.plan = make_tile2_plan((int)M, (int)N, 2 * resident, (int)(k_bytes / kStepBytes), gelu, false);
   return d;
 }
@@ -927,36 +580,13 @@ static gpusq_status launch_typed(const GemmArgs& a, hipStream_t s) {
   }
   if (choice == 0) return launch_small<IS_I8, 4, 1, 1, 4>(a, s);
   if (choice == 1) return launch_small<IS_I8, 4, 4, 2, 2>(a, s);
-  // persistent grid: one workgroup per CU, never more workgroups than tiles
-  const int ksteps = (int)(k_bytes / kStepBytes);
-  const TilePlan plan = dec.plan;
-  const dim3 grid((unsigned)grid_for(plan, resident));
-  if ((ceil_div(plan.total, grid.x) + 2) * ksteps >= ((int64_t)1 << 30)) return GPUSQ_ERR_UNSUPPORTED;
+  const unsigned grid = 8u * (unsigned)dec.even.grid8;  // persistent
+  if (even_total(dec.even) >= ((int64_t)1 << 31)) return GPUSQ_ERR_UNSUPPORTED;
+  if ((dec.even.rounds + 2) * (k_bytes / kStepBytes) >= ((int64_t)1 << 30)) return GPUSQ_ERR_UNSUPPORTED;
   if ((int64_t)a.N * 16 * 4 >= ((int64_t)1 << 31)) return GPUSQ_ERR_UNSUPPORTED;  // 32-bit lane offsets inside 16 rows of Y
   // 32-bit lane offsets inside the 256 rows of X of a tile (tile_x_offsets; the patch gather has its own limit)
   if (a.patch_P == 0 && 255 * k_bytes + kStepBytes >= ((int64_t)1 << 32)) return GPUSQ_ERR_UNSUPPORTED;
-  if (a.patch_P != 0) {
-    spgemm_tile_kernel<IS_I8, 0, GPUSQ_F16, true><<<grid, 512, 0, s>>>(a, plan);
-    return check_launch();
-  }
-  if constexpr (IS_I8) {
-    if (a.out_dt == GPUSQ_I32)
-      spgemm_tile_kernel<true, 0, GPUSQ_I32><<<grid, 512, 0, s>>>(a, plan);
-    else if (a.out_dt == GPUSQ_I8 && gelu)
-      spgemm_tile_kernel<true, 1, GPUSQ_I8><<<grid, 512, 0, s>>>(a, plan);
-    else if (a.out_dt == GPUSQ_I8)
-      spgemm_tile_kernel<true, 0, GPUSQ_I8><<<grid, 512, 0, s>>>(a, plan);
-    else if (gelu)
-      spgemm_tile_kernel<true, 1, GPUSQ_F16><<<grid, 512, 0, s>>>(a, plan);
-    else
-      spgemm_tile_kernel<true, 0, GPUSQ_F16><<<grid, 512, 0, s>>>(a, plan);
-  } else {
-    if (gelu)
-      spgemm_tile_kernel<false, 1, GPUSQ_F16><<<grid, 512, 0, s>>>(a, plan);
-    else
-      spgemm_tile_kernel<false, 0, GPUSQ_F16><<<grid, 512, 0, s>>>(a, plan);
-  }
-  return check_launch();
+  return IS_I8 ? launch_tile1_i8(a, dec.even, grid, s) : launch_tile1_f16(a, dec.even, grid, s);
 }
 
 // Quantise X and multiply.  Where the problem goes to the kernel for few rows, X is fp16 and its K is not too long, that

@@ -55,6 +55,39 @@ __host__ __device__ __forceinline__ int div_tiles_n(const TilePlan& p, int idx) 
 #endif
 }
 
+// The tiles of a launch of the kernel with one workgroup per CU: the rows in chunks of whole 32-row units, the first `higher` of
+// them a unit higher than the others, times the 256-channel blocks (n fastest); behind them, perhaps, tail chunks of
+// `tail_units`.  Round i takes the tiles from i * grid on, in runs of grid / 8 to an XCD, so that tiles that share an X slab
+// meet in one L2.  The higher ones all come in the first round or rounds: no workgroup meets more of them than another by more
+// than one.  (What a workgroup begins with, it executes from a cold instruction cache and scalar cache: with the higher chunks
+// spread over the XCDs, which took it sixty more instructions or another line of kernel arguments, every launch took 1.4 us
+// longer.)
+struct EvenPlan {
+  int tiles_n, chunks;
+  int units, higher;
+  int tail_chunks, tail_units;
+  uint32_t inv;  // tile / tiles_n = (tile * inv >> 32) >> shift for tiles below 2^31 (Granlund & Montgomery 1994); tiles_n = 1: unused
+  int shift;
+  int rounds, last_round;  // whole rounds of tiles; tiles behind them
+  int grid8;               // grid / 8
+};
+struct EvenTile {
+  int n_blk, slabs;  // height in slabs of 16 rows
+  int64_t m0;
+};
+__host__ __forceinline__ int even_units(const EvenPlan& p) { return p.units + (p.higher > 0); }  // of the highest tile
+__host__ __forceinline__ int64_t even_total(const EvenPlan& p) { return (int64_t)(p.chunks + p.tail_chunks) * p.tiles_n; }
+__device__ __forceinline__ EvenTile even_tile(const EvenPlan& p, int idx) {
+  const int chunk = p.tiles_n > 1 ? (int)(__umulhi((unsigned)idx, p.inv) >> p.shift) : idx;
+  const int over = chunk - p.chunks;  // >= 0: in the tail
+  EvenTile t;
+  t.n_blk = idx - chunk * p.tiles_n;
+  t.slabs = 2 * (over < 0 ? p.units + (chunk < p.higher ? 1 : 0) : p.tail_units);
+  const int main = over < 0 ? chunk : p.chunks, tail = over < 0 ? 0 : over;
+  t.m0 = (int64_t)(main * p.units + (main < p.higher ? main : p.higher) + tail * p.tail_units) * 32;  // (units of 32 rows: below 2^26)
+  return t;
+}
+
 struct Tile {
   int n_blk;
   int tm;      // 16-row slabs per wavefront (4 wavefronts along m): the tile has 64*tm rows
@@ -262,7 +295,8 @@ __device__ __forceinline__ void store_line_pair(const ep_v4i& first, const ep_v4
   if (ok2) __builtin_nontemporal_store(s2, (global_v4i*)(y + half_bytes + off));
 }
 
-template <bool IS_I8, int GELU, int OUT, bool CHECKED, int TM>
+// MT <= TM: the slabs to do (CHECKED: at most; tm_active of them).
+template <bool IS_I8, int GELU, int OUT, bool CHECKED, int TM, int MT = TM>
 __device__ __forceinline__ void line_epilogue(const GemmArgs& a, const typename AccT<IS_I8>::type (&acc)[kTileTN][TM],
                                               const float* p, float s_a, float so, float rso, int n_wave, int64_t m_wave, int lane,
                                               int tm_active) {
@@ -319,7 +353,7 @@ __device__ __forceinline__ void line_epilogue(const GemmArgs& a, const typename 
       batch_constants(2 * gp, c8[0], b8[0]);
       batch_constants(2 * gp + 1, c8[1], b8[1]);
 #pragma unroll
-      for (int mt = 0; mt < TM; ++mt) {
+      for (int mt = 0; mt < MT; ++mt) {
         if (!CHECKED || mt < tm_active) {
           ep_v4i H[2];
 #pragma unroll
@@ -344,7 +378,7 @@ __device__ __forceinline__ void line_epilogue(const GemmArgs& a, const typename 
       const int nb = (g >> 1) * kRowBlock + (g & 1) * 32 + q * 8 + up * 4;  // first of the 4 channels this lane stores
       const bool n_ok = n_wave + nb < a.N;
 #pragma unroll
-      for (int mt = 0; mt < TM; ++mt) {
+      for (int mt = 0; mt < MT; ++mt) {
         if (!CHECKED || mt < tm_active) {
           const int64_t row = m_wave + mt * 16 + (c & 7);
           store_line_pair(acc[2 * g][mt], acc[2 * g + 1][mt], ywave + mt * slab_bytes, row_off + nb * 4, half_bytes,
@@ -358,13 +392,13 @@ __device__ __forceinline__ void line_epilogue(const GemmArgs& a, const typename 
     // of lane c - 8; even q hold batches 0 (first) and 1 (second), odd q batches 2 and 3, channels 16 * (q / 2) ...
     const int piece = 4 * (q & 1) + 2 * up + (q >> 1);
     const bool n_ok = n_wave + piece * 16 < a.N;
-    unsigned d[TM][4][2];
+    unsigned d[MT][4][2];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       float c8[8], b8[8];
       batch_constants(g, c8, b8);
 #pragma unroll
-      for (int mt = 0; mt < TM; ++mt) {
+      for (int mt = 0; mt < MT; ++mt) {
         if (!CHECKED || mt < tm_active) {
           float v[8];
           batch_values(g, mt, c8, b8, v);
@@ -373,7 +407,7 @@ __device__ __forceinline__ void line_epilogue(const GemmArgs& a, const typename 
       }
     }
 #pragma unroll
-    for (int mt = 0; mt < TM; ++mt) {
+    for (int mt = 0; mt < MT; ++mt) {
       if (!CHECKED || mt < tm_active) {
         ep_v4i first, second;
 #pragma unroll
@@ -393,6 +427,10 @@ __device__ __forceinline__ void line_epilogue(const GemmArgs& a, const typename 
   }
 }
 
+
+// ---- the tile kernel with one workgroup per CU (tile1.h)
+gpusq_status launch_tile1_i8(const GemmArgs& a, const EvenPlan& plan, unsigned grid, hipStream_t s);
+gpusq_status launch_tile1_f16(const GemmArgs& a, const EvenPlan& plan, unsigned grid, hipStream_t s);
 
 // ---- the tile kernel with two resident workgroups per CU (tile2.hip), sparse and dense
 TilePlan make_tile2_plan(int M, int N, int resident, int ksteps, bool gelu, bool dense);
