@@ -598,8 +598,9 @@ constexpr int64_t kRangeHereBytes = 128 * 1024;
 
 // 1 + the launches in front of the GEMM's own; `folds`: the GEMM quantises
 static int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int resident, bool& folds) {
-  folds = dt == GPUSQ_F16 && decide(true, a.M, a.N, a.K, (a.epilogue & GPUSQ_EPI_GELU) != 0, resident, false).choice == 4 &&
-          fewrows_supports(a) && fewrows_folds_quantiser(a.M, a.N, a.K, resident);
+  // (the sizes first: a large layer is not planned for this)
+  folds = dt == GPUSQ_F16 && fewrows_folds_quantiser(a.M, a.N, a.K, resident) && fewrows_supports(a) &&
+          decide(true, a.M, a.N, a.K, (a.epilogue & GPUSQ_EPI_GELU) != 0, resident, false).choice == 4;
   if (!folds) return scale_is_input ? 2 : 3;
   return scale_is_input || (int64_t)a.M * a.K * 2 <= kRangeHereBytes ? 1 : 2;
 }
