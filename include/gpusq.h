@@ -257,14 +257,15 @@ gpusq_status gpusq_patch_embed16_fp16(const void* img, const void* Wpacked, cons
  * chunks covered by full tiles, out[5] = tail_tm (the remaining rows are cut into tiles of u * tail_tm rows), out[6] =
  * tiles in all, out[7] = workgroups launched.  Same argument checks as the GEMM calls (sizes only).
  * (The heights are those of a plan in whole units, by which the kernel is chosen; kernel 2 cuts the same rows in steps of 32
- * instead, so that its tiles fill whole rounds over the CUs.)
+ * instead, so that its tiles fill whole rounds over the CUs.  A K of no whole 128-byte steps is reported as 0 or 1, the small
+ * kernel that gpusq_spgemm_int8_xf16 runs it on, also where the GEMM calls take kernel 2.)
  * The query describes gpusq_spgemm_fp16 / gpusq_spgemm_int8 only: the fused patch-embedding calls
  * (gpusq_patch_embed16_*) run on the kernel for few rows or on tile kernel 2, whatever this query reports for a GEMM of the same
  * sizes. */
 gpusq_status gpusq_spgemm_plan(gpusq_dtype dt, int64_t M, int64_t N, int64_t K, int epilogue, int cus, int32_t out[8]);
 
 /* Testing aid: kernel = 0 (64 x 64 tiles), 1, 2, 3 or 4 (few rows, shown as 0 by gpusq_spgemm_plan) makes the sparse GEMM entry
- * points (and gpusq_spgemm_plan's out[0]) take that kernel for every problem it can run (the tile kernels need K * element size % 128 == 0), so that every kernel can be checked on
+ * points (and gpusq_spgemm_plan's out[0]) take that kernel for every problem it can run (kernel 3 needs K * element size % 128 == 0), so that every kernel can be checked on
  * the same shapes; 0 and 1 also keep the dense twins on their small kernel; any other value gives the choice back to the
  * size rules.  Returns the previous setting (-1 = none).  Process-wide; the environment variable GPUSQ_FORCE_KERNEL (0..4)
  * gives the initial setting and is read once, when the library is loaded.  Not meant for production callers. */

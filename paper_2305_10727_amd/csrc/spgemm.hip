@@ -16,7 +16,7 @@
 //
 // Here: spgemm_small_kernel (64 x 64 / 128 x 128 tiles through registers; any K % 16 == 0; used for small or ragged-K problems)
 // and the choice between it, the kernel for few rows (fewrows.hip) and the two tile kernels (tile1.h, tile2.hip), which bring
-// operands into an LDS ring by direct global->LDS copies and need K * element size % 128 == 0.
+// operands into an LDS ring by direct global->LDS copies (tile2.hip needs K * element size % 128 == 0).
 #include <atomic>
 #include <cstdlib>
 #include <type_traits>
@@ -464,7 +464,9 @@ static EvenPlan even_plan(int64_t M, int64_t N, int resident, int ksteps, bool g
 }
 
 // Which kernel a problem takes: 0 = small kernel with 64 x 64 tiles, 1 = small kernel with 128 x 128 tiles, 2 = tile
-// kernel.  K that is not a whole number of 128-byte steps needs the zero-filling small kernel.  Otherwise the estimated
+// kernel.  K that is not a whole number of 128-byte steps runs on the small kernels and on tile kernel 2, by the same estimates
+// (788 x 576 -> 2304 int8 6.4 us on the 64 x 64 tiles, 6.6 on the tile kernel; 2000 x 4496 -> 300 10.5 and 18.4; 1576 x 448 -> 1792
+// 7.1 and 6.6; the 128 x 128 tiles were behind one of the two on every size tried).  The estimated
 // run times decide (microseconds, fitted to graph-replayed launches on MI355X for M = 197 ... 6304): the small kernel
 // keeps two workgroups per CU busy, costs about 0.7 us + 0.45 us per K step per round of 512 workgroups and never less than what
 // one workgroup's chain of loads takes; the tile kernel costs its plan's makespan plus the start-up of its pipeline.
@@ -477,20 +479,24 @@ static EvenPlan even_plan(int64_t M, int64_t N, int resident, int ksteps, bool g
 static bool few_rows(bool is_i8, int64_t M, int64_t N, int resident) {
   return ceil_div(M, 32) * ceil_div(N, kRowBlock) <= (is_i8 ? 3 : 6) * (int64_t)resident;
 }
+// Of the two small kernels: 64 x 64 tiles while these fit one round of two workgroups per CU, 128 x 128 beyond.
+static int small_choice(int64_t M, int64_t N, int resident) { return ceil_div(M, 64) * ceil_div(N, 64) <= 2 * (int64_t)resident ? 0 : 1; }
 static int kernel_choice(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu, int resident, bool fused_patches = false) {
   const int64_t k_bytes = K * (is_i8 ? 1 : 2);
   const int64_t ksteps = ceil_div(k_bytes, kStepBytes);
   const int64_t wgs64 = ceil_div(M, 64) * ceil_div(N, 64);
   // Testing aid: a forced kernel overrides the choice (2 only where the tile kernel can run the problem).
   if (const int c = g_forced_kernel.load(std::memory_order_relaxed); c >= 0) {
-    if (c < 2 || c == 4 || k_bytes % kStepBytes == 0) return c;
+    if (c != 3 || k_bytes % kStepBytes == 0) return c;
   }
   // (the fused patch gather is refused up to 256 K outputs; beyond, it takes the kernel a GEMM of its sizes would, so that both
   // add up in the same order)
   if (fused_patches && M * N <= (int64_t)256 * 1024) return 0;
   if (few_rows(is_i8, M, N, resident)) return 4;
   if (M * N <= (int64_t)256 * 1024) return 0;
-  if (k_bytes % kStepBytes != 0) return wgs64 <= 2 * resident ? 0 : 1;
+  const bool ragged = k_bytes % kStepBytes != 0;
+  // (beyond the 32-bit lane offsets of a tile of 256 rows; the small kernels' tiles have fewer)
+  if (ragged && (k_bytes >= ((int64_t)1 << 24) || N >= ((int64_t)1 << 25))) return small_choice(M, N, resident);
   if (fused_patches) return 2;
   // Between the two tile kernels the measured times decide (every linear layer of the ViT-B, Swin-B, ViT-L and ViT-H
   // workloads, FP16 and INT8, with hot and with cold buffers, the two kernels timed in turn; they are within 10 % of each
@@ -500,7 +506,7 @@ static int kernel_choice(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu,
   // behind once the activations come from HBM).  The single-workgroup kernel keeps the wide layers, the GELU layers and
   // every long-K layer, where its deeper ring hides the latency of cold activations (the other kernel is 10-25 % behind
   // there on cold buffers).
-  const int tile_kernel = (N <= 1536 && K <= 1024 && !gelu && (is_i8 || N >= 1024)) ? 3 : 2;
+  const int tile_kernel = (!ragged && N <= 1536 && K <= 1024 && !gelu && (is_i8 || N >= 1024)) ? 3 : 2;
   if (wgs64 > 16 * resident) return tile_kernel;  // far beyond the crossover with the small kernel: skip the planning
   const double per_round = 0.7 + 0.45 * ksteps, chain = 3.6 + 0.25 * ksteps;
   const double throughput = 4.0 + per_round * (double)wgs64 / (2.0 * resident);
@@ -517,6 +523,10 @@ gpusq_status plan_spgemm(bool is_i8, int64_t M, int64_t N, int64_t K, int epilog
   for (int i = 0; i < 8; ++i) out[i] = 0;
   out[0] = choice == 4 ? 0 : choice;  // (both kernels for small problems are reported as 0)
   if (choice < 2 || choice == 4) return GPUSQ_OK;
+  if (K * (is_i8 ? 1 : 2) % kStepBytes != 0) {  // a ragged K: the small kernel that takes it where X is quantised on the way in
+    out[0] = small_choice(M, N, resident);
+    return GPUSQ_OK;
+  }
   const int ksteps = (int)(K * (is_i8 ? 1 : 2) / kStepBytes);
   const bool gelu = (epilogue & GPUSQ_EPI_GELU) != 0;
   const TilePlan p = choice == 2 ? make_plan((int)M, (int)N, resident, ksteps, gelu) : make_tile2_plan((int)M, (int)N, 2 * resident, ksteps, gelu, false);
@@ -557,7 +567,7 @@ static const Decision& decide(bool is_i8, int64_t M, int64_t N, int64_t K, bool 
   if (used < kSlots) ++used;
   d = Decision{is_i8, gelu, patches, forced, M, N, K, resident, kernel_choice(is_i8, M, N, K, gelu, resident, patches), TilePlan{}, EvenPlan{}};
   const int64_t k_bytes = K * (is_i8 ? 1 : 2);
-  if (d.choice == 2) d.even = even_plan(M, N, resident, (int)(k_bytes / kStepBytes), gelu);
+  if (d.choice == 2) d.even = even_plan(M, N, resident, (int)ceil_div(k_bytes, kStepBytes), gelu);
   if (d.choice == 3) d.plan = make_tile2_plan((int)M, (int)N, 2 * resident, (int)(k_bytes / kStepBytes), gelu, false);
   return d;
 }
@@ -568,10 +578,11 @@ static gpusq_status launch_typed(const GemmArgs& a, hipStream_t s) {
   const bool gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
   const int resident = num_cus();
   const Decision& dec = decide(IS_I8, a.M, a.N, a.K, gelu, resident, a.patch_P != 0);
-  const int choice = dec.choice;
+  int choice = dec.choice;
+  // quantising fp16 activations on the way in exists in the small kernels only, and those take every ragged K
+  if (a.x_f16 && choice == 2 && k_bytes % kStepBytes != 0) choice = small_choice(a.M, a.N, resident);
   // the fused patch gather exists in the tile kernel and in the one for few rows, for 16 x 16 patches, fp16 output, no GELU
   if (a.patch_P != 0 && ((choice != 2 && choice != 4) || a.patch_P != 16 || a.out_dt != GPUSQ_F16 || gelu)) return GPUSQ_ERR_UNSUPPORTED;
-  // quantising fp16 activations on the way in exists in the small kernel only (X passes through its registers)
   if (a.x_f16 && (!IS_I8 || choice == 2 || choice == 3)) return GPUSQ_ERR_UNSUPPORTED;
   if (choice == 4) return fewrows_supports(a) ? launch_fewrows(IS_I8, a, resident, s) : launch_small<IS_I8, 4, 1, 1, 4>(a, s);
   if (choice == 3) {
@@ -582,10 +593,11 @@ static gpusq_status launch_typed(const GemmArgs& a, hipStream_t s) {
   if (choice == 1) return launch_small<IS_I8, 4, 4, 2, 2>(a, s);
   const unsigned grid = 8u * (unsigned)dec.even.grid8;  // persistent
   if (even_total(dec.even) >= ((int64_t)1 << 31)) return GPUSQ_ERR_UNSUPPORTED;
-  if ((dec.even.rounds + 2) * (k_bytes / kStepBytes) >= ((int64_t)1 << 30)) return GPUSQ_ERR_UNSUPPORTED;
+  if ((dec.even.rounds + 2) * ceil_div(k_bytes, kStepBytes) >= ((int64_t)1 << 30)) return GPUSQ_ERR_UNSUPPORTED;
   if ((int64_t)a.N * 16 * 4 >= ((int64_t)1 << 31)) return GPUSQ_ERR_UNSUPPORTED;  // 32-bit lane offsets inside 16 rows of Y
   // 32-bit lane offsets inside the 256 rows of X of a tile (tile_x_offsets; the patch gather has its own limit)
   if (a.patch_P == 0 && 255 * k_bytes + kStepBytes >= ((int64_t)1 << 32)) return GPUSQ_ERR_UNSUPPORTED;
+  if (k_bytes % kStepBytes != 0) return IS_I8 ? launch_tile1_i8_ragged(a, dec.even, grid, s) : launch_tile1_f16_ragged(a, dec.even, grid, s);
   return IS_I8 ? launch_tile1_i8(a, dec.even, grid, s) : launch_tile1_f16(a, dec.even, grid, s);
 }
 

@@ -1,5 +1,5 @@
 // Tile kernel of the 2:4 sparse GEMM with one persistent workgroup per CU: tiles of 256 channels x up to 256 rows.  (A header:
-// its many instantiations are compiled in two translation units, tile1_i8.hip and tile1_f16.hip.)
+// its many instantiations are compiled in four translation units, tile1_{i8,f16}{,_ragged}.hip.)
 //
 // 8 wavefronts, 2 along n x 4 along m, 128 channels x up to 4 slabs of 16 rows each and 128 accumulator registers.  All of them
 // run the K loop of a tile, then all run its epilogue.  With two wavefronts per SIMD in the same phase, a SIMD always has a
@@ -24,6 +24,13 @@
 // step g+R are requested there, R-1 whole steps before they are needed, also across tile boundaries (the next tile's first
 // steps land during the epilogue).  Every wavefront executes exactly one barrier per step of every tile of the workgroup, plus
 // one at start-up.
+//
+// Ragged K (no whole number of 128-byte steps): the weights are packed with zeros past the row end, and in a row's last step the
+// lanes whose 16-byte chunk lies past it re-read the step's first.  int8 needs no more (whatever is multiplied by the zeros adds
+// nothing); fp16 activations may hold infinities or NaN, so there the wavefront that copied those chunks overwrites them with
+// zeros once they have landed, in front of the barrier that publishes the stage.  Such problems took the small kernel's
+// 128 x 128 tiles before: 65536 x 592 -> 1280 int8 80.0 -> 57.4 us, fp16 122.8 -> 85.7; 25088 x 4400 -> 1100 int8 148 -> 95, fp16
+// 300 -> 182; 12544 x 192 -> 768 int8 12.6 -> 7.7; 3152 x 576 -> 1728 int8 10.4 -> 8.1, fp16 13.3 -> 9.6.
 #pragma once
 #include <type_traits>
 
@@ -92,6 +99,9 @@ __device__ __forceinline__ void tile_x_offsets(uint32_t (&xoff)[NX], int64_t m0,
     xoff[i] = (uint32_t)(rr * k_bytes + c * 16);
   }
 }
+
+// The 16-byte chunk of a K step that a lane fetches in tile_x_offsets, the same in each of its NX blocks.
+__device__ __forceinline__ int tile_x_chunk(int wave, int lane) { return (lane & 7) ^ ((4 * wave + (lane >> 4)) & 7); }
 
 // The same for the patch-embedding mode with P = 16 (see patch_chunk_offset).
 template <bool IS_I8, int NX>
@@ -183,13 +193,14 @@ __device__ __forceinline__ void load_step_head(v8i (&b)[NX], v4i (&av)[kTileTN],
 // the last step: they land in a free stage and are never read).
 // behind_stores: the awaited copies are older than the previous tile's output stores, of which STORES may stay in flight too.
 // drain: nothing may stay in flight.
+// landed(): called once, when the wavefront's own copies of the next step have landed, in front of the barrier;
 // behind_barrier(): called once, right behind the barrier and before the step's copy requests.
-template <bool IS_I8, int NX, int TMA, int STORES, class Hook>
+template <bool IS_I8, int NX, int TMA, int STORES, class Landed, class Hook>
 __device__ __forceinline__ void tile_step(bool behind_stores, bool drain, const uint8_t* stage, const uint8_t* next, const BOffsets& bo,
                                           typename AccT<IS_I8>::type (&acc)[kTileTN][NX], v8i (&b)[NX], v4i (&av)[kTileTN],
                                           IndexWords<IS_I8>& ix, uint32_t a_off, uint32_t i_off, uint32_t req_lds_wave,
                                           uint32_t req_lds_idx, const uint8_t* req_x, const uint8_t* req_w, const uint32_t (&xoff)[NX],
-                                          uint32_t loff, uint32_t loff8k, uint32_t ioff, Hook&& behind_barrier) {
+                                          uint32_t loff, uint32_t loff8k, uint32_t ioff, Landed&& landed, Hook&& behind_barrier) {
   typedef Ring<IS_I8, NX> R;
   const uint8_t* abase = stage + R::kXSlab + a_off;
   const uint8_t* ibase = stage + R::kXSlab + i_off;
@@ -210,6 +221,7 @@ __device__ __forceinline__ void tile_step(bool behind_stores, bool drain, const 
         wait_vm<0>();
       else
         wait_vm<kBehind>();
+      landed();
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");  // no LDS read moves above the barrier
       behind_barrier();
@@ -250,7 +262,9 @@ __device__ __forceinline__ void tile_step(bool behind_stores, bool drain, const 
 }
 
 // NX: see above.  PATCH: the X operand is gathered from an image batch (patch embedding with P = 16, see patch_chunk_offset).
-template <bool IS_I8, int GELU, int OUT, int NX, bool PATCH = false>
+// RAGGED: K is no whole number of steps (a variant of its own: the tail's length in a scalar register more, the kernel spills 4-20
+// scalar values more across the K loop).
+template <bool IS_I8, int GELU, int OUT, int NX, bool PATCH = false, bool RAGGED = false>
 __global__ void __launch_bounds__(512, 1) spgemm_tile_kernel(const GemmArgs a, const EvenPlan plan) {
   typedef typename AccT<IS_I8>::type acc_t;
   typedef Ring<IS_I8, NX> R;
@@ -267,7 +281,8 @@ __global__ void __launch_bounds__(512, 1) spgemm_tile_kernel(const GemmArgs a, c
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wn = wave & 1, wm = wave >> 1;
   const int64_t k_bytes = (int64_t)a.K * ES;
-  const int ksteps = (int)(k_bytes / kStepBytes);
+  const int ksteps = (int)((k_bytes + kStepBytes - 1) / kStepBytes);
+  const int tail_bytes = RAGGED ? (int)(k_bytes % kStepBytes) : 0;  // of a row in its last step
   const uint8_t* Xg = (const uint8_t*)a.X;
   const uint8_t* Wg = (const uint8_t*)a.W;
   const int64_t w_col_bytes = (int64_t)ksteps * tile_bytes(IS_I8);
@@ -325,6 +340,28 @@ __global__ void __launch_bounds__(512, 1) spgemm_tile_kernel(const GemmArgs a, c
   int pf_item = 0, pf_ks = 0;
   const uint8_t *pf_x = Xg, *pf_w = Wg;
   uint32_t pf_xoff[NX];
+  // The cursor has come to a tile's last step: a chunk past the end of a ragged row re-reads the step's first.
+  auto clip_tail = [&]() {
+    if (RAGGED && pf_ks + 1 == ksteps) {  // uniform
+      int lane_now = lane;
+      asm volatile("" : "+v"(lane_now));
+      const int at = tile_x_chunk(wave, lane_now) * 16;
+      const uint32_t back = at >= tail_bytes ? (uint32_t)at : 0u;
+#pragma unroll
+      for (int i = 0; i < NX; ++i) pf_xoff[i] -= back;
+    }
+  };
+  // fp16: those chunks of the stage at byte offset `stage_off` become zeros, before the barrier that publishes the stage.
+  auto zero_tail = [&](int stage_off) {
+    int lane_now = lane;
+    asm volatile("" : "+v"(lane_now));
+    if (tile_x_chunk(wave, lane_now) * 16 >= tail_bytes) {
+#pragma unroll
+      for (int i = 0; i < NX; ++i) *(v4i*)(ring + stage_off + wave * 1024 + i * 8192 + lane_now * 16) = v4i{0, 0, 0, 0};
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): written
+  };
   auto seek = [&](int item) {
     pf_item = item;
     pf_ks = 0;
@@ -337,6 +374,7 @@ __global__ void __launch_bounds__(512, 1) spgemm_tile_kernel(const GemmArgs a, c
     } else {
       tile_x_offsets(pf_xoff, t.m0, a.M, 16 * t.slabs, k_bytes, wave, lane_now);
       pf_x = Xg + t.m0 * k_bytes;
+      clip_tail();
     }
     pf_w = Wg + t.n_blk * w_col_bytes + wave_lds;
   };
@@ -347,6 +385,7 @@ __global__ void __launch_bounds__(512, 1) spgemm_tile_kernel(const GemmArgs a, c
         pf_x = Xg + patch_step_offset<IS_I8>(a, pf_ks);
       else
         pf_x += kStepBytes;
+      clip_tail();
       pf_w += tile_bytes(IS_I8);
     } else if (pf_item + 1 < my_items) {
       seek(pf_item + 1);
@@ -380,6 +419,9 @@ __global__ void __launch_bounds__(512, 1) spgemm_tile_kernel(const GemmArgs a, c
     advance();
   }
   wait_vm<(R::kStages - 1) * R::kCopies>();  // the constants and step 0 have landed
+  if constexpr (RAGGED && !IS_I8) {
+    if (ksteps == 1) zero_tail(0);
+  }
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
@@ -419,6 +461,11 @@ __global__ void __launch_bounds__(512, 1) spgemm_tile_kernel(const GemmArgs a, c
         tile_step<IS_I8, NX, TMA, kStores>(stores_behind && ks < R::kStages - 1, ksteps < R::kStages, ring + slot_off, ring + next_off, bo, acc, b, av, ix,
                                            a_off, i_off, ring_lds + (uint32_t)slot_off + wave_lds, ring_lds + (uint32_t)slot_off + idx_lds,
                                            pf_x, pf_w, pf_xoff, loff, loff8k, ioff, [&]() {
+                           // (the next step is a tile's last)
+                           if constexpr (RAGGED && !IS_I8) {
+                             if (ks + 2 == ksteps || ksteps == 1) zero_tail(next_off);
+                           }
+                         }, [&]() {
                            // The next tile's constants go into the other constants array, which was last read in the
                            // previous tile's epilogue (every wavefront has left it: it passed this tile's barriers).
                            // They are older than this step's copy requests, which the next tile's barriers wait for
@@ -457,38 +504,38 @@ __global__ void __launch_bounds__(512, 1) spgemm_tile_kernel(const GemmArgs a, c
   wait_vm<0>();  // the copies requested past the end of the sequence land before the LDS is given up
 }
 
-template <bool IS_I8, int NX>
+template <bool IS_I8, bool RAGGED, int NX>
 static gpusq_status launch_tile1_nx(const GemmArgs& a, const EvenPlan& plan, unsigned grid, hipStream_t s) {
   const bool gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
-  if (a.patch_P != 0) {
-    spgemm_tile_kernel<IS_I8, 0, GPUSQ_F16, NX, true><<<grid, 512, 0, s>>>(a, plan);
+  if (a.patch_P != 0) {  // (a row is whole steps)
+    if constexpr (!RAGGED) spgemm_tile_kernel<IS_I8, 0, GPUSQ_F16, NX, true><<<grid, 512, 0, s>>>(a, plan);
   } else if constexpr (IS_I8) {
     if (a.out_dt == GPUSQ_I32)
-      spgemm_tile_kernel<true, 0, GPUSQ_I32, NX><<<grid, 512, 0, s>>>(a, plan);
+      spgemm_tile_kernel<true, 0, GPUSQ_I32, NX, false, RAGGED><<<grid, 512, 0, s>>>(a, plan);
     else if (a.out_dt == GPUSQ_I8 && gelu)
-      spgemm_tile_kernel<true, 1, GPUSQ_I8, NX><<<grid, 512, 0, s>>>(a, plan);
+      spgemm_tile_kernel<true, 1, GPUSQ_I8, NX, false, RAGGED><<<grid, 512, 0, s>>>(a, plan);
     else if (a.out_dt == GPUSQ_I8)
-      spgemm_tile_kernel<true, 0, GPUSQ_I8, NX><<<grid, 512, 0, s>>>(a, plan);
+      spgemm_tile_kernel<true, 0, GPUSQ_I8, NX, false, RAGGED><<<grid, 512, 0, s>>>(a, plan);
     else if (gelu)
-      spgemm_tile_kernel<true, 1, GPUSQ_F16, NX><<<grid, 512, 0, s>>>(a, plan);
+      spgemm_tile_kernel<true, 1, GPUSQ_F16, NX, false, RAGGED><<<grid, 512, 0, s>>>(a, plan);
     else
-      spgemm_tile_kernel<true, 0, GPUSQ_F16, NX><<<grid, 512, 0, s>>>(a, plan);
+      spgemm_tile_kernel<true, 0, GPUSQ_F16, NX, false, RAGGED><<<grid, 512, 0, s>>>(a, plan);
   } else {
     if (gelu)
-      spgemm_tile_kernel<false, 1, GPUSQ_F16, NX><<<grid, 512, 0, s>>>(a, plan);
+      spgemm_tile_kernel<false, 1, GPUSQ_F16, NX, false, RAGGED><<<grid, 512, 0, s>>>(a, plan);
     else
-      spgemm_tile_kernel<false, 0, GPUSQ_F16, NX><<<grid, 512, 0, s>>>(a, plan);
+      spgemm_tile_kernel<false, 0, GPUSQ_F16, NX, false, RAGGED><<<grid, 512, 0, s>>>(a, plan);
   }
   return check_launch();
 }
 
-template <bool IS_I8>
+template <bool IS_I8, bool RAGGED>
 static gpusq_status launch_tile1_typed(const GemmArgs& a, const EvenPlan& plan, unsigned grid, hipStream_t s) {
   switch ((even_units(plan) + 1) / 2) {
-    case 1: return launch_tile1_nx<IS_I8, 1>(a, plan, grid, s);
-    case 2: return launch_tile1_nx<IS_I8, 2>(a, plan, grid, s);
-    case 3: return launch_tile1_nx<IS_I8, 3>(a, plan, grid, s);
-    default: return launch_tile1_nx<IS_I8, 4>(a, plan, grid, s);
+    case 1: return launch_tile1_nx<IS_I8, RAGGED, 1>(a, plan, grid, s);
+    case 2: return launch_tile1_nx<IS_I8, RAGGED, 2>(a, plan, grid, s);
+    case 3: return launch_tile1_nx<IS_I8, RAGGED, 3>(a, plan, grid, s);
+    default: return launch_tile1_nx<IS_I8, RAGGED, 4>(a, plan, grid, s);
   }
 }
 

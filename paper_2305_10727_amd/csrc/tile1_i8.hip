@@ -2,5 +2,5 @@
 #include "tile1.h"
 
 namespace gpusq {
-gpusq_status launch_tile1_i8(const GemmArgs& a, const EvenPlan& plan, unsigned grid, hipStream_t s) { return launch_tile1_typed<true>(a, plan, grid, s); }
+gpusq_status launch_tile1_i8(const GemmArgs& a, const EvenPlan& plan, unsigned grid, hipStream_t s) { return launch_tile1_typed<true, false>(a, plan, grid, s); }
 }  // namespace gpusq

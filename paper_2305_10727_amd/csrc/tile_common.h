@@ -431,6 +431,8 @@ __device__ __forceinline__ void line_epilogue(const GemmArgs& a, const typename 
 // ---- the tile kernel with one workgroup per CU (tile1.h)
 gpusq_status launch_tile1_i8(const GemmArgs& a, const EvenPlan& plan, unsigned grid, hipStream_t s);
 gpusq_status launch_tile1_f16(const GemmArgs& a, const EvenPlan& plan, unsigned grid, hipStream_t s);
+gpusq_status launch_tile1_i8_ragged(const GemmArgs& a, const EvenPlan& plan, unsigned grid, hipStream_t s);
+gpusq_status launch_tile1_f16_ragged(const GemmArgs& a, const EvenPlan& plan, unsigned grid, hipStream_t s);
 
 // ---- the tile kernel with two resident workgroups per CU (tile2.hip), sparse and dense
 TilePlan make_tile2_plan(int M, int N, int resident, int ksteps, bool gelu, bool dense);
