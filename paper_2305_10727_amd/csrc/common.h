@@ -124,9 +124,11 @@ __device__ __forceinline__ int quantize_code(float x, float s, float r, float qm
 // every fp16 x if they agree on the two fp16 neighbours of each code boundary (c + 0.5) * s, 254 values, one per thread; any
 // other x lies at least one fp16 spacing, 2^-11 of it, from every boundary, thousands of times the rounding errors of either.
 // Where they disagree, the workgroup refines every product to the correctly rounded quotient first (t = x r, then t + r times
-// the exact remainder x - t s: Markstein's division with a correctly rounded reciprocal), which takes three more operations.
-// A scale outside 2^-100 .. 2^100 (denormal, 0, infinite, NaN) needs neither: every quotient is then far beyond the largest
-// code or rounds to 0, or is NaN, and so is the product.
+// the exact remainder x - t s: Markstein's division with a correctly rounded reciprocal), which takes four more operations: t
+// is held within +-1024, far beyond every code, so that the remainder of an infinite x is infinite and not infinity less infinity.
+// A negative scale decides like its magnitude: the quotient and the product change their signs together, and the rounding is
+// symmetric.  A magnitude outside 2^-100 .. 2^100 (denormal, 0, infinite, NaN) needs neither: every quotient is then far beyond
+// the largest code or rounds to 0, or is NaN, and so is the product.
 struct Fp16Quantiser {
   typedef _Float16 h8 __attribute__((ext_vector_type(8)));
   typedef _Float16 h2 __attribute__((ext_vector_type(2)));
@@ -138,13 +140,14 @@ struct Fp16Quantiser {
   __device__ __forceinline__ bool prepare(float scale, int tid) {
     s = scale;
     r = scale_reciprocal(scale);
-    if (!(scale >= 0x1p-100f && scale <= 0x1p100f) || tid >= 254) return false;
-    const float boundary = ((float)(tid >> 1) + 0.5f) * scale;
+    const float mag = fabsf(scale), rmag = fabsf(r);
+    if (!(mag >= 0x1p-100f && mag <= 0x1p100f) || tid >= 254) return false;
+    const float boundary = ((float)(tid >> 1) + 0.5f) * mag;
     const h2 down = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(boundary, 0.0f));
     const unsigned short bits = (unsigned short)(__builtin_bit_cast(unsigned short, down[0]) + (tid & 1));
-    if (bits >= 0x7C00) return false;  // no fp16 number there; infinity is clamped either way
+    if (bits >= 0x7C00) return false;  // no finite fp16 number there
     const float x = (float)__builtin_bit_cast(_Float16, bits);
-    const float fast = __fmaf_rn(x, r, 12582912.0f) - 12582912.0f, exact = rintf(__fdiv_rn(x, scale));
+    const float fast = __fmaf_rn(x, rmag, 12582912.0f) - 12582912.0f, exact = rintf(__fdiv_rn(x, mag));
     return fminf(fast, 127.0f) != fminf(exact, 127.0f);
   }
   // Codes of 8 values as bytes.  CLAMP: values may exceed 127 s (a given scale; with the scale of the data's own range no
@@ -157,7 +160,7 @@ struct Fp16Quantiser {
     if (refine) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const float t = (float)x[j] * r;
+        const float t = __builtin_amdgcn_fmed3f((float)x[j] * r, -1024.0f, 1024.0f);
         y[j] = __builtin_fmaf(__builtin_fmaf(-t, s, (float)x[j]), r, t) + 12582912.0f;
       }
     } else {
