@@ -55,12 +55,11 @@ __device__ __forceinline__ float scale_reciprocal(float s) { return __fdiv_rn(1.
 // correctly rounded quotient is within 2^-24 |x/s| of x/s, so the quotient lies within 0.38 |t| 2^-21 of t.  rint()
 // of the two can differ only if a half-integer lies between them or on one of them, which is excluded when t is at
 // least |t| 2^-21 away from every half-integer (t - floor(t) is exact in fp32).  Only the rare element inside that
-// band (about 1 in 10^5 for |t| near 100) pays for the division; |t| >= 2^20, where the test always fails, is clamped
-// either way.  +-inf and tiny or zero t take the multiply path and give the same code as the division.
-__device__ __forceinline__ int finish_code(float x, float q, float qmax = 127.0f) {
-  q = rintf(q);
-  q = fminf(fmaxf(q, -qmax), qmax);  // NaN -> -qmax -> handled below
-  return (x != x) ? 0 : (int)q;
+// band (about 1 in 10^5 for |t| near 100) pays for the division, and |t| >= 2^20, where the test always fails.  It is written
+// as "not >=", so that an infinite or NaN t divides as well: under a denormal scale r is infinite and the quotient may be small.
+__device__ __forceinline__ int finish_code(float q, float qmax = 127.0f) {
+  const float c = fminf(fmaxf(rintf(q), -qmax), qmax);
+  return (q != q) ? 0 : (int)c;  // of a NaN, or of a quotient without a value (infinity by infinity, 0 by 0): 0
 }
 // N values at once: the band test of all N values of all lanes is folded into one wavefront-uniform branch, so the
 // common case executes no division at all (a per-element conditional is turned into a select by the compiler, which
@@ -72,14 +71,14 @@ __device__ __forceinline__ void quantize_codes(const float (&x)[N], float s, flo
 #pragma unroll
   for (int j = 0; j < N; ++j) {
     t[j] = x[j] * r;
-    near_half |= fabsf(__builtin_amdgcn_fractf(t[j]) - 0.5f) < fabsf(t[j]) * 0x1p-21f;
+    near_half |= !(fabsf(__builtin_amdgcn_fractf(t[j]) - 0.5f) >= fabsf(t[j]) * 0x1p-21f);
   }
   if (__builtin_amdgcn_ballot_w64(near_half) != 0) {  // some element of some lane sits next to a rounding boundary
 #pragma unroll
     for (int j = 0; j < N; ++j) t[j] = __fdiv_rn(x[j], s);
   }
 #pragma unroll
-  for (int j = 0; j < N; ++j) q[j] = finish_code(x[j], t[j]);
+  for (int j = 0; j < N; ++j) q[j] = finish_code(t[j]);
 }
 // The codes of 8 values as bytes, packed into two words (value 0 in the low byte of `lo`): the same codes as
 // quantize_codes, with less arithmetic in the common case, for epilogues that are bound by the vector ALU.
@@ -100,7 +99,7 @@ __device__ __forceinline__ void quantize_bytes8(const float (&x)[8], float s, fl
   unsigned b[8];
   if (__builtin_amdgcn_ballot_w64(exact_path) != 0) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) b[j] = (unsigned)finish_code(x[j], __fdiv_rn(x[j], s));
+    for (int j = 0; j < 8; ++j) b[j] = (unsigned)finish_code(__fdiv_rn(x[j], s));
   } else {
 #pragma unroll
     for (int j = 0; j < 8; ++j) b[j] = __float_as_uint(__builtin_amdgcn_fmed3f(t[j], -127.0f, 127.0f) + 12582912.0f);
@@ -168,8 +167,9 @@ struct Fp16Quantiser {
       for (int j = 0; j < 8; ++j) y[j] = __builtin_fmaf((float)x[j], r, 12582912.0f);
     }
     const _Float16 all = sum[0] + sum[1];
-    // a NaN (or infinities of both signs, which lose nothing here), or a scale so small that 0 * r is one
-    if (__builtin_amdgcn_ballot_w64(!(all == all)) != 0 || !(r <= 3.4028234663852886e38f)) {
+    // a NaN (or infinities of both signs, which lose nothing here), or a reciprocal whose product with 0 or infinity is one: there
+    // the quotient is NaN as well, or 0 by a denormal
+    if (__builtin_amdgcn_ballot_w64(!(all == all)) != 0 || !(fabsf(r) > 0.0f && fabsf(r) <= 3.4028234663852886e38f)) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) y[j] = y[j] == y[j] ? y[j] : 12582912.0f;
     }

@@ -55,3 +55,50 @@ def test_given_scale(g, force_kernel, s):
         exp, _ = oracle.quantize_tensor_int8(X.astype(np.float32), scale=float(np.float32(s)))
         for name, q in _codes_of_every_entry_point(g, force_kernel, X, s):
             assert np.array_equal(q, exp), name
+
+
+# a scale by which quotients have no value (infinity by infinity, 0 by 0, NaN) or by which a finite value's product with the
+# reciprocal overflows though its quotient is small
+@pytest.mark.parametrize("s", [np.inf, -np.inf, np.nan, 0.0, -0.0, 1e-45, -1e-45, 3e-39, 1e38, 3.4e38])
+def test_scale_without_a_reciprocal(g, force_kernel, s):
+    for X in _every_fp16():
+        with np.errstate(all="ignore"):
+            exp, _ = oracle.quantize_tensor_int8(X.astype(np.float32), scale=float(np.float32(s)))
+        for name, q in _codes_of_every_entry_point(g, force_kernel, X, s):
+            assert np.array_equal(q, exp), name
+    rng = np.random.default_rng(5)
+    for cols in (1024, 1021):  # whole vectors; element by element
+        X = (rng.integers(0, 2**32, (8, cols), dtype=np.uint64).astype(np.uint32)).view(np.float32).copy()  # every exponent
+        X[1] *= np.float32(1e-38)  # denormals
+        X[:, ::9], X[:, 4::9], X[::2, 7::9], X[:, 2::31] = np.inf, -np.inf, np.nan, 0.0
+        with np.errstate(all="ignore"):
+            exp, _ = oracle.quantize_tensor_int8(X, scale=float(np.float32(s)))
+        given = np.float32(s)
+        assert np.array_equal(host(g.quantize_int8(dev(X), g.PER_TENSOR, scale=dev(np.array([given])))[0]), exp)
+        assert np.array_equal(host(g.quantize_int8(dev(X), g.PER_ROW, scale=dev(np.full(8, given)))[0]), exp)
+
+
+# infinities in the data whose own range gives the scale: finite values 0, infinity by infinity 0
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("cols", [1024, 1021])
+def test_range_with_infinities(g, dtype, cols):
+    X = np.random.default_rng(6).standard_normal((9, cols)).astype(dtype)
+    X[2, 5], X[4, 100], X[4, 900], X[7, ::3], X[8] = np.inf, -np.inf, np.nan, -np.inf, np.nan
+    x, x32 = dev(X), X.astype(np.float32)
+    with np.errstate(all="ignore"):
+        for mode, ref in ((g.PER_ROW, oracle.quantize_rows_int8), (g.PER_TENSOR, lambda v: oracle.quantize_tensor_int8(v))):
+            q, s = g.quantize_int8(x, mode)
+            exp_q, exp_s = ref(x32)
+            assert np.array_equal(host(q), exp_q) and np.array_equal(host(s), np.atleast_1d(np.asarray(exp_s, np.float32)))
+
+
+def test_weights_with_infinities(g):
+    W = (np.random.default_rng(7).standard_normal((70, 260)) * 0.02).astype(np.float32)
+    W[3, 7], W[5, ::4], W[9, 250:] = np.inf, -np.inf, np.inf
+    W[11] = W[11] * np.float32(1e-38)  # denormals: the scale's reciprocal is infinite
+    out = g.prepare_weights(dev(W), torch.int8, want_intermediates=True)
+    with np.errstate(all="ignore"):
+        exp_q, exp_s = oracle.quantize_rows_int8(oracle.prune_2to4(W)[0])
+    assert np.array_equal(host(out["w_scale"]), exp_s) and np.array_equal(host(out["W_low"]), exp_q)
+    values, meta = oracle.compress(exp_q)[:2]
+    assert np.array_equal(host(out["packed"]), host(g.pack(dev(values), dev(meta), 260)))
