@@ -78,7 +78,7 @@ __device__ __forceinline__ void quantize_codes(const float (&x)[N], float s, flo
     for (int j = 0; j < N; ++j) t[j] = __fdiv_rn(x[j], s);
   }
 #pragma unroll
-  for (int j = 0; j < N; ++j) q[j] = finish_code(t[j]);
+  for (int j = 0; j < N; ++j) q[j] = finish_code(t[j], qmax);
 }
 // The codes of 8 values as bytes, packed into two words (value 0 in the low byte of `lo`): the same codes as
 // quantize_codes, with less arithmetic in the common case, for epilogues that are bound by the vector ALU.

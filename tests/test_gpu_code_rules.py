@@ -102,3 +102,15 @@ def test_weights_with_infinities(g):
     assert np.array_equal(host(out["w_scale"]), exp_s) and np.array_equal(host(out["W_low"]), exp_q)
     values, meta = oracle.compress(exp_q)[:2]
     assert np.array_equal(host(out["packed"]), host(g.pack(dev(values), dev(meta), 260)))
+
+
+# given scales several times smaller than the row's own: quotients beyond 7 are clamped to it, so that the codes fit 4 bits
+@pytest.mark.parametrize("cols", [1024, 1021, 5120])
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+def test_int4_rows_under_a_given_scale(g, dtype, cols):
+    X = (np.random.default_rng(cols).standard_normal((9, cols)) * 3).astype(dtype)
+    X[:, ::50], X[:, 7::50] = np.inf, -np.inf
+    s = np.random.default_rng(8).uniform(0.02, 0.3, 9).astype(np.float32)
+    exp, _ = oracle.quantize_rows_int4(X.astype(np.float32), scale=s)
+    assert abs(exp).max() == 7
+    assert np.array_equal(host(g.quantize_rows_int4(dev(X), scale=dev(s))[0]), exp)
