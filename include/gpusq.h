@@ -205,7 +205,7 @@ gpusq_status gpusq_spgemm_int8(const int8_t* Xq, const void* Wpacked, const floa
  * that gpusq_spgemm_plan assigns to a tile kernel (kernel >= 2) returns GPUSQ_ERR_UNSUPPORTED and is served by
  * gpusq_quantize_int8 + gpusq_spgemm_int8.  Every workgroup quantises the rows of its own tile, so the saving is that
  * of a launch (a few microseconds) against extra work per K step; gpusq_linear_int8 takes whichever is the faster.
- * All other arguments as for gpusq_spgemm_int8. */
+ * act_scale is required for every out_dt; all other arguments as for gpusq_spgemm_int8. */
 gpusq_status gpusq_spgemm_int8_xf16(const void* X, const void* Wpacked, const float* act_scale, const float* w_scale,
                                     const float* bias, void* Y, gpusq_dtype out_dt, const float* out_scale,
                                     int64_t M, int64_t N, int64_t K, int epilogue, void* stream);

@@ -317,6 +317,7 @@ gpusq_status gpusq_spgemm_int8_xf16(const void* X, const void* Wpacked, const fl
   if (st != GPUSQ_OK) return st;
   st = check_int8_extras(act_scale, w_scale, out_dt, out_scale);
   if (st != GPUSQ_OK) return st;
+  if (!act_scale) return GPUSQ_ERR_NULL;  // it quantises X, whatever the output
   GemmArgs a{X, Wpacked, act_scale, w_scale, bias, out_scale, Y, (int)M, (int)N, (int)K, epilogue, (int)out_dt};
   a.x_f16 = 1;
   return launch_spgemm(true, a, (hipStream_t)stream);

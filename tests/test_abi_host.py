@@ -79,6 +79,8 @@ def test_argument_errors_are_caught_on_the_host(lib):
     lib.gpusq_spgemm_int8_xf16.argtypes = [vp, vp, vp, vp, vp, vp, ci, vp, i64, i64, i64, ci, vp]
     assert lib.gpusq_spgemm_int8_xf16(good, good, None, None, None, good, 1, None, 8, 8, 32, 0, None) == ERR_NULL  # scales
     assert lib.gpusq_spgemm_int8_xf16(good, good, good, good, None, good, 2, None, 8, 8, 32, 0, None) == ERR_NULL  # out_scale
+    # the scale quantises X, so it is required for raw accumulators as well
+    assert lib.gpusq_spgemm_int8_xf16(good, good, None, None, None, good, 3, None, 8, 8, 32, 0, None) == ERR_NULL
     assert lib.gpusq_spgemm_int8_xf16(good, good, good, good, None, odd, 1, None, 8, 8, 32, 0, None) == ERR_ALIGN
     assert lib.gpusq_spgemm_int8_xf16(good, good, good, good, None, good, 1, None, 12608, 3072, 768, 0, None) == ERR_UNSUPPORTED
     lib.gpusq_spgemm_fp16.argtypes = [vp, vp, vp, vp, i64, i64, i64, ci, vp]
