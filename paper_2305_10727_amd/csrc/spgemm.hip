@@ -622,11 +622,18 @@ int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, 
   return linear_int8_launches(a, dt, scale_is_input, cus > 0 ? cus : num_cus(), folds);
 }
 
+static bool overlap(const void* p, int64_t p_bytes, const void* q, int64_t q_bytes) {
+  const uintptr_t a = (uintptr_t)p, b = (uintptr_t)q;
+  return a < b + (uintptr_t)q_bytes && b < a + (uintptr_t)p_bytes;
+}
+
 gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, void* workspace, hipStream_t s) {
   bool folds;
   const int launches = linear_int8_launches(a, dt, scale_is_input, num_cus(), folds);
   a.act_scale = scale;
-  if (folds) {
+  // Y may lie over X (a square layer run on its own output): the separate quantiser has read X before the GEMM writes Y, but the
+  // GEMM that quantises reads a row of X in every column of tiles, beside workgroups that already write.
+  if (folds && !overlap(a.X, (int64_t)a.M * a.K * 2, a.Y, (int64_t)a.M * a.N * dtype_bytes(a.out_dt))) {
     a.x_f16 = 1;
     a.xq_out = Xq;
     if (!scale_is_input) {

@@ -102,3 +102,24 @@ def test_fp16_codes_decide_as_the_division_does(g):
             exp, _ = oracle.quantize_tensor_int8(X.astype(np.float32), scale=float(s))
         _, q, _ = _layer(g, dev(X), packed, sw, b, 62, N, K, dev(np.array([s], np.float32)))
         assert np.array_equal(q, exp), s
+
+
+# a square layer run on its own output, whole or partly over X: as from a copy of X, where the GEMM would quantise for itself
+@pytest.mark.parametrize("M,K", [(64, 768), (197, 768), (16, 256)])
+@pytest.mark.parametrize("given", [False, True])
+@pytest.mark.parametrize("shift", [0, 8, -8])
+def test_one_call_layer_writes_over_its_input(g, M, K, given, shift):
+    N = K
+    assert g.lib().gpusq_linear_int8_launches(g.F16, M, N, K, g.EPI_BIAS, int(given), 0) < (2 if given else 3)
+    Wq, s_w, vals, meta = _oracle_weights(synth.weights(N, K, seed=M, ids=(5,), sigma=0.05))
+    packed, sw, b = g.pack(dev(vals), dev(meta), K), dev(s_w), dev(synth.bias(N, seed=M, ids=(6,)))
+    X = (np.random.default_rng(M).standard_normal((M, K)) * 1.5).astype(np.float16)
+    scale = dev(np.array([4 / 127], np.float32)) if given else torch.empty(1, dtype=torch.float32, device="cuda")
+    y, q, s = _layer(g, dev(X), packed, sw, b, M, N, K, scale if given else None)
+    buf = torch.zeros(M * K + 16, dtype=torch.float16, device="cuda")
+    x, over = buf[8:8 + M * K], buf[8 + shift:8 + shift + M * N]
+    x.copy_(dev(X).view(-1))
+    Xq, ws = torch.full((M, K), 99, dtype=torch.int8, device="cuda"), torch.empty(4096, dtype=torch.uint8, device="cuda")
+    g.calls.gpusq_linear_int8(x, g.F16, packed, scale, int(given), sw, b, over, g.F16, None, Xq, ws, M, N, K, g.EPI_BIAS)
+    assert np.array_equal(host(Xq), q) and host(scale)[0] == s[0]
+    assert np.array_equal(host(over).reshape(M, N).view(np.uint16), y.view(np.uint16))
