@@ -6,7 +6,7 @@
 //
 // Signature, one letter per C parameter:
 //   p  tensor, integer address or None (NULL)
-//   t  the same, and a tensor must be on the GPU and contiguous (ValueError)
+//   t  tensor on the GPU and contiguous (else ValueError), or None
 //   i  integer (int, int64_t, an enum)
 //   s  torch's current stream; takes no argument
 // All of them travel in integer registers or 8-byte stack slots, so a function of any such parameters can be called through
@@ -38,7 +38,7 @@ bool address_of(PyObject* o, bool check, long* out) {
     *out = 0;
     return true;
   }
-  if (PyLong_Check(o)) {
+  if (!check && PyLong_Check(o)) {
     *out = (long)PyLong_AsUnsignedLongLongMask(o);
     return !PyErr_Occurred();
   }

@@ -142,6 +142,16 @@ def test_binding_refuses_host_tensors():
         gpusq.prune_2to4(torch.zeros(4, 8))
 
 
+def test_binding_refuses_addresses():
+    """The checked calls take tensors: an integer is none and must not reach the GPU as an address."""
+    pytest.importorskip("torch")
+    from paper_2305_10727_amd import gpusq
+    with pytest.raises(AttributeError):
+        gpusq.calls.gpusq_cast_f16(4096, None, 16)
+    with pytest.raises(AttributeError):
+        gpusq.calls.gpusq_cast_f16(None, True, 16)
+
+
 def _plan(lib, dt, M, N, K, epi, cus):
     out = (ctypes.c_int32 * 8)()
     lib.gpusq_spgemm_plan.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int,
