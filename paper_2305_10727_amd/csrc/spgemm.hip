@@ -631,9 +631,13 @@ gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* s
   bool folds;
   const int launches = linear_int8_launches(a, dt, scale_is_input, num_cus(), folds);
   a.act_scale = scale;
-  // Y may lie over X (a square layer run on its own output): the separate quantiser has read X before the GEMM writes Y, but the
-  // GEMM that quantises reads a row of X in every column of tiles, beside workgroups that already write.
-  if (folds && !overlap(a.X, (int64_t)a.M * a.K * 2, a.Y, (int64_t)a.M * a.N * dtype_bytes(a.out_dt))) {
+  // The operands may overlap in ways in which only a GEMM behind a finished quantiser gives the same: Y over X (a square layer run
+  // on its own output) or over the partial maxima, which the GEMM that quantises reads in every workgroup, beside others that
+  // already write; and an out_scale that is the activation scale itself, which it would read while one workgroup writes it.
+  const int64_t y_bytes = (int64_t)a.M * a.N * dtype_bytes(a.out_dt), range_bytes = (int64_t)gpusq_quantize_workspace_bytes(GPUSQ_PER_TENSOR, a.M, a.K);
+  const bool apart = !overlap(a.X, (int64_t)a.M * a.K * 2, a.Y, y_bytes) &&
+                     (scale_is_input || (a.out_scale != scale && (launches == 1 || !overlap(workspace, range_bytes, a.Y, y_bytes))));
+  if (folds && apart) {
     a.x_f16 = 1;
     a.xq_out = Xq;
     if (!scale_is_input) {

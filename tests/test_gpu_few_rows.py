@@ -123,3 +123,25 @@ def test_one_call_layer_writes_over_its_input(g, M, K, given, shift):
     g.calls.gpusq_linear_int8(x, g.F16, packed, scale, int(given), sw, b, over, g.F16, None, Xq, ws, M, N, K, g.EPI_BIAS)
     assert np.array_equal(host(Xq), q) and host(scale)[0] == s[0]
     assert np.array_equal(host(over).reshape(M, N).view(np.uint16), y.view(np.uint16))
+
+
+# out_scale the activation scale that the call itself finds (by every workgroup, or behind a range pass), and Y over the partial
+# maxima of the range pass: as from operands that lie apart
+@pytest.mark.parametrize("M,K,N", [(64, 768, 1000), (197, 768, 768), (197, 768, 2304)])
+@pytest.mark.parametrize("out", ["scale", "workspace"])
+def test_one_call_layer_with_shared_operands(g, M, K, N, out):
+    assert g.lib().gpusq_linear_int8_launches(g.F16, M, N, K, g.EPI_BIAS, 0, 0) < 3
+    Wq, s_w, vals, meta = _oracle_weights(synth.weights(N, K, seed=M, ids=(7,), sigma=0.05))
+    packed, sw, b = g.pack(dev(vals), dev(meta), K), dev(s_w), dev(synth.bias(N, seed=M, ids=(8,)))
+    x = dev((np.random.default_rng(N).standard_normal((M, K)) * 1.5).astype(np.float16))
+    exp_q, exp_s = g.quantize_int8(x, g.PER_TENSOR)
+    Xq, scale = torch.empty((M, K), dtype=torch.int8, device="cuda"), torch.full((1,), 1e3, device="cuda")
+    if out == "scale":  # the scale in memory before the call is another one
+        Y, ws = torch.empty((M, N), dtype=torch.int8, device="cuda"), torch.empty(4096, dtype=torch.uint8, device="cuda")
+        exp = g.spgemm_int8(exp_q, packed, N, act_scale=exp_s, w_scale=sw, bias=b, out_dtype=torch.int8, out_scale=exp_s)
+        g.calls.gpusq_linear_int8(x, g.F16, packed, scale, 0, sw, b, Y, g.I8, scale, Xq, ws, M, N, K, g.EPI_BIAS)
+    else:
+        Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+        exp = g.spgemm_int8(exp_q, packed, N, act_scale=exp_s, w_scale=sw, bias=b)
+        g.calls.gpusq_linear_int8(x, g.F16, packed, scale, 0, sw, b, Y, g.F16, None, Xq, Y, M, N, K, g.EPI_BIAS)
+    assert torch.equal(Xq, exp_q) and torch.equal(scale, exp_s) and torch.equal(Y, exp)
