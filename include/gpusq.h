@@ -203,8 +203,9 @@ gpusq_status gpusq_spgemm_int8(const int8_t* Xq, const void* Wpacked, const floa
  * gpusq_quantize_int8 with scale_is_input != 0; bit-identical to calling that first), so a layer with a static scale is
  * one launch instead of two.  Only the kernels for small problems, through whose registers X passes, can do this: a problem
  * that gpusq_spgemm_plan assigns to a tile kernel (kernel >= 2) returns GPUSQ_ERR_UNSUPPORTED and is served by
- * gpusq_quantize_int8 + gpusq_spgemm_int8.  Every workgroup quantises the rows of its own tile, so the saving is that
- * of a launch (a few microseconds) against extra work per K step; gpusq_linear_int8 takes whichever is the faster.
+ * gpusq_quantize_int8 + gpusq_spgemm_int8, but for a K of no whole 128-byte steps, which a small kernel takes.  Every
+ * workgroup quantises the rows of its own tile, so the saving is that of a launch (a few microseconds) against extra work per
+ * K step; gpusq_linear_int8 takes whichever is the faster.
  * act_scale is required for every out_dt; all other arguments as for gpusq_spgemm_int8. */
 gpusq_status gpusq_spgemm_int8_xf16(const void* X, const void* Wpacked, const float* act_scale, const float* w_scale,
                                     const float* bias, void* Y, gpusq_dtype out_dt, const float* out_scale,
@@ -255,12 +256,9 @@ gpusq_status gpusq_patch_embed16_fp16(const void* img, const void* Wpacked, cons
  * 64 channels x 16 or 32 rows with K split over the wavefronts of a workgroup; 1: small kernel, 128 x 128 tiles, any K % 16 == 0;
  * 2: tile kernel with one workgroup per CU, tiles of 256 channels x up to 256 rows; 3: tile kernel with two workgroups per
  * CU, tiles of 256 channels x up to 128 rows, the template the dense twins are built from); for the tile kernels out[1] =
- * rows per tile unit u, out[2] = 256-channel blocks, out[3] = full_tm (a full tile has u * full_tm rows), out[4] = row
- * chunks covered by full tiles, out[5] = tail_tm (the remaining rows are cut into tiles of u * tail_tm rows), out[6] =
- * tiles in all, out[7] = workgroups launched.  Same argument checks as the GEMM calls (sizes only).
- * (The heights are those of a plan in whole units, by which the kernel is chosen; kernel 2 cuts the same rows in steps of 32
- * instead, so that its tiles fill whole rounds over the CUs.  A K of no whole 128-byte steps is reported as 0 or 1, the small
- * kernel that gpusq_spgemm_int8_xf16 runs it on, also where the GEMM calls take kernel 2.)
+ * rows per tile unit u (kernel 2: 32, kernel 3: 64), out[2] = 256-channel blocks, out[3] = full_tm (a full tile has u * full_tm
+ * rows), out[4] = row chunks covered by full tiles, out[5] = tail_tm (the remaining rows are cut into tiles of u * tail_tm rows),
+ * out[6] = tiles in all, out[7] = workgroups launched.  Same argument checks as the GEMM calls (sizes only).
  * The query describes gpusq_spgemm_fp16 / gpusq_spgemm_int8 only: the fused patch-embedding calls
  * (gpusq_patch_embed16_*) run on the kernel for few rows or on tile kernel 2, whatever this query reports for a GEMM of the same
  * sizes. */

@@ -374,7 +374,7 @@ static int grid_for(const TilePlan& p, int resident) { return (int)ceil_div(p.to
 
 constexpr int kTileTM = 4;  // 64-row units of the highest tile
 
-// The plan in units of 64 rows by which the kernel is chosen (even_plan is what runs).  Candidates: full tiles of 64, 128, 192 or 256
+// The plan in units of 64 rows by whose estimate the kernel is chosen (what runs is even_plan's, which is no longer).  Candidates: full tiles of 64, 128, 192 or 256
 // rows, either over all of M, or for as many whole rounds over the resident
 // workgroups as the problem has with the remaining rows in tail tiles of 64..64*full_tm rows; the one whose busiest
 // workgroup finishes first wins.
@@ -407,59 +407,6 @@ static TilePlan make_plan(int M, int N, int resident, int ksteps, bool gelu) {
       for (int ttm = ftm; ttm >= 1; --ttm) consider(ftm, full_chunks, ttm);
     }
   }
-  return best;
-}
-
-// The plan the tile kernel with one workgroup per CU runs (tile1.h).  For each number of rounds over the CUs from the fewest
-// (tiles of at most 8 units of 32 rows) on: as many chunks as fill them.  Where the rows are a few more than whole rounds of the
-// highest tiles: those, and the rest in tail chunks.  The shortest estimate wins (microseconds, fitted to timings of every plan of
-// sixteen layers' sizes on MI355X): a K step of u units takes 0.24 + 0.113 u and no less than 0.41, so rows spread over more
-// rounds cost 0.24 per K step and round.  A tail tile's K steps are those of a lone workgroup, and part of its time vanishes
-// in the 5 % by which the workgroups' ends differ anyway (65792 x 5120 -> 1280: 6 even rounds 291 us, 5 and a tail 269).
-static EvenPlan even_plan(int64_t M, int64_t N, int resident, int ksteps, bool gelu) {
-  constexpr int kTallest = 8, kTail = 6;  // (a tail tile is one that the loop for tiles of 7 and 8 units can run)
-  const int tiles_n = (int)ceil_div(N, kTileBN);
-  const int64_t units = ceil_div(M, 32);
-  const double epi_unit = gelu ? 0.5 : 0.3;
-  auto round_cost = [&](double u) {
-    const double step = 0.24 + 0.113 * u;
-    return ksteps * (step > 0.41 ? step : 0.41) + 0.3 + epi_unit * u;
-  };
-  EvenPlan best{};
-  double best_cost = -1;
-  auto consider = [&](int64_t main_units, int64_t chunks, int64_t tail_units, double cost) {
-    if (best_cost >= 0 && cost >= best_cost) return;
-    best_cost = cost;
-    best.tiles_n = tiles_n;
-    best.chunks = (int)chunks;
-    best.units = (int)(main_units / chunks);
-    best.higher = (int)(main_units % chunks);
-    best.tail_units = kTail;
-    best.tail_chunks = (int)ceil_div(tail_units, kTail);
-  };
-  const int64_t least = ceil_div(ceil_div(units, kTallest) * tiles_n, resident);
-  for (int64_t rounds = least; rounds <= least + 2; ++rounds) {
-    int64_t chunks = rounds * resident / tiles_n;  // (>= units / kTallest)
-    if (chunks > units) chunks = units;
-    const int64_t r = ceil_div(chunks * tiles_n, resident);
-    // what the workgroup with the most higher tiles has
-    const int64_t most = r * (units / chunks) + ceil_div((units % chunks) * tiles_n, resident);
-    consider(units, chunks, 0, r * round_cost((double)most / r));
-  }
-  const int64_t whole = (least - 1) * resident / tiles_n;  // chunks of the highest tiles that fill the rounds but the last
-  const int64_t rest = units - whole * kTallest;
-  if (least >= 4 && whole > 0 && rest > 0 && ceil_div(rest, kTail) * tiles_n <= resident) {
-    const double all = (least - 1) * round_cost(kTallest), tail = ksteps * 0.5 + 0.3 + epi_unit * kTail - 0.05 * all;
-    consider(whole * kTallest, whole, rest, all + (tail > 0 ? tail : 0));
-  }
-  const int64_t total = even_total(best);
-  best.grid8 = (int)ceil_div(total < resident ? total : resident, 8);  // one workgroup per CU, never more workgroups than tiles
-  best.rounds = (int)(total / (8 * best.grid8));
-  best.last_round = (int)(total % (8 * best.grid8));
-  int log2 = 1;
-  while (((int64_t)1 << log2) < tiles_n) ++log2;
-  best.shift = log2 - 1;
-  best.inv = tiles_n > 1 ? (uint32_t)(((uint64_t)1 << (31 + log2)) / tiles_n + ((((uint64_t)1 << (31 + log2)) % tiles_n) != 0)) : 0u;
   return best;
 }
 
@@ -522,21 +469,27 @@ gpusq_status plan_spgemm(bool is_i8, int64_t M, int64_t N, int64_t K, int epilog
   const int choice = kernel_choice(is_i8, M, N, K, (epilogue & GPUSQ_EPI_GELU) != 0, resident);
   for (int i = 0; i < 8; ++i) out[i] = 0;
   out[0] = choice == 4 ? 0 : choice;  // (both kernels for small problems are reported as 0)
-  if (choice < 2 || choice == 4) return GPUSQ_OK;
-  if (K * (is_i8 ? 1 : 2) % kStepBytes != 0) {  // a ragged K: the small kernel that takes it where X is quantised on the way in
-    out[0] = small_choice(M, N, resident);
-    return GPUSQ_OK;
-  }
-  const int ksteps = (int)(K * (is_i8 ? 1 : 2) / kStepBytes);
+  const int ksteps = (int)ceil_div(K * (is_i8 ? 1 : 2), kStepBytes);
   const bool gelu = (epilogue & GPUSQ_EPI_GELU) != 0;
-  const TilePlan p = choice == 2 ? make_plan((int)M, (int)N, resident, ksteps, gelu) : make_tile2_plan((int)M, (int)N, 2 * resident, ksteps, gelu, false);
-  out[1] = 64;
-  out[2] = p.tiles_n;
-  out[3] = p.full_tm;
-  out[4] = p.full_chunks;
-  out[5] = p.tail_tm;
-  out[6] = p.total;
-  out[7] = choice == 2 ? grid_for(p, resident) : tile2_grid_of(p, 2 * resident);
+  if (choice == 2) {  // main chunks of two heights, or of one and tail chunks
+    const EvenPlan p = even_plan(M, N, resident, ksteps, gelu);
+    out[1] = 32;
+    out[2] = p.tiles_n;
+    out[3] = even_units(p);
+    out[4] = p.higher > 0 ? p.higher : p.chunks;
+    out[5] = p.tail_chunks > 0 ? p.tail_units : p.units;
+    out[6] = (int32_t)even_total(p);
+    out[7] = 8 * p.grid8;
+  } else if (choice == 3) {
+    const TilePlan p = make_tile2_plan((int)M, (int)N, 2 * resident, ksteps, gelu, false);
+    out[1] = 64;
+    out[2] = p.tiles_n;
+    out[3] = p.full_tm;
+    out[4] = p.full_chunks;
+    out[5] = p.tail_tm;
+    out[6] = p.total;
+    out[7] = tile2_grid_of(p, 2 * resident);
+  }
   return GPUSQ_OK;
 }
 

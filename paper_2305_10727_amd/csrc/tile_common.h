@@ -4,10 +4,10 @@
 #pragma once
 #include "common.h"
 #include "epilogue.h"
+#include "even_plan.h"
 
 namespace gpusq {
 
-constexpr int kTileBN = 256;       // output channels of a tile = one packed weight tile
 constexpr int kTileTN = 8;         // 16-channel fragments per wavefront: a wavefront spans 128 channels
 constexpr int kTileUnitRows = 64;  // tile heights are multiples of 4 wavefronts x 16 rows
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -53,39 +53,6 @@ __host__ __device__ __forceinline__ int div_tiles_n(const TilePlan& p, int idx) 
 #else
   return p.inv_tiles_n ? (int)(((uint64_t)(unsigned)idx * p.inv_tiles_n) >> 32) : idx / p.tiles_n;
 #endif
-}
-
-// The tiles of a launch of the kernel with one workgroup per CU: the rows in chunks of whole 32-row units, the first `higher` of
-// them a unit higher than the others, times the 256-channel blocks (n fastest); behind them, perhaps, tail chunks of
-// `tail_units`.  Round i takes the tiles from i * grid on, in runs of grid / 8 to an XCD, so that tiles that share an X slab
-// meet in one L2.  The higher ones all come in the first round or rounds: no workgroup meets more of them than another by more
-// than one.  (What a workgroup begins with, it executes from a cold instruction cache and scalar cache: with the higher chunks
-// spread over the XCDs, which took it sixty more instructions or another line of kernel arguments, every launch took 1.4 us
-// longer.)
-struct EvenPlan {
-  int tiles_n, chunks;
-  int units, higher;
-  int tail_chunks, tail_units;
-  uint32_t inv;  // tile / tiles_n = (tile * inv >> 32) >> shift for tiles below 2^31 (Granlund & Montgomery 1994); tiles_n = 1: unused
-  int shift;
-  int rounds, last_round;  // whole rounds of tiles; tiles behind them
-  int grid8;               // grid / 8
-};
-struct EvenTile {
-  int n_blk, slabs;  // height in slabs of 16 rows
-  int64_t m0;
-};
-__host__ __forceinline__ int even_units(const EvenPlan& p) { return p.units + (p.higher > 0); }  // of the highest tile
-__host__ __forceinline__ int64_t even_total(const EvenPlan& p) { return (int64_t)(p.chunks + p.tail_chunks) * p.tiles_n; }
-__device__ __forceinline__ EvenTile even_tile(const EvenPlan& p, int idx) {
-  const int chunk = p.tiles_n > 1 ? (int)(__umulhi((unsigned)idx, p.inv) >> p.shift) : idx;
-  const int over = chunk - p.chunks;  // >= 0: in the tail
-  EvenTile t;
-  t.n_blk = idx - chunk * p.tiles_n;
-  t.slabs = 2 * (over < 0 ? p.units + (chunk < p.higher ? 1 : 0) : p.tail_units);
-  const int main = over < 0 ? chunk : p.chunks, tail = over < 0 ? 0 : over;
-  t.m0 = (int64_t)(main * p.units + (main < p.higher ? main : p.higher) + tail * p.tail_units) * 32;  // (units of 32 rows: below 2^26)
-  return t;
 }
 
 struct Tile {

@@ -3,6 +3,7 @@ arguments before touching the GPU.  No kernel is launched here."""
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -162,8 +163,8 @@ def _plan(lib, dt, M, N, K, epi, cus):
 
 def test_tile_plan_covers_every_row_exactly_once(lib):
     """The host-side tile plan of the sparse GEMM: the full tiles and the tail tiles partition the rows of X, the tile
-    count is consistent, no more workgroups than tiles or compute units (rounded to the 8 XCDs), and a small or ragged-K
-    problem takes the small kernel."""
+    count is consistent, no more workgroups than tiles or compute units (rounded to the 8 XCDs), and a small problem
+    takes the small kernel."""
     I8, F16 = 2, 1
     shapes = [(12608, 3072, 768), (25216, 768, 3072), (12544, 512, 2048), (65792, 5120, 1280), (50432, 1024, 4096),
               (600, 512, 384), (1500, 388, 256), (2100, 520, 128), (12345, 264, 128), (70000, 256, 128), (257, 1024, 1024),
@@ -183,8 +184,8 @@ def test_tile_plan_covers_every_row_exactly_once(lib):
                         assert p[1:] == [0] * 7 and -(-M // 64) * -(-N // 64) <= 16 * cus
                         continue
                     # kernel 2: one workgroup per CU, tiles of up to 256 rows; kernel 3: two per CU, up to 128 rows
-                    max_tm, per_cu = (4, 1) if kernel == 2 else (2, 2)
-                    assert u == 64 and tiles_n == -(-N // 256)
+                    unit, max_tm, per_cu = (32, 8, 1) if kernel == 2 else (64, 2, 2)
+                    assert u == unit and tiles_n == -(-N // 256)
                     assert 1 <= ftm <= max_tm and 1 <= ttm <= max_tm and fchunks >= 0
                     full_rows = fchunks * u * ftm
                     assert full_rows - u * ftm < M          # no full tile lies entirely beyond M
@@ -204,9 +205,11 @@ def test_tile_plan_covers_every_row_exactly_once(lib):
     assert _plan(lib, F16, 12608, 3072, 768, 3, 256)[1][0] == 2 and _plan(lib, F16, 50432, 1024, 4096, 1, 256)[1][0] == 2
     assert _plan(lib, I8, 25216, 768, 768, 1, 256)[1][0] == 3 and _plan(lib, F16, 12544, 1536, 512, 1, 256)[1][0] == 3
     assert _plan(lib, F16, 25216, 768, 768, 1, 256)[1][0] == 2  # FP16: only from 1024 output channels on
-    # ragged K (not a multiple of the 128-byte K step) -> zero-filling small kernel; argument errors are reported
-    assert _plan(lib, I8, 4096, 4096, 144, 0, 256) == (0, [1, 0, 0, 0, 0, 0, 0, 0])
-    assert _plan(lib, F16, 4096, 4096, 64, 0, 256)[1][0] == 2 and _plan(lib, F16, 4096, 4096, 80, 0, 256)[1][0] == 1
+    # ragged K (not a multiple of the 128-byte K step): the tile kernel with one workgroup per CU takes it, the other does not;
+    # argument errors are reported
+    assert _plan(lib, I8, 4096, 4096, 144, 0, 256) == _plan(lib, I8, 4096, 4096, 256, 0, 256) == (0, [2, 32, 16, 8, 16, 8, 256, 256])
+    assert _plan(lib, F16, 4096, 4096, 64, 0, 256)[1][0] == 2 and _plan(lib, F16, 4096, 4096, 80, 0, 256)[1][0] == 2
+    assert _plan(lib, I8, 25216, 768, 784, 1, 256)[1][0] == 2
     assert _plan(lib, I8, 0, 4096, 128, 0, 256)[0] == 2 and _plan(lib, I8, 128, 4096, 130, 0, 256)[0] == 2
     assert _plan(lib, 0, 128, 4096, 128, 0, 256)[0] == 4 and _plan(lib, I8, 128, 4098, 128, 0, 256)[0] == 4
 
@@ -222,8 +225,9 @@ def test_force_kernel_override_is_an_explicit_call(lib):
         assert _plan(lib, I8, 12608, 3072, 768, 0, 256)[1][0] == 0
         assert lib.gpusq_force_kernel(2) == 0
         assert _plan(lib, I8, 197, 768, 768, 0, 256)[1][0] == 2
-        assert _plan(lib, I8, 197, 768, 144, 0, 256)[1][0] != 2   # ragged K cannot run on the tile kernel: the rules decide
+        assert _plan(lib, I8, 197, 768, 144, 0, 256)[1][0] == 2
         assert lib.gpusq_force_kernel(3) == 2
+        assert _plan(lib, I8, 197, 768, 144, 0, 256)[1][0] == 0   # ragged K cannot run on kernel 3: the rules decide
         assert _plan(lib, I8, 12608, 3072, 768, 0, 256)[1][0] == 3
         assert lib.gpusq_force_kernel(7) == 3                      # anything else clears the override
         assert lib.gpusq_force_kernel(-1) == -1
@@ -245,3 +249,15 @@ def test_gelu_fit_stays_within_its_stated_bound_of_the_exact_function():
     assert 0.05 < err.max() <= gelu_fit.FIT_BOUND_ULP16
     # so a rounded fp16 output is within one unit of the exact value's rounding, and a re-quantised code moves only at a tie
     assert np.isfinite(gelu_fit.gelu_fit_f32(np.array([-65504.0, 65504.0, 0.0, -0.0], np.float32))).all()
+
+
+def test_every_tile_of_the_one_workgroup_kernel_is_met_once(tmp_path):
+    """The plans of tile kernel 2 walked on the host with the code the kernel reads them with (tile_plan_walk.cpp), over random sizes
+    and several numbers of compute units"""
+    exe = str(tmp_path / "walk")
+    build = subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                            "-I", os.path.join(ROOT, "paper_2305_10727_amd", "csrc"), os.path.join(ROOT, "tests", "tile_plan_walk.cpp"), "-o", exe],
+                           capture_output=True, text=True)
+    assert build.returncode == 0, build.stderr
+    run = subprocess.run([exe, "20000"], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0 and run.stdout == "20000 plans\n", run.stdout

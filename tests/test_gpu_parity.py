@@ -635,10 +635,10 @@ def test_dense_twin_tile_kernel_shapes(g, M, K, N, seed):
     assert np.array_equal(yh.view(np.uint16), oracle.epilogue_fp16_f64(a64)["y16"].view(np.uint16))
 
 
-# One shape per tile height of the tile kernel (its K loop exists once per height: 64, 128, 192 and 256 rows), and one
-# whose plan mixes full-height tiles with 64-row tail tiles; the heights are what the planner picks on 256 CUs.
-HEIGHT_SHAPES = [(11229, 512, 256, 21, {1}), (8208, 512, 512, 22, {2}), (10911, 512, 768, 23, {3}), (12289, 512, 1024, 24, {4}),
-                 (13084, 512, 1280, 25, {4, 1})]
+# The tile kernel with one workgroup per CU at chunks of 1 to 7 units of 32 rows, one and two rounds of tiles; the heights (in
+# units) are what the planner picks on 256 CUs.
+HEIGHT_SHAPES = [(11229, 512, 256, 21, {1, 2}), (8208, 512, 512, 22, {2, 3}), (10911, 512, 768, 23, {4, 5}), (12289, 512, 1024, 24, {6, 7}),
+                 (13084, 512, 1280, 25, {4, 5})]
 
 
 @pytest.mark.parametrize("M,K,N,seed,heights", HEIGHT_SHAPES)
@@ -646,7 +646,7 @@ def test_tile_kernel_every_tile_height(g, force_kernel, M, K, N, seed, heights):
     force_kernel(2)
     for dt in (torch.int8, torch.float16):
         plan = g.spgemm_plan(dt, M, N, K)
-        assert plan["kernel"] == 2
+        assert plan["kernel"] == 2 and plan["unit_rows"] == 32
         got = {plan["full_tm"]} if plan["full_chunks"] else set()
         if plan["tiles"] > plan["full_chunks"] * plan["tiles_n"]:
             got.add(plan["tail_tm"])

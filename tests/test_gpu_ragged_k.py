@@ -46,10 +46,9 @@ def test_fp16(g, force_kernel, M, K, N):
 
 
 def test_fp16_input_of_the_int8_product(g):
-    """Many rows take the tile kernel; the product that quantises its input keeps the small kernels, which the plan reports, for
-    every ragged K."""
+    """Many rows take the tile kernel; the product that quantises its input keeps the small kernels for every ragged K."""
     M, K, N = 12544, 592, 1280
-    assert g.spgemm_plan(torch.int8, M, N, K)["kernel"] == 1 and g.spgemm_plan(torch.float16, M, N, K)["kernel"] == 1
+    assert g.spgemm_plan(torch.int8, M, N, K)["kernel"] == 2 and g.spgemm_plan(torch.float16, M, N, K)["kernel"] == 2
     Wq, s_w, vals, meta = _oracle_weights(synth.weights(N, K, seed=3, ids=(1,)))
     packed = g.pack(dev(vals), dev(meta), K)
     X = torch.randn((M, K), device="cuda").half()

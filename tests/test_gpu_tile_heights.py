@@ -12,9 +12,11 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 # (on 256 CUs; 1024 channels: 64 chunks to a round) one round of each height, the last with a part of a slab, and two
-# of chunks of two heights; then rounds of 2 and 3, the last tile partly outside Y, and channels that are no whole lines
+# of chunks of two heights; whole rounds of the highest tiles with a tail behind them; then rounds of 2 and 3, the last tile partly
+# outside Y, and channels that are no whole lines
 SHAPES = [(1024 * h - 5, (128, 256, 384, 512, 640, 768)[h % 6], 1024) for h in range(1, 17)]
 SHAPES += [(1024 * h + 70, (640, 128, 512, 384)[h % 4], 1024) for h in (1, 3, 4, 8, 11, 12, 15)]
+SHAPES += [(13556, 512, 5120)]
 SHAPES += [(51 * 256 * 3 + 300, 128, 1280), (20000, 128, 1024), (20000, 512, 1024), (12608, 768, 1000), (30000, 256, 264), (12608, 128, 300), (5000, 384, 4)]
 
 
