@@ -93,11 +93,13 @@ __global__ void __launch_bounds__(256) im2col_patches_kernel(const T* __restrict
 
 // The same for patch sizes whose rows are not multiples of 16 bytes (P = 14): one workgroup per (image, row of patches).  The
 // rows of X it makes are one contiguous run of W/P * K_pad elements, written with 16-byte stores; what they hold, the P image
-// rows of every channel, is read into LDS whole.  A thread writes the same 16-byte column chunk of every (third, ...) patch: where
-// its pieces of U bytes (the largest power of two that divides a patch row) lie in a patch is worked out once, and a store
-// costs it 16/U LDS reads and no division.
-// Memory-bound: 256 x 3 x 224 x 224 fp16, P = 14: 65 us with a workgroup per channel that wrote runs of P*P columns 4 bytes at
-// a time, 32 us so (77 MB read, 84 MB written: 5.0 TB/s).
+// rows of every channel, is read into LDS whole, several words in flight per thread.  A thread writes the same 16-byte column chunk
+// of every (third, ...) patch: where its pieces of U bytes (the largest power of two that divides a patch row) lie in a patch is
+// worked out once, and a store costs it 16/U LDS reads and no division.
+// Memory-bound: 256 x 3 x 224 x 224 fp16, P = 14, cold: 65 us with a workgroup per channel that wrote runs of P*P columns 4 bytes at
+// a time, 32 us so (77 MB read, 84 MB written: 5.0 TB/s).  With few workgroups it is latency: with one word in flight per thread and
+// two divisions per piece instead of two per chunk, 18 x 3 x 280 x 308 int8 (4-byte words) took 7.3 us, 6.1 so, and 256 x 3 x 224 x 224
+// int8 22.9, 19.0 so.
 // Needs K_pad * sizeof(T) % 16 == 0, plane and strip sizes in whole 4-byte words and the strips of all channels in 64 KB.
 constexpr size_t kStripBytes = 64 * 1024;
 template <typename T, int U>
@@ -111,19 +113,27 @@ __global__ void __launch_bounds__(256) im2col_rows_kernel(const T* __restrict__ 
   const int span = P * W * ES;  // bytes of a channel's strip
   const int64_t plane = (int64_t)H * W * ES;
   const uint8_t* src = (const uint8_t*)img + (int64_t)b * C * plane + (int64_t)py * span;
-  if (((span | (int)(plane & 15)) & 15) == 0) {
-    const int vecs = span / 16;
-    for (int i = tid; i < C * vecs; i += 256) {
-      const int c = i / vecs;
-      *(uint4*)(strip + 16 * i) = *(const uint4*)(src + c * plane + 16 * (i - c * vecs));
+  // (the strips' words, several requested before the first is stored)
+  auto fill = [&](auto word) {
+    typedef decltype(word) word_t;
+    constexpr int S = (int)sizeof(word_t), B = S == 16 ? 4 : 8;
+    const int per = span / S, all = C * per;
+    for (int base = tid; base < all; base += 256 * B) {
+      word_t v[B];
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int i = base + 256 * u < all ? base + 256 * u : tid, c = i / per;
+        v[u] = *(const word_t*)(src + c * plane + S * (i - c * per));
+      }
+#pragma unroll
+      for (int u = 0; u < B; ++u)
+        if (base + 256 * u < all) *(word_t*)(strip + S * (base + 256 * u)) = v[u];
     }
-  } else {
-    const int words = span / 4;
-    for (int i = tid; i < C * words; i += 256) {
-      const int c = i / words;
-      *(uint32_t*)(strip + 4 * i) = *(const uint32_t*)(src + c * plane + 4 * (i - c * words));
-    }
-  }
+  };
+  if (((span | (int)(plane & 15)) & 15) == 0)
+    fill(uint4{});
+  else
+    fill(uint32_t{});
   __syncthreads();
   const int chunks = K_pad * ES / 16;                    // of a row of X
   const int side = chunks < 256 ? 256 / chunks : 1;      // patches side by side
@@ -131,11 +141,17 @@ __global__ void __launch_bounds__(256) im2col_rows_kernel(const T* __restrict__ 
   for (int kc = tid; kc < side * chunks; kc += 256) {
     const int px0 = kc / chunks, chunk = kc - px0 * chunks;
     int at[PIECES];  // LDS offset of each piece in patch 0; < 0: a padding column
+    int k = chunk * (16 / ES);
+    int c = k / (P * P), i = (k - c * P * P) / P, j = k - (c * P + i) * P;
 #pragma unroll
     for (int e = 0; e < PIECES; ++e) {
-      const int k = (chunk * 16 + e * U) / ES;
-      const int c = k / (P * P), r = k - c * P * P, i = r / P, j = r - i * P;
       at[e] = k < K ? ((c * P + i) * W + j) * ES : -1;
+      k += U / ES;
+      j += U / ES;
+      if (j == P) {  // (a piece never crosses a patch row)
+        j = 0;
+        if (++i == P) i = 0, ++c;
+      }
     }
     for (int px = px0; px < px_n; px += side) {
       union {
@@ -203,7 +219,13 @@ static gpusq_status launch_im2col_typed(const T* img, T* X, int64_t B, int64_t C
   int vec = 16 / (int)sizeof(T);
   while (vec > 1 && (P % vec != 0 || W % vec != 0 || K_pad % vec != 0)) vec >>= 1;
   const int64_t span_bytes = P * W * (int64_t)sizeof(T);
-  if (vec * sizeof(T) < 16 && (K_pad * sizeof(T)) % 16 == 0 && span_bytes % 4 == 0 && (H * W * sizeof(T)) % 4 == 0 &&
+  const bool ragged = vec * sizeof(T) < 16;
+  const bool strips = ragged && (W * sizeof(T)) % 4 == 0 && (P * P * sizeof(T)) % 4 == 0 && (K_pad * sizeof(T)) % 4 == 0 &&
+                      (K * sizeof(T)) % 4 == 0 && span_bytes <= 48 * 1024 && B * C * (H / P) <= INT32_MAX;
+  // int8, up to 256 strips (4 images of 224 x 224): the kernel with a workgroup per channel has three times the workgroups, each a
+  // third of the chain (P = 14, 1 image: 3.5 us against 3.8; 8 images 4.1 against 4.0; fp16, 1 image: 4.2 against 4.1)
+  const bool few = strips && sizeof(T) == 1 && B * C * (H / P) <= 256;
+  if (ragged && !few && (K_pad * sizeof(T)) % 16 == 0 && span_bytes % 4 == 0 && (H * W * sizeof(T)) % 4 == 0 &&
       C * span_bytes <= (int64_t)kStripBytes && B * (H / P) <= INT32_MAX) {
     int u = 8;  // bytes of the pieces a patch row is made of
     while ((P * (int)sizeof(T)) % u != 0 || (W * (int)sizeof(T)) % u != 0) u >>= 1;
@@ -216,8 +238,7 @@ static gpusq_status launch_im2col_typed(const T* img, T* X, int64_t B, int64_t C
 #undef GPUSQ_IM2COL_ROWS
     return check_launch();
   }
-  if (vec * sizeof(T) < 16 && (W * sizeof(T)) % 4 == 0 && (P * P * sizeof(T)) % 4 == 0 && (K_pad * sizeof(T)) % 4 == 0 &&
-      (K * sizeof(T)) % 4 == 0 && span_bytes <= 48 * 1024 && B * C * (H / P) <= INT32_MAX) {
+  if (strips) {
     im2col_strip_kernel<T><<<(unsigned)(B * C * (H / P)), 256, (size_t)span_bytes, s>>>(img, X, (int)C, (int)H, (int)W, (int)P, K, (int)K_pad);
     return check_launch();
   }
