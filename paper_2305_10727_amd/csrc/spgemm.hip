@@ -420,11 +420,20 @@ static TilePlan make_plan(int M, int N, int resident, int ksteps, bool gelu) {
 // With few rows (one image: M = 197) the tile kernel has too few tiles for the chip and the small kernel is about
 // twice as fast; from a few thousand rows on the tile kernel wins.  fused_patches: the patch gather exists in the tile
 // kernel only, so that mode keeps the plain size rule.
-// Few rows: up to 3 rounds of the 64-channel x 32-row tiles of the kernel with K split over its wavefronts (fp16: 6, its K
-// has twice the steps).  Around that line it is level with the 64 x 64 tiles (int8, 788 x 768 -> 2304, 3.5 rounds: 7.3 us
-// against 6.9; fp16, 788 x 1024 -> 4096, 6.3 rounds: 12.9 us against 17.6 and the tile kernel's 13.7).
-static bool few_rows(bool is_i8, int64_t M, int64_t N, int resident) {
-  return ceil_div(M, 32) * ceil_div(N, kRowBlock) <= (is_i8 ? 3 : 6) * (int64_t)resident;
+// Few rows: 4 (the kernel with K split over its wavefronts), 0 (the 64 x 64 tiles) or -1 (by the estimates), by how many of the
+// former's 64-channel x 32-row tiles each CU gets.  Two of its workgroups run side by side on a CU (int8; fp16: three), and where
+// K has few steps another round costs most of a launch.  Timed at 7 widths, which agree; 768 channels, few rows / 64 x 64 tiles /
+// the faster tile kernel, us:
+//   int8  2 tiles, K = 192: 4.0 / 4.4 / 4.0, 768: 4.9 / 5.4 / 6.7;  3 tiles, K = 192: 5.7 / 5.0 / 5.5, 640: 6.7 / 6.0 / 6.5, 768: 7.1 / 6.7 /
+//         6.9, 1024: 7.2 / 7.2 / 7.7, 1536: 8.6 / 9.1 / 9.2;  3.5 tiles: behind or level at every K
+//   fp16  3 tiles, K = 192: 4.3 / 4.9 / 5.6;  4 tiles, K = 128: 5.5 / 5.2 / 5.3, 256: 5.9 / 6.0 / 6.1 (on 512 channels 5.9 / 5.4 / 6.2), 384: 7.0
+//         / 7.8 / 7.0;  5 tiles, K = 192: 6.4 / 5.8 / 5.9, 384: 7.6 / 8.0 / 7.1, 512: 7.7 / 8.7 / 8.0, 1536: 14.3 / 18.3 / 14.2;
+//         6 tiles, K = 192: 6.9 / 6.0 / 6.1, 768: 10.4 / 11.5 / 9.4, 3072: 29.5 / 32.9 / 25.4
+static int few_rows_choice(bool is_i8, int64_t M, int64_t N, int64_t ksteps, int resident) {
+  const int64_t tiles = ceil_div(M, 32) * ceil_div(N, kRowBlock), r = resident;
+  if (is_i8) return tiles <= (ksteps >= 8 ? 3 : 2) * r ? 4 : -1;
+  if (ksteps <= 4) return tiles <= 3 * r ? 4 : (tiles <= 5 * r ? 0 : -1);
+  return tiles <= (ksteps >= 8 ? 5 : 4) * r ? 4 : -1;
 }
 // Of the two small kernels: 64 x 64 tiles while these fit one round of two workgroups per CU, 128 x 128 beyond.
 static int small_choice(int64_t M, int64_t N, int resident) { return ceil_div(M, 64) * ceil_div(N, 64) <= 2 * (int64_t)resident ? 0 : 1; }
@@ -439,7 +448,8 @@ static int kernel_choice(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu,
   // (the fused patch gather is refused up to 256 K outputs; beyond, it takes the kernel a GEMM of its sizes would, so that both
   // add up in the same order)
   if (fused_patches && M * N <= (int64_t)256 * 1024) return 0;
-  if (few_rows(is_i8, M, N, resident)) return 4;
+  // (the patch gather has no 64 x 64 tiles)
+  if (const int c = few_rows_choice(is_i8, M, N, ksteps, resident); c == 4 || (c == 0 && !fused_patches)) return c;
   if (M * N <= (int64_t)256 * 1024) return 0;
   const bool ragged = k_bytes % kStepBytes != 0;
   // (beyond the 32-bit lane offsets of a tile of 256 rows; the small kernels' tiles have fewer)

@@ -199,6 +199,8 @@ def test_tile_plan_covers_every_row_exactly_once(lib):
     for N, K in ((2304, 768), (3072, 768), (768, 3072), (768, 768)):
         assert _plan(lib, I8, 197, N, K, 0, 256)[1][0] == 0 and _plan(lib, I8, 12608, N, K, 0, 256)[1][0] in (2, 3)
         assert _plan(lib, F16, 197, N, K, 0, 256)[1][0] == 0 and _plan(lib, F16, 12608, N, K, 0, 256)[1][0] in (2, 3)
+    # beyond the few rows whose kernel splits K over its wavefronts the estimates decide again (fp16: 6 tiles of 32 rows to a CU)
+    assert _plan(lib, F16, 1344, 2304, 3072, 1, 256)[1][0] == 2 and _plan(lib, F16, 4096, 768, 1536, 1, 256)[1][0] == 2
     # between the two tile kernels: wide, GELU and long-K layers stay on the one-workgroup kernel, layers with few output
     # channels, short K and no GELU take the kernel with two workgroups per CU
     assert _plan(lib, I8, 12608, 3072, 768, 3, 256)[1][0] == 2 and _plan(lib, I8, 25216, 768, 3072, 1, 256)[1][0] == 2
