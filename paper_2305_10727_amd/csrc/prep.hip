@@ -222,13 +222,14 @@ static gpusq_status launch_im2col_typed(const T* img, T* X, int64_t B, int64_t C
   const bool ragged = vec * sizeof(T) < 16;
   const bool strips = ragged && (W * sizeof(T)) % 4 == 0 && (P * P * sizeof(T)) % 4 == 0 && (K_pad * sizeof(T)) % 4 == 0 &&
                       (K * sizeof(T)) % 4 == 0 && span_bytes <= 48 * 1024 && B * C * (H / P) <= INT32_MAX;
-  // int8, up to 256 strips (4 images of 224 x 224): the kernel with a workgroup per channel has three times the workgroups, each a
-  // third of the chain (P = 14, 1 image: 3.5 us against 3.8; 8 images 4.1 against 4.0; fp16, 1 image: 4.2 against 4.1)
-  const bool few = strips && sizeof(T) == 1 && B * C * (H / P) <= 256;
+  int u = 8;  // bytes of the pieces a patch row is made of
+  while ((P * (int)sizeof(T)) % u != 0 || (W * (int)sizeof(T)) % u != 0) u >>= 1;
+  // Pieces of 1 or 2 bytes and up to 256 strips (4 images of 224 x 224, P = 14): the kernels with more workgroups, each with less of a
+  // chain (int8, P = 14, 1 image: 3.5 us against 3.8; 8 images 4.1 against 4.0; P = 7, 1 image: 3.3 against 4.2; pieces of 4 bytes, fp16,
+  // P = 14, 1 image: 4.2 against 4.1)
+  const bool few = u <= 2 && B * C * (H / P) <= 256;
   if (ragged && !few && (K_pad * sizeof(T)) % 16 == 0 && span_bytes % 4 == 0 && (H * W * sizeof(T)) % 4 == 0 &&
       C * span_bytes <= (int64_t)kStripBytes && B * (H / P) <= INT32_MAX) {
-    int u = 8;  // bytes of the pieces a patch row is made of
-    while ((P * (int)sizeof(T)) % u != 0 || (W * (int)sizeof(T)) % u != 0) u >>= 1;
     const unsigned grid = (unsigned)(B * (H / P));
 #define GPUSQ_IM2COL_ROWS(U) im2col_rows_kernel<T, U><<<grid, 256, (size_t)(C * span_bytes), s>>>(img, X, (int)C, (int)H, (int)W, (int)P, K, (int)K_pad)
     if (u >= 8) GPUSQ_IM2COL_ROWS(8);

@@ -9,13 +9,13 @@ from test_gpu_parity import dev, g, host  # noqa: F401
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-# strips of up to and of more than one batch of words in flight (2048 4-byte words, 1024 16-byte vectors), whole vectors and not, and
-# int8 at 256 strips (the kernel per channel) and above
-EDGES = [(1, 3, 14, 154, 14, 640), (2, 3, 42, 308, 14, 592), (1, 11, 28, 182, 14, 2160), (1, 5, 28, 224, 14, 992), (1, 12, 14, 112, 14, 2352),
-         (4, 1, 896, 28, 14, 208), (1, 257, 14, 28, 14, 50384), (257, 1, 14, 42, 14, 208)]
+# more than 256 strips, from which pieces of 1 and 2 bytes take the kernel that reads whole rows of patches: one and more than one batch
+# of words in flight (2048 4-byte words, 1024 16-byte vectors), rows of X of more chunks than threads; and 256 strips
+MANY = [(90, 3, 20, 40, 5, 80), (30, 3, 42, 308, 14, 592), (24, 11, 28, 224, 14, 2160), (130, 2, 28, 42, 14, 4112), (257, 1, 14, 42, 14, 208),
+        (4, 1, 896, 28, 14, 208), (1, 257, 14, 28, 14, 50384), (1, 11, 28, 182, 14, 2160), (1, 12, 14, 112, 14, 2352)]
 
 
-@pytest.mark.parametrize("B,C,H,W,P,K_pad", EDGES + [(2, 3, 20, 40, 5, 80), (3, 1, 36, 12, 3, 16), (1, 2, 28, 42, 14, 4112), (2, 3, 42, 56, 14, 592),
+@pytest.mark.parametrize("B,C,H,W,P,K_pad", MANY + [(2, 3, 20, 40, 5, 80), (3, 1, 36, 12, 3, 16), (1, 2, 28, 42, 14, 4112), (2, 3, 42, 56, 14, 592),
                                              (1, 90, 28, 28, 14, 17648), (5, 3, 24, 40, 8, 208), (2, 3, 12, 20, 2, 16), (1, 3, 98, 14, 14, 640)])
 @pytest.mark.parametrize("dtype", [np.float16, np.int8])
 def test_patch_rows(g, B, C, H, W, P, K_pad, dtype):
