@@ -80,6 +80,30 @@ __device__ __forceinline__ void quantize_codes(const float (&x)[N], float s, flo
 #pragma unroll
   for (int j = 0; j < N; ++j) q[j] = finish_code(t[j], qmax);
 }
+// The low bytes of four words as one.  (v_perm_b32: selector bytes 0..3 take bytes of the second operand, 4..7 of the first, 0x0c zero)
+__device__ __forceinline__ unsigned low_bytes(unsigned b0, unsigned b1, unsigned b2, unsigned b3) {
+  return __builtin_amdgcn_perm(b1, b0, 0x0c0c0400u) | __builtin_amdgcn_perm(b3, b2, 0x04000c0cu);
+}
+// The same codes as bytes, four to a word: a finite t is clamped first, then rounded half to even by adding 1.5 * 2^23, whose low byte
+// is the two's-complement code.
+template <int N>
+__device__ __forceinline__ void quantize_words(const float (&x)[N], float s, float r, unsigned (&w)[N / 4], float qmax) {
+  float t[N];
+  unsigned b[N];
+  bool near_half = false;
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    t[j] = x[j] * r;
+    near_half |= !(fabsf(__builtin_amdgcn_fractf(t[j]) - 0.5f) >= fabsf(t[j]) * 0x1p-21f);
+    b[j] = __float_as_uint(__builtin_amdgcn_fmed3f(t[j], -qmax, qmax) + 12582912.0f);
+  }
+  if (__builtin_amdgcn_ballot_w64(near_half) != 0) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) b[j] = (unsigned)finish_code(__fdiv_rn(x[j], s), qmax);
+  }
+#pragma unroll
+  for (int j = 0; j < N; j += 4) w[j / 4] = low_bytes(b[j], b[j + 1], b[j + 2], b[j + 3]);
+}
 // The codes of 8 values as bytes, packed into two words (value 0 in the low byte of `lo`): the same codes as
 // quantize_codes, with less arithmetic in the common case, for epilogues that are bound by the vector ALU.
 //   * band test |fract(t) - 0.5| < 2^-14 instead of |t| 2^-21: for |t| < 128 it is the wider of the two, and for

@@ -326,15 +326,14 @@ __device__ __forceinline__ float wave_max(float v) {
 }
 
 // One wavefront per row (= per output channel), 4 rows per workgroup.
-// Rows of whole 16-byte vectors (VEC elements): a batch of kRowBatch vectors per lane is requested before the first is used,
-// and a row of one batch stays in registers between the range and the codes; a longer one is read again.
-// A load per loop turn, and two turns over the row, took a trip to memory each: 5120 x 1280 fp32 12.6 us, 9.1 so.
-// kRowBatch: 8, or 20 for the rows that then stay in registers (up to 5120 fp32 elements).
-template <typename T, int kRowBatch>
+// Rows of whole vectors of VEC elements: a batch of kRowBatch vectors per lane is requested before the first is used, and a row of
+// one batch stays in registers between the range and the codes; a longer one is read again.
+// A load per loop turn, and two turns over the row, took a trip to memory each: 768 x 3072 fp32 11.0 us, 5.3 so.
+template <typename T, int VEC, int kRowBatch, int QMAX>
 __global__ void __launch_bounds__(256) quantize_rows_kernel(const T* __restrict__ X, int8_t* __restrict__ Q,
                                                             float* __restrict__ scale, int scale_is_input,
-                                                            int64_t rows, int64_t cols, float qmax) {
-  constexpr int VEC = 16 / (int)sizeof(T);
+                                                            int64_t rows, int64_t cols) {
+  constexpr float qmax = (float)QMAX;
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -378,15 +377,13 @@ __global__ void __launch_bounds__(256) quantize_rows_kernel(const T* __restrict_
         const int64_t i = base + j * 64 + lane;
         if (base + j * 64 >= vecs) break;  // wavefront-uniform
         float xs[VEC];
-        int qc[VEC];
+        unsigned w[VEC / 4];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) xs[e] = (float)v[j][e];
-        quantize_codes<VEC>(xs, s, rs, qc, qmax);
+        quantize_words<VEC>(xs, s, rs, w, qmax);
         if (i < vecs) {
 #pragma unroll
-          for (int e = 0; e < VEC; e += 4)
-            *(uint32_t*)(q + i * VEC + e) = (uint32_t)(qc[e] & 0xFF) | ((uint32_t)(qc[e + 1] & 0xFF) << 8) | ((uint32_t)(qc[e + 2] & 0xFF) << 16) |
-                                            ((uint32_t)(qc[e + 3] & 0xFF) << 24);
+          for (int e = 0; e < VEC; e += 4) *(uint32_t*)(q + i * VEC + e) = w[e / 4];
         }
       }
       base += kRowBatch * 64;
@@ -408,15 +405,30 @@ __global__ void __launch_bounds__(256) quantize_rows_kernel(const T* __restrict_
   for (int64_t c = lane; c < cols; c += 64) q[c] = (int8_t)quantize_code(load_as_f32(x, c), s, rs, qmax);
 }
 
-template <typename T>
-static gpusq_status launch_quantize_rows(const T* X, int8_t* Xq, float* scale, int scale_is_input, int64_t rows, int64_t cols, float qmax,
-                                         hipStream_t s) {
+// kRowBatch: the fewest of 1, 2, 4, 8 and 20 that hold a row (a batch of 8 for every short row: 12608 x 768 fp32 11.9 us, 10.2 so;
+// 100000 x 64 41, 22), 8 for the longest.  With given scales there is no range to keep the row for, and more wavefronts
+// hide the trips: 8 at most (4096 x 4096 fp32 20.0 us with 20, 14.7 so), 4 of the vectors of 8 (fp16 13.3 with 8, 12.8 so).
+template <typename T, int VEC, int QMAX>
+static void launch_quantize_rows_vec(const T* X, int8_t* Xq, float* scale, int scale_is_input, int64_t rows, int64_t cols, hipStream_t s) {
   const unsigned blocks = (unsigned)ceil_div(rows, 4);
-  const int64_t vecs = cols * (int64_t)sizeof(T) / 16;
-  if (vecs > 8 * 64 && vecs <= 20 * 64)
-    quantize_rows_kernel<T, 20><<<blocks, 256, 0, s>>>(X, Xq, scale, scale_is_input, rows, cols, qmax);
+  const int64_t per_lane = ceil_div(cols, VEC * 64);
+#define GPUSQ_QUANTIZE_ROWS(B) quantize_rows_kernel<T, VEC, B, QMAX><<<blocks, 256, 0, s>>>(X, Xq, scale, scale_is_input, rows, cols)
+  if (per_lane <= 1 || cols % VEC != 0) GPUSQ_QUANTIZE_ROWS(1);
+  else if (per_lane <= 2) GPUSQ_QUANTIZE_ROWS(2);
+  else if (per_lane <= 4 || (scale_is_input && VEC > 4)) GPUSQ_QUANTIZE_ROWS(4);
+  else if (per_lane > 8 && per_lane <= 20 && !scale_is_input) GPUSQ_QUANTIZE_ROWS(20);
+  else GPUSQ_QUANTIZE_ROWS(8);
+#undef GPUSQ_QUANTIZE_ROWS
+}
+// Vectors of 16 bytes, or of 4 fp16 values where those leave fewer of a wavefront's lanes idle: what a vector costs is the arithmetic
+// of its codes (100000 x 64 fp16 33 us with 8 values, 24 with 4; 12608 x 768 11.5 and 9.5).
+template <typename T, int QMAX>
+static gpusq_status launch_quantize_rows(const T* X, int8_t* Xq, float* scale, int scale_is_input, int64_t rows, int64_t cols, hipStream_t s) {
+  constexpr int WIDE = 16 / (int)sizeof(T);
+  if (WIDE > 4 && cols % WIDE == 0 && ceil_div(cols, 4 * 64) * 4 < ceil_div(cols, WIDE * 64) * WIDE)
+    launch_quantize_rows_vec<T, 4, QMAX>(X, Xq, scale, scale_is_input, rows, cols, s);
   else
-    quantize_rows_kernel<T, 8><<<blocks, 256, 0, s>>>(X, Xq, scale, scale_is_input, rows, cols, qmax);
+    launch_quantize_rows_vec<T, WIDE, QMAX>(X, Xq, scale, scale_is_input, rows, cols, s);
   return check_launch();
 }
 
@@ -554,7 +566,7 @@ template <typename T>
 static gpusq_status quantize_typed(const T* X, int8_t* Xq, float* scale, int mode, int scale_is_input, int64_t rows,
                                    int64_t cols, void* workspace, hipStream_t s) {
   if (mode == GPUSQ_PER_ROW) {
-    return launch_quantize_rows(X, Xq, scale, scale_is_input, rows, cols, 127.0f, s);
+    return launch_quantize_rows<T, 127>(X, Xq, scale, scale_is_input, rows, cols, s);
   }
   const int64_t n = rows * cols;
   const int64_t want = ceil_div(n * (int64_t)sizeof(T), 16 * 256 * 2);  // two 16-byte vectors per thread ...
@@ -631,8 +643,8 @@ gpusq_status launch_quantize_tensor_static(const void* X, gpusq_dtype dt, int8_t
 // The same per-row quantiser with the 4-bit range: codes -7..7 in int8 containers, scale = max|row| / 7.
 gpusq_status launch_quantize_rows_int4(const void* X, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, int64_t rows,
                                        int64_t cols, hipStream_t s) {
-  if (dt == GPUSQ_F32) return launch_quantize_rows((const float*)X, Xq, scale, scale_is_input, rows, cols, 7.0f, s);
-  return launch_quantize_rows((const _Float16*)X, Xq, scale, scale_is_input, rows, cols, 7.0f, s);
+  if (dt == GPUSQ_F32) return launch_quantize_rows<float, 7>((const float*)X, Xq, scale, scale_is_input, rows, cols, s);
+  return launch_quantize_rows<_Float16, 7>((const _Float16*)X, Xq, scale, scale_is_input, rows, cols, s);
 }
 
 // ------------------------------------------------------------------------------------------------------------ compress

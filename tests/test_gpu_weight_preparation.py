@@ -40,3 +40,20 @@ def test_row_quantiser_batches(g, rows, cols, dtype):
     q, s = g.quantize_int8(dev(X), g.PER_ROW)
     exp_q, exp_s = oracle.quantize_rows_int8(X.astype(np.float32))
     assert np.array_equal(host(q), exp_q) and np.array_equal(host(s), exp_s)
+
+
+# rows of up to 1, 2, 4, 8 and 20 vectors per lane and more, of 4 and of 8 values, with their own and with given scales
+@pytest.mark.parametrize("cols", [8, 64, 256, 264, 512, 516, 520, 768, 1024, 1032, 1280, 2048, 2056, 4096, 4104, 5120, 10240, 10248])
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+def test_row_quantiser_vectors(g, cols, dtype):
+    import oracle
+    rng = np.random.default_rng(cols)
+    X = (rng.standard_normal((6, cols)) * 3).astype(dtype)
+    X[0, -1], X[1, 0] = 40, -40  # the ranges of two rows at their ends
+    given = rng.uniform(0.02, 0.3, 6).astype(np.float32)
+    for quantise, ref in ((lambda x, s: g.quantize_int8(x, g.PER_ROW, scale=s), oracle.quantize_rows_int8),
+                          (lambda x, s: g.quantize_rows_int4(x, scale=s), oracle.quantize_rows_int4)):
+        q, s = quantise(dev(X), None)
+        exp_q, exp_s = ref(X.astype(np.float32))
+        assert np.array_equal(host(q), exp_q) and np.array_equal(host(s), exp_s)
+        assert np.array_equal(host(quantise(dev(X), dev(given))[0]), ref(X.astype(np.float32), scale=given)[0])
