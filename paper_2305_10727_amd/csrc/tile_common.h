@@ -262,7 +262,7 @@ __device__ __forceinline__ void store_line_pair(const ep_v4i& first, const ep_v4
   if (ok2) __builtin_nontemporal_store(s2, (global_v4i*)(y + half_bytes + off));
 }
 
-// MT <= TM: the slabs to do (CHECKED: at most; tm_active of them).
+// MT <= TM: the slabs to do (CHECKED and int8 output: at most; tm_active of them).
 template <bool IS_I8, int GELU, int OUT, bool CHECKED, int TM, int MT = TM>
 __device__ __forceinline__ void line_epilogue(const GemmArgs& a, const typename AccT<IS_I8>::type (&acc)[kTileTN][TM],
                                               const float* p, float s_a, float so, float rso, int n_wave, int64_t m_wave, int lane,
@@ -366,7 +366,7 @@ __device__ __forceinline__ void line_epilogue(const GemmArgs& a, const typename 
       batch_constants(g, c8, b8);
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
-        if (!CHECKED || mt < tm_active) {
+        if (mt < tm_active) {
           float v[8];
           batch_values(g, mt, c8, b8, v);
           quantize_bytes8(v, so, rso, d[mt][g][0], d[mt][g][1]);
@@ -375,7 +375,7 @@ __device__ __forceinline__ void line_epilogue(const GemmArgs& a, const typename 
     }
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      if (!CHECKED || mt < tm_active) {
+      if (mt < tm_active) {
         ep_v4i first, second;
 #pragma unroll
         for (int w = 0; w < 2; ++w) {
