@@ -259,6 +259,7 @@ gpusq_status gpusq_patch_embed16_fp16(const void* img, const void* Wpacked, cons
  * rows per tile unit u (kernel 2: 32, kernel 3: 64), out[2] = 256-channel blocks, out[3] = full_tm (a full tile has u * full_tm
  * rows), out[4] = row chunks covered by full tiles, out[5] = tail_tm (the remaining rows are cut into tiles of u * tail_tm rows),
  * out[6] = tiles in all, out[7] = workgroups launched.  Same argument checks as the GEMM calls (sizes only).
+ * (1 is the choice for fp16 and int32 output; int8 output takes kernel 2 there, or 0 up to 64 channels.)
  * The query describes gpusq_spgemm_fp16 / gpusq_spgemm_int8 only: the fused patch-embedding calls
  * (gpusq_patch_embed16_*) run on the kernel for few rows or on tile kernel 2, whatever this query reports for a GEMM of the same
  * sizes. */

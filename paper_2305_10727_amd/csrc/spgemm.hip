@@ -411,11 +411,8 @@ static TilePlan make_plan(int M, int N, int resident, int ksteps, bool gelu) {
 }
 
 // Which kernel a problem takes: 0 = small kernel with 64 x 64 tiles, 1 = small kernel with 128 x 128 tiles, 2 = tile
-// kernel.  K that is not a whole number of 128-byte steps runs on the small kernels and on tile kernel 2, by the same estimates
-// (788 x 576 -> 2304 int8 6.4 us on the 64 x 64 tiles, 6.6 on the tile kernel; 2000 x 4496 -> 300 10.5 and 18.4; 1576 x 448 -> 1792
-// 7.1 and 6.6; the 128 x 128 tiles were behind one of the two on every size tried).  The estimated
-// run times decide (microseconds, fitted to graph-replayed launches on MI355X for M = 197 ... 6304): the small kernel
-// keeps two workgroups per CU busy, costs about 0.7 us + 0.45 us per K step per round of 512 workgroups and never less than what
+// kernel.  The estimated run times decide (microseconds, fitted to graph-replayed launches on MI355X for M = 197 ... 6304): the small
+// kernel keeps two workgroups per CU busy, costs about 0.7 us + 0.45 us per K step per round of 512 workgroups and never less than what
 // one workgroup's chain of loads takes; the tile kernel costs its plan's makespan plus the start-up of its pipeline.
 // With few rows (one image: M = 197) the tile kernel has too few tiles for the chip and the small kernel is about
 // twice as fast; from a few thousand rows on the tile kernel wins.  fused_patches: the patch gather exists in the tile
@@ -432,7 +429,7 @@ static TilePlan make_plan(int M, int N, int resident, int ksteps, bool gelu) {
 static int few_rows_choice(bool is_i8, int64_t M, int64_t N, int64_t ksteps, int resident) {
   const int64_t tiles = ceil_div(M, 32) * ceil_div(N, kRowBlock), r = resident;
   if (is_i8) return tiles <= (ksteps >= 8 ? 3 : 2) * r ? 4 : -1;
-  if (ksteps <= 4) return tiles <= 3 * r ? 4 : (tiles <= 5 * r ? 0 : -1);
+  if (ksteps <= 5) return tiles <= 3 * r ? 4 : (tiles <= 5 * r ? 0 : -1);
   return tiles <= (ksteps >= 8 ? 5 : 4) * r ? 4 : -1;
 }
 // Of the two small kernels: 64 x 64 tiles while these fit one round of two workgroups per CU, 128 x 128 beyond.
@@ -452,8 +449,16 @@ static int kernel_choice(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu,
   if (const int c = few_rows_choice(is_i8, M, N, ksteps, resident); c == 4 || (c == 0 && !fused_patches)) return c;
   if (M * N <= (int64_t)256 * 1024) return 0;
   const bool ragged = k_bytes % kStepBytes != 0;
+  // A K of no whole number of 128-byte steps: the estimates are of the kernels for whole steps.  One round of 64 x 64 tiles, then, while
+  // the steps are few, one of 128 x 128 tiles, then tile kernel 2, are each the fastest (of 180 sizes timed, 0.4 % behind the fastest of
+  // the three on average; us, 64 x 64 / 128 x 128 / kernel 2: int8 3152 x 192 -> 576 5.1 / 6.2 / 6.0, 50432 x 192 -> 128 12.3 / 8.2 / 8.4, 25216 x
+  // 592 -> 128 9.9 / 8.5 / 8.3; fp16 6304 x 208 -> 576 9.3 / 7.4 / 8.3, 12608 x 400 -> 192 8.8 / 8.8 / 7.9).
   // (beyond the 32-bit lane offsets of a tile of 256 rows; the small kernels' tiles have fewer)
   if (ragged && (k_bytes >= ((int64_t)1 << 24) || N >= ((int64_t)1 << 25))) return small_choice(M, N, resident);
+  if (ragged) {
+    if (wgs64 <= 2 * resident) return 0;
+    return ksteps <= (is_i8 ? 2 : 4) && ceil_div(M, 128) * ceil_div(N, 128) <= 2 * (int64_t)resident ? 1 : 2;
+  }
   if (fused_patches) return 2;
   // Between the two tile kernels the measured times decide (every linear layer of the ViT-B, Swin-B, ViT-L and ViT-H
   // workloads, FP16 and INT8, with hot and with cold buffers, the two kernels timed in turn; they are within 10 % of each
@@ -463,7 +468,7 @@ static int kernel_choice(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu,
   // behind once the activations come from HBM).  The single-workgroup kernel keeps the wide layers, the GELU layers and
   // every long-K layer, where its deeper ring hides the latency of cold activations (the other kernel is 10-25 % behind
   // there on cold buffers).
-  const int tile_kernel = (!ragged && N <= 1536 && K <= 1024 && !gelu && (is_i8 || N >= 1024)) ? 3 : 2;
+  const int tile_kernel = (N <= 1536 && K <= 1024 && !gelu && (is_i8 || N >= 1024)) ? 3 : 2;
   if (wgs64 > 16 * resident) return tile_kernel;  // far beyond the crossover with the small kernel: skip the planning
   const double per_round = 0.7 + 0.45 * ksteps, chain = 3.6 + 0.25 * ksteps;
   const double throughput = 4.0 + per_round * (double)wgs64 / (2.0 * resident);
@@ -512,7 +517,7 @@ struct Decision {
   int64_t M, N, K;
   int resident, choice;
   TilePlan plan;  // valid when choice == 3
-  EvenPlan even;  // valid when choice == 2
+  EvenPlan even;  // valid when choice == 2, and when it is 1 for a ragged K within kernel 2's limits
 };
 static const Decision& decide(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu, int resident, bool patches) {
   constexpr int kSlots = 16;
@@ -530,7 +535,8 @@ static const Decision& decide(bool is_i8, int64_t M, int64_t N, int64_t K, bool 
   if (used < kSlots) ++used;
   d = Decision{is_i8, gelu, patches, forced, M, N, K, resident, kernel_choice(is_i8, M, N, K, gelu, resident, patches), TilePlan{}, EvenPlan{}};
   const int64_t k_bytes = K * (is_i8 ? 1 : 2);
-  if (d.choice == 2) d.even = even_plan(M, N, resident, (int)ceil_div(k_bytes, kStepBytes), gelu);
+  const bool limits = k_bytes < ((int64_t)1 << 24) && N < ((int64_t)1 << 25);  // (as in kernel_choice)
+  if (d.choice == 2 || (d.choice == 1 && limits)) d.even = even_plan(M, N, resident, (int)ceil_div(k_bytes, kStepBytes), gelu);
   if (d.choice == 3) d.plan = make_tile2_plan((int)M, (int)N, 2 * resident, (int)(k_bytes / kStepBytes), gelu, false);
   return d;
 }
@@ -542,6 +548,15 @@ static gpusq_status launch_typed(const GemmArgs& a, hipStream_t s) {
   const int resident = num_cus();
   const Decision& dec = decide(IS_I8, a.M, a.N, a.K, gelu, resident, a.patch_P != 0);
   int choice = dec.choice;
+  // The 128 x 128 tiles are the choice for fp16 and int32 output: the narrow lines of int8 output, and quantising fp16 X, cost them more
+  // than the other kernels (6304 x 192 -> 576 int8 output 9.0 us, kernel 2 7.6; 50432 x 192 -> 64 9.4, 64 x 64 tiles 8.9, kernel 2 10.5;
+  // 25216 x 64 -> 128 from fp16 11.4, 64 x 64 tiles 8.6).
+  if (choice == 1 && dec.forced < 0 && dec.even.tiles_n > 0) {
+    if (a.x_f16)
+      choice = 0;
+    else if (IS_I8 && a.out_dt == GPUSQ_I8)
+      choice = a.N <= kRowBlock ? 0 : 2;
+  }
   // quantising fp16 activations on the way in exists in the small kernels only, and those take every ragged K
   if (a.x_f16 && choice == 2 && k_bytes % kStepBytes != 0) choice = small_choice(a.M, a.N, resident);
   // the fused patch gather exists in the tile kernel and in the one for few rows, for 16 x 16 patches, fp16 output, no GELU

@@ -55,3 +55,23 @@ def test_fp16_input_of_the_int8_product(g):
     Xq, s = g.quantize_int8(X, g.PER_TENSOR)
     a = g.spgemm_int8_xf16(X, packed, N, s, dev(s_w), out_dtype=torch.int32)
     assert torch.equal(a, g.spgemm_int8(Xq, packed, N, out_dtype=torch.int32))
+
+
+# both sides of the lines between the 64 x 64 tiles, the 128 x 128 tiles and tile kernel 2 (and of the kernel for few rows where fp16 is
+# quantised on the way in): each output type as from the 64 x 64 tiles
+@pytest.mark.parametrize("M,K,N", [(3136, 192, 640), (3137, 192, 704), (8192, 192, 1024), (8193, 192, 1024), (6304, 272, 576), (25216, 64, 128),
+                                   (8192, 64, 64), (8193, 64, 64), (16400, 64, 64)])
+def test_choice_by_size(g, force_kernel, M, K, N):
+    Wq, s_w, vals, meta = _oracle_weights(synth.weights(N, K, seed=N, ids=(3,)))
+    packed, sw, bias = g.pack(dev(vals), dev(meta), K), dev(s_w), dev(synth.bias(N, seed=M, ids=(4,)))
+    X = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(M), device="cuda").half()
+    Xq, s = g.quantize_int8(X, g.PER_TENSOR)
+    so = dev(np.array([0.05], np.float32))
+    outs = lambda x, f: [f(x, packed, N, s, sw, bias, out_dtype=dt, out_scale=so if dt == torch.int8 else None) for dt in (torch.float16, torch.int8, torch.int32)]
+    own, xf16 = outs(Xq, g.spgemm_int8), outs(X, g.spgemm_int8_xf16)
+    w16 = g.prepare_weights(dev(synth.weights(N, K, seed=N, ids=(5,))), torch.float16)["packed"]
+    y16 = g.spgemm_fp16(X, w16, N, bias)
+    force_kernel(0)
+    for a, b, c in zip(own, xf16, outs(Xq, g.spgemm_int8)):
+        assert torch.equal(a, c) and torch.equal(b, c)
+    assert rel_err(host(y16), host(g.spgemm_fp16(X, w16, N, bias))) <= 2e-3
