@@ -559,6 +559,9 @@ static gpusq_status launch_typed(const GemmArgs& a, hipStream_t s) {
   }
   // quantising fp16 activations on the way in exists in the small kernels only, and those take every ragged K
   if (a.x_f16 && choice == 2 && k_bytes % kStepBytes != 0) choice = small_choice(a.M, a.N, resident);
+  // The kernel for few rows quantises in tiles of 16 rows: beyond one round of them, and with few K steps, the 64 x 64 tiles are ahead
+  // (1576 x 192 -> 576 5.9 us against 7.5, 6304 x 64 -> 128 4.7 against 7.1; but 788 x 768 -> 768 10.7 against 8.8).
+  if (a.x_f16 && choice == 4 && dec.forced != 4 && ceil_div(k_bytes, kStepBytes) <= 3 && ceil_div(a.M, 16) * ceil_div(a.N, kRowBlock) > 2 * (int64_t)resident) choice = 0;
   // the fused patch gather exists in the tile kernel and in the one for few rows, for 16 x 16 patches, fp16 output, no GELU
   if (a.patch_P != 0 && ((choice != 2 && choice != 4) || a.patch_P != 16 || a.out_dt != GPUSQ_F16 || gelu)) return GPUSQ_ERR_UNSUPPORTED;
   if (a.x_f16 && (!IS_I8 || choice == 2 || choice == 3)) return GPUSQ_ERR_UNSUPPORTED;
