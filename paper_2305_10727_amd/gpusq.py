@@ -57,8 +57,8 @@ _SIGNATURES = {
 
 class _Calls:
     """The library's launching calls as attributes, built on first use: calls.gpusq_pack(values, meta, packed, dt, N, K) takes
-    tensors (or None), checks them (device, contiguity) and raises GpusqError for a status other than OK.  check=False: for
-    callers that own the tensors they pass."""
+    tensors (or None), checks them (device, contiguity) and raises GpusqError for a status other than OK.  check=False: the
+    addresses are passed on as they are; pipeline.py, whose caller answers for the device, the layout and the sizes of what it hands in."""
 
     def __init__(self, check):
         self._check = check

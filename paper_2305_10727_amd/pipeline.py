@@ -1,6 +1,7 @@
 """One linear layer's full path with preallocated device buffers: prune -> quantise -> compress -> pack (weight
 side), quantise activations, sparse GEMM with fused epilogue.  Every step is one call into libgpusq; this class only owns
-the buffers and passes pointers (PyTorch = device memory + current stream).
+the buffers and passes pointers (PyTorch = device memory + current stream).  What the caller hands in (weights, activations,
+biases, scales) has to be contiguous, on the GPU and of the object's sizes and types: it is not checked here.
 """
 import ctypes
 
