@@ -13,7 +13,8 @@
 // ones; the two wavefronts of a SIMD are 2 apart along m, so every SIMD has as many.  (Steps of 16 rows leave two SIMDs with
 // a slab less than the others: no faster than the next step of 32.)  With both (and the K step below), before and
 // now: 12608 x 768 -> 3072 + GELU fp16 50.2 -> 47.6 us, 3136 x 4096 -> 1024 int8 20.6 -> 17.6, fp16 37.7 -> 30.1, 3152 x 768 ->
-// 3072 + GELU int8 14.2 -> 12.5, 65792 x 1280 -> 5120 + GELU int8 366 -> 357 (of 128 us for its matrix instructions alone).
+// 3072 + GELU int8 14.2 -> 12.5; 65792 x 1280 -> 5120 + GELU int8, whose rounds were even before, stays at 370 (128 of them for its
+// matrix instructions alone).
 //
 // LDS: a ring of stages (X slab NX * 8 KB, kept values 16 KB, index words 4/2 KB).  NX = ceil(slabs of the highest tile / 4) is fixed per launch:
 // copies per wavefront and K step along X, and slabs per wavefront; a ring of lower tiles has lower, more stages (3, 3, 4, 5 for
