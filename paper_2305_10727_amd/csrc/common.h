@@ -146,9 +146,13 @@ __device__ __forceinline__ int quantize_code(float x, float s, float r, float qm
 // rint(x / s) does depends on s alone and is checked once per scale and workgroup: both are monotone in x, so they agree on
 // every fp16 x if they agree on the two fp16 neighbours of each code boundary (c + 0.5) * s, 254 values, one per thread; any
 // other x lies at least one fp16 spacing, 2^-11 of it, from every boundary, thousands of times the rounding errors of either.
-// Where they disagree, the workgroup refines every product to the correctly rounded quotient first (t = x r, then t + r times
-// the exact remainder x - t s: Markstein's division with a correctly rounded reciprocal), which takes four more operations: t
-// is held within +-1024, far beyond every code, so that the remainder of an infinite x is infinite and not infinity less infinity.
+// r is the correctly rounded 1 / s or one of the two floats next to it, whichever agrees: the scale of a tensor's own range,
+// amax / 127, puts x = amax / 2, an fp16 number, on the boundary 63.5 but for the roundings of s, and there the rounded
+// reciprocal decides the other way for two scales in five.
+// Where none agrees (one such scale in 250), the workgroup refines every product to the correctly rounded quotient first (t = x r,
+// then t + r times the exact remainder x - t s: Markstein's division with a correctly rounded reciprocal), which takes four more
+// operations: t is held within +-1024, far beyond every code, so that the remainder of an infinite x is infinite and not infinity
+// less infinity.  (The few rows of 333 x 1040 -> 520 under a given scale take 5.0 us without and 6.1 with them.)
 // A negative scale decides like its magnitude: the quotient and the product change their signs together, and the rounding is
 // symmetric.  A magnitude outside 2^-100 .. 2^100 (denormal, 0, infinite, NaN) needs neither: every quotient is then far beyond
 // the largest code or rounds to 0, or is NaN, and so is the product.
@@ -157,28 +161,56 @@ struct Fp16Quantiser {
   typedef _Float16 h2 __attribute__((ext_vector_type(2)));
   typedef int i4 __attribute__((ext_vector_type(4)));
   float s, r;
-  bool refine;  // set by the caller from the threads' votes
+  bool refine;
 
-  // The check of thread `tid` of a workgroup of 256 or more: true if it found a disagreement.
-  __device__ __forceinline__ bool prepare(float scale, int tid) {
+  static __device__ __forceinline__ float neighbour(float r, int step) { return __uint_as_float(__float_as_uint(r) + (unsigned)step); }
+  // The check of thread `tid` of a workgroup of 256 or more: bit c of the result is set if reciprocal c (0: the rounded one, 1, 2: its
+  // neighbours above and below in magnitude) disagrees; the same in every lane of a wavefront.
+  __device__ __forceinline__ unsigned prepare(float scale, int tid) {
     s = scale;
     r = scale_reciprocal(scale);
     const float mag = fabsf(scale), rmag = fabsf(r);
-    if (!(mag >= 0x1p-100f && mag <= 0x1p100f) || tid >= 254) return false;
-    const float boundary = ((float)(tid >> 1) + 0.5f) * mag;
-    const h2 down = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(boundary, 0.0f));
-    const unsigned short bits = (unsigned short)(__builtin_bit_cast(unsigned short, down[0]) + (tid & 1));
-    if (bits >= 0x7C00) return false;  // no finite fp16 number there
-    const float x = (float)__builtin_bit_cast(_Float16, bits);
-    const float fast = __fmaf_rn(x, rmag, 12582912.0f) - 12582912.0f, exact = rintf(__fdiv_rn(x, mag));
-    return fminf(fast, 127.0f) != fminf(exact, 127.0f);
+    bool bad[3] = {false, false, false};
+    if (mag >= 0x1p-100f && mag <= 0x1p100f && tid < 254) {
+      const float boundary = ((float)(tid >> 1) + 0.5f) * mag;
+      const h2 down = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(boundary, 0.0f));
+      const unsigned short bits = (unsigned short)(__builtin_bit_cast(unsigned short, down[0]) + (tid & 1));
+      if (bits < 0x7C00) {  // else no finite fp16 number there
+        const float x = (float)__builtin_bit_cast(_Float16, bits);
+        const float exact = fminf(rintf(__fdiv_rn(x, mag)), 127.0f);
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+          bad[c] = fminf(__fmaf_rn(x, neighbour(rmag, c == 2 ? -1 : c), 12582912.0f) - 12582912.0f, 127.0f) != exact;
+      }
+    }
+    unsigned votes = 0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) votes |= __builtin_amdgcn_ballot_w64(bad[c]) != 0 ? 1u << c : 0u;
+    return votes;
+  }
+  // With the votes of all threads.
+  __device__ __forceinline__ void decide(unsigned votes) {
+    refine = (votes & 7u) == 7u;
+    if ((votes & 1u) != 0 && !refine) r = neighbour(r, (votes & 2u) == 0 ? 1 : -1);
+  }
+  // Wavefront-uniform: some lane's 8 N values need `odd` codes: a NaN is among them (or infinities of both signs, which lose nothing
+  // there), or the reciprocal is one whose product with 0 or infinity is NaN; there the quotient is NaN as well, or 0 by a denormal.
+  template <int N>
+  __device__ __forceinline__ bool odd(const i4 (&raw)[N]) const {
+    h2 sum = h2(0);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const h8 x = __builtin_bit_cast(h8, raw[j]);
+      sum += (h2{x[0], x[1]} + h2{x[2], x[3]}) + (h2{x[4], x[5]} + h2{x[6], x[7]});
+    }
+    const _Float16 all = sum[0] + sum[1];
+    return __builtin_amdgcn_ballot_w64(!(all == all)) != 0 || !(fabsf(r) > 0.0f && fabsf(r) <= 3.4028234663852886e38f);
   }
   // Codes of 8 values as bytes.  CLAMP: values may exceed 127 s (a given scale; with the scale of the data's own range no
   // quotient reaches 127.5).  The code of a NaN is 0.
   template <bool CLAMP>
-  __device__ __forceinline__ void codes(i4 raw, unsigned& lo, unsigned& hi) const {
+  __device__ __forceinline__ void codes(i4 raw, bool odd, unsigned& lo, unsigned& hi) const {
     const h8 x = __builtin_bit_cast(h8, raw);
-    const h2 sum = (h2{x[0], x[1]} + h2{x[2], x[3]}) + (h2{x[4], x[5]} + h2{x[6], x[7]});
     float y[8];
     if (refine) {
 #pragma unroll
@@ -190,10 +222,7 @@ struct Fp16Quantiser {
 #pragma unroll
       for (int j = 0; j < 8; ++j) y[j] = __builtin_fmaf((float)x[j], r, 12582912.0f);
     }
-    const _Float16 all = sum[0] + sum[1];
-    // a NaN (or infinities of both signs, which lose nothing here), or a reciprocal whose product with 0 or infinity is one: there
-    // the quotient is NaN as well, or 0 by a denormal
-    if (__builtin_amdgcn_ballot_w64(!(all == all)) != 0 || !(fabsf(r) > 0.0f && fabsf(r) <= 3.4028234663852886e38f)) {
+    if (odd) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) y[j] = y[j] == y[j] ? y[j] : 12582912.0f;
     }
@@ -204,34 +233,59 @@ struct Fp16Quantiser {
     unsigned b[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) b[j] = __float_as_uint(y[j]);
-    const unsigned p01 = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), p23 = __builtin_amdgcn_perm(b[3], b[2], 0x04000c0cu);
-    const unsigned p45 = __builtin_amdgcn_perm(b[5], b[4], 0x0c0c0400u), p67 = __builtin_amdgcn_perm(b[7], b[6], 0x04000c0cu);
-    lo = p01 | p23;
-    hi = p45 | p67;
+    lo = low_bytes(b[0], b[1], b[2], b[3]);
+    hi = low_bytes(b[4], b[5], b[6], b[7]);
   }
 };
 
-// Largest magnitude (NaN aside) of this thread's share of n fp16 values, n % 8 == 0: 16-byte loads, eight of them in flight.
+// The largest of a wavefront's values, none of them negative or NaN (their bit patterns then compare as they do): data-parallel
+// primitives instead of six trips through the LDS crossbar.
+__device__ __forceinline__ float wave_max_magnitude(float v) {
+  unsigned m = __float_as_uint(v);
+#define GPUSQ_MAX_DPP(CTRL, ROWS) \
+  {                               \
+    const unsigned o = (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, CTRL, ROWS, 0xF, false); \
+    m = m > o ? m : o;            \
+  }
+  GPUSQ_MAX_DPP(0x111, 0xF)  // row_shr 1, 2, 4, 8: the last lane of each row of 16 has the row's
+  GPUSQ_MAX_DPP(0x112, 0xF)
+  GPUSQ_MAX_DPP(0x114, 0xF)
+  GPUSQ_MAX_DPP(0x118, 0xF)
+  GPUSQ_MAX_DPP(0x142, 0xA)  // row_bcast 15 to rows 1 and 3, row_bcast 31 to rows 2 and 3: lane 63 has the wavefront's
+  GPUSQ_MAX_DPP(0x143, 0xC)
+#undef GPUSQ_MAX_DPP
+  return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)m, 63));
+}
+
+// Largest magnitude (NaN aside) of this thread's share of n fp16 values, n % 8 == 0 and n / 8 below 2^27: 16-byte loads, eight of
+// them in flight.  Magnitudes are compared as whole numbers; a thread that meets a NaN, the largest of these, goes over its share
+// again with the comparison that ignores it.
 __device__ __forceinline__ float range_of_fp16(const uint8_t* X, int64_t n, int tid, int threads) {
   typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+  typedef unsigned short us8 __attribute__((ext_vector_type(8)));
   typedef unsigned u4 __attribute__((ext_vector_type(4)));
-  const u4* x = (const u4*)X;
-  const int64_t vecs = n / 8;
-  h8 m = h8(0);
-  for (int64_t i = tid; i < vecs; i += 8 * (int64_t)threads) {
+  const int vecs = (int)(n / 8);
+  auto at = [&](int i) { return *(const u4*)(X + 16u * (uint32_t)i) & 0x7fff7fffu; };
+  us8 m = us8(0);
+  for (int i = tid; i < vecs; i += 8 * threads) {
     u4 v[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int64_t at = i + j * (int64_t)threads;
-      v[j] = x[at < vecs ? at : vecs - 1];
-    }
+    for (int j = 0; j < 8; ++j) v[j] = at(i + j * threads < vecs ? i + j * threads : vecs - 1);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) m = __builtin_elementwise_max(m, __builtin_bit_cast(h8, v[j] & 0x7fff7fffu));
+    for (int j = 0; j < 8; ++j) m = __builtin_elementwise_max(m, __builtin_bit_cast(us8, v[j]));
   }
-  float amax = 0.0f;
+  unsigned top = 0;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) amax = fmaxf(amax, (float)m[j]);
-  return amax;
+  for (int j = 0; j < 8; ++j) top = m[j] > top ? m[j] : top;
+  if (top > 0x7C00u) {
+    h8 f = h8(0);
+    for (int i = tid; i < vecs; i += threads) f = __builtin_elementwise_max(f, __builtin_bit_cast(h8, at(i)));
+    float amax = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) amax = fmaxf(amax, (float)f[j]);
+    return amax;
+  }
+  return (float)__builtin_bit_cast(_Float16, (unsigned short)top);
 }
 
 // Selection rule inside one group of 4 [Sec. 3.1: two of every four contiguous elements are zero; the rule is this

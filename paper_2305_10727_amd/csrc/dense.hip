@@ -78,6 +78,7 @@ __global__ void __launch_bounds__(256) dense_kernel(const GemmArgs a, const int 
     prm.publish(cs, bs, tid);  // made visible by the barriers of the main loop
   }
 
+  const OutScale os = out_scale_of<IS_I8>(a);
   acc_t acc[2][TM];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -166,13 +167,14 @@ __global__ void __launch_bounds__(256) dense_kernel(const GemmArgs a, const int 
         for (int j = 0; j < 8; ++j) {
           if constexpr (IS_I8) {
             raw[j] = acc[t][mt][8 * u + j];
-            v[j] = epilogue_value<true>(raw[j], 0.0f, c8[j], b8[j], use_gelu);
+            v[j] = epilogue_value<true>(raw[j], 0.0f, c8[j], b8[j]);
           } else {
             raw[j] = 0;
-            v[j] = epilogue_value<false>(0, acc[t][mt][8 * u + j], c8[j], b8[j], use_gelu);
+            v[j] = epilogue_value<false>(0, acc[t][mt][8 * u + j], c8[j], b8[j]);
           }
         }
-        if (m < M) store_8<IS_I8>(a, m, n, v, raw);
+        if (use_gelu) gelu_f32_x8(v);
+        if (m < M) store_8<IS_I8>(a, m, n, v, raw, os);
       }
     }
 }

@@ -20,17 +20,6 @@ typedef _Float16 ep_v4h __attribute__((ext_vector_type(4)));
 constexpr float kGeluP5 = -0.0003336848458275199f, kGeluP4 = 0.005954924505203962f, kGeluP3 = -0.04866418614983559f,
                 kGeluP2 = -0.46354809403419495f, kGeluP1 = -1.149438738822937f, kGeluP0 = -1.0001022815704346f;
 
-__device__ __forceinline__ float gelu_f32(float x) {
-  const float t = fabsf(x);
-  float p = __fmaf_rn(t, kGeluP5, kGeluP4);
-  p = __fmaf_rn(p, t, kGeluP3);
-  p = __fmaf_rn(p, t, kGeluP2);
-  p = __fmaf_rn(p, t, kGeluP1);
-  p = __fmaf_rn(p, t, kGeluP0);
-  const float q = __builtin_amdgcn_exp2f(p);
-  return __fmaf_rn(-t, q, fmaxf(x, 0.0f));
-}
-
 // Pins 8 values in registers at this point of the instruction stream (an empty volatile asm that "modifies" them): the
 // instructions that produce them cannot be moved below it, sunk into a later conditional block, or merged with the
 // instructions that consume them.
@@ -38,7 +27,7 @@ __device__ __forceinline__ void pin8(float (&x)[8]) {
   asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
 }
 
-// The same function on 8 values at once, written stage by stage so that the 8 dependency chains interleave: a lone
+// GELU of 8 values at once, written stage by stage so that the 8 dependency chains interleave: a lone
 // wavefront on a SIMD then issues an independent instruction every slot instead of waiting on each result.  The pins
 // between the stages keep the compiler from folding the chains back into pairs (which it does to save registers).
 __device__ __forceinline__ void gelu_f32_x8(float (&v)[8]) {
@@ -87,15 +76,24 @@ struct ChannelParams {
   }
 };
 
-// INT8 path: v = fma((float)acc, c, b); FP16 path: v = acc + b.  Then optional GELU.
+// INT8 path: v = fma((float)acc, c, b); FP16 path: v = acc + b.  (GELU afterwards, 8 values at a time: one uniform branch.)
 template <bool IS_I8>
-__device__ __forceinline__ float epilogue_value(int raw, float accf, float c, float b, bool use_gelu) {  // use_gelu: uniform
-  float v;
+__device__ __forceinline__ float epilogue_value(int raw, float accf, float c, float b) {
   if constexpr (IS_I8)
-    v = __fmaf_rn((float)raw, c, b);
+    return __fmaf_rn((float)raw, c, b);
   else
-    v = accf + b;
-  return use_gelu ? gelu_f32(v) : v;
+    return accf + b;
+}
+
+// The scale of int8 output and its reciprocal (1 where the output has another type).
+struct OutScale {
+  float s, r;
+};
+template <bool IS_I8, int OUT = -1>
+__device__ __forceinline__ OutScale out_scale_of(const GemmArgs& a) {
+  const int out_dt = OUT >= 0 ? OUT : a.out_dt;
+  const float s = IS_I8 && out_dt == GPUSQ_I8 ? a.out_scale[0] : 1.0f;
+  return OutScale{s, scale_reciprocal(s)};
 }
 
 // Converts and stores 8 consecutive output channels [n, n+8) of one activation row held by one lane; `yp` points at
@@ -108,8 +106,9 @@ __device__ __forceinline__ float epilogue_value(int raw, float accf, float c, fl
 // shape: the same hint makes the dense kernel's stores, and narrower or strided stores (int8 / int32 output), markedly
 // slower.
 // OUT: output dtype fixed at compile time (a gpusq_dtype value), or -1 to take it from the arguments at run time.
+// os: read by the caller long before (read here, a trip to memory stood between the last value and its code).
 template <bool IS_I8, int OUT = -1, bool STREAM = false>
-__device__ __forceinline__ void store_8_at(const GemmArgs& a, void* yp, int n, const float (&v)[8], const int (&raw)[8]) {
+__device__ __forceinline__ void store_8_at(const GemmArgs& a, void* yp, int n, const float (&v)[8], const int (&raw)[8], const OutScale& os) {
   const int N = a.N;
   const int out_dt = OUT >= 0 ? OUT : a.out_dt;
   if (n >= N) return;
@@ -120,18 +119,14 @@ __device__ __forceinline__ void store_8_at(const GemmArgs& a, void* yp, int n, c
     *(ep_v4i*)y = ep_v4i{raw[0], raw[1], raw[2], raw[3]};
     if (second) *(ep_v4i*)(y + 4) = ep_v4i{raw[4], raw[5], raw[6], raw[7]};
   } else if (IS_I8 && out_dt == GPUSQ_I8) {
-    const float so = a.out_scale[0], rso = scale_reciprocal(so);  // the same code rule as the quantiser of the activations
     int8_t* y = (int8_t*)yp;
-    int q[8];
-    quantize_codes<8>(v, so, rso, q);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) q[j] &= 0xFF;
-    const int lo = q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24), hi = q[4] | (q[5] << 8) | (q[6] << 16) | (q[7] << 24);
+    unsigned lo, hi;
+    quantize_bytes8(v, os.s, os.r, lo, hi);  // the same code rule as the quantiser of the activations
     if (whole) {
-      *(ep_v2i*)y = ep_v2i{lo, hi};
+      *(ep_v2u*)y = ep_v2u{lo, hi};
     } else {
-      *(int*)y = lo;
-      if (second) *(int*)(y + 4) = hi;
+      *(unsigned*)y = lo;
+      if (second) *(unsigned*)(y + 4) = hi;
     }
   } else {
     _Float16* y = (_Float16*)yp;
@@ -160,9 +155,9 @@ __host__ __device__ constexpr int dtype_bytes(int dt) { return dt == GPUSQ_I8 ? 
 
 // The same with the address computed from the row m and channel n.
 template <bool IS_I8, int OUT = -1>
-__device__ __forceinline__ void store_8(const GemmArgs& a, int64_t m, int n, const float (&v)[8], const int (&raw)[8]) {
+__device__ __forceinline__ void store_8(const GemmArgs& a, int64_t m, int n, const float (&v)[8], const int (&raw)[8], const OutScale& os) {
   const int out_dt = OUT >= 0 ? OUT : a.out_dt;
-  store_8_at<IS_I8, OUT>(a, (uint8_t*)a.Y + (m * a.N + n) * dtype_bytes(out_dt), n, v, raw);
+  store_8_at<IS_I8, OUT>(a, (uint8_t*)a.Y + (m * a.N + n) * dtype_bytes(out_dt), n, v, raw, os);
 }
 
 }  // namespace gpusq

@@ -14,7 +14,7 @@
 //     one batch per wavefront, and the run time is close to one trip to memory plus the launch.
 // Measured against the 64 x 64 tiles (int8 / fp16, us, graph replays): 197 x 768 -> 768 4.8 -> 3.2 / 6.2 -> 3.4, 64 x 768 ->
 // 2304 4.8 -> 3.3 / 6.2 -> 3.4, 197 x 3072 -> 768 9.8 -> 4.5 / 16.6 -> 6.0.  With 8 wavefronts instead of 4 the longest K
-// gain 2 % and every problem of more than one round of workgroups loses 20-40 %.
+// gain 2 % and every problem of more than one round of workgroups loses 20-40 %; where the kernel quantises see fewrows_wide.
 //
 // INT8 with fp16 activations: the rows are quantised on their way through the registers, with a given scale, with the partial
 // maxima that a range pass left behind, or (small X) with the range of all of X, which every workgroup reads for itself: one
@@ -34,14 +34,14 @@ typedef __attribute__((address_space(1))) ep_v2u global_v2u;
 
 // XQ: 0 = X is the operand; 1 = fp16 to be quantised with a given scale; 2 = with the scale of X's range (see GemmArgs)
 // PATCH: the rows of X are 16 x 16 patches gathered from an image batch (see patch_chunk_offset).
-template <bool IS_I8, int TM, int XQ, bool PATCH = false>
-__global__ void __launch_bounds__(64 * kFrWaves, 2) spgemm_fewrows_kernel(const GemmArgs a, const int tiles_n, const int tiles_m, const int n_fast) {
+template <bool IS_I8, int TM, int XQ, bool PATCH = false, int NW = kFrWaves>
+__global__ void __launch_bounds__(64 * NW, 2) spgemm_fewrows_kernel(const GemmArgs a, const int tiles_n, const int tiles_m, const int n_fast) {
   constexpr bool XF16 = XQ != 0;
   static_assert(IS_I8 || !XF16, "the fp16 path takes fp16 X as it is");
   typedef typename AccT<IS_I8>::type acc_t;
   constexpr int ES = IS_I8 ? 1 : 2;
   constexpr int XW = XF16 ? 2 : 1;   // bytes of X in memory per byte of the operand
-  constexpr int NW = kFrWaves, ROWS = 16 * TM;
+  constexpr int ROWS = 16 * TM;
   constexpr int XL = 2 * TM * XW;    // 16-byte loads per lane for the X rows of a step
   constexpr int D = kFrBatch;
 
@@ -49,7 +49,7 @@ __global__ void __launch_bounds__(64 * kFrWaves, 2) spgemm_fewrows_kernel(const 
   constexpr int kPiece = ROWS * kFrRow > 4 * TM * 1024 ? ROWS * kFrRow : 4 * TM * 1024;
   __shared__ __attribute__((aligned(16))) uint8_t lds[NW][kPiece];
   __shared__ float part[NW];
-  __shared__ int inexact[NW];
+  __shared__ unsigned votes[4];
 
   // tiles that share the larger operand run side by side on one XCD
   const int tiles_total = tiles_n * tiles_m, per_xcd = (tiles_total + 7) / 8;
@@ -134,17 +134,22 @@ __global__ void __launch_bounds__(64 * kFrWaves, 2) spgemm_fewrows_kernel(const 
   }
 
   float s_a = 1.0f;
+  const OutScale os = out_scale_of<IS_I8>(a);
   Fp16Quantiser qz;
   if constexpr (XF16) {
     if constexpr (XQ == 2) {
       float amax = 0.0f;
       if (a.range_mode == kRangePartials) {
-        for (int i = tid; i < a.npartial; i += 64 * NW) amax = fmaxf(amax, a.partial[i]);
+        for (int i = tid; i < a.npartial; i += 4 * 64 * NW) {  // (none is below 0; a range pass leaves at most 1024)
+          float p[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) p[j] = a.partial[i + j * 64 * NW < a.npartial ? i + j * 64 * NW : i];
+          amax = fmaxf(fmaxf(amax, fmaxf(p[0], p[1])), fmaxf(p[2], p[3]));
+        }
       } else {
         amax = range_of_fp16((const uint8_t*)a.X, (int64_t)a.M * a.K, tid, 64 * NW);
       }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+      amax = wave_max_magnitude(amax);
       if (lane == 0) part[wave] = amax;
       __syncthreads();
       amax = part[0];
@@ -155,10 +160,10 @@ __global__ void __launch_bounds__(64 * kFrWaves, 2) spgemm_fewrows_kernel(const 
     } else {
       s_a = a.act_scale[0];
     }
-    const bool wave_bad = __builtin_amdgcn_ballot_w64(qz.prepare(s_a, tid)) != 0;
-    if (lane == 0) inexact[wave] = wave_bad;
+    const unsigned wave_votes = qz.prepare(s_a, tid);
+    if (lane == 0 && wave < 4) votes[wave] = wave_votes;
     __syncthreads();
-    qz.refine = __builtin_amdgcn_readfirstlane(inexact[0] | inexact[1] | inexact[2] | inexact[3]) != 0;  // (threads 0..255)
+    qz.decide((unsigned)__builtin_amdgcn_readfirstlane((int)(votes[0] | votes[1] | votes[2] | votes[3])));  // (threads 0..255)
   } else if (IS_I8 && !raw_out) {
     s_a = a.act_scale[0];
   }
@@ -179,10 +184,11 @@ __global__ void __launch_bounds__(64 * kFrWaves, 2) spgemm_fewrows_kernel(const 
       for (int j = 0; j < XL; ++j) xr[slot][j] = v4i{0, 0, 0, 0};
     }
     if constexpr (XF16) {
+      const bool odd = qz.odd(xr[slot]);
 #pragma unroll
       for (int j = 0; j < XL; ++j) {  // 8 fp16 values -> 8 codes
         unsigned lo, hi;
-        qz.codes<XQ == 1>(xr[slot][j], lo, hi);
+        qz.codes<XQ == 1>(xr[slot][j], odd, lo, hi);
         const int r = 4 * j + (lane >> 4), col = (lane & 15) * 8;
         *(ep_v2u*)(xs + r * kFrRow + col) = ep_v2u{lo, hi};
         if (write_codes && r <= last_row && ks * kStepBytes + col < a.K)
@@ -240,14 +246,15 @@ __global__ void __launch_bounds__(64 * kFrWaves, 2) spgemm_fewrows_kernel(const 
   for (int j = 0; j < 8; ++j) {
     if constexpr (IS_I8) {
       raw[j] = sum[j >> 2][j & 3];
-      v[j] = epilogue_value<true>(raw[j], 0.0f, s_a * c8[j], b8[j], use_gelu);
+      v[j] = epilogue_value<true>(raw[j], 0.0f, s_a * c8[j], b8[j]);
     } else {
       raw[j] = 0;
-      v[j] = epilogue_value<false>(0, sum[j >> 2][j & 3], 1.0f, b8[j], use_gelu);
+      v[j] = epilogue_value<false>(0, sum[j >> 2][j & 3], 1.0f, b8[j]);
     }
   }
+  if (use_gelu) gelu_f32_x8(v);
   const int64_t m = m0 + unit_mt * 16 + (lane & 15);
-  if (m < a.M) store_8<IS_I8>(a, m, n_lane, v, raw);
+  if (m < a.M) store_8<IS_I8>(a, m, n_lane, v, raw, os);
 }
 
 // Rows per tile: a round of 32-row tiles takes about half as long again as one of 16-row tiles, whichever needs less.
@@ -264,6 +271,16 @@ bool fewrows_folds_quantiser(int64_t M, int64_t N, int64_t K, int resident) {
   return ceil_div(M, 16) * ceil_div(N, kRowBlock) <= 2 * (int64_t)resident && ceil_div(K, kStepBytes) <= kFrWaves * kFrBatch;
 }
 
+// 8 wavefronts to a workgroup that quantises, while there is at most one to a CU: a wavefront alone on its SIMD issues an instruction
+// every 2.1 ns, and quantising takes some 40 of them per 16 bytes of X and lane.  Up to four K steps, or a range of X found here
+// over no more than 96 KB, are too little work for it (graph replays, 4 / 8 wavefronts, us: given scale 333 x 1040 -> 520 5.9 / 5.0, 16 x 3072
+// -> 768 8.9 / 6.7, 64 x 1024 -> 1024 5.1 / 4.6, but 197 x 192 -> 768 3.9 / 4.1, 100 x 384 -> 384 3.9 / 4.1; range found here
+// 331 x 192 -> 384, 127 KB, 6.2 / 5.9, 197 x 192 -> 768, 75 KB, 5.5 / 5.8).
+static bool fewrows_wide(const GemmArgs& a, int tiles_n, int tiles_m, int resident) {
+  const bool long_range = a.range_mode == kRangeHere && (int64_t)a.M * a.K * 2 > 96 * 1024;
+  return (int64_t)tiles_n * tiles_m <= resident && (ceil_div(a.K, kStepBytes) > 4 || long_range);
+}
+
 bool fewrows_supports(const GemmArgs& a) {
   return (int64_t)a.K * 2 * 32 < ((int64_t)1 << 31);  // 32-bit lane offsets inside a tile's rows of X
 }
@@ -275,7 +292,10 @@ gpusq_status launch_fewrows(bool is_i8, const GemmArgs& a, int resident, hipStre
   const unsigned grid = (unsigned)ceil_div((int64_t)tiles_n * tiles_m, 8) * 8;
   const bool quantise = is_i8 && a.x_f16, given = a.range_mode == kRangeGiven;
 #define GPUSQ_FEWROWS(...) spgemm_fewrows_kernel<__VA_ARGS__><<<grid, 64 * kFrWaves, 0, s>>>(a, tiles_n, tiles_m, n_fast)
-  if (quantise && given) GPUSQ_FEWROWS(true, 1, 1);
+#define GPUSQ_FEWROWS_WIDE(...) spgemm_fewrows_kernel<__VA_ARGS__, false, 8><<<grid, 512, 0, s>>>(a, tiles_n, tiles_m, n_fast)
+  if (quantise && fewrows_wide(a, tiles_n, tiles_m, resident) && given) GPUSQ_FEWROWS_WIDE(true, 1, 1);
+  else if (quantise && fewrows_wide(a, tiles_n, tiles_m, resident)) GPUSQ_FEWROWS_WIDE(true, 1, 2);
+  else if (quantise && given) GPUSQ_FEWROWS(true, 1, 1);
   else if (quantise) GPUSQ_FEWROWS(true, 1, 2);
   else if (a.patch_P != 0 && is_i8 && tm == 2) GPUSQ_FEWROWS(true, 2, 0, true);
   else if (a.patch_P != 0 && is_i8) GPUSQ_FEWROWS(true, 1, 0, true);
@@ -286,6 +306,7 @@ gpusq_status launch_fewrows(bool is_i8, const GemmArgs& a, int resident, hipStre
   else if (tm == 2) GPUSQ_FEWROWS(false, 2, 0);
   else GPUSQ_FEWROWS(false, 1, 0);
 #undef GPUSQ_FEWROWS
+#undef GPUSQ_FEWROWS_WIDE
   return check_launch();
 }
 

@@ -319,12 +319,6 @@ gpusq_status launch_prune_n_of_m(const float* Win, float* Wout, int n_keep, int 
 __device__ __forceinline__ float load_as_f32(const float* p, int64_t i) { return p[i]; }
 __device__ __forceinline__ float load_as_f32(const _Float16* p, int64_t i) { return (float)p[i]; }
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
 // One wavefront per row (= per output channel), 4 rows per workgroup.
 // Rows of whole vectors of VEC elements: a batch of kRowBatch vectors per lane is requested before the first is used, and a row of
 // one batch stays in registers between the range and the codes; a longer one is read again.
@@ -365,7 +359,7 @@ __global__ void __launch_bounds__(256) quantize_rows_kernel(const T* __restrict_
         if (base >= vecs) break;
         load(base);
       }
-      amax = wave_max(amax);
+      amax = wave_max_magnitude(amax);
       s = (amax == 0.0f) ? 1.0f : __fdiv_rn(amax, qmax);
       if (lane == 0) scale[row] = s;
       if (vecs > kRowBatch * 64) load(0);
@@ -397,7 +391,7 @@ __global__ void __launch_bounds__(256) quantize_rows_kernel(const T* __restrict_
   } else {
     float amax = 0.0f;
     for (int64_t c = lane; c < cols; c += 64) amax = fmaxf(amax, fabsf(load_as_f32(x, c)));
-    amax = wave_max(amax);
+    amax = wave_max_magnitude(amax);
     s = (amax == 0.0f) ? 1.0f : __fdiv_rn(amax, qmax);
     if (lane == 0) scale[row] = s;
   }
@@ -438,7 +432,7 @@ constexpr int kAmaxMaxBlocks = 1024;  // per-block partial maxima kept in the ca
 
 __device__ __forceinline__ float block_max(float v) {
   __shared__ float part[4];
-  v = wave_max(v);
+  v = wave_max_magnitude(v);
   __syncthreads();  // a previous use of part[] has been read
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
   __syncthreads();
@@ -507,21 +501,22 @@ __global__ void __launch_bounds__(256) quantize_tensor_kernel(const T* __restric
   const float rs = scale_reciprocal(s);
   Fp16Quantiser qz;
   if constexpr (VEC == 8) {
-    __shared__ int inexact[4];
-    const bool bad = __builtin_amdgcn_ballot_w64(qz.prepare(s, threadIdx.x)) != 0;
-    if ((threadIdx.x & 63) == 0) inexact[threadIdx.x >> 6] = bad;
+    __shared__ unsigned votes[4];
+    const unsigned wave_votes = qz.prepare(s, threadIdx.x);
+    if ((threadIdx.x & 63) == 0) votes[threadIdx.x >> 6] = wave_votes;
     __syncthreads();
-    qz.refine = __builtin_amdgcn_readfirstlane(inexact[0] | inexact[1] | inexact[2] | inexact[3]) != 0;
+    qz.decide((unsigned)__builtin_amdgcn_readfirstlane((int)(votes[0] | votes[1] | votes[2] | votes[3])));
   }
   while (at < vecs) {
     unsigned q[U][2];
     if constexpr (VEC == 8) {
+      const bool odd = qz.odd(v);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (partial)  // uniform
-          qz.codes<false>(v[u], q[u][0], q[u][1]);
+          qz.codes<false>(v[u], odd, q[u][0], q[u][1]);
         else
-          qz.codes<true>(v[u], q[u][0], q[u][1]);
+          qz.codes<true>(v[u], odd, q[u][0], q[u][1]);
       }
     } else {
 #pragma unroll
@@ -929,7 +924,7 @@ __global__ void __launch_bounds__(256) prepare_weights_kernel(const float* __res
       if (base >= groups) break;
       load(base);
     }
-    amax = wave_max(amax);
+    amax = wave_max_magnitude(amax);
     if constexpr (WPR > 1) {
       __shared__ float part[ROWS * WPR];
       if (lane == 0) part[wave] = amax;

@@ -40,7 +40,7 @@ __device__ __forceinline__ int xcd_tile(int tiles_total) {
 template <bool IS_I8, int TN, int TM, int GELU = -1, int OUT = -1>
 __device__ __forceinline__ void wave_epilogue(const GemmArgs& a, const typename AccT<IS_I8>::type (&acc)[TN][TM],
                                               const float* cs, const float* bs, int n_tile, int n_wave, int64_t m_wave,
-                                              int lane, int tm_active = TM) {
+                                              int lane, const OutScale& os, int tm_active = TM) {
   const bool use_gelu = GELU >= 0 ? (GELU != 0) : ((a.epilogue & GPUSQ_EPI_GELU) != 0);
 #pragma unroll
   for (int g = 0; g < TN / 2; ++g) {  // pairs of fragments = 32 channels; this lane holds 8 of them
@@ -65,13 +65,14 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs& a, const typename 
           const int j = 4 * t + r;
           if constexpr (IS_I8) {
             raw[j] = acc[2 * g + t][mt][r];
-            v[j] = epilogue_value<true>(raw[j], 0.0f, c8[j], b8[j], use_gelu);
+            v[j] = epilogue_value<true>(raw[j], 0.0f, c8[j], b8[j]);
           } else {
             raw[j] = 0;
-            v[j] = epilogue_value<false>(0, acc[2 * g + t][mt][r], c8[j], b8[j], use_gelu);
+            v[j] = epilogue_value<false>(0, acc[2 * g + t][mt][r], c8[j], b8[j]);
           }
         }
-      if (m < a.M) store_8<IS_I8, OUT>(a, m, n, v, raw);
+      if (use_gelu) gelu_f32_x8(v);
+      if (m < a.M) store_8<IS_I8, OUT>(a, m, n, v, raw, os);
     }
   }
 }
@@ -115,6 +116,7 @@ __global__ void __launch_bounds__(256) spgemm_small_kernel(const GemmArgs a, con
     prm.fetch<IS_I8>(a, n_blk * BN + tid);
     prm.publish(cs, bs, tid);  // made visible by the barriers of the main loop
   }
+  const OutScale os = out_scale_of<IS_I8>(a);
   const int64_t k_bytes = (int64_t)a.K * ES;
   const int ksteps = (int)((k_bytes + kStepBytes - 1) / kStepBytes);
   const uint8_t* Xg = (const uint8_t*)a.X;
@@ -291,7 +293,7 @@ __global__ void __launch_bounds__(256) spgemm_small_kernel(const GemmArgs a, con
   for (int d = 0; d < D - 1; ++d)
     if (d < rest) compute_step(ks + d, d);  // workgroup-uniform
   __syncthreads();  // the per-channel constants written at the top are read below (also when K has no step at all)
-  wave_epilogue<IS_I8, TN, TM>(a, acc, cs, bs, n_blk * BN, n_blk * BN + wn * TN * 16, (int64_t)m_blk * BM + wm * TM * 16, lane);
+  wave_epilogue<IS_I8, TN, TM>(a, acc, cs, bs, n_blk * BN, n_blk * BN + wn * TN * 16, (int64_t)m_blk * BM + wm * TM * 16, lane, os);
 }
 
 template <bool IS_I8, int TN, int TM, int WN, int WM>

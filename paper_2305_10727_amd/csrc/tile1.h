@@ -501,7 +501,7 @@ __global__ void __launch_bounds__(512, 1) spgemm_tile_kernel(const GemmArgs a, c
     else if (lines)
       line_epilogue<IS_I8, GELU, OUT, true, NX, NX>(a, acc, p, s_a, s_out, r_out, n_wave, m_wave, lane, mine);
     else
-      batch_epilogue<IS_I8, GELU, OUT, NX>(a, acc, p, s_a, n_wave, m_wave, lane, mine);
+      batch_epilogue<IS_I8, GELU, OUT, NX>(a, acc, p, s_a, OutScale{s_out, r_out}, n_wave, m_wave, lane, mine);
     stores_behind = inside && mine > 0 && ksteps >= R::kStages;
   }
   wait_vm<0>();  // the copies requested past the end of the sequence land before the LDS is given up

@@ -301,7 +301,7 @@ __global__ void __launch_bounds__(512, 4) gemm_tile2_kernel(const GemmArgs a, co
         line_epilogue<IS_I8, GELU, OUT, true, kT2TM>(a, acc, prm[wn], s_a, s_out, r_out, n_wave, m_wave, lane, t.tm);
       }
     } else {
-      batch_epilogue<IS_I8, GELU, OUT, kT2TM>(a, acc, prm[wn], s_a, n_wave, m_wave, lane, t.tm);
+      batch_epilogue<IS_I8, GELU, OUT, kT2TM>(a, acc, prm[wn], s_a, OutScale{s_out, r_out}, n_wave, m_wave, lane, t.tm);
     }
   }
 }

@@ -158,7 +158,7 @@ __device__ __forceinline__ int64_t patch_step_offset(const GemmArgs& a, int ks) 
 // biases).
 template <bool IS_I8, int GELU, int OUT, int TM>
 __device__ __forceinline__ void batch_epilogue(const GemmArgs& a, const typename AccT<IS_I8>::type (&acc)[kTileTN][TM],
-                                             const float* p, float s_a, int n_wave, int64_t m_wave, int lane, int tm_active) {
+                                             const float* p, float s_a, const OutScale& os, int n_wave, int64_t m_wave, int lane, int tm_active) {
   constexpr bool RAW = IS_I8 && OUT == GPUSQ_I32;
   constexpr int OB = dtype_bytes(OUT);
   asm volatile("" : "+v"(lane));  // see line_epilogue
@@ -212,7 +212,7 @@ __device__ __forceinline__ void batch_epilogue(const GemmArgs& a, const typename
           for (int j = 0; j < 8; ++j) v[j] = __fmaf_rn(v[j], c8[j], b8[j]);
         }
         if constexpr (GELU != 0) gelu_f32_x8(v);
-        if (row_ok[mt]) store_8_at<IS_I8, OUT, true>(a, yrow[mt] + nb * OB, n_wave + nl, v, raw);
+        if (row_ok[mt]) store_8_at<IS_I8, OUT, true>(a, yrow[mt] + nb * OB, n_wave + nl, v, raw, os);
       }
     }
   }

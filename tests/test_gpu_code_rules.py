@@ -47,7 +47,7 @@ def _codes_of_every_entry_point(g, force_kernel, X, s):
         yield "spgemm_int8_xf16, kernel %d" % kernel, host(y)
 
 
-# scales under which values lie on code boundaries, so that the quantiser refines its products (0.03 ... 3/64), and others;
+# scales under which values lie on code boundaries (0.03 ... 3/64), and others;
 # negative scales decide as the division does too
 @pytest.mark.parametrize("s", [0.03, 0.07, 0.7, 0.75, 3 / 64, 4 / 127, 1.0, 0.1, -0.03, -0.75, -3 / 64, -4 / 127])
 def test_given_scale(g, force_kernel, s):
@@ -55,6 +55,38 @@ def test_given_scale(g, force_kernel, s):
         exp, _ = oracle.quantize_tensor_int8(X.astype(np.float32), scale=float(np.float32(s)))
         for name, q in _codes_of_every_entry_point(g, force_kernel, X, s):
             assert np.array_equal(q, exp), name
+
+
+def _reciprocals_that_agree(s):
+    """Of the rounded 1 / s and the floats above and below it, which give every finite fp16 value the code of the division by one
+    multiplication and one rounding to a whole number.  (The product of an fp16 value and a float is exact in 64 bits.)"""
+    x = np.arange(0, 0x7C00, dtype=np.uint16).view(np.float16)
+    exact = np.minimum(np.rint(x.astype(np.float32) / s), 127)
+    r = np.float32(1) / s
+    cand = (r, np.nextafter(r, np.float32(np.inf)), np.nextafter(r, np.float32(0)))
+    return tuple(bool((np.minimum(np.rint(x.astype(np.float64) * np.float64(c)), 127) == exact).all()) for c in cand)
+
+
+# a scale of each kind: the rounded reciprocal serves, only the one above or only the one below does, none (every product is refined)
+@pytest.mark.parametrize("kind", ["rounded", "above", "below", "none"])
+def test_reciprocal_next_to_the_rounded_one(g, force_kernel, kind):
+    own = [np.float32(a) / np.float32(127) for a in np.arange(0x3C00, 0x4000, dtype=np.uint16).view(np.float16)]  # of amax in [1, 2)
+    own += [np.float32(np.float32(v) / np.float32(c + 0.5)) for v, c in zip(np.linspace(0.5, 2, 200, dtype=np.float16), np.arange(200) % 127)]
+    want = {"rounded": lambda a: a[0], "above": lambda a: not a[0] and a[1], "below": lambda a: not a[0] and not a[1] and a[2], "none": lambda a: not any(a)}[kind]
+    scales = [s for s in own[::7] if want(_reciprocals_that_agree(s))][:4] or [s for s in own if want(_reciprocals_that_agree(s))][:4]
+    assert scales
+    for s in scales:
+        for X in _every_fp16()[:2]:
+            exp, _ = oracle.quantize_tensor_int8(X.astype(np.float32), scale=float(s))
+            for name, q in _codes_of_every_entry_point(g, force_kernel, X, s):
+                assert np.array_equal(q, exp), (name, s)
+        # the scale of the data's own range
+        top = np.float32(s) * np.float32(127)
+        X = _every_fp16()[0].copy()
+        X[np.abs(X.astype(np.float32)) > top] = 0
+        exp_q, exp_s = oracle.quantize_tensor_int8(X.astype(np.float32))
+        q, s_own = g.quantize_int8(dev(X), g.PER_TENSOR)
+        assert host(s_own)[0] == np.float32(exp_s) and np.array_equal(host(q), exp_q)
 
 
 # a scale by which quotients have no value (infinity by infinity, 0 by 0, NaN) or by which a finite value's product with the
