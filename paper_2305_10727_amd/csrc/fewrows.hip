@@ -263,12 +263,15 @@ static int fewrows_tm(int64_t M, int64_t N, int resident) {
   return 2 * ceil_div(ceil_div(M, 16) * blocks, resident) > 3 * ceil_div(ceil_div(M, 32) * blocks, resident) ? 2 : 1;
 }
 
-// Quantising on the way in pays while one batch of K steps per wavefront and two workgroups per CU carry the whole problem:
-// it then costs the GEMM about 2 us, and a quantiser's launch about 3 with the gap in front of it (given scale: 197 x 768 ->
-// 768 6.1 -> 5.2 us, 394 x 768 -> 768 6.8 -> 5.8, 197 x 768 -> 2304 6.6 -> 5.7; but 788 x 768 -> 768, 600 workgroups, 7.2 ->
-// 8.9, and 197 x 3072 -> 768, two batches, 8.6 -> 10.2).  The tiles are of 16 rows then: with 32 the 2304 take 7.2 us.
+// Quantising on the way in pays while one workgroup per CU carries the whole problem (eight wavefronts then, see below), or two do and
+// one batch of K steps per wavefront is all.  Given scale, quantiser and GEMM / both in one, us (graph replays; a launch less is
+// worth another microsecond where the host is what launches wait for): one workgroup per CU 320 x 1536 -> 768 6.9 / 5.4, 16 x 3072
+// -> 1024 7.5 / 6.7, 96 x 4096 -> 2304 8.8 / 8.0; two, up to 12 steps 224 x 1024 -> 2304 6.7 / 6.2, 160 x 1536 -> 2304 7.2 / 7.2, beyond 160 x
+// 3072 -> 2304 9.3 / 9.8, 160 x 4096 -> 2304 10.6 / 11.6; three 272 x 1024 -> 2304 7.3 / 8.8.  The tiles are of 16 rows then: with 32 the
+// 2304 channels take longer.
 bool fewrows_folds_quantiser(int64_t M, int64_t N, int64_t K, int resident) {
-  return ceil_div(M, 16) * ceil_div(N, kRowBlock) <= 2 * (int64_t)resident && ceil_div(K, kStepBytes) <= kFrWaves * kFrBatch;
+  const int64_t tiles = ceil_div(M, 16) * ceil_div(N, kRowBlock), ksteps = ceil_div(K, kStepBytes);
+  return tiles <= resident ? ksteps <= 40 : (tiles <= 2 * (int64_t)resident && ksteps <= kFrWaves * kFrBatch);
 }
 
 // 8 wavefronts to a workgroup that quantises, while there is at most one to a CU: a wavefront alone on its SIMD issues an instruction

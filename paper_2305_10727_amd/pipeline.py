@@ -102,9 +102,10 @@ class SparseLinear:
             _call.gpusq_gemm_fp16_dense(X, self.W_low, bias, self.Y, M, N, K, self.epilogue)
         return self.Y
 
-    def forward(self, X, bias, out_scale=None):
+    def forward(self, X, bias, out_scale=None, static=False):
+        """static=True (INT8 path): act_scale already holds a calibrated scale and is used as it is"""
         if self.precision == "int8":  # quantise and multiply in one call: one to three launches
-            _call.gpusq_linear_int8(X, G._TORCH_DT[X.dtype], self.packed, self.act_scale, 0, self.w_scale, bias, self.Y,
+            _call.gpusq_linear_int8(X, G._TORCH_DT[X.dtype], self.packed, self.act_scale, 1 if static else 0, self.w_scale, bias, self.Y,
                                     G._TORCH_DT[self.out_dtype], out_scale, self.Xq, self.workspace, self.M, self.N, self.K,
                                     self.epilogue)
             return self.Y
@@ -177,7 +178,8 @@ class EncoderBlockLinears:
     re-quantisation of a layer's output with the next layer's input scale is fused into its epilogue (qkv -> int8,
     fc1 -> GELU -> int8, which fc2 reads directly), so one block is six launches of the library:
         quantise x, qkv, [attention], proj, [residual + norm], quantise h, fc1 (GELU), fc2;
-    with few rows (problems of the latency kernel) qkv and fc1 quantise their fp16 input on the way in: four launches.
+    with few rows (problems of the latency kernel) qkv and fc1 quantise their fp16 input on the way in, each where its sizes
+    favour it: five or four launches.
     Attention and the normalisation are not part of the library: `attention(qkv_int8 [M,3D], out_int8 [M,D])` and
     `norm(proj_fp16 [M,D]) -> fp16 [M,D]` are the caller's (stubs in the tests and the report).  capture() records the
     whole sequence into a HIP graph, which takes the host out of the loop.
@@ -197,7 +199,8 @@ class EncoderBlockLinears:
         self.fc1.act_scale = scales["h"]
         self.fc2.act_scale = scales["g"]
         self.fc2.Xq = self.fc1.Y  # fc2 reads the codes fc1's epilogue wrote: no pass in between
-        # few rows (the latency kernel): qkv and fc1 quantise their fp16 input themselves, four launches per block
+        # few rows (the latency kernel): both qkv and fc1 quantise their fp16 input themselves, four launches per block, and nothing
+        # reads their codes, which are then not written; otherwise the one-call layer decides for each of them
         self.fold_quantise = self.qkv.takes_fp16_input() and self.fc1.takes_fp16_input()
         self.graph = None
 
@@ -210,8 +213,7 @@ class EncoderBlockLinears:
         if self.fold_quantise:
             self.qkv.gemm_from_f16(x, biases[0], self.scales["qkv"])
         else:
-            self.qkv.quantize_activations(x, static=True)
-            self.qkv.gemm(None, biases[0], self.scales["qkv"])
+            self.qkv.forward(x, biases[0], self.scales["qkv"], static=True)
         attention(self.qkv.Y, self.proj.Xq)
         h = self.proj.gemm(None, biases[1])
         if norm is not None:
@@ -219,8 +221,7 @@ class EncoderBlockLinears:
         if self.fold_quantise:
             self.fc1.gemm_from_f16(h, biases[2], self.scales["g"])
         else:
-            self.fc1.quantize_activations(h, static=True)
-            self.fc1.gemm(None, biases[2], self.scales["g"])
+            self.fc1.forward(h, biases[2], self.scales["g"], static=True)
         return self.fc2.gemm(None, biases[3])
 
     def capture(self, x, biases, attention, norm=None):

@@ -64,8 +64,8 @@ def _layer(g, X, packed, sw, b, M, N, K, scale=None, gelu=False):
 
 # the range of X found by every workgroup (small X) and by a pass of its own, the codes written by the first column of tiles,
 # fp32 activations and a problem of the tile kernels (quantiser and GEMM one behind the other); 8 wavefronts for a long range
-# (331 x 192) and for one workgroup of many steps
-@pytest.mark.parametrize("M,K,N,seed", SHAPES + [(700, 768, 512, 11), (4100, 256, 384, 12), (331, 192, 384, 13), (16, 1536, 64, 14)])
+# (331 x 192) and for one workgroup of many steps, several batches of them per wavefront
+@pytest.mark.parametrize("M,K,N,seed", SHAPES + [(700, 768, 512, 11), (4100, 256, 384, 12), (331, 192, 384, 13), (16, 1536, 64, 14), (20, 5120, 196, 15), (40, 3088, 64, 16)])
 @pytest.mark.parametrize("dtype", [np.float16, np.float32])
 @pytest.mark.parametrize("given", [False, True])
 def test_one_call_layer(g, M, K, N, seed, dtype, given):
