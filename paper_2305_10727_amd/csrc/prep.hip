@@ -439,26 +439,40 @@ __device__ __forceinline__ float block_max(float v) {
   return fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
 }
 
-// Per-tensor max |x|, first pass: every workgroup streams its share with 16-byte loads, two per thread in flight, and leaves one
-// partial maximum in the workspace; the quantising pass folds the partials (no atomics, nothing to clear beforehand).
+// The two passes of the per-tensor quantiser: the range, then the codes.  A workgroup takes blocks of 256 x 2 consecutive 16-byte
+// vectors, every gridDim.x-th one, two vectors in flight per thread; both passes have the same grid, so that a workgroup id,
+// and with it an XCD, meets the same blocks in both, and the second pass goes over them backwards: what the first one read last is
+// still in that XCD's L2 (4 MB each, read at 12 TB/s where HBM and the memory-side cache give 6 to 7).
+// Memory-bound, up to some 20 MB by what a workgroup does before its first code: fold the partial maxima, check its reciprocal
+// (Fp16Quantiser).  So X is asked for before that, and there are no more than 1024 workgroups.  With the grids apart, the second pass
+// forwards on 2048 workgroups and X waited for in front of the scale, both passes, us: 1576 x 768 fp16 5.9, now 5.2; 12544 x 512 10.3, 8.4;
+// 12608 x 768 fp16 12.2, 10.0, fp32 16.9, 14.4; 25216 x 3072 fp16 70, 68, fp32 126, 116; a given scale: 12544 x 512 6.1, 5.1, 12608 x 768 7.4,
+// 6.3.  (Four vectors in flight, 512 or 2048 workgroups: within 3 % or behind.)
+constexpr int kQuantVecs = 2, kQuantBlock = 256 * kQuantVecs;
+
 __device__ __forceinline__ float range_of_vec(const float4& v) { return fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))); }
 
+// Per-tensor max |x|: one partial maximum per workgroup into the workspace; the second pass folds them (no atomics, nothing to
+// clear beforehand).
 template <typename T>
 __global__ void __launch_bounds__(256) tensor_amax_kernel(const T* __restrict__ X, int64_t n, float* __restrict__ partial) {
-  constexpr int VEC = 16 / (int)sizeof(T);
+  constexpr int VEC = 16 / (int)sizeof(T), U = kQuantVecs;
   typedef _Float16 h8 __attribute__((ext_vector_type(8)));
   typedef unsigned u4 __attribute__((ext_vector_type(4)));
   const int64_t vecs = n / VEC;
   float amax = 0.0f;
   h8 m = h8(0);
-  const int64_t stride = (int64_t)gridDim.x * 512;
-  for (int64_t i = (int64_t)blockIdx.x * 512 + threadIdx.x; i < vecs; i += stride) {
-    const u4 a = ((const u4*)X)[i], b = ((const u4*)X)[i + 256 < vecs ? i + 256 : i];
-    if constexpr (VEC == 8) {
-      m = __builtin_elementwise_max(m, __builtin_bit_cast(h8, a & 0x7fff7fffu));
-      m = __builtin_elementwise_max(m, __builtin_bit_cast(h8, b & 0x7fff7fffu));
-    } else {
-      amax = fmaxf(amax, fmaxf(range_of_vec(__builtin_bit_cast(float4, a)), range_of_vec(__builtin_bit_cast(float4, b))));
+  const int64_t stride = (int64_t)gridDim.x * kQuantBlock;
+  for (int64_t i = (int64_t)blockIdx.x * kQuantBlock + threadIdx.x; i < vecs; i += stride) {
+    u4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = ((const u4*)X)[i + 256 * u < vecs ? i + 256 * u : i];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if constexpr (VEC == 8)
+        m = __builtin_elementwise_max(m, __builtin_bit_cast(h8, v[u] & 0x7fff7fffu));
+      else
+        amax = fmaxf(amax, range_of_vec(__builtin_bit_cast(float4, v[u])));
     }
   }
   if constexpr (VEC == 8) {
@@ -470,34 +484,66 @@ __global__ void __launch_bounds__(256) tensor_amax_kernel(const T* __restrict__ 
   if (threadIdx.x == 0) partial[blockIdx.x] = amax;
 }
 
-// The codes: consecutive lanes read consecutive 16-byte vectors, U per thread in flight.
+// The codes, with the scale of the partial maxima (OWN) or a given one.  A workgroup has blocks_each blocks, the first blocks_over
+// workgroups one more.
 // (Stored with the non-temporal hint the two passes take 60 us instead of 69 on 25216 x 3072 fp16, but the GEMM behind them
 // then finds its codes in HBM instead of the memory-side cache and loses more: 65792 x 1280 -> 5120 both together 394 -> 419.)
-template <typename T, int U>
+template <typename T, bool OWN>
 __global__ void __launch_bounds__(256) quantize_tensor_kernel(const T* __restrict__ X, int8_t* __restrict__ Q,
                                                               float* __restrict__ scale, const float* __restrict__ partial,
-                                                              int npartial, int64_t n) {
-  constexpr int VEC = 16 / (int)sizeof(T);
+                                                              int npartial, int64_t n, int blocks_each, int blocks_over,
+                                                              bool backwards) {
+  constexpr int VEC = 16 / (int)sizeof(T), U = kQuantVecs;
   typedef int i4 __attribute__((ext_vector_type(4)));
-  const int64_t vecs = n / VEC, stride = (int64_t)gridDim.x * 256 * U;
-  int64_t at = (int64_t)blockIdx.x * 256 * U + threadIdx.x;
+  constexpr int P = kAmaxMaxBlocks / 256;
+  float known[P];
+  auto ask = [&]() {
+    if constexpr (OWN) {
+#pragma unroll
+      for (int j = 0; j < P; ++j) known[j] = partial[(int)threadIdx.x + 256 * j < npartial ? threadIdx.x + 256 * j : 0];
+    } else {
+      known[0] = scale[0];
+    }
+  };
+  auto scale_of_known = [&]() {
+    if constexpr (!OWN) return known[0];
+    float amax = known[0];
+#pragma unroll
+    for (int j = 1; j < P; ++j) amax = fmaxf(amax, known[j]);
+    amax = block_max(amax);
+    const float s = (amax == 0.0f) ? 1.0f : __fdiv_rn(amax, 127.0f);
+    if (blockIdx.x == 0 && threadIdx.x == 0) scale[0] = s;
+    return s;
+  };
+  const int64_t vecs = n / VEC, stride = (int64_t)gridDim.x * kQuantBlock;
+  auto tail = [&](float s, float rs) {
+    if (blockIdx.x == 0 && vecs * VEC + threadIdx.x < n)
+      Q[vecs * VEC + threadIdx.x] = (int8_t)quantize_code(load_as_f32(X, vecs * VEC + threadIdx.x), s, rs);
+  };
+  if (vecs == 0) {  // fewer values than a vector, one workgroup
+    ask();
+    const float s = scale_of_known();
+    tail(s, scale_reciprocal(s));
+    return;
+  }
+  // The partial maxima or the scale are asked for first and the first vectors of X right behind them, without a condition: the scale
+  // and what is derived from it then take their time while X is on its way.
+  ask();
+  int left = blocks_each + ((int)blockIdx.x < blocks_over ? 1 : 0);  // this workgroup's blocks, at least one
+  const int64_t step = backwards ? -stride : stride;
+  int64_t at = (int64_t)blockIdx.x * kQuantBlock + (backwards ? (left - 1) * stride : 0) + threadIdx.x;
   i4 v[U];
   auto load = [&](int64_t i) {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (i + 256 * u < vecs) v[u] = ((const i4*)X)[i + 256 * u];
+    for (int u = 0; u < U; ++u) {
+      if constexpr (OWN)
+        v[u] = ((const i4*)X)[i + 256 * u < vecs ? i + 256 * u : vecs - 1];
+      else if (i + 256 * u < vecs)
+        v[u] = ((const i4*)X)[i + 256 * u];
+    }
   };
   load(at);
-  float s;
-  if (partial) {
-    float amax = 0.0f;
-    for (int i = threadIdx.x; i < npartial; i += 256) amax = fmaxf(amax, partial[i]);
-    amax = block_max(amax);
-    s = (amax == 0.0f) ? 1.0f : __fdiv_rn(amax, 127.0f);
-    if (blockIdx.x == 0 && threadIdx.x == 0) scale[0] = s;
-  } else {
-    s = scale[0];
-  }
+  const float s = scale_of_known();
   const float rs = scale_reciprocal(s);
   Fp16Quantiser qz;
   if constexpr (VEC == 8) {
@@ -507,17 +553,12 @@ __global__ void __launch_bounds__(256) quantize_tensor_kernel(const T* __restric
     __syncthreads();
     qz.decide((unsigned)__builtin_amdgcn_readfirstlane((int)(votes[0] | votes[1] | votes[2] | votes[3])));
   }
-  while (at < vecs) {
+  while (left > 0) {
     unsigned q[U][2];
     if constexpr (VEC == 8) {
       const bool odd = qz.odd(v);
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (partial)  // uniform
-          qz.codes<false>(v[u], odd, q[u][0], q[u][1]);
-        else
-          qz.codes<true>(v[u], odd, q[u][0], q[u][1]);
-      }
+      for (int u = 0; u < U; ++u) qz.codes<!OWN>(v[u], odd, q[u][0], q[u][1]);
     } else {
 #pragma unroll
       for (int u = 0; u < U; u += 2) {
@@ -527,8 +568,8 @@ __global__ void __launch_bounds__(256) quantize_tensor_kernel(const T* __restric
       }
     }
     const int64_t here = at;
-    at += stride;
-    if (at < vecs) load(at);
+    at += step;
+    if (--left > 0) load(at);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t i = here + 256 * u;
@@ -540,16 +581,20 @@ __global__ void __launch_bounds__(256) quantize_tensor_kernel(const T* __restric
       }
     }
   }
-  if (blockIdx.x == 0 && vecs * VEC + threadIdx.x < n)
-    Q[vecs * VEC + threadIdx.x] = (int8_t)quantize_code(load_as_f32(X, vecs * VEC + threadIdx.x), s, rs);
+  tail(s, rs);
+}
+
+// Workgroups of either pass for a tensor of that many bytes (no more than the workspace holds partial maxima).
+static int quantize_grid(int64_t bytes) {
+  const int64_t blocks = ceil_div(bytes / 16, kQuantBlock);
+  return (int)(blocks < 1 ? 1 : (blocks < kAmaxMaxBlocks ? blocks : kAmaxMaxBlocks));
 }
 
 template <typename T>
 static int launch_amax_typed(const T* X, int64_t n, float* partial, hipStream_t s) {
-  const int64_t want = ceil_div(n, 256 * 8 * 2);
-  const int blocks = (int)(want < kAmaxMaxBlocks ? want : kAmaxMaxBlocks);
-  tensor_amax_kernel<T><<<(unsigned)blocks, 256, 0, s>>>(X, n, partial);
-  return blocks;
+  const int grid = quantize_grid(n * (int64_t)sizeof(T));
+  tensor_amax_kernel<T><<<(unsigned)grid, 256, 0, s>>>(X, n, partial);
+  return grid;
 }
 
 int launch_amax(const void* X, gpusq_dtype dt, int64_t n, void* workspace, hipStream_t s) {
@@ -563,23 +608,18 @@ static gpusq_status quantize_typed(const T* X, int8_t* Xq, float* scale, int mod
   if (mode == GPUSQ_PER_ROW) {
     return launch_quantize_rows<T, 127>(X, Xq, scale, scale_is_input, rows, cols, s);
   }
-  const int64_t n = rows * cols;
-  const int64_t want = ceil_div(n * (int64_t)sizeof(T), 16 * 256 * 2);  // two 16-byte vectors per thread ...
-  // ... up to 2048 workgroups (every workgroup of the quantising pass first reduces the partial maxima: with 8192 of them the
-  // pass took 1.5 us longer on 12608 x 768 activations, with 1024 or fewer the large tensors slow down)
-  const unsigned blocks_q = (unsigned)(want < 2048 ? want : 2048);
-  int blocks_a = 0;
-  const float* partial = nullptr;
-  if (!scale_is_input) {
-    blocks_a = launch_amax_typed<T>(X, n, (float*)workspace, s);
-    partial = (const float*)workspace;
+  const int64_t n = rows * cols, bytes = n * (int64_t)sizeof(T);
+  const int grid = quantize_grid(bytes);
+  const int64_t blocks = ceil_div(bytes / 16, kQuantBlock);
+  const int each = (int)(blocks / grid), over = (int)(blocks % grid);
+  if (scale_is_input) {
+    quantize_tensor_kernel<T, false><<<(unsigned)grid, 256, 0, s>>>(X, Xq, scale, nullptr, 0, n, each, over, false);
+    return check_launch();
   }
-  // (large tensors take 4 vectors in flight: 25216 x 3072 fp32, both passes, 131 -> 123 us; 12608 x 768 fp16 would lose half a
-  // microsecond of 12)
-  if (n * (int64_t)sizeof(T) > ((int64_t)48 << 20))
-    quantize_tensor_kernel<T, 4><<<blocks_q, 256, 0, s>>>(X, Xq, scale, partial, blocks_a, n);
-  else
-    quantize_tensor_kernel<T, 2><<<blocks_q, 256, 0, s>>>(X, Xq, scale, partial, blocks_a, n);
+  // (large fp16 tensors, of which little is left in the L2s, forwards: as fast, and the GEMM behind them 2 % faster)
+  const bool backwards = sizeof(T) == 4 || bytes <= ((int64_t)96 << 20);
+  launch_amax_typed<T>(X, n, (float*)workspace, s);
+  quantize_tensor_kernel<T, true><<<(unsigned)grid, 256, 0, s>>>(X, Xq, scale, (const float*)workspace, grid, n, each, over, backwards);
   return check_launch();
 }
 

@@ -146,3 +146,19 @@ def test_int4_rows_under_a_given_scale(g, dtype, cols):
     exp, _ = oracle.quantize_rows_int4(X.astype(np.float32), scale=s)
     assert abs(exp).max() == 7
     assert np.array_equal(host(g.quantize_rows_int4(dev(X), scale=dev(s))[0]), exp)
+
+
+# the per-tensor quantiser at the edges of its vectors (8 or 4 values), of its blocks (512 vectors) and of its grid (up to 1024
+# workgroups, then several blocks to each, backwards in the second pass; fp16 beyond 96 MiB forwards)
+@pytest.mark.parametrize("dtype,n", [(np.float16, n) for n in (1, 7, 8, 9, 4095, 4096, 4097, 4194304, 4194305, 4198401, 9000007, 50331656)]
+                         + [(np.float32, n) for n in (1, 3, 4, 5, 2047, 2048, 2049, 2097152, 2097153, 2099201, 25165828)])
+def test_per_tensor_quantiser_over_its_grid(g, dtype, n):
+    X = (np.random.default_rng(n).standard_normal((1, n), dtype=np.float32) * 3).astype(dtype)
+    X[0, n - 1] = dtype(40)  # the largest value last: in the scalar tail, or the last vector
+    x = dev(X)
+    exp_q, exp_s = oracle.quantize_tensor_int8(X.astype(np.float32))
+    q, s = g.quantize_int8(x, g.PER_TENSOR)
+    assert host(s)[0] == np.float32(exp_s) and np.array_equal(host(q), exp_q)
+    given = np.float32(0.011)
+    exp_q, _ = oracle.quantize_tensor_int8(X.astype(np.float32), scale=float(given))
+    assert np.array_equal(host(g.quantize_int8(x, g.PER_TENSOR, scale=dev(np.array([given])))[0]), exp_q)
