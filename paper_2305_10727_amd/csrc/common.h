@@ -104,35 +104,79 @@ __device__ __forceinline__ void quantize_words(const float (&x)[N], float s, flo
 #pragma unroll
   for (int j = 0; j < N; j += 4) w[j / 4] = low_bytes(b[j], b[j + 1], b[j + 2], b[j + 3]);
 }
-// The codes of 8 values as bytes, packed into two words (value 0 in the low byte of `lo`): the same codes as
-// quantize_codes, with less arithmetic in the common case, for epilogues that are bound by the vector ALU.
-//   * band test |fract(t) - 0.5| < 2^-14 instead of |t| 2^-21: for |t| < 128 it is the wider of the two, and for
-//     |t| >= 128 the quotient exceeds 127.5 whenever t does, so both clamp to the same code; written as "not >=", it
-//     also sends every NaN to the exact path;
-//   * otherwise clamp first (for finite t, rint and the clamp to whole numbers commute), then add 1.5 * 2^23: the sum is
-//     rounded to a whole number half-to-even by the addition itself, and the low byte of its bit pattern is the
-//     two's-complement code.
+// The codes of 8 values as bytes, the same ones as quantize_codes, with less arithmetic in the common case, for epilogues that are
+// bound by the vector ALU.  In units of 2^-16: u = x (65536 r) + 32769 as a whole number, whose upper half is the code, floor(x / s +
+// 1/2), and whose lower half says how far the quotient is from a boundary between codes.
+//   * |u - (65536 x / s + 32769)| < 1.75 for |x / s| <= 127 (beyond, both clamp to the same code): half a unit from r (2^-24 of 127 2^16),
+//     a quarter from the rounding of the fused multiply-add below 2^23, less than one from the conversion, which drops the fraction.
+//     The quotient rounded to fp32 is within a quarter of a unit of x / s.  So a lower half of 3 or more puts it strictly between the
+//     two boundaries of that code: 3 - 1.75 - 1 >= 1/4 above the lower one, 65535 + 1.75 - 1 <= 65536 - 1/4 below the upper one.  Other
+//     values go to the division: 3 lower halves in 65536.
+//   * The conversion saturates: +infinity to a lower half of 65535 and the code 127, -infinity and NaN (0) to a lower half of 0, that
+//     is to the division.  A reciprocal that leaves no room for the factor 65536 (|s| below 2^-111) or is not finite sends every value
+//     there.
+// Four and a half vector instructions a value with the question, the clamp and the packing.
+struct ByteQuantiser {
+  float s, r16;
+  __device__ __forceinline__ ByteQuantiser(float scale, float r) : s(scale), r16(fabsf(r) < 0x1p111f ? r * 65536.0f : __builtin_nanf("")) {
+    asm("" : "+v"(r16));  // (the choice is made once, not for every value)
+  }
+  __device__ __forceinline__ void units(const float (&x)[8], int (&u)[8]) const {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float t = __fmaf_rn(x[j], r16, 32769.0f);
+      asm("v_cvt_i32_f32 %0, %1" : "=v"(u[j]) : "v"(t));  // (saturates, NaN gives 0: a C++ cast would promise neither)
+    }
+  }
+  static __device__ __forceinline__ bool some_near(const int (&u)[8]) {  // wavefront-uniform
+    unsigned m;  // of the lower halves the least (16-bit operations: the upper halves do not matter)
+    asm("v_min3_u16 %0, %1, %2, %3" : "=v"(m) : "v"(u[0]), "v"(u[1]), "v"(u[2]));
+    asm("v_min3_u16 %0, %0, %1, %2" : "+v"(m) : "v"(u[3]), "v"(u[4]));
+    asm("v_min3_u16 %0, %0, %1, %2" : "+v"(m) : "v"(u[5]), "v"(u[6]));
+    asm("v_min_u16 %0, %0, %1" : "+v"(m) : "v"(u[7]));
+    return __builtin_amdgcn_ballot_w64((unsigned short)m < 3) != 0;
+  }
+  // Each lane divides one of its values that ask for it at a time (a second one in a lane is rare, but where all of them do).  Marked
+  // as unlikely, so that it stands behind the epilogue's own code: eight IEEE divisions in line, jumped over 15 times out of 16, and two
+  // instructions more for every value took 49 us for 25216 x 768 -> 2304 where this takes 46, 31.6 for 50432 x 192 -> 768 + GELU (29.0),
+  // 10.5 for 6304 x 384 -> 1000 (8.6).
+  __device__ __forceinline__ void settle(const float (&x)[8], int (&u)[8]) const {
+    if (__builtin_expect(some_near(u), 0)) {
+      do {
+        int which = 8;
+        float xv = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const bool near = ((unsigned)u[j] & 0xFFFFu) < 3u;
+          which = near ? j : which;
+          xv = near ? x[j] : xv;
+        }
+        const int code = finish_code(__fdiv_rn(xv, s)) * 65536 + 32768;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) u[j] = which == j ? code : u[j];
+      } while (some_near(u));
+    }
+  }
+  // value 0 in the low byte of `lo`
+  static __device__ __forceinline__ void pack(const int (&u)[8], unsigned& lo, unsigned& hi) {
+    unsigned c[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int least_code = -127 * 65536, most_code = 127 * 65536 + 65535;
+      const int v = u[j] < least_code ? least_code : u[j];
+      c[j] = (unsigned)(v > most_code ? most_code : v);
+    }
+    // byte 2 of each (v_perm_b32: selector bytes 0..3 take bytes of the second operand, 4..7 of the first, 0x0c zero)
+    lo = __builtin_amdgcn_perm(c[1], c[0], 0x0c0c0602u) | __builtin_amdgcn_perm(c[3], c[2], 0x06020c0cu);
+    hi = __builtin_amdgcn_perm(c[5], c[4], 0x0c0c0602u) | __builtin_amdgcn_perm(c[7], c[6], 0x06020c0cu);
+  }
+};
 __device__ __forceinline__ void quantize_bytes8(const float (&x)[8], float s, float r, unsigned& lo, unsigned& hi) {
-  float t[8];
-  bool exact_path = false;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    t[j] = x[j] * r;
-    exact_path |= !(fabsf(__builtin_amdgcn_fractf(t[j]) - 0.5f) >= 0x1p-14f);
-  }
-  unsigned b[8];
-  if (__builtin_amdgcn_ballot_w64(exact_path) != 0) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) b[j] = (unsigned)finish_code(__fdiv_rn(x[j], s));
-  } else {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) b[j] = __float_as_uint(__builtin_amdgcn_fmed3f(t[j], -127.0f, 127.0f) + 12582912.0f);
-  }
-  // v_perm_b32: selector bytes 0..3 take bytes of the second operand, 4..7 of the first, 0x0c gives zero
-  const unsigned p01 = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), p23 = __builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u);
-  const unsigned p45 = __builtin_amdgcn_perm(b[5], b[4], 0x0c0c0400u), p67 = __builtin_amdgcn_perm(b[7], b[6], 0x0c0c0400u);
-  lo = p01 | (p23 << 16);
-  hi = p45 | (p67 << 16);
+  const ByteQuantiser q(s, r);
+  int u[8];
+  q.units(x, u);
+  q.settle(x, u);
+  q.pack(u, lo, hi);
 }
 __device__ __forceinline__ int quantize_code(float x, float s, float r, float qmax = 127.0f) {
   const float xs[1] = {x};

@@ -162,3 +162,33 @@ def test_per_tensor_quantiser_over_its_grid(g, dtype, n):
     given = np.float32(0.011)
     exp_q, _ = oracle.quantize_tensor_int8(X.astype(np.float32), scale=float(given))
     assert np.array_equal(host(g.quantize_int8(x, g.PER_TENSOR, scale=dev(np.array([given])))[0]), exp_q)
+
+
+# fp32 values on the boundaries between codes and up to 3 units in the last place beside them, through the fp32 quantiser and through
+# every kernel's int8 output (zero activations: the value quantised is the bias); scales with a mantissa of ones, too small for
+# the factor 65536 of the reciprocal, huge, negative, zero
+@pytest.mark.parametrize("s", [0.03, 1 / 3, 4 / 127, 2.0 ** -7, float(np.nextafter(np.float32(0.5), np.float32(0))), -0.07, 1e-3, 3e-34, 1e-36, 1e30, 0.0])
+def test_fp32_codes_beside_their_boundaries(g, force_kernel, s):
+    s = np.float32(s)
+    h = (np.arange(-131, 131) + 0.5).astype(np.float32) * s
+    steps = [h]
+    for way in (np.float32(np.inf), np.float32(-np.inf)):
+        v = h
+        for _ in range(3):
+            v = np.nextafter(v, way)
+            steps.append(v)
+    x = np.concatenate(steps + [np.array([0.0, -0.0, np.inf, -np.inf, np.nan, 3e38, -3e38, 1e-40, 6e4 * s, -6e4 * s], np.float32)])
+    x = np.resize(x, 2048).astype(np.float32)
+    with np.errstate(all="ignore"):
+        exp, _ = oracle.quantize_tensor_int8(x[None], scale=float(s))
+    scale = dev(np.array([s]))
+    assert np.array_equal(host(g.quantize_int8(dev(x[None]), g.PER_TENSOR, scale=scale)[0]), exp)
+    K, one = 128, dev(np.ones(1, np.float32))
+    for N in (2048, 2044):  # whole 16-byte pieces of int8; 4-byte ones
+        packed = g.prepare_weights(torch.zeros((N, K), device="cuda"), torch.int8)["packed"]
+        for M in (5, 300):
+            X = torch.zeros((M, K), dtype=torch.int8, device="cuda")
+            for kernel in (0, 1, 2, 3, 4):
+                force_kernel(kernel)
+                y = host(g.spgemm_int8(X, packed, N, act_scale=one, w_scale=torch.zeros(N, device="cuda"), bias=dev(x[:N]), out_dtype=torch.int8, out_scale=scale))
+                assert np.array_equal(y, np.broadcast_to(exp[:, :N], (M, N))), (N, M, kernel)
