@@ -73,7 +73,7 @@ __device__ __forceinline__ void quantize_codes(const float (&x)[N], float s, flo
     t[j] = x[j] * r;
     near_half |= !(fabsf(__builtin_amdgcn_fractf(t[j]) - 0.5f) >= fabsf(t[j]) * 0x1p-21f);
   }
-  if (__builtin_amdgcn_ballot_w64(near_half) != 0) {  // some element of some lane sits next to a rounding boundary
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(near_half) != 0, 0)) {  // some element of some lane sits next to a rounding boundary
 #pragma unroll
     for (int j = 0; j < N; ++j) t[j] = __fdiv_rn(x[j], s);
   }
@@ -97,7 +97,7 @@ __device__ __forceinline__ void quantize_words(const float (&x)[N], float s, flo
     near_half |= !(fabsf(__builtin_amdgcn_fractf(t[j]) - 0.5f) >= fabsf(t[j]) * 0x1p-21f);
     b[j] = __float_as_uint(__builtin_amdgcn_fmed3f(t[j], -qmax, qmax) + 12582912.0f);
   }
-  if (__builtin_amdgcn_ballot_w64(near_half) != 0) {
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(near_half) != 0, 0)) {
 #pragma unroll
     for (int j = 0; j < N; ++j) b[j] = (unsigned)finish_code(__fdiv_rn(x[j], s), qmax);
   }
@@ -256,7 +256,7 @@ struct Fp16Quantiser {
   __device__ __forceinline__ void codes(i4 raw, bool odd, unsigned& lo, unsigned& hi) const {
     const h8 x = __builtin_bit_cast(h8, raw);
     float y[8];
-    if (refine) {
+    if (__builtin_expect(refine, 0)) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const float t = __builtin_amdgcn_fmed3f((float)x[j] * r, -1024.0f, 1024.0f);
@@ -266,7 +266,7 @@ struct Fp16Quantiser {
 #pragma unroll
       for (int j = 0; j < 8; ++j) y[j] = __builtin_fmaf((float)x[j], r, 12582912.0f);
     }
-    if (odd) {
+    if (__builtin_expect(odd, 0)) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) y[j] = y[j] == y[j] ? y[j] : 12582912.0f;
     }
