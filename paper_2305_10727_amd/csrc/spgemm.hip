@@ -341,8 +341,8 @@ int set_forced_kernel(int kernel) {
   return g_forced_kernel.exchange(kernel >= 0 && kernel <= 4 ? kernel : -1);
 }
 
-// Estimated run time (microseconds, fitted to traces and timings of the kernel on MI355X) of one tile of 64*tm rows: a
-// K step costs nearly the same whatever tm (a short tile copies and reads whole operands and only leaves out the matrix
+// The estimate that decides which problems may quantise fp16 activations on their way into the small kernel (see kernel_choice), of
+// the tile kernel in full and tail tiles of whole 64-row units: run time (microseconds) of one tile of 64*tm rows.  A K step costs nearly the same whatever tm (a short tile copies and reads whole operands and only leaves out the matrix
 // instructions of the slabs it does not have: 1.1 us for tm = 4, about 0.075 us less per slab left out), the epilogue
 // scales with the rows stored and is larger with GELU.
 // `busy` is the fraction of the CUs that have a workgroup: the fewer run, the faster each one's K steps (the chip runs
@@ -376,7 +376,7 @@ static int grid_for(const TilePlan& p, int resident) { return (int)ceil_div(p.to
 
 constexpr int kTileTM = 4;  // 64-row units of the highest tile
 
-// The plan in units of 64 rows by whose estimate the kernel is chosen (what runs is even_plan's, which is no longer).  Candidates: full tiles of 64, 128, 192 or 256
+// The plan of that estimate (what runs is even_plan's).  Candidates: full tiles of 64, 128, 192 or 256
 // rows, either over all of M, or for as many whole rounds over the resident
 // workgroups as the problem has with the remaining rows in tail tiles of 64..64*full_tm rows; the one whose busiest
 // workgroup finishes first wins.
@@ -413,12 +413,8 @@ static TilePlan make_plan(int M, int N, int resident, int ksteps, bool gelu) {
 }
 
 // Which kernel a problem takes: 0 = small kernel with 64 x 64 tiles, 1 = small kernel with 128 x 128 tiles, 2 = tile
-// kernel.  The estimated run times decide (microseconds, fitted to graph-replayed launches on MI355X for M = 197 ... 6304): the small
-// kernel keeps two workgroups per CU busy, costs about 0.7 us + 0.45 us per K step per round of 512 workgroups and never less than what
-// one workgroup's chain of loads takes; the tile kernel costs its plan's makespan plus the start-up of its pipeline.
-// With few rows (one image: M = 197) the tile kernel has too few tiles for the chip and the small kernel is about
-// twice as fast; from a few thousand rows on the tile kernel wins.  fused_patches: the patch gather exists in the tile
-// kernel only, so that mode keeps the plain size rule.
+// kernel with one workgroup per CU, 3 = with two, 4 = the kernel for few rows.  fused_patches: the patch gather exists in kernels 2 and 4
+// only.
 // Few rows: 4 (the kernel with K split over its wavefronts), 0 (the 64 x 64 tiles) or -1 (by the estimates), by how many of the
 // former's 64-channel x 32-row tiles each CU gets.  Two of its workgroups run side by side on a CU (int8; fp16: three), and where
 // K has few steps another round costs most of a launch.  Timed at 7 widths, which agree; 768 channels, few rows / 64 x 64 tiles /
@@ -436,7 +432,42 @@ static int few_rows_choice(bool is_i8, int64_t M, int64_t N, int64_t ksteps, int
 }
 // Of the two small kernels: 64 x 64 tiles while these fit one round of two workgroups per CU, 128 x 128 beyond.
 static int small_choice(int64_t M, int64_t N, int resident) { return ceil_div(M, 64) * ceil_div(N, 64) <= 2 * (int64_t)resident ? 0 : 1; }
-static int kernel_choice(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu, int resident, bool fused_patches = false) {
+
+// Whole 128-byte steps, more rows than the kernel for few of them takes: run times in microseconds, fitted to 1515 sizes timed on MI355X (M
+// 600 ... 65792, N 64 ... 5120, K 64 ... 5120, both types, with and without GELU, fp16 and int8 output, three buffers in turn; kernel 2 to 6 %,
+// kernel 0 to 8 %).  Kernel 2: the even plan's rounds r over the CUs with u units of 32 rows in each on the busiest CU; a K step is faster with
+// fewer CUs at work (the board's power limit).  Kernel 0: rounds of 512 workgroups and the chain of one.
+struct EvenRounds {
+  double r, u, busy;
+};
+static EvenRounds even_rounds(const EvenPlan& p, int resident) {
+  const int64_t total = even_total(p), r = ceil_div(total, resident);
+  const int64_t most = r * p.units + ceil_div((int64_t)p.higher * p.tiles_n, resident);
+  return EvenRounds{(double)r, (double)most / (double)r, total < resident ? (double)total / resident : 1.0};
+}
+static double estimate_kernel2(const EvenRounds& e, bool is_i8, bool gelu, int64_t ksteps) {
+  const double step = 0.135 + 0.121 * e.u, epi = is_i8 ? (gelu ? 0.85 : 0.5) : (gelu ? 0.70 : 0.44);
+  return 3.4 + e.r * (ksteps * (step > 0.42 ? step : 0.42) * (0.49 + 0.51 * e.busy) + 0.7 + epi * e.u);
+}
+static double estimate_kernel0(int64_t wgs64, int resident, bool is_i8, bool gelu, int64_t ksteps) {
+  const double epi = is_i8 ? (gelu ? 2.05 : 1.65) : (gelu ? 1.85 : 1.5);
+  return 2.6 + 0.19 * ksteps + (0.32 * ksteps + epi) * (double)wgs64 / (2.0 * resident);
+}
+// Of those sizes the estimates and the lines below pick a kernel 0.8 % behind the fastest on average, where the plan in units of 64 rows and
+// a line by widths (kernel 3 for N <= 1536, K <= 1024, no GELU) were 3.6 % behind: 2096 x 2752 -> 1728 fp16 + GELU 38.4 -> 23.1 us, 12608 x 768 -> 768
+// int8 13.4 -> 11.2, 12544 x 512 -> 512 8.6 -> 7.8, 61579 x 128 -> 128 11.7 -> 7.5.
+// Kernel 3's 64- and 128-row tiles on two workgroups per CU are ahead at the heights that fit them, with few K steps: one round of 2 units,
+// or of 8 while its own tiles are one round; two rounds of up to 5 (medians 2 to 9 % ahead; 12544 x 512 -> 1536 int8 output 15.7 / 14.1 us, 10216 x
+// 384 -> 2048 14.5 / 12.6, 1790 x 192 -> 1792 fp16 6.4 / 5.8; int8 with GELU at 2 units 6 % behind).  Beyond 8 steps even or behind, at all other
+// heights 2 to 20 % behind.
+static bool kernel3_ahead(const EvenRounds& e, bool is_i8, bool gelu, int64_t M, int64_t N, int64_t ksteps, int resident) {
+  const int64_t tiles = ceil_div(M, 128) * ceil_div(N, kTileBN);
+  if (ksteps > 8) return false;
+  if (e.r == 1) return (e.u > 1 && e.u <= 2 && !(is_i8 && gelu)) || (e.u > 7 && tiles < 2 * (int64_t)resident);
+  return e.r == 2 && e.u <= 5;
+}
+
+static int kernel_choice(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu, int resident, bool fused_patches = false, bool x_f16 = false) {
   const int64_t k_bytes = K * (is_i8 ? 1 : 2);
   const int64_t ksteps = ceil_div(k_bytes, kStepBytes);
   const int64_t wgs64 = ceil_div(M, 64) * ceil_div(N, 64);
@@ -462,22 +493,21 @@ static int kernel_choice(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu,
     return ksteps <= (is_i8 ? 2 : 4) && ceil_div(M, 128) * ceil_div(N, 128) <= 2 * (int64_t)resident ? 1 : 2;
   }
   if (fused_patches) return 2;
-  // Between the two tile kernels the times measured against kernel 2 while its tiles came in steps of 64 rows decide (every linear
-  // layer of the ViT-B, Swin-B, ViT-L and ViT-H workloads, FP16 and INT8, with hot and with cold buffers, the two kernels timed in
-  // turn; they were within 10 % of each other almost everywhere): the kernel with two workgroups per CU was ahead, by 15-20 %, on
-  // layers with few output channels, short K and no GELU (the attention projections and the QKV layer of the narrow models: few
-  // tiles per CU); for FP16 only from 1024 output channels on (below that up to 14 % behind once the activations come from HBM).
-  // The single-workgroup kernel keeps the wide layers, the GELU layers and every long-K layer, where its deeper ring hides the
-  // latency of cold activations (the other kernel 10-25 % behind there on cold buffers).
-  const int tile_kernel = (N <= 1536 && K <= 1024 && !gelu && (is_i8 || N >= 1024)) ? 3 : 2;
-  if (wgs64 > 16 * resident) return tile_kernel;  // far beyond the crossover with the small kernel: skip the planning
-  const double per_round = 0.7 + 0.45 * ksteps, chain = 3.6 + 0.25 * ksteps;
-  const double throughput = 4.0 + per_round * (double)wgs64 / (2.0 * resident);
-  const double est_small = chain > throughput ? chain : throughput;
-  const TilePlan p = make_plan((int)M, (int)N, resident, (int)ksteps, gelu);
-  const int grid = grid_for(p, resident);
-  const double est_tile = plan_makespan(p, grid, (int)ksteps, gelu, (double)(p.total < grid ? p.total : grid) / resident) + 2.8;
-  return est_small < est_tile ? 0 : tile_kernel;
+  if (x_f16) {
+    // Which problems the small kernel quantises fp16 activations for was settled by an estimate of the tile kernel in units of 64 rows
+    // and is kept: a caller may have built on it.
+    if (wgs64 > 16 * resident) return 2;
+    const double per_round = 0.7 + 0.45 * ksteps, chain = 3.6 + 0.25 * ksteps;
+    const double throughput = 4.0 + per_round * (double)wgs64 / (2.0 * resident);
+    const double est_small = chain > throughput ? chain : throughput;
+    const TilePlan p = make_plan((int)M, (int)N, resident, (int)ksteps, gelu);
+    const int grid = grid_for(p, resident);
+    const double est_tile = plan_makespan(p, grid, (int)ksteps, gelu, (double)(p.total < grid ? p.total : grid) / resident) + 2.8;
+    return est_small < est_tile ? 0 : 2;
+  }
+  const EvenRounds e = even_rounds(even_plan(M, N, resident, (int)ksteps, gelu), resident);
+  if (wgs64 <= 16 * resident && estimate_kernel0(wgs64, resident, is_i8, gelu, ksteps) < estimate_kernel2(e, is_i8, gelu, ksteps)) return 0;
+  return kernel3_ahead(e, is_i8, gelu, M, N, ksteps, resident) ? 3 : 2;
 }
 
 gpusq_status plan_spgemm(bool is_i8, int64_t M, int64_t N, int64_t K, int epilogue, int cus, int32_t* out) {
@@ -513,28 +543,28 @@ gpusq_status plan_spgemm(bool is_i8, int64_t M, int64_t N, int64_t K, int epilog
 // launched over and over with the same sizes, and planning (a dozen candidate plans, each walked over every workgroup)
 // takes the host several microseconds, which is what a launch of a 10 us GEMM is bound by when it is repeated.
 struct Decision {
-  bool is_i8, gelu, patches;
+  bool is_i8, gelu, patches, x_f16;
   int forced;  // the forced kernel when the decision was taken, -1 for none
   int64_t M, N, K;
   int resident, choice;
   TilePlan plan;  // valid when choice == 3
   EvenPlan even;  // valid when choice == 2, and when it is 1 for a ragged K within kernel 2's limits
 };
-static const Decision& decide(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu, int resident, bool patches) {
+static const Decision& decide(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu, int resident, bool patches, bool x_f16 = false) {
   constexpr int kSlots = 16;
   thread_local Decision cache[kSlots];
   thread_local int used = 0, next = 0;
   const int forced = g_forced_kernel.load(std::memory_order_relaxed);
   for (int i = 0; i < used; ++i) {
     const Decision& d = cache[i];
-    if (d.M == M && d.N == N && d.K == K && d.is_i8 == is_i8 && d.gelu == gelu && d.patches == patches && d.forced == forced &&
-        d.resident == resident)
+    if (d.M == M && d.N == N && d.K == K && d.is_i8 == is_i8 && d.gelu == gelu && d.patches == patches && d.x_f16 == x_f16 &&
+        d.forced == forced && d.resident == resident)
       return d;
   }
   Decision& d = cache[next];
   next = (next + 1) % kSlots;
   if (used < kSlots) ++used;
-  d = Decision{is_i8, gelu, patches, forced, M, N, K, resident, kernel_choice(is_i8, M, N, K, gelu, resident, patches), TilePlan{}, EvenPlan{}};
+  d = Decision{is_i8, gelu, patches, x_f16, forced, M, N, K, resident, kernel_choice(is_i8, M, N, K, gelu, resident, patches, x_f16), TilePlan{}, EvenPlan{}};
   const int64_t k_bytes = K * (is_i8 ? 1 : 2);
   const bool limits = k_bytes < ((int64_t)1 << 24) && N < ((int64_t)1 << 25);  // (as in kernel_choice)
   if (d.choice == 2 || (d.choice == 1 && limits)) d.even = even_plan(M, N, resident, (int)ceil_div(k_bytes, kStepBytes), gelu);
@@ -547,7 +577,7 @@ static gpusq_status launch_typed(const GemmArgs& a, hipStream_t s) {
   const int64_t k_bytes = (int64_t)a.K * (IS_I8 ? 1 : 2);
   const bool gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
   const int resident = num_cus();
-  const Decision& dec = decide(IS_I8, a.M, a.N, a.K, gelu, resident, a.patch_P != 0);
+  const Decision& dec = decide(IS_I8, a.M, a.N, a.K, gelu, resident, a.patch_P != 0, a.x_f16 != 0);
   int choice = dec.choice;
   // The 128 x 128 tiles are the choice for fp16 and int32 output: the narrow lines of int8 output, and quantising fp16 X, cost them more
   // than the other kernels (6304 x 192 -> 576 int8 output 9.0 us, kernel 2 7.6; 50432 x 192 -> 64 9.4, 64 x 64 tiles 8.9, kernel 2 10.5;
