@@ -121,12 +121,14 @@ struct ByteQuantiser {
   __device__ __forceinline__ ByteQuantiser(float scale, float r) : s(scale), r16(fabsf(r) < 0x1p111f ? r * 65536.0f : __builtin_nanf("")) {
     asm("" : "+v"(r16));  // (the choice is made once, not for every value)
   }
+  static constexpr unsigned short kNear = 3;  // a lower half below it: near a boundary
+  __device__ __forceinline__ void units(float x, int& u) const {
+    const float t = __fmaf_rn(x, r16, 32769.0f);
+    asm("v_cvt_i32_f32 %0, %1" : "=v"(u) : "v"(t));  // (saturates, NaN gives 0: a C++ cast would promise neither)
+  }
   __device__ __forceinline__ void units(const float (&x)[8], int (&u)[8]) const {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float t = __fmaf_rn(x[j], r16, 32769.0f);
-      asm("v_cvt_i32_f32 %0, %1" : "=v"(u[j]) : "v"(t));  // (saturates, NaN gives 0: a C++ cast would promise neither)
-    }
+    for (int j = 0; j < 8; ++j) units(x[j], u[j]);
   }
   static __device__ __forceinline__ bool some_near(const int (&u)[8]) {  // wavefront-uniform
     unsigned m;  // of the lower halves the least (16-bit operations: the upper halves do not matter)
@@ -134,7 +136,7 @@ struct ByteQuantiser {
     asm("v_min3_u16 %0, %0, %1, %2" : "+v"(m) : "v"(u[3]), "v"(u[4]));
     asm("v_min3_u16 %0, %0, %1, %2" : "+v"(m) : "v"(u[5]), "v"(u[6]));
     asm("v_min_u16 %0, %0, %1" : "+v"(m) : "v"(u[7]));
-    return __builtin_amdgcn_ballot_w64((unsigned short)m < 3) != 0;
+    return __builtin_amdgcn_ballot_w64((unsigned short)m < kNear) != 0;
   }
   // Each lane divides one of its values that ask for it at a time (a second one in a lane is rare, but where all of them do).  Marked
   // as unlikely, so that it stands behind the epilogue's own code: eight IEEE divisions in line, jumped over 15 times out of 16, and two
@@ -147,7 +149,7 @@ struct ByteQuantiser {
         float xv = 0.0f;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-          const bool near = ((unsigned)u[j] & 0xFFFFu) < 3u;
+          const bool near = (unsigned short)u[j] < kNear;
           which = near ? j : which;
           xv = near ? x[j] : xv;
         }

@@ -921,6 +921,61 @@ gpusq_status launch_pack(const void* values, const uint8_t* meta, void* packed, 
 // With a thread per 32 elements, LDS for the rows and one load in flight per thread, int8: 3072 x 768 9.8 us, 6.0 so; 768 x
 // 3072 10.0, 6.1 so; 5120 x 1280 17.3, 12.2 so.  Workgroups of 256 threads: with 512 and 1024 the 1280 x 5120 take 16 and 20
 // us instead of 13 (their last round is thin), and WPR = 4 at K = 768 12 instead of 6 (one row per workgroup).
+// The two kept elements of a group of 4 and their positions: the selection rule of keep_mask_of_4 on lane masks (element i is dropped iff two
+// or more of the others beat it, where of a pair the second beats the first iff it is larger: six comparisons, the rest is scalar logic).
+struct KeptPair {
+  float first, second;
+  unsigned p0, p1;
+  bool keep[4];
+  __device__ __forceinline__ explicit KeptPair(const float4& x) {
+    const unsigned k0 = __float_as_uint(x.x) & 0x7FFFFFFFu, k1 = __float_as_uint(x.y) & 0x7FFFFFFFu;
+    const unsigned k2 = __float_as_uint(x.z) & 0x7FFFFFFFu, k3 = __float_as_uint(x.w) & 0x7FFFFFFFu;
+    const bool c01 = k1 > k0, c02 = k2 > k0, c03 = k3 > k0, c12 = k2 > k1, c13 = k3 > k1, c23 = k3 > k2;
+    auto two_of = [](bool p, bool q, bool r) { return (p & q) | (r & (p | q)); };
+    keep[0] = !two_of(c01, c02, c03);
+    keep[1] = !two_of(!c01, c12, c13);
+    keep[2] = !two_of(!c02, !c12, c23);
+    keep[3] = !two_of(!c03, !c13, !c23);
+    p0 = keep[0] ? 0u : (keep[1] ? 1u : 2u);
+    p1 = keep[3] ? 3u : (keep[2] ? 2u : 1u);
+    first = keep[0] ? x.x : (keep[1] ? x.y : x.z);
+    second = keep[3] ? x.w : (keep[2] ? x.z : x.y);
+  }
+};
+// The positions recorded are those of the rule applied to the low-precision group (kept: its two values), which differ from the
+// fp32 group's only where a kept value became zero: then zeros are kept from the lowest index on.
+template <bool IS_I8>
+__device__ __forceinline__ void low_precision_positions(unsigned& kept, unsigned& p0, unsigned& p1) {
+  constexpr int BITS = IS_I8 ? 8 : 16;
+  constexpr unsigned ONE = (1u << BITS) - 1u, MAGNITUDE = IS_I8 ? 0xFFu : 0x7FFFu;
+  const uint64_t group = ((uint64_t)(kept & ONE) << (BITS * p0)) | ((uint64_t)(kept >> BITS) << (BITS * p1));
+  unsigned nz = 0;  // the non-zero elements of the low-precision group: at most two, and they come first
+#pragma unroll
+  for (int i = 0; i < 4; ++i) nz |= (unsigned)(((unsigned)(group >> (BITS * i)) & MAGNITUDE) != 0) << i;
+  const unsigned nib = nibble_of_mask(keep_mask_of_4(nz & 1u, (nz >> 1) & 1u, (nz >> 2) & 1u, (nz >> 3) & 1u));
+  p0 = nib & 3u;
+  p1 = nib >> 2;
+  kept = ((unsigned)(group >> (BITS * p0)) & ONE) | (((unsigned)(group >> (BITS * p1)) & ONE) << BITS);
+}
+// The positions of a packed lane's GU (4 or 8) groups, the first group's in the low nibble: exchanged inside its lanes
+// (quad_perm 1,0,3,2 = 0xB1, quad_perm 2,3,0,1 = 0x4E, row_half_mirror = 0x141)
+template <int GU>
+__device__ __forceinline__ unsigned lane_positions(unsigned nib, int lane) {
+  unsigned ix = nib << (4 * (lane & (GU - 1)));
+  ix |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)ix, 0xB1, 0xF, 0xF, true);
+  ix |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)ix, 0x4E, 0xF, 0xF, true);
+  if constexpr (GU == 8) ix |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)ix, 0x141, 0xF, 0xF, true);
+  return ix;
+}
+// Workgroup id -> (64-channel block, fragment t of it, ROWS of its 16 rows), the last varying fastest; the ids that share a
+// line (8 rows) go to workgroups 8 apart, which the dispatcher places on one XCD.
+template <int ROWS>
+__device__ __forceinline__ int prepare_place() {
+  constexpr int SHARE = 8 / ROWS;
+  const int id = (int)blockIdx.x;
+  return (id & ~(8 * SHARE - 1)) | ((id & 7) * SHARE) | ((id >> 3) & (SHARE - 1));
+}
+
 constexpr int kPrepBatch = 8;
 template <bool IS_I8, int WPR>
 __global__ void __launch_bounds__(256) prepare_weights_kernel(const float* __restrict__ W, float* __restrict__ Wp,
@@ -933,11 +988,7 @@ __global__ void __launch_bounds__(256) prepare_weights_kernel(const float* __res
   constexpr int B = kPrepBatch;
   constexpr int ROWS = 4 / WPR, STRIDE = 64 * WPR;  // rows of a workgroup; groups between a lane's consecutive ones
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // Workgroup id (64-channel block, fragment t of it, ROWS of its 16 rows), the last varying fastest; the ids that share a
-  // line (8 rows) go to workgroups 8 apart, which the dispatcher places on one XCD.
-  constexpr int SHARE = 8 / ROWS;
-  int id = (int)blockIdx.x;
-  id = (id & ~(8 * SHARE - 1)) | ((id & 7) * SHARE) | ((id >> 3) & (SHARE - 1));
+  const int id = prepare_place<ROWS>();
   constexpr int PER_FRAG = 16 / ROWS;
   const int blk = id / (4 * PER_FRAG), t = (id / PER_FRAG) & 3, r = ROWS * (id % PER_FRAG) + wave / WPR;
   const int64_t n = (int64_t)blk * kRowBlock + packed_row_to_channel(t, r);
@@ -986,16 +1037,10 @@ __global__ void __launch_bounds__(256) prepare_weights_kernel(const float* __res
       if (base + j * STRIDE >= padded) break;  // wavefront-uniform
       const int g = base + j * STRIDE + lane;
       const float4 x = v[j];
-      // the selection rule of keep_mask_of_4 on lane masks: element i is dropped iff two or more of the others beat it, where
-      // of a pair the second beats the first iff it is larger (six comparisons, the rest is scalar logic)
-      const unsigned k0 = __float_as_uint(x.x) & 0x7FFFFFFFu, k1 = __float_as_uint(x.y) & 0x7FFFFFFFu;
-      const unsigned k2 = __float_as_uint(x.z) & 0x7FFFFFFFu, k3 = __float_as_uint(x.w) & 0x7FFFFFFFu;
-      const bool c01 = k1 > k0, c02 = k2 > k0, c03 = k3 > k0, c12 = k2 > k1, c13 = k3 > k1, c23 = k3 > k2;
-      auto two_of = [](bool p, bool q, bool r) { return (p & q) | (r & (p | q)); };
-      const bool keep0 = !two_of(c01, c02, c03), keep1 = !two_of(!c01, c12, c13), keep2 = !two_of(!c02, !c12, c23);
-      const bool keep3 = !two_of(!c03, !c13, !c23);
-      unsigned p0 = keep0 ? 0u : (keep1 ? 1u : 2u), p1 = keep3 ? 3u : (keep2 ? 2u : 1u);
-      const float first = keep0 ? x.x : (keep1 ? x.y : x.z), second = keep3 ? x.w : (keep2 ? x.z : x.y);
+      const KeptPair two(x);
+      const bool keep0 = two.keep[0], keep1 = two.keep[1], keep2 = two.keep[2], keep3 = two.keep[3];
+      const float first = two.first, second = two.second;
+      unsigned p0 = two.p0, p1 = two.p1;
       const bool in_row = g < groups;
       if (Wp && in_row) *(float4*)(Wp + n * K + 4 * g) = float4{keep0 ? x.x : 0.0f, keep1 ? x.y : 0.0f, keep2 ? x.z : 0.0f, keep3 ? x.w : 0.0f};
       // the two kept values in low precision; the positions recorded are those of the rule applied to the low-precision group,
@@ -1019,25 +1064,9 @@ __global__ void __launch_bounds__(256) prepare_weights_kernel(const float* __res
         else
           *(uint64_t*)(Wlow + (n * K + 4 * g) * 2) = ((uint64_t)(kept & 0xFFFFu) << (16 * p0)) | ((uint64_t)(kept >> 16) << (16 * p1));
       }
-      if (__builtin_amdgcn_ballot_w64(zero) != 0) {
-        constexpr int BITS = IS_I8 ? 8 : 16;
-        constexpr unsigned ONE = (1u << BITS) - 1u, MAGNITUDE = IS_I8 ? 0xFFu : 0x7FFFu;
-        const uint64_t group = ((uint64_t)(kept & ONE) << (BITS * p0)) | ((uint64_t)(kept >> BITS) << (BITS * p1));
-        unsigned nz = 0;  // the non-zero elements of the low-precision group: at most two, and they come first
-#pragma unroll
-        for (int i = 0; i < 4; ++i) nz |= (unsigned)(((unsigned)(group >> (BITS * i)) & MAGNITUDE) != 0) << i;
-        const unsigned nib = nibble_of_mask(keep_mask_of_4(nz & 1u, (nz >> 1) & 1u, (nz >> 2) & 1u, (nz >> 3) & 1u));
-        p0 = nib & 3u;
-        p1 = nib >> 2;
-        kept = ((unsigned)(group >> (BITS * p0)) & ONE) | (((unsigned)(group >> (BITS * p1)) & ONE) << BITS);
-      }
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(zero) != 0, 0)) low_precision_positions<IS_I8>(kept, p0, p1);
       const unsigned nib = in_row ? p0 | (p1 << 2) : 0u;
-      // the positions of a packed lane's GU groups, the first group's in the low nibble: exchanged inside its 4 (8) lanes
-      // (quad_perm 1,0,3,2 = 0xB1, quad_perm 2,3,0,1 = 0x4E, row_half_mirror = 0x141)
-      unsigned ix = nib << (4 * (lane & (GU - 1)));
-      ix |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)ix, 0xB1, 0xF, 0xF, true);
-      ix |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)ix, 0x4E, 0xF, 0xF, true);
-      if constexpr (GU == 8) ix |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)ix, 0x141, 0xF, 0xF, true);
+      const unsigned ix = lane_positions<GU>(nib, lane);
       if (in_row) {
         if (values) {
           if constexpr (IS_I8)
@@ -1069,11 +1098,140 @@ __global__ void __launch_bounds__(256) prepare_weights_kernel(const float* __res
   }
 }
 
+// The same where only what the sparse GEMM reads is asked for (packed operand, scales): a row stays in B registers of 16 bytes per
+// lane (B = 8: or comes in batches of 8), loads and stores have a wavefront's address and a 32-bit lane offset that grows by a constant,
+// an int8 code takes five operations (see ByteQuantiser), and what few wavefronts run stands behind.  Some 45 vector instructions for a
+// group of 4 where the kernel above takes 130; with its 114 registers it also leaves a fifth of the wavefronts of 5120 x 1280 to a
+// second round.  5120 x 1280 int8 12.3 us, 9.2 so;
+// fp16 10.5, 9.3; 3072 x 768 int8 6.6, 4.8; 768 x 192 3.4, 2.5.  What is left is one burst: all rows are asked for at once and come at some 6 TB/s.
+template <bool IS_I8, int WPR, int B>
+__global__ void __launch_bounds__(256) prepare_packed_kernel(const float* __restrict__ W, float* __restrict__ w_scale,
+                                                             uint8_t* __restrict__ packed, int64_t N, int K, int ksteps) {
+  constexpr int GS = step_elems(IS_I8) / 4;  // groups per K step
+  constexpr int GU = GS / 4;                 // groups per packed lane
+  constexpr int GB = 16 / GU;                // bytes of kept values per group
+  constexpr int ROWS = 4 / WPR, STRIDE = 64 * WPR, PER_FRAG = 16 / ROWS;
+  constexpr bool ONE_BATCH = B < kPrepBatch;
+  static_assert(STRIDE % GS == 0, "a lane's groups lie at the same place of their K steps");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int id = prepare_place<ROWS>(), blk = id / (4 * PER_FRAG), t = (id / PER_FRAG) & 3, r = ROWS * (id % PER_FRAG) + wave / WPR;
+  const int64_t n = (int64_t)blk * kRowBlock + packed_row_to_channel(t, r);
+  const bool live = n < N;  // wavefront-uniform, as all that follows from the wavefront's number
+  const int groups = live ? K / 4 : 0, last = live ? K / 4 - 1 : 0, padded = ksteps * GS, start = (wave % WPR) * 64;
+  const uint8_t* row = (const uint8_t*)(W + (live ? n : 0) * K);
+  float4 v[B];
+  auto load = [&](int base) {  // (groups past the end re-read the last one; they count as zeros below)
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      const int g = base + j * STRIDE + lane;
+      v[j] = *(const float4*)(row + 16u * (uint32_t)(g < last ? g : last));
+    }
+  };
+  load(start);
+  float s = 1.0f;
+  if constexpr (IS_I8) {
+    float amax = 0.0f;
+    for (int base = start;;) {
+#pragma unroll
+      for (int j = 0; j < B; ++j) amax = fmaxf(fmaxf(amax, fmaxf(fabsf(v[j].x), fabsf(v[j].y))), fmaxf(fabsf(v[j].z), fabsf(v[j].w)));
+      base += B * STRIDE;
+      if (ONE_BATCH || base >= groups) break;
+      load(base);
+    }
+    amax = wave_max_magnitude(amax);
+    if constexpr (WPR > 1) {
+      __shared__ float part[ROWS * WPR];
+      if (lane == 0) part[wave] = amax;
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < WPR; ++w) amax = fmaxf(amax, part[wave / WPR * WPR + w]);
+    }
+    s = (amax == 0.0f) ? 1.0f : __fdiv_rn(amax, 127.0f);
+    if (live && start == 0 && lane == 0) w_scale[n] = s;
+    if (!ONE_BATCH && start + B * STRIDE < groups) load(start);
+  }
+  const ByteQuantiser bq(s, IS_I8 ? scale_reciprocal(s) : 1.0f);
+  const int f = (blk & 3) * 4 + t;  // fragment of the packed tile
+  uint8_t* column = packed + (n / kTileRows) * ksteps * tile_bytes(IS_I8);
+  const int q4 = (lane & (GS - 1)) / GU, in_lane = lane & (GU - 1);
+  const uint32_t first_step = (uint32_t)((start + lane) / GS) * tile_bytes(IS_I8);
+  uint32_t value_at = first_step + f * kFragValueBytes + (r + 16 * q4) * 16 + in_lane * GB, index_at = first_step + index_offset(IS_I8, f, r + 16 * q4);
+  for (int base = start; base < padded;) {
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      if (base + j * STRIDE >= padded) break;  // wavefront-uniform
+      const int g = base + j * STRIDE + lane;
+      KeptPair two(v[j]);
+      unsigned kept;
+      bool zero;
+      if constexpr (IS_I8) {
+        int u[2];
+        bq.units(two.first, u[0]);
+        bq.units(two.second, u[1]);
+        const unsigned short l0 = (unsigned short)u[0], l1 = (unsigned short)u[1];
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64((l0 < l1 ? l0 : l1) < ByteQuantiser::kNear) != 0, 0)) {
+          u[0] = finish_code(__fdiv_rn(two.first, s)) * 65536;
+          u[1] = finish_code(__fdiv_rn(two.second, s)) * 65536;
+        }
+        kept = __builtin_amdgcn_perm((unsigned)u[1], (unsigned)u[0], 0x0c0c0602u);  // (no quotient reaches 127.5 here)
+        zero = (kept & 0xFFu) == 0 || kept < 0x100u;
+      } else {
+        const unsigned h0 = __builtin_bit_cast(unsigned short, (_Float16)two.first), h1 = __builtin_bit_cast(unsigned short, (_Float16)two.second);
+        kept = h0 | (h1 << 16);
+        zero = (h0 & 0x7FFFu) == 0 || (h1 & 0x7FFFu) == 0;
+      }
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(zero) != 0, 0)) low_precision_positions<IS_I8>(kept, two.p0, two.p1);
+      const bool in_row = g < groups;
+      kept = in_row ? kept : 0u;
+      const unsigned ix = lane_positions<GU>(in_row ? two.p0 | (two.p1 << 2) : 0u, lane);
+      if (g < padded) {
+        if constexpr (IS_I8)
+          *(uint16_t*)(column + value_at) = (uint16_t)kept;
+        else
+          *(uint32_t*)(column + value_at) = kept;
+        if (in_lane == 0) {
+          if constexpr (IS_I8)
+            *(uint32_t*)(column + index_at) = ix;
+          else
+            *(uint16_t*)(column + index_at) = (uint16_t)ix;
+        }
+      }
+      value_at += STRIDE / GS * tile_bytes(IS_I8);
+      index_at += STRIDE / GS * tile_bytes(IS_I8);
+    }
+    base += B * STRIDE;
+    if (ONE_BATCH) break;
+    if (base < padded) load(base);
+  }
+}
+
+template <bool IS_I8, int WPR>
+static void launch_prepare_packed(const float* W, float* w_scale, uint8_t* packed, int64_t N, int64_t K, int ksteps, unsigned tiles, hipStream_t s) {
+#define GPUSQ_PREPARE_PACKED(B) \
+  prepare_packed_kernel<IS_I8, WPR, B><<<tiles * (kTileRows * WPR / 4), 256, 0, s>>>(W, w_scale, packed, N, (int)K, ksteps)
+  const int64_t per_lane = ceil_div((int64_t)ksteps * (step_elems(IS_I8) / 4), 64 * WPR);  // groups, the padding's too
+  if (per_lane <= 1) GPUSQ_PREPARE_PACKED(1);
+  else if (per_lane == 2) GPUSQ_PREPARE_PACKED(2);
+  else if (per_lane == 3) GPUSQ_PREPARE_PACKED(3);
+  else if (per_lane == 4) GPUSQ_PREPARE_PACKED(4);
+  else if (per_lane == 5) GPUSQ_PREPARE_PACKED(5);
+  else if (per_lane == 6) GPUSQ_PREPARE_PACKED(6);
+  else GPUSQ_PREPARE_PACKED(8);
+#undef GPUSQ_PREPARE_PACKED
+}
+
 gpusq_status launch_prepare_weights(const float* W, gpusq_dtype dt, float* Wp, void* Wlow, float* w_scale, void* values,
                                     uint8_t* meta, void* packed, int64_t N, int64_t K, hipStream_t s) {
   const bool is_i8 = dt == GPUSQ_I8;
   const int ksteps = (int)ceil_div(K, step_elems(is_i8));
   const unsigned tiles = (unsigned)ceil_div(N, kTileRows);  // the padding rows of the last tile have their workgroups as well
+  if (!Wp && !Wlow && !values && !meta && K < (1 << 20)) {  // (32-bit offsets inside a row and a column of packed tiles)
+    if (is_i8 && K > 2048) launch_prepare_packed<true, 4>(W, w_scale, (uint8_t*)packed, N, K, ksteps, tiles, s);
+    else if (is_i8) launch_prepare_packed<true, 1>(W, w_scale, (uint8_t*)packed, N, K, ksteps, tiles, s);
+    else if (K > 2048) launch_prepare_packed<false, 4>(W, w_scale, (uint8_t*)packed, N, K, ksteps, tiles, s);
+    else launch_prepare_packed<false, 1>(W, w_scale, (uint8_t*)packed, N, K, ksteps, tiles, s);
+    return check_launch();
+  }
 #define GPUSQ_PREPARE(I8, WPR, ROWS)                                                                                                  \
   prepare_weights_kernel<I8, WPR><<<tiles * (kTileRows / ROWS), 64 * WPR * ROWS, 0, s>>>(W, Wp, (uint8_t*)Wlow, w_scale, (uint8_t*)values, \
                                                                                           meta, (uint8_t*)packed, N, K, ksteps)

@@ -32,6 +32,27 @@ def test_fused_preparation_equals_the_separate_calls(g, N, K, dtype):
     assert torch.equal(g.prepare_weights(dev(W), tdt)["packed"], packed)  # without the optional outputs
 
 
+# only what the GEMM reads: 1 to 6 and 8 vectors of a row per lane, in one wavefront or four, several batches of 8; rows that end inside
+# a lane, infinities and rows of zeros and denormals (whose scale has no reciprocal)
+@pytest.mark.parametrize("N,K", [(1, 4), (12, 64), (70, 260), (33, 516), (300, 768), (40, 1028), (257, 1280), (8, 1540), (9, 1796), (30, 2052), (5, 3076), (70, 4096),
+                                 (6, 5120), (3, 6148), (4, 7172), (5, 12292)])
+@pytest.mark.parametrize("dtype", ["int8", "fp16"])
+def test_packed_operand_and_scales_alone(g, N, K, dtype):
+    rng = np.random.default_rng(N * 7 + K)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    W[0, ::3] = np.float32(1e-9)
+    if N > 4:
+        W[1], W[2] = 0.0, W[2] * np.float32(1e-38)
+        W[3, 1], W[4, K // 2] = np.inf, -np.inf
+    tdt = torch.int8 if dtype == "int8" else torch.float16
+    out = g.prepare_weights(dev(W), tdt)
+    Wp = g.prune_2to4(dev(W))
+    Wl, s = g.quantize_int8(Wp, g.PER_ROW) if dtype == "int8" else (g.cast_f16(Wp), None)
+    values, meta = g.compress(Wl)
+    assert torch.equal(out["packed"], g.pack(values, meta, K))
+    assert s is None or torch.equal(out["w_scale"], s)
+
+
 @pytest.mark.parametrize("rows,cols", [(3, 2048), (5, 2052), (2, 5120), (7, 5124), (3, 1001), (1, 4)])
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
 def test_row_quantiser_batches(g, rows, cols, dtype):
