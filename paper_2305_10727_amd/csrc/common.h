@@ -334,6 +334,21 @@ __device__ __forceinline__ float range_of_fp16(const uint8_t* X, int64_t n, int 
   return (float)__builtin_bit_cast(_Float16, (unsigned short)top);
 }
 
+// The same of fp32 values, n % 4 == 0.
+__device__ __forceinline__ float range_of_fp32(const float* X, int64_t n, int tid, int threads) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  const int vecs = (int)(n / 4);
+  float amax = 0.0f;
+  for (int i = tid; i < vecs; i += 8 * threads) {
+    f4 v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = ((const f4*)X)[i + j * threads < vecs ? i + j * threads : vecs - 1];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) amax = fmaxf(fmaxf(amax, fmaxf(fabsf(v[j][0]), fabsf(v[j][1]))), fmaxf(fabsf(v[j][2]), fabsf(v[j][3])));
+  }
+  return amax;
+}
+
 // Selection rule inside one group of 4 [Sec. 3.1: two of every four contiguous elements are zero; the rule is this
 // library's reading]: element i is kept iff fewer than two elements beat it, where j beats i when |w_j| > |w_i|, or
 // |w_j| == |w_i| and j < i.  Magnitudes are compared as sign-cleared bit patterns (a total order).
@@ -370,7 +385,8 @@ struct GemmArgs {
   // patch (py, px) of image b, column (c*P + i)*P + j its pixel (py*P + i, px*P + j) of channel c; M = B*(H/P)*(W/P),
   // K = C*P*P.  The tile kernel then fetches its X slabs from the image directly (no flattened-patch buffer).
   int patch_P = 0, patch_C = 0, patch_H = 0, patch_W = 0;
-  // INT8 path, small kernels only: X holds fp16 activations, quantised inside the kernel with the static act_scale
+  // INT8 path, small kernels only: X holds fp16 (1) activations, quantised inside the kernel with the static act_scale; in the kernel
+  // for few rows fp32 (2) as well
   int x_f16 = 0;
   // ... or, in the kernel for few rows, with the scale of X's own range: that of the `npartial` partial maxima a range pass
   // left behind, or of all of X, read by every workgroup; the scale goes to scale_out, the codes to xq_out (if not NULL)
@@ -385,7 +401,7 @@ gpusq_status launch_spgemm(bool is_i8, const GemmArgs& a, hipStream_t s);
 gpusq_status launch_dense(bool is_i8, const GemmArgs& a, hipStream_t s);
 // the sparse GEMM for few rows (fewrows.hip)
 bool fewrows_supports(const GemmArgs& a);
-bool fewrows_folds_quantiser(int64_t M, int64_t N, int64_t K, int resident);
+bool fewrows_folds_quantiser(int64_t M, int64_t N, int64_t K, int resident, bool fp32);
 gpusq_status launch_fewrows(bool is_i8, const GemmArgs& a, int resident, hipStream_t s);
 // quantise (dt of X, workspace as for launch_quantize) and multiply: one, two or three launches
 gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, void* workspace, hipStream_t s);

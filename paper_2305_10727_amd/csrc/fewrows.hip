@@ -16,7 +16,7 @@
 // 2304 4.8 -> 3.3 / 6.2 -> 3.4, 197 x 3072 -> 768 9.8 -> 4.5 / 16.6 -> 6.0.  With 8 wavefronts instead of 4 the longest K
 // gain 2 % and every problem of more than one round of workgroups loses 20-40 %; where the kernel quantises see fewrows_wide.
 //
-// INT8 with fp16 activations: the rows are quantised on their way through the registers, with a given scale, with the partial
+// INT8 with fp16 or fp32 activations: the rows are quantised on their way through the registers, with a given scale, with the partial
 // maxima that a range pass left behind, or (small X) with the range of all of X, which every workgroup reads for itself: one
 // launch for the whole layer.  The workgroups of the first column of tiles write the codes out if asked.
 #include "tile_common.h"
@@ -32,15 +32,16 @@ __device__ __forceinline__ float scale_of_range(float amax) { return amax == 0.0
 typedef __attribute__((address_space(1))) v4i global_v4;
 typedef __attribute__((address_space(1))) ep_v2u global_v2u;
 
-// XQ: 0 = X is the operand; 1 = fp16 to be quantised with a given scale; 2 = with the scale of X's range (see GemmArgs)
+// XQ: 0 = X is the operand; 1 = fp16 or fp32 to be quantised with a given scale; 2 = with the scale of X's range (see GemmArgs)
 // PATCH: the rows of X are 16 x 16 patches gathered from an image batch (see patch_chunk_offset).
-template <bool IS_I8, int TM, int XQ, bool PATCH = false, int NW = kFrWaves>
+// XW: bytes of X in memory per byte of the operand (quantised: 2 = fp16, 4 = fp32).
+template <bool IS_I8, int TM, int XQ, bool PATCH = false, int NW = kFrWaves, int XW = XQ != 0 ? 2 : 1>
 __global__ void __launch_bounds__(64 * NW, 2) spgemm_fewrows_kernel(const GemmArgs a, const int tiles_n, const int tiles_m, const int n_fast) {
-  constexpr bool XF16 = XQ != 0;
-  static_assert(IS_I8 || !XF16, "the fp16 path takes fp16 X as it is");
+  constexpr bool QUANT = XQ != 0, FP32 = XW == 4;
+  static_assert(IS_I8 || !QUANT, "the fp16 path takes fp16 X as it is");
+  static_assert(QUANT ? XW == 2 || XW == 4 : XW == 1, "an operand as it is, fp16 or fp32");
   typedef typename AccT<IS_I8>::type acc_t;
   constexpr int ES = IS_I8 ? 1 : 2;
-  constexpr int XW = XF16 ? 2 : 1;   // bytes of X in memory per byte of the operand
   constexpr int ROWS = 16 * TM;
   constexpr int XL = 2 * TM * XW;    // 16-byte loads per lane for the X rows of a step
   constexpr int D = kFrBatch;
@@ -64,12 +65,12 @@ __global__ void __launch_bounds__(64 * NW, 2) spgemm_fewrows_kernel(const GemmAr
   const int mine = (ksteps - wave + NW - 1) / NW;  // K steps wave, wave + NW, ... (none if there are fewer steps than wavefronts)
   const int tail_bytes = (int)(k_bytes % kStepBytes);
 
-  // X: a load instruction covers 8 (fp16 to be quantised: 4) rows x 128 (256) bytes, every line whole
+  // X: a load instruction covers 8 (fp16 to be quantised: 4, fp32: 2) rows x 128 (256, 512) bytes, every line whole
   constexpr int LPR = 8 * XW;  // lanes per row
   const int64_t m0 = (int64_t)m_blk * ROWS;
   const int64_t last_row = (int64_t)a.M - 1 - m0;  // >= 0: a tile starts inside X; rows past the end re-read the last one
   const global_u8* Xtile = uniform_ptr((const uint8_t*)a.X + (PATCH ? 0 : m0 * k_bytes * XW));
-  // Row (of the 8 or 4) and 16-byte chunk of a step that this lane fetches: consecutive lanes along a row of X, or, for
+  // Row (of the 8, 4 or 2) and 16-byte chunk of a step that this lane fetches: consecutive lanes along a row of X, or, for
   // patches, along a row of the image, where neighbouring patches' 16 bytes (fp16: 32) are contiguous.
   int lrow = lane / LPR, lchunk = lane % LPR;
   if constexpr (PATCH) {
@@ -136,7 +137,7 @@ __global__ void __launch_bounds__(64 * NW, 2) spgemm_fewrows_kernel(const GemmAr
   float s_a = 1.0f;
   const OutScale os = out_scale_of<IS_I8>(a);
   Fp16Quantiser qz;
-  if constexpr (XF16) {
+  if constexpr (QUANT) {
     if constexpr (XQ == 2) {
       float amax = 0.0f;
       if (a.range_mode == kRangePartials) {
@@ -147,7 +148,7 @@ __global__ void __launch_bounds__(64 * NW, 2) spgemm_fewrows_kernel(const GemmAr
           amax = fmaxf(fmaxf(amax, fmaxf(p[0], p[1])), fmaxf(p[2], p[3]));
         }
       } else {
-        amax = range_of_fp16((const uint8_t*)a.X, (int64_t)a.M * a.K, tid, 64 * NW);
+        amax = FP32 ? range_of_fp32((const float*)a.X, (int64_t)a.M * a.K, tid, 64 * NW) : range_of_fp16((const uint8_t*)a.X, (int64_t)a.M * a.K, tid, 64 * NW);
       }
       amax = wave_max_magnitude(amax);
       if (lane == 0) part[wave] = amax;
@@ -160,14 +161,17 @@ __global__ void __launch_bounds__(64 * NW, 2) spgemm_fewrows_kernel(const GemmAr
     } else {
       s_a = a.act_scale[0];
     }
-    const unsigned wave_votes = qz.prepare(s_a, tid);
-    if (lane == 0 && wave < 4) votes[wave] = wave_votes;
-    __syncthreads();
-    qz.decide((unsigned)__builtin_amdgcn_readfirstlane((int)(votes[0] | votes[1] | votes[2] | votes[3])));  // (threads 0..255)
+    if constexpr (!FP32) {
+      const unsigned wave_votes = qz.prepare(s_a, tid);
+      if (lane == 0 && wave < 4) votes[wave] = wave_votes;
+      __syncthreads();
+      qz.decide((unsigned)__builtin_amdgcn_readfirstlane((int)(votes[0] | votes[1] | votes[2] | votes[3])));  // (threads 0..255)
+    }
   } else if (IS_I8 && !raw_out) {
     s_a = a.act_scale[0];
   }
-  const bool write_codes = XF16 && a.xq_out != nullptr && n_blk == 0;
+  const float r_a = FP32 ? scale_reciprocal(s_a) : 1.0f;
+  const bool write_codes = QUANT && a.xq_out != nullptr && n_blk == 0;
 
   acc_t acc[4][TM];
 #pragma unroll
@@ -183,7 +187,22 @@ __global__ void __launch_bounds__(64 * NW, 2) spgemm_fewrows_kernel(const GemmAr
 #pragma unroll
       for (int j = 0; j < XL; ++j) xr[slot][j] = v4i{0, 0, 0, 0};
     }
-    if constexpr (XF16) {
+    if constexpr (FP32) {
+#pragma unroll
+      for (int j = 0; j < XL; j += 2) {  // 4 fp32 values of row 2j + lane / 32 and 4 of two rows further -> 8 codes
+        const ep_v4f lo = __builtin_bit_cast(ep_v4f, xr[slot][j]), hi = __builtin_bit_cast(ep_v4f, xr[slot][j + 1]);
+        const float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        unsigned q[2];
+        quantize_bytes8(x, s_a, r_a, q[0], q[1]);
+        const int col = (lane & 31) * 4;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int r = 2 * (j + h) + (lane >> 5);
+          *(unsigned*)(xs + r * kFrRow + col) = q[h];
+          if (write_codes && r <= last_row && ks * kStepBytes + col < a.K) *(unsigned*)(a.xq_out + (m0 + r) * a.K + ks * kStepBytes + col) = q[h];
+        }
+      }
+    } else if constexpr (QUANT) {
       const bool odd = qz.odd(xr[slot]);
 #pragma unroll
       for (int j = 0; j < XL; ++j) {  // 8 fp16 values -> 8 codes
@@ -269,8 +288,11 @@ static int fewrows_tm(int64_t M, int64_t N, int resident) {
 // -> 1024 7.5 / 6.7, 96 x 4096 -> 2304 8.8 / 8.0; two, up to 12 steps 224 x 1024 -> 2304 6.7 / 6.2, 160 x 1536 -> 2304 7.2 / 7.2, beyond 160 x
 // 3072 -> 2304 9.3 / 9.8, 160 x 4096 -> 2304 10.6 / 11.6; three 272 x 1024 -> 2304 7.3 / 8.8.  The tiles are of 16 rows then: with 32 the
 // 2304 channels take longer.
-bool fewrows_folds_quantiser(int64_t M, int64_t N, int64_t K, int resident) {
+// fp32 rows are twice the bytes and come in vectors of 4: 320 x 384 -> 768 5.2 / 4.1, 320 x 1536 -> 768 6.6 / 6.0, but 320 x 3072 -> 768 8.6 / 10.2; two
+// workgroups 672 x 384 -> 768 5.5 / 4.9, 672 x 768 -> 768 6.0 / 6.4.
+bool fewrows_folds_quantiser(int64_t M, int64_t N, int64_t K, int resident, bool fp32) {
   const int64_t tiles = ceil_div(M, 16) * ceil_div(N, kRowBlock), ksteps = ceil_div(K, kStepBytes);
+  if (fp32) return tiles <= resident ? ksteps <= 12 : (tiles <= 2 * (int64_t)resident && ksteps <= 4);
   return tiles <= resident ? ksteps <= 40 : (tiles <= 2 * (int64_t)resident && ksteps <= kFrWaves * kFrBatch);
 }
 
@@ -280,7 +302,7 @@ bool fewrows_folds_quantiser(int64_t M, int64_t N, int64_t K, int resident) {
 // -> 768 8.9 / 6.7, 64 x 1024 -> 1024 5.1 / 4.6, but 197 x 192 -> 768 3.9 / 4.1, 100 x 384 -> 384 3.9 / 4.1; range found here
 // 331 x 192 -> 384, 127 KB, 6.2 / 5.9, 197 x 192 -> 768, 75 KB, 5.5 / 5.8).
 static bool fewrows_wide(const GemmArgs& a, int tiles_n, int tiles_m, int resident) {
-  const bool long_range = a.range_mode == kRangeHere && (int64_t)a.M * a.K * 2 > 96 * 1024;
+  const bool long_range = a.range_mode == kRangeHere && (int64_t)a.M * a.K * (a.x_f16 == 2 ? 4 : 2) > 96 * 1024;
   return (int64_t)tiles_n * tiles_m <= resident && (ceil_div(a.K, kStepBytes) > 4 || long_range);
 }
 
@@ -296,7 +318,15 @@ gpusq_status launch_fewrows(bool is_i8, const GemmArgs& a, int resident, hipStre
   const bool quantise = is_i8 && a.x_f16, given = a.range_mode == kRangeGiven;
 #define GPUSQ_FEWROWS(...) spgemm_fewrows_kernel<__VA_ARGS__><<<grid, 64 * kFrWaves, 0, s>>>(a, tiles_n, tiles_m, n_fast)
 #define GPUSQ_FEWROWS_WIDE(...) spgemm_fewrows_kernel<__VA_ARGS__, false, 8><<<grid, 512, 0, s>>>(a, tiles_n, tiles_m, n_fast)
-  if (quantise && fewrows_wide(a, tiles_n, tiles_m, resident) && given) GPUSQ_FEWROWS_WIDE(true, 1, 1);
+#define GPUSQ_FEWROWS_FP32(XQ, NW) spgemm_fewrows_kernel<true, 1, XQ, false, NW, 4><<<grid, 64 * NW, 0, s>>>(a, tiles_n, tiles_m, n_fast)
+  if (quantise && a.x_f16 == 2) {
+    const bool wide = fewrows_wide(a, tiles_n, tiles_m, resident);
+    if (wide && given) GPUSQ_FEWROWS_FP32(1, 8);
+    else if (wide) GPUSQ_FEWROWS_FP32(2, 8);
+    else if (given) GPUSQ_FEWROWS_FP32(1, 4);
+    else GPUSQ_FEWROWS_FP32(2, 4);
+  }
+  else if (quantise && fewrows_wide(a, tiles_n, tiles_m, resident) && given) GPUSQ_FEWROWS_WIDE(true, 1, 1);
   else if (quantise && fewrows_wide(a, tiles_n, tiles_m, resident)) GPUSQ_FEWROWS_WIDE(true, 1, 2);
   else if (quantise && given) GPUSQ_FEWROWS(true, 1, 1);
   else if (quantise) GPUSQ_FEWROWS(true, 1, 2);
@@ -310,6 +340,7 @@ gpusq_status launch_fewrows(bool is_i8, const GemmArgs& a, int resident, hipStre
   else GPUSQ_FEWROWS(false, 1, 0);
 #undef GPUSQ_FEWROWS
 #undef GPUSQ_FEWROWS_WIDE
+#undef GPUSQ_FEWROWS_FP32
   return check_launch();
 }
 

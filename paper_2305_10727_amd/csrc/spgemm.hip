@@ -613,8 +613,8 @@ static gpusq_status launch_typed(const GemmArgs& a, hipStream_t s) {
   return IS_I8 ? launch_tile1_i8(a, dec.even, grid, s) : launch_tile1_f16(a, dec.even, grid, s);
 }
 
-// Quantise X and multiply.  Where the problem goes to the kernel for few rows, X is fp16 and its K is not too long, that
-// kernel quantises: with a given scale, or a range of X small enough for every workgroup to find for itself, in the one
+// Quantise X and multiply.  Where the problem goes to the kernel for few rows and its K is not too long, that kernel
+// quantises: with a given scale, or a range of X small enough for every workgroup to find for itself, in the one
 // launch, else behind the range pass.  Otherwise the quantiser's one or two launches and the GEMM's.
 // A range of 128 KB read by every workgroup costs what the range pass does: 75 KB (197 x 192) 5.8 against 6.7 us, 133 KB (64 x
 // 1040) 8.2 against 8.6, 151 KB (394 x 192) 8.4 against 7.1.
@@ -623,10 +623,10 @@ constexpr int64_t kRangeHereBytes = 128 * 1024;
 // 1 + the launches in front of the GEMM's own; `folds`: the GEMM quantises
 static int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int resident, bool& folds) {
   // (the sizes first: a large layer is not planned for this)
-  folds = dt == GPUSQ_F16 && fewrows_folds_quantiser(a.M, a.N, a.K, resident) && fewrows_supports(a) &&
+  folds = fewrows_folds_quantiser(a.M, a.N, a.K, resident, dt == GPUSQ_F32) && fewrows_supports(a) &&
           decide(true, a.M, a.N, a.K, (a.epilogue & GPUSQ_EPI_GELU) != 0, resident, false).choice == 4;
   if (!folds) return scale_is_input ? 2 : 3;
-  return scale_is_input || (int64_t)a.M * a.K * 2 <= kRangeHereBytes ? 1 : 2;
+  return scale_is_input || (int64_t)a.M * a.K * dtype_bytes(dt) <= kRangeHereBytes ? 1 : 2;
 }
 
 int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int cus) {
@@ -647,10 +647,10 @@ gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* s
   // on its own output) or over the partial maxima, which the GEMM that quantises reads in every workgroup, beside others that
   // already write; and an out_scale that is the activation scale itself, which it would read while one workgroup writes it.
   const int64_t y_bytes = (int64_t)a.M * a.N * dtype_bytes(a.out_dt), range_bytes = (int64_t)gpusq_quantize_workspace_bytes(GPUSQ_PER_TENSOR, a.M, a.K);
-  const bool apart = !overlap(a.X, (int64_t)a.M * a.K * 2, a.Y, y_bytes) &&
+  const bool apart = !overlap(a.X, (int64_t)a.M * a.K * dtype_bytes(dt), a.Y, y_bytes) &&
                      (scale_is_input || (a.out_scale != scale && (launches == 1 || !overlap(workspace, range_bytes, a.Y, y_bytes))));
   if (folds && apart) {
-    a.x_f16 = 1;
+    a.x_f16 = dt == GPUSQ_F32 ? 2 : 1;
     a.xq_out = Xq;
     if (!scale_is_input) {
       a.scale_out = scale;

@@ -105,6 +105,31 @@ def test_fp16_codes_decide_as_the_division_does(g):
         assert np.array_equal(q, exp), s
 
 
+# fp32 activations quantised by the kernel for few rows: 4 and 8 wavefronts, one and two workgroups per CU, the range found by every
+# workgroup and by a pass, rows that end inside a K step; NaN and infinities beside a given scale; int8 output
+@pytest.mark.parametrize("M,K,N", [(1, 16, 4), (50, 192, 260), (331, 192, 384), (700, 384, 512), (33, 656, 132), (197, 1536, 64), (17, 1040, 68)])
+@pytest.mark.parametrize("given", [False, True])
+def test_one_call_layer_of_fp32_rows(g, M, K, N, given):
+    assert g.lib().gpusq_linear_int8_launches(g.F32, M, N, K, g.EPI_BIAS, int(given), 0) < (2 if given else 3)
+    rng = np.random.default_rng(M + K)
+    X = (rng.standard_normal((M, K)) * 1.5).astype(np.float32)
+    if given:
+        X.reshape(-1)[:8] = np.array([0.0, -0.0, 3e38, -3e38, 1e-40, np.inf, -np.inf, np.nan], np.float32)
+    _, s_w, vals, meta = _oracle_weights(synth.weights(N, K, seed=M, ids=(9,), sigma=0.05))
+    bias = synth.bias(N, seed=M, ids=(10,))
+    packed, sw, b = g.pack(dev(vals), dev(meta), K), dev(s_w), dev(bias)
+    scale = np.float32(4.0 / 127.0) if given else None
+    exp_q, exp_s = oracle.quantize_tensor_int8(X, scale=None if scale is None else float(scale))
+    acc = oracle.spgemm_int8(exp_q, vals, meta)
+    y, q, s = _layer(g, dev(X), packed, sw, b, M, N, K, None if scale is None else dev(np.array([scale])))
+    assert s[0] == np.float32(exp_s) and np.array_equal(q, exp_q)
+    assert np.array_equal(y.view(np.uint16), oracle.epilogue_int8_f32(acc, float(s[0]), s_w, bias)["y16"].view(np.uint16))
+    so = np.float32(np.abs(acc).max() * s[0] * s_w.max() / 127.0 + 1e-9)
+    Y, Xq, sa = torch.empty((M, N), dtype=torch.int8, device="cuda"), torch.empty((M, K), dtype=torch.int8, device="cuda"), dev(s.copy())
+    g.calls.gpusq_linear_int8(dev(X), g.F32, packed, sa, int(given), sw, b, Y, g.I8, dev(np.array([so])), Xq, torch.empty(4096, dtype=torch.uint8, device="cuda"), M, N, K, g.EPI_BIAS)
+    assert np.array_equal(host(Y), oracle.epilogue_int8_f32(acc, float(s[0]), s_w, bias, out_scale=float(so))["q8"])
+
+
 # a square layer run on its own output, whole or partly over X: as from a copy of X, where the GEMM would quantise for itself
 @pytest.mark.parametrize("M,K", [(64, 768), (197, 768), (16, 256)])
 @pytest.mark.parametrize("given", [False, True])
