@@ -493,9 +493,10 @@ static int kernel_choice(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu,
     return ksteps <= (is_i8 ? 2 : 4) && ceil_div(M, 128) * ceil_div(N, 128) <= 2 * (int64_t)resident ? 1 : 2;
   }
   if (fused_patches) return 2;
-  if (x_f16) {
-    // Which problems the small kernel quantises fp16 activations for was settled by an estimate of the tile kernel in units of 64 rows
-    // and is kept: a caller may have built on it.
+  if (x_f16 || 255 * k_bytes + kStepBytes >= ((int64_t)1 << 32)) {
+    // Which problems the small kernel quantises fp16 activations for, and which it takes where K is beyond kernel 2's 32-bit lane offsets
+    // (the others are refused there), was settled by an estimate of the tile kernel in units of 64 rows and is kept: a caller may have
+    // built on it.
     if (wgs64 > 16 * resident) return 2;
     const double per_round = 0.7 + 0.45 * ksteps, chain = 3.6 + 0.25 * ksteps;
     const double throughput = 4.0 + per_round * (double)wgs64 / (2.0 * resident);

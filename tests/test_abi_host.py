@@ -161,6 +161,14 @@ def _plan(lib, dt, M, N, K, epi, cus):
     return st, list(out)
 
 
+@pytest.mark.parametrize("dt,M,N,K", [(2, 1847, 972, 17920000), (2, 2807, 608, 17920000), (1, 3063, 884, 16777216), (1, 810, 3744, 8960000)])
+def test_long_rows_beyond_the_tile_kernels_offsets_stay_with_the_small_kernel(lib, dt, M, N, K):
+    """255 rows of K bytes past 2^32: kernel 2 refuses them, so what the 64 x 64 tiles took has to go on going there."""
+    assert 255 * K * (1 if dt == 2 else 2) + 128 >= 2 ** 32
+    st, p = _plan(lib, dt, M, N, K, 0, 256)
+    assert st == 0 and p[0] == 0
+
+
 def test_tile_plan_covers_every_row_exactly_once(lib):
     """The host-side tile plan of the sparse GEMM: the full tiles and the tail tiles partition the rows of X, the tile
     count is consistent, no more workgroups than tiles or compute units (rounded to the 8 XCDs), and a small problem
