@@ -202,8 +202,9 @@ gpusq_status gpusq_spgemm_int8(const int8_t* Xq, const void* Wpacked, const floa
  * Xq = clamp(rint(X / act_scale[0]), -127, 127) on its way to the matrix instructions (the code rule of
  * gpusq_quantize_int8 with scale_is_input != 0; bit-identical to calling that first), so a layer with a static scale is
  * one launch instead of two.  Only the kernels for small problems, through whose registers X passes, can do this: a problem
- * that gpusq_spgemm_plan assigns to a tile kernel (kernel >= 2) returns GPUSQ_ERR_UNSUPPORTED and is served by
- * gpusq_quantize_int8 + gpusq_spgemm_int8, but for a K of no whole 128-byte steps, which a small kernel takes.  Every
+ * whose estimated time is shorter on a tile kernel returns GPUSQ_ERR_UNSUPPORTED and is served by gpusq_quantize_int8 +
+ * gpusq_spgemm_int8, but for a K of no whole 128-byte steps, which a small kernel takes.  (The estimate is this call's own; beside
+ * the crossover gpusq_spgemm_plan may report another kernel for the product alone.)  Every
  * workgroup quantises the rows of its own tile, so the saving is that of a launch (a few microseconds) against extra work per
  * K step; gpusq_linear_int8 takes whichever is the faster.
  * act_scale is required for every out_dt; all other arguments as for gpusq_spgemm_int8. */

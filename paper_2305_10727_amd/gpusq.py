@@ -394,8 +394,8 @@ def spgemm_int8(Xq, Wpacked, N, act_scale=None, w_scale=None, bias=None, gelu=Fa
 
 def spgemm_int8_xf16(X, Wpacked, N, act_scale, w_scale, bias=None, gelu=False, out_dtype=torch.float16, out_scale=None,
                      out=None):
-    """X fp16 [M,K], quantised inside the GEMM with the static act_scale (latency kernel only: raises GpusqError with
-    ERR_UNSUPPORTED for problems of whole K steps that spgemm_plan assigns to a tile kernel)"""
+    """X fp16 [M,K], quantised inside the GEMM with the static act_scale (small kernels only: raises GpusqError with
+    ERR_UNSUPPORTED for problems of whole K steps that are estimated to be faster on a tile kernel)"""
     M, K = X.shape
     Y = torch.empty((M, N), dtype=out_dtype, device=X.device) if out is None else out
     calls.gpusq_spgemm_int8_xf16(X, Wpacked, act_scale, w_scale, bias, Y, _TORCH_DT[out_dtype], out_scale, M, N, K, _epi(bias, gelu))
