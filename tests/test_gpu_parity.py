@@ -901,8 +901,9 @@ def _oracle_weights(W):
     return Wq, s_w, vals, meta
 
 
-@pytest.mark.parametrize("M,D,hidden,seed", [(197, 192, 768, 51), (1576, 384, 1536, 52)])
-def test_encoder_block_chain_and_its_graph(g, M, D, hidden, seed):
+# both qkv and fc1 quantise their input inside the GEMM, qkv alone does, neither does
+@pytest.mark.parametrize("M,D,hidden,seed,launches", [(197, 192, 768, 51, (1, 1)), (197, 768, 3072, 53, (1, 2)), (1576, 384, 1536, 52, (2, 2))])
+def test_encoder_block_chain_and_its_graph(g, M, D, hidden, seed, launches):
     """qkv -> [attention stub: V passes through] -> proj -> quantise -> fc1 (GELU, int8 out) -> fc2 with static scales,
     against the same chain composed from the oracle's layer functions.  Everything up to fc1's input has no GELU and is
     bit-exact; the GELU codes may differ by one in rare near-ties (the kernel's GELU is a fit, the oracle's is erf), and
@@ -942,21 +943,26 @@ def test_encoder_block_chain_and_its_graph(g, M, D, hidden, seed):
     blk.prepare_weights(*[dev(W) for W in Ws])
     x, biases = dev(X), [dev(b) for b in bs]
     stub = lambda q, out: out.copy_(q[:, 2 * D:])
-    # first with a quantise launch in front of qkv and fc1 (six launches), which leaves the codes to look at; then, for
-    # few rows, the route the helper picks there: qkv and fc1 quantise their fp16 input themselves (four launches)
-    folds = blk.fold_quantise
-    assert folds == (M <= 256 and D <= 384)
-    blk.fold_quantise = False
-    y = host(blk.forward(x, biases, stub))
+    assert tuple(g.lib().gpusq_linear_int8_launches(g.F16, l.M, l.N, l.K, l.epilogue, 1, 0) for l in (blk.qkv, blk.fc1)) == launches
+    # first every pass by itself: the quantisers of x and h, and the GEMMs (six launches)
+    blk.qkv.quantize_activations(x, static=True)
+    blk.qkv.gemm(None, biases[0], sc["qkv"])
+    stub(blk.qkv.Y, blk.proj.Xq)
+    blk.fc1.quantize_activations(blk.proj.gemm(None, biases[1]), static=True)
+    blk.fc1.gemm(None, biases[2], sc["g"])
+    y = host(blk.fc2.gemm(None, biases[3]))
     assert np.array_equal(host(blk.qkv.Xq), Xq) and np.array_equal(host(blk.qkv.Y), qkv)
     assert np.array_equal(host(blk.proj.Y).view(np.uint16), proj.view(np.uint16)) and np.array_equal(host(blk.fc1.Xq), hq)
-    if folds:
-        codes6, y6 = blk.fc1.Y.clone(), blk.fc2.Y.clone()
-        blk.fold_quantise = True
-        for t in (blk.qkv.Y, blk.proj.Y, blk.fc1.Y, blk.fc2.Y):
+    # then the block: one-call layers for qkv and fc1, which leave the codes, and, where both quantise inside the GEMM, the form that
+    # writes none (four launches)
+    codes6, y6, folds = blk.fc1.Y.clone(), blk.fc2.Y.clone(), blk.fold_quantise
+    assert folds == (launches == (1, 1))
+    for blk.fold_quantise in (False, True) if folds else (False,):
+        for t in (blk.qkv.Xq, blk.fc1.Xq, blk.qkv.Y, blk.proj.Y, blk.fc1.Y, blk.fc2.Y):
             t.zero_()
-        y = host(blk.forward(x, biases, stub))
+        blk.forward(x, biases, stub)
         assert np.array_equal(host(blk.qkv.Y), qkv) and torch.equal(blk.fc1.Y, codes6) and torch.equal(blk.fc2.Y, y6)
+        assert blk.fold_quantise or (np.array_equal(host(blk.qkv.Xq), Xq) and np.array_equal(host(blk.fc1.Xq), hq))
     g_hip = host(blk.fc1.Y).astype(np.int32)
     flips = g_hip != gq.astype(np.int32)
     assert check_gelu_codes(g_hip, acc_fc1, float(s_h), ow[2][1], bs[2], s_g) == flips.sum()  # every flip is a near-tie
