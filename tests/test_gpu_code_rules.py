@@ -164,12 +164,8 @@ def test_per_tensor_quantiser_over_its_grid(g, dtype, n):
     assert np.array_equal(host(g.quantize_int8(x, g.PER_TENSOR, scale=dev(np.array([given])))[0]), exp_q)
 
 
-# fp32 values on the boundaries between codes and up to 3 units in the last place beside them, through the fp32 quantiser and through
-# every kernel's int8 output (zero activations: the value quantised is the bias); scales with a mantissa of ones, too small for
-# the factor 65536 of the reciprocal, huge, negative, zero
-@pytest.mark.parametrize("s", [0.03, 1 / 3, 4 / 127, 2.0 ** -7, float(np.nextafter(np.float32(0.5), np.float32(0))), -0.07, 1e-3, 3e-34, 1e-36, 1e30, 0.0])
-def test_fp32_codes_beside_their_boundaries(g, force_kernel, s):
-    s = np.float32(s)
+def _beside_boundaries(s):
+    """Of one code and the next under the scale s, and values of other kinds"""
     h = (np.arange(-131, 131) + 0.5).astype(np.float32) * s
     steps = [h]
     for way in (np.float32(np.inf), np.float32(-np.inf)):
@@ -177,8 +173,16 @@ def test_fp32_codes_beside_their_boundaries(g, force_kernel, s):
         for _ in range(3):
             v = np.nextafter(v, way)
             steps.append(v)
-    x = np.concatenate(steps + [np.array([0.0, -0.0, np.inf, -np.inf, np.nan, 3e38, -3e38, 1e-40, 6e4 * s, -6e4 * s], np.float32)])
-    x = np.resize(x, 2048).astype(np.float32)
+    return np.concatenate(steps + [np.array([0.0, -0.0, np.inf, -np.inf, np.nan, 3e38, -3e38, 1e-40, 6e4 * s, -6e4 * s], np.float32)])
+
+
+# fp32 values on the boundaries between codes and up to 3 units in the last place beside them, through the fp32 quantiser and through
+# every kernel's int8 output (zero activations: the value quantised is the bias); scales with a mantissa of ones, too small for
+# the factor 65536 of the reciprocal, huge, negative, zero
+@pytest.mark.parametrize("s", [0.03, 1 / 3, 4 / 127, 2.0 ** -7, float(np.nextafter(np.float32(0.5), np.float32(0))), -0.07, 1e-3, 3e-34, 1e-36, 1e30, 0.0])
+def test_fp32_codes_beside_their_boundaries(g, force_kernel, s):
+    s = np.float32(s)
+    x = np.resize(_beside_boundaries(s), 2048).astype(np.float32)
     with np.errstate(all="ignore"):
         exp, _ = oracle.quantize_tensor_int8(x[None], scale=float(s))
     scale = dev(np.array([s]))
@@ -192,3 +196,20 @@ def test_fp32_codes_beside_their_boundaries(g, force_kernel, s):
                 force_kernel(kernel)
                 y = host(g.spgemm_int8(X, packed, N, act_scale=one, w_scale=torch.zeros(N, device="cuda"), bias=dev(x[:N]), out_dtype=torch.int8, out_scale=scale))
                 assert np.array_equal(y, np.broadcast_to(exp[:, :N], (M, N))), (N, M, kernel)
+
+
+# the same values as fp32 activations that the kernel for few rows quantises: their codes written out, and the operand itself (its
+# product with the unit matrix); a workgroup of 4 wavefronts (2 K steps) and of 8 (5 steps, the last one short)
+@pytest.mark.parametrize("s", [0.03, 1 / 3, 4 / 127, 2.0 ** -7, float(np.nextafter(np.float32(0.5), np.float32(0))), -0.07, 1e-3, 3e-34, 1e-36, 1e-45, 1e30, 0.0, -0.0,
+                               np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("M,K", [(8, 256), (5, 560)])
+def test_fp32_codes_beside_their_boundaries_inside_the_gemm(g, s, M, K):
+    s = np.float32(s)
+    X = np.resize(_beside_boundaries(s if np.isfinite(s) else np.float32(0.03)), M * K).astype(np.float32).reshape(M, K)
+    with np.errstate(all="ignore"):
+        exp, _ = oracle.quantize_tensor_int8(X, scale=float(s))
+    assert g.lib().gpusq_linear_int8_launches(g.F32, M, K, K, 0, 1, 0) == 1
+    packed = g.pack(*g.compress(torch.eye(K, dtype=torch.int8, device="cuda")), K)
+    Y, Xq = torch.empty((M, K), dtype=torch.int32, device="cuda"), torch.full((M, K), 99, dtype=torch.int8, device="cuda")
+    g.calls.gpusq_linear_int8(dev(X), g.F32, packed, dev(np.array([s])), 1, None, None, Y, g.I32, None, Xq, None, M, K, K, 0)
+    assert np.array_equal(host(Xq), exp) and np.array_equal(host(Y), exp)

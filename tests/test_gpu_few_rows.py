@@ -130,44 +130,48 @@ def test_one_call_layer_of_fp32_rows(g, M, K, N, given):
     assert np.array_equal(host(Y), oracle.epilogue_int8_f32(acc, float(s[0]), s_w, bias, out_scale=float(so))["q8"])
 
 
-# a square layer run on its own output, whole or partly over X: as from a copy of X, where the GEMM would quantise for itself
+# a square layer run on its own output, whole or partly over X, or from half of the bytes of fp32 rows on (right behind fp16 ones): as
+# from a copy of X, where the GEMM would quantise for itself
 @pytest.mark.parametrize("M,K", [(64, 768), (197, 768), (16, 256)])
 @pytest.mark.parametrize("given", [False, True])
-@pytest.mark.parametrize("shift", [0, 8, -8])
-def test_one_call_layer_writes_over_its_input(g, M, K, given, shift):
-    N = K
-    assert g.lib().gpusq_linear_int8_launches(g.F16, M, N, K, g.EPI_BIAS, int(given), 0) < (2 if given else 3)
+@pytest.mark.parametrize("shift", [0, 8, -8, "M * K"])
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+def test_one_call_layer_writes_over_its_input(g, M, K, given, shift, dtype):
+    N, shift, x_dt = K, M * K if shift == "M * K" else shift, g.F16 if dtype == np.float16 else g.F32
+    assert g.lib().gpusq_linear_int8_launches(x_dt, M, N, K, g.EPI_BIAS, int(given), 0) < (2 if given else 3)
     Wq, s_w, vals, meta = _oracle_weights(synth.weights(N, K, seed=M, ids=(5,), sigma=0.05))
     packed, sw, b = g.pack(dev(vals), dev(meta), K), dev(s_w), dev(synth.bias(N, seed=M, ids=(6,)))
-    X = (np.random.default_rng(M).standard_normal((M, K)) * 1.5).astype(np.float16)
+    X = (np.random.default_rng(M).standard_normal((M, K)) * 1.5).astype(dtype)
     scale = dev(np.array([4 / 127], np.float32)) if given else torch.empty(1, dtype=torch.float32, device="cuda")
     y, q, s = _layer(g, dev(X), packed, sw, b, M, N, K, scale if given else None)
-    buf = torch.zeros(M * K + 16, dtype=torch.float16, device="cuda")
-    x, over = buf[8:8 + M * K], buf[8 + shift:8 + shift + M * N]
+    buf = torch.zeros(3 * M * K + 16, dtype=torch.float16, device="cuda")
+    x, over = buf[8:8 + M * K * X.itemsize // 2].view(dev(X).dtype), buf[8 + shift:8 + shift + M * N]
     x.copy_(dev(X).view(-1))
     Xq, ws = torch.full((M, K), 99, dtype=torch.int8, device="cuda"), torch.empty(4096, dtype=torch.uint8, device="cuda")
-    g.calls.gpusq_linear_int8(x, g.F16, packed, scale, int(given), sw, b, over, g.F16, None, Xq, ws, M, N, K, g.EPI_BIAS)
+    g.calls.gpusq_linear_int8(x, x_dt, packed, scale, int(given), sw, b, over, g.F16, None, Xq, ws, M, N, K, g.EPI_BIAS)
     assert np.array_equal(host(Xq), q) and host(scale)[0] == s[0]
     assert np.array_equal(host(over).reshape(M, N).view(np.uint16), y.view(np.uint16))
 
 
 # out_scale the activation scale that the call itself finds (by every workgroup, or behind a range pass), and Y over the partial
 # maxima of the range pass: as from operands that lie apart
-@pytest.mark.parametrize("M,K,N", [(64, 768, 1000), (197, 768, 768), (197, 768, 2304)])
+@pytest.mark.parametrize("M,K,N,dtype", [(64, 768, 1000, np.float16), (197, 768, 768, np.float16), (197, 768, 2304, np.float16), (64, 768, 1000, np.float32),
+                                         (197, 768, 768, np.float32), (197, 512, 2304, np.float32), (40, 256, 512, np.float32)])
 @pytest.mark.parametrize("out", ["scale", "workspace"])
-def test_one_call_layer_with_shared_operands(g, M, K, N, out):
-    assert g.lib().gpusq_linear_int8_launches(g.F16, M, N, K, g.EPI_BIAS, 0, 0) < 3
+def test_one_call_layer_with_shared_operands(g, M, K, N, dtype, out):
+    x_dt = g.F16 if dtype == np.float16 else g.F32
+    assert g.lib().gpusq_linear_int8_launches(x_dt, M, N, K, g.EPI_BIAS, 0, 0) < 3
     Wq, s_w, vals, meta = _oracle_weights(synth.weights(N, K, seed=M, ids=(7,), sigma=0.05))
     packed, sw, b = g.pack(dev(vals), dev(meta), K), dev(s_w), dev(synth.bias(N, seed=M, ids=(8,)))
-    x = dev((np.random.default_rng(N).standard_normal((M, K)) * 1.5).astype(np.float16))
+    x = dev((np.random.default_rng(N).standard_normal((M, K)) * 1.5).astype(dtype))
     exp_q, exp_s = g.quantize_int8(x, g.PER_TENSOR)
     Xq, scale = torch.empty((M, K), dtype=torch.int8, device="cuda"), torch.full((1,), 1e3, device="cuda")
     if out == "scale":  # the scale in memory before the call is another one
         Y, ws = torch.empty((M, N), dtype=torch.int8, device="cuda"), torch.empty(4096, dtype=torch.uint8, device="cuda")
         exp = g.spgemm_int8(exp_q, packed, N, act_scale=exp_s, w_scale=sw, bias=b, out_dtype=torch.int8, out_scale=exp_s)
-        g.calls.gpusq_linear_int8(x, g.F16, packed, scale, 0, sw, b, Y, g.I8, scale, Xq, ws, M, N, K, g.EPI_BIAS)
+        g.calls.gpusq_linear_int8(x, x_dt, packed, scale, 0, sw, b, Y, g.I8, scale, Xq, ws, M, N, K, g.EPI_BIAS)
     else:
         Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
         exp = g.spgemm_int8(exp_q, packed, N, act_scale=exp_s, w_scale=sw, bias=b)
-        g.calls.gpusq_linear_int8(x, g.F16, packed, scale, 0, sw, b, Y, g.F16, None, Xq, Y, M, N, K, g.EPI_BIAS)
+        g.calls.gpusq_linear_int8(x, x_dt, packed, scale, 0, sw, b, Y, g.F16, None, Xq, Y, M, N, K, g.EPI_BIAS)
     assert torch.equal(Xq, exp_q) and torch.equal(scale, exp_s) and torch.equal(Y, exp)
