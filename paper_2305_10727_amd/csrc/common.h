@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "../../include/gpusq.h"
+#include "launch_rules.h"
 
 namespace gpusq {
 
@@ -36,7 +37,6 @@ __host__ __device__ constexpr int index_offset(bool is_i8, int f, int l) {
   return kTileValueBytes + (f >> 3) * (64 * 8 * ib) + l * (8 * ib) + (f & 7) * ib;
 }
 
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Row r (0..15) of fragment t (0..3) inside a 64-row block holds output channel
 //   n = 64*blk + 32*(t/2) + 8*(r/4) + 4*(t%2) + (r%4).

@@ -37,13 +37,9 @@ __global__ void __launch_bounds__(256) prune_pairs_f32_kernel(const float4* __re
 }
 
 gpusq_status launch_prune_pairs(const float* Win, float* Wout, uint8_t* mask, int one_per_group, int64_t N, int64_t K, hipStream_t s) {
-  const int64_t chunks = N * (K / 8);
-  // (rows of fewer than 64 chunks, longer rows or more of them than the grid's second and third dimensions count: whole workgroups of
-  // consecutive chunks)
-  const bool by_rows = K / 2 >= 256 && K / 2 <= 256 * (int64_t)65535 && ceil_div(N, 32) <= 65535;
-  const int64_t per_rows = by_rows ? K / 2 : 256 * ceil_div(chunks, (int64_t)256 * 8 * 65535);
-  const dim3 grid(8, (unsigned)ceil_div(per_rows, 256), (unsigned)ceil_div(chunks, 8 * per_rows));
-  prune_pairs_f32_kernel<<<grid, 256, 0, s>>>((const float4*)Win, (float4*)Wout, mask, one_per_group, chunks, per_rows);
+  const PrunePairsGrid g = prune_pairs_grid(N, K);
+  const dim3 grid(8, (unsigned)g.y, (unsigned)g.z);
+  prune_pairs_f32_kernel<<<grid, 256, 0, s>>>((const float4*)Win, (float4*)Wout, mask, one_per_group, N * (K / 8), g.per_rows);
   return check_launch();
 }
 

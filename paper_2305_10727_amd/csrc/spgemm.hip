@@ -635,21 +635,13 @@ int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, 
   return linear_int8_launches(a, dt, scale_is_input, cus > 0 ? cus : num_cus(), folds);
 }
 
-static bool overlap(const void* p, int64_t p_bytes, const void* q, int64_t q_bytes) {
-  const uintptr_t a = (uintptr_t)p, b = (uintptr_t)q;
-  return a < b + (uintptr_t)q_bytes && b < a + (uintptr_t)p_bytes;
-}
-
 gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, void* workspace, hipStream_t s) {
   bool folds;
   const int launches = linear_int8_launches(a, dt, scale_is_input, num_cus(), folds);
   a.act_scale = scale;
-  // The operands may overlap in ways in which only a GEMM behind a finished quantiser gives the same: Y over X (a square layer run
-  // on its own output) or over the partial maxima, which the GEMM that quantises reads in every workgroup, beside others that
-  // already write; and an out_scale that is the activation scale itself, which it would read while one workgroup writes it.
-  const int64_t y_bytes = (int64_t)a.M * a.N * dtype_bytes(a.out_dt), range_bytes = (int64_t)gpusq_quantize_workspace_bytes(GPUSQ_PER_TENSOR, a.M, a.K);
-  const bool apart = !overlap(a.X, (int64_t)a.M * a.K * dtype_bytes(dt), a.Y, y_bytes) &&
-                     (scale_is_input || (a.out_scale != scale && (launches == 1 || !overlap(workspace, range_bytes, a.Y, y_bytes))));
+  const int64_t range_bytes = launches == 2 ? (int64_t)gpusq_quantize_workspace_bytes(GPUSQ_PER_TENSOR, a.M, a.K) : 0;
+  const bool apart = may_quantise_inside(a.X, dtype_bytes(dt), a.Y, dtype_bytes(a.out_dt), a.M, a.N, a.K, scale, scale_is_input != 0, a.out_scale,
+                                         workspace, range_bytes);
   if (folds && apart) {
     a.x_f16 = dt == GPUSQ_F32 ? 2 : 1;
     a.xq_out = Xq;

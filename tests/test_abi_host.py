@@ -271,3 +271,14 @@ def test_every_tile_of_the_one_workgroup_kernel_is_met_once(tmp_path):
     assert build.returncode == 0, build.stderr
     run = subprocess.run([exe, "20000"], capture_output=True, text=True, timeout=120)
     assert run.returncode == 0 and run.stdout == "20000 plans\n", run.stdout
+
+
+def test_launch_rules(tmp_path):
+    """The grid of the pair-wise pruning kernel and the question whether a GEMM may quantise its own activations, by the code the
+    library launches with (launch_rules_walk.cpp)"""
+    exe = str(tmp_path / "rules")
+    build = subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2305_10727_amd", "csrc"),
+                            os.path.join(ROOT, "tests", "launch_rules_walk.cpp"), "-o", exe], capture_output=True, text=True)
+    assert build.returncode == 0, build.stderr
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0 and run.stdout == "ok\n", run.stdout
