@@ -228,7 +228,7 @@ gpusq_status gpusq_prepare_weights(const float* W, gpusq_dtype dt, float* W_prun
   if (st != GPUSQ_OK) return st;
   if (dt != GPUSQ_F16 && dt != GPUSQ_I8) return GPUSQ_ERR_UNSUPPORTED;
   if (dt == GPUSQ_I8 && !w_scale) return GPUSQ_ERR_NULL;
-  if (K > 16384) return GPUSQ_ERR_UNSUPPORTED;
+  if (K > kPrepareMaxK) return GPUSQ_ERR_UNSUPPORTED;
   if (!aligned16(W) || !aligned16(packed) || (W_pruned && !aligned16(W_pruned)) || (W_low && !aligned16(W_low)) ||
       (values && !aligned16(values)) || (meta && !aligned16(meta)))
     return GPUSQ_ERR_ALIGN;

@@ -23,6 +23,7 @@ constexpr int kTileRows = 256;         // output channels per packed tile
 constexpr int kStepBytes = 128;        // bytes of a dense activation row consumed per K step
 constexpr int kFragValueBytes = 1024;  // 64 lanes x 16 bytes of kept values
 constexpr int kTileValueBytes = 16 * kFragValueBytes;
+constexpr int kPrepareMaxK = 16384;    // longest row that gpusq_prepare_weights takes
 
 __host__ __device__ constexpr int step_elems(bool is_i8) { return is_i8 ? 128 : 64; }
 // index bytes of one fragment: 2 bits per kept value; 16 int8 values (32 bits) or 8 fp16 values (16 bits) per lane

@@ -1100,10 +1100,11 @@ __global__ void __launch_bounds__(256) prepare_weights_kernel(const float* __res
 
 // The same where only what the sparse GEMM reads is asked for (packed operand, scales): a row stays in B registers of 16 bytes per
 // lane (B = 8: or comes in batches of 8), loads and stores have a wavefront's address and a 32-bit lane offset that grows by a constant,
-// an int8 code takes five operations (see ByteQuantiser), and what few wavefronts run stands behind.  Some 45 vector instructions for a
+// an int8 code takes some four operations (see ByteQuantiser), and what few wavefronts run stands behind.  Some 45 vector instructions for a
 // group of 4 where the kernel above takes 130; with its 114 registers it also leaves a fifth of the wavefronts of 5120 x 1280 to a
-// second round.  5120 x 1280 int8 12.3 us, 9.2 so;
-// fp16 10.5, 9.3; 3072 x 768 int8 6.6, 4.8; 768 x 192 3.4, 2.5.  What is left is one burst: all rows are asked for at once and come at some 6 TB/s.
+// second round.  5120 x 1280 int8 12.3 us, 9.2 so; fp16 10.5, 9.3; 3072 x 768 int8 6.6, 4.8; 768 x 192 3.4, 2.5.  What is left is one burst: all
+// rows are asked for at once and come at some 6 TB/s.
+// The 32-bit offsets inside a row and inside a column of packed tiles hold K up to kPrepareMaxK with much to spare.
 template <bool IS_I8, int WPR, int B>
 __global__ void __launch_bounds__(256) prepare_packed_kernel(const float* __restrict__ W, float* __restrict__ w_scale,
                                                              uint8_t* __restrict__ packed, int64_t N, int K, int ksteps) {
@@ -1225,7 +1226,7 @@ gpusq_status launch_prepare_weights(const float* W, gpusq_dtype dt, float* Wp, v
   const bool is_i8 = dt == GPUSQ_I8;
   const int ksteps = (int)ceil_div(K, step_elems(is_i8));
   const unsigned tiles = (unsigned)ceil_div(N, kTileRows);  // the padding rows of the last tile have their workgroups as well
-  if (!Wp && !Wlow && !values && !meta && K < (1 << 20)) {  // (32-bit offsets inside a row and a column of packed tiles)
+  if (!Wp && !Wlow && !values && !meta) {
     if (is_i8 && K > 2048) launch_prepare_packed<true, 4>(W, w_scale, (uint8_t*)packed, N, K, ksteps, tiles, s);
     else if (is_i8) launch_prepare_packed<true, 1>(W, w_scale, (uint8_t*)packed, N, K, ksteps, tiles, s);
     else if (K > 2048) launch_prepare_packed<false, 4>(W, w_scale, (uint8_t*)packed, N, K, ksteps, tiles, s);
