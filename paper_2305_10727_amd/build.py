@@ -13,7 +13,7 @@ SOURCES = ["api.hip", "prep.hip", "int4.hip", "spgemm.hip", "fewrows.hip", "tile
 FASTCALL = os.path.join(HERE, "_fastcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off",
-    # packed-fp32 instructions are kept out of the generated code on the test machines
+    # packed-fp32 instructions are kept out of the generated code: some of their forms give wrong results
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-value", "-Wno-inline-asm",
 ]

@@ -342,9 +342,9 @@ int set_forced_kernel(int kernel) {
 }
 
 // The estimate that decides which problems may quantise fp16 activations on their way into the small kernel (see kernel_choice), of
-// the tile kernel in full and tail tiles of whole 64-row units: run time (microseconds) of one tile of 64*tm rows.  A K step costs nearly the same whatever tm (a short tile copies and reads whole operands and only leaves out the matrix
-// instructions of the slabs it does not have: 1.1 us for tm = 4, about 0.075 us less per slab left out), the epilogue
-// scales with the rows stored and is larger with GELU.
+// the tile kernel in full and tail tiles of whole 64-row units: run time (microseconds) of one tile of 64*tm rows.  A K step costs nearly
+// the same whatever tm (a short tile copies and reads whole operands and only leaves out the matrix instructions of the slabs it does not
+// have: 1.1 us for tm = 4, about 0.075 us less per slab left out), the epilogue scales with the rows stored and is larger with GELU.
 // `busy` is the fraction of the CUs that have a workgroup: the fewer run, the faster each one's K steps (the chip runs
 // at its power limit when all of them multiply: 1.1 us per step on 256 CUs, 0.63 on 150, 0.46 on 100).
 static double tile_cost(int tm, int ksteps, bool gelu, double busy) {
@@ -412,9 +412,6 @@ static TilePlan make_plan(int M, int N, int resident, int ksteps, bool gelu) {
   return best;
 }
 
-// Which kernel a problem takes: 0 = small kernel with 64 x 64 tiles, 1 = small kernel with 128 x 128 tiles, 2 = tile
-// kernel with one workgroup per CU, 3 = with two, 4 = the kernel for few rows.  fused_patches: the patch gather exists in kernels 2 and 4
-// only.
 // Few rows: 4 (the kernel with K split over its wavefronts), 0 (the 64 x 64 tiles) or -1 (by the estimates), by how many of the
 // former's 64-channel x 32-row tiles each CU gets.  Two of its workgroups run side by side on a CU (int8; fp16: three), and where
 // K has few steps another round costs most of a launch.  Timed at 7 widths, which agree; 768 channels, few rows / 64 x 64 tiles /
@@ -467,6 +464,9 @@ static bool kernel3_ahead(const EvenRounds& e, bool is_i8, bool gelu, int64_t M,
   return e.r == 2 && e.u <= 5;
 }
 
+// Which kernel a problem takes: 0 = small kernel with 64 x 64 tiles, 1 = small kernel with 128 x 128 tiles, 2 = tile
+// kernel with one workgroup per CU, 3 = with two, 4 = the kernel for few rows.  fused_patches: the patch gather exists in kernels 2 and 4
+// only.
 static int kernel_choice(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu, int resident, bool fused_patches = false, bool x_f16 = false) {
   const int64_t k_bytes = K * (is_i8 ? 1 : 2);
   const int64_t ksteps = ceil_div(k_bytes, kStepBytes);
@@ -475,8 +475,8 @@ static int kernel_choice(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu,
   if (const int c = g_forced_kernel.load(std::memory_order_relaxed); c >= 0) {
     if (c != 3 || k_bytes % kStepBytes == 0) return c;
   }
-  // (the fused patch gather is refused up to 256 K outputs; beyond, it takes the kernel a GEMM of its sizes would, so that both
-  // add up in the same order)
+  // (the fused patch gather is refused up to 256 K outputs; beyond, it goes to the kernel for few rows where a GEMM of its sizes would, else
+  // to kernel 2, whichever of 0, 2 and 3 the GEMM takes: those add up in one order)
   if (fused_patches && M * N <= (int64_t)256 * 1024) return 0;
   // (the patch gather has no 64 x 64 tiles)
   if (const int c = few_rows_choice(is_i8, M, N, ksteps, resident); c == 4 || (c == 0 && !fused_patches)) return c;

@@ -30,7 +30,7 @@ def _fma32(a, b, c):
 
 
 def gelu_fit_f32(x):
-    """the kernel's operation sequence (gelu_f32) in numpy; v_exp_f32 is modelled as a correctly rounded 2^p"""
+    """the kernel's operation sequence (gelu_f32_x8) in numpy; v_exp_f32 is modelled as a correctly rounded 2^p"""
     P = coefficients()
     x = np.asarray(x, np.float32)
     t = np.abs(x)
