@@ -53,7 +53,8 @@ __device__ __forceinline__ void compress_chunk(unsigned w0, unsigned w1, unsigne
   auto key_of = [](unsigned pair) { return __builtin_amdgcn_sad_u8(pair, 0x80808080u, 0u); };
   const unsigned k0 = key_of((z0 & 0xFFFFu) | 0x80800000u), k1 = key_of((z0 >> 16) | 0x80800000u);
   const unsigned k2 = key_of((z1 & 0xFFFFu) | 0x80800000u), k3 = key_of((z1 >> 16) | 0x80800000u);
-  // the selection rule of keep_mask_of_4 on lane masks (see prepare_weights_kernel)
+  // the selection rule of keep_mask_of_4 on lane masks, as KeptPair has it (through one struct for both the pass takes 4 % longer: 5120 x 1280
+  // 3.36 -> 3.53 us)
   const bool c01 = k1 > k0, c02 = k2 > k0, c03 = k3 > k0, c12 = k2 > k1, c13 = k3 > k1, c23 = k3 > k2;
   auto two_of = [](bool p, bool q, bool r) { return (p & q) | (r & (p | q)); };
   const bool keep0 = !two_of(c01, c02, c03), keep1 = !two_of(!c01, c12, c13), keep2 = !two_of(!c02, !c12, c23);

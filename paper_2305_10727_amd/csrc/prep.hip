@@ -907,20 +907,6 @@ gpusq_status launch_pack(const void* values, const uint8_t* meta, void* packed, 
 }
 
 // ------------------------------------------------------------------------------------------------------------ fused
-// prune -> (INT8: per-output-channel quantise | FP16: round) -> compress -> pack for one weight matrix in one launch.
-// One wavefront per output channel, one lane per group of 4: a lane prunes its group, quantises or rounds it, applies the
-// compression rule to the low-precision group and writes its two kept values and its positions to every requested output.
-// All arithmetic is the same sequence of operations as the separate kernels above, so the results are bit-identical to running
-// them in turn.  (Pruning never removes the row maximum, so the maximum of the row is that of the pruned row.)
-// What bounds it is latency: the row, its maximum, the codes.  So a row's groups are requested in batches of kPrepBatch per
-// lane, all before the first is used, and a row of one batch stays in registers (a longer one is read twice, the second time
-// from the L2); the maximum takes wavefront shuffles.  Rows of more than 2048 elements are dealt out over WPR = 4 wavefronts
-// (768 x 3072: with one wavefront per row the chip has fewer wavefronts than SIMDs).  A workgroup takes 4 (WPR = 4: 1) rows of
-// a fragment, and the workgroups whose packed lanes share 128-byte lines run on one XCD.  The rows of the packed
-// tiles past N and the K range past the row end are written (zero) by the wavefronts that own them.
-// With a thread per 32 elements, LDS for the rows and one load in flight per thread, int8: 3072 x 768 9.8 us, 6.0 so; 768 x
-// 3072 10.0, 6.1 so; 5120 x 1280 17.3, 12.2 so.  Workgroups of 256 threads: with 512 and 1024 the 1280 x 5120 take 16 and 20
-// us instead of 13 (their last round is thin), and WPR = 4 at K = 768 12 instead of 6 (one row per workgroup).
 // The two kept elements of a group of 4 and their positions: the selection rule of keep_mask_of_4 on lane masks (element i is dropped iff two
 // or more of the others beat it, where of a pair the second beats the first iff it is larger: six comparisons, the rest is scalar logic).
 struct KeptPair {
@@ -976,6 +962,20 @@ __device__ __forceinline__ int prepare_place() {
   return (id & ~(8 * SHARE - 1)) | ((id & 7) * SHARE) | ((id >> 3) & (SHARE - 1));
 }
 
+// prune -> (INT8: per-output-channel quantise | FP16: round) -> compress -> pack for one weight matrix in one launch.
+// One wavefront per output channel, one lane per group of 4: a lane prunes its group, quantises or rounds it, applies the
+// compression rule to the low-precision group and writes its two kept values and its positions to every requested output.
+// All arithmetic is the same sequence of operations as the separate kernels above, so the results are bit-identical to running
+// them in turn.  (Pruning never removes the row maximum, so the maximum of the row is that of the pruned row.)
+// What bounds it is latency: the row, its maximum, the codes.  So a row's groups are requested in batches of kPrepBatch per
+// lane, all before the first is used, and a row of one batch stays in registers (a longer one is read twice, the second time
+// from the L2); the maximum takes data-parallel primitives (wave_max_magnitude).  Rows of more than 2048 elements are dealt out over WPR = 4 wavefronts
+// (768 x 3072: with one wavefront per row the chip has fewer wavefronts than SIMDs).  A workgroup takes 4 (WPR = 4: 1) rows of
+// a fragment, and the workgroups whose packed lanes share 128-byte lines run on one XCD.  The rows of the packed
+// tiles past N and the K range past the row end are written (zero) by the wavefronts that own them.
+// With a thread per 32 elements, LDS for the rows and one load in flight per thread, int8: 3072 x 768 9.8 us, 6.0 so; 768 x
+// 3072 10.0, 6.1 so; 5120 x 1280 17.3, 12.2 so.  Workgroups of 256 threads: with 512 and 1024 the 1280 x 5120 take 16 and 20
+// us instead of 13 (their last round is thin), and WPR = 4 at K = 768 12 instead of 6 (one row per workgroup).
 constexpr int kPrepBatch = 8;
 template <bool IS_I8, int WPR>
 __global__ void __launch_bounds__(256) prepare_weights_kernel(const float* __restrict__ W, float* __restrict__ Wp,
@@ -1043,8 +1043,7 @@ __global__ void __launch_bounds__(256) prepare_weights_kernel(const float* __res
       unsigned p0 = two.p0, p1 = two.p1;
       const bool in_row = g < groups;
       if (Wp && in_row) *(float4*)(Wp + n * K + 4 * g) = float4{keep0 ? x.x : 0.0f, keep1 ? x.y : 0.0f, keep2 ? x.z : 0.0f, keep3 ? x.w : 0.0f};
-      // the two kept values in low precision; the positions recorded are those of the rule applied to the low-precision group,
-      // which differ only where a kept value became zero (then zeros are kept from the lowest index on)
+      // the two kept values in low precision
       unsigned kept;
       bool zero;
       if constexpr (IS_I8) {
