@@ -23,12 +23,14 @@ def main():
     ap.add_argument("--path", default="int8", choices=["int8", "fp16"])
     ap.add_argument("--kind", default="sparse", choices=["sparse", "dense"])
     ap.add_argument("--out", default="fp16", choices=["fp16", "int8"], help="output type of the int8 path")
+    ap.add_argument("--K", type=int, default=0, help="reduction length in place of the layer's (a short one is almost only epilogue)")
     ap.add_argument("--iters", type=int, default=20)
     ap.add_argument("--calibrate", action="store_true")
     a = ap.parse_args()
     cfg = synth.CONFIGS[a.config]
     M = cfg["M"]
     _, K, N, gelu, dist = [l for l in cfg["layers"] if l[0] == a.layer][0]
+    K = a.K or K
     dev = torch.device("cuda")
     g = torch.Generator(device=dev)
     g.manual_seed(0)

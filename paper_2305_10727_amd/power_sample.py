@@ -47,6 +47,8 @@ def main():
     ap.add_argument("--layer", default="fc1")
     ap.add_argument("--path", default="int8", choices=["int8", "fp16"])
     ap.add_argument("--kind", default="sparse", choices=["sparse", "dense"])
+    ap.add_argument("--out-type", default="fp16", choices=["fp16", "int8"], help="output type of the int8 path")
+    ap.add_argument("--K", type=int, default=0, help="reduction length in place of the layer's")
     ap.add_argument("--seconds", type=float, default=8.0)
     ap.add_argument("--us-per-launch", type=float, default=40.0, help="rough launch time, to size the child's loop")
     ap.add_argument("--out", default="")
@@ -54,7 +56,7 @@ def main():
     lines = ["command: python3 -m paper_2305_10727_amd.power_sample " + " ".join(sys.argv[1:]), "", "idle before: " + sample()]
     iters = int(a.seconds * 1e6 / a.us_per_launch)
     child = subprocess.Popen([sys.executable, "-m", "paper_2305_10727_amd.gemm_loop", "--config", a.config, "--layer", a.layer,
-                              "--path", a.path, "--kind", a.kind, "--iters", str(iters)], stdout=subprocess.PIPE, text=True)
+                              "--path", a.path, "--kind", a.kind, "--out", a.out_type, "--K", str(a.K), "--iters", str(iters)], stdout=subprocess.PIPE, text=True)
     t0 = time.time()
     time.sleep(1.0)
     while child.poll() is None and time.time() - t0 < a.seconds + 120:

@@ -1,6 +1,6 @@
 """Per-GEMM timing table over the linear-layer shapes of all workload configurations (c0 ... c4): sparse INT8 and FP16
 against their dense twins, with buffers that stay in the memory-side cache ("hot") and with a rotation of buffer sets
-larger than it ("cold").  `python -m paper_2305_10727_amd.report [--out FILE]` on a GPU machine; prints a markdown table.
+larger than it ("cold").  `python -m paper_2305_10727_amd.report [--out FILE]` on a machine with the GPU; prints a markdown table.
 
 Inputs are random device tensors of the configurations' shapes and distributions (N(0,1) activations, N(0, 0.02)
 weights); every number is a sparse or dense GEMM launch through the C ABI, timed with HIP events on the launch stream.
@@ -113,6 +113,70 @@ def layer_rows(M, K, N, gelu, iters):
     return rows
 
 
+def choice_rows(count, seed=0):
+    """The size rules' choice between the tile kernels (ids 2, 3) and the 64 x 64 tiles (0), against the three timed: random layers
+    of whole K steps with more rows than the kernel for few of them takes, three buffers in turn, the kernels in turn, median of
+    five rounds."""
+    import random
+    rng, dev, rows = random.Random(seed), torch.device("cuda"), []
+    log = lambda lo, hi: int(round(lo * (hi / lo) ** rng.random()))
+    while len(rows) < count:
+        prec, gelu = rng.choice(("int8", "fp16")), rng.random() < 0.4
+        out = rng.choice((torch.float16, torch.int8)) if prec == "int8" else torch.float16
+        K, N = log(64, 5120) // 64 * 64, log(64, 5120) // 64 * 64
+        if prec == "int8":
+            K = -(-K // 128) * 128
+        M = log(600, min(65792, (1 << 38) // (K * N)))
+        epi = G.EPI_BIAS | (G.EPI_GELU if gelu else 0)
+        wdt = torch.int8 if prec == "int8" else torch.float16
+        few = -(-M // 32) * -(-N // 64) <= (3 if prec == "int8" else 5) * 256  # (the kernel for few rows is not among the three)
+        if few or M * N <= 256 * 1024:
+            continue
+        rule = G.spgemm_plan(wdt, M, N, K, epi)["kernel"]
+        W, bias, out_scale = torch.randn(N, K, device=dev) * 0.02, torch.randn(N, device=dev) * 0.01, torch.full((1,), 0.02, device=dev)
+        sets = []
+        for _ in range(3):
+            lin = SparseLinear(M, K, N, prec, gelu=gelu, bias=True, out_dtype=out)
+            if sets:
+                for name in ("packed",) + (("w_scale",) if prec == "int8" else ()):
+                    setattr(lin, name, getattr(sets[0][0], name))
+            else:
+                lin.prepare_weights(W)
+            X = torch.randn(M, K, device=dev).half()
+            if prec == "int8":
+                lin.quantize_activations(X)
+            sets.append((lin, X))
+        fns = [lambda s=s: s[0].gemm(s[1], bias, out_scale) for s in sets]
+        samples = {k: [] for k in (0, 2, 3)}
+        iters = 30 if M * N * K < 1 << 34 else 9
+        for _round in range(5):
+            for k in samples:
+                G.force_kernel(k)
+                samples[k].append(_time(fns, iters))
+        G.force_kernel(None)
+        rows.append(dict(M=M, K=K, N=N, prec=prec, gelu=gelu, out="int8" if out == torch.int8 else "fp16", rule=rule,
+                         t={k: sorted(v)[2] for k, v in samples.items()}))
+        print("%s" % rows[-1], flush=True)
+        del sets, fns
+        torch.cuda.empty_cache()
+    return rows
+
+
+def choice_report(count):
+    rows = choice_rows(count)
+    loss = lambda sel: "%.1f %%" % (100 * (sum(r["t"][r["rule"]] / min(r["t"].values()) for r in sel) / len(sel) - 1))
+    lines = ["%d random layers: the kernel that the size rules pick is %s behind the fastest of the three on average (always kernel 2: %s)." % (
+        len(rows), loss(rows), "%.1f %%" % (100 * (sum(r["t"][2] / min(r["t"].values()) for r in rows) / len(rows) - 1))), "",
+        "| path | GELU | output | layers | behind the fastest |", "|---|---|---|---|---|"]
+    for prec, gelu, out in sorted({(r["prec"], r["gelu"], r["out"]) for r in rows}):
+        sel = [r for r in rows if (r["prec"], r["gelu"], r["out"]) == (prec, gelu, out)]
+        lines.append("| %s | %s | %s | %d | %s |" % (prec, "yes" if gelu else "no", out, len(sel), loss(sel)))
+    lines += ["", "| M | K | N | path | GELU | output | rule | kernel 0 us | kernel 2 us | kernel 3 us |", "|---|---|---|---|---|---|---|---|---|---|"]
+    lines += ["| %d | %d | %d | %s | %s | %s | %d | %.1f | %.1f | %.1f |" % (r["M"], r["K"], r["N"], r["prec"], "yes" if r["gelu"] else "no", r["out"],
+                                                                         r["rule"], r["t"][0], r["t"][2], r["t"][3]) for r in rows]
+    return lines
+
+
 def full_depth_row(cfg, prec, iters):
     """every linear layer of the model, depth times, each layer with weights of its own"""
     dev = torch.device("cuda")
@@ -161,7 +225,16 @@ def main():
     ap.add_argument("--configs", default="c0,c1,c2,c3,c4_vitl,c4_vith")
     ap.add_argument("--only-blocks", action="store_true", help="skip the per-layer and patch-embedding tables")
     ap.add_argument("--only-int4", action="store_true", help="only the INT4 format table")
+    ap.add_argument("--choices", type=int, default=0, help="only the kernel choice over so many random layers")
     a = ap.parse_args()
+    if a.choices:
+        text = "command: python -m paper_2305_10727_amd.report --choices %d\n\n" % a.choices + "\n".join(choice_report(a.choices)) + "\n"
+        if a.out:
+            with open(a.out, "w") as fh:
+                fh.write(text)
+        else:
+            print(text)
+        return
     lines = ["Sparse GEMM against its dense twin per linear layer.  The dense twin is the dense instantiation of tile kernel 3 (two workgroups "
              "per CU); `same template` is the sparse instantiation of that kernel, `sparse` the kernel the size rules pick (column `kernel`).  "
              "`ideal` = both sides on their own roofline at the nominal peaks (sparse 10.07 / 5.03, dense 5.03 / 2.52 P(FL)OP/s, 8 TB/s).", "",
@@ -234,7 +307,7 @@ def main():
     lines += ["", "Linear layers of one encoder block on the INT8 path (qkv, proj, fc1 + GELU, fc2; attention and normalisation left out: "
               "proj and fc1 read buffers that nothing refreshes), us per block, hot buffers.  Unchained: every layer writes fp16 and the next "
               "one quantises it with a dynamic per-tensor scale (12 launches).  Chained: static scales, the re-quantisation fused into the "
-              "producer's epilogue (6 launches), launched one by one or replayed as one HIP graph:", "",
+              "producer's epilogue (6 launches, with few rows 5 or 4), launched one by one or replayed as one HIP graph:", "",
               "| model | M | D | hidden | unchained us | chained us | chained, HIP graph us |", "|---|---|---|---|---|---|---|"]
     for model, M, D, hidden in [] if a.only_int4 else [("DeiT-Tiny, batch 1", 197, 192, 768), ("DeiT-Small, batch 1", 197, 384, 1536), ("ViT-B/16, batch 1", 197, 768, 3072),
                                 ("ViT-B/16, batch 8", 1576, 768, 3072), ("ViT-B/16, batch 64", 12608, 768, 3072)]:
