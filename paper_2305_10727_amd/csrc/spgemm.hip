@@ -456,7 +456,8 @@ static double estimate_kernel0(int64_t wgs64, int resident, bool is_i8, bool gel
 // Kernel 3's 64- and 128-row tiles on two workgroups per CU are ahead at the heights that fit them, with few K steps: one round of 2 units,
 // or of 8 while its own tiles are one round; two rounds of up to 5 (medians 2 to 9 % ahead; 12544 x 512 -> 1536 int8 output 15.7 / 14.1 us, 10216 x
 // 384 -> 2048 14.5 / 12.6, 1790 x 192 -> 1792 fp16 6.4 / 5.8; int8 with GELU at 2 units 6 % behind).  Beyond 8 steps even or behind, at all other
-// heights 2 to 20 % behind.
+// heights 2 to 20 % behind as a rule (of 300 sizes timed afterwards it was further ahead than 10 % at two: 21450 x 512 -> 1920 37.7 / 31.0, 20979 x 448 ->
+// 3392 fp16 66.8 / 58.7; the choice 1.1 % behind the fastest there, 31 % at the most: 33970 x 512 -> 128 goes to kernel 0, 11.5, with kernel 2 at 8.8).
 static bool kernel3_ahead(const EvenRounds& e, bool is_i8, bool gelu, int64_t M, int64_t N, int64_t ksteps, int resident) {
   const int64_t tiles = ceil_div(M, 128) * ceil_div(N, kTileBN);
   if (ksteps > 8) return false;
