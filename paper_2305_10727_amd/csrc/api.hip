@@ -310,6 +310,21 @@ gpusq_status gpusq_spgemm_int8(const int8_t* Xq, const void* Wpacked, const floa
   return launch_spgemm(true, a, (hipStream_t)stream);
 }
 
+gpusq_status gpusq_spgemm_int8_codes(const int8_t* Xq, const void* Wpacked, const float* act_scale, const float* w_scale,
+                                     const float* bias, void* Y, int8_t* Yq, const float* codes_scale, int64_t M, int64_t N, int64_t K,
+                                     int epilogue, void* stream) {
+  gpusq_status st = check_gemm(Xq, Wpacked, bias, Y, M, N, K, epilogue);
+  if (st != GPUSQ_OK) return st;
+  if (!Yq || !codes_scale) return GPUSQ_ERR_NULL;
+  if (!aligned16(Yq)) return GPUSQ_ERR_ALIGN;
+  if (epilogue & GPUSQ_EPI_GELU) return GPUSQ_ERR_UNSUPPORTED;
+  st = check_int8_extras(act_scale, w_scale, GPUSQ_F16, nullptr);
+  if (st != GPUSQ_OK) return st;
+  GemmArgs a{Xq, Wpacked, act_scale, w_scale, bias, codes_scale, Y, (int)M, (int)N, (int)K, epilogue, (int)GPUSQ_F16};
+  a.codes_out = Yq;
+  return launch_spgemm(true, a, (hipStream_t)stream);
+}
+
 gpusq_status gpusq_spgemm_int8_xf16(const void* X, const void* Wpacked, const float* act_scale, const float* w_scale,
                                     const float* bias, void* Y, gpusq_dtype out_dt, const float* out_scale, int64_t M,
                                     int64_t N, int64_t K, int epilogue, void* stream) {

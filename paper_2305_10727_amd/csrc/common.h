@@ -395,7 +395,12 @@ struct GemmArgs {
   const float* partial = nullptr;
   float* scale_out = nullptr;
   int8_t* xq_out = nullptr;
+  // INT8 path, fp16 output without GELU: the codes of that output as well, under out_scale (not NULL then)
+  int8_t* codes_out = nullptr;
 };
+// What a kernel writes where its template says so: a gpusq_dtype, or fp16 and its codes (GemmArgs::codes_out)
+constexpr int kOutF16Codes = 16;
+__host__ __device__ constexpr bool is_f16_out(int out) { return out == GPUSQ_F16 || out == kOutF16Codes; }
 enum { kRangeGiven = 0, kRangePartials = 1, kRangeHere = 2 };
 
 gpusq_status launch_spgemm(bool is_i8, const GemmArgs& a, hipStream_t s);

@@ -93,8 +93,16 @@ struct OutScale {
 template <bool IS_I8, int OUT = -1>
 __device__ __forceinline__ OutScale out_scale_of(const GemmArgs& a) {
   const int out_dt = OUT >= 0 ? OUT : a.out_dt;
-  const float s = IS_I8 && out_dt == GPUSQ_I8 ? a.out_scale[0] : 1.0f;
+  const float s = IS_I8 && (out_dt == GPUSQ_I8 || a.codes_out != nullptr) ? a.out_scale[0] : 1.0f;
   return OutScale{s, scale_reciprocal(s)};
+}
+
+// The codes of 8 fp16 values, as the quantiser of the activations gives them.
+__device__ __forceinline__ void quantize_half8(const ep_v8h& h, float s, float r, unsigned& lo, unsigned& hi) {
+  float x[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) x[j] = (float)h[j];
+  quantize_bytes8(x, s, r, lo, hi);
 }
 
 // Converts and stores 8 consecutive output channels [n, n+8) of one activation row held by one lane; `yp` points at
@@ -106,7 +114,7 @@ __device__ __forceinline__ OutScale out_scale_of(const GemmArgs& a) {
 // measured there, it cuts the HBM reads by 40% and the run time by 8%.  It is a measured choice per kernel and store
 // shape: the same hint makes the dense kernel's stores, and narrower or strided stores (int8 / int32 output), markedly
 // slower.
-// OUT: output dtype fixed at compile time (a gpusq_dtype value), or -1 to take it from the arguments at run time.
+// OUT: output fixed at compile time (a gpusq_dtype value or kOutF16Codes), or -1 to take it from the arguments at run time.
 // os: read by the caller long before (read here, a trip to memory stood between the last value and its code).
 template <bool IS_I8, int OUT = -1, bool STREAM = false>
 __device__ __forceinline__ void store_8_at(const GemmArgs& a, void* yp, int n, const float (&v)[8], const int (&raw)[8], const OutScale& os) {
@@ -137,22 +145,33 @@ __device__ __forceinline__ void store_8_at(const GemmArgs& a, void* yp, int n, c
 #pragma unroll
     for (int j = 0; j < 8; ++j) w[j] = v[j];
     pin8(w);
-    if (whole) {
-      ep_v8h h;
+    ep_v8h h;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) h[j] = (_Float16)w[j];
+    for (int j = 0; j < 8; ++j) h[j] = (_Float16)w[j];
+    if (OUT == kOutF16Codes || (OUT < 0 && IS_I8 && a.codes_out != nullptr)) {
+      unsigned lo, hi;
+      quantize_half8(h, os.s, os.r, lo, hi);
+      int8_t* q = a.codes_out + (y - (const _Float16*)a.Y);
+      if (whole) {
+        *(ep_v2u*)q = ep_v2u{lo, hi};
+      } else {
+        *(unsigned*)q = lo;
+        if (second) *(unsigned*)(q + 4) = hi;
+      }
+    }
+    if (whole) {
       if constexpr (STREAM)
         __builtin_nontemporal_store(h, (ep_v8h*)y);
       else
         *(ep_v8h*)y = h;
     } else {
-      *(ep_v4h*)y = ep_v4h{(_Float16)w[0], (_Float16)w[1], (_Float16)w[2], (_Float16)w[3]};
-      if (second) *(ep_v4h*)(y + 4) = ep_v4h{(_Float16)w[4], (_Float16)w[5], (_Float16)w[6], (_Float16)w[7]};
+      *(ep_v4h*)y = ep_v4h{h[0], h[1], h[2], h[3]};
+      if (second) *(ep_v4h*)(y + 4) = ep_v4h{h[4], h[5], h[6], h[7]};
     }
   }
 }
 
-__host__ __device__ constexpr int dtype_bytes(int dt) { return dt == GPUSQ_I8 ? 1 : (dt == GPUSQ_F16 ? 2 : 4); }
+__host__ __device__ constexpr int dtype_bytes(int dt) { return dt == GPUSQ_I8 ? 1 : (is_f16_out(dt) ? 2 : 4); }
 
 // The same with the address computed from the row m and channel n.
 template <bool IS_I8, int OUT = -1>

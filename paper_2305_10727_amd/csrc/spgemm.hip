@@ -550,7 +550,7 @@ struct Decision {
   int64_t M, N, K;
   int resident, choice;
   TilePlan plan;  // valid when choice == 3
-  EvenPlan even;  // valid when choice == 2, and when it is 1 for a ragged K within kernel 2's limits
+  EvenPlan even;  // valid when choice == 2 or 3, and when it is 1 for a ragged K within kernel 2's limits
 };
 static const Decision& decide(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu, int resident, bool patches, bool x_f16 = false) {
   constexpr int kSlots = 16;
@@ -569,7 +569,7 @@ static const Decision& decide(bool is_i8, int64_t M, int64_t N, int64_t K, bool 
   d = Decision{is_i8, gelu, patches, x_f16, forced, M, N, K, resident, kernel_choice(is_i8, M, N, K, gelu, resident, patches, x_f16), TilePlan{}, EvenPlan{}};
   const int64_t k_bytes = K * (is_i8 ? 1 : 2);
   const bool limits = k_bytes < ((int64_t)1 << 24) && N < ((int64_t)1 << 25);  // (as in kernel_choice)
-  if (d.choice == 2 || (d.choice == 1 && limits)) d.even = even_plan(M, N, resident, (int)ceil_div(k_bytes, kStepBytes), gelu);
+  if (d.choice == 2 || d.choice == 3 || (d.choice == 1 && limits)) d.even = even_plan(M, N, resident, (int)ceil_div(k_bytes, kStepBytes), gelu);
   if (d.choice == 3) d.plan = make_tile2_plan((int)M, (int)N, 2 * resident, (int)(k_bytes / kStepBytes), gelu, false);
   return d;
 }
@@ -590,6 +590,8 @@ static gpusq_status launch_typed(const GemmArgs& a, hipStream_t s) {
     else if (IS_I8 && a.out_dt == GPUSQ_I8)
       choice = a.N <= kRowBlock ? 0 : 2;
   }
+  // fp16 output and its codes: kernel 3 has no such epilogue
+  if (a.codes_out != nullptr && choice == 3) choice = 2;
   // quantising fp16 activations on the way in exists in the small kernels only, and those take every ragged K
   if (a.x_f16 && choice == 2 && k_bytes % kStepBytes != 0) choice = small_choice(a.M, a.N, resident);
   // The kernel for few rows quantises in tiles of 16 rows: beyond one round of them, and with few K steps, the 64 x 64 tiles are ahead

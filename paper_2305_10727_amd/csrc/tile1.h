@@ -273,7 +273,7 @@ __global__ void __launch_bounds__(512, 1) spgemm_tile_kernel(const GemmArgs a, c
   constexpr bool RAW = IS_I8 && OUT == GPUSQ_I32;
   // Store instructions per slab of a wavefront whose 128 channels lie inside Y, and how many of the previous tile's a wait may
   // leave in flight: the fewest a wavefront issues for a tile inside Y (a count too high would let copies go unwaited).
-  constexpr int kStoresPerSlab = OUT == GPUSQ_F16 ? 4 : (OUT == GPUSQ_I8 ? 2 : 8);
+  constexpr int kStoresPerSlab = is_f16_out(OUT) ? 4 : (OUT == GPUSQ_I8 ? 2 : 8);
   constexpr int kStores = kStoresPerSlab * (NX > 1 ? NX - 1 : 1);
   __shared__ __attribute__((aligned(1024))) uint8_t ring[R::kStages * R::kStage];
   // per tile parity and 128-channel half: 128 weight scales, 128 biases
@@ -298,7 +298,7 @@ __global__ void __launch_bounds__(512, 1) spgemm_tile_kernel(const GemmArgs a, c
   auto tile_of = [&](int i) { return even_tile(plan, i * 8 * plan.grid8 + place); };
   const bool has_bias = !RAW && (a.epilogue & GPUSQ_EPI_BIAS) != 0;
   const float s_a = (IS_I8 && !RAW) ? a.act_scale[0] : 1.0f;
-  const float s_out = OUT == GPUSQ_I8 ? a.out_scale[0] : 1.0f, r_out = scale_reciprocal(s_out);  // read once: a load in the epilogue would wait for the copies in flight
+  const float s_out = OUT == GPUSQ_I8 || OUT == kOutF16Codes ? a.out_scale[0] : 1.0f, r_out = scale_reciprocal(s_out);  // read once: a load in the epilogue would wait for the copies in flight
   if (!has_bias && wm == 0) {  // the bias halves stay zero for the whole launch (visible after the first barrier)
 #pragma unroll
     for (int par = 0; par < 2; ++par) {
@@ -489,7 +489,7 @@ __global__ void __launch_bounds__(512, 1) spgemm_tile_kernel(const GemmArgs a, c
     const int64_t m_wave = t.m0 + row0;
     const int64_t rows = (int64_t)a.M - m_wave;
     const int chans = a.N - n_wave;
-    const bool lines = OUT == GPUSQ_F16 ? (a.N & 7) == 0 : (OUT == GPUSQ_I8 ? (a.N & 15) == 0 : true);
+    const bool lines = OUT == GPUSQ_F16 ? (a.N & 7) == 0 : (OUT == GPUSQ_I8 || OUT == kOutF16Codes ? (a.N & 15) == 0 : true);
     const bool inside = lines && rows >= mine * 16 && chans >= kTileTN * 16;
     const float* p = prm[item & 1][wn];
     // int8 output: one copy of the code for both heights (it is 40 KB with its exact quotients, and the wavefronts of a CU that run
@@ -513,7 +513,9 @@ static gpusq_status launch_tile1_nx(const GemmArgs& a, const EvenPlan& plan, uns
   if (a.patch_P != 0) {  // (a row is whole steps)
     if constexpr (!RAGGED) spgemm_tile_kernel<IS_I8, 0, GPUSQ_F16, NX, true><<<grid, 512, 0, s>>>(a, plan);
   } else if constexpr (IS_I8) {
-    if (a.out_dt == GPUSQ_I32)
+    if (a.codes_out != nullptr)
+      spgemm_tile_kernel<true, 0, kOutF16Codes, NX, false, RAGGED><<<grid, 512, 0, s>>>(a, plan);
+    else if (a.out_dt == GPUSQ_I32)
       spgemm_tile_kernel<true, 0, GPUSQ_I32, NX, false, RAGGED><<<grid, 512, 0, s>>>(a, plan);
     else if (a.out_dt == GPUSQ_I8 && gelu)
       spgemm_tile_kernel<true, 1, GPUSQ_I8, NX, false, RAGGED><<<grid, 512, 0, s>>>(a, plan);

@@ -230,6 +230,8 @@ __device__ __forceinline__ void batch_epilogue(const GemmArgs& a, const typename
 // The two pieces and the line they share:
 //   fp16  (N % 8 == 0):  two batches of 32 channels are paired (64 consecutive channels = 128 bytes of a row); the
 //                        lane's 8 channels of the first batch and of the second.
+//                        With its codes beside it (kOutF16Codes, N % 16 == 0): these as for int8, 64 channels at a time, 16 rows x 64
+//                        bytes to a store.
 //   int32 (N % 4 == 0):  one batch of 32 channels is a line; the lane's two accumulator fragments (4 channels each).
 //   int8  (N % 16 == 0): the wavefront's 128 channels are a line, of which a lane holds 8 bytes in each of the 4
 //                        batches.  Lanes q = 2j and 2j+1 exchange halves with v_permlane16_swap (the odd 16-lane rows of
@@ -311,7 +313,10 @@ __device__ __forceinline__ void line_epilogue(const GemmArgs& a, const typename 
     }
     if constexpr (GELU != 0) gelu_f32_x8(v);
   };
-  if constexpr (OUT == GPUSQ_F16) {
+  if constexpr (is_f16_out(OUT)) {
+    const int cn = (q & 1) * 32 + (q >> 1) * 16;                            // codes: channel of the lane's 16 within 64, ...
+    const uint32_t c_off = (uint32_t)c * (uint32_t)a.N + (uint32_t)cn;  // ... of row c
+    global_u8* cwave = OUT == kOutF16Codes ? uniform_ptr(a.codes_out + m_wave * a.N + n_wave) : ywave;
 #pragma unroll
     for (int gp = 0; gp < kTileTN / 4; ++gp) {
       // the channels this lane stores: those of its own half of the line
@@ -323,6 +328,7 @@ __device__ __forceinline__ void line_epilogue(const GemmArgs& a, const typename 
       for (int mt = 0; mt < MT; ++mt) {
         if (!CHECKED || mt < tm_active) {
           ep_v4i H[2];
+          unsigned d[2][2];
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
             float v[8];
@@ -332,6 +338,16 @@ __device__ __forceinline__ void line_epilogue(const GemmArgs& a, const typename 
 #pragma unroll
             for (int j = 0; j < 8; ++j) hh[j] = (_Float16)v[j];
             H[h] = __builtin_bit_cast(ep_v4i, hh);
+            if constexpr (OUT == kOutF16Codes) quantize_half8(hh, so, rso, d[h][0], d[h][1]);
+          }
+          if constexpr (OUT == kOutF16Codes) {
+            // even q: their own half of the first 32 channels and that of q + 1, odd q of the second 32
+            const ep_v2u x = __builtin_amdgcn_permlane16_swap(d[0][0], d[1][0], false, false);
+            const ep_v2u y = __builtin_amdgcn_permlane16_swap(d[0][1], d[1][1], false, false);
+            uint32_t off = c_off + gp * kRowBlock;
+            asm volatile("" : "+v"(off));
+            if (!CHECKED || (n_wave + gp * kRowBlock + cn < a.N && m_wave + mt * 16 + c < a.M))
+              *(global_v4i*)(cwave + (int64_t)mt * 16 * a.N + off) = ep_v4i{(int)x[0], (int)y[0], (int)x[1], (int)y[1]};
           }
           const int64_t row = m_wave + mt * 16 + (c & 7);
           store_line_pair(H[0], H[1], ywave + mt * slab_bytes, row_off + gp * (kRowBlock * 2) + up * 64 + q * 16, half_bytes,

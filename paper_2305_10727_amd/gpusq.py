@@ -25,7 +25,7 @@ EXPORTS = [
     "gpusq_status_string", "gpusq_last_hip_error", "gpusq_version", "gpusq_prune_2to4", "gpusq_cast_f16",
     "gpusq_quantize_workspace_bytes",
     "gpusq_quantize_int8", "gpusq_compress", "gpusq_check_2to4", "gpusq_decompress", "gpusq_packed_bytes", "gpusq_pack", "gpusq_prepare_weights", "gpusq_spgemm_fp16",
-    "gpusq_spgemm_int8", "gpusq_spgemm_int8_xf16", "gpusq_spgemm_plan", "gpusq_im2col_patches", "gpusq_patch_embed16_int8", "gpusq_patch_embed16_fp16", "gpusq_gemm_fp16_dense", "gpusq_gemm_int8_dense",
+    "gpusq_spgemm_int8", "gpusq_spgemm_int8_codes", "gpusq_spgemm_int8_xf16", "gpusq_spgemm_plan", "gpusq_im2col_patches", "gpusq_patch_embed16_int8", "gpusq_patch_embed16_fp16", "gpusq_gemm_fp16_dense", "gpusq_gemm_int8_dense",
     "gpusq_prune_4to8_pairs", "gpusq_quantize_rows_int4", "gpusq_compress_int4", "gpusq_decompress_int4",
     "gpusq_int4_to_sparse_int8", "gpusq_prune_n_of_m", "gpusq_force_kernel",
     "gpusq_quantize_tensor_int8_noalloc", "gpusq_linear_int8", "gpusq_linear_int8_launches",
@@ -47,6 +47,7 @@ _SIGNATURES = {
     "gpusq_quantize_tensor_int8_noalloc": "tittiiis", "gpusq_compress": "ttttiiis", "gpusq_check_2to4": "titiis",
     "gpusq_decompress": "tttiiis", "gpusq_pack": "tttiiis", "gpusq_prepare_weights": "tittttttiis",
     "gpusq_spgemm_fp16": "ttttiiiis", "gpusq_spgemm_int8": "ttttttitiiiis", "gpusq_spgemm_int8_xf16": "ttttttitiiiis",
+    "gpusq_spgemm_int8_codes": "ttttttttiiiis",
     "gpusq_linear_int8": "tittitttitttiiiis",
     "gpusq_im2col_patches": "ttiiiiiiis", "gpusq_patch_embed16_int8": "ttttttiiiiiis", "gpusq_patch_embed16_fp16": "ttttiiiiiis",
     "gpusq_gemm_fp16_dense": "ttttiiiis", "gpusq_gemm_int8_dense": "ttttttitiiiis", "gpusq_prune_4to8_pairs": "tttiiis",
@@ -127,6 +128,8 @@ def lib():
         L.gpusq_spgemm_int8.argtypes = [vp, vp, vp, vp, vp, vp, ci, vp, i64, i64, i64, ci, vp]
         L.gpusq_spgemm_int8_xf16.argtypes = [vp, vp, vp, vp, vp, vp, ci, vp, i64, i64, i64, ci, vp]
         L.gpusq_spgemm_int8_xf16.restype = ci
+        L.gpusq_spgemm_int8_codes.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, i64, i64, i64, ci, vp]
+        L.gpusq_spgemm_int8_codes.restype = ci
         L.gpusq_linear_int8.argtypes = [vp, ci, vp, vp, ci, vp, vp, vp, ci, vp, vp, vp, i64, i64, i64, ci, vp]
         L.gpusq_linear_int8.restype = ci
         L.gpusq_linear_int8_launches.argtypes = [ci, i64, i64, i64, ci, ci, ci]

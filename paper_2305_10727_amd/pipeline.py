@@ -81,6 +81,12 @@ class SparseLinear:
             _call.gpusq_spgemm_fp16(X, self.packed, bias, self.Y, M, N, K, self.epilogue)
         return self.Y
 
+    def gemm_and_codes(self, following, bias):
+        """INT8 path, fp16 output: the product, and its codes as the input of `following` (of K = this layer's N, its act_scale given)"""
+        _call.gpusq_spgemm_int8_codes(self.Xq, self.packed, self.act_scale, self.w_scale, bias, self.Y, following.Xq, following.act_scale,
+                                      self.M, self.N, self.K, self.epilogue)
+        return self.Y
+
     def takes_fp16_input(self):
         """True when the INT8 GEMM of this layer should quantise fp16 activations itself (static scale): few rows and a K that
         is not too long, as the library's one-call layer decides it (one launch instead of two)."""
@@ -176,10 +182,11 @@ class EncoderBlockLinears:
     """The four linear layers of one encoder block (qkv, proj, fc1, fc2) on the INT8 path with static, calibrated
     activation scales, the deployment form with quantise / dequantise nodes around every linear layer: the
     re-quantisation of a layer's output with the next layer's input scale is fused into its epilogue (qkv -> int8,
-    fc1 -> GELU -> int8, which fc2 reads directly), so one block is six launches of the library:
-        quantise x, qkv, [attention], proj, [residual + norm], quantise h, fc1 (GELU), fc2;
-    with few rows (problems of the latency kernel) qkv and fc1 quantise their fp16 input on the way in, each where its sizes
-    favour it: five or four launches.
+    fc1 -> GELU -> int8, which fc2 reads directly), and without a norm in between proj writes fc1's codes beside its fp16 output, so one block is
+    five launches of the library, with a norm six:
+        quantise x, qkv, [attention], proj, [residual + norm, quantise h], fc1 (GELU), fc2;
+    with few rows (problems of the latency kernel) qkv, and fc1 behind a norm, quantise their fp16 input on the way in, each where its sizes
+    favour it: a launch less for each.
     Attention and the normalisation are not part of the library: `attention(qkv_int8 [M,3D], out_int8 [M,D])` and
     `norm(proj_fp16 [M,D]) -> fp16 [M,D]` are the caller's (stubs in the tests and the report).  capture() records the
     whole sequence into a HIP graph, which takes the host out of the loop.
@@ -215,9 +222,11 @@ class EncoderBlockLinears:
         else:
             self.qkv.forward(x, biases[0], self.scales["qkv"], static=True)
         attention(self.qkv.Y, self.proj.Xq)
-        h = self.proj.gemm(None, biases[1])
-        if norm is not None:
-            h = norm(h)
+        if norm is None:
+            self.proj.gemm_and_codes(self.fc1, biases[1])
+            self.fc1.gemm(None, biases[2], self.scales["g"])
+            return self.fc2.gemm(None, biases[3])
+        h = norm(self.proj.gemm(None, biases[1]))
         if self.fold_quantise:
             self.fc1.gemm_from_f16(h, biases[2], self.scales["g"])
         else:
