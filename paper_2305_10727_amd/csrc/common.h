@@ -283,6 +283,20 @@ struct Fp16Quantiser {
     lo = low_bytes(b[0], b[1], b[2], b[3]);
     hi = low_bytes(b[4], b[5], b[6], b[7]);
   }
+  // The codes of N vectors: one question for all of them, and what is rare stands out of line (a wavefront alone on its SIMD pays for every
+  // branch it meets).
+  template <bool CLAMP, int N>
+  __device__ __forceinline__ void codes_of(const i4 (&raw)[N], unsigned (&c)[N][2]) const {
+    const bool some_odd = odd(raw);
+    if (__builtin_expect(some_odd || refine, 0)) {
+#pragma unroll
+      for (int j = 0; j < N; ++j) codes<CLAMP>(raw[j], some_odd, c[j][0], c[j][1]);
+    } else {
+      const Fp16Quantiser plain{s, r, false};
+#pragma unroll
+      for (int j = 0; j < N; ++j) plain.codes<CLAMP>(raw[j], false, c[j][0], c[j][1]);
+    }
+  }
 };
 
 // The largest of a wavefront's values, none of them negative or NaN (their bit patterns then compare as they do): data-parallel

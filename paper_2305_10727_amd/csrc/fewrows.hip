@@ -203,15 +203,17 @@ __global__ void __launch_bounds__(64 * NW, 2) spgemm_fewrows_kernel(const GemmAr
         }
       }
     } else if constexpr (QUANT) {
-      const bool odd = qz.odd(xr[slot]);
+      unsigned c[XL][2];
+      qz.codes_of<XQ == 1>(xr[slot], c);
+      const int col = (lane & 15) * 8;
 #pragma unroll
-      for (int j = 0; j < XL; ++j) {  // 8 fp16 values -> 8 codes
-        unsigned lo, hi;
-        qz.codes<XQ == 1>(xr[slot][j], odd, lo, hi);
-        const int r = 4 * j + (lane >> 4), col = (lane & 15) * 8;
-        *(ep_v2u*)(xs + r * kFrRow + col) = ep_v2u{lo, hi};
-        if (write_codes && r <= last_row && ks * kStepBytes + col < a.K)
-          *(ep_v2u*)(a.xq_out + (m0 + r) * a.K + ks * kStepBytes + col) = ep_v2u{lo, hi};
+      for (int j = 0; j < XL; ++j) *(ep_v2u*)(xs + (4 * j + (lane >> 4)) * kFrRow + col) = ep_v2u{c[j][0], c[j][1]};  // 8 fp16 values -> 8 codes
+      if (write_codes) {
+#pragma unroll
+        for (int j = 0; j < XL; ++j) {
+          const int r = 4 * j + (lane >> 4);
+          if (r <= last_row && ks * kStepBytes + col < a.K) *(ep_v2u*)(a.xq_out + (m0 + r) * a.K + ks * kStepBytes + col) = ep_v2u{c[j][0], c[j][1]};
+        }
       }
     } else {
 #pragma unroll
