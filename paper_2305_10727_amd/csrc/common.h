@@ -224,6 +224,7 @@ struct Fp16Quantiser {
       const unsigned short bits = (unsigned short)(__builtin_bit_cast(unsigned short, down[0]) + (tid & 1));
       if (bits < 0x7C00) {  // else no finite fp16 number there
         const float x = (float)__builtin_bit_cast(_Float16, bits);
+        // (Markstein's quotient is not the rounded one under a scale one unit below a power of two, x = s / 2: a division)
         const float exact = fminf(rintf(__fdiv_rn(x, mag)), 127.0f);
 #pragma unroll
         for (int c = 0; c < 3; ++c)
@@ -290,7 +291,11 @@ struct Fp16Quantiser {
     const bool some_odd = odd(raw);
     if (__builtin_expect(some_odd || refine, 0)) {
 #pragma unroll
-      for (int j = 0; j < N; ++j) codes<CLAMP>(raw[j], some_odd, c[j][0], c[j][1]);
+      for (int j = 0; j < N; ++j) {
+        i4 x = raw[j];
+        asm volatile("" : "+v"(x));  // (nothing of it is shared with the other branch, and computed in front of both)
+        codes<CLAMP>(x, some_odd, c[j][0], c[j][1]);
+      }
     } else {
       const Fp16Quantiser plain{s, r, false};
 #pragma unroll

@@ -31,6 +31,7 @@ __device__ __forceinline__ float scale_of_range(float amax) { return amax == 0.0
 
 typedef __attribute__((address_space(1))) v4i global_v4;
 typedef __attribute__((address_space(1))) ep_v2u global_v2u;
+typedef __attribute__((address_space(1))) unsigned global_u32;
 
 // XQ: 0 = X is the operand; 1 = fp16 or fp32 to be quantised with a given scale; 2 = with the scale of X's range (see GemmArgs)
 // PATCH: the rows of X are 16 x 16 patches gathered from an image batch (see patch_chunk_offset).
@@ -172,6 +173,7 @@ __global__ void __launch_bounds__(64 * NW, 2) spgemm_fewrows_kernel(const GemmAr
   }
   const float r_a = FP32 ? scale_reciprocal(s_a) : 1.0f;
   const bool write_codes = QUANT && a.xq_out != nullptr && n_blk == 0;
+  global_u8* xq_tile = uniform_ptr(a.xq_out + m0 * a.K);  // (rows past the end are the last one again, and so are their codes)
 
   acc_t acc[4][TM];
 #pragma unroll
@@ -199,7 +201,7 @@ __global__ void __launch_bounds__(64 * NW, 2) spgemm_fewrows_kernel(const GemmAr
         for (int h = 0; h < 2; ++h) {
           const int r = 2 * (j + h) + (lane >> 5);
           *(unsigned*)(xs + r * kFrRow + col) = q[h];
-          if (write_codes && r <= last_row && ks * kStepBytes + col < a.K) *(unsigned*)(a.xq_out + (m0 + r) * a.K + ks * kStepBytes + col) = q[h];
+          if (write_codes && ks * kStepBytes + col < a.K) *(global_u32*)(xq_tile + ks * kStepBytes + xoff[j + h] / XW) = q[h];
         }
       }
     } else if constexpr (QUANT) {
@@ -208,12 +210,9 @@ __global__ void __launch_bounds__(64 * NW, 2) spgemm_fewrows_kernel(const GemmAr
       const int col = (lane & 15) * 8;
 #pragma unroll
       for (int j = 0; j < XL; ++j) *(ep_v2u*)(xs + (4 * j + (lane >> 4)) * kFrRow + col) = ep_v2u{c[j][0], c[j][1]};  // 8 fp16 values -> 8 codes
-      if (write_codes) {
+      if (write_codes && ks * kStepBytes + col < a.K) {
 #pragma unroll
-        for (int j = 0; j < XL; ++j) {
-          const int r = 4 * j + (lane >> 4);
-          if (r <= last_row && ks * kStepBytes + col < a.K) *(ep_v2u*)(a.xq_out + (m0 + r) * a.K + ks * kStepBytes + col) = ep_v2u{c[j][0], c[j][1]};
-        }
+        for (int j = 0; j < XL; ++j) *(global_v2u*)(xq_tile + ks * kStepBytes + xoff[j] / XW) = ep_v2u{c[j][0], c[j][1]};
       }
     } else {
 #pragma unroll

@@ -105,6 +105,22 @@ def test_fp16_codes_decide_as_the_division_does(g):
         assert np.array_equal(q, exp), s
 
 
+def test_codes_under_scales_one_unit_off_a_power_of_two(g):
+    """One unit below a power of two a rounded reciprocal and one correction do not give the rounded quotient of half the scale, which
+    lies on the boundary between codes 0 and 1: the codes are those of the division there, given and found."""
+    X = np.arange(0, 0x7C00, 7, dtype=np.uint16)[:2048].view(np.float16).reshape(2, 1024)
+    N, K = 4, 1024
+    _, s_w, vals, meta = _oracle_weights(synth.weights(N, K, seed=1))
+    packed, sw, b = g.pack(dev(vals), dev(meta), K), dev(s_w), dev(synth.bias(N))
+    for e in range(-8, 9):
+        p = np.float32(2.0 ** e)
+        for s in (np.nextafter(p, np.float32(0)), p, np.nextafter(p, np.float32(1e9))):
+            x = X.copy()
+            x[0, :4] = np.array([p / 2, -p / 2, 1.5 * p, -2.5 * p], np.float16)
+            exp, _ = oracle.quantize_tensor_int8(x.astype(np.float32), scale=float(s))
+            assert np.array_equal(_layer(g, dev(x), packed, sw, b, 2, N, K, dev(np.array([s])))[1], exp), s
+
+
 # fp32 activations quantised by the kernel for few rows: 4 and 8 wavefronts, one and two workgroups per CU, the range found by every
 # workgroup and by a pass, rows that end inside a K step; NaN and infinities beside a given scale; int8 output
 @pytest.mark.parametrize("M,K,N", [(1, 16, 4), (50, 192, 260), (331, 192, 384), (700, 384, 512), (33, 656, 132), (197, 1536, 64), (17, 1040, 68)])
