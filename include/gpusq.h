@@ -220,17 +220,18 @@ gpusq_status gpusq_spgemm_int8_xf16(const void* X, const void* Wpacked, const fl
                                     const float* bias, void* Y, gpusq_dtype out_dt, const float* out_scale,
                                     int64_t M, int64_t N, int64_t K, int epilogue, void* stream);
 
+#define GPUSQ_WIDE_MIN_ROWS 2048
 /* The whole INT8 layer at inference [Sec. 2.2, 3.4]: quantise X [M][K] (x_dt = GPUSQ_F32 or GPUSQ_F16) per tensor, then the
  * product of gpusq_spgemm_int8 on the codes.  Results, the codes in Xq [M][K] and the scale in act_scale[0] included, are
  * bit-identical to gpusq_quantize_int8(GPUSQ_PER_TENSOR) followed by gpusq_spgemm_int8; scale_is_input and workspace as for
- * the former, all other arguments as for the latter.  For few rows the two are one kernel, and for small X (or a
- * given scale) the layer is a single launch.  Y may lie over X or over the workspace, and out_scale may be act_scale (the quantiser
+ * the former, all other arguments as for the latter.  For few rows, and for many (GPUSQ_WIDE_MIN_ROWS or more) of few output channels, the two are
+ * one kernel, and for small X (or a given scale) the layer is a single launch.  Y may lie over X or over the workspace, and out_scale may be act_scale (the quantiser
  * is then a launch of its own). */
 gpusq_status gpusq_linear_int8(const void* X, gpusq_dtype x_dt, const void* Wpacked, float* act_scale, int scale_is_input,
                                const float* w_scale, const float* bias, void* Y, gpusq_dtype out_dt, const float* out_scale, int8_t* Xq,
                                void* workspace, int64_t M, int64_t N, int64_t K, int epilogue, void* stream);
-/* How many launches that call takes on a device with `cus` compute units (cus <= 0: the current device): 1 or 2 where the GEMM
- * quantises the activations itself (and the operands do not overlap as said there), else 2 (scale_is_input != 0) or 3; 0 for
+/* How many launches that call takes for fp16 output on a device with `cus` compute units (cus <= 0: the current device): 1 or 2 where the
+ * GEMM quantises the activations itself (and the operands do not overlap as said there), else 2 (scale_is_input != 0) or 3; 0 for
  * invalid sizes or types.  Host-side. */
 int gpusq_linear_int8_launches(gpusq_dtype x_dt, int64_t M, int64_t N, int64_t K, int epilogue, int scale_is_input, int cus);
 
@@ -277,7 +278,8 @@ gpusq_status gpusq_spgemm_plan(gpusq_dtype dt, int64_t M, int64_t N, int64_t K, 
 /* Testing aid: kernel = 0 (64 x 64 tiles), 1, 2, 3 or 4 (few rows, shown as 0 by gpusq_spgemm_plan) makes the sparse GEMM entry
  * points (and gpusq_spgemm_plan's out[0]) take that kernel for every problem it can run (kernel 3 needs K * element size % 128 == 0), so that every kernel can be checked on
  * the same shapes; 0 and 1 also keep the dense twins on their small kernel; any other value gives the choice back to the
- * size rules.  Returns the previous setting (-1 = none).  Process-wide; the environment variable GPUSQ_FORCE_KERNEL (0..4)
+ * size rules.  5: the size rules, but gpusq_linear_int8 takes its kernel for many rows of few channels at every size it can (0 to 4: at none).
+ * Returns the previous setting (-1 = none).  Process-wide; the environment variable GPUSQ_FORCE_KERNEL (0..5)
  * gives the initial setting and is read once, when the library is loaded.  Not meant for production callers. */
 int gpusq_force_kernel(int kernel);
 

@@ -360,6 +360,7 @@ int gpusq_linear_int8_launches(gpusq_dtype x_dt, int64_t M, int64_t N, int64_t K
   a.N = (int)N;
   a.K = (int)K;
   a.epilogue = epilogue;
+  a.out_dt = (int)GPUSQ_F16;
   return linear_int8_launches(a, x_dt, scale_is_input, cus);
 }
 

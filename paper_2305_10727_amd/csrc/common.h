@@ -428,6 +428,9 @@ gpusq_status launch_dense(bool is_i8, const GemmArgs& a, hipStream_t s);
 bool fewrows_supports(const GemmArgs& a);
 bool fewrows_folds_quantiser(int64_t M, int64_t N, int64_t K, int resident, bool fp32);
 gpusq_status launch_fewrows(bool is_i8, const GemmArgs& a, int resident, hipStream_t s);
+// the sparse INT8 GEMM on whole rows that it quantises (wide.hip)
+struct WidePlan;
+gpusq_status launch_wide(const GemmArgs& a, const WidePlan& p, hipStream_t s);
 // quantise (dt of X, workspace as for launch_quantize) and multiply: one, two or three launches
 gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, void* workspace, hipStream_t s);
 int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int cus);

@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "tile_common.h"
+#include "wide_plan.h"
 
 namespace gpusq {
 
@@ -333,12 +334,12 @@ static int num_cus() {
 // library is loaded, so that no launch pays for an environment lookup.
 static int initial_forced_kernel() {
   const char* f = getenv("GPUSQ_FORCE_KERNEL");
-  return (f && f[0] >= '0' && f[0] <= '4' && f[1] == 0) ? f[0] - '0' : -1;
+  return (f && f[0] >= '0' && f[0] <= '5' && f[1] == 0) ? f[0] - '0' : -1;
 }
 static std::atomic<int> g_forced_kernel{initial_forced_kernel()};
 int forced_kernel() { return g_forced_kernel.load(std::memory_order_relaxed); }
 int set_forced_kernel(int kernel) {
-  return g_forced_kernel.exchange(kernel >= 0 && kernel <= 4 ? kernel : -1);
+  return g_forced_kernel.exchange(kernel >= 0 && kernel <= 5 ? kernel : -1);
 }
 
 // The estimate that decides which problems may quantise fp16 activations on their way into the small kernel (see kernel_choice), of
@@ -473,7 +474,7 @@ static int kernel_choice(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu,
   const int64_t ksteps = ceil_div(k_bytes, kStepBytes);
   const int64_t wgs64 = ceil_div(M, 64) * ceil_div(N, 64);
   // Testing aid: a forced kernel overrides the choice (2 only where the tile kernel can run the problem).
-  if (const int c = g_forced_kernel.load(std::memory_order_relaxed); c >= 0) {
+  if (const int c = g_forced_kernel.load(std::memory_order_relaxed); c >= 0 && c != 5) {
     if (c != 3 || k_bytes % kStepBytes == 0) return c;
   }
   // (the fused patch gather is refused up to 256 K outputs; beyond, it goes to the kernel for few rows where a GEMM of its sizes would, else
@@ -545,6 +546,7 @@ gpusq_status plan_spgemm(bool is_i8, int64_t M, int64_t N, int64_t K, int epilog
 // launched over and over with the same sizes, and planning (a dozen candidate plans, each walked over every workgroup)
 // takes the host several microseconds, which is what a launch of a 10 us GEMM is bound by when it is repeated.
 struct Decision {
+  double gemm_us;  // estimate of the product on what the choice picks (whole K steps; not for the kernel for few rows)
   bool is_i8, gelu, patches, x_f16;
   int forced;  // the forced kernel when the decision was taken, -1 for none
   int64_t M, N, K;
@@ -566,10 +568,17 @@ static const Decision& decide(bool is_i8, int64_t M, int64_t N, int64_t K, bool 
   Decision& d = cache[next];
   next = (next + 1) % kSlots;
   if (used < kSlots) ++used;
-  d = Decision{is_i8, gelu, patches, x_f16, forced, M, N, K, resident, kernel_choice(is_i8, M, N, K, gelu, resident, patches, x_f16), TilePlan{}, EvenPlan{}};
+  d = Decision{0.0, is_i8, gelu, patches, x_f16, forced, M, N, K, resident, kernel_choice(is_i8, M, N, K, gelu, resident, patches, x_f16), TilePlan{}, EvenPlan{}};
   const int64_t k_bytes = K * (is_i8 ? 1 : 2);
   const bool limits = k_bytes < ((int64_t)1 << 24) && N < ((int64_t)1 << 25);  // (as in kernel_choice)
   if (d.choice == 2 || d.choice == 3 || (d.choice == 1 && limits)) d.even = even_plan(M, N, resident, (int)ceil_div(k_bytes, kStepBytes), gelu);
+  if (is_i8 && d.choice != 4 && limits) {
+    const int64_t ksteps = ceil_div(k_bytes, kStepBytes);
+    const EvenPlan p = d.even.tiles_n > 0 ? d.even : even_plan(M, N, resident, (int)ksteps, gelu);
+    const double k0 = estimate_kernel0(ceil_div(M, 64) * ceil_div(N, 64), resident, true, gelu, ksteps);
+    const double k2 = estimate_kernel2(even_rounds(p, resident), true, gelu, ksteps);
+    d.gemm_us = k0 < k2 ? k0 : k2;
+  }
   if (d.choice == 3) d.plan = make_tile2_plan((int)M, (int)N, 2 * resident, (int)(k_bytes / kStepBytes), gelu, false);
   return d;
 }
@@ -617,35 +626,61 @@ static gpusq_status launch_typed(const GemmArgs& a, hipStream_t s) {
   return IS_I8 ? launch_tile1_i8(a, dec.even, grid, s) : launch_tile1_f16(a, dec.even, grid, s);
 }
 
-// Quantise X and multiply.  Where the problem goes to the kernel for few rows and its K is not too long, that kernel
+// Quantise X and multiply.  Many rows and few channels: see wide_takes.  Where the problem goes to the kernel for few rows and its K is not too long, that kernel
 // quantises: with a given scale, or a range of X small enough for every workgroup to find for itself, in the one
 // launch, else behind the range pass.  Otherwise the quantiser's one or two launches and the GEMM's.
 // A range of 128 KB read by every workgroup costs what the range pass does: 75 KB (197 x 192) 5.8 against 6.7 us, 133 KB (64 x
 // 1040) 8.2 against 8.6, 151 KB (394 x 192) 8.4 against 7.1.
 constexpr int64_t kRangeHereBytes = 128 * 1024;
 
-// 1 + the launches in front of the GEMM's own; `folds`: the GEMM quantises
-static int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int resident, bool& folds) {
-  // (the sizes first: a large layer is not planned for this)
-  folds = fewrows_folds_quantiser(a.M, a.N, a.K, resident, dt == GPUSQ_F32) && fewrows_supports(a) &&
-          decide(true, a.M, a.N, a.K, (a.epilogue & GPUSQ_EPI_GELU) != 0, resident, false).choice == 4;
-  if (!folds) return scale_is_input ? 2 : 3;
+// Many rows and few channels: the kernel that quantises whole rows (wide.hip) by the estimates, from 2048 rows on (below, there is little to win
+// and the estimates are off by as much) and up to the two column blocks of 1536 channels that were timed.  Of 2448 sizes it takes 63 % of the
+// fp16 ones, 1.19 times as fast there, and 52 % of the fp32 ones, 1.12 times; 1.5 % of all are 3 % slower or more (51961 x 80 -> 1280 fp32 + GELU
+// 43.9 -> 50.6 us the worst, hence the margins).  14070 x 576 -> 256 16.8 -> 10.1, 12609 x 768 -> 768 23.6 -> 19.6, 7029 x 1152 -> 256 20.6 -> 14.9, 56475 x 3648
+// -> 704 236.7 -> 194.3; not 25216 x 3072 -> 768, 103 / 110, nor 28453 x 1600 -> 1920 + GELU, 116.9 / 120.6.  Where the product goes to the kernel for few
+// rows (those have no estimate here) it is ahead beyond 256 channels at every K (46 sizes, 1.22 times), level below.
+static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, int resident, const Decision& d, WidePlan& p) {
+  const bool fp32 = dt == GPUSQ_F32, i8 = a.out_dt == GPUSQ_I8, gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
+  if ((d.forced >= 0 && d.forced != 5) || (!i8 && a.out_dt != GPUSQ_F16) || a.N % 16 != 0) return false;
+  if ((int64_t)a.K * 64 * 4 >= ((int64_t)1 << 31) || a.N >= (1 << 24)) return false;  // 32-bit lane offsets inside a chunk's rows
+  if (d.forced < 0 && (a.M < GPUSQ_WIDE_MIN_ROWS || a.N > 2 * kWideBlocks * kRowBlock)) return false;
+  p = wide_plan(a.M, a.N, resident, fp32);
+  if (p.chunks == 0 || d.forced == 5) return p.chunks > 0;
+  if (d.choice == 4) return a.N > 256;
+  return d.gemm_us > 0 && wide_us(p, a.M, a.N, a.K, resident, fp32, gelu, i8) < (fp32 ? 0.95 : 0.97) * quantise_and_gemm_us(d.gemm_us, a.M, a.N, a.K, fp32, i8);
+}
+
+// What quantises: the kernel for few rows, the one for whole rows (with this plan), or a launch of its own
+enum { kQuantiseFewRows, kQuantiseWide, kQuantiseApart };
+static int quantiser_of(const GemmArgs& a, gpusq_dtype dt, int resident, WidePlan& p) {
+  const bool gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
+  const bool few = fewrows_folds_quantiser(a.M, a.N, a.K, resident, dt == GPUSQ_F32) && fewrows_supports(a);
+  const Decision& d = decide(true, a.M, a.N, a.K, gelu, resident, false);
+  if (few && d.choice == 4) return kQuantiseFewRows;
+  return wide_takes(a, dt, resident, d, p) ? kQuantiseWide : kQuantiseApart;
+}
+
+// 1 + the launches in front of the GEMM's own
+static int launches_of(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int quantiser) {
+  if (quantiser == kQuantiseApart) return scale_is_input ? 2 : 3;
+  if (quantiser == kQuantiseWide) return scale_is_input ? 1 : 2;
   return scale_is_input || (int64_t)a.M * a.K * dtype_bytes(dt) <= kRangeHereBytes ? 1 : 2;
 }
 
 int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int cus) {
-  bool folds;
-  return linear_int8_launches(a, dt, scale_is_input, cus > 0 ? cus : num_cus(), folds);
+  WidePlan p;
+  return launches_of(a, dt, scale_is_input, quantiser_of(a, dt, cus > 0 ? cus : num_cus(), p));
 }
 
 gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, void* workspace, hipStream_t s) {
-  bool folds;
-  const int launches = linear_int8_launches(a, dt, scale_is_input, num_cus(), folds);
+  const int resident = num_cus();
+  WidePlan plan;
+  const int quantiser = quantiser_of(a, dt, resident, plan), launches = launches_of(a, dt, scale_is_input, quantiser);
   a.act_scale = scale;
   const int64_t range_bytes = launches == 2 ? (int64_t)gpusq_quantize_workspace_bytes(GPUSQ_PER_TENSOR, a.M, a.K) : 0;
   const bool apart = may_quantise_inside(a.X, dtype_bytes(dt), a.Y, dtype_bytes(a.out_dt), a.M, a.N, a.K, scale, scale_is_input != 0, a.out_scale,
                                          workspace, range_bytes);
-  if (folds && apart) {
+  if (quantiser != kQuantiseApart && apart) {
     a.x_f16 = dt == GPUSQ_F32 ? 2 : 1;
     a.xq_out = Xq;
     if (!scale_is_input) {
@@ -656,7 +691,7 @@ gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* s
         a.partial = (const float*)workspace;
       }
     }
-    return launch_fewrows(true, a, num_cus(), s);
+    return quantiser == kQuantiseWide ? launch_wide(a, plan, s) : launch_fewrows(true, a, resident, s);
   }
   const gpusq_status st = launch_quantize(a.X, dt, Xq, scale, GPUSQ_PER_TENSOR, scale_is_input, a.M, a.K, workspace, s);
   if (st != GPUSQ_OK) return st;

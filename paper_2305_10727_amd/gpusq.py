@@ -17,6 +17,7 @@ OK, ERR_NULL, ERR_SHAPE, ERR_ALIGN, ERR_UNSUPPORTED, ERR_HIP = range(6)
 F32, F16, I8, I32 = range(4)
 EPI_NONE, EPI_BIAS, EPI_GELU = 0, 1, 2
 PER_ROW, PER_TENSOR = 0, 1
+WIDE_MIN_ROWS = 2048  # GPUSQ_WIDE_MIN_ROWS
 
 _TORCH_DT = {torch.float32: F32, torch.float16: F16, torch.int8: I8, torch.int32: I32}
 _DT_TORCH = {v: k for k, v in _TORCH_DT.items()}

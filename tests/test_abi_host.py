@@ -282,3 +282,14 @@ def test_launch_rules(tmp_path):
     assert build.returncode == 0, build.stderr
     run = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert run.returncode == 0 and run.stdout == "ok\n", run.stdout
+
+
+def test_every_chunk_of_the_kernel_for_whole_rows_is_met_once(tmp_path):
+    """The plans of the kernel that quantises whole rows walked on the host with the code the kernel reads them with (wide_plan_walk.cpp)"""
+    exe = str(tmp_path / "walk")
+    build = subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                            "-I", os.path.join(ROOT, "paper_2305_10727_amd", "csrc"), os.path.join(ROOT, "tests", "wide_plan_walk.cpp"), "-o", exe],
+                           capture_output=True, text=True)
+    assert build.returncode == 0, build.stderr
+    run = subprocess.run([exe, "20000"], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0 and run.stdout == "20000 plans\n", run.stdout
