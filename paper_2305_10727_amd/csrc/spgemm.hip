@@ -634,9 +634,9 @@ static gpusq_status launch_typed(const GemmArgs& a, hipStream_t s) {
 constexpr int64_t kRangeHereBytes = 128 * 1024;
 
 // Many rows and few channels: the kernel that quantises whole rows (wide.hip) by the estimates, from 2048 rows on (below, there is little to win
-// and the estimates are off by as much) and up to the two column blocks of 1536 channels that were timed.  Of 2448 sizes it takes 63 % of the
-// fp16 ones, 1.19 times as fast there, and 52 % of the fp32 ones, 1.12 times; 1.5 % of all are 3 % slower or more (51961 x 80 -> 1280 fp32 + GELU
-// 43.9 -> 50.6 us the worst, hence the margins).  14070 x 576 -> 256 16.8 -> 10.1, 12609 x 768 -> 768 23.6 -> 19.6, 7029 x 1152 -> 256 20.6 -> 14.9, 56475 x 3648
+// and the estimates are off by as much) and up to the two column blocks of 1536 channels that were timed.  Of 2448 sizes it takes some 60 % of the
+// fp16 ones, 1.19 times as fast there, and half of the fp32 ones, 1.12 times; 2 % of all are 3 % slower or more (30706 x 2256 -> 256
+// 73.6 -> 81.6 us, 19429 x 3312 -> 192 71.5 -> 77.0).  14070 x 576 -> 256 16.8 -> 10.1, 12609 x 768 -> 768 23.6 -> 19.6, 7029 x 1152 -> 256 20.6 -> 14.9, 56475 x 3648
 // -> 704 236.7 -> 194.3; not 25216 x 3072 -> 768, 103 / 110, nor 28453 x 1600 -> 1920 + GELU, 116.9 / 120.6.  Where the product goes to the kernel for few
 // rows (those have no estimate here) it is ahead beyond 256 channels at every K (46 sizes, 1.22 times), level below.
 static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, int resident, const Decision& d, WidePlan& p) {
@@ -647,7 +647,9 @@ static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, int resident, const De
   p = wide_plan(a.M, a.N, resident, fp32);
   if (p.chunks == 0 || d.forced == 5) return p.chunks > 0;
   if (d.choice == 4) return a.N > 256;
-  return d.gemm_us > 0 && wide_us(p, a.M, a.N, a.K, resident, fp32, gelu, i8) < (fp32 ? 0.95 : 0.97) * quantise_and_gemm_us(d.gemm_us, a.M, a.N, a.K, fp32, i8);
+  // (a long K is estimated 8 % short)
+  const double margin = a.K > 24 * kStepBytes ? 0.9 : (fp32 ? 0.92 : 0.97);
+  return d.gemm_us > 0 && wide_us(p, a.M, a.N, a.K, resident, fp32, gelu, i8) < margin * quantise_and_gemm_us(d.gemm_us, a.M, a.N, a.K, fp32, i8);
 }
 
 // What quantises: the kernel for few rows, the one for whole rows (with this plan), or a launch of its own

@@ -65,8 +65,11 @@ inline WidePlan wide_plan_of(int64_t M, int64_t N, int resident, int slabs, bool
   p.over = (int)(M % chunks);
   return p;
 }
-// Chunks as high as they go: 64 rows are 2 % behind the best of 16, 32, 48 and 64 (495 sizes).
-inline WidePlan wide_plan(int64_t M, int64_t N, int resident, bool fp32) { return wide_plan_of(M, N, resident, kWideSlabs, fp32); }
+// Chunks as high as they go (64 rows are 2 % behind the best of 16, 32, 48 and 64 of each of 1381 sizes), but for many fp32 rows of up to 256
+// channels, of which LDS then holds one workgroup to a CU: 32 rows are 2 to 7 % ahead there.
+inline WidePlan wide_plan(int64_t M, int64_t N, int resident, bool fp32) {
+  return wide_plan_of(M, N, resident, fp32 && N <= 256 && M >= 8192 ? 2 : kWideSlabs, fp32);
+}
 
 // Run time in microseconds of that kernel, without the range pass, and of the quantiser and a GEMM of `gemm_us` behind it: fitted to 2448 sizes
 // timed on MI355X (M 2048 ... 65792, K 64 ... 5120, N 64 ... 1536, fp16 and fp32, both outputs, with and without GELU, three buffers in turn; 9 % and
