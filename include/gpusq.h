@@ -257,6 +257,13 @@ gpusq_status gpusq_im2col_patches(const void* img, void* X, gpusq_dtype dt, int6
 gpusq_status gpusq_patch_embed16_int8(const int8_t* img, const void* Wpacked, const float* act_scale, const float* w_scale,
                                       const float* bias, void* Y, int64_t B, int64_t C, int64_t H, int64_t W, int64_t D,
                                       int epilogue, void* stream);
+/* The INT8 layer with the quantiser of the images in front of it, in one call: bit-identical, the codes in img_q [B][C][H][W] and the scale in
+ * act_scale[0] included, to gpusq_quantize_int8(GPUSQ_PER_TENSOR) on the images (dt = GPUSQ_F16 or GPUSQ_F32; workspace as there) followed by
+ * gpusq_patch_embed16_int8 on the codes, with the limits of both.  Where gpusq_linear_int8 takes a layer of these sizes to its kernel for many rows the
+ * second pass over the images and the product are one launch. */
+gpusq_status gpusq_patch_embed16_images(const void* img, gpusq_dtype dt, const void* Wpacked, float* act_scale, const float* w_scale,
+                                        const float* bias, void* Y, int8_t* img_q, void* workspace, int64_t B, int64_t C, int64_t H,
+                                        int64_t W, int64_t D, int epilogue, void* stream);
 gpusq_status gpusq_patch_embed16_fp16(const void* img, const void* Wpacked, const float* bias, void* Y, int64_t B, int64_t C,
                                       int64_t H, int64_t W, int64_t D, int epilogue, void* stream);
 

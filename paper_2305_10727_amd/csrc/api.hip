@@ -247,23 +247,44 @@ gpusq_status gpusq_im2col_patches(const void* img, void* X, gpusq_dtype dt, int6
   return launch_im2col_patches(img, X, dt, B, C, H, W, P, K_pad, (hipStream_t)stream);
 }
 
-static gpusq_status patch_embed16(bool is_i8, const void* img, const void* Wpacked, const float* act_scale, const float* w_scale,
-                                  const float* bias, void* Y, int64_t B, int64_t C, int64_t H, int64_t W, int64_t D, int epilogue,
-                                  void* stream) {
-  if (is_i8 && (!act_scale || !w_scale)) return GPUSQ_ERR_NULL;
+// Checks and arguments of the patch embeddings (img: of elements of `size` bytes)
+static gpusq_status patch_args(GemmArgs& a, const void* img, int size, const void* Wpacked, const float* act_scale, const float* w_scale, const float* bias,
+                               void* Y, int64_t B, int64_t C, int64_t H, int64_t W, int64_t D, int epilogue) {
   if (B <= 0 || C <= 0 || H <= 0 || W <= 0 || H % 16 != 0 || W % 16 != 0) return GPUSQ_ERR_SHAPE;
   if (C > 65536 || H > (1 << 20) || W > (1 << 20)) return GPUSQ_ERR_SHAPE;
   const int64_t M = B * (H / 16) * (W / 16), K = C * 256;
   gpusq_status st = check_gemm(img, Wpacked, bias, Y, M, D, K, epilogue);
   if (st != GPUSQ_OK) return st;
-  if (B * C * H * W * (is_i8 ? 1 : 2) >= ((int64_t)1 << 32)) return GPUSQ_ERR_SHAPE;  // 32-bit per-lane byte offsets
+  if (B * C * H * W * size >= ((int64_t)1 << 32)) return GPUSQ_ERR_SHAPE;  // 32-bit per-lane byte offsets
   if (epilogue & GPUSQ_EPI_GELU) return GPUSQ_ERR_UNSUPPORTED;
-  GemmArgs a{img, Wpacked, act_scale, w_scale, bias, nullptr, Y, (int)M, (int)D, (int)K, epilogue, (int)GPUSQ_F16};
+  a = GemmArgs{img, Wpacked, act_scale, w_scale, bias, nullptr, Y, (int)M, (int)D, (int)K, epilogue, (int)GPUSQ_F16};
   a.patch_P = 16;
   a.patch_C = (int)C;
   a.patch_H = (int)H;
   a.patch_W = (int)W;
-  return launch_spgemm(is_i8, a, (hipStream_t)stream);
+  return GPUSQ_OK;
+}
+
+static gpusq_status patch_embed16(bool is_i8, const void* img, const void* Wpacked, const float* act_scale, const float* w_scale,
+                                  const float* bias, void* Y, int64_t B, int64_t C, int64_t H, int64_t W, int64_t D, int epilogue,
+                                  void* stream) {
+  if (is_i8 && (!act_scale || !w_scale)) return GPUSQ_ERR_NULL;
+  GemmArgs a{};
+  const gpusq_status st = patch_args(a, img, is_i8 ? 1 : 2, Wpacked, act_scale, w_scale, bias, Y, B, C, H, W, D, epilogue);
+  return st != GPUSQ_OK ? st : launch_spgemm(is_i8, a, (hipStream_t)stream);
+}
+
+gpusq_status gpusq_patch_embed16_images(const void* img, gpusq_dtype dt, const void* Wpacked, float* act_scale, const float* w_scale, const float* bias,
+                                        void* Y, int8_t* img_q, void* workspace, int64_t B, int64_t C, int64_t H, int64_t W, int64_t D, int epilogue,
+                                        void* stream) {
+  if (!act_scale || !w_scale || !img_q || !workspace) return GPUSQ_ERR_NULL;
+  if (dt != GPUSQ_F32 && dt != GPUSQ_F16) return GPUSQ_ERR_UNSUPPORTED;
+  GemmArgs a{};
+  const gpusq_status st = patch_args(a, img, 1, Wpacked, act_scale, w_scale, bias, Y, B, C, H, W, D, epilogue);
+  if (st != GPUSQ_OK) return st;
+  if (B * C * H * W > INT32_MAX) return GPUSQ_ERR_SHAPE;  // (the quantiser's columns)
+  if (!aligned16(img_q) || !aligned16(workspace)) return GPUSQ_ERR_ALIGN;
+  return launch_patch_embed_int8(a, dt, img_q, act_scale, workspace, (hipStream_t)stream);
 }
 
 gpusq_status gpusq_patch_embed16_int8(const int8_t* img, const void* Wpacked, const float* act_scale, const float* w_scale,

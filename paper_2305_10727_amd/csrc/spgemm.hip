@@ -701,6 +701,32 @@ gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* s
   return launch_typed<true>(a, s);
 }
 
+// The images in front of a patch embedding: the kernel for whole rows takes a product of its sizes as it takes a layer's.
+gpusq_status launch_patch_embed_int8(GemmArgs a, gpusq_dtype dt, int8_t* img_q, float* scale, void* workspace, hipStream_t s) {
+  const int resident = num_cus();
+  const int choice = decide(true, a.M, a.N, a.K, false, resident, true).choice;
+  if (choice != 2 && choice != 4) return GPUSQ_ERR_UNSUPPORTED;  // (before anything is launched)
+  const int64_t pixels = (int64_t)a.M * a.K;
+  a.act_scale = scale;
+  WidePlan plan;
+  const bool wide = pixels * dtype_bytes(dt) < ((int64_t)1 << 32) && wide_takes(a, dt, resident, decide(true, a.M, a.N, a.K, false, resident, false), plan) &&
+                    may_quantise_inside(a.X, dtype_bytes(dt), a.Y, 2, a.M, a.N, a.K, scale, false, nullptr, workspace,
+                                        (int64_t)gpusq_quantize_workspace_bytes(GPUSQ_PER_TENSOR, 1, pixels));
+  if (wide) {
+    a.x_f16 = dt == GPUSQ_F32 ? 2 : 1;
+    a.xq_out = img_q;
+    a.scale_out = scale;
+    a.range_mode = kRangePartials;
+    a.npartial = launch_amax(a.X, dt, pixels, workspace, s);
+    a.partial = (const float*)workspace;
+    return launch_wide(a, plan, s);
+  }
+  const gpusq_status st = launch_quantize(a.X, dt, img_q, scale, GPUSQ_PER_TENSOR, 0, 1, pixels, workspace, s);
+  if (st != GPUSQ_OK) return st;
+  a.X = img_q;
+  return launch_typed<true>(a, s);
+}
+
 gpusq_status launch_spgemm(bool is_i8, const GemmArgs& a, hipStream_t s) {
   return is_i8 ? launch_typed<true>(a, s) : launch_typed<false>(a, s);
 }

@@ -134,13 +134,16 @@ __device__ __forceinline__ void load_index_half(int (&ai)[kTileTN], int half, co
 // wavefront-uniform part per step (patch_step_offset).
 // (32-bit unsigned arithmetic: M < 2^31, and 64-bit divisions cost the tile kernel's K loop, into which the tile change is
 // inlined, scores of registers)
-template <bool IS_I8>
-__device__ __forceinline__ uint32_t patch_chunk_offset(const GemmArgs& a, uint32_t m, int ch) {
-  constexpr int ES = IS_I8 ? 1 : 2;
+__device__ __forceinline__ uint32_t patch_pixel(const GemmArgs& a, uint32_t m) {  // the first pixel of patch m, in channel 0
   const uint32_t px_n = (uint32_t)a.patch_W / 16u, py_n = (uint32_t)a.patch_H / 16u;
   const uint32_t prow = m / px_n, px = m - prow * px_n;
   const uint32_t b = prow / py_n, py = prow - b * py_n;
-  const int64_t pixel = (((int64_t)b * a.patch_C) * a.patch_H + py * 16) * a.patch_W + px * 16;  // first pixel of the patch, channel 0
+  return (uint32_t)((((int64_t)b * a.patch_C) * a.patch_H + py * 16) * a.patch_W + px * 16);  // (the host keeps the images below 2^32 bytes)
+}
+template <bool IS_I8>
+__device__ __forceinline__ uint32_t patch_chunk_offset(const GemmArgs& a, uint32_t m, int ch) {
+  constexpr int ES = IS_I8 ? 1 : 2;
+  const int64_t pixel = patch_pixel(a, m);
   const int row_in_step = IS_I8 ? ch : (ch >> 1), half = IS_I8 ? 0 : (ch & 1);
   return (uint32_t)((pixel + (int64_t)row_in_step * a.patch_W) * ES + half * 16);
 }

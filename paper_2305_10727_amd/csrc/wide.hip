@@ -33,7 +33,8 @@ typedef __attribute__((address_space(1))) ep_v2u global_v2u;
 
 // S: slabs of 16 rows of the highest chunk.
 // GELU, OUT: the epilogue (fp16 or int8 output, whole 16-byte pieces of a row: N % 8 == 0 or N % 16 == 0).
-template <int S, bool FP32, int GELU, int OUT>
+// PATCH: X is an image batch, a row a 16 x 16 patch (see patch_chunk_offset), and the codes are those of the images, where their pixels are.
+template <int S, bool FP32, int GELU, int OUT, bool PATCH = false>
 __global__ void __launch_bounds__(64 * kWideWaves) spgemm_wide_kernel(const GemmArgs a, const WidePlan p) {
   constexpr int XW = FP32 ? 4 : 2;           // bytes of X in memory per code
   constexpr int XL = S * XW / 2;             // 16-byte copies per producer lane and K step
@@ -79,8 +80,12 @@ __global__ void __launch_bounds__(64 * kWideWaves) spgemm_wide_kernel(const Gemm
   if (wave < kProducers) {
     // ------------------------------------------------------------------------------------------------ producers
     constexpr int LPR = 8 * XW, RPL = kProducerThreads / LPR;  // lanes per row, rows per load
-    const int row = tid / LPR;                                 // of the first copy
-    const int code = (tid % LPR) * (16 / XW);                  // first code of a copy within the step
+    // row of a lane's first copy, and its first code within the step: consecutive lanes along a row of X, or along a row of the image, where
+    // neighbouring patches' pieces of 16 pixels are contiguous
+    constexpr int PPR = XW;                                    // 16-byte pieces of 16 pixels
+    const int in_wave = PATCH ? (lane / PPR) % (64 / LPR) : lane / LPR;
+    const int row = wave * (64 / LPR) + in_wave;
+    const int code = PATCH ? lane / (64 / 8) * 16 + lane % PPR * (16 / XW) : lane % LPR * (16 / XW);
     const uint32_t raw_lds = lds_address(raw) + (uint32_t)wave * 1024u;
     // The cursor of the requests, and behind it, D steps, that of the codes: chunk, K step, and where they are in memory.  A row past the
     // chunk's last is the last again, a piece of X past the end of a ragged row the step's first (its weights are zero): their codes are
@@ -102,18 +107,21 @@ __global__ void __launch_bounds__(64 * kWideWaves) spgemm_wide_kernel(const Gemm
       const WideChunk ch = wide_chunk(p, at, item);
       c.item = item;
       c.ks = 0;
-      c.at = ch.m0 * a.K;
+      c.at = PATCH ? 0 : ch.m0 * a.K;
 #pragma unroll
       for (int j = 0; j < XL; ++j) {
         const int r = row + RPL * j;
-        c.off[j] = (uint32_t)(r < ch.rows ? r : ch.rows - 1) * (uint32_t)a.K + (uint32_t)code;  // (the host keeps 64 rows of X below 2 GiB)
+        if constexpr (PATCH)
+          c.off[j] = patch_pixel(a, (uint32_t)ch.m0 + (uint32_t)(r < ch.rows ? r : ch.rows - 1)) + (uint32_t)(code / 16 * a.patch_W + code % 16);
+        else
+          c.off[j] = (uint32_t)(r < ch.rows ? r : ch.rows - 1) * (uint32_t)a.K + (uint32_t)code;  // (the host keeps 64 rows of X below 2 GiB)
       }
       clip(c);
     };
     auto advance = [&](Cursor& c) __attribute__((always_inline)) {
       if (c.ks + 1 < ksteps) {
         ++c.ks;
-        c.at += kStepBytes;
+        c.at = PATCH ? patch_step_offset<true>(a, c.ks) : c.at + kStepBytes;
         clip(c);
       } else if (c.item + 1 < at.items) {
         seek(c, c.item + 1);
@@ -360,8 +368,9 @@ gpusq_status launch_wide(const GemmArgs& a, const WidePlan& p, hipStream_t s) {
   const unsigned grid = 8u * (unsigned)p.per_xcd, threads = 64u * (unsigned)(kProducers + p.blocks);
   const int slabs = wide_slabs(p);
   const bool gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
+  // (few of the combinations exist with patches: fp16 output without GELU)
 #define GPUSQ_WIDE_X(S, FP32)                                                                                              \
-  (a.out_dt == GPUSQ_I8 ? (gelu ? spgemm_wide_kernel<S, FP32, 1, GPUSQ_I8> : spgemm_wide_kernel<S, FP32, 0, GPUSQ_I8>)    \
+  (a.patch_P != 0 ? spgemm_wide_kernel<S, FP32, 0, GPUSQ_F16, true> : a.out_dt == GPUSQ_I8 ? (gelu ? spgemm_wide_kernel<S, FP32, 1, GPUSQ_I8> : spgemm_wide_kernel<S, FP32, 0, GPUSQ_I8>)    \
                         : (gelu ? spgemm_wide_kernel<S, FP32, 1, GPUSQ_F16> : spgemm_wide_kernel<S, FP32, 0, GPUSQ_F16>)) \
       <<<grid, threads, 0, s>>>(a, p)
 #define GPUSQ_WIDE(S)         \

@@ -160,6 +160,11 @@ class SparsePatchEmbed:
     def forward(self, img, bias):
         """img [B,C,H,W] fp16 (or fp32 on the int8 path)"""
         B, C, H, W = self.shape
+        if self.precision == "int8" and self.fused:  # quantiser and product in one call
+            lin = self.linear
+            _call.gpusq_patch_embed16_images(img, G._TORCH_DT[img.dtype], lin.packed, lin.act_scale, lin.w_scale, bias, lin.Y, self.img_q, self.workspace,
+                                             B, C, H, W, self.D, lin.epilogue & G.EPI_BIAS)
+            return lin.Y
         if self.precision == "int8":
             _call.gpusq_quantize_int8(img, G._TORCH_DT[img.dtype], self.img_q, self.linear.act_scale, G.PER_TENSOR, 0, 1,
                                       B * C * H * W, self.workspace)
@@ -167,11 +172,8 @@ class SparsePatchEmbed:
         else:
             src, dt = img, G.F16
         if self.fused:
-            lin, epi = self.linear, self.linear.epilogue & G.EPI_BIAS
-            if self.precision == "int8":
-                _call.gpusq_patch_embed16_int8(src, lin.packed, lin.act_scale, lin.w_scale, bias, lin.Y, B, C, H, W, self.D, epi)
-            else:
-                _call.gpusq_patch_embed16_fp16(src, lin.packed, bias, lin.Y, B, C, H, W, self.D, epi)
+            lin = self.linear
+            _call.gpusq_patch_embed16_fp16(src, lin.packed, bias, lin.Y, B, C, H, W, self.D, lin.epilogue & G.EPI_BIAS)
             return lin.Y
         _call.gpusq_im2col_patches(src, self.X, dt, B, C, H, W, self.P, self.K_pad)
         if self.precision == "int8":

@@ -1,0 +1,59 @@
+"""The INT8 patch embedding with the quantiser of the images in one call (gpusq_patch_embed16_images), on the kernel that quantises whole rows
+and on the others: codes and scale against the oracle's quantiser, tokens against its convolution's product."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2305_10727_amd import synth
+from test_gpu_parity import dev, g, force_kernel, host, _oracle_weights  # noqa: F401
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _images(B, C, H, W, dtype, seed):
+    return (np.random.default_rng(seed).standard_normal((B, C, H, W)) * 1.5).astype(dtype)
+
+
+def _patches(codes):
+    B, C, H, W = codes.shape
+    return np.ascontiguousarray(codes.reshape(B, C, H // 16, 16, W // 16, 16).transpose(0, 2, 4, 1, 3, 5).reshape(B * (H // 16) * (W // 16), C * 256))
+
+
+# one channel and three, rows of one patch and of odd numbers of them, chunks of patches of several images, one and two column blocks, several
+# rounds; as the rules choose: the kernel for whole rows, the one for few rows, the tile kernel
+@pytest.mark.parametrize("kernel,B,C,H,W,D", [(5, 40, 1, 112, 16, 1040), (5, 13, 3, 48, 208, 784), (5, 64, 3, 224, 224, 192), (5, 130, 3, 224, 240, 768), (-1, 64, 3, 224, 224, 768),
+                                              (-1, 5, 3, 224, 224, 768), (-1, 64, 3, 224, 224, 1280), (-1, 300, 2, 64, 64, 256), (-1, 33, 3, 96, 160, 260)])
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+def test_images(g, force_kernel, kernel, B, C, H, W, D, dtype):
+    force_kernel(kernel)
+    img = _images(B, C, H, W, dtype, B + D)
+    _, s_w, vals, meta = _oracle_weights(synth.weights(D, C * 256, seed=B, ids=(1,)))
+    bias = synth.bias(D, seed=B, ids=(2,))
+    exp_q, exp_s = oracle.quantize_tensor_int8(img.astype(np.float32).reshape(1, -1))
+    X = _patches(exp_q.reshape(img.shape))
+    M = len(X)
+    r = np.unique(np.concatenate([np.arange(min(M, 300)), np.arange(max(0, M - 300), M), np.arange(0, M, 41)]))
+    exp = oracle.epilogue_int8_f32(oracle.spgemm_int8(X[r], vals, meta), float(exp_s), s_w, bias)["y16"]
+    Y, img_q = torch.full((M, D), 7.0, dtype=torch.float16, device="cuda"), torch.full((B, C, H, W), 99, dtype=torch.int8, device="cuda")
+    sa, ws, x = torch.zeros(1, device="cuda"), torch.empty(4096, dtype=torch.uint8, device="cuda"), dev(img)
+    g.calls.gpusq_patch_embed16_images(x, g._TORCH_DT[x.dtype], g.pack(dev(vals), dev(meta), C * 256), sa, dev(s_w), dev(bias), Y, img_q, ws, B, C, H, W, D, g.EPI_BIAS)
+    assert host(sa)[0] == np.float32(exp_s) and np.array_equal(host(img_q).reshape(-1), exp_q.reshape(-1))
+    assert np.array_equal(host(Y)[r].view(np.uint16), exp.view(np.uint16))
+
+
+def test_refusals(g):
+    B, C, H, W, D = 64, 3, 224, 224, 768
+    img, Y = torch.zeros((B, C, H, W), dtype=torch.float16, device="cuda"), torch.empty((B * 196, D), dtype=torch.float16, device="cuda")
+    q, sw, ws, sa = torch.full(img.shape, 99, dtype=torch.int8, device="cuda"), torch.ones(D, device="cuda"), torch.empty(4096, dtype=torch.uint8, device="cuda"), torch.zeros(1, device="cuda")
+    packed = torch.zeros(g.packed_bytes(torch.int8, D, C * 256), dtype=torch.uint8, device="cuda")
+    good = [img, g.F16, packed, sa, sw, None, Y, q, ws, B, C, H, W, D, 0]
+    for at, value in ((1, g.I8), (3, None), (4, None), (7, None), (8, None), (11, 220), (14, g.EPI_GELU), (14, g.EPI_BIAS), (9, 1)):
+        args = list(good)
+        args[at] = value
+        if at == 9:
+            args[13] = 64  # too small for the gather: refused before the quantiser is launched
+        with pytest.raises(g.GpusqError):
+            g.calls.gpusq_patch_embed16_images(*args)
+    torch.cuda.synchronize()
+    assert (host(q) == 99).all()
