@@ -3,7 +3,7 @@
 // The tile kernels read codes that a quantiser pass has written, each column tile all of them again.  Here a workgroup has all
 // channels of its rows (up to 12 blocks of 64; more are split into equal column blocks), so the fp16 or fp32 activations come from
 // memory once, are turned into codes on the way and multiplied, and the pass that did nothing else is gone.
-//   - 4 wavefronts (producers) request the rows of X several K steps ahead into registers, quantise a step and put its codes into
+//   - 4 wavefronts (producers) request the rows of X several K steps ahead into LDS, quantise a step and put its codes into
 //     one of two LDS buffers, and into Xq; one wavefront per 64 channels (consumers) reads the other buffer and multiplies.  One barrier per
 //     K step.  The roles are wavefronts of their own because loads return in order per wavefront: a consumer's weights, an L2 hit away,
 //     would wait behind rows of X from HBM.
@@ -11,7 +11,10 @@
 //     no two of them need the same.
 //   - persistent: a workgroup keeps its column block and walks row chunks; the producers' requests run on across chunks.
 // A K step of 64 rows and 768 channels brings 61 KB of weights and 16 KB of X into the CU (1200 clocks at 64 bytes a clock), its matrix
-// instructions take 790 clocks: bound by memory (X in, codes and Y out) as long as a chunk has enough K steps.
+// instructions take 790 clocks: bound by memory (X in, codes and Y out) as long as a chunk has enough K steps.  In the kernel (12608 rows of 768,
+// clocks): 6000 until the first codes (range, constants, HBM), six steps of 1900 to 2000, 2900 for the epilogue.
+// The layer in us, the quantiser and the GEMM one after the other against this (fp16 X and Y, own range, three buffers in turn):
+//   14070 x 576 -> 256  16.8 / 10.1     12608 x 768 -> 768  23.6 / 19.5     7029 x 1152 -> 256  20.6 / 14.9     50432 x 192 -> 192  17.8 here
 #include <type_traits>
 
 #include "tile_common.h"
@@ -92,13 +95,14 @@ __global__ void __launch_bounds__(64 * kWideWaves) spgemm_wide_kernel(const Gemm
     // then written once more to where they stand already, and every step has the same copies and stores, without a condition, which the
     // waits count.  So do the requests and the codes past the last step: they are that step again.
     struct Cursor {
+      uint32_t unit;      // bytes of a value (X) or a code
       int item, ks;
-      int64_t at;         // chunk and step: in codes from the first
-      uint32_t off[XL];   // this lane's pieces, from there
+      int64_t at;         // chunk and step: in values from the first
+      uint32_t off[XL];   // this lane's pieces, in bytes from there
     };
     auto clip = [&](Cursor& c) __attribute__((always_inline)) {  // the step is a row's last, and ragged
       if (tail != 0 && c.ks + 1 == ksteps) {
-        const uint32_t back = code >= tail ? (uint32_t)code : 0u;
+        const uint32_t back = code >= tail ? (uint32_t)code * c.unit : 0u;
 #pragma unroll
         for (int j = 0; j < XL; ++j) c.off[j] -= back;
       }
@@ -112,9 +116,9 @@ __global__ void __launch_bounds__(64 * kWideWaves) spgemm_wide_kernel(const Gemm
       for (int j = 0; j < XL; ++j) {
         const int r = row + RPL * j;
         if constexpr (PATCH)
-          c.off[j] = patch_pixel(a, (uint32_t)ch.m0 + (uint32_t)(r < ch.rows ? r : ch.rows - 1)) + (uint32_t)(code / 16 * a.patch_W + code % 16);
+          c.off[j] = (patch_pixel(a, (uint32_t)ch.m0 + (uint32_t)(r < ch.rows ? r : ch.rows - 1)) + (uint32_t)(code / 16 * a.patch_W + code % 16)) * c.unit;
         else
-          c.off[j] = (uint32_t)(r < ch.rows ? r : ch.rows - 1) * (uint32_t)a.K + (uint32_t)code;  // (the host keeps 64 rows of X below 2 GiB)
+          c.off[j] = ((uint32_t)(r < ch.rows ? r : ch.rows - 1) * (uint32_t)a.K + (uint32_t)code) * c.unit;  // (the host keeps 64 rows of X below 2 GiB)
       }
       clip(c);
     };
@@ -128,18 +132,21 @@ __global__ void __launch_bounds__(64 * kWideWaves) spgemm_wide_kernel(const Gemm
       }
     };
     Cursor pf;
+    pf.unit = FP32 ? 1 : XW;  // (fp32: to bytes at the request; 1.5 % faster there)
     seek(pf, 0);
     auto request = [&](uint32_t slot) __attribute__((always_inline)) {  // slot: byte offset of the step's stage
       const global_u8* x = uniform_ptr((const uint8_t*)a.X + pf.at * XW);
 #pragma unroll
-      for (int j = 0; j < XL; ++j) copy16_to_lds((const void*)x, pf.off[j] * (uint32_t)XW, raw_lds + slot + (uint32_t)j * (1024u * kProducers));
+      for (int j = 0; j < XL; ++j) copy16_to_lds((const void*)x, pf.off[j] * (uint32_t)(FP32 ? XW : 1), raw_lds + slot + (uint32_t)j * (1024u * kProducers));
       advance(pf);
     };
     constexpr uint32_t kRawStage = XL * 1024u * kProducers;
+    constexpr int early = FP32 ? D : 1;
 #pragma nounroll
-    for (int d = 0; d < D; ++d) request((uint32_t)d * kRawStage);
-
+    for (int d = 0; d < early; ++d) request((uint32_t)d * kRawStage);
     __syncthreads();  // the scale
+#pragma nounroll
+    for (int d = early; d < D; ++d) request((uint32_t)d * kRawStage);
     const float s_a = scale();
     if (!given && blockIdx.x == 0 && tid == 0) a.scale_out[0] = s_a;
     Fp16Quantiser qz;
@@ -156,7 +163,7 @@ __global__ void __launch_bounds__(64 * kWideWaves) spgemm_wide_kernel(const Gemm
     // where this lane's codes lie in a buffer: row-major, 16-byte chunk c of row r at c ^ ((r >> 1) & 7)
     const uint32_t ring_off = (uint32_t)(row * kStepBytes + (((code >> 4) ^ ((row >> 1) & 7)) << 4) + (code & 15));
     // The codes go past the caches (nothing here reads them again) where a step's are whole 128-byte lines; in parts of lines they are left to
-    // the L2 to put together: 28919 x 2256 -> 128 under a given scale 73 us without, XX so.
+    // the L2 to put together: 28919 x 2256 -> 128 under a given scale 46.3 us, 75.5 past the caches (the quantiser and the GEMM one after the other: 50.0).
     auto store_codes = [&](auto v, auto* at) __attribute__((always_inline)) {
       if (tail == 0)
         __builtin_nontemporal_store(v, at);
@@ -164,11 +171,16 @@ __global__ void __launch_bounds__(64 * kWideWaves) spgemm_wide_kernel(const Gemm
         *at = v;
     };
     Cursor here;
+    here.unit = 1;
     seek(here, 0);
     uint32_t slot = 0;
     // One step: its rows have landed when no more than the copies and stores requested behind them are in flight.
-    auto produce = [&](auto write, bool first, uint8_t* dst) __attribute__((always_inline)) {
+    // MODE (fp16): 0 the scale of X's own range and one fused multiply-add a value (the code of a NaN is 0 as it is: its low byte), 1 a given
+    // scale, 2 products that are refined.  Loops of their own, with no question per step: 50432 x 192 -> 192 18.9 -> 17.9 us, under a given scale
+    // 14.2 -> 13.4; 12608 x 768 -> 768 20.6 -> 20.3, 15.5 -> 15.0 (with the first step alone requested in front of the scale's barrier).
+    auto produce = [&](auto write, auto mode, bool first, uint8_t* dst) __attribute__((always_inline)) {
       constexpr bool WRITE = decltype(write)::value;
+      constexpr int MODE = decltype(mode)::value;
       if (WRITE && !first)
         wait_vm<(D - 1) * 2 * XL>();
       else
@@ -187,16 +199,17 @@ __global__ void __launch_bounds__(64 * kWideWaves) spgemm_wide_kernel(const Gemm
           quantize_bytes8(v, s_a, r_a, c[j][0], c[j + 1][0]);
         }
       } else {
-        const bool odd = qz.odd(x);
-        if (__builtin_expect(odd || qz.refine, 0)) {
+        const bool odd = MODE != 0 && qz.odd(x);
+        if (MODE == 2 || __builtin_expect(odd, 0)) {
 #pragma unroll
-          for (int j = 0; j < XL; ++j) qz.codes<true>(x[j], odd, c[j][0], c[j][1]);
-        } else if (given) {
-#pragma unroll
-          for (int j = 0; j < XL; ++j) Fp16Quantiser{qz.s, qz.r, false}.codes<true>(x[j], false, c[j][0], c[j][1]);
+          for (int j = 0; j < XL; ++j) {
+            if constexpr (MODE == 1) asm volatile("" : "+v"(x[j]));  // (shares nothing with the other branch)
+            qz.codes<true>(x[j], odd, c[j][0], c[j][1]);
+          }
         } else {
+          const Fp16Quantiser plain{qz.s, qz.r, false};
 #pragma unroll
-          for (int j = 0; j < XL; ++j) Fp16Quantiser{qz.s, qz.r, false}.codes<false>(x[j], false, c[j][0], c[j][1]);
+          for (int j = 0; j < XL; ++j) plain.codes<MODE != 0>(x[j], false, c[j][0], c[j][1]);
         }
       }
       global_u8* q = uniform_ptr(a.xq_out + here.at);
@@ -217,19 +230,27 @@ __global__ void __launch_bounds__(64 * kWideWaves) spgemm_wide_kernel(const Gemm
       request(slot);
       slot = slot + kRawStage == D * kRawStage ? 0 : slot + kRawStage;
     };
-    auto run = [&](auto write) __attribute__((always_inline)) {
+    auto run = [&](auto write, auto mode) __attribute__((always_inline)) {
       uint32_t buf = 0;
 #pragma nounroll
       for (int g = 0; g <= steps; ++g) {  // (behind the last step: that one again, into the buffer that nothing reads any more)
-        produce(write, g <= D, ring[0] + buf);
+        produce(write, mode, g <= D, ring[0] + buf);
         buf ^= kStage;
         __syncthreads();
       }
     };
-    if (at.n_blk == 0)
-      run(std::true_type{});
+    auto run_mode = [&](auto mode) __attribute__((always_inline)) {
+      if (at.n_blk == 0)
+        run(std::true_type{}, mode);
+      else
+        run(std::false_type{}, mode);
+    };
+    if (FP32 || (!given && !qz.refine))
+      run_mode(std::integral_constant<int, 0>{});
+    else if (!qz.refine)
+      run_mode(std::integral_constant<int, 1>{});
     else
-      run(std::false_type{});
+      run_mode(std::integral_constant<int, 2>{});
     wait_vm<0>();  // the copies requested past the end land before the LDS is given up
     return;
   }
