@@ -77,6 +77,24 @@ def test_codes(g, force_kernel):
         assert np.array_equal(_layer(g, dev(X), packed, sw, b, 62, N, K, dev(np.array([s], np.float32)), torch.float16, None, False)[1], exp), s
 
 
+# the scale of X's own range where X holds no, only tiny or not only numbers: as from the quantiser and the GEMM
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("kind", ["nan", "inf", "both", "zero", "tiny", "all nan"])
+def test_own_range(g, force_kernel, dtype, kind):
+    M, K, N = 130, 272, 80
+    X = (np.random.default_rng(5).standard_normal((M, K)) * {"zero": 0, "tiny": 1e-7}.get(kind, 1)).astype(dtype)
+    for v, k in ((np.nan, ("nan", "both")), (np.inf, ("inf", "both")), (-np.inf, ("both",))):
+        if kind in k: X.reshape(-1)[np.random.default_rng(len(k)).integers(0, M * K, 50)] = v
+    if kind == "all nan": X[:] = np.nan
+    _, s_w, vals, meta = _oracle_weights(synth.weights(N, K, seed=M, ids=(9,), sigma=0.05))
+    packed, sw, b, x = g.pack(dev(vals), dev(meta), K), dev(s_w), dev(synth.bias(N, seed=M, ids=(10,))), dev(X)
+    q, s = g.quantize_int8(x, g.PER_TENSOR)
+    exp = host(g.spgemm_int8(q, packed, N, act_scale=s, w_scale=sw, bias=b))
+    force_kernel(5)
+    y, codes, scale = _layer(g, x, packed, sw, b, M, N, K, None, torch.float16, None, False)
+    assert np.array_equal(codes, host(q)) and np.array_equal(scale.view(np.uint32), host(s).view(np.uint32)) and np.array_equal(y, exp, equal_nan=True)
+
+
 # Y over X, over the partial maxima of the range pass, out_scale the scale that the call finds: as from operands that lie apart
 @pytest.mark.parametrize("how", ["input", "workspace", "scale"])
 def test_shared_operands(g, force_kernel, how):
