@@ -306,8 +306,8 @@ def main():
             torch.cuda.empty_cache()
     lines += ["", "Linear layers of one encoder block on the INT8 path (qkv, proj, fc1 + GELU, fc2; attention and normalisation left out: "
               "proj and fc1 read buffers that nothing refreshes), us per block, hot buffers.  Unchained: every layer writes fp16 and the next "
-              "one quantises it with a dynamic per-tensor scale (12 launches).  Chained: static scales, the re-quantisation fused into the "
-              "producer's epilogue (6 launches, with few rows 5 or 4), launched one by one or replayed as one HIP graph:", "",
+              "one quantises it with a dynamic per-tensor scale (12 launches at the most).  Chained: static scales, the re-quantisation fused into the "
+              "producer's epilogue (5 launches, 4 where qkv quantises its rows itself), launched one by one or replayed as one HIP graph:", "",
               "| model | M | D | hidden | unchained us | chained us | chained, HIP graph us |", "|---|---|---|---|---|---|---|"]
     for model, M, D, hidden in [] if a.only_int4 else [("DeiT-Tiny, batch 1", 197, 192, 768), ("DeiT-Small, batch 1", 197, 384, 1536), ("ViT-B/16, batch 1", 197, 768, 3072),
                                 ("ViT-B/16, batch 8", 1576, 768, 3072), ("ViT-B/16, batch 64", 12608, 768, 3072)]:
