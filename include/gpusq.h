@@ -200,7 +200,8 @@ gpusq_status gpusq_spgemm_int8(const int8_t* Xq, const void* Wpacked, const floa
 /* The same product with fp16 output (no GELU), and the codes of that output for the layer behind it, in one launch:
  * Yq[m][n] = clamp(rint(Y[m][n] / codes_scale[0]), -127, 127) of the rounded fp16 value, bit-identical to gpusq_spgemm_int8 followed by
  * gpusq_quantize_int8(GPUSQ_PER_TENSOR) with that scale given.  Y [M][N] fp16, Yq [M][N] int8, codes_scale: device pointer to 1 float.  All
- * other arguments as for gpusq_spgemm_int8; GPUSQ_EPI_GELU is not implemented (GPUSQ_ERR_UNSUPPORTED). */
+ * other arguments as for gpusq_spgemm_int8; GPUSQ_EPI_GELU is not implemented (GPUSQ_ERR_UNSUPPORTED).  Yq may be Xq or overlap it (two
+ * layers with one buffer of codes): that takes two launches. */
 gpusq_status gpusq_spgemm_int8_codes(const int8_t* Xq, const void* Wpacked, const float* act_scale, const float* w_scale,
                                      const float* bias, void* Y, int8_t* Yq, const float* codes_scale, int64_t M, int64_t N,
                                      int64_t K, int epilogue, void* stream);

@@ -342,6 +342,11 @@ gpusq_status gpusq_spgemm_int8_codes(const int8_t* Xq, const void* Wpacked, cons
   st = check_int8_extras(act_scale, w_scale, GPUSQ_F16, nullptr);
   if (st != GPUSQ_OK) return st;
   GemmArgs a{Xq, Wpacked, act_scale, w_scale, bias, codes_scale, Y, (int)M, (int)N, (int)K, epilogue, (int)GPUSQ_F16};
+  if (overlap(ByteRange{Xq, M * K}, ByteRange{Yq, M * N})) {  // layers that share one buffer of codes: other workgroups still read Xq
+    a.out_scale = nullptr;
+    st = launch_spgemm(true, a, (hipStream_t)stream);
+    return st != GPUSQ_OK ? st : launch_quantize(Y, GPUSQ_F16, Yq, const_cast<float*>(codes_scale), GPUSQ_PER_TENSOR, 1, M, N, nullptr, (hipStream_t)stream);
+  }
   a.codes_out = Yq;
   return launch_spgemm(true, a, (hipStream_t)stream);
 }

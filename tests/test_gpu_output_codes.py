@@ -38,6 +38,25 @@ def test_output_and_codes(g, force_kernel, kernel, M, K, N, biased):
     assert np.array_equal(host(Yq)[rows], codes)
 
 
+@pytest.mark.parametrize("kernel,M,N", [(4, 197, 192), (0, 300, 256), (2, 2048, 768)])
+@pytest.mark.parametrize("at", [0, 64])
+def test_codes_over_the_input(g, force_kernel, kernel, M, N, at):
+    """Yq over Xq, whole or from a later row on: the same as with buffers of their own"""
+    force_kernel(kernel)
+    rng = np.random.default_rng(M)
+    Xq = dev(rng.integers(-127, 128, (M, N)).astype(np.int8))
+    _, s_w, vals, meta = _oracle_weights(synth.weights(N, N, seed=M, ids=(1,)))
+    packed, scale = g.pack(dev(vals), dev(meta), N), dev(np.array([0.02, 0.05], np.float32))
+    both = torch.zeros((M + at, N), dtype=torch.int8, device="cuda")
+    both[:M] = Xq
+    out = []
+    for x, q in ((Xq, torch.empty_like(Xq)), (both[:M], both[at:])):
+        Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+        g.calls.gpusq_spgemm_int8_codes(x, packed, scale[:1], dev(s_w), None, Y, q, scale[1:], M, N, N, 0)
+        out.append((host(Y), host(q)))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
 def test_infinite_outputs_and_refusals(g):
     """Outputs beyond fp16 and their codes; GELU is refused, and so is a missing scale."""
     M, K, N = 64, 128, 64
