@@ -287,8 +287,9 @@ static int fewrows_tm(int64_t M, int64_t N, int resident) {
 // one batch of K steps per wavefront is all.  Given scale, quantiser and GEMM / both in one, us (graph replays; a launch less is
 // worth another microsecond where the host is what launches wait for): one workgroup per CU 320 x 1536 -> 768 6.9 / 5.4, 16 x 3072
 // -> 1024 7.5 / 6.7, 96 x 4096 -> 2304 8.8 / 8.0; two, up to 12 steps 224 x 1024 -> 2304 6.7 / 6.2, 160 x 1536 -> 2304 7.2 / 7.2, beyond 160 x
-// 3072 -> 2304 9.3 / 9.8, 160 x 4096 -> 2304 10.6 / 11.6; three 272 x 1024 -> 2304 7.3 / 8.8.  The tiles are of 16 rows then: with 32 the
-// 2304 channels take longer.
+// 3072 -> 2304 9.3 / 9.8, 160 x 4096 -> 2304 10.6 / 11.6; three 272 x 1024 -> 2304 7.3 / 8.8, and so at any K (64 to 1024, 256 to 4352
+// channels, both types, either scale; quantiser and GEMM over both in one, graph replays: 2.4 to 3 workgroups 0.74 to 1.03, 6 0.58 to 0.82).
+// The tiles are of 16 rows then: with 32 the 2304 channels take longer.
 // fp32 rows are twice the bytes and come in vectors of 4: 320 x 384 -> 768 5.2 / 4.1, 320 x 1536 -> 768 6.6 / 6.0, but 320 x 3072 -> 768 8.6 / 10.2; two
 // workgroups 672 x 384 -> 768 5.5 / 4.9, 672 x 768 -> 768 6.0 / 6.4.
 bool fewrows_folds_quantiser(int64_t M, int64_t N, int64_t K, int resident, bool fp32) {
