@@ -378,16 +378,26 @@ gpusq_status gpusq_linear_int8(const void* X, gpusq_dtype x_dt, const void* Wpac
   return launch_linear_int8(a, x_dt, Xq, act_scale, scale_is_input, workspace, (hipStream_t)stream);
 }
 
-int gpusq_linear_int8_launches(gpusq_dtype x_dt, int64_t M, int64_t N, int64_t K, int epilogue, int scale_is_input, int cus) {
-  if (M <= 0 || M > INT32_MAX || check_nk(N, K) != GPUSQ_OK || K % 16 != 0 || N % 4 != 0) return 0;
-  if (x_dt != GPUSQ_F32 && x_dt != GPUSQ_F16) return 0;
-  GemmArgs a{};
+// The sizes and types of a layer that is asked about, and not run; false if they are invalid
+static bool layer_sizes(GemmArgs& a, gpusq_dtype x_dt, gpusq_dtype out_dt, int64_t M, int64_t N, int64_t K, int epilogue) {
+  if (M <= 0 || M > INT32_MAX || check_nk(N, K) != GPUSQ_OK || K % 16 != 0 || N % 4 != 0) return false;
+  if ((x_dt != GPUSQ_F32 && x_dt != GPUSQ_F16) || (out_dt != GPUSQ_F16 && out_dt != GPUSQ_I32 && out_dt != GPUSQ_I8)) return false;
   a.M = (int)M;
   a.N = (int)N;
   a.K = (int)K;
   a.epilogue = epilogue;
-  a.out_dt = (int)GPUSQ_F16;
-  return linear_int8_launches(a, x_dt, scale_is_input, cus);
+  a.out_dt = (int)out_dt;
+  return true;
+}
+
+int gpusq_linear_int8_launches(gpusq_dtype x_dt, int64_t M, int64_t N, int64_t K, int epilogue, int scale_is_input, int cus) {
+  GemmArgs a{};
+  return layer_sizes(a, x_dt, GPUSQ_F16, M, N, K, epilogue) ? linear_int8_launches(a, x_dt, scale_is_input, cus) : 0;
+}
+
+int gpusq_linear_int8_quantiser(gpusq_dtype x_dt, gpusq_dtype out_dt, int64_t M, int64_t N, int64_t K, int epilogue, int cus) {
+  GemmArgs a{};
+  return layer_sizes(a, x_dt, out_dt, M, N, K, epilogue) ? linear_int8_quantiser(a, x_dt, cus) : -1;
 }
 
 gpusq_status gpusq_gemm_fp16_dense(const void* X, const void* W, const float* bias, void* Y, int64_t M, int64_t N,

@@ -652,26 +652,29 @@ static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, int resident, const De
   return d.gemm_us > 0 && wide_us(p, a.M, a.N, a.K, resident, fp32, gelu, i8) < margin * quantise_and_gemm_us(d.gemm_us, a.M, a.N, a.K, fp32, i8);
 }
 
-// What quantises: the kernel for few rows, the one for whole rows (with this plan), or a launch of its own
-enum { kQuantiseFewRows, kQuantiseWide, kQuantiseApart };
+// What quantises (GPUSQ_QUANTISE_*); WHOLE_ROWS: with this plan
 static int quantiser_of(const GemmArgs& a, gpusq_dtype dt, int resident, WidePlan& p) {
   const bool gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
   const bool few = fewrows_folds_quantiser(a.M, a.N, a.K, resident, dt == GPUSQ_F32) && fewrows_supports(a);
   const Decision& d = decide(true, a.M, a.N, a.K, gelu, resident, false);
-  if (few && d.choice == 4) return kQuantiseFewRows;
-  return wide_takes(a, dt, resident, d, p) ? kQuantiseWide : kQuantiseApart;
+  if (few && d.choice == 4) return GPUSQ_QUANTISE_FEW_ROWS;
+  return wide_takes(a, dt, resident, d, p) ? GPUSQ_QUANTISE_WHOLE_ROWS : GPUSQ_QUANTISE_APART;
 }
 
 // 1 + the launches in front of the GEMM's own
 static int launches_of(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int quantiser) {
-  if (quantiser == kQuantiseApart) return scale_is_input ? 2 : 3;
-  if (quantiser == kQuantiseWide) return scale_is_input ? 1 : 2;
+  if (quantiser == GPUSQ_QUANTISE_APART) return scale_is_input ? 2 : 3;
+  if (quantiser == GPUSQ_QUANTISE_WHOLE_ROWS) return scale_is_input ? 1 : 2;
   return scale_is_input || (int64_t)a.M * a.K * dtype_bytes(dt) <= kRangeHereBytes ? 1 : 2;
 }
 
 int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int cus) {
   WidePlan p;
   return launches_of(a, dt, scale_is_input, quantiser_of(a, dt, cus > 0 ? cus : num_cus(), p));
+}
+int linear_int8_quantiser(const GemmArgs& a, gpusq_dtype dt, int cus) {
+  WidePlan p;
+  return quantiser_of(a, dt, cus > 0 ? cus : num_cus(), p);
 }
 
 gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, void* workspace, hipStream_t s) {
@@ -682,7 +685,7 @@ gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* s
   const int64_t range_bytes = launches == 2 ? (int64_t)gpusq_quantize_workspace_bytes(GPUSQ_PER_TENSOR, a.M, a.K) : 0;
   const bool apart = may_quantise_inside(a.X, dtype_bytes(dt), a.Y, dtype_bytes(a.out_dt), a.M, a.N, a.K, scale, scale_is_input != 0, a.out_scale,
                                          workspace, range_bytes);
-  if (quantiser != kQuantiseApart && apart) {
+  if (quantiser != GPUSQ_QUANTISE_APART && apart) {
     a.x_f16 = dt == GPUSQ_F32 ? 2 : 1;
     a.xq_out = Xq;
     if (!scale_is_input) {
@@ -693,7 +696,7 @@ gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* s
         a.partial = (const float*)workspace;
       }
     }
-    return quantiser == kQuantiseWide ? launch_wide(a, plan, s) : launch_fewrows(true, a, resident, s);
+    return quantiser == GPUSQ_QUANTISE_WHOLE_ROWS ? launch_wide(a, plan, s) : launch_fewrows(true, a, resident, s);
   }
   const gpusq_status st = launch_quantize(a.X, dt, Xq, scale, GPUSQ_PER_TENSOR, scale_is_input, a.M, a.K, workspace, s);
   if (st != GPUSQ_OK) return st;

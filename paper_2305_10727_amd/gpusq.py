@@ -17,7 +17,7 @@ OK, ERR_NULL, ERR_SHAPE, ERR_ALIGN, ERR_UNSUPPORTED, ERR_HIP = range(6)
 F32, F16, I8, I32 = range(4)
 EPI_NONE, EPI_BIAS, EPI_GELU = 0, 1, 2
 PER_ROW, PER_TENSOR = 0, 1
-WIDE_MIN_ROWS = 2048  # GPUSQ_WIDE_MIN_ROWS
+QUANTISE_APART, QUANTISE_FEW_ROWS, QUANTISE_WHOLE_ROWS = range(3)
 
 _TORCH_DT = {torch.float32: F32, torch.float16: F16, torch.int8: I8, torch.int32: I32}
 _DT_TORCH = {v: k for k, v in _TORCH_DT.items()}
@@ -29,7 +29,7 @@ EXPORTS = [
     "gpusq_spgemm_int8", "gpusq_spgemm_int8_codes", "gpusq_spgemm_int8_xf16", "gpusq_spgemm_plan", "gpusq_im2col_patches", "gpusq_patch_embed16_int8", "gpusq_patch_embed16_fp16", "gpusq_patch_embed16_images", "gpusq_gemm_fp16_dense", "gpusq_gemm_int8_dense",
     "gpusq_prune_4to8_pairs", "gpusq_quantize_rows_int4", "gpusq_compress_int4", "gpusq_decompress_int4",
     "gpusq_int4_to_sparse_int8", "gpusq_prune_n_of_m", "gpusq_force_kernel",
-    "gpusq_quantize_tensor_int8_noalloc", "gpusq_linear_int8", "gpusq_linear_int8_launches",
+    "gpusq_quantize_tensor_int8_noalloc", "gpusq_linear_int8", "gpusq_linear_int8_launches", "gpusq_linear_int8_quantiser",
 ]
 
 
@@ -136,6 +136,8 @@ def lib():
         L.gpusq_linear_int8.restype = ci
         L.gpusq_linear_int8_launches.argtypes = [ci, i64, i64, i64, ci, ci, ci]
         L.gpusq_linear_int8_launches.restype = ci
+        L.gpusq_linear_int8_quantiser.argtypes = [ci, ci, i64, i64, i64, ci, ci]
+        L.gpusq_linear_int8_quantiser.restype = ci
         L.gpusq_gemm_fp16_dense.argtypes = [vp, vp, vp, vp, i64, i64, i64, ci, vp]
         L.gpusq_gemm_int8_dense.argtypes = [vp, vp, vp, vp, vp, vp, ci, vp, i64, i64, i64, ci, vp]
         L.gpusq_im2col_patches.argtypes = [vp, vp, ci, i64, i64, i64, i64, i64, i64, vp]

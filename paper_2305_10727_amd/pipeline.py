@@ -89,9 +89,10 @@ class SparseLinear:
 
     def takes_fp16_input(self):
         """True when the INT8 GEMM of this layer should quantise fp16 activations itself (static scale): few rows and a K that
-        is not too long, as the library's one-call layer decides it (one launch instead of two)."""
-        return (self.precision == "int8" and self.M < G.WIDE_MIN_ROWS and
-                G.lib().gpusq_linear_int8_launches(G.F16, self.M, self.N, self.K, self.epilogue, 1, 0) == 1)
+        is not too long, as the library's one-call layer decides it (one launch instead of two).  Not where that call takes its
+        kernel for many rows: the GEMM alone does not."""
+        return self.precision == "int8" and G.lib().gpusq_linear_int8_quantiser(
+            G.F16, G._TORCH_DT[self.out_dtype], self.M, self.N, self.K, self.epilogue, 0) == G.QUANTISE_FEW_ROWS
 
     def gemm_from_f16(self, X, bias, out_scale=None):
         """INT8 path with a static act_scale: quantise + GEMM in one launch (see takes_fp16_input)"""

@@ -293,3 +293,32 @@ def test_every_chunk_of_the_kernel_for_whole_rows_is_met_once(tmp_path):
     assert build.returncode == 0, build.stderr
     run = subprocess.run([exe, "20000"], capture_output=True, text=True, timeout=120)
     assert run.returncode == 0 and run.stdout == "20000 plans\n", run.stdout
+
+
+@pytest.mark.parametrize("M,K,N,takes", [(197, 768, 768, True), (2047, 256, 64, True), (2048, 256, 64, True), (4096, 256, 64, True), (4097, 256, 128, False),
+                                         (8192, 256, 64, True), (8193, 256, 64, False), (12608, 768, 768, False), (7029, 1152, 256, False)])
+def test_layers_whose_gemm_takes_fp16_activations(M, K, N, takes):
+    """Those for which the kernel for few rows quantises, whatever their number of rows, and not those of the kernel for many rows (the call
+    that makes one launch of both as well)."""
+    torch = pytest.importorskip("torch")
+    from paper_2305_10727_amd import gpusq
+    from paper_2305_10727_amd.pipeline import SparseLinear
+    for out in (torch.float16, torch.int8):
+        assert SparseLinear(M, K, N, "int8", out_dtype=out, device="cpu").takes_fp16_input() == takes
+    if takes:
+        assert gpusq.lib().gpusq_linear_int8_launches(gpusq.F16, M, N, K, gpusq.EPI_BIAS, 1, 256) == 1
+
+
+def test_what_quantises_a_layer(lib):
+    """The answers of gpusq_linear_int8_quantiser and gpusq_linear_int8_launches agree; int32 output has no kernel for whole rows"""
+    f = lib.gpusq_linear_int8_quantiser
+    f.argtypes = [ctypes.c_int, ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int] * 2
+    launches = lib.gpusq_linear_int8_launches
+    launches.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int] * 3
+    F32, F16, I8, I32 = range(4)
+    for x_dt in (F32, F16):
+        for M, N, K, what in ((197, 768, 768, 1), (1576, 1152, 384, 0), (12608, 768, 768, 2), (12608, 3072, 768, 0)):
+            assert f(x_dt, F16, M, N, K, 1, 256) == what
+            assert launches(x_dt, M, N, K, 1, 1, 256) == (2 if what == 0 else 1)
+        assert f(x_dt, I32, 12608, 768, 768, 1, 256) == 0 and f(x_dt, I8, 12608, 768, 768, 1, 256) == 2
+    assert f(I8, F16, 197, 768, 768, 0, 256) == f(F16, F32, 197, 768, 768, 0, 256) == f(F16, F16, 197, 768, 100, 0, 256) == f(F16, F16, 0, 768, 768, 0, 256) == -1
