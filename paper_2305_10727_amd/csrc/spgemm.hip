@@ -657,6 +657,7 @@ static int quantiser_of(const GemmArgs& a, gpusq_dtype dt, int resident, WidePla
   const bool gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
   const bool few = fewrows_folds_quantiser(a.M, a.N, a.K, resident, dt == GPUSQ_F32) && fewrows_supports(a);
   const Decision& d = decide(true, a.M, a.N, a.K, gelu, resident, false);
+  if (d.forced == 5 && wide_takes(a, dt, resident, d, p)) return GPUSQ_QUANTISE_WHOLE_ROWS;
   if (few && d.choice == 4) return GPUSQ_QUANTISE_FEW_ROWS;
   return wide_takes(a, dt, resident, d, p) ? GPUSQ_QUANTISE_WHOLE_ROWS : GPUSQ_QUANTISE_APART;
 }

@@ -239,6 +239,15 @@ def test_force_kernel_override_is_an_explicit_call(lib):
         assert lib.gpusq_force_kernel(3) == 2
         assert _plan(lib, I8, 197, 768, 144, 0, 256)[1][0] == 0   # ragged K cannot run on kernel 3: the rules decide
         assert _plan(lib, I8, 12608, 3072, 768, 0, 256)[1][0] == 3
+        # 5: the size rules, but the layer on the kernel for whole rows at every size it can, those of the kernel for few rows among them
+        assert lib.gpusq_force_kernel(5) == 3
+        for M, N, K in ((1, 16, 16), (130, 80, 272), (62, 16, 1024), (17, 768, 384), (2048, 64, 256), (12608, 3072, 768)):
+            for x_dt in (0, 1):
+                assert lib.gpusq_linear_int8_quantiser(x_dt, 1, ctypes.c_int64(M), ctypes.c_int64(N), ctypes.c_int64(K), 0, 256) == 2
+                assert lib.gpusq_linear_int8_launches(x_dt, ctypes.c_int64(M), ctypes.c_int64(N), ctypes.c_int64(K), 0, 0, 256) == 2
+        assert lib.gpusq_linear_int8_quantiser(1, 1, ctypes.c_int64(130), ctypes.c_int64(84), ctypes.c_int64(272), 0, 256) == 1  # N % 16
+        assert _plan(lib, I8, 12608, 3072, 768, 0, 256)[1][0] == 2
+        assert lib.gpusq_force_kernel(3) == 5
         assert lib.gpusq_force_kernel(7) == 3                      # anything else clears the override
         assert lib.gpusq_force_kernel(-1) == -1
     finally:

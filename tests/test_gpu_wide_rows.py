@@ -17,6 +17,26 @@ SHAPES = [(1, 16, 16), (15, 128, 64), (16, 144, 80), (17, 384, 768), (4096, 512,
           (33000, 256, 528), (50000, 128, 128), (2500, 1296, 1552), (3000, 3088, 192)]
 
 
+def _is_wide(g, dtype, out, M, K, N, gelu=False):
+    return g.lib().gpusq_linear_int8_quantiser(g.F16 if dtype == np.float16 else g.F32, g._TORCH_DT[out], M, N, K, g.EPI_GELU if gelu else 0, 0) == g.QUANTISE_WHOLE_ROWS
+
+
+def _refined(s):
+    """whether no reciprocal of the scale (rounded, the next above, below) decides all codes of fp16 values as the division does: for one of the
+    two fp16 neighbours of a code boundary each of them fails"""
+    s, c = np.float32(abs(s)), np.arange(254)
+    if not 2.0 ** -100 <= s <= 2.0 ** 100:
+        return False
+    with np.errstate(over="ignore"):
+        b = ((c >> 1).astype(np.float32) + np.float32(0.5)) * s
+        down = b.astype(np.float16)
+    bits = down.view(np.uint16).astype(np.int32) - (down.astype(np.float32) > b) + (c & 1)
+    x = bits[bits < 0x7C00].astype(np.uint16).view(np.float16).astype(np.float32)
+    exact, r = np.minimum(np.rint(x / s), 127), int((np.float32(1) / s).view(np.uint32))
+    fma = lambda r: (x.astype(np.longdouble) * np.longdouble(np.uint32(r).view(np.float32)) + np.longdouble(12582912)).astype(np.float32)  # exact before it is rounded
+    return all((np.minimum(fma(r + d) - np.float32(12582912), 127) != exact).any() for d in (0, 1, -1))
+
+
 def _rows(M):
     m = np.arange(M)
     m = m[(m % 16 == 0) | (m % 16 == 15) | (m == M - 1)]
@@ -35,7 +55,8 @@ def _layer(g, X, packed, sw, b, M, N, K, scale, out, out_scale, gelu):
 @pytest.mark.parametrize("given", [False, True])
 def test_layer(g, force_kernel, M, K, N, dtype, given):
     force_kernel(5)
-    assert g.lib().gpusq_linear_int8_launches(g.F16 if dtype == np.float16 else g.F32, M, N, K, g.EPI_BIAS, int(given), 0) <= (1 if given else 2)
+    assert all(_is_wide(g, dtype, out, M, K, N, gelu) for out in (torch.float16, torch.int8) for gelu in (False, True))
+    assert g.lib().gpusq_linear_int8_launches(g.F16 if dtype == np.float16 else g.F32, M, N, K, g.EPI_BIAS, int(given), 0) == (1 if given else 2)
     rng = np.random.default_rng(M + K)
     X = (rng.standard_normal((M, K)) * 1.5).astype(dtype)
     if given:  # clamped, 0
@@ -60,37 +81,45 @@ def test_layer(g, force_kernel, M, K, N, dtype, given):
     check_gelu_codes(y[r].astype(np.int32), acc, float(s[0]), s_w, bias, so)
 
 
-# scales whose codes one fused multiply-add does not decide, or whose quotients leave the numbers: every fp16 value
+# scales whose codes one fused multiply-add does not decide (eight of them), or whose quotients leave the numbers: every fp16 value
 def test_codes(g, force_kernel):
     force_kernel(5)
     h = np.arange(0, 0x7C00, dtype=np.uint16).view(np.float16)
     X = np.concatenate([h, -h]).reshape(62, 1024)
     N, K = 16, 1024
+    assert _is_wide(g, np.float16, torch.float16, 62, K, N)
     _, s_w, vals, meta = _oracle_weights(synth.weights(N, K, seed=1))
     packed, sw, b = g.pack(dev(vals), dev(meta), K), dev(s_w), dev(synth.bias(N))
     rng = np.random.default_rng(3)
     scales = [np.float32(v) for v in (1.0, 1 / 3, 0.7, 3e-5, 5e-8, 511.5, 1e-38, 1e-45, 1e38, 0.0, np.inf, -0.25)]
     scales += [np.float32(np.float32(v) / np.float32(c + 0.5)) for v, c in zip(rng.uniform(0.5, 2.0, 40).astype(np.float16), rng.integers(0, 127, 40))]
+    assert sum(_refined(s) for s in scales) >= 4
     for s in scales:
         with np.errstate(all="ignore"):
             exp, _ = oracle.quantize_tensor_int8(X.astype(np.float32), scale=float(s))
         assert np.array_equal(_layer(g, dev(X), packed, sw, b, 62, N, K, dev(np.array([s], np.float32)), torch.float16, None, False)[1], exp), s
 
 
-# the scale of X's own range where X holds no, only tiny or not only numbers: as from the quantiser and the GEMM
+# the scale of X's own range where X holds no, only tiny or not only numbers, or where no reciprocal decides: as from the quantiser and the GEMM
 @pytest.mark.parametrize("dtype", [np.float16, np.float32])
-@pytest.mark.parametrize("kind", ["nan", "inf", "both", "zero", "tiny", "all nan"])
+@pytest.mark.parametrize("kind", ["nan", "inf", "both", "zero", "tiny", "all nan", "refined"])
 def test_own_range(g, force_kernel, dtype, kind):
     M, K, N = 130, 272, 80
     X = (np.random.default_rng(5).standard_normal((M, K)) * {"zero": 0, "tiny": 1e-7}.get(kind, 1)).astype(dtype)
     for v, k in ((np.nan, ("nan", "both")), (np.inf, ("inf", "both")), (-np.inf, ("both",))):
         if kind in k: X.reshape(-1)[np.random.default_rng(len(k)).integers(0, M * K, 50)] = v
     if kind == "all nan": X[:] = np.nan
+    if kind == "refined":  # a largest value whose scale is such a one, and values on its code boundaries
+        amax = next(v for v in np.arange(0x4400, 0x4800, dtype=np.uint16).view(np.float16) if _refined(np.float32(v) / np.float32(127)))
+        X = np.clip(X, -amax, amax).astype(dtype)
+        X[0, :128] = (amax / np.float32(127) * (np.arange(128, dtype=np.float32) - np.float32(0.5))).astype(np.float16)
+        X[0, 0] = amax
     _, s_w, vals, meta = _oracle_weights(synth.weights(N, K, seed=M, ids=(9,), sigma=0.05))
     packed, sw, b, x = g.pack(dev(vals), dev(meta), K), dev(s_w), dev(synth.bias(N, seed=M, ids=(10,))), dev(X)
     q, s = g.quantize_int8(x, g.PER_TENSOR)
     exp = host(g.spgemm_int8(q, packed, N, act_scale=s, w_scale=sw, bias=b))
     force_kernel(5)
+    assert _is_wide(g, dtype, torch.float16, M, K, N)
     y, codes, scale = _layer(g, x, packed, sw, b, M, N, K, None, torch.float16, None, False)
     assert np.array_equal(codes, host(q)) and np.array_equal(scale.view(np.uint32), host(s).view(np.uint32)) and np.array_equal(y, exp, equal_nan=True)
 
