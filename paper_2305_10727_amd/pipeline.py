@@ -210,8 +210,9 @@ class EncoderBlockLinears:
         self.fc1.act_scale = scales["h"]
         self.fc2.act_scale = scales["g"]
         self.fc2.Xq = self.fc1.Y  # fc2 reads the codes fc1's epilogue wrote: no pass in between
-        # few rows (the latency kernel): both qkv and fc1 quantise their fp16 input themselves, four launches per block, and nothing
-        # reads their codes, which are then not written; otherwise the one-call layer decides for each of them
+        # few rows (the latency kernel) in both qkv and fc1: what quantises its fp16 input in its GEMM (qkv, and fc1 behind a norm) writes
+        # no codes, which nothing would read, and a block is four launches; otherwise the one-call layer decides for each and writes
+        # them.  Without a norm fc1's codes come from proj, whatever this says.
         self.fold_quantise = self.qkv.takes_fp16_input() and self.fc1.takes_fp16_input()
         self.graph = None
 

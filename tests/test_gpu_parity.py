@@ -953,8 +953,8 @@ def test_encoder_block_chain_and_its_graph(g, M, D, hidden, seed, launches):
     y = host(blk.fc2.gemm(None, biases[3]))
     assert np.array_equal(host(blk.qkv.Xq), Xq) and np.array_equal(host(blk.qkv.Y), qkv)
     assert np.array_equal(host(blk.proj.Y).view(np.uint16), proj.view(np.uint16)) and np.array_equal(host(blk.fc1.Xq), hq)
-    # then the block: one-call layers for qkv and fc1, which leave the codes, and, where both quantise inside the GEMM, the form that
-    # writes none (four launches)
+    # then the block without a norm: a one-call layer for qkv, which leaves its codes, or, where both quantise inside the GEMM, the form
+    # that writes none; fc1's codes come from proj (four launches, five where qkv's quantiser stands apart)
     codes6, y6, folds = blk.fc1.Y.clone(), blk.fc2.Y.clone(), blk.fold_quantise
     assert folds == (launches == (1, 1))
     for blk.fold_quantise in (False, True) if folds else (False,):
@@ -987,6 +987,56 @@ def test_encoder_block_chain_and_its_graph(g, M, D, hidden, seed, launches):
         y_graph = blk.replay()
         torch.cuda.synchronize()
         assert torch.equal(y_graph, y_eager) and torch.equal(blk.fc1.Y, codes_eager)
+
+
+# few rows: qkv and fc1 quantise inside their GEMMs, qkv alone does, neither; many rows: the kernel for whole rows in both, in qkv alone
+@pytest.mark.parametrize("M,D,hidden,quantisers", [(197, 192, 768, (1, 1)), (197, 768, 3072, (1, 0)), (1576, 384, 1536, (0, 0)), (6304, 384, 1536, (2, 2)), (6304, 512, 2048, (2, 0))])
+def test_encoder_block_with_a_norm(g, M, D, hidden, quantisers):
+    """A norm between proj and fc1 (here: residual, then a scaling by rows): fc1 quantises what the norm returns.  Against every pass by itself and
+    the oracle's quantiser, with and without a buffer of codes where both forms exist, and as a graph."""
+    from paper_2305_10727_amd.pipeline import EncoderBlockLinears
+    f32, rng = np.float32, np.random.default_rng(M + D)
+    scales = {k: dev(np.array([v], f32)) for k, v in dict(x=4 / 127, qkv=0.03, attn=0.03, h=3 / 127, g=0.02).items()}
+    blk = EncoderBlockLinears(M, D, hidden, scales)
+    assert tuple(g.lib().gpusq_linear_int8_quantiser(g.F16, g.I8, l.M, l.N, l.K, l.epilogue, 0) for l in (blk.qkv, blk.fc1)) == quantisers
+    assert blk.fold_quantise == (quantisers == (1, 1))
+    blk.prepare_weights(*[dev(synth.weights(n, k, seed=M, ids=(i,), sigma=0.05)) for i, (n, k) in enumerate([(3 * D, D), (D, D), (hidden, D), (D, hidden)])])
+    biases = [dev(synth.bias(n, seed=M, ids=(4 + i,))) for i, n in enumerate((3 * D, D, hidden, D))]
+    gain = dev(rng.uniform(0.5, 2.0, (M, 1)).astype(np.float16))
+    x = torch.empty((M, D), dtype=torch.float16, device="cuda")
+    fill = lambda: x.copy_(dev(rng.standard_normal((M, D)).astype(np.float16)))
+    attention, norm = lambda q, out: out.copy_(q[:, 2 * D:]), lambda h: (h + x) * gain
+    outputs = lambda: tuple(t.clone() for t in (blk.qkv.Y, blk.proj.Y, blk.fc1.Y, blk.fc2.Y))
+
+    def apart():
+        blk.qkv.quantize_activations(x, static=True)
+        blk.qkv.gemm(None, biases[0], scales["qkv"])
+        attention(blk.qkv.Y, blk.proj.Xq)
+        h = norm(blk.proj.gemm(None, biases[1]))
+        blk.fc1.quantize_activations(h, static=True)
+        assert np.array_equal(host(blk.fc1.Xq), oracle.quantize_tensor_int8(host(h).astype(f32), scale=float(f32(3 / 127)))[0])
+        blk.fc1.gemm(None, biases[2], scales["g"])
+        blk.fc2.gemm(None, biases[3])
+        return outputs(), (blk.qkv.Xq.clone(), blk.fc1.Xq.clone())
+
+    fill()
+    exp, codes = apart()
+    for blk.fold_quantise in (False, True) if blk.fold_quantise else (False,):
+        for t in (blk.qkv.Xq, blk.fc1.Xq, blk.qkv.Y, blk.proj.Y, blk.fc1.Y, blk.fc2.Y):
+            t.zero_()
+        assert blk.forward(x, biases, attention, norm) is blk.fc2.Y
+        assert all(torch.equal(a, b) for a, b in zip(outputs(), exp))
+        assert blk.fold_quantise or (torch.equal(blk.qkv.Xq, codes[0]) and torch.equal(blk.fc1.Xq, codes[1]))
+    blk.capture(x, biases, attention, norm)
+    for _ in range(3):
+        fill()
+        exp, _ = apart()
+        for t in (blk.qkv.Y, blk.proj.Y, blk.fc1.Y, blk.fc2.Y):
+            t.zero_()
+        torch.cuda.synchronize()
+        blk.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(outputs(), exp))
 
 
 # ------------------------------------------------------------------------------------------------ INT4 pair-wise 4:8
