@@ -57,6 +57,28 @@ def test_codes_over_the_input(g, force_kernel, kernel, M, N, at):
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
 
 
+@pytest.mark.parametrize("kernel,M,K,N", [(4, 33, 144, 132), (0, 65, 192, 68), (1, 129, 128, 256), (2, 1111, 512, 272), (2, 700, 272, 260)])
+@pytest.mark.parametrize("scale", [0.0, -0.0, np.inf, -0.04, 1e-45, 1e-38, 3e38, np.nan])
+def test_scales_and_outputs_that_leave_the_numbers(g, force_kernel, kernel, M, K, N, scale):
+    """Zero, infinite, negative, denormal and no scales on outputs of which some are infinite and some are no numbers: the codes of the
+    oracle's quantiser, and the output of gpusq_spgemm_int8"""
+    force_kernel(kernel)
+    Xq = dev(np.random.default_rng(M).integers(-127, 128, (M, K)).astype(np.int8))
+    _, s_w, vals, meta = _oracle_weights(synth.weights(N, K, seed=M, ids=(1,)))
+    s_w[:8] = [np.nan, np.inf, -np.inf, 1e30, -1e30, 0.0, 1e-45, np.float32(6e-8)]
+    bias = synth.bias(N, seed=M, ids=(2,))
+    bias[8:12] = [np.nan, np.inf, -np.inf, 1e-40]
+    packed, sa, sw, b = g.pack(dev(vals), dev(meta), K), dev(np.array([0.02], np.float32)), dev(s_w), dev(bias)
+    y = g.spgemm_int8(Xq, packed, N, act_scale=sa, w_scale=sw, bias=b)
+    assert torch.isnan(y).any() and torch.isinf(y).any()
+    with np.errstate(all="ignore"):
+        codes, _ = oracle.quantize_tensor_int8(host(y).astype(np.float32), scale=scale)
+    Y, Yq = torch.full((M, N), 7.0, dtype=torch.float16, device="cuda"), torch.full((M, N), 99, dtype=torch.int8, device="cuda")
+    g.calls.gpusq_spgemm_int8_codes(Xq, packed, sa, sw, b, Y, Yq, dev(np.array([scale], np.float32)), M, N, K, g.EPI_BIAS)
+    assert np.array_equal(host(Y), host(y), equal_nan=True)
+    assert np.array_equal(host(Yq), codes)
+
+
 def test_infinite_outputs_and_refusals(g):
     """Outputs beyond fp16 and their codes; GELU is refused, and so is a missing scale."""
     M, K, N = 64, 128, 64

@@ -42,6 +42,50 @@ def test_images(g, force_kernel, kernel, B, C, H, W, D, dtype):
     assert np.array_equal(host(Y)[r].view(np.uint16), exp.view(np.uint16))
 
 
+def _both(g, img, packed, sw, b, Y, ws, D):
+    """(Y, codes, scale) of the one call into Y, and before it of the quantiser and the product apart"""
+    B, C, H, W = img.shape
+    q, s = g.quantize_int8(img.view(1, -1), g.PER_TENSOR)
+    exp = torch.empty((B * (H // 16) * (W // 16), D), dtype=torch.float16, device="cuda")
+    g.calls.gpusq_patch_embed16_int8(q, packed, s, sw, b, exp, B, C, H, W, D, g.EPI_BIAS)
+    img_q, sa = torch.full((B, C, H, W), 99, dtype=torch.int8, device="cuda"), torch.full((1,), 1e3, device="cuda")
+    g.calls.gpusq_patch_embed16_images(img, g._TORCH_DT[img.dtype], packed, sa, sw, b, Y, img_q, ws, B, C, H, W, D, g.EPI_BIAS)
+    return (exp, q.view(-1), s), (Y, img_q.view(-1), sa)
+
+
+# pixels that are no numbers, infinite, all zero, tiny; as the rules choose, the kernel for whole rows, the one for few rows, the tile kernel
+@pytest.mark.parametrize("B,C,H,W,D", [(64, 3, 224, 224, 768), (5, 3, 224, 224, 768), (64, 3, 224, 224, 1536)])
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("kind", ["nan", "inf", "both", "zero", "tiny", "all nan"])
+def test_pixels_that_leave_the_numbers(g, B, C, H, W, D, dtype, kind):
+    img = (_images(B, C, H, W, np.float32, B) * {"zero": 0, "tiny": 1e-7}.get(kind, 1)).astype(dtype)
+    for v, k in ((np.nan, ("nan", "both")), (np.inf, ("inf", "both")), (-np.inf, ("both",))):
+        if kind in k: img.reshape(-1)[np.random.default_rng(len(k)).integers(0, img.size, 500)] = v
+    if kind == "all nan": img[:] = np.nan
+    _, s_w, vals, meta = _oracle_weights(synth.weights(D, C * 256, seed=B, ids=(1,)))
+    Y, ws = torch.full((B * (H // 16) * (W // 16), D), 7.0, dtype=torch.float16, device="cuda"), torch.empty(4096, dtype=torch.uint8, device="cuda")
+    exp, got = _both(g, dev(img), g.pack(dev(vals), dev(meta), C * 256), dev(s_w), dev(synth.bias(D, seed=B)), Y, ws, D)
+    for e, t in zip(exp, got):
+        assert np.array_equal(host(e), host(t), equal_nan=e.dtype != torch.int8)
+
+
+# the tokens over the images, over their end and over the partial maxima of the range pass: as from buffers that lie apart
+@pytest.mark.parametrize("how", ["images", "end", "workspace"])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+def test_shared_operands(g, how, dtype):
+    B, C, H, W, D = 64, 3, 224, 224, 768
+    M, n = B * 196, B * C * H * W
+    _, s_w, vals, meta = _oracle_weights(synth.weights(D, C * 256, seed=B, ids=(1,)))
+    room = torch.empty(4 * n, dtype=torch.float16, device="cuda")
+    img = room.view(dtype)[:n].view(B, C, H, W)
+    img.copy_(dev(_images(B, C, H, W, np.float16, D)))
+    at = {"images": 0, "end": n * img.element_size() // 2 - 768, "workspace": 2 * n}[how]
+    Y = room[at:at + M * D].view(M, D)
+    ws = Y.view(-1).view(torch.uint8)[:4096] if how == "workspace" else torch.empty(4096, dtype=torch.uint8, device="cuda")
+    exp, got = _both(g, img, g.pack(dev(vals), dev(meta), C * 256), dev(s_w), dev(synth.bias(D, seed=B)), Y, ws, D)
+    assert all(torch.equal(e, t) for e, t in zip(exp, got))
+
+
 def test_refusals(g):
     B, C, H, W, D = 64, 3, 224, 224, 768
     img, Y = torch.zeros((B, C, H, W), dtype=torch.float16, device="cuda"), torch.empty((B * 196, D), dtype=torch.float16, device="cuda")
