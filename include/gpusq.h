@@ -237,11 +237,11 @@ gpusq_status gpusq_linear_int8(const void* X, gpusq_dtype x_dt, const void* Wpac
 int gpusq_linear_int8_launches(gpusq_dtype x_dt, int64_t M, int64_t N, int64_t K, int epilogue, int scale_is_input, int cus);
 /* What quantises the activations in that call, with the same reservation: GPUSQ_QUANTISE_APART, launches of its own; GPUSQ_QUANTISE_FEW_ROWS, the
  * GEMM kernel for few rows (gpusq_spgemm_int8_xf16 with that scale given then serves as well, without the codes);
- * GPUSQ_QUANTISE_WHOLE_ROWS, the one for many rows of few channels.  -1 for invalid sizes or types.  Host-side. */
+ * GPUSQ_QUANTISE_WHOLE_ROWS, the one for many rows of few channels (more layers under a given scale than with a range pass in front).  -1 for invalid sizes or types.  Host-side. */
 #define GPUSQ_QUANTISE_APART 0
 #define GPUSQ_QUANTISE_FEW_ROWS 1
 #define GPUSQ_QUANTISE_WHOLE_ROWS 2
-int gpusq_linear_int8_quantiser(gpusq_dtype x_dt, gpusq_dtype out_dt, int64_t M, int64_t N, int64_t K, int epilogue, int cus);
+int gpusq_linear_int8_quantiser(gpusq_dtype x_dt, gpusq_dtype out_dt, int64_t M, int64_t N, int64_t K, int epilogue, int scale_is_input, int cus);
 
 /* ---- patch embedding [Sec. 3.3: the patch-embedding layer is a convolution with C input channels, D_embed output
  * channels and kernel size = stride = P on images N x C x H x W, each P x P patch becoming one token; 2:4 sparsity is

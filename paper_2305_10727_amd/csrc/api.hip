@@ -395,9 +395,9 @@ int gpusq_linear_int8_launches(gpusq_dtype x_dt, int64_t M, int64_t N, int64_t K
   return layer_sizes(a, x_dt, GPUSQ_F16, M, N, K, epilogue) ? linear_int8_launches(a, x_dt, scale_is_input, cus) : 0;
 }
 
-int gpusq_linear_int8_quantiser(gpusq_dtype x_dt, gpusq_dtype out_dt, int64_t M, int64_t N, int64_t K, int epilogue, int cus) {
+int gpusq_linear_int8_quantiser(gpusq_dtype x_dt, gpusq_dtype out_dt, int64_t M, int64_t N, int64_t K, int epilogue, int scale_is_input, int cus) {
   GemmArgs a{};
-  return layer_sizes(a, x_dt, out_dt, M, N, K, epilogue) ? linear_int8_quantiser(a, x_dt, cus) : -1;
+  return layer_sizes(a, x_dt, out_dt, M, N, K, epilogue) ? linear_int8_quantiser(a, x_dt, scale_is_input, cus) : -1;
 }
 
 gpusq_status gpusq_gemm_fp16_dense(const void* X, const void* W, const float* bias, void* Y, int64_t M, int64_t N,

@@ -434,7 +434,7 @@ gpusq_status launch_wide(const GemmArgs& a, const WidePlan& p, hipStream_t s);
 // quantise (dt of X, workspace as for launch_quantize) and multiply: one, two or three launches
 gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, void* workspace, hipStream_t s);
 int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int cus);
-int linear_int8_quantiser(const GemmArgs& a, gpusq_dtype dt, int cus);
+int linear_int8_quantiser(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int cus);
 // the same for a patch embedding (GemmArgs::patch_P): images of dt, their codes
 gpusq_status launch_patch_embed_int8(GemmArgs a, gpusq_dtype dt, int8_t* img_q, float* scale, void* workspace, hipStream_t s);
 // the range pass of the per-tensor quantiser alone; returns the number of partial maxima it leaves in the workspace

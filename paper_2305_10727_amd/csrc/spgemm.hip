@@ -634,32 +634,44 @@ static gpusq_status launch_typed(const GemmArgs& a, hipStream_t s) {
 constexpr int64_t kRangeHereBytes = 128 * 1024;
 
 // Many rows and few channels: the kernel that quantises whole rows (wide.hip) by the estimates, from 2048 rows on (below, there is little to win
-// and the estimates are off by as much) and up to the two column blocks of 1536 channels that were timed.  Of 2448 sizes it takes some 60 % of the
-// fp16 ones, 1.19 times as fast there, and half of the fp32 ones, 1.12 times; 2 % of all are 3 % slower or more (30706 x 2256 -> 256
-// 73.6 -> 81.6 us, 19429 x 3312 -> 192 71.5 -> 77.0).  14070 x 576 -> 256 16.8 -> 10.1, 12609 x 768 -> 768 23.6 -> 19.6, 7029 x 1152 -> 256 20.6 -> 14.9, 56475 x 3648
-// -> 704 236.7 -> 194.3; not 25216 x 3072 -> 768, 103 / 110, nor 28453 x 1600 -> 1920 + GELU, 116.9 / 120.6.  Where the product goes to the kernel for few
-// rows (those have no estimate here) it is ahead beyond 256 channels at every K (46 sizes, 1.22 times), level below.
-static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, int resident, const Decision& d, WidePlan& p) {
+// and the estimates are off by as much) and up to the two column blocks of 1536 channels that were timed.  Calls in turn on three buffers of normal
+// values, us, apart / here, own range and given scale: 14070 x 576 -> 256 16.3 / 14.2 and 12.8 / 10.0, 12608 x 768 -> 768 20.6 / 20.0 and 17.1 / 15.1, 7029 x 1152
+// -> 256 17.0 / 15.0 and 13.5 / 10.9, 56475 x 3648 -> 704 306 / 266 and 235 / 187, 25216 x 3072 -> 768 106.7 / 107.5 and 86.5 / 83.9 (of what a GELU returns, which
+// takes less power, with an own range 102.5 / 100.3).  Behind a range pass there is less to win (quantiser_behind_range_us), with fp32 rows least,
+// and these go there under a given scale only: 54412 x 1744 -> 256 112.4 / 113.6 and 89.0 / 79.1, 30706 x 2256 -> 256 80.8 / 84.4 and 65.5 / 58.3, 19429 x 3312
+// -> 192 78.3 / 80.7 and 62.8 / 58.1, 12609 x 768 -> 768 fp32 24.7 / 25.7 and 19.7 / 18.3, 20738 x 3072 -> 704 + GELU 86.9 / 95.0 (and 70.5 / 75.9); not 28453 x 1600
+// -> 1920 + GELU 113 / 114.  The ratio of the estimates is off by 10 % (one standard deviation), hence the margins.  Of 14022 sizes so timed (M 2048 ... 65792, K
+// 64 ... 5120, N 32 ... 1536, both types and outputs, with and without GELU) it takes 61 % of the fp16 ones with an own range, 1.16 times as fast there, and 70 %
+// under a given scale, 1.23 times; 36 and 58 % of the fp32 ones, 1.09 and 1.20 times.  0.8 % of what it takes are slower by more than 5 % (8094 x 4608
+// -> 768 + GELU, int8 output, 59.3 / 66.5; under a given scale most of them two column blocks of more than 50000 rows: 52052 x 640 -> 1440 67.5 / 79.3).
+// Where the product goes to the kernel for few rows (those have no estimate here) it is ahead beyond 256 channels up to 12 K steps (1.1 to 1.3
+// times), with more of them by 5 % with an own range, or behind, and by 15 under a given scale.
+static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, bool given, int resident, const Decision& d, WidePlan& p) {
   const bool fp32 = dt == GPUSQ_F32, i8 = a.out_dt == GPUSQ_I8, gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
   if ((d.forced >= 0 && d.forced != 5) || (!i8 && a.out_dt != GPUSQ_F16) || a.N % 16 != 0) return false;
   if ((int64_t)a.K * 64 * 4 >= ((int64_t)1 << 31) || a.N >= (1 << 24)) return false;  // 32-bit lane offsets inside a chunk's rows
   if (d.forced < 0 && (a.M < GPUSQ_WIDE_MIN_ROWS || a.N > 2 * kWideBlocks * kRowBlock)) return false;
   p = wide_plan(a.M, a.N, resident, fp32);
   if (p.chunks == 0 || d.forced == 5) return p.chunks > 0;
-  if (d.choice == 4) return a.N > 256;
-  // (a long K is estimated 8 % short)
-  const double margin = a.K > 24 * kStepBytes ? 0.9 : (fp32 ? 0.92 : 0.97);
-  return d.gemm_us > 0 && wide_us(p, a.M, a.N, a.K, resident, fp32, gelu, i8) < margin * quantise_and_gemm_us(d.gemm_us, a.M, a.N, a.K, fp32, i8);
+  if (d.choice == 4) return a.N > 256 && (given || a.K <= 12 * kStepBytes);
+  if (d.gemm_us <= 0) return false;
+  double apart = quantise_and_gemm_us(d.gemm_us, a.M, a.N, a.K, fp32, i8), margin = fp32 ? 0.92 : 0.97;
+  if (!given) {
+    apart -= quantiser_behind_range_us(a.M, a.K, fp32) + (d.choice == 3 ? 0.09 * d.gemm_us : 0.0);  // (kernel 3: chosen where it is ahead of the estimate)
+    margin = a.N <= kRowBlock && a.K <= 3 * kStepBytes ? 0.8 : (fp32 ? 0.9 : 0.97);
+  }
+  if (a.K > 24 * kStepBytes && margin > 0.9) margin = 0.9;  // (a long K is estimated 8 % short)
+  return wide_us(p, a.M, a.N, a.K, resident, fp32, gelu, i8) < margin * apart;
 }
 
 // What quantises (GPUSQ_QUANTISE_*); WHOLE_ROWS: with this plan
-static int quantiser_of(const GemmArgs& a, gpusq_dtype dt, int resident, WidePlan& p) {
+static int quantiser_of(const GemmArgs& a, gpusq_dtype dt, bool given, int resident, WidePlan& p) {
   const bool gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
   const bool few = fewrows_folds_quantiser(a.M, a.N, a.K, resident, dt == GPUSQ_F32) && fewrows_supports(a);
   const Decision& d = decide(true, a.M, a.N, a.K, gelu, resident, false);
-  if (d.forced == 5 && wide_takes(a, dt, resident, d, p)) return GPUSQ_QUANTISE_WHOLE_ROWS;
+  if (d.forced == 5 && wide_takes(a, dt, given, resident, d, p)) return GPUSQ_QUANTISE_WHOLE_ROWS;
   if (few && d.choice == 4) return GPUSQ_QUANTISE_FEW_ROWS;
-  return wide_takes(a, dt, resident, d, p) ? GPUSQ_QUANTISE_WHOLE_ROWS : GPUSQ_QUANTISE_APART;
+  return wide_takes(a, dt, given, resident, d, p) ? GPUSQ_QUANTISE_WHOLE_ROWS : GPUSQ_QUANTISE_APART;
 }
 
 // 1 + the launches in front of the GEMM's own
@@ -671,17 +683,17 @@ static int launches_of(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, in
 
 int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int cus) {
   WidePlan p;
-  return launches_of(a, dt, scale_is_input, quantiser_of(a, dt, cus > 0 ? cus : num_cus(), p));
+  return launches_of(a, dt, scale_is_input, quantiser_of(a, dt, scale_is_input != 0, cus > 0 ? cus : num_cus(), p));
 }
-int linear_int8_quantiser(const GemmArgs& a, gpusq_dtype dt, int cus) {
+int linear_int8_quantiser(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int cus) {
   WidePlan p;
-  return quantiser_of(a, dt, cus > 0 ? cus : num_cus(), p);
+  return quantiser_of(a, dt, scale_is_input != 0, cus > 0 ? cus : num_cus(), p);
 }
 
 gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, void* workspace, hipStream_t s) {
   const int resident = num_cus();
   WidePlan plan;
-  const int quantiser = quantiser_of(a, dt, resident, plan), launches = launches_of(a, dt, scale_is_input, quantiser);
+  const int quantiser = quantiser_of(a, dt, scale_is_input != 0, resident, plan), launches = launches_of(a, dt, scale_is_input, quantiser);
   a.act_scale = scale;
   const int64_t range_bytes = launches == 2 ? (int64_t)gpusq_quantize_workspace_bytes(GPUSQ_PER_TENSOR, a.M, a.K) : 0;
   const bool apart = may_quantise_inside(a.X, dtype_bytes(dt), a.Y, dtype_bytes(a.out_dt), a.M, a.N, a.K, scale, scale_is_input != 0, a.out_scale,
@@ -713,7 +725,7 @@ gpusq_status launch_patch_embed_int8(GemmArgs a, gpusq_dtype dt, int8_t* img_q, 
   const int64_t pixels = (int64_t)a.M * a.K;
   a.act_scale = scale;
   WidePlan plan;
-  const bool wide = pixels * dtype_bytes(dt) < ((int64_t)1 << 32) && wide_takes(a, dt, resident, decide(true, a.M, a.N, a.K, false, resident, false), plan) &&
+  const bool wide = pixels * dtype_bytes(dt) < ((int64_t)1 << 32) && wide_takes(a, dt, false, resident, decide(true, a.M, a.N, a.K, false, resident, false), plan) &&
                     may_quantise_inside(a.X, dtype_bytes(dt), a.Y, 2, a.M, a.N, a.K, scale, false, nullptr, workspace,
                                         (int64_t)gpusq_quantize_workspace_bytes(GPUSQ_PER_TENSOR, 1, pixels));
   if (wide) {

@@ -88,5 +88,13 @@ inline double quantise_and_gemm_us(double gemm_us, int64_t M, int64_t N, int64_t
   const double pass = 2.2 + (double)M * K * (fp32 ? 5 : 3) / 5.83e6;
   return 1.3 + (pass > 2.8 ? pass : 2.8) + 0.9 * gemm_us + (int8_out ? 0.48e-7 * M * N : 0.0);
 }
+// Behind a range pass the quantiser is faster than those estimates (of a given scale) say: what the range pass read last it finds in the L2s, or X
+// in the last level cache, which the kernel for whole rows, bound by more than X, gains little from.  Medians of 4008 sizes, us, of X in MB
+// (of the difference that the range makes to the one, less what it makes to the other): fp16 4-12 0.3, 16-32 1.0, 48-120 -1 to 1, 130-280 5 to 10; fp32 6-12 1.2, 24-32
+// 2.4, 32-120 2.7 to 4, 120-200 4 to 5, 220-280 11, beyond 16.
+inline double quantiser_behind_range_us(int64_t M, int64_t K, bool fp32) {
+  const double mb = (double)M * K * (fp32 ? 4e-6 : 2e-6), l2 = mb < 32 ? mb : 32;
+  return fp32 ? 0.08 * l2 + (mb > 220 ? 8.0 : 0.0) : 0.03 * l2 + (mb > 120 ? 6.5 : 0.0);
+}
 
 }  // namespace gpusq

@@ -136,7 +136,7 @@ def lib():
         L.gpusq_linear_int8.restype = ci
         L.gpusq_linear_int8_launches.argtypes = [ci, i64, i64, i64, ci, ci, ci]
         L.gpusq_linear_int8_launches.restype = ci
-        L.gpusq_linear_int8_quantiser.argtypes = [ci, ci, i64, i64, i64, ci, ci]
+        L.gpusq_linear_int8_quantiser.argtypes = [ci, ci, i64, i64, i64, ci, ci, ci]
         L.gpusq_linear_int8_quantiser.restype = ci
         L.gpusq_gemm_fp16_dense.argtypes = [vp, vp, vp, vp, i64, i64, i64, ci, vp]
         L.gpusq_gemm_int8_dense.argtypes = [vp, vp, vp, vp, vp, vp, ci, vp, i64, i64, i64, ci, vp]

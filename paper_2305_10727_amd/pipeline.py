@@ -92,7 +92,7 @@ class SparseLinear:
         is not too long, as the library's one-call layer decides it (one launch instead of two).  Not where that call takes its
         kernel for many rows: the GEMM alone does not."""
         return self.precision == "int8" and G.lib().gpusq_linear_int8_quantiser(
-            G.F16, G._TORCH_DT[self.out_dtype], self.M, self.N, self.K, self.epilogue, 0) == G.QUANTISE_FEW_ROWS
+            G.F16, G._TORCH_DT[self.out_dtype], self.M, self.N, self.K, self.epilogue, 1, 0) == G.QUANTISE_FEW_ROWS
 
     def gemm_from_f16(self, X, bias, out_scale=None):
         """INT8 path with a static act_scale: quantise + GEMM in one launch (see takes_fp16_input)"""

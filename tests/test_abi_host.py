@@ -243,9 +243,9 @@ def test_force_kernel_override_is_an_explicit_call(lib):
         assert lib.gpusq_force_kernel(5) == 3
         for M, N, K in ((1, 16, 16), (130, 80, 272), (62, 16, 1024), (17, 768, 384), (2048, 64, 256), (12608, 3072, 768)):
             for x_dt in (0, 1):
-                assert lib.gpusq_linear_int8_quantiser(x_dt, 1, ctypes.c_int64(M), ctypes.c_int64(N), ctypes.c_int64(K), 0, 256) == 2
+                assert lib.gpusq_linear_int8_quantiser(x_dt, 1, ctypes.c_int64(M), ctypes.c_int64(N), ctypes.c_int64(K), 0, 0, 256) == 2
                 assert lib.gpusq_linear_int8_launches(x_dt, ctypes.c_int64(M), ctypes.c_int64(N), ctypes.c_int64(K), 0, 0, 256) == 2
-        assert lib.gpusq_linear_int8_quantiser(1, 1, ctypes.c_int64(130), ctypes.c_int64(84), ctypes.c_int64(272), 0, 256) == 1  # N % 16
+        assert lib.gpusq_linear_int8_quantiser(1, 1, ctypes.c_int64(130), ctypes.c_int64(84), ctypes.c_int64(272), 0, 0, 256) == 1  # N % 16
         assert _plan(lib, I8, 12608, 3072, 768, 0, 256)[1][0] == 2
         assert lib.gpusq_force_kernel(3) == 5
         assert lib.gpusq_force_kernel(7) == 3                      # anything else clears the override
@@ -318,16 +318,33 @@ def test_layers_whose_gemm_takes_fp16_activations(M, K, N, takes):
         assert gpusq.lib().gpusq_linear_int8_launches(gpusq.F16, M, N, K, gpusq.EPI_BIAS, 1, 256) == 1
 
 
+@pytest.mark.parametrize("M,K,N,gelu,x_dt,out_dt,own,given", [
+    # timed with the kernel for whole rows and without: slower with an own range; with either; faster with either
+    (54412, 1744, 256, False, 1, 1, 0, 2), (30706, 2256, 256, False, 1, 1, 0, 2), (19429, 3312, 192, False, 1, 1, 0, 2), (20738, 3072, 704, True, 1, 1, 0, 2),
+    (28758, 2960, 16, False, 1, 2, 0, 2), (26920, 2672, 64, True, 1, 1, 0, 2), (32855, 256, 32, False, 0, 2, 0, 2), (12609, 768, 768, False, 0, 1, 0, 2),
+    (22807, 256, 128, True, 0, 2, 0, 2), (29239, 176, 64, True, 0, 1, 0, 2), (11620, 2304, 1056, False, 0, 1, 0, 2), (2164, 1920, 448, True, 1, 2, 0, 2),
+    (12544, 512, 1536, False, 1, 2, 0, 2), (12066, 768, 1280, False, 1, 2, 0, 2), (28453, 1600, 1920, True, 1, 1, 0, 0), (12544, 768, 768, False, 1, 1, 2, 2), (25216, 3072, 768, False, 1, 1, 2, 2),
+    (14070, 576, 256, False, 1, 1, 2, 2), (7029, 1152, 256, False, 1, 1, 2, 2), (56475, 3648, 704, False, 1, 1, 2, 2), (50432, 192, 192, False, 1, 1, 2, 2)])
+def test_layers_of_the_kernel_for_whole_rows(lib, M, K, N, gelu, x_dt, out_dt, own, given):
+    f = lib.gpusq_linear_int8_quantiser
+    f.argtypes = [ctypes.c_int, ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int] * 3
+    assert (f(x_dt, out_dt, M, N, K, 3 if gelu else 1, 0, 256), f(x_dt, out_dt, M, N, K, 3 if gelu else 1, 1, 256)) == (own, given)
+    if out_dt == 1:
+        launches = lib.gpusq_linear_int8_launches
+        launches.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int] * 3
+        assert launches(x_dt, M, N, K, 3 if gelu else 1, 0, 256) == (3 if own == 0 else 2) and launches(x_dt, M, N, K, 3 if gelu else 1, 1, 256) == (2 if given == 0 else 1)
+
+
 def test_what_quantises_a_layer(lib):
     """The answers of gpusq_linear_int8_quantiser and gpusq_linear_int8_launches agree; int32 output has no kernel for whole rows"""
     f = lib.gpusq_linear_int8_quantiser
-    f.argtypes = [ctypes.c_int, ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int] * 2
+    f.argtypes = [ctypes.c_int, ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int] * 3
     launches = lib.gpusq_linear_int8_launches
     launches.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int] * 3
     F32, F16, I8, I32 = range(4)
     for x_dt in (F32, F16):
         for M, N, K, what in ((197, 768, 768, 1), (1576, 1152, 384, 0), (12608, 768, 768, 2), (12608, 3072, 768, 0)):
-            assert f(x_dt, F16, M, N, K, 1, 256) == what
+            assert f(x_dt, F16, M, N, K, 1, 1, 256) == what
             assert launches(x_dt, M, N, K, 1, 1, 256) == (2 if what == 0 else 1)
-        assert f(x_dt, I32, 12608, 768, 768, 1, 256) == 0 and f(x_dt, I8, 12608, 768, 768, 1, 256) == 2
-    assert f(I8, F16, 197, 768, 768, 0, 256) == f(F16, F32, 197, 768, 768, 0, 256) == f(F16, F16, 197, 768, 100, 0, 256) == f(F16, F16, 0, 768, 768, 0, 256) == -1
+        assert f(x_dt, I32, 12608, 768, 768, 1, 1, 256) == 0 and f(x_dt, I8, 12608, 768, 768, 1, 1, 256) == 2
+    assert f(I8, F16, 197, 768, 768, 0, 1, 256) == f(F16, F32, 197, 768, 768, 0, 1, 256) == f(F16, F16, 197, 768, 100, 0, 1, 256) == f(F16, F16, 0, 768, 768, 0, 1, 256) == -1

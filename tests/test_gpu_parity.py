@@ -998,7 +998,7 @@ def test_encoder_block_with_a_norm(g, M, D, hidden, quantisers):
     f32, rng = np.float32, np.random.default_rng(M + D)
     scales = {k: dev(np.array([v], f32)) for k, v in dict(x=4 / 127, qkv=0.03, attn=0.03, h=3 / 127, g=0.02).items()}
     blk = EncoderBlockLinears(M, D, hidden, scales)
-    assert tuple(g.lib().gpusq_linear_int8_quantiser(g.F16, g.I8, l.M, l.N, l.K, l.epilogue, 0) for l in (blk.qkv, blk.fc1)) == quantisers
+    assert tuple(g.lib().gpusq_linear_int8_quantiser(g.F16, g.I8, l.M, l.N, l.K, l.epilogue, 1, 0) for l in (blk.qkv, blk.fc1)) == quantisers
     assert blk.fold_quantise == (quantisers == (1, 1))
     blk.prepare_weights(*[dev(synth.weights(n, k, seed=M, ids=(i,), sigma=0.05)) for i, (n, k) in enumerate([(3 * D, D), (D, D), (hidden, D), (D, hidden)])])
     biases = [dev(synth.bias(n, seed=M, ids=(4 + i,))) for i, n in enumerate((3 * D, D, hidden, D))]

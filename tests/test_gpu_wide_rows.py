@@ -18,7 +18,7 @@ SHAPES = [(1, 16, 16), (15, 128, 64), (16, 144, 80), (17, 384, 768), (4096, 512,
 
 
 def _is_wide(g, dtype, out, M, K, N, gelu=False):
-    return g.lib().gpusq_linear_int8_quantiser(g.F16 if dtype == np.float16 else g.F32, g._TORCH_DT[out], M, N, K, g.EPI_GELU if gelu else 0, 0) == g.QUANTISE_WHOLE_ROWS
+    return g.lib().gpusq_linear_int8_quantiser(g.F16 if dtype == np.float16 else g.F32, g._TORCH_DT[out], M, N, K, g.EPI_GELU if gelu else 0, 0, 0) == g.QUANTISE_WHOLE_ROWS
 
 
 def _refined(s):
