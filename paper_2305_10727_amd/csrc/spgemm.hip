@@ -646,17 +646,17 @@ constexpr int64_t kRangeHereBytes = 128 * 1024;
 // -> 768 + GELU, int8 output, 59.3 / 66.5; under a given scale most of them two column blocks of more than 50000 rows: 52052 x 640 -> 1440 67.5 / 79.3).
 // Where the product goes to the kernel for few rows (those have no estimate here) it is ahead beyond 256 channels up to 12 K steps (1.1 to 1.3
 // times), with more of them by 5 % with an own range, or behind, and by 15 under a given scale.
-static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, bool given, int resident, const Decision& d, WidePlan& p) {
+static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, bool behind_range, int resident, const Decision& d, WidePlan& p) {
   const bool fp32 = dt == GPUSQ_F32, i8 = a.out_dt == GPUSQ_I8, gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
   if ((d.forced >= 0 && d.forced != 5) || (!i8 && a.out_dt != GPUSQ_F16) || a.N % 16 != 0) return false;
   if ((int64_t)a.K * 64 * 4 >= ((int64_t)1 << 31) || a.N >= (1 << 24)) return false;  // 32-bit lane offsets inside a chunk's rows
   if (d.forced < 0 && (a.M < GPUSQ_WIDE_MIN_ROWS || a.N > 2 * kWideBlocks * kRowBlock)) return false;
   p = wide_plan(a.M, a.N, resident, fp32);
   if (p.chunks == 0 || d.forced == 5) return p.chunks > 0;
-  if (d.choice == 4) return a.N > 256 && (given || a.K <= 12 * kStepBytes);
+  if (d.choice == 4) return a.N > 256 && (!behind_range || a.K <= 12 * kStepBytes);
   if (d.gemm_us <= 0) return false;
   double apart = quantise_and_gemm_us(d.gemm_us, a.M, a.N, a.K, fp32, i8), margin = fp32 ? 0.92 : 0.97;
-  if (!given) {
+  if (behind_range) {
     apart -= quantiser_behind_range_us(a.M, a.K, fp32) + (d.choice == 3 ? 0.09 * d.gemm_us : 0.0);  // (kernel 3: chosen where it is ahead of the estimate)
     margin = a.N <= kRowBlock && a.K <= 3 * kStepBytes ? 0.8 : (fp32 ? 0.9 : 0.97);
   }
@@ -669,9 +669,9 @@ static int quantiser_of(const GemmArgs& a, gpusq_dtype dt, bool given, int resid
   const bool gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
   const bool few = fewrows_folds_quantiser(a.M, a.N, a.K, resident, dt == GPUSQ_F32) && fewrows_supports(a);
   const Decision& d = decide(true, a.M, a.N, a.K, gelu, resident, false);
-  if (d.forced == 5 && wide_takes(a, dt, given, resident, d, p)) return GPUSQ_QUANTISE_WHOLE_ROWS;
+  if (d.forced == 5 && wide_takes(a, dt, !given, resident, d, p)) return GPUSQ_QUANTISE_WHOLE_ROWS;
   if (few && d.choice == 4) return GPUSQ_QUANTISE_FEW_ROWS;
-  return wide_takes(a, dt, given, resident, d, p) ? GPUSQ_QUANTISE_WHOLE_ROWS : GPUSQ_QUANTISE_APART;
+  return wide_takes(a, dt, !given, resident, d, p) ? GPUSQ_QUANTISE_WHOLE_ROWS : GPUSQ_QUANTISE_APART;
 }
 
 // 1 + the launches in front of the GEMM's own
@@ -717,7 +717,10 @@ gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* s
   return launch_typed<true>(a, s);
 }
 
-// The images in front of a patch embedding: the kernel for whole rows takes a product of its sizes as it takes a layer's.
+// The images in front of a patch embedding: the kernel for whole rows takes a product of its sizes as it takes a layer's under a given scale.  A
+// range pass does come first, but the kernels that gather patches take longer than a layer's, which makes up for it.  Of 403 sizes timed (72 to
+// 576 patches an image, 256 to 1024 values each, 192 to 1536 channels) it takes 238 of fp16, 1.19 times as fast, none slower, and 101 of fp32, 1.06 times, 8 %
+// slower at the most (29120 x 256 -> 1088); the rule for a layer behind a range pass would not take 62 fp32 images of 304 x 304 -> 704, 41.2 / 37.4.
 gpusq_status launch_patch_embed_int8(GemmArgs a, gpusq_dtype dt, int8_t* img_q, float* scale, void* workspace, hipStream_t s) {
   const int resident = num_cus();
   const int choice = decide(true, a.M, a.N, a.K, false, resident, true).choice;
