@@ -13,8 +13,10 @@
 // A K step of 64 rows and 768 channels brings 61 KB of weights and 16 KB of X into the CU (1200 clocks at 64 bytes a clock), its matrix
 // instructions take 790 clocks: bound by memory (X in, codes and Y out) as long as a chunk has enough K steps.  In the kernel (12608 rows of 768,
 // clocks): 6000 until the first codes (range, constants, HBM), six steps of 1900 to 2000, 2900 for the epilogue.
-// The layer in us, the quantiser and the GEMM one after the other against this (fp16 X and Y, own range, three buffers in turn):
-//   14070 x 576 -> 256  16.8 / 10.1     12608 x 768 -> 768  23.6 / 19.5     7029 x 1152 -> 256  20.6 / 14.9     50432 x 192 -> 192  17.8 here
+// The layer in us, the quantiser and the GEMM one after the other against this (fp16 X and Y, normal values, calls in turn on three buffers; cards
+// differ by 3 %), own range and given scale:
+//   14070 x 576 -> 256  16.3 / 14.2, 12.8 / 10.0     12608 x 768 -> 768  20.6 / 20.0, 17.1 / 15.1     7029 x 1152 -> 256  17.0 / 15.0, 13.5 / 10.9
+//   50432 x 192 -> 192  18.9 / 17.4, 15.5 / 13.2     25216 x 3072 -> 768  106.7 / 107.5, 86.5 / 83.9 (GELU's output, own range: 102.5 / 100.3)
 #include <type_traits>
 
 #include "tile_common.h"
@@ -162,8 +164,10 @@ __global__ void __launch_bounds__(64 * kWideWaves) spgemm_wide_kernel(const Gemm
 
     // where this lane's codes lie in a buffer: row-major, 16-byte chunk c of row r at c ^ ((r >> 1) & 7)
     const uint32_t ring_off = (uint32_t)(row * kStepBytes + (((code >> 4) ^ ((row >> 1) & 7)) << 4) + (code & 15));
-    // The codes go past the caches (nothing here reads them again) where a step's are whole 128-byte lines; in parts of lines they are left to
-    // the L2 to put together: 28919 x 2256 -> 128 under a given scale 46.3 us, 75.5 past the caches (the quantiser and the GEMM one after the other: 50.0).
+    // The codes go past the caches (nothing here reads them again) where a step's are whole 128-byte lines; rows that start inside a line are
+    // left to the L2 to put together: 28919 x 2256 -> 128 under a given scale 52.5 us, 75.6 past the caches (the quantiser and the GEMM one after the other: 62.7).
+    // Those of images are pieces of 32 or 64 bytes along a row of pixels, whose lines are whole a few instructions later: either way is as fast (123
+    // sizes, 0.1 % on average, 3 % at the most).
     auto store_codes = [&](auto v, auto* at) __attribute__((always_inline)) {
       if (tail == 0)
         __builtin_nontemporal_store(v, at);
@@ -176,8 +180,8 @@ __global__ void __launch_bounds__(64 * kWideWaves) spgemm_wide_kernel(const Gemm
     uint32_t slot = 0;
     // One step: its rows have landed when no more than the copies and stores requested behind them are in flight.
     // MODE (fp16): 0 the scale of X's own range and one fused multiply-add a value (the code of a NaN is 0 as it is: its low byte), 1 a given
-    // scale, 2 products that are refined.  Loops of their own, with no question per step: 50432 x 192 -> 192 18.9 -> 17.9 us, under a given scale
-    // 14.2 -> 13.4; 12608 x 768 -> 768 20.6 -> 20.3, 15.5 -> 15.0 (with the first step alone requested in front of the scale's barrier).
+    // scale, 2 products that are refined.  Loops of their own, with no question per step, and the first step alone requested in front of the
+    // scale's barrier, before -> after on one card: 50432 x 192 -> 192 18.9 -> 17.9 us, under a given scale 14.2 -> 13.4; 12608 x 768 -> 768 -0.3, -0.5 us.
     auto produce = [&](auto write, auto mode, bool first, uint8_t* dst) __attribute__((always_inline)) {
       constexpr bool WRITE = decltype(write)::value;
       constexpr int MODE = decltype(mode)::value;

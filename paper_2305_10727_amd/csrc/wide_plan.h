@@ -73,7 +73,7 @@ inline WidePlan wide_plan(int64_t M, int64_t N, int resident, bool fp32) {
 
 // Run time in microseconds of that kernel, without the range pass, and of the quantiser and a GEMM of `gemm_us` behind it: fitted to 2448 sizes
 // timed on MI355X (M 2048 ... 65792, K 64 ... 5120, N 64 ... 1536, fp16 and fp32, both outputs, with and without GELU, three buffers in turn; 9 % and
-// 8 %).  A K step of the former is a chain of 0.4 us, or what its operands take on their way into the CU and its codes in the vector units,
+// 8 %, on 14022 others 10 % and 10 %).  A K step of the former is a chain of 0.4 us, or what its operands take on their way into the CU and its codes in the vector units,
 // shared by the workgroups on a CU.
 inline double wide_us(const WidePlan& p, int64_t M, int64_t N, int64_t K, int resident, bool fp32, bool gelu, bool int8_out) {
   const int slabs = wide_slabs(p), lanes = 8 * p.lanes_xcd;
