@@ -637,15 +637,14 @@ constexpr int64_t kRangeHereBytes = 128 * 1024;
 // and the estimates are off by as much) and up to the two column blocks of 1536 channels that were timed.  Calls in turn on three buffers of normal
 // values, us, apart / here, own range and given scale: 14070 x 576 -> 256 16.3 / 14.2 and 12.8 / 10.0, 12608 x 768 -> 768 20.6 / 20.0 and 17.1 / 15.1, 7029 x 1152
 // -> 256 17.0 / 15.0 and 13.5 / 10.9, 56475 x 3648 -> 704 306 / 266 and 235 / 187, 25216 x 3072 -> 768 106.7 / 107.5 and 86.5 / 83.9 (of what a GELU returns, which
-// takes less power, with an own range 102.5 / 100.3).  Behind a range pass there is less to win (quantiser_behind_range_us), with fp32 rows least,
-// and these go there under a given scale only: 54412 x 1744 -> 256 112.4 / 113.6 and 89.0 / 79.1, 30706 x 2256 -> 256 80.8 / 84.4 and 65.5 / 58.3, 19429 x 3312
-// -> 192 78.3 / 80.7 and 62.8 / 58.1, 12609 x 768 -> 768 fp32 24.7 / 25.7 and 19.7 / 18.3, 20738 x 3072 -> 704 + GELU 86.9 / 95.0 (and 70.5 / 75.9); not 28453 x 1600
-// -> 1920 + GELU 113 / 114.  The ratio of the estimates is off by 10 % (one standard deviation), hence the margins.  Of 14022 sizes so timed (M 2048 ... 65792, K
-// 64 ... 5120, N 32 ... 1536, both types and outputs, with and without GELU) it takes 61 % of the fp16 ones with an own range, 1.16 times as fast there, and 70 %
-// under a given scale, 1.23 times; 36 and 58 % of the fp32 ones, 1.09 and 1.20 times.  0.8 % of what it takes are slower by more than 5 % (8094 x 4608
-// -> 768 + GELU, int8 output, 59.3 / 66.5; under a given scale most of them two column blocks of more than 50000 rows: 52052 x 640 -> 1440 67.5 / 79.3).
-// Where the product goes to the kernel for few rows (those have no estimate here) it is ahead beyond 256 channels up to 12 K steps (1.1 to 1.3
-// times), with more of them by 5 % with an own range, or behind, and by 15 under a given scale.
+// takes less power, with an own range 102.5 / 100.3).  Behind a range pass there is less to win (wide_margin_behind_range), and these go there
+// under a given scale only: 30706 x 2256 -> 256 80.8 / 84.4 and 65.5 / 58.3, 19429 x 3312 -> 192 78.3 / 80.7 and 62.8 / 58.1, 20738 x 3072 -> 704 + GELU 86.9 / 95.0 (and
+// 70.5 / 75.9), 22807 x 256 -> 128 fp32 + GELU, int8 output 16.0 / 18.4 (and 12.5 / 13.0), 11620 x 2304 -> 1056 fp32 61.2 / 66.3; not 28453 x 1600 -> 1920 + GELU 113 / 114.  Of
+// 20022 sizes so timed (M 2048 ... 65792, K 64 ... 5120, N 32 ... 1536, both types and outputs, with and without GELU) it takes 68 % of the fp16 ones with an
+// own range, 1.15 times as fast there, and 70 % under a given scale, 1.22 times; 49 and 58 % of the fp32 ones, 1.08 and 1.20 times.  2 % of those with an own range
+// and 0.7 % of the others are slower by more than 5 % (8094 x 4608 -> 768 + GELU, int8 output, 59.3 / 66.5; 52052 x 640 -> 1440 under a given scale 67.5 / 79.3).
+// Where the product goes to the kernel for few rows (those have no estimate here) it is ahead beyond 256 channels: 1.1 to 1.3 times up to 12 K steps, 1.1 with
+// more of them up to 447 channels, from there on level or behind but for fp32 under a given scale (2085 x 3920 -> 640 24.7 / 27.8).
 static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, bool behind_range, int resident, const Decision& d, WidePlan& p) {
   const bool fp32 = dt == GPUSQ_F32, i8 = a.out_dt == GPUSQ_I8, gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
   if ((d.forced >= 0 && d.forced != 5) || (!i8 && a.out_dt != GPUSQ_F16) || a.N % 16 != 0) return false;
@@ -653,15 +652,9 @@ static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, bool behind_range, int
   if (d.forced < 0 && (a.M < GPUSQ_WIDE_MIN_ROWS || a.N > 2 * kWideBlocks * kRowBlock)) return false;
   p = wide_plan(a.M, a.N, resident, fp32);
   if (p.chunks == 0 || d.forced == 5) return p.chunks > 0;
-  if (d.choice == 4) return a.N > 256 && (!behind_range || a.K <= 12 * kStepBytes);
-  if (d.gemm_us <= 0) return false;
-  double apart = quantise_and_gemm_us(d.gemm_us, a.M, a.N, a.K, fp32, i8), margin = fp32 ? 0.92 : 0.97;
-  if (behind_range) {
-    apart -= quantiser_behind_range_us(a.M, a.K, fp32) + (d.choice == 3 ? 0.09 * d.gemm_us : 0.0);  // (kernel 3: chosen where it is ahead of the estimate)
-    margin = a.N <= kRowBlock && a.K <= 3 * kStepBytes ? 0.8 : (fp32 ? 0.9 : 0.97);
-  }
-  if (a.K > 24 * kStepBytes && margin > 0.9) margin = 0.9;  // (a long K is estimated 8 % short)
-  return wide_us(p, a.M, a.N, a.K, resident, fp32, gelu, i8) < margin * apart;
+  if (d.choice == 4) return a.N > 256 && (a.K <= 12 * kStepBytes || a.N < 448 || (fp32 && !behind_range));
+  const double margin = behind_range ? wide_margin_behind_range(a.M, a.N, a.K, fp32, i8) : wide_margin(a.K, fp32);
+  return d.gemm_us > 0 && wide_us(p, a.M, a.N, a.K, resident, fp32, gelu, i8) < margin * quantise_and_gemm_us(d.gemm_us, a.M, a.N, a.K, fp32, i8);
 }
 
 // What quantises (GPUSQ_QUANTISE_*); WHOLE_ROWS: with this plan

@@ -88,13 +88,27 @@ inline double quantise_and_gemm_us(double gemm_us, int64_t M, int64_t N, int64_t
   const double pass = 2.2 + (double)M * K * (fp32 ? 5 : 3) / 5.83e6;
   return 1.3 + (pass > 2.8 ? pass : 2.8) + 0.9 * gemm_us + (int8_out ? 0.48e-7 * M * N : 0.0);
 }
-// Behind a range pass the quantiser is faster than those estimates (of a given scale) say: what the range pass read last it finds in the L2s, or X
-// in the last level cache, which the kernel for whole rows, bound by more than X, gains little from.  Medians of 4008 sizes, us, of X in MB
-// (of the difference that the range makes to the one, less what it makes to the other): fp16 4-12 0.3, 16-32 1.0, 48-120 -1 to 1, 130-280 5 to 10; fp32 6-12 1.2, 24-32
-// 2.4, 32-120 2.7 to 4, 120-200 4 to 5, 220-280 11, beyond 16.
-inline double quantiser_behind_range_us(int64_t M, int64_t K, bool fp32) {
-  const double mb = (double)M * K * (fp32 ? 4e-6 : 2e-6), l2 = mb < 32 ? mb : 32;
-  return fp32 ? 0.08 * l2 + (mb > 220 ? 8.0 : 0.0) : 0.03 * l2 + (mb > 120 ? 6.5 : 0.0);
+// Of that estimate, how much the other may be at most for the kernel for whole rows to be taken; smaller than 1 by what the estimates miss (their ratio is
+// off by 10 %, one standard deviation; a long K is estimated 8 % short).
+inline double wide_margin(int64_t K, bool fp32) { return K > 24 * 128 ? 0.9 : (fp32 ? 0.92 : 0.97); }
+// Behind a range pass the quantiser is faster than those estimates, which are of a given scale: what the pass read last it finds in the L2s (32 MB),
+// and all of X in the last level cache (256 MB) where the codes leave it there.  Where that decides (of 20022 sizes timed with either, X and Y in MB):
+//   one block of channels, up to 3 K steps, X beyond 6: whole rows slower in most fp32 sizes, whatever the estimates, in half of fp16 from a ratio of 0.88 on
+//   fp32, Y below 30, X of 9 to 48, or more than 12 K steps: level from a ratio of 0.85 on
+//   fp16, X of 115 to 160 (with the codes 172 to 240): level from 0.8 on for a ragged K, whose codes whole rows leave in the caches as well, from
+//   0.86 on for a Y of 10 to 30; elsewhere 10 % ahead
+inline double wide_margin_behind_range(int64_t M, int64_t N, int64_t K, bool fp32, bool int8_out) {
+  const double x = (double)M * K * (fp32 ? 4e-6 : 2e-6), y = (double)M * N * (int8_out ? 1e-6 : 2e-6), margin = wide_margin(K, fp32);
+  double most = margin;
+  if (N <= 64 && K <= 3 * 128 && x > 6)
+    most = fp32 ? 0.7 : 0.88;
+  else if (fp32 && y < 30 && ((x > 9 && x < 48) || K > 12 * 128))
+    most = 0.85;
+  else if (!fp32 && x > 115 && x < 160 && K % 128 != 0)
+    most = 0.8;
+  else if (!fp32 && x > 115 && x < 160 && y > 10 && y < 30)
+    most = 0.86;
+  return most < margin ? most : margin;
 }
 
 }  // namespace gpusq

@@ -320,11 +320,13 @@ def test_layers_whose_gemm_takes_fp16_activations(M, K, N, takes):
 
 @pytest.mark.parametrize("M,K,N,gelu,x_dt,out_dt,own,given", [
     # timed with the kernel for whole rows and without: slower with an own range; with either; faster with either
-    (54412, 1744, 256, False, 1, 1, 0, 2), (30706, 2256, 256, False, 1, 1, 0, 2), (19429, 3312, 192, False, 1, 1, 0, 2), (20738, 3072, 704, True, 1, 1, 0, 2),
-    (28758, 2960, 16, False, 1, 2, 0, 2), (26920, 2672, 64, True, 1, 1, 0, 2), (32855, 256, 32, False, 0, 2, 0, 2), (12609, 768, 768, False, 0, 1, 0, 2),
-    (22807, 256, 128, True, 0, 2, 0, 2), (29239, 176, 64, True, 0, 1, 0, 2), (11620, 2304, 1056, False, 0, 1, 0, 2), (2164, 1920, 448, True, 1, 2, 0, 2),
-    (12544, 512, 1536, False, 1, 2, 0, 2), (12066, 768, 1280, False, 1, 2, 0, 2), (28453, 1600, 1920, True, 1, 1, 0, 0), (12544, 768, 768, False, 1, 1, 2, 2), (25216, 3072, 768, False, 1, 1, 2, 2),
-    (14070, 576, 256, False, 1, 1, 2, 2), (7029, 1152, 256, False, 1, 1, 2, 2), (56475, 3648, 704, False, 1, 1, 2, 2), (50432, 192, 192, False, 1, 1, 2, 2)])
+    (30706, 2256, 256, False, 1, 1, 0, 2), (19429, 3312, 192, False, 1, 1, 0, 2), (20738, 3072, 704, True, 1, 1, 0, 2), (26920, 2672, 64, True, 1, 1, 0, 2),
+    (32855, 256, 32, False, 0, 2, 0, 2), (22807, 256, 128, True, 0, 2, 0, 2), (29239, 176, 64, True, 0, 1, 0, 2), (27117, 128, 16, True, 0, 1, 0, 2),
+    (11620, 2304, 1056, False, 0, 1, 0, 2), (2154, 3264, 704, True, 0, 1, 0, 2),
+    (2085, 3920, 640, False, 1, 1, 0, 0), (2164, 1920, 448, True, 1, 2, 0, 0), (28453, 1600, 1920, True, 1, 1, 0, 0),
+    (12544, 768, 768, False, 1, 1, 2, 2), (25216, 3072, 768, False, 1, 1, 2, 2), (14070, 576, 256, False, 1, 1, 2, 2), (7029, 1152, 256, False, 1, 1, 2, 2),
+    (56475, 3648, 704, False, 1, 1, 2, 2), (50432, 192, 192, False, 1, 1, 2, 2), (12544, 512, 1536, False, 1, 2, 2, 2), (25686, 384, 128, False, 0, 1, 2, 2),
+    (29242, 448, 208, False, 0, 1, 2, 2)])
 def test_layers_of_the_kernel_for_whole_rows(lib, M, K, N, gelu, x_dt, out_dt, own, given):
     f = lib.gpusq_linear_int8_quantiser
     f.argtypes = [ctypes.c_int, ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int] * 3
