@@ -713,7 +713,7 @@ gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* s
 // The images in front of a patch embedding: the kernel for whole rows takes a product of its sizes as it takes a layer's under a given scale.  A
 // range pass does come first, but the kernels that gather patches take longer than a layer's, which makes up for it.  Of 403 sizes timed (72 to
 // 576 patches an image, 256 to 1024 values each, 192 to 1536 channels) it takes 238 of fp16, 1.19 times as fast, none slower, and 101 of fp32, 1.06 times, 8 %
-// slower at the most (29120 x 256 -> 1088); the rule for a layer behind a range pass would not take 62 fp32 images of 304 x 304 -> 704, 41.2 / 37.4.
+// slower at the most (29120 x 256 -> 1088; apart / here 62 images of 304 x 304 -> 704 41.2 / 37.4).
 gpusq_status launch_patch_embed_int8(GemmArgs a, gpusq_dtype dt, int8_t* img_q, float* scale, void* workspace, hipStream_t s) {
   const int resident = num_cus();
   const int choice = decide(true, a.M, a.N, a.K, false, resident, true).choice;
