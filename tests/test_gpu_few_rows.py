@@ -191,3 +191,20 @@ def test_one_call_layer_with_shared_operands(g, M, K, N, dtype, out):
         exp = g.spgemm_int8(exp_q, packed, N, act_scale=exp_s, w_scale=sw, bias=b)
         g.calls.gpusq_linear_int8(x, x_dt, packed, scale, 0, sw, b, Y, g.F16, None, Xq, Y, M, N, K, g.EPI_BIAS)
     assert torch.equal(Xq, exp_q) and torch.equal(scale, exp_s) and torch.equal(Y, exp)
+
+
+# as many rows as the kernel for whole rows asks for, of so few channels that the kernel for few rows takes them: with and without the codes
+@pytest.mark.parametrize("M,K,N", [(2048, 256, 64), (4096, 256, 64), (8192, 256, 64)])
+def test_many_rows_of_one_block(g, M, K, N):
+    from paper_2305_10727_amd.pipeline import SparseLinear
+    lin = SparseLinear(M, K, N, "int8")
+    assert lin.takes_fp16_input()
+    lin.prepare_weights(dev(synth.weights(N, K, seed=M)))
+    x, b = dev((np.random.default_rng(M).standard_normal((M, K)) * 1.5).astype(np.float16)), dev(synth.bias(N, seed=M))
+    lin.act_scale.fill_(4 / 127)
+    exp_q, _ = g.quantize_int8(x, g.PER_TENSOR, scale=lin.act_scale)
+    exp = g.spgemm_int8(exp_q, lin.packed, N, act_scale=lin.act_scale, w_scale=lin.w_scale, bias=b)
+    lin.Xq.fill_(99)
+    assert torch.equal(lin.gemm_from_f16(x, b), exp) and (lin.Xq == 99).all()
+    lin.Y.zero_()
+    assert torch.equal(lin.forward(x, b, static=True), exp) and torch.equal(lin.Xq, exp_q)
