@@ -206,6 +206,21 @@ gpusq_status gpusq_spgemm_int8_codes(const int8_t* Xq, const void* Wpacked, cons
                                      const float* bias, void* Y, int8_t* Yq, const float* codes_scale, int64_t M, int64_t N,
                                      int64_t K, int epilogue, void* stream);
 
+/* The linear layers behind attention in an encoder block on calibrated scales, without a norm between them, in one call: proj on the codes of
+ * attention, its codes, fc1 with GELU, fc2; results (P, Pq, G, Y) bit-identical to
+ *   gpusq_spgemm_int8_codes(Xq, Wproj, x_scale, wproj_scale, bproj, P, Pq, h_scale, M, D, D, GPUSQ_EPI_BIAS),
+ *   gpusq_spgemm_int8(Pq, Wfc1, h_scale, wfc1_scale, bfc1, G, GPUSQ_I8, g_scale, M, H, D, GPUSQ_EPI_BIAS | GPUSQ_EPI_GELU),
+ *   gpusq_spgemm_int8(G, Wfc2, g_scale, wfc2_scale, bfc2, Y, GPUSQ_F16, NULL, M, D, H, GPUSQ_EPI_BIAS),
+ * with the limits of these.  One launch for rows of up to 512 channels (D % 64 == 0, H % 64 == 0, H <= 8 D) where that is faster and none of Xq, P, Pq, G, Y
+ * overlap, else those three. */
+gpusq_status gpusq_block_mlp_int8(const int8_t* Xq, const void* Wproj, const float* x_scale, const float* wproj_scale,
+                                  const float* bproj, void* P, int8_t* Pq, const float* h_scale, const void* Wfc1,
+                                  const float* wfc1_scale, const float* bfc1, int8_t* G, const float* g_scale, const void* Wfc2,
+                                  const float* wfc2_scale, const float* bfc2, void* Y, int64_t M, int64_t D, int64_t H, void* stream);
+/* How many launches that call takes on a device with `cus` compute units (cus <= 0: the current device) where nothing overlaps: 1 or 3; 0 for
+ * invalid sizes.  Host-side. */
+int gpusq_block_mlp_int8_launches(int64_t M, int64_t D, int64_t H, int cus);
+
 /* The same product with the quantise node of the activations [Sec. 2.2: activations are quantised at run time with a
  * calibrated scale before every quantised layer] folded into the GEMM: X [M][K] fp16 is turned into the codes
  * Xq = clamp(rint(X / act_scale[0]), -127, 127) on its way to the matrix instructions (the code rule of
@@ -293,8 +308,9 @@ gpusq_status gpusq_spgemm_plan(gpusq_dtype dt, int64_t M, int64_t N, int64_t K, 
 /* Testing aid: kernel = 0 (64 x 64 tiles), 1, 2, 3 or 4 (few rows, shown as 0 by gpusq_spgemm_plan) makes the sparse GEMM entry
  * points (and gpusq_spgemm_plan's out[0]) take that kernel for every problem it can run (kernel 3 needs K * element size % 128 == 0), so that every kernel can be checked on
  * the same shapes; 0 and 1 also keep the dense twins on their small kernel; any other value gives the choice back to the
- * size rules.  5: the size rules, but gpusq_linear_int8 takes its kernel for many rows of few channels at every size it can (0 to 4: at none).
- * Returns the previous setting (-1 = none).  Process-wide; the environment variable GPUSQ_FORCE_KERNEL (0..5)
+ * size rules.  5: the size rules, but gpusq_linear_int8 takes its kernel for many rows of few channels at every size it can (0 to 4: at none).  6: the size rules, but gpusq_block_mlp_int8 is one launch at every size it can (0 to 4:
+ * at none).
+ * Returns the previous setting (-1 = none).  Process-wide; the environment variable GPUSQ_FORCE_KERNEL (0..6)
  * gives the initial setting and is read once, when the library is loaded.  Not meant for production callers. */
 int gpusq_force_kernel(int kernel);
 

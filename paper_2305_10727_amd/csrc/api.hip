@@ -351,6 +351,31 @@ gpusq_status gpusq_spgemm_int8_codes(const int8_t* Xq, const void* Wpacked, cons
   return launch_spgemm(true, a, (hipStream_t)stream);
 }
 
+gpusq_status gpusq_block_mlp_int8(const int8_t* Xq, const void* Wproj, const float* x_scale, const float* wproj_scale, const float* bproj, void* P,
+                                  int8_t* Pq, const float* h_scale, const void* Wfc1, const float* wfc1_scale, const float* bfc1, int8_t* G,
+                                  const float* g_scale, const void* Wfc2, const float* wfc2_scale, const float* bfc2, void* Y, int64_t M, int64_t D,
+                                  int64_t H, void* stream) {
+  if (!bproj || !bfc1 || !bfc2 || !Pq || !x_scale || !h_scale || !g_scale) return GPUSQ_ERR_NULL;
+  gpusq_status st = check_gemm(Xq, Wproj, bproj, P, M, D, D, GPUSQ_EPI_BIAS);
+  if (st == GPUSQ_OK) st = check_gemm(Pq, Wfc1, bfc1, G, M, H, D, GPUSQ_EPI_BIAS);
+  if (st == GPUSQ_OK) st = check_gemm(G, Wfc2, bfc2, Y, M, D, H, GPUSQ_EPI_BIAS);
+  if (st == GPUSQ_OK) st = check_int8_extras(x_scale, wproj_scale, GPUSQ_F16, nullptr);
+  if (st == GPUSQ_OK) st = check_int8_extras(h_scale, wfc1_scale, GPUSQ_I8, g_scale);
+  if (st == GPUSQ_OK) st = check_int8_extras(g_scale, wfc2_scale, GPUSQ_F16, nullptr);
+  if (st != GPUSQ_OK) return st;
+  MlpArgs a{Xq, Wproj, Wfc1, Wfc2, x_scale, h_scale, g_scale, wproj_scale, wfc1_scale, wfc2_scale, bproj, bfc1, bfc2, P, Pq, G, Y, (int)M, (int)D, (int)H};
+  if (mlp_in_one_launch(a)) return launch_mlp(a, (hipStream_t)stream);
+  st = gpusq_spgemm_int8_codes(Xq, Wproj, x_scale, wproj_scale, bproj, P, Pq, h_scale, M, D, D, GPUSQ_EPI_BIAS, stream);
+  if (st == GPUSQ_OK) st = gpusq_spgemm_int8(Pq, Wfc1, h_scale, wfc1_scale, bfc1, G, GPUSQ_I8, g_scale, M, H, D, GPUSQ_EPI_BIAS | GPUSQ_EPI_GELU, stream);
+  if (st == GPUSQ_OK) st = gpusq_spgemm_int8(G, Wfc2, g_scale, wfc2_scale, bfc2, Y, GPUSQ_F16, nullptr, M, D, H, GPUSQ_EPI_BIAS, stream);
+  return st;
+}
+
+int gpusq_block_mlp_int8_launches(int64_t M, int64_t D, int64_t H, int cus) {
+  if (M <= 0 || M > INT32_MAX || check_nk(D, D) != GPUSQ_OK || check_nk(H, D) != GPUSQ_OK || D % 16 != 0 || H % 16 != 0) return 0;
+  return mlp_launches(M, D, H, cus);
+}
+
 gpusq_status gpusq_spgemm_int8_xf16(const void* X, const void* Wpacked, const float* act_scale, const float* w_scale,
                                     const float* bias, void* Y, gpusq_dtype out_dt, const float* out_scale, int64_t M,
                                     int64_t N, int64_t K, int epilogue, void* stream) {

@@ -431,6 +431,22 @@ gpusq_status launch_fewrows(bool is_i8, const GemmArgs& a, int resident, hipStre
 // the sparse INT8 GEMM on whole rows that it quantises (wide.hip)
 struct WidePlan;
 gpusq_status launch_wide(const GemmArgs& a, const WidePlan& p, hipStream_t s);
+// the layers behind attention on calibrated scales (mlp.hip): attention's codes Xq [M][D]; proj's output P and its codes Hq [M][D], the codes G [M][H]
+// of fc1's GELU, fc2's output Y [M][D]
+struct MlpArgs {
+  const int8_t* Xq;
+  const void *Wp, *W1, *W2;
+  const float *s_attn, *s_h, *s_g;
+  const float *ws_proj, *ws_fc1, *ws_fc2, *b_proj, *b_fc1, *b_fc2;
+  void* P;
+  int8_t *Hq, *G;
+  void* Y;
+  int M, D, H;
+};
+bool mlp_in_one_launch(const MlpArgs& a);
+int mlp_launches(int64_t M, int64_t D, int64_t H, int cus);
+gpusq_status launch_mlp(const MlpArgs& a, hipStream_t s);
+int num_cus();                      // of the current device
 // quantise (dt of X, workspace as for launch_quantize) and multiply: one, two or three launches
 gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, void* workspace, hipStream_t s);
 int linear_int8_launches(const GemmArgs& a, gpusq_dtype dt, int scale_is_input, int cus);

@@ -18,8 +18,8 @@
 
 namespace {
 
-constexpr int kMaxArgs = 20;
-typedef int (*fn_t)(long, long, long, long, long, long, long, long, long, long, long, long, long, long, long, long, long, long, long, long);
+constexpr int kMaxArgs = 24;
+typedef int (*fn_t)(long, long, long, long, long, long, long, long, long, long, long, long, long, long, long, long, long, long, long, long, long, long, long, long);
 
 struct FastCall {
   PyObject_HEAD
@@ -100,7 +100,8 @@ PyObject* call(PyObject* self, PyObject* const* args, size_t nargsf, PyObject* k
   }
   int status;
   Py_BEGIN_ALLOW_THREADS
-  status = f->fn(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10], a[11], a[12], a[13], a[14], a[15], a[16], a[17], a[18], a[19]);
+  status = f->fn(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10], a[11], a[12], a[13], a[14], a[15], a[16], a[17], a[18], a[19], a[20],
+                 a[21], a[22], a[23]);
   Py_END_ALLOW_THREADS
   if (f->raw) return PyLong_FromLong(status);
   if (status == 0) Py_RETURN_NONE;
@@ -126,7 +127,7 @@ PyObject* make(PyTypeObject* type, PyObject* args, PyObject*) {
   if (!PyArg_ParseTuple(args, "UKs|p", &name, &address, &sig, &raw)) return nullptr;
   const size_t n = strlen(sig);
   if (n > kMaxArgs || strspn(sig, "ptis") != n) {
-    PyErr_SetString(PyExc_ValueError, "signature: up to 20 of p, t, i, s");
+    PyErr_SetString(PyExc_ValueError, "signature: up to 24 of p, t, i, s");
     return nullptr;
   }
   FastCall* f = (FastCall*)type->tp_alloc(type, 0);

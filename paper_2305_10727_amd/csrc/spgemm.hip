@@ -316,7 +316,7 @@ static gpusq_status launch_small(const GemmArgs& a, hipStream_t s) {
 }
 
 // Compute units of the current device, read once per device (a racing first call reads the same value twice).
-static int num_cus() {
+int num_cus() {
   constexpr int kMaxDevices = 64;
   static std::atomic<int> cus[kMaxDevices];
   int dev = 0;
@@ -334,12 +334,12 @@ static int num_cus() {
 // library is loaded, so that no launch pays for an environment lookup.
 static int initial_forced_kernel() {
   const char* f = getenv("GPUSQ_FORCE_KERNEL");
-  return (f && f[0] >= '0' && f[0] <= '5' && f[1] == 0) ? f[0] - '0' : -1;
+  return (f && f[0] >= '0' && f[0] <= '6' && f[1] == 0) ? f[0] - '0' : -1;
 }
 static std::atomic<int> g_forced_kernel{initial_forced_kernel()};
 int forced_kernel() { return g_forced_kernel.load(std::memory_order_relaxed); }
 int set_forced_kernel(int kernel) {
-  return g_forced_kernel.exchange(kernel >= 0 && kernel <= 5 ? kernel : -1);
+  return g_forced_kernel.exchange(kernel >= 0 && kernel <= 6 ? kernel : -1);
 }
 
 // The estimate that decides which problems may quantise fp16 activations on their way into the small kernel (see kernel_choice), of
@@ -474,7 +474,7 @@ static int kernel_choice(bool is_i8, int64_t M, int64_t N, int64_t K, bool gelu,
   const int64_t ksteps = ceil_div(k_bytes, kStepBytes);
   const int64_t wgs64 = ceil_div(M, 64) * ceil_div(N, 64);
   // Testing aid: a forced kernel overrides the choice (2 only where the tile kernel can run the problem).
-  if (const int c = g_forced_kernel.load(std::memory_order_relaxed); c >= 0 && c != 5) {
+  if (const int c = g_forced_kernel.load(std::memory_order_relaxed); c >= 0 && c < 5) {
     if (c != 3 || k_bytes % kStepBytes == 0) return c;
   }
   // (the fused patch gather is refused up to 256 K outputs; beyond, it goes to the kernel for few rows where a GEMM of its sizes would, else
@@ -647,7 +647,7 @@ constexpr int64_t kRangeHereBytes = 128 * 1024;
 // more of them up to 447 channels, from there on level or behind but for fp32 under a given scale (2085 x 3920 -> 640 24.7 / 27.8).
 static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, bool behind_range, int resident, const Decision& d, WidePlan& p) {
   const bool fp32 = dt == GPUSQ_F32, i8 = a.out_dt == GPUSQ_I8, gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
-  if ((d.forced >= 0 && d.forced != 5) || (!i8 && a.out_dt != GPUSQ_F16) || a.N % 16 != 0) return false;
+  if ((d.forced >= 0 && d.forced < 5) || (!i8 && a.out_dt != GPUSQ_F16) || a.N % 16 != 0) return false;
   if ((int64_t)a.K * 64 * 4 >= ((int64_t)1 << 31) || a.N >= (1 << 24)) return false;  // 32-bit lane offsets inside a chunk's rows
   if (d.forced < 0 && (a.M < GPUSQ_WIDE_MIN_ROWS || a.N > 2 * kWideBlocks * kRowBlock)) return false;
   p = wide_plan(a.M, a.N, resident, fp32);

@@ -30,6 +30,7 @@ EXPORTS = [
     "gpusq_prune_4to8_pairs", "gpusq_quantize_rows_int4", "gpusq_compress_int4", "gpusq_decompress_int4",
     "gpusq_int4_to_sparse_int8", "gpusq_prune_n_of_m", "gpusq_force_kernel",
     "gpusq_quantize_tensor_int8_noalloc", "gpusq_linear_int8", "gpusq_linear_int8_launches", "gpusq_linear_int8_quantiser",
+    "gpusq_block_mlp_int8", "gpusq_block_mlp_int8_launches",
 ]
 
 
@@ -50,6 +51,7 @@ _SIGNATURES = {
     "gpusq_spgemm_fp16": "ttttiiiis", "gpusq_spgemm_int8": "ttttttitiiiis", "gpusq_spgemm_int8_xf16": "ttttttitiiiis",
     "gpusq_spgemm_int8_codes": "ttttttttiiiis",
     "gpusq_linear_int8": "tittitttitttiiiis",
+    "gpusq_block_mlp_int8": "tttttttttttttttttiiis",
     "gpusq_im2col_patches": "ttiiiiiiis", "gpusq_patch_embed16_int8": "ttttttiiiiiis", "gpusq_patch_embed16_fp16": "ttttiiiiiis",
     "gpusq_patch_embed16_images": "titttttttiiiiiis",
     "gpusq_gemm_fp16_dense": "ttttiiiis", "gpusq_gemm_int8_dense": "ttttttitiiiis", "gpusq_prune_4to8_pairs": "tttiiis",
@@ -132,6 +134,10 @@ def lib():
         L.gpusq_spgemm_int8_xf16.restype = ci
         L.gpusq_spgemm_int8_codes.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, i64, i64, i64, ci, vp]
         L.gpusq_spgemm_int8_codes.restype = ci
+        L.gpusq_block_mlp_int8.argtypes = [vp] * 17 + [i64] * 3 + [vp]
+        L.gpusq_block_mlp_int8.restype = ci
+        L.gpusq_block_mlp_int8_launches.argtypes = [i64, i64, i64, ci]
+        L.gpusq_block_mlp_int8_launches.restype = ci
         L.gpusq_linear_int8.argtypes = [vp, ci, vp, vp, ci, vp, vp, vp, ci, vp, vp, vp, i64, i64, i64, ci, vp]
         L.gpusq_linear_int8.restype = ci
         L.gpusq_linear_int8_launches.argtypes = [ci, i64, i64, i64, ci, ci, ci]

@@ -190,7 +190,7 @@ class EncoderBlockLinears:
     five launches of the library, with a norm six:
         quantise x, qkv, [attention], proj, [residual + norm, quantise h], fc1 (GELU), fc2;
     with few rows (problems of the latency kernel) qkv, and fc1 behind a norm, quantise their fp16 input on the way in, each where its sizes
-    favour it: a launch less for each.
+    favour it: a launch less for each; and without a norm proj, fc1 and fc2 are one launch up to 512 channels (gpusq_block_mlp_int8).
     Attention and the normalisation are not part of the library: `attention(qkv_int8 [M,3D], out_int8 [M,D])` and
     `norm(proj_fp16 [M,D]) -> fp16 [M,D]` are the caller's (stubs in the tests and the report).  capture() records the
     whole sequence into a HIP graph, which takes the host out of the loop.
@@ -228,9 +228,11 @@ class EncoderBlockLinears:
             self.qkv.forward(x, biases[0], self.scales["qkv"], static=True)
         attention(self.qkv.Y, self.proj.Xq)
         if norm is None:
-            self.proj.gemm_and_codes(self.fc1, biases[1])
-            self.fc1.gemm(None, biases[2], self.scales["g"])
-            return self.fc2.gemm(None, biases[3])
+            proj, fc1, fc2 = self.proj, self.fc1, self.fc2
+            _call.gpusq_block_mlp_int8(proj.Xq, proj.packed, proj.act_scale, proj.w_scale, biases[1], proj.Y, fc1.Xq, fc1.act_scale,
+                                       fc1.packed, fc1.w_scale, biases[2], fc1.Y, self.scales["g"], fc2.packed, fc2.w_scale, biases[3], fc2.Y,
+                                       self.M, self.D, self.hidden)
+            return fc2.Y
         h = norm(self.proj.gemm(None, biases[1]))
         if self.fold_quantise:
             self.fc1.gemm_from_f16(h, biases[2], self.scales["g"])

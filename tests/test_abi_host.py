@@ -304,6 +304,25 @@ def test_every_chunk_of_the_kernel_for_whole_rows_is_met_once(tmp_path):
     assert run.returncode == 0 and run.stdout == "20000 plans\n", run.stdout
 
 
+def test_walk_block_mlp_plans(tmp_path):
+    """The plans of the kernel for the layers behind attention, walked on the host with the code the kernel reads them with (mlp_plan_walk.cpp)"""
+    exe = str(tmp_path / "walk")
+    build = subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                            "-I", os.path.join(ROOT, "paper_2305_10727_amd", "csrc"), os.path.join(ROOT, "tests", "mlp_plan_walk.cpp"), "-o", exe],
+                           capture_output=True, text=True)
+    assert build.returncode == 0, build.stderr
+    run = subprocess.run([exe, "20000"], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0 and run.stdout == "20000 plans\n", run.stdout
+
+
+# few rows and small operands; few rows of large ones; many; beyond 512 channels; no whole 64 channels; few slabs to LDS, one round and more; invalid
+@pytest.mark.parametrize("M,D,H,launches", [(197, 192, 768, 1), (197, 512, 2048, 3), (12544, 512, 2048, 1), (12608, 768, 3072, 3), (4000, 208, 832, 3),
+                                            (4492, 448, 3584, 1), (17053, 384, 3072, 3), (0, 512, 2048, 0), (16, 24, 96, 0)])
+def test_launches_behind_attention(M, D, H, launches):
+    from paper_2305_10727_amd import gpusq
+    assert gpusq.lib().gpusq_block_mlp_int8_launches(M, D, H, 256) == launches
+
+
 @pytest.mark.parametrize("M,K,N,takes", [(197, 768, 768, True), (2047, 256, 64, True), (2048, 256, 64, True), (4096, 256, 64, True), (4097, 256, 128, False),
                                          (8192, 256, 64, True), (8193, 256, 64, False), (12608, 768, 768, False), (7029, 1152, 256, False)])
 def test_layers_whose_gemm_takes_fp16_activations(M, K, N, takes):
