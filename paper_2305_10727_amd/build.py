@@ -31,6 +31,17 @@ def _run(cmd, verbose):
         print(err, file=sys.stderr)
 
 
+def _fastcall_command():
+    """The extension module uses torch's C++ interface: its headers (as system headers), its ABI, its libraries by their own path."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    libs = os.path.join(root, "lib")
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+            "-I" + sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"), "-isystem",
+            os.path.join(root, "include", "torch", "csrc", "api", "include"), os.path.join(CSRC, "fastcall.cpp"), "-o", FASTCALL,
+            "-L" + libs, "-Wl,-rpath," + libs, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
 def build(verbose=False):
     """Compile every HIP source (one hipcc process each, side by side) and link paper_2305_10727_amd/libgpusq.so, and the
     extension module that calls it; always recompiles; raises on failure.  The objects live in a temporary directory, not in the tree."""
@@ -41,8 +52,7 @@ def build(verbose=False):
     with tempfile.TemporaryDirectory(prefix="gpusq_build_") as tmp:
         objs = [os.path.join(tmp, s.replace(".hip", ".o")) for s in SOURCES]
         cmds = [[hipcc, *compile_flags, "-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objs)]
-        cmds.append(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
-                     os.path.join(CSRC, "fastcall.cpp"), "-o", FASTCALL])
+        cmds.append(_fastcall_command())
         with concurrent.futures.ThreadPoolExecutor(max_workers=min(len(cmds), os.cpu_count() or 1)) as pool:
             for f in [pool.submit(_run, c, verbose) for c in cmds]:
                 f.result()

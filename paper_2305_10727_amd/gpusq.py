@@ -97,6 +97,14 @@ def _stream_of(device):
 # looked up once; without it the public route is used.
 _stream_of = getattr(torch._C, "_cuda_getCurrentRawStream", _stream_of)
 
+def _empty(like, dtype, *sizes):
+    """torch.empty(sizes, dtype=dtype, device=like.device) at 0.7 us where that takes 1.8; the extension module, loaded on first use, takes its place"""
+    global _empty
+    from . import _fastcall
+    _empty = _fastcall.empty
+    return _empty(like, dtype, *sizes)
+
+
 _lib = None
 
 
@@ -197,8 +205,8 @@ def version():
 def prune_2to4(W, out=None, want_mask=False):
     """gpusq_prune_2to4: W [N,K] fp32/fp16 -> pruned W (and the [N,K/4] keep-mask bytes if asked)."""
     N, K = W.shape
-    out = torch.empty_like(W) if out is None else out
-    mask = torch.empty((N, max(K // 4, 1)), dtype=torch.uint8, device=W.device) if want_mask else None
+    out = _empty(W, W.dtype, N, K) if out is None else out
+    mask = _empty(W, torch.uint8, N, max(K // 4, 1)) if want_mask else None
     calls.gpusq_prune_2to4(W, out, mask, _TORCH_DT[W.dtype], N, K)
     return (out, mask) if want_mask else out
 
@@ -214,12 +222,12 @@ def quantize_int8(X, mode, scale=None):
     """gpusq_quantize_int8: returns (Xq int8, scale tensor).  mode PER_ROW: scale [rows]; PER_TENSOR: scale [1].
     Pass `scale` (device fp32 tensor) to quantise with given scales."""
     rows, cols = X.shape
-    Xq = torch.empty((rows, cols), dtype=torch.int8, device=X.device)
+    Xq = _empty(X, torch.int8, rows, cols)
     given = scale is not None
     if not given:
-        scale = torch.empty(rows if mode == PER_ROW else 1, dtype=torch.float32, device=X.device)
+        scale = _empty(X, torch.float32, rows if mode == PER_ROW else 1)
     ws_bytes = lib().gpusq_quantize_workspace_bytes(mode, rows, cols)
-    ws = torch.empty(max(ws_bytes, 16), dtype=torch.uint8, device=X.device)
+    ws = _empty(X, torch.uint8, max(ws_bytes, 16))
     calls.gpusq_quantize_int8(X, _TORCH_DT[X.dtype], Xq, scale, mode, int(given), rows, cols, ws)
     return Xq, scale
 
@@ -235,9 +243,9 @@ def quantize_tensor_int8_noalloc(X, Xq, scale, scale_is_input=False):
 def compress(W, want_violations=False):
     """gpusq_compress: W [N,K] fp16/int8 -> (values [N,K/2], meta [N,ceil(K/8)] uint8[, violations int32[1]])."""
     N, K = W.shape
-    values = torch.empty((N, max(K // 2, 1)), dtype=W.dtype, device=W.device)
-    meta = torch.empty((N, max(meta_row_bytes(K), 1)), dtype=torch.uint8, device=W.device)
-    viol = torch.empty(1, dtype=torch.int32, device=W.device) if want_violations else None
+    values = _empty(W, W.dtype, N, max(K // 2, 1))
+    meta = _empty(W, torch.uint8, N, max(meta_row_bytes(K), 1))
+    viol = _empty(W, torch.int32, 1) if want_violations else None
     calls.gpusq_compress(W, values, meta, viol, _TORCH_DT[W.dtype], N, K)
     return (values, meta, viol) if want_violations else (values, meta)
 
@@ -248,7 +256,7 @@ ERR_NOT_2TO4 = 6
 def check_2to4(W):
     """gpusq_check_2to4: W [N,K] fp32/fp16/int8 -> (is_2to4, groups with more than two non-zeros); waits for the stream"""
     N, K = W.shape
-    viol = torch.empty(1, dtype=torch.int32, device=W.device)
+    viol = _empty(W, torch.int32, 1)
     st = calls.gpusq_check_2to4(W, _TORCH_DT[W.dtype], viol, N, K)
     if st not in (0, ERR_NOT_2TO4):
         _check(st, "gpusq_check_2to4")
@@ -257,7 +265,7 @@ def check_2to4(W):
 
 def decompress(values, meta, K):
     N = values.shape[0]
-    W = torch.empty((N, K), dtype=values.dtype, device=values.device)
+    W = _empty(values, values.dtype, N, K)
     calls.gpusq_decompress(values, meta, W, _TORCH_DT[values.dtype], N, K)
     return W
 
@@ -265,7 +273,7 @@ def decompress(values, meta, K):
 def prune_n_of_m(W, n, m):
     """gpusq_prune_n_of_m: W [N,K] fp32 -> copy with the n largest magnitudes of every m contiguous elements kept"""
     N, K = W.shape
-    out = torch.empty_like(W)
+    out = _empty(W, W.dtype, N, K)
     calls.gpusq_prune_n_of_m(W, out, n, m, N, K)
     return out
 
@@ -273,8 +281,8 @@ def prune_n_of_m(W, n, m):
 def prune_4to8_pairs(W, want_mask=False, one_per_group=False):
     """gpusq_prune_4to8_pairs: W [N,K] fp32 -> pruned copy (and the keep mask [N,K/8] uint8)"""
     N, K = W.shape
-    out = torch.empty_like(W)
-    mask = torch.empty((N, K // 8), dtype=torch.uint8, device=W.device) if want_mask else None
+    out = _empty(W, W.dtype, N, K)
+    mask = _empty(W, torch.uint8, N, K // 8) if want_mask else None
     calls.gpusq_prune_4to8_pairs(W, out, mask, int(one_per_group), N, K)
     return (out, mask) if want_mask else out
 
@@ -282,9 +290,9 @@ def prune_4to8_pairs(W, want_mask=False, one_per_group=False):
 def int4_to_sparse_int8(values4, meta4, K, want_mismatches=False):
     """gpusq_int4_to_sparse_int8: INT4 pair-wise storage -> (values [N,K/2] int8, meta [N,K/8] uint8[, mismatches int32[1]])"""
     N = values4.shape[0]
-    values8 = torch.empty((N, K // 2), dtype=torch.int8, device=values4.device)
-    meta8 = torch.empty((N, K // 8), dtype=torch.uint8, device=values4.device)
-    bad = torch.empty(1, dtype=torch.int32, device=values4.device) if want_mismatches else None
+    values8 = _empty(values4, torch.int8, N, K // 2)
+    meta8 = _empty(values4, torch.uint8, N, K // 8)
+    bad = _empty(values4, torch.int32, 1) if want_mismatches else None
     calls.gpusq_int4_to_sparse_int8(values4, meta4, values8, meta8, bad, N, K)
     return (values8, meta8, bad) if want_mismatches else (values8, meta8)
 
@@ -292,10 +300,10 @@ def int4_to_sparse_int8(values4, meta4, K, want_mismatches=False):
 def quantize_rows_int4(X, scale=None):
     """gpusq_quantize_rows_int4: returns (4-bit codes in an int8 tensor, scale [rows])"""
     rows, cols = X.shape
-    Xq = torch.empty((rows, cols), dtype=torch.int8, device=X.device)
+    Xq = _empty(X, torch.int8, rows, cols)
     given = scale is not None
     if not given:
-        scale = torch.empty(rows, dtype=torch.float32, device=X.device)
+        scale = _empty(X, torch.float32, rows)
     calls.gpusq_quantize_rows_int4(X, _TORCH_DT[X.dtype], Xq, scale, int(given), rows, cols)
     return Xq, scale
 
@@ -303,16 +311,16 @@ def quantize_rows_int4(X, scale=None):
 def compress_int4(Wq, want_violations=False):
     """gpusq_compress_int4: Wq [N,K] int8 (4-bit codes) -> (values [N,K/4] uint8, meta [N,ceil(K/16)] uint8[, violations])"""
     N, K = Wq.shape
-    values = torch.empty((N, K // 4), dtype=torch.uint8, device=Wq.device)
-    meta = torch.empty((N, (K // 8 + 1) // 2), dtype=torch.uint8, device=Wq.device)
-    viol = torch.empty(1, dtype=torch.int32, device=Wq.device) if want_violations else None
+    values = _empty(Wq, torch.uint8, N, K // 4)
+    meta = _empty(Wq, torch.uint8, N, (K // 8 + 1) // 2)
+    viol = _empty(Wq, torch.int32, 1) if want_violations else None
     calls.gpusq_compress_int4(Wq, values, meta, viol, N, K)
     return (values, meta, viol) if want_violations else (values, meta)
 
 
 def decompress_int4(values, meta, K):
     N = values.shape[0]
-    W = torch.empty((N, K), dtype=torch.int8, device=values.device)
+    W = _empty(values, torch.int8, N, K)
     calls.gpusq_decompress_int4(values, meta, W, N, K)
     return W
 
@@ -322,7 +330,7 @@ def im2col_patches(img, P, K_pad=None):
     B, C, H, W = img.shape
     K = C * P * P
     K_pad = K if K_pad is None else K_pad
-    X = torch.empty((B * (H // P) * (W // P), K_pad), dtype=img.dtype, device=img.device)
+    X = _empty(img, img.dtype, B * (H // P) * (W // P), K_pad)
     calls.gpusq_im2col_patches(img, X, _TORCH_DT[img.dtype], B, C, H, W, P, K_pad)
     return X
 
@@ -330,7 +338,7 @@ def im2col_patches(img, P, K_pad=None):
 def patch_embed16(img, packed, D, act_scale=None, w_scale=None, bias=None):
     """gpusq_patch_embed16_int8 / _fp16: img [B,C,H,W] int8 or fp16 -> tokens [B*(H/16)*(W/16), D] fp16 (patches gathered by the GEMM)"""
     B, C, H, W = img.shape
-    Y = torch.empty((B * (H // 16) * (W // 16), D), dtype=torch.float16, device=img.device)
+    Y = _empty(img, torch.float16, B * (H // 16) * (W // 16), D)
     epi = EPI_BIAS if bias is not None else 0
     if img.dtype == torch.int8:
         calls.gpusq_patch_embed16_int8(img, packed, act_scale, w_scale, bias, Y, B, C, H, W, D, epi)
@@ -363,7 +371,7 @@ def pack(values, meta, K):
     nbytes = packed_bytes(values.dtype, N, K)
     if nbytes == 0:
         raise GpusqError(ERR_SHAPE, "gpusq_packed_bytes")
-    packed = torch.empty(nbytes, dtype=torch.uint8, device=values.device)
+    packed = _empty(values, torch.uint8, nbytes)
     calls.gpusq_pack(values, meta, packed, _TORCH_DT[values.dtype], N, K)
     return packed
 
@@ -373,14 +381,14 @@ def prepare_weights(W, dtype, want_intermediates=False):
     With want_intermediates also returns W_pruned, W_low, values, meta."""
     N, K = W.shape
     dt = _TORCH_DT[dtype]
-    packed = torch.empty(packed_bytes(dtype, N, K), dtype=torch.uint8, device=W.device)
-    w_scale = torch.empty(N, dtype=torch.float32, device=W.device) if dtype == torch.int8 else None
+    packed = _empty(W, torch.uint8, packed_bytes(dtype, N, K))
+    w_scale = _empty(W, torch.float32, N) if dtype == torch.int8 else None
     Wp = Wl = values = meta = None
     if want_intermediates:
         Wp = torch.empty_like(W)
-        Wl = torch.empty((N, K), dtype=dtype, device=W.device)
-        values = torch.empty((N, K // 2), dtype=dtype, device=W.device)
-        meta = torch.empty((N, meta_row_bytes(K)), dtype=torch.uint8, device=W.device)
+        Wl = _empty(W, dtype, N, K)
+        values = _empty(W, dtype, N, K // 2)
+        meta = _empty(W, torch.uint8, N, meta_row_bytes(K))
     calls.gpusq_prepare_weights(W, dt, Wp, Wl, w_scale, values, meta, packed, N, K)
     out = dict(packed=packed, w_scale=w_scale)
     if want_intermediates:
@@ -394,7 +402,7 @@ def _epi(bias, gelu):
 
 def spgemm_fp16(X, Wpacked, N, bias=None, gelu=False, out=None):
     M, K = X.shape
-    Y = torch.empty((M, N), dtype=torch.float16, device=X.device) if out is None else out
+    Y = _empty(X, torch.float16, M, N) if out is None else out
     calls.gpusq_spgemm_fp16(X, Wpacked, bias, Y, M, N, K, _epi(bias, gelu))
     return Y
 
@@ -402,7 +410,7 @@ def spgemm_fp16(X, Wpacked, N, bias=None, gelu=False, out=None):
 def spgemm_int8(Xq, Wpacked, N, act_scale=None, w_scale=None, bias=None, gelu=False, out_dtype=torch.float16,
                 out_scale=None, out=None):
     M, K = Xq.shape
-    Y = torch.empty((M, N), dtype=out_dtype, device=Xq.device) if out is None else out
+    Y = _empty(Xq, out_dtype, M, N) if out is None else out
     calls.gpusq_spgemm_int8(Xq, Wpacked, act_scale, w_scale, bias, Y, _TORCH_DT[out_dtype], out_scale, M, N, K, _epi(bias, gelu))
     return Y
 
@@ -412,7 +420,7 @@ def spgemm_int8_xf16(X, Wpacked, N, act_scale, w_scale, bias=None, gelu=False, o
     """X fp16 [M,K], quantised inside the GEMM with the static act_scale (small kernels only: raises GpusqError with
     ERR_UNSUPPORTED for problems of whole K steps that are estimated to be faster on a tile kernel)"""
     M, K = X.shape
-    Y = torch.empty((M, N), dtype=out_dtype, device=X.device) if out is None else out
+    Y = _empty(X, out_dtype, M, N) if out is None else out
     calls.gpusq_spgemm_int8_xf16(X, Wpacked, act_scale, w_scale, bias, Y, _TORCH_DT[out_dtype], out_scale, M, N, K, _epi(bias, gelu))
     return Y
 
@@ -420,7 +428,7 @@ def spgemm_int8_xf16(X, Wpacked, N, act_scale, w_scale, bias=None, gelu=False, o
 def gemm_fp16_dense(X, W, bias=None, gelu=False, out=None):
     M, K = X.shape
     N = W.shape[0]
-    Y = torch.empty((M, N), dtype=torch.float16, device=X.device) if out is None else out
+    Y = _empty(X, torch.float16, M, N) if out is None else out
     calls.gpusq_gemm_fp16_dense(X, W, bias, Y, M, N, K, _epi(bias, gelu))
     return Y
 
@@ -429,6 +437,6 @@ def gemm_int8_dense(Xq, Wq, act_scale=None, w_scale=None, bias=None, gelu=False,
                     out=None):
     M, K = Xq.shape
     N = Wq.shape[0]
-    Y = torch.empty((M, N), dtype=out_dtype, device=Xq.device) if out is None else out
+    Y = _empty(Xq, out_dtype, M, N) if out is None else out
     calls.gpusq_gemm_int8_dense(Xq, Wq, act_scale, w_scale, bias, Y, _TORCH_DT[out_dtype], out_scale, M, N, K, _epi(bias, gelu))
     return Y

@@ -315,6 +315,56 @@ def test_walk_block_mlp_plans(tmp_path):
     assert run.returncode == 0 and run.stdout == "20000 plans\n", run.stdout
 
 
+def test_empty_of_the_extension_module_is_torch_empty():
+    torch = pytest.importorskip("torch")
+    from paper_2305_10727_amd import _fastcall
+    like = torch.zeros(3)
+    for dtype in (torch.float32, torch.float16, torch.int8, torch.uint8, torch.int32):
+        for sizes in ((5,), (0,), (4, 6), (1, 0), (2, 3, 4)):
+            t = _fastcall.empty(like, dtype, *sizes)
+            ref = torch.empty(sizes, dtype=dtype)
+            assert type(t) is torch.Tensor and t.shape == ref.shape and t.dtype == ref.dtype and t.device == ref.device and t.stride() == ref.stride()
+            assert not t.requires_grad
+    assert _fastcall.empty(torch.nn.Parameter(like), torch.int8, 2).requires_grad is False
+    with torch.inference_mode():
+        assert _fastcall.empty(like, torch.int8, 2).is_inference()
+    with pytest.raises(RuntimeError):
+        _fastcall.empty(like, torch.int8, -1)
+    for wrong in ((None, torch.int8, 2), (like, "int8", 2), (like, torch.int8), (like, torch.int8, 1, 1, 1, 1, 1), (like, torch.int8, 1.5)):
+        with pytest.raises(TypeError):
+            _fastcall.empty(*wrong)
+
+
+def test_calls_take_the_address_of_a_tensor_and_of_what_acts_like_one():
+    """A tensor, a parameter, a subclass, an object with data_ptr(), an integer and None, checked and not"""
+    import ctypes
+    torch = pytest.importorskip("torch")
+    from paper_2305_10727_amd import _fastcall
+    met = []
+    c_function = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_uint64)(lambda p: met.append(p) or 0)
+    address = ctypes.cast(c_function, ctypes.c_void_p).value
+    unchecked, checked = (_fastcall.FastCall("f", address, sig, True) for sig in ("p", "t"))
+    x = torch.zeros((6, 8), dtype=torch.int8)
+
+    class Sub(torch.Tensor):
+        pass
+
+    class Acts:
+        def data_ptr(self):
+            return x.data_ptr()
+
+    for v in (x, x[:3], torch.nn.Parameter(x, requires_grad=False), x.as_subclass(Sub), Acts(), x.data_ptr(), x[1:], x.t(), None):
+        unchecked(v)
+    assert met == [x.data_ptr()] * 6 + [x.data_ptr() + 8, x.data_ptr(), 0]
+    checked(None)
+    for v in (x, x.as_subclass(Sub)):  # (not on the GPU)
+        with pytest.raises(ValueError):
+            checked(v)
+    with pytest.raises((TypeError, AttributeError)):
+        unchecked("x")
+    assert met[9:] == [0]
+
+
 # few rows and small operands; few rows of large ones; many; beyond 512 channels; no whole 64 channels; few slabs to LDS, one round and more; invalid
 @pytest.mark.parametrize("M,D,H,launches", [(197, 192, 768, 1), (197, 512, 2048, 3), (12544, 512, 2048, 1), (12608, 768, 3072, 3), (4000, 208, 832, 3),
                                             (4492, 448, 3584, 1), (17053, 384, 3072, 3), (0, 512, 2048, 0), (16, 24, 96, 0)])
