@@ -270,6 +270,16 @@ int gpusq_linear_int8_quantiser(gpusq_dtype x_dt, gpusq_dtype out_dt, int64_t M,
 gpusq_status gpusq_im2col_patches(const void* img, void* X, gpusq_dtype dt, int64_t B, int64_t C, int64_t H, int64_t W,
                                   int64_t P, int64_t K_pad, void* stream);
 
+/* The fp16 layer from images to tokens in one call: what gpusq_im2col_patches and gpusq_spgemm_fp16 give, in one launch that cuts the patches in
+ * LDS where that is ahead (even P other than 16, D % 64 == 0, many patches), else by these two.
+ *   img, X [B*(H/P)*(W/P)][K_pad], sizes and errors as there, epilogue and Y [B*(H/P)*(W/P)][D] as for gpusq_spgemm_fp16.  X is
+ *   scratch: it holds the flattened patches afterwards where there were two launches, and is left as it is otherwise. */
+gpusq_status gpusq_patch_embed_fp16(const void* img, const void* Wpacked, const float* bias, void* Y, void* X, int64_t B, int64_t C,
+                                    int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D, int epilogue, void* stream);
+/* Its launches on a device with `cus` compute units (cus <= 0: the current device): 1 or 2; 0 for invalid sizes.  (2 whatever the sizes where Y
+ * overlaps the images.)  Host-side. */
+int gpusq_patch_embed_fp16_launches(int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D, int epilogue, int cus);
+
 /* The same layer without the flattened-patch buffer, for P = 16: the sparse GEMM fetches its activation tiles from the
  * images directly (for P = 16 a 16-byte piece of a flattened patch is 16 consecutive pixels of one image row).
  *   img [B][C][H][W] int8 (quantised with gpusq_quantize_int8, scale act_scale[0]) or fp16; Wpacked from
@@ -308,8 +318,8 @@ gpusq_status gpusq_spgemm_plan(gpusq_dtype dt, int64_t M, int64_t N, int64_t K, 
 /* Testing aid: kernel = 0 (64 x 64 tiles), 1, 2, 3 or 4 (few rows, shown as 0 by gpusq_spgemm_plan) makes the sparse GEMM entry
  * points (and gpusq_spgemm_plan's out[0]) take that kernel for every problem it can run (kernel 3 needs K * element size % 128 == 0), so that every kernel can be checked on
  * the same shapes; 0 and 1 also keep the dense twins on their small kernel; any other value gives the choice back to the
- * size rules.  5: the size rules, but gpusq_linear_int8 takes its kernel for many rows of few channels at every size it can (0 to 4: at none).  6: the size rules, but gpusq_block_mlp_int8 is one launch at every size it can (0 to 4:
- * at none).
+ * size rules.  5: the size rules, but gpusq_linear_int8 takes its kernel for many rows of few channels at every size it can (0 to 4: at none).  6: the size rules, but gpusq_block_mlp_int8 and
+ * gpusq_patch_embed_fp16 are one launch at every size they can (0 to 4: at none).
  * Returns the previous setting (-1 = none).  Process-wide; the environment variable GPUSQ_FORCE_KERNEL (0..6)
  * gives the initial setting and is read once, when the library is loaded.  Not meant for production callers. */
 int gpusq_force_kernel(int kernel);

@@ -7,7 +7,7 @@ import sysconfig
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgpusq.so")
-SOURCES = ["api.hip", "prep.hip", "int4.hip", "spgemm.hip", "fewrows.hip", "wide.hip", "mlp.hip", "tile1_i8.hip", "tile1_f16.hip",
+SOURCES = ["api.hip", "prep.hip", "int4.hip", "spgemm.hip", "fewrows.hip", "wide.hip", "mlp.hip", "patches.hip", "tile1_i8.hip", "tile1_f16.hip",
            "tile1_i8_ragged.hip", "tile1_f16_ragged.hip", "tile2.hip", "dense.hip"]
 # Python's side of the binding: a host-only extension module beside the library (no GPU code, so the host compiler)
 FASTCALL = os.path.join(HERE, "_fastcall" + sysconfig.get_config_var("EXT_SUFFIX"))

@@ -235,16 +235,41 @@ gpusq_status gpusq_prepare_weights(const float* W, gpusq_dtype dt, float* W_prun
   return launch_prepare_weights(W, dt, W_pruned, W_low, w_scale, values, meta, packed, N, K, (hipStream_t)stream);
 }
 
-gpusq_status gpusq_im2col_patches(const void* img, void* X, gpusq_dtype dt, int64_t B, int64_t C, int64_t H, int64_t W,
-                                  int64_t P, int64_t K_pad, void* stream) {
-  if (!img || !X) return GPUSQ_ERR_NULL;
+// Sizes of images and of the flattened patches they are cut into
+static gpusq_status check_patches(int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad) {
   if (B <= 0 || C <= 0 || H <= 0 || W <= 0 || P <= 0 || H % P != 0 || W % P != 0) return GPUSQ_ERR_SHAPE;
   if (C > 65536 || P > 4096 || H > (1 << 20) || W > (1 << 20)) return GPUSQ_ERR_SHAPE;
   if (C * P * P > INT32_MAX || K_pad < C * P * P || K_pad > INT32_MAX) return GPUSQ_ERR_SHAPE;
   if (B * C * H * W > kMaxElems || B * (H / P) * (W / P) * K_pad > kMaxElems) return GPUSQ_ERR_SHAPE;
+  return GPUSQ_OK;
+}
+
+gpusq_status gpusq_im2col_patches(const void* img, void* X, gpusq_dtype dt, int64_t B, int64_t C, int64_t H, int64_t W,
+                                  int64_t P, int64_t K_pad, void* stream) {
+  if (!img || !X) return GPUSQ_ERR_NULL;
+  const gpusq_status st = check_patches(B, C, H, W, P, K_pad);
+  if (st != GPUSQ_OK) return st;
   if (dt != GPUSQ_F16 && dt != GPUSQ_I8) return GPUSQ_ERR_UNSUPPORTED;
   if (!aligned16(img) || !aligned16(X)) return GPUSQ_ERR_ALIGN;
   return launch_im2col_patches(img, X, dt, B, C, H, W, P, K_pad, (hipStream_t)stream);
+}
+
+gpusq_status gpusq_patch_embed_fp16(const void* img, const void* Wpacked, const float* bias, void* Y, void* X, int64_t B, int64_t C, int64_t H,
+                                    int64_t W, int64_t P, int64_t K_pad, int64_t D, int epilogue, void* stream) {
+  if (!img) return GPUSQ_ERR_NULL;
+  gpusq_status st = check_patches(B, C, H, W, P, K_pad);
+  if (st != GPUSQ_OK) return st;
+  const int64_t M = B * (H / P) * (W / P);
+  st = check_gemm(X, Wpacked, bias, Y, M, D, K_pad, epilogue);
+  if (st != GPUSQ_OK) return st;
+  if (!aligned16(img)) return GPUSQ_ERR_ALIGN;
+  GemmArgs a{X, Wpacked, nullptr, nullptr, bias, nullptr, Y, (int)M, (int)D, (int)K_pad, epilogue, (int)GPUSQ_F16};
+  return launch_patch_embed_f16(a, img, B, C, H, W, P, (hipStream_t)stream);
+}
+
+int gpusq_patch_embed_fp16_launches(int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D, int epilogue, int cus) {
+  if (check_patches(B, C, H, W, P, K_pad) != GPUSQ_OK || check_nk(D, K_pad) != GPUSQ_OK || K_pad % 16 != 0 || D % 4 != 0) return 0;
+  return patch_embed_f16_launches(B, C, H, W, P, K_pad, D, epilogue, cus);
 }
 
 // Checks and arguments of the patch embeddings (img: of elements of `size` bytes)

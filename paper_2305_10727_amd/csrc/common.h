@@ -446,6 +446,9 @@ struct MlpArgs {
 bool mlp_in_one_launch(const MlpArgs& a);
 int mlp_launches(int64_t M, int64_t D, int64_t H, int cus);
 gpusq_status launch_mlp(const MlpArgs& a, hipStream_t s);
+// a patch embedding on fp16 images in one launch (patches.hip), or by flattened patches in a.X and the GEMM
+gpusq_status launch_patch_embed_f16(GemmArgs a, const void* img, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, hipStream_t s);
+int patch_embed_f16_launches(int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D, int epilogue, int cus);
 int num_cus();                      // of the current device
 // quantise (dt of X, workspace as for launch_quantize) and multiply: one, two or three launches
 gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, void* workspace, hipStream_t s);

@@ -318,7 +318,7 @@ __global__ void __launch_bounds__(F == 4 || KS < 3 ? 512 : 768, F == 4 ? 2 : (KS
 // 3584 47.6 / 41.3), more are not (17053 x 384, 3072 82.9 / 92.8).
 static MlpPlan mlp_plan_where_ahead(int64_t M, int64_t D, int64_t H, int resident) {
   const int forced = forced_kernel();
-  if ((forced >= 0 && forced != 6) || !mlp_takes_sizes(D, H)) return MlpPlan{};
+  if ((forced >= 0 && forced < 5) || !mlp_takes_sizes(D, H)) return MlpPlan{};
   const MlpPlan p = mlp_plan(M, D, H, resident);
   const int64_t operands = (D * D + 2 * D * H) * 5 / 8;
   if (forced == 6 || ((operands <= 460 * 1000 || M * 550 >= operands) && (p.chunks <= resident || mlp_lds(D, H, kMlpSlabs) <= kMlpLds))) return p;

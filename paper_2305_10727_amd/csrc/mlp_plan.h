@@ -5,9 +5,6 @@
 
 #include "launch_rules.h"
 
-#ifndef MLPF4
-#define MLPF4 4
-#endif
 namespace gpusq {
 
 constexpr int kMlpSlabs = 4;   // 16-row slabs of a workgroup at most

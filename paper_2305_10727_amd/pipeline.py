@@ -132,12 +132,15 @@ class SparsePatchEmbed:
     gpusq_im2col_patches, then multiplied by gpusq_spgemm_*; with P = 16 (and a problem large enough for the tile kernel)
     gpusq_patch_embed16_* lets the GEMM gather the patches itself (fused=True, the default where it applies: it saves
     the im2col pass, most on the fp16 path, where a patch row is 32 contiguous bytes; a 16-byte piece of an int8 patch
-    row touches a cache line of its own, which gives part of the saving back)."""
+    row touches a cache line of its own, which gives part of the saving back).  Other fp16 patches are one call,
+    gpusq_patch_embed_fp16, which cuts them in LDS where its sizes favour it; X, which holds flattened patches, is then not
+    written.  fused=False: the two calls whatever the sizes."""
 
     def __init__(self, B, C, H, W, P, D, precision="int8", bias=True, device="cuda", fused=None):
         self.shape = (B, C, H, W)
         can_fuse = P == 16 and B * (H // P) * (W // P) * D > 256 * 1024
         self.fused = can_fuse if fused is None else (fused and can_fuse)
+        self.one_call = precision == "fp16" and not self.fused and fused is not False
         self.P, self.D, self.precision = P, D, precision
         self.K = C * P * P
         step = 128 if precision == "int8" else 64  # whole 128-byte K steps: the tile kernel's requirement
@@ -175,6 +178,10 @@ class SparsePatchEmbed:
         if self.fused:
             lin = self.linear
             _call.gpusq_patch_embed16_fp16(src, lin.packed, bias, lin.Y, B, C, H, W, self.D, lin.epilogue & G.EPI_BIAS)
+            return lin.Y
+        if self.one_call:
+            lin = self.linear
+            _call.gpusq_patch_embed_fp16(src, lin.packed, bias, lin.Y, self.X, B, C, H, W, self.P, self.K_pad, self.D, lin.epilogue)
             return lin.Y
         _call.gpusq_im2col_patches(src, self.X, dt, B, C, H, W, self.P, self.K_pad)
         if self.precision == "int8":

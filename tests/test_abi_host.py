@@ -315,6 +315,50 @@ def test_walk_block_mlp_plans(tmp_path):
     assert run.returncode == 0 and run.stdout == "20000 plans\n", run.stdout
 
 
+def test_walk_patch_embedding_plans(tmp_path):
+    """The plans of the kernel for patch embeddings, and where it keeps their values, walked on the host with the code the kernel uses (patches_plan_walk.cpp)"""
+    exe = str(tmp_path / "walk")
+    build = subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                            "-I", os.path.join(ROOT, "paper_2305_10727_amd", "csrc"), os.path.join(ROOT, "tests", "patches_plan_walk.cpp"), "-o", exe],
+                           capture_output=True, text=True)
+    assert build.returncode == 0, build.stderr
+    run = subprocess.run([exe, "20000"], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0 and run.stdout == "20000 plans\n", run.stdout
+
+
+@pytest.mark.parametrize("sizes,launches", [
+    ((256, 3, 224, 224, 14, 640, 1280, 1), 1), ((3, 3, 224, 224, 14, 592, 512, 0), 1), ((64, 3, 224, 224, 14, 640, 2048, 1), 1),
+    ((2, 3, 224, 224, 14, 640, 128, 1), 2),     # fewer than 640 patches
+    ((12, 3, 224, 224, 14, 640, 1088, 1), 2),   # too few for the weights: 3072 patches, 1088 channels
+    ((64, 3, 252, 252, 18, 976, 512, 1), 1), ((64, 3, 252, 252, 18, 976, 576, 1), 2),  # LDS for two slabs: up to 512 channels,
+    ((10, 3, 252, 252, 18, 976, 512, 1), 2),                                           # from 2048 patches on
+    ((64, 3, 224, 224, 28, 2368, 192, 1), 2),   # LDS for one slab
+    ((64, 3, 224, 224, 16, 768, 768, 1), 2), ((4, 3, 224, 224, 16, 768, 192, 1), 1),  # 16-byte pieces: gpusq_patch_embed16_fp16, from 2^18 outputs on
+    ((64, 3, 225, 225, 15, 704, 768, 1), 2),    # no pairs of pixels
+    ((64, 3, 224, 224, 14, 640, 776, 1), 2),    # part of a block of channels
+    ((64, 3, 224, 224, 14, 640, 768, 3), 2),    # GELU
+    ((2, 3, 32760, 32760, 14, 640, 768, 1), 2), # images of 4 GiB or more
+    ((1, 3, 225, 224, 14, 640, 768, 1), 0), ((1, 3, 224, 224, 14, 580, 768, 1), 0), ((1, 3, 224, 224, 14, 640, 770, 1), 0), ((0, 3, 224, 224, 14, 640, 768, 1), 0)])
+def test_patch_embedding_launches(sizes, launches):
+    from paper_2305_10727_amd import gpusq
+    assert gpusq.lib().gpusq_patch_embed_fp16_launches(*sizes, 256) == launches
+
+
+def test_patch_embedding_argument_checks(lib):
+    ERR_NULL, ERR_SHAPE, ERR_ALIGN, ERR_UNSUPPORTED = 1, 2, 3, 4
+    vp, i64, ci = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int
+    lib.gpusq_patch_embed_fp16.argtypes = [vp] * 5 + [i64] * 7 + [ci, vp]
+    call = lambda img=16, W=16, bias=16, Y=16, X=16, B=1, C=3, H=28, Wd=28, P=14, K_pad=592, D=64, epi=1: lib.gpusq_patch_embed_fp16(
+        img, W, bias, Y, X, B, C, H, Wd, P, K_pad, D, epi, None)
+    for missing in ("img", "W", "bias", "Y", "X"):
+        assert call(**{missing: None}) == ERR_NULL
+        assert call(**{missing: 24}) == ERR_ALIGN
+    for wrong in (dict(B=0), dict(H=27), dict(Wd=30), dict(P=0), dict(K_pad=576), dict(D=0), dict(C=70000)):
+        assert call(**wrong) == ERR_SHAPE
+    for wrong in (dict(epi=4), dict(K_pad=596), dict(D=66)):
+        assert call(**wrong) == ERR_UNSUPPORTED
+
+
 def test_empty_of_the_extension_module_is_torch_empty():
     torch = pytest.importorskip("torch")
     from paper_2305_10727_amd import _fastcall
