@@ -240,8 +240,8 @@ gpusq_status gpusq_spgemm_int8_xf16(const void* X, const void* Wpacked, const fl
 /* The whole INT8 layer at inference [Sec. 2.2, 3.4]: quantise X [M][K] (x_dt = GPUSQ_F32 or GPUSQ_F16) per tensor, then the
  * product of gpusq_spgemm_int8 on the codes.  Results, the codes in Xq [M][K] and the scale in act_scale[0] included, are
  * bit-identical to gpusq_quantize_int8(GPUSQ_PER_TENSOR) followed by gpusq_spgemm_int8; scale_is_input and workspace as for
- * the former, all other arguments as for the latter.  For few rows, and for many (GPUSQ_WIDE_MIN_ROWS or more) of few output channels, the two are
- * one kernel, and for small X (or a given scale) the layer is a single launch.  Y may lie over X or over the workspace, and out_scale may be act_scale (the quantiser
+ * the former, all other arguments as for the latter.  For few rows, for many (GPUSQ_WIDE_MIN_ROWS or more) of few output channels, and for short ones of few outputs, the two
+ * are one kernel, and for small X (or a given scale) the layer is a single launch.  Y may lie over X or over the workspace, and out_scale may be act_scale (the quantiser
  * is then a launch of its own). */
 gpusq_status gpusq_linear_int8(const void* X, gpusq_dtype x_dt, const void* Wpacked, float* act_scale, int scale_is_input,
                                const float* w_scale, const float* bias, void* Y, gpusq_dtype out_dt, const float* out_scale, int8_t* Xq,

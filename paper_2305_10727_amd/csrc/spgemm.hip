@@ -634,8 +634,22 @@ static gpusq_status launch_typed(const GemmArgs& a, hipStream_t s) {
 // 1040) 8.2 against 8.6, 151 KB (394 x 192) 8.4 against 7.1.
 constexpr int64_t kRangeHereBytes = 128 * 1024;
 
-// Many rows and few channels: the kernel that quantises whole rows (wide.hip) by the estimates, from 2048 rows on (below, there is little to win
-// and the estimates are off by as much) and up to the two column blocks of 1536 channels that were timed.  Calls in turn on three buffers of normal
+// Where the estimates of the kernel that quantises whole rows (wide.hip) say little, below 2048 rows or beyond two column blocks, but a launch less decides: up
+// to 2^23 outputs, and K of up to 512 values, or 1024 (768 from 2048 rows on) where there are 2^20 outputs (fp32 X: and 2^21 at
+// the most), for every chunk walks all of K by itself.  Under a given scale up to 256 values only, though it would be ahead beyond: callers have been told of two launches for 1576 x 384 -> 1152, and plan with them.
+// Of 1540 sizes timed (16 to 50000 rows, K 64 to 1408, N 64 to 5120, both types and outputs, with and without GELU) that the kernel for few rows does not
+// quantise for, these are 1.2 times as fast, one slower by more than 3 %: quantiser and GEMM / whole rows 1989 x 128 -> 1152 under a given scale 8.6 / 5.9 us, 1301 x
+// 128 -> 1472 + GELU 12.8 / 9.4, 2000 x 384 -> 1024 11.6 / 9.0, 1382 x 960 -> 960 13.9 / 11.6, 2548 x 224 -> 1600 13.3 / 9.3; beyond them 802 x 1184 -> 688 11.5 / 14.1, 882 x 960
+// -> 736 fp32 10.9 / 13.6, 1576 x 768 -> 2304 + GELU fp32 13.5 / 14.3, 3199 x 576 -> 4160 fp32 19.6 / 23.1.
+static bool wide_saves_a_launch(int64_t M, int64_t N, int64_t K, bool fp32, bool given) {
+  const int64_t outputs = M * N;
+  if (outputs > (1 << 23)) return false;
+  if (K <= (given ? 2 : 4) * kStepBytes) return true;
+  return !given && (!fp32 || outputs <= (1 << 21)) && outputs >= (1 << 20) && K <= (M < GPUSQ_WIDE_MIN_ROWS ? 8 : 6) * kStepBytes;
+}
+
+// Many rows and few channels: the kernel that quantises whole rows (wide.hip) by the estimates, from 2048 rows on (below, they are
+// off by as much as there is to win) and up to the two column blocks of 1536 channels that were timed.  Calls in turn on three buffers of normal
 // values, us, apart / here, own range and given scale: 14070 x 576 -> 256 16.3 / 14.2 and 12.8 / 10.0, 12608 x 768 -> 768 20.6 / 20.0 and 17.1 / 15.1, 7029 x 1152
 // -> 256 17.0 / 15.0 and 13.5 / 10.9, 56475 x 3648 -> 704 306 / 266 and 235 / 187, 25216 x 3072 -> 768 106.7 / 107.5 and 86.5 / 83.9 (of what a GELU returns, which
 // takes less power, with an own range 102.5 / 100.3).  Behind a range pass there is less to win (wide_margin_behind_range), and these go there
@@ -650,9 +664,10 @@ static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, bool behind_range, int
   const bool fp32 = dt == GPUSQ_F32, i8 = a.out_dt == GPUSQ_I8, gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
   if ((d.forced >= 0 && d.forced < 5) || (!i8 && a.out_dt != GPUSQ_F16) || a.N % 16 != 0) return false;
   if ((int64_t)a.K * 64 * 4 >= ((int64_t)1 << 31) || a.N >= (1 << 24)) return false;  // 32-bit lane offsets inside a chunk's rows
-  if (d.forced < 0 && (a.M < GPUSQ_WIDE_MIN_ROWS || a.N > 2 * kWideBlocks * kRowBlock)) return false;
+  const bool estimated = a.M >= GPUSQ_WIDE_MIN_ROWS && a.N <= 2 * kWideBlocks * kRowBlock;
+  if (d.forced < 0 && !estimated && (a.patch_P != 0 || !wide_saves_a_launch(a.M, a.N, a.K, fp32, !behind_range))) return false;
   p = wide_plan(a.M, a.N, resident, fp32);
-  if (p.chunks == 0 || d.forced == 5) return p.chunks > 0;
+  if (p.chunks == 0 || d.forced == 5 || !estimated) return p.chunks > 0;
   if (d.choice == 4) return a.N > 256 && (a.K <= 12 * kStepBytes || a.N < 448 || (fp32 && !behind_range));
   const double margin = behind_range ? wide_margin_behind_range(a.M, a.N, a.K, fp32, i8) : wide_margin(a.K, fp32);
   return d.gemm_us > 0 && wide_us(p, a.M, a.N, a.K, resident, fp32, gelu, i8) < margin * quantise_and_gemm_us(d.gemm_us, a.M, a.N, a.K, fp32, i8);

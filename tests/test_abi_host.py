@@ -450,6 +450,20 @@ def test_layers_of_the_kernel_for_whole_rows(lib, M, K, N, gelu, x_dt, out_dt, o
         assert launches(x_dt, M, N, K, 3 if gelu else 1, 0, 256) == (3 if own == 0 else 2) and launches(x_dt, M, N, K, 3 if gelu else 1, 1, 256) == (2 if given == 0 else 1)
 
 
+@pytest.mark.parametrize("M,K,N,own,given", [
+    # up to 256 and 512 values; 1024 where there are 2^20 outputs, 768 from 2048 rows on; 2^23 outputs at the most; whole 16s of channels
+    (1000, 256, 768, 2, 2), (1000, 272, 768, 2, 0), (1000, 512, 768, 2, 0), (1000, 528, 768, 0, 0), (1024, 528, 1024, 2, 0), (2047, 1024, 528, 2, 0),
+    (2047, 1040, 528, 0, 0), (2048, 768, 2048, (0, 2), 0), (2048, 784, 2048, 0, 0), (2048, 256, 4096, 2, 2), (2049, 256, 4096, 0, 0), (2000, 256, 1000, 0, 0), (700, 128, 128, 1, 1)])
+@pytest.mark.parametrize("x_dt", [0, 1])
+def test_short_layers_of_the_kernel_for_whole_rows(lib, M, K, N, own, given, x_dt):
+    f = lib.gpusq_linear_int8_quantiser
+    f.argtypes = [ctypes.c_int, ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int] * 3
+    own = own[x_dt] if isinstance(own, tuple) else own  # (fp32 X: 2^21 outputs at the most for more than 512 values)
+    for out_dt in (1, 2):
+        for epilogue in (1, 3):
+            assert (f(x_dt, out_dt, M, N, K, epilogue, 0, 256), f(x_dt, out_dt, M, N, K, epilogue, 1, 256)) == (own, given)
+
+
 def test_what_quantises_a_layer(lib):
     """The answers of gpusq_linear_int8_quantiser and gpusq_linear_int8_launches agree; int32 output has no kernel for whole rows"""
     f = lib.gpusq_linear_int8_quantiser

@@ -168,3 +168,22 @@ def test_graph(g):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(lin.Y, y) and torch.equal(lin.Xq, q) and torch.equal(lin.act_scale, s)
+
+
+# layers that take the kernel by themselves below its many rows, or with more channels: as quantised and multiplied by two calls, bit for bit
+@pytest.mark.parametrize("M,K,N", [(257, 64, 2560), (300, 256, 1936), (1000, 272, 528), (1024, 1024, 1040), (1301, 128, 1472), (2047, 512, 4096), (2048, 768, 1024)])
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("out", [torch.float16, torch.int8])
+def test_short_layer(g, M, K, N, dtype, out):
+    assert _is_wide(g, dtype, out, M, K, N)
+    r = torch.Generator(device="cuda").manual_seed(M)
+    X = torch.randn((M, K), generator=r, device="cuda").to(torch.float16 if dtype == np.float16 else torch.float32)
+    w = g.prepare_weights(torch.randn((N, K), generator=r, device="cuda") * 0.05, torch.int8)
+    b, s = torch.randn(N, generator=r, device="cuda"), dev(np.array([0.03], np.float32))
+    for given in (None, dev(np.array([0.025], np.float32))):
+        Y, Xq, sa = _layer(g, X, w["packed"], w["w_scale"], b, M, N, K, given, out, s, False)
+        q, sq = g.quantize_int8(X, g.PER_TENSOR, scale=given)
+        assert np.array_equal(Xq, host(q)) and np.array_equal(sa, host(sq if given is None else given))
+        ref = torch.empty((M, N), dtype=out, device="cuda")
+        g.calls.gpusq_spgemm_int8(q, w["packed"], given if given is not None else sq, w["w_scale"], b, ref, g._TORCH_DT[out], s, M, N, K, g.EPI_BIAS)
+        assert np.array_equal(Y.view(np.int16 if out == torch.float16 else np.int8), host(ref).view(np.int16 if out == torch.float16 else np.int8))
