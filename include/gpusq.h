@@ -318,7 +318,8 @@ gpusq_status gpusq_spgemm_plan(gpusq_dtype dt, int64_t M, int64_t N, int64_t K, 
 /* Testing aid: kernel = 0 (64 x 64 tiles), 1, 2, 3 or 4 (few rows, shown as 0 by gpusq_spgemm_plan) makes the sparse GEMM entry
  * points (and gpusq_spgemm_plan's out[0]) take that kernel for every problem it can run (kernel 3 needs K * element size % 128 == 0), so that every kernel can be checked on
  * the same shapes; 0 and 1 also keep the dense twins on their small kernel; any other value gives the choice back to the
- * size rules.  5: the size rules, but gpusq_linear_int8 takes its kernel for many rows of few channels at every size it can (0 to 4: at none).  6: the size rules, but gpusq_block_mlp_int8 and
+ * size rules.  5: the size rules, but gpusq_linear_int8 takes its kernel for many rows of few channels at every size it can (where
+ * N % 16 != 0, at those that its kernel for few rows does not; 0 to 4: at none).  6: the size rules, but gpusq_block_mlp_int8 and
  * gpusq_patch_embed_fp16 are one launch at every size they can (0 to 4: at none).
  * Returns the previous setting (-1 = none).  Process-wide; the environment variable GPUSQ_FORCE_KERNEL (0..6)
  * gives the initial setting and is read once, when the library is loaded.  Not meant for production callers. */

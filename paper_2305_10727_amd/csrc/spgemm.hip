@@ -658,11 +658,13 @@ static bool wide_saves_a_launch(int64_t M, int64_t N, int64_t K, bool fp32, bool
 // 20022 sizes so timed (M 2048 ... 65792, K 64 ... 5120, N 32 ... 1536, both types and outputs, with and without GELU) it takes 68 % of the fp16 ones with an
 // own range, 1.15 times as fast there, and 70 % under a given scale, 1.22 times; 49 and 58 % of the fp32 ones, 1.08 and 1.20 times.  2 % of those with an own range
 // and 0.7 % of the others are slower by more than 5 % (8094 x 4608 -> 768 + GELU, int8 output, 59.3 / 66.5; 52052 x 640 -> 1440 under a given scale 67.5 / 79.3).
+// Rows of Y that are no whole 16 channels are stored by four, and the rules are the same: of 218 such sizes they take 1.15 times as fast, 4 slower by more than 3 %
+// (12608 x 768 -> 772 27.6 / 23.7, 50000 x 384 -> 388 38.6 / 33.5, 1576 x 384 -> 1148 11.5 / 8.9; 29916 x 128 -> 1176 fp32, int8 output, under a given scale 27.8 / 29.8).
 // Where the product goes to the kernel for few rows (those have no estimate here) it is ahead beyond 256 channels: 1.1 to 1.3 times up to 12 K steps, 1.1 with
 // more of them up to 447 channels, from there on level or behind but for fp32 under a given scale (2085 x 3920 -> 640 24.7 / 27.8).
 static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, bool behind_range, int resident, const Decision& d, WidePlan& p) {
   const bool fp32 = dt == GPUSQ_F32, i8 = a.out_dt == GPUSQ_I8, gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
-  if ((d.forced >= 0 && d.forced < 5) || (!i8 && a.out_dt != GPUSQ_F16) || a.N % 16 != 0) return false;
+  if ((d.forced >= 0 && d.forced < 5) || (!i8 && a.out_dt != GPUSQ_F16)) return false;
   if ((int64_t)a.K * 64 * 4 >= ((int64_t)1 << 31) || a.N >= (1 << 24)) return false;  // 32-bit lane offsets inside a chunk's rows
   const bool estimated = a.M >= GPUSQ_WIDE_MIN_ROWS && a.N <= 2 * kWideBlocks * kRowBlock;
   if (d.forced < 0 && !estimated && (a.patch_P != 0 || !wide_saves_a_launch(a.M, a.N, a.K, fp32, !behind_range))) return false;
@@ -678,7 +680,7 @@ static int quantiser_of(const GemmArgs& a, gpusq_dtype dt, bool given, int resid
   const bool gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
   const bool few = fewrows_folds_quantiser(a.M, a.N, a.K, resident, dt == GPUSQ_F32) && fewrows_supports(a);
   const Decision& d = decide(true, a.M, a.N, a.K, gelu, resident, false);
-  if (d.forced == 5 && wide_takes(a, dt, !given, resident, d, p)) return GPUSQ_QUANTISE_WHOLE_ROWS;
+  if (d.forced == 5 && a.N % 16 == 0 && wide_takes(a, dt, !given, resident, d, p)) return GPUSQ_QUANTISE_WHOLE_ROWS;
   if (few && d.choice == 4) return GPUSQ_QUANTISE_FEW_ROWS;
   return wide_takes(a, dt, !given, resident, d, p) ? GPUSQ_QUANTISE_WHOLE_ROWS : GPUSQ_QUANTISE_APART;
 }

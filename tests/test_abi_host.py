@@ -451,9 +451,9 @@ def test_layers_of_the_kernel_for_whole_rows(lib, M, K, N, gelu, x_dt, out_dt, o
 
 
 @pytest.mark.parametrize("M,K,N,own,given", [
-    # up to 256 and 512 values; 1024 where there are 2^20 outputs, 768 from 2048 rows on; 2^23 outputs at the most; whole 16s of channels
+    # up to 256 and 512 values; 1024 where there are 2^20 outputs, 768 from 2048 rows on; 2^23 outputs at the most; rows of no whole 16 channels
     (1000, 256, 768, 2, 2), (1000, 272, 768, 2, 0), (1000, 512, 768, 2, 0), (1000, 528, 768, 0, 0), (1024, 528, 1024, 2, 0), (2047, 1024, 528, 2, 0),
-    (2047, 1040, 528, 0, 0), (2048, 768, 2048, (0, 2), 0), (2048, 784, 2048, 0, 0), (2048, 256, 4096, 2, 2), (2049, 256, 4096, 0, 0), (2000, 256, 1000, 0, 0), (700, 128, 128, 1, 1)])
+    (2047, 1040, 528, 0, 0), (2048, 768, 2048, (0, 2), 0), (2048, 784, 2048, 0, 0), (2048, 256, 4096, 2, 2), (2049, 256, 4096, 0, 0), (2000, 256, 1004, 2, 2), (700, 128, 128, 1, 1)])
 @pytest.mark.parametrize("x_dt", [0, 1])
 def test_short_layers_of_the_kernel_for_whole_rows(lib, M, K, N, own, given, x_dt):
     f = lib.gpusq_linear_int8_quantiser

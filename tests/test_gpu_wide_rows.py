@@ -170,8 +170,10 @@ def test_graph(g):
         assert torch.equal(lin.Y, y) and torch.equal(lin.Xq, q) and torch.equal(lin.act_scale, s)
 
 
-# layers that take the kernel by themselves below its many rows, or with more channels: as quantised and multiplied by two calls, bit for bit
-@pytest.mark.parametrize("M,K,N", [(257, 64, 2560), (300, 256, 1936), (1000, 272, 528), (1024, 1024, 1040), (1301, 128, 1472), (2047, 512, 4096), (2048, 768, 1024)])
+# layers that take the kernel by themselves below its many rows, or with more channels; rows of Y of no whole 16 channels, the last four in every place of a lane's
+# eight and of a wavefront's 64, two column blocks, chunks that end inside a slab: as quantised and multiplied by two calls, bit for bit
+@pytest.mark.parametrize("M,K,N", [(257, 64, 2560), (300, 256, 1936), (1000, 272, 528), (1024, 1024, 1040), (1301, 128, 1472), (2047, 512, 4096), (2048, 768, 1024),
+                                   (1000, 128, 644), (1003, 192, 780), (9001, 320, 72), (9001, 576, 76), (5001, 384, 1500), (14070, 576, 252), (30000, 448, 212)])
 @pytest.mark.parametrize("dtype", [np.float16, np.float32])
 @pytest.mark.parametrize("out", [torch.float16, torch.int8])
 def test_short_layer(g, M, K, N, dtype, out):
