@@ -667,7 +667,7 @@ static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, bool behind_range, int
   if ((d.forced >= 0 && d.forced < 5) || (!i8 && a.out_dt != GPUSQ_F16)) return false;
   if ((int64_t)a.K * 64 * 4 >= ((int64_t)1 << 31) || a.N >= (1 << 24)) return false;  // 32-bit lane offsets inside a chunk's rows
   const bool estimated = a.M >= GPUSQ_WIDE_MIN_ROWS && a.N <= 2 * kWideBlocks * kRowBlock;
-  if (d.forced < 0 && !estimated && (a.patch_P != 0 || !wide_saves_a_launch(a.M, a.N, a.K, fp32, !behind_range))) return false;
+  if (d.forced < 0 && !estimated && !wide_saves_a_launch(a.M, a.N, a.K, fp32, !behind_range && a.patch_P == 0)) return false;
   p = wide_plan(a.M, a.N, resident, fp32);
   if (p.chunks == 0 || d.forced == 5 || !estimated) return p.chunks > 0;
   if (d.choice == 4) return a.N > 256 && (a.K <= 12 * kStepBytes || a.N < 448 || (fp32 && !behind_range));
@@ -731,7 +731,8 @@ gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* s
 // The images in front of a patch embedding: the kernel for whole rows takes a product of its sizes as it takes a layer's under a given scale.  A
 // range pass does come first, but the kernels that gather patches take longer than a layer's, which makes up for it.  Of 403 sizes timed (72 to
 // 576 patches an image, 256 to 1024 values each, 192 to 1536 channels) it takes 238 of fp16, 1.19 times as fast, none slower, and 101 of fp32, 1.06 times, 8 %
-// slower at the most (29120 x 256 -> 1088; apart / here 62 images of 304 x 304 -> 704 41.2 / 37.4).
+// slower at the most (29120 x 256 -> 1088; apart / here 62 images of 304 x 304 -> 704 41.2 / 37.4).  Below 2048 patches the line for a layer with an own range is theirs
+// as well (1536 x 768 -> 832 13.4 / 10.3, 560 x 256 -> 640 10.9 / 8.4, 704 x 768 -> 640 fp32 10.9 / 12.1; 53 sizes 1.2 times as fast, none slower).
 gpusq_status launch_patch_embed_int8(GemmArgs a, gpusq_dtype dt, int8_t* img_q, float* scale, void* workspace, hipStream_t s) {
   const int resident = num_cus();
   const int choice = decide(true, a.M, a.N, a.K, false, resident, true).choice;

@@ -101,3 +101,18 @@ def test_refusals(g):
             g.calls.gpusq_patch_embed16_images(*args)
     torch.cuda.synchronize()
     assert (host(q) == 99).all()
+
+
+# fewer than 2048 patches, by themselves on the kernel for whole rows (one channel: 256 values; 2^20 outputs) and not
+@pytest.mark.parametrize("B,C,H,W,D", [(5, 1, 160, 192, 640), (1, 1, 336, 352, 576), (8, 3, 224, 224, 768), (5, 4, 240, 256, 900), (4, 3, 208, 176, 516)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+def test_few_images_are_the_quantiser_and_the_product(g, B, C, H, W, D, dtype):
+    r = torch.Generator(device="cuda").manual_seed(D)
+    img = torch.randn((B, C, H, W), generator=r, device="cuda").to(dtype)
+    w = g.prepare_weights(torch.randn((D, C * 256), generator=r, device="cuda") * 0.05, torch.int8)
+    b, M = torch.randn(D, generator=r, device="cuda"), B * (H // 16) * (W // 16)
+    q, s = g.quantize_int8(img.reshape(1, -1), g.PER_TENSOR)
+    ref = g.patch_embed16(q.reshape(B, C, H, W), w["packed"], D, act_scale=s, w_scale=w["w_scale"], bias=b)
+    Y, img_q, sa = torch.full((M, D), 7, dtype=torch.float16, device="cuda"), torch.full((B, C, H, W), 99, dtype=torch.int8, device="cuda"), torch.zeros(1, device="cuda")
+    g.calls.gpusq_patch_embed16_images(img, g._TORCH_DT[dtype], w["packed"], sa, w["w_scale"], b, Y, img_q, torch.empty(4096, dtype=torch.uint8, device="cuda"), B, C, H, W, D, g.EPI_BIAS)
+    assert torch.equal(img_q.reshape(-1), q.reshape(-1)) and torch.equal(sa, s.reshape(1)) and torch.equal(Y.view(torch.int16), ref.view(torch.int16))
