@@ -280,6 +280,14 @@ gpusq_status gpusq_patch_embed_fp16(const void* img, const void* Wpacked, const 
  * overlaps the images.)  Host-side. */
 int gpusq_patch_embed_fp16_launches(int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D, int epilogue, int cus);
 
+/* The int8 layer likewise, from fp16 or fp32 images (dt): bit-identical, the codes in img_q [B][C][H][W] and the scale in act_scale[0] included, to
+ * gpusq_quantize_int8(GPUSQ_PER_TENSOR) on the images (workspace as there), gpusq_im2col_patches and gpusq_spgemm_int8 to fp16; behind the range pass one
+ * launch where that is ahead, with the same conditions, else these.  X is scratch as above.  Launches: 2 or 4. */
+gpusq_status gpusq_patch_embed_int8(const void* img, gpusq_dtype dt, const void* Wpacked, float* act_scale, const float* w_scale, const float* bias,
+                                    void* Y, int8_t* img_q, void* X, void* workspace, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P,
+                                    int64_t K_pad, int64_t D, int epilogue, void* stream);
+int gpusq_patch_embed_int8_launches(gpusq_dtype dt, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D, int epilogue, int cus);
+
 /* The same layer without the flattened-patch buffer, for P = 16: the sparse GEMM fetches its activation tiles from the
  * images directly (for P = 16 a 16-byte piece of a flattened patch is 16 consecutive pixels of one image row).
  *   img [B][C][H][W] int8 (quantised with gpusq_quantize_int8, scale act_scale[0]) or fp16; Wpacked from
@@ -320,7 +328,7 @@ gpusq_status gpusq_spgemm_plan(gpusq_dtype dt, int64_t M, int64_t N, int64_t K, 
  * the same shapes; 0 and 1 also keep the dense twins on their small kernel; any other value gives the choice back to the
  * size rules.  5: the size rules, but gpusq_linear_int8 takes its kernel for many rows of few channels at every size it can (where
  * N % 16 != 0, at those that its kernel for few rows does not; 0 to 4: at none).  6: the size rules, but gpusq_block_mlp_int8 and
- * gpusq_patch_embed_fp16 are one launch at every size they can (0 to 4: at none).
+ * gpusq_patch_embed_fp16 are one launch, gpusq_patch_embed_int8 two, at every size they can (0 to 4: at none).
  * Returns the previous setting (-1 = none).  Process-wide; the environment variable GPUSQ_FORCE_KERNEL (0..6)
  * gives the initial setting and is read once, when the library is loaded.  Not meant for production callers. */
 int gpusq_force_kernel(int kernel);

@@ -267,6 +267,28 @@ gpusq_status gpusq_patch_embed_fp16(const void* img, const void* Wpacked, const 
   return launch_patch_embed_f16(a, img, B, C, H, W, P, (hipStream_t)stream);
 }
 
+gpusq_status gpusq_patch_embed_int8(const void* img, gpusq_dtype dt, const void* Wpacked, float* act_scale, const float* w_scale, const float* bias, void* Y,
+                                    int8_t* img_q, void* X, void* workspace, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D,
+                                    int epilogue, void* stream) {
+  if (!img || !act_scale || !w_scale || !img_q || !workspace) return GPUSQ_ERR_NULL;
+  if (dt != GPUSQ_F32 && dt != GPUSQ_F16) return GPUSQ_ERR_UNSUPPORTED;
+  gpusq_status st = check_patches(B, C, H, W, P, K_pad);
+  if (st != GPUSQ_OK) return st;
+  if (B * C * H * W > INT32_MAX) return GPUSQ_ERR_SHAPE;  // (the quantiser's columns)
+  const int64_t M = B * (H / P) * (W / P);
+  st = check_gemm(X, Wpacked, bias, Y, M, D, K_pad, epilogue);
+  if (st != GPUSQ_OK) return st;
+  if (!aligned16(img) || !aligned16(img_q) || !aligned16(workspace)) return GPUSQ_ERR_ALIGN;
+  GemmArgs a{X, Wpacked, act_scale, w_scale, bias, nullptr, Y, (int)M, (int)D, (int)K_pad, epilogue, (int)GPUSQ_F16};
+  return launch_patch_embed_i8(a, img, dt, img_q, act_scale, workspace, B, C, H, W, P, (hipStream_t)stream);
+}
+
+int gpusq_patch_embed_int8_launches(gpusq_dtype dt, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D, int epilogue, int cus) {
+  if (dt != GPUSQ_F32 && dt != GPUSQ_F16) return 0;
+  if (check_patches(B, C, H, W, P, K_pad) != GPUSQ_OK || check_nk(D, K_pad) != GPUSQ_OK || K_pad % 16 != 0 || D % 4 != 0 || B * C * H * W > INT32_MAX) return 0;
+  return patch_embed_i8_launches(dt, B, C, H, W, P, K_pad, D, epilogue, cus);
+}
+
 int gpusq_patch_embed_fp16_launches(int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D, int epilogue, int cus) {
   if (check_patches(B, C, H, W, P, K_pad) != GPUSQ_OK || check_nk(D, K_pad) != GPUSQ_OK || K_pad % 16 != 0 || D % 4 != 0) return 0;
   return patch_embed_f16_launches(B, C, H, W, P, K_pad, D, epilogue, cus);

@@ -449,6 +449,10 @@ gpusq_status launch_mlp(const MlpArgs& a, hipStream_t s);
 // a patch embedding on fp16 images in one launch (patches.hip), or by flattened patches in a.X and the GEMM
 gpusq_status launch_patch_embed_f16(GemmArgs a, const void* img, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, hipStream_t s);
 int patch_embed_f16_launches(int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D, int epilogue, int cus);
+// the int8 one: range pass and the same kernel, or quantiser, flattened patches in a.X and the GEMM
+gpusq_status launch_patch_embed_i8(GemmArgs a, const void* img, gpusq_dtype dt, int8_t* img_q, float* scale, void* workspace, int64_t B, int64_t C, int64_t H,
+                                   int64_t W, int64_t P, hipStream_t s);
+int patch_embed_i8_launches(gpusq_dtype dt, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D, int epilogue, int cus);
 int num_cus();                      // of the current device
 // quantise (dt of X, workspace as for launch_quantize) and multiply: one, two or three launches
 gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* scale, int scale_is_input, void* workspace, hipStream_t s);

@@ -24,8 +24,8 @@ __host__ __device__ inline uint32_t patch_lds_at(uint32_t kb, int r, uint32_t sw
 }
 
 // Whether the kernel takes the sizes: whole pairs of pixels, whole blocks of 64 channels, lane offsets of 32 bits inside the images
-inline bool patch_takes_sizes(int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D) {
-  return P % 2 == 0 && D % 64 == 0 && B * C * H * W * 2 < ((int64_t)1 << 32) && patch_lds(ceil_div(K_pad, 64), 1) <= kPatchLds;
+inline bool patch_takes_sizes(int x_bytes, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t ksteps, int64_t D) {
+  return P % 2 == 0 && D % 64 == 0 && B * C * H * W * x_bytes < ((int64_t)1 << 32) && patch_lds(ksteps, 1) <= kPatchLds;
 }
 // chunks == 0: none.  Workgroups as high as they go, for each reads all weights, but no higher than gives every CU one, or where that takes more than
 // the accumulators two (23040 x 588 -> 768 with 3 slabs 23.5 us, with 4 24.9); behind that round the chunks even out over the CUs by themselves, and the
@@ -34,9 +34,9 @@ inline int patch_slabs(int64_t ksteps) {
   const int64_t fit = kPatchLds / patch_lds(ksteps, 1);
   return (int)(fit < kPatchSlabs ? fit : kPatchSlabs);
 }
-inline PatchPlan patch_plan(int64_t M, int64_t K_pad, int64_t D, int resident) {
+inline PatchPlan patch_plan(int64_t M, int64_t ksteps, int64_t D, int resident) {
   PatchPlan p{};
-  const int64_t ksteps = ceil_div(K_pad, 64), slabs = ceil_div(M, 16);
+  const int64_t slabs = ceil_div(M, 16);
   const int most = patch_slabs(ksteps);
   if (most == 0) return p;
   const int64_t even = ceil_div(slabs, slabs <= (int64_t)most * resident ? resident : 2 * (int64_t)resident);

@@ -26,7 +26,8 @@ EXPORTS = [
     "gpusq_status_string", "gpusq_last_hip_error", "gpusq_version", "gpusq_prune_2to4", "gpusq_cast_f16",
     "gpusq_quantize_workspace_bytes",
     "gpusq_quantize_int8", "gpusq_compress", "gpusq_check_2to4", "gpusq_decompress", "gpusq_packed_bytes", "gpusq_pack", "gpusq_prepare_weights", "gpusq_spgemm_fp16",
-    "gpusq_spgemm_int8", "gpusq_spgemm_int8_codes", "gpusq_spgemm_int8_xf16", "gpusq_spgemm_plan", "gpusq_im2col_patches", "gpusq_patch_embed16_int8", "gpusq_patch_embed16_fp16", "gpusq_patch_embed16_images", "gpusq_patch_embed_fp16", "gpusq_patch_embed_fp16_launches", "gpusq_gemm_fp16_dense", "gpusq_gemm_int8_dense",
+    "gpusq_spgemm_int8", "gpusq_spgemm_int8_codes", "gpusq_spgemm_int8_xf16", "gpusq_spgemm_plan", "gpusq_im2col_patches", "gpusq_patch_embed16_int8", "gpusq_patch_embed16_fp16", "gpusq_patch_embed16_images", "gpusq_patch_embed_fp16", "gpusq_patch_embed_fp16_launches",
+    "gpusq_patch_embed_int8", "gpusq_patch_embed_int8_launches", "gpusq_gemm_fp16_dense", "gpusq_gemm_int8_dense",
     "gpusq_prune_4to8_pairs", "gpusq_quantize_rows_int4", "gpusq_compress_int4", "gpusq_decompress_int4",
     "gpusq_int4_to_sparse_int8", "gpusq_prune_n_of_m", "gpusq_force_kernel",
     "gpusq_quantize_tensor_int8_noalloc", "gpusq_linear_int8", "gpusq_linear_int8_launches", "gpusq_linear_int8_quantiser",
@@ -54,6 +55,7 @@ _SIGNATURES = {
     "gpusq_block_mlp_int8": "tttttttttttttttttiiis",
     "gpusq_im2col_patches": "ttiiiiiiis", "gpusq_patch_embed16_int8": "ttttttiiiiiis", "gpusq_patch_embed16_fp16": "ttttiiiiiis",
     "gpusq_patch_embed16_images": "titttttttiiiiiis", "gpusq_patch_embed_fp16": "tttttiiiiiiiis",
+    "gpusq_patch_embed_int8": "tittttttttiiiiiiiis",
     "gpusq_gemm_fp16_dense": "ttttiiiis", "gpusq_gemm_int8_dense": "ttttttitiiiis", "gpusq_prune_4to8_pairs": "tttiiis",
     "gpusq_quantize_rows_int4": "tittiiis", "gpusq_compress_int4": "ttttiis", "gpusq_decompress_int4": "tttiis",
     "gpusq_int4_to_sparse_int8": "tttttiis", "gpusq_prune_n_of_m": "ttiiiis",
@@ -159,6 +161,10 @@ def lib():
         L.gpusq_patch_embed16_fp16.argtypes = [vp, vp, vp, vp, i64, i64, i64, i64, i64, ci, vp]
         L.gpusq_patch_embed16_images.argtypes = [vp, ci, vp, vp, vp, vp, vp, vp, vp, i64, i64, i64, i64, i64, ci, vp]
         L.gpusq_patch_embed16_images.restype = ci
+        L.gpusq_patch_embed_int8.argtypes = [vp, ci] + [vp] * 8 + [i64] * 7 + [ci, vp]
+        L.gpusq_patch_embed_int8.restype = ci
+        L.gpusq_patch_embed_int8_launches.argtypes = [ci] + [i64] * 7 + [ci, ci]
+        L.gpusq_patch_embed_int8_launches.restype = ci
         L.gpusq_patch_embed_fp16.argtypes = [vp] * 5 + [i64] * 7 + [ci, vp]
         L.gpusq_patch_embed_fp16.restype = ci
         L.gpusq_patch_embed_fp16_launches.argtypes = [i64] * 7 + [ci, ci]

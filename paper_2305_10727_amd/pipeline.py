@@ -132,15 +132,15 @@ class SparsePatchEmbed:
     gpusq_im2col_patches, then multiplied by gpusq_spgemm_*; with P = 16 (and a problem large enough for the tile kernel)
     gpusq_patch_embed16_* lets the GEMM gather the patches itself (fused=True, the default where it applies: it saves
     the im2col pass, most on the fp16 path, where a patch row is 32 contiguous bytes; a 16-byte piece of an int8 patch
-    row touches a cache line of its own, which gives part of the saving back).  Other fp16 patches are one call,
-    gpusq_patch_embed_fp16, which cuts them in LDS where its sizes favour it; X, which holds flattened patches, is then not
+    row touches a cache line of its own, which gives part of the saving back).  Other patches are one call,
+    gpusq_patch_embed_fp16 / _int8, which cuts them in LDS where its sizes favour it; X, which holds flattened patches, is then not
     written.  fused=False: the two calls whatever the sizes."""
 
     def __init__(self, B, C, H, W, P, D, precision="int8", bias=True, device="cuda", fused=None):
         self.shape = (B, C, H, W)
         can_fuse = P == 16 and B * (H // P) * (W // P) * D > 256 * 1024
         self.fused = can_fuse if fused is None else (fused and can_fuse)
-        self.one_call = precision == "fp16" and not self.fused and fused is not False
+        self.one_call = not self.fused and fused is not False
         self.P, self.D, self.precision = P, D, precision
         self.K = C * P * P
         step = 128 if precision == "int8" else 64  # whole 128-byte K steps: the tile kernel's requirement
@@ -168,6 +168,12 @@ class SparsePatchEmbed:
             lin = self.linear
             _call.gpusq_patch_embed16_images(img, G._TORCH_DT[img.dtype], lin.packed, lin.act_scale, lin.w_scale, bias, lin.Y, self.img_q, self.workspace,
                                              B, C, H, W, self.D, lin.epilogue & G.EPI_BIAS)
+            return lin.Y
+        if self.precision == "int8" and self.one_call:
+            lin = self.linear
+            lin.Xq = self.X
+            _call.gpusq_patch_embed_int8(img, G._TORCH_DT[img.dtype], lin.packed, lin.act_scale, lin.w_scale, bias, lin.Y, self.img_q, self.X, self.workspace,
+                                         B, C, H, W, self.P, self.K_pad, self.D, lin.epilogue)
             return lin.Y
         if self.precision == "int8":
             _call.gpusq_quantize_int8(img, G._TORCH_DT[img.dtype], self.img_q, self.linear.act_scale, G.PER_TENSOR, 0, 1,

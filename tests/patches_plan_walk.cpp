@@ -15,8 +15,9 @@
 using namespace gpusq;
 
 static const char* walk(int64_t M, int64_t K_pad, int64_t D, int cus, bool every_byte) {
-  const PatchPlan p = patch_plan(M, K_pad, D, cus);
-  if (p.chunks == 0) return patch_lds(ceil_div(K_pad, 64), 1) > kPatchLds ? nullptr : "no plan";
+  const int64_t ksteps = ceil_div(K_pad, 64);
+  const PatchPlan p = patch_plan(M, ksteps, D, cus);
+  if (p.chunks == 0) return patch_lds(ksteps, 1) > kPatchLds ? nullptr : "no plan";
   if (p.slabs < 1 || p.slabs > kPatchSlabs) return "height";
   if ((int64_t)p.chunks * 16 * p.slabs < M || ((int64_t)p.chunks - 1) * 16 * p.slabs >= M) return "patches not covered, or a workgroup without one";
   if (p.units * 64 != D || p.ksteps * 64 < K_pad || (p.ksteps - 1) * 64 >= K_pad) return "units or K steps";

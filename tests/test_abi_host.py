@@ -344,6 +344,25 @@ def test_patch_embedding_launches(sizes, launches):
     assert gpusq.lib().gpusq_patch_embed_fp16_launches(*sizes, 256) == launches
 
 
+@pytest.mark.parametrize("sizes,launches", [
+    ((256, 3, 224, 224, 14, 640, 1280, 1), 2), ((1, 3, 14, 14, 14, 592, 512, 0), 2), ((2, 3, 56, 56, 8, 192, 256, 1), 2),
+    ((4, 3, 224, 224, 14, 640, 1088, 1), 4),    # too few for the weights: 1024 patches, 1088 channels
+    ((16, 3, 224, 224, 14, 640, 1536, 1), 4),   # beyond 1408 channels 6 patches for each from 512 on, not 2
+    ((64, 3, 224, 224, 16, 768, 768, 1), 4), ((64, 3, 252, 252, 18, 1024, 256, 1), 4),  # more than 14 rows
+    ((64, 9, 224, 224, 14, 1792, 192, 1), 4),   # LDS for fewer than three slabs
+    ((64, 3, 225, 225, 15, 704, 768, 1), 4), ((64, 3, 224, 224, 14, 640, 776, 1), 4), ((64, 3, 224, 224, 14, 640, 768, 3), 4),
+    ((2, 3, 32760, 32760, 14, 640, 768, 1), 0), # more pixels than the quantiser has columns
+    ((1, 3, 225, 224, 14, 640, 768, 1), 0), ((1, 3, 224, 224, 14, 640, 770, 1), 0)])
+def test_int8_patch_embedding_launches(sizes, launches):
+    from paper_2305_10727_amd import gpusq
+    for dt in (gpusq.F16, gpusq.F32):
+        assert gpusq.lib().gpusq_patch_embed_int8_launches(dt, *sizes, 256) == launches
+    assert gpusq.lib().gpusq_patch_embed_int8_launches(gpusq.I8, *sizes, 256) == 0
+    # fp32 images of 4 GiB or more
+    assert gpusq.lib().gpusq_patch_embed_int8_launches(gpusq.F16, 1, 3, 19600, 19600, 14, 640, 768, 1, 256) == 2
+    assert gpusq.lib().gpusq_patch_embed_int8_launches(gpusq.F32, 1, 3, 19600, 19600, 14, 640, 768, 1, 256) == 4
+
+
 def test_patch_embedding_argument_checks(lib):
     ERR_NULL, ERR_SHAPE, ERR_ALIGN, ERR_UNSUPPORTED = 1, 2, 3, 4
     vp, i64, ci = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int
@@ -357,6 +376,16 @@ def test_patch_embedding_argument_checks(lib):
         assert call(**wrong) == ERR_SHAPE
     for wrong in (dict(epi=4), dict(K_pad=596), dict(D=66)):
         assert call(**wrong) == ERR_UNSUPPORTED
+    lib.gpusq_patch_embed_int8.argtypes = [vp, ci] + [vp] * 8 + [i64] * 7 + [ci, vp]
+    call8 = lambda img=16, dt=1, W=16, sa=16, sw=16, bias=16, Y=16, q=16, X=16, ws=16, B=1, C=3, H=28, Wd=28, P=14, K_pad=592, D=64, epi=1: lib.gpusq_patch_embed_int8(
+        img, dt, W, sa, sw, bias, Y, q, X, ws, B, C, H, Wd, P, K_pad, D, epi, None)
+    for missing in ("img", "W", "sa", "sw", "bias", "Y", "q", "X", "ws"):
+        assert call8(**{missing: None}) == ERR_NULL
+        assert missing in ("sa", "sw") or call8(**{missing: 24}) == ERR_ALIGN
+    for wrong in (dict(B=0), dict(H=27), dict(P=0), dict(K_pad=576), dict(D=0), dict(H=28 * 1400, Wd=28 * 1400)):
+        assert call8(**wrong) == ERR_SHAPE
+    for wrong in (dict(epi=4), dict(K_pad=596), dict(D=66), dict(dt=2), dict(dt=3)):
+        assert call8(**wrong) == ERR_UNSUPPORTED
 
 
 def test_empty_of_the_extension_module_is_torch_empty():

@@ -1,0 +1,124 @@
+"""Patch embeddings on the int8 path in one call (gpusq_patch_embed_int8) against the three calls that it stands for, each of which is held against
+the oracle elsewhere: tokens, codes of the images and scale bit for bit."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import force_kernel, g  # noqa: F401
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _three(g, img, w, bias, P, K_pad, D):
+    B, C, H, W = img.shape
+    q, s = g.quantize_int8(img.reshape(1, -1), g.PER_TENSOR)
+    q = q.reshape(img.shape)
+    return g.spgemm_int8(g.im2col_patches(q, P, K_pad), w["packed"], D, act_scale=s, w_scale=w["w_scale"], bias=bias), q, s.reshape(1)
+
+
+def _one(g, img, w, bias, P, K_pad, D):
+    B, C, H, W = img.shape
+    M, n = B * (H // P) * (W // P), img.numel()
+    new = lambda shape, dt, v: torch.full(shape, v, dtype=dt, device="cuda")
+    Y, q, s, X = new((M, D), torch.float16, 7), new((B, C, H, W), torch.int8, 99), new((1,), torch.float32, 3), new((M, K_pad), torch.int8, 99)
+    ws = torch.empty(max(g.lib().gpusq_quantize_workspace_bytes(g.PER_TENSOR, 1, n), 16), dtype=torch.uint8, device="cuda")
+    g.calls.gpusq_patch_embed_int8(img, g._TORCH_DT[img.dtype], w["packed"], s, w["w_scale"], bias, Y, q, X, ws, B, C, H, W, P, K_pad, D, 0 if bias is None else g.EPI_BIAS)
+    return (Y, q, s), X
+
+
+def _same(one, three):
+    assert torch.equal(one[0].view(torch.int16), three[0].view(torch.int16)) and torch.equal(one[1], three[1]) and torch.equal(one[2], three[2])
+
+
+# a patch; parts of a slab and of an image row's patches; 1 to 4 slabs to a workgroup, the last part of one; rows of 2 to 28 pixels, fewer and more than those
+# in flight; one K step to twelve, whole and not; one block of channels, as many as wavefronts, one more; K_pad beyond the last step's; a second round
+SIZES = [(1, 3, 14, 14, 14, 592, 64), (2, 3, 42, 70, 14, 592, 320), (9, 3, 224, 224, 14, 640, 256), (1, 1, 6, 10, 2, 16, 64), (3, 3, 24, 40, 4, 48, 192),
+         (5, 3, 64, 72, 8, 192, 128), (2, 1, 84, 56, 28, 784, 64), (30, 3, 224, 224, 14, 592, 64), (45, 3, 224, 224, 14, 592, 64), (150, 3, 224, 224, 14, 592, 128),
+         (3, 5, 60, 84, 12, 768, 64), (2, 8, 42, 28, 14, 1568, 64), (2, 3, 42, 28, 14, 720, 64)]
+
+
+@pytest.mark.parametrize("B,C,H,W,P,K_pad,D", SIZES)
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+def test_one_call_is_the_three(g, force_kernel, B, C, H, W, P, K_pad, D, dtype):
+    r = torch.Generator(device="cuda").manual_seed(B + H)
+    img = torch.randn((B, C, H, W), generator=r, device="cuda").to(dtype)
+    wt = torch.zeros((D, K_pad), device="cuda")
+    wt[:, : C * P * P] = torch.randn((D, C * P * P), generator=r, device="cuda") * 0.05
+    w, bias = g.prepare_weights(wt, torch.int8), torch.randn(D, generator=r, device="cuda")
+    force_kernel(6)
+    assert g.lib().gpusq_patch_embed_int8_launches(g._TORCH_DT[dtype], B, C, H, W, P, K_pad, D, g.EPI_BIAS, 0) == 2
+    one, X = _one(g, img, w, bias, P, K_pad, D)
+    plain, _ = _one(g, img, w, None, P, K_pad, D)
+    force_kernel(None)
+    assert bool((X == 99).all())  # (left as it is)
+    _same(one, _three(g, img, w, bias, P, K_pad, D))
+    _same(plain, _three(g, img, w, None, P, K_pad, D))
+
+
+# no number but 0, numbers that are none, only tiny ones, infinities; a scale for which no reciprocal decides all codes
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+@pytest.mark.parametrize("what", ["zero", "nan", "tiny", "inf", "refined"])
+def test_ranges(g, force_kernel, dtype, what):
+    B, C, H, W, P, K_pad, D = 3, 3, 56, 42, 14, 640, 64
+    r = torch.Generator(device="cuda").manual_seed(4)
+    img = torch.randn((B, C, H, W), generator=r, device="cuda").to(dtype)
+    if what == "zero":
+        img.zero_()
+    elif what == "tiny":
+        img.mul_(1e-6)
+    elif what == "nan":
+        img.view(-1)[::37] = float("nan")
+    elif what == "inf":
+        img.view(-1)[::1001] = float("-inf")
+    else:  # ranges up to the next power of two: among them those whose reciprocals are off at a boundary between codes
+        img.clamp_(-1, 1)
+    w = g.prepare_weights(torch.randn((D, K_pad), generator=r, device="cuda") * 0.05, torch.int8)
+    for top in (None,) if what != "refined" else (1.0, 1.0625, 1.123046875, 1.3330078125, 1.576171875, 1.7548828125, 1.9990234375):
+        if top is not None:
+            img.view(-1)[5] = top
+        force_kernel(6)
+        one, _ = _one(g, img, w, None, P, K_pad, D)
+        force_kernel(None)
+        _same(one, _three(g, img, w, None, P, K_pad, D))
+
+
+def test_overlaps_are_the_three(g, force_kernel):
+    """Y over the codes, and over the images: what reads them is then done before Y is written"""
+    B, C, H, W, P, K_pad, D = 8, 3, 28, 28, 14, 592, 64
+    r = torch.Generator(device="cuda").manual_seed(6)
+    w = g.prepare_weights(torch.randn((D, K_pad), generator=r, device="cuda") * 0.05, torch.int8)
+    M, n = 32, B * C * H * W
+    ws = torch.empty(4096, dtype=torch.uint8, device="cuda")
+    for over in ("codes", "images"):
+        img = torch.randn((B, C, H, W), generator=r, device="cuda").half()
+        expected = _three(g, img, w, None, P, K_pad, D)[0]
+        q, s, X = torch.empty((B, C, H, W), dtype=torch.int8, device="cuda"), torch.zeros(1, device="cuda"), torch.full((M, K_pad), 99, dtype=torch.int8, device="cuda")
+        Y = (q.view(-1).view(torch.float16) if over == "codes" else img.view(-1))[: M * D].view(M, D)
+        force_kernel(6)
+        g.calls.gpusq_patch_embed_int8(img, g.F16, w["packed"], s, w["w_scale"], None, Y, q, X, ws, B, C, H, W, P, K_pad, D, 0)
+        force_kernel(None)
+        assert torch.equal(Y.view(torch.int16), expected.view(torch.int16)) and not bool((X == 99).all())
+
+
+def test_patch_embed_of_the_pipeline_in_a_graph(g):
+    from paper_2305_10727_amd.pipeline import SparsePatchEmbed
+    B, C, H, W, P, D = 9, 3, 224, 224, 14, 192
+    r = torch.Generator(device="cuda").manual_seed(1)
+    wt, bias = torch.randn((D, C, P, P), generator=r, device="cuda") * 0.05, torch.randn(D, generator=r, device="cuda")
+    e, apart = SparsePatchEmbed(B, C, H, W, P, D), SparsePatchEmbed(B, C, H, W, P, D, fused=False)
+    assert e.one_call and not apart.one_call
+    assert g.lib().gpusq_patch_embed_int8_launches(g.F16, B, C, H, W, P, e.K_pad, D, e.linear.epilogue, 0) == 2
+    e.prepare_weights(wt)
+    apart.prepare_weights(wt)
+    img = torch.empty((B, C, H, W), dtype=torch.float16, device="cuda").normal_(generator=r)
+    s, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(s):
+        e.forward(img, bias)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=s):
+        y = e.forward(img, bias)
+    for i in range(3):
+        img.normal_(generator=r).mul_(i + 1)
+        graph.replay()
+        torch.cuda.synchronize()
+        _same((y, e.img_q, e.linear.act_scale), (apart.forward(img, bias), apart.img_q, apart.linear.act_scale))
