@@ -449,6 +449,9 @@ gpusq_status launch_mlp(const MlpArgs& a, hipStream_t s);
 // a patch embedding on fp16 images in one launch (patches.hip), or by flattened patches in a.X and the GEMM
 gpusq_status launch_patch_embed_f16(GemmArgs a, const void* img, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, hipStream_t s);
 int patch_embed_f16_launches(int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D, int epilogue, int cus);
+// 16 x 16 patches, few of them, on the kernel for whole rows behind a range pass (a: with the fields of a patch embedding)
+bool few_patches_take_whole_rows(int64_t M, int64_t N, int64_t K, int epilogue, gpusq_dtype dt, int cus);
+gpusq_status launch_few_patches(const GemmArgs& a, gpusq_dtype dt, int8_t* img_q, float* scale, void* workspace, hipStream_t s);
 // the int8 one: range pass and the same kernel, or quantiser, flattened patches in a.X and the GEMM
 gpusq_status launch_patch_embed_i8(GemmArgs a, const void* img, gpusq_dtype dt, int8_t* img_q, float* scale, void* workspace, int64_t B, int64_t C, int64_t H,
                                    int64_t W, int64_t P, hipStream_t s);

@@ -367,22 +367,34 @@ gpusq_status launch_patch_embed_f16(GemmArgs a, const void* img, int64_t B, int6
 }
 
 int patch_embed_i8_launches(gpusq_dtype dt, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D, int epilogue, int cus) {
-  return patch_plan_where_ahead(true, dt == GPUSQ_F32 ? 4 : 2, B, C, H, W, P, ceil_div(K_pad, 128), D, epilogue, cus > 0 ? cus : num_cus()).chunks > 0 ? 2 : 4;
+  const int resident = cus > 0 ? cus : num_cus();
+  if (P == 16 && K_pad == C * 256 && few_patches_take_whole_rows(B * (H / P) * (W / P), D, K_pad, epilogue, dt, resident)) return 2;
+  return patch_plan_where_ahead(true, dt == GPUSQ_F32 ? 4 : 2, B, C, H, W, P, ceil_div(K_pad, 128), D, epilogue, resident).chunks > 0 ? 2 : 4;
 }
 
 gpusq_status launch_patch_embed_i8(GemmArgs a, const void* img, gpusq_dtype dt, int8_t* img_q, float* scale, void* workspace, int64_t B, int64_t C, int64_t H,
                                    int64_t W, int64_t P, hipStream_t s) {
   const int64_t pixels = B * C * H * W;
   const int x_bytes = dt == GPUSQ_F32 ? 4 : 2;
-  const PatchPlan p = patch_plan_where_ahead(true, x_bytes, B, C, H, W, P, ceil_div(a.K, 128), a.N, a.epilogue, num_cus());
+  const int resident = num_cus();
+  const bool whole_rows = P == 16 && a.K == C * 256 && few_patches_take_whole_rows(a.M, a.N, a.K, a.epilogue, dt, resident);
+  const PatchPlan p = patch_plan_where_ahead(true, x_bytes, B, C, H, W, P, ceil_div(a.K, 128), a.N, a.epilogue, resident);
   const ByteRange in{img, pixels * x_bytes}, codes{img_q, pixels}, y{a.Y, (int64_t)a.M * a.N * 2};
   const ByteRange range{workspace, (int64_t)gpusq_quantize_workspace_bytes(GPUSQ_PER_TENSOR, 1, pixels)};
   a.act_scale = scale;
-  if (p.chunks == 0 || overlap(in, y) || overlap(in, codes) || overlap(codes, y) || overlap(range, y) || overlap(range, codes)) {
+  if ((!whole_rows && p.chunks == 0) || overlap(in, y) || overlap(in, codes) || overlap(codes, y) || overlap(range, y) || overlap(range, codes)) {
     gpusq_status st = launch_quantize(img, dt, img_q, scale, GPUSQ_PER_TENSOR, 0, 1, pixels, workspace, s);
     if (st != GPUSQ_OK) return st;
     st = launch_im2col_patches(img_q, const_cast<void*>(a.X), GPUSQ_I8, B, C, H, W, P, a.K, s);
     return st != GPUSQ_OK ? st : launch_spgemm(true, a, s);
+  }
+  if (whole_rows) {
+    a.X = img;
+    a.patch_P = (int)P;
+    a.patch_C = (int)C;
+    a.patch_H = (int)H;
+    a.patch_W = (int)W;
+    return launch_few_patches(a, dt, img_q, scale, workspace, s);
   }
   a.xq_out = img_q;
   a.scale_out = scale;

@@ -728,6 +728,36 @@ gpusq_status launch_linear_int8(GemmArgs a, gpusq_dtype dt, int8_t* Xq, float* s
   return launch_typed<true>(a, s);
 }
 
+// The range pass over a.X, images of dt, and the kernel for whole rows on them
+static gpusq_status launch_wide_patches(GemmArgs a, gpusq_dtype dt, int8_t* img_q, float* scale, void* workspace, const WidePlan& p, hipStream_t s) {
+  a.x_f16 = dt == GPUSQ_F32 ? 2 : 1;
+  a.xq_out = img_q;
+  a.scale_out = scale;
+  a.range_mode = kRangePartials;
+  a.npartial = launch_amax(a.X, dt, (int64_t)a.M * a.K, workspace, s);
+  a.partial = (const float*)workspace;
+  return launch_wide(a, p, s);
+}
+
+// Patches of 16 x 16 too few for the kernels that gather them (launch_patch_embed_int8): two launches instead of quantiser, flattened patches and GEMM, four. Of
+// 63 sizes timed (24 to 840 patches of one to four channels, 128 to 1216 channels out, fp16 and fp32) 1.46 times as fast, none less than 1.19: 150 x 768 -> 640 13.8 / 10.3 us, 700 x 1024 -> 192
+// 14.9 / 12.3; more than 1024 values were not timed.
+static bool few_patches_take_whole_rows(int64_t M, int64_t N, int64_t K, int epilogue, gpusq_dtype dt, int resident, WidePlan& p) {
+  const int forced = forced_kernel();
+  if ((forced >= 0 && forced < 5) || (epilogue & GPUSQ_EPI_GELU) || M * N > 256 * 1024 || K > 8 * kStepBytes || M * K * dtype_bytes(dt) >= ((int64_t)1 << 32)) return false;
+  p = wide_plan(M, N, resident, dt == GPUSQ_F32);
+  return p.chunks > 0;
+}
+gpusq_status launch_few_patches(const GemmArgs& a, gpusq_dtype dt, int8_t* img_q, float* scale, void* workspace, hipStream_t s) {
+  WidePlan p;
+  if (!few_patches_take_whole_rows(a.M, a.N, a.K, a.epilogue, dt, num_cus(), p)) return GPUSQ_ERR_UNSUPPORTED;
+  return launch_wide_patches(a, dt, img_q, scale, workspace, p, s);
+}
+bool few_patches_take_whole_rows(int64_t M, int64_t N, int64_t K, int epilogue, gpusq_dtype dt, int cus) {
+  WidePlan p;
+  return few_patches_take_whole_rows(M, N, K, epilogue, dt, cus, p);
+}
+
 // The images in front of a patch embedding: the kernel for whole rows takes a product of its sizes as it takes a layer's under a given scale.  A
 // range pass does come first, but the kernels that gather patches take longer than a layer's, which makes up for it.  Of 403 sizes timed (72 to
 // 576 patches an image, 256 to 1024 values each, 192 to 1536 channels) it takes 238 of fp16, 1.19 times as fast, none slower, and 101 of fp32, 1.06 times, 8 %
@@ -743,15 +773,7 @@ gpusq_status launch_patch_embed_int8(GemmArgs a, gpusq_dtype dt, int8_t* img_q, 
   const bool wide = pixels * dtype_bytes(dt) < ((int64_t)1 << 32) && wide_takes(a, dt, false, resident, decide(true, a.M, a.N, a.K, false, resident, false), plan) &&
                     may_quantise_inside(a.X, dtype_bytes(dt), a.Y, 2, a.M, a.N, a.K, scale, false, nullptr, workspace,
                                         (int64_t)gpusq_quantize_workspace_bytes(GPUSQ_PER_TENSOR, 1, pixels));
-  if (wide) {
-    a.x_f16 = dt == GPUSQ_F32 ? 2 : 1;
-    a.xq_out = img_q;
-    a.scale_out = scale;
-    a.range_mode = kRangePartials;
-    a.npartial = launch_amax(a.X, dt, pixels, workspace, s);
-    a.partial = (const float*)workspace;
-    return launch_wide(a, plan, s);
-  }
+  if (wide) return launch_wide_patches(a, dt, img_q, scale, workspace, plan, s);
   const gpusq_status st = launch_quantize(a.X, dt, img_q, scale, GPUSQ_PER_TENSOR, 0, 1, pixels, workspace, s);
   if (st != GPUSQ_OK) return st;
   a.X = img_q;

@@ -348,7 +348,8 @@ def test_patch_embedding_launches(sizes, launches):
     ((256, 3, 224, 224, 14, 640, 1280, 1), 2), ((1, 3, 14, 14, 14, 592, 512, 0), 2), ((2, 3, 56, 56, 8, 192, 256, 1), 2),
     ((4, 3, 224, 224, 14, 640, 1088, 1), 4),    # too few for the weights: 1024 patches, 1088 channels
     ((16, 3, 224, 224, 14, 640, 1536, 1), 4),   # beyond 1408 channels 6 patches for each from 512 on, not 2
-    ((64, 3, 224, 224, 16, 768, 768, 1), 4), ((64, 3, 252, 252, 18, 1024, 256, 1), 4),  # more than 14 rows
+    ((64, 3, 224, 224, 16, 768, 768, 1), 4), ((1, 3, 224, 224, 16, 768, 772, 1), 2), ((1, 3, 224, 224, 16, 768, 768, 3), 4),  # 16 x 16: few of them, on the kernel for whole rows
+    ((1, 3, 224, 224, 16, 784, 768, 1), 4), ((1, 4, 224, 224, 16, 1024, 768, 1), 2), ((1, 5, 224, 224, 16, 1280, 768, 1), 4), ((64, 3, 252, 252, 18, 1024, 256, 1), 4),  # more than 14 rows
     ((64, 9, 224, 224, 14, 1792, 192, 1), 4),   # LDS for fewer than three slabs
     ((64, 3, 225, 225, 15, 704, 768, 1), 4), ((64, 3, 224, 224, 14, 640, 776, 1), 4), ((64, 3, 224, 224, 14, 640, 768, 3), 4),
     ((2, 3, 32760, 32760, 14, 640, 768, 1), 0), # more pixels than the quantiser has columns

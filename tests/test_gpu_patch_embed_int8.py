@@ -34,7 +34,8 @@ def _same(one, three):
 # in flight; one K step to twelve, whole and not; one block of channels, as many as wavefronts, one more; K_pad beyond the last step's; a second round
 SIZES = [(1, 3, 14, 14, 14, 592, 64), (2, 3, 42, 70, 14, 592, 320), (9, 3, 224, 224, 14, 640, 256), (1, 1, 6, 10, 2, 16, 64), (3, 3, 24, 40, 4, 48, 192),
          (5, 3, 64, 72, 8, 192, 128), (2, 1, 84, 56, 28, 784, 64), (30, 3, 224, 224, 14, 592, 64), (45, 3, 224, 224, 14, 592, 64), (150, 3, 224, 224, 14, 592, 128),
-         (3, 5, 60, 84, 12, 768, 64), (2, 8, 42, 28, 14, 1568, 64), (2, 3, 42, 28, 14, 720, 64)]
+         (3, 5, 60, 84, 12, 768, 64), (2, 8, 42, 28, 14, 1568, 64), (2, 3, 42, 28, 14, 720, 64),
+         (1, 3, 16, 16, 16, 768, 64), (1, 3, 224, 208, 16, 768, 516), (3, 1, 64, 112, 16, 256, 1280), (5, 4, 64, 80, 16, 1024, 192)]  # on the kernel for whole rows
 
 
 @pytest.mark.parametrize("B,C,H,W,P,K_pad,D", SIZES)
