@@ -23,9 +23,9 @@ __host__ __device__ inline uint32_t patch_lds_at(uint32_t kb, int r, uint32_t sw
   return (uint32_t)r * kPatchPanelBytes + (kb / kPatchPanelBytes) * (uint32_t)(16 * slabs * kPatchPanelBytes) + ((kb % kPatchPanelBytes) ^ swizzle);
 }
 
-// Whether the kernel takes the sizes: whole pairs of pixels, whole blocks of 64 channels, lane offsets of 32 bits inside the images
+// Whether the kernel takes the sizes: whole pairs of pixels, whole blocks of 64 channels, lane offsets of 32 bits inside the images and 64 rows of Y
 inline bool patch_takes_sizes(int x_bytes, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t ksteps, int64_t D) {
-  return P % 2 == 0 && D % 64 == 0 && B * C * H * W * x_bytes < ((int64_t)1 << 32) && patch_lds(ksteps, 1) <= kPatchLds;
+  return P % 2 == 0 && D % 64 == 0 && D < ((int64_t)1 << 24) && B * C * H * W * x_bytes < ((int64_t)1 << 32) && patch_lds(ksteps, 1) <= kPatchLds;
 }
 // chunks == 0: none.  Workgroups as high as they go, for each reads all weights, but no higher than gives every CU one, or where that takes more than
 // the accumulators two (23040 x 588 -> 768 with 3 slabs 23.5 us, with 4 24.9); behind that round the chunks even out over the CUs by themselves, and the
