@@ -334,8 +334,8 @@ static gpusq_status launch_patches(GemmArgs a, const PatchPlan& p, const void* i
 // The plan of one launch; chunks == 0: flattened patches in memory and the GEMM.  Every workgroup reads all weights, so it takes patches enough for them and LDS for
 // at least two slabs.  Of 540 sizes timed (650 to 66000 patches of 2 x 2 to 28 x 28, 1 to 4 channels, 128 to 1408 channels out, calls in turn on three buffers) these are 1.5
 // times as fast in one launch (8192 x 588 -> 192 14.1 / 8.9 us, 2048 x 588 -> 768 12.6 / 11.8, 16384 x 588 -> 1280 33.2 / 25.7), 2 of 226 slower by 3 %; of the others 1105 x 588
-// -> 1280 12.7 / 15.1, 8192 x 588 -> 3072 35.7 / 38.4, with two slabs (972 to 1280 values) 2160 x 1200 -> 1152 24.0 / 24.7, with one 42390 x 1600 -> 448 124 / 137.  16 x 16 patches of more
-// than 2^18 outputs have gpusq_patch_embed16_fp16, whose 16-byte pieces need no cutting (25088 x 768 -> 768 28.3, here 43.1).
+// -> 1280 12.7 / 15.1, 8192 x 588 -> 3072 35.7 / 38.4, with two slabs (972 to 1280 values) 2160 x 1200 -> 1152 24.0 / 24.7, with one 42390 x 1600 -> 448 124 / 137.  16 x 16 patches, whose
+// 16-byte pieces need no cutting, have gpusq_patch_embed16_fp16 (25088 x 768 -> 768 28.3, here 43.1) or, few of them, the two launches (832 x 768 -> 256 7.8, here 8.1).
 // int8: two launches instead of four, so for fewer patches too (98 x 588 -> 256 15.6 / 10.6, 896 x 588 -> 1088 20.9 / 16.2; 672 x 588 -> 1024 14.2 / 14.9); of 190 sizes of
 // 14 x 14 patches (24 to 62000, 128 to 1408 channels) 1.35 times as fast, none slower by more than 3 %.  Patches of more than 14 rows are 28 rows of work (4464 x 972 -> 896 24.0 / 30.4).
 static PatchPlan patch_plan_where_ahead(bool is_i8, int x_bytes, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t ksteps, int64_t D, int epilogue, int resident) {
@@ -346,7 +346,7 @@ static PatchPlan patch_plan_where_ahead(bool is_i8, int x_bytes, int64_t B, int6
   if (forced != 6) {
     const int slabs = patch_slabs(ksteps);
     if (is_i8 ? P > 14 || slabs < 3 || M < (D <= 1408 ? 2 : 6) * (D - 512)
-              : (P == 16 && M * D > 256 * 1024) || slabs < 2 || (slabs == 2 ? M < 2048 || D > 512 : M < 640 || M < 6 * (D - 512)))
+              : P == 16 || slabs < 2 || (slabs == 2 ? M < 2048 || D > 512 : M < 640 || M < 6 * (D - 512)))
       return PatchPlan{};
   }
   return patch_plan(M, ksteps, D, resident);

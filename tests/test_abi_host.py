@@ -333,7 +333,7 @@ def test_walk_patch_embedding_plans(tmp_path):
     ((64, 3, 252, 252, 18, 976, 512, 1), 1), ((64, 3, 252, 252, 18, 976, 576, 1), 2),  # LDS for two slabs: up to 512 channels,
     ((10, 3, 252, 252, 18, 976, 512, 1), 2),                                           # from 2048 patches on
     ((64, 3, 224, 224, 28, 2368, 192, 1), 2),   # LDS for one slab
-    ((64, 3, 224, 224, 16, 768, 768, 1), 2), ((4, 3, 224, 224, 16, 768, 192, 1), 1),  # 16-byte pieces: gpusq_patch_embed16_fp16, from 2^18 outputs on
+    ((64, 3, 224, 224, 16, 768, 768, 1), 2), ((4, 3, 224, 224, 16, 768, 192, 1), 2),  # 16-byte pieces
     ((64, 3, 225, 225, 15, 704, 768, 1), 2),    # no pairs of pixels
     ((64, 3, 224, 224, 14, 640, 776, 1), 2),    # part of a block of channels
     ((64, 3, 224, 224, 14, 640, 768, 3), 2),    # GELU
