@@ -277,6 +277,7 @@ gpusq_status gpusq_patch_embed_int8(const void* img, gpusq_dtype dt, const void*
   if (B * C * H * W > INT32_MAX) return GPUSQ_ERR_SHAPE;  // (the quantiser's columns)
   const int64_t M = B * (H / P) * (W / P);
   st = check_gemm(X, Wpacked, bias, Y, M, D, K_pad, epilogue);
+  if (st == GPUSQ_OK) st = check_int8_extras(act_scale, w_scale, GPUSQ_F16, nullptr);
   if (st != GPUSQ_OK) return st;
   if (!aligned16(img) || !aligned16(img_q) || !aligned16(workspace)) return GPUSQ_ERR_ALIGN;
   GemmArgs a{X, Wpacked, act_scale, w_scale, bias, nullptr, Y, (int)M, (int)D, (int)K_pad, epilogue, (int)GPUSQ_F16};
