@@ -10,6 +10,7 @@ import torch
 from . import gpusq as G
 
 _call = G.calls_unchecked
+_BIAS_GELU = G.EPI_BIAS | G.EPI_GELU
 
 
 def _p(t):
@@ -233,6 +234,15 @@ class EncoderBlockLinears:
         for lin, W in ((self.qkv, Wqkv), (self.proj, Wproj), (self.fc1, Wfc1), (self.fc2, Wfc2)):
             lin.prepare_weights(W)
 
+    def _one_call_behind_attention(self):
+        """Whether proj, fc1 and fc2 are what gpusq_block_mlp_int8 stands for.  They are this object's attributes, for a caller to change: other
+        buffers, scales, sizes or epilogues are honoured by the layers' own calls."""
+        proj, fc1, fc2 = self.proj, self.fc1, self.fc2
+        M, D, hidden = proj.M, proj.N, fc1.N
+        return (fc2.Xq is fc1.Y and fc2.act_scale is self.scales["g"] and proj.epilogue == fc2.epilogue == G.EPI_BIAS and
+                fc1.epilogue == _BIAS_GELU and fc1.out_dtype is torch.int8 and fc2.out_dtype is torch.float16 and
+                M == fc1.M == fc2.M and D == proj.K == fc1.K == fc2.N and hidden == fc2.K)
+
     def forward(self, x, biases, attention, norm=None):
         """x fp16 [M,D]; biases: (b_qkv, b_proj, b_fc1, b_fc2); returns fc2's fp16 output [M,D] (a buffer of this object)"""
         if self.fold_quantise:
@@ -242,10 +252,14 @@ class EncoderBlockLinears:
         attention(self.qkv.Y, self.proj.Xq)
         if norm is None:
             proj, fc1, fc2 = self.proj, self.fc1, self.fc2
-            _call.gpusq_block_mlp_int8(proj.Xq, proj.packed, proj.act_scale, proj.w_scale, biases[1], proj.Y, fc1.Xq, fc1.act_scale,
-                                       fc1.packed, fc1.w_scale, biases[2], fc1.Y, self.scales["g"], fc2.packed, fc2.w_scale, biases[3], fc2.Y,
-                                       self.M, self.D, self.hidden)
-            return fc2.Y
+            if self._one_call_behind_attention():
+                _call.gpusq_block_mlp_int8(proj.Xq, proj.packed, proj.act_scale, proj.w_scale, biases[1], proj.Y, fc1.Xq, fc1.act_scale,
+                                           fc1.packed, fc1.w_scale, biases[2], fc1.Y, self.scales["g"], fc2.packed, fc2.w_scale, biases[3], fc2.Y,
+                                           proj.M, proj.N, fc1.N)
+                return fc2.Y
+            proj.gemm_and_codes(fc1, biases[1])
+            fc1.gemm(None, biases[2], self.scales["g"])
+            return fc2.gemm(None, biases[3])
         h = norm(self.proj.gemm(None, biases[1]))
         if self.fold_quantise:
             self.fc1.gemm_from_f16(h, biases[2], self.scales["g"])

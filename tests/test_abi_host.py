@@ -447,6 +447,58 @@ def test_launches_behind_attention(M, D, H, launches):
     assert gpusq.lib().gpusq_block_mlp_int8_launches(M, D, H, 256) == launches
 
 
+class _Recorder:
+    """Stands for the library's calls: which ones, with what arguments"""
+
+    def __init__(self):
+        self.met = []
+
+    def __getattr__(self, name):
+        return lambda *args: self.met.append((name, args))
+
+
+@pytest.mark.parametrize("change", [None, "fc2.Xq", "fc2.act_scale", "scales", "proj.epilogue", "fc1.epilogue", "fc2.epilogue", "fc2.out_dtype", "rows", "hidden"])
+def test_a_block_honours_its_layers_attributes(monkeypatch, change):
+    """proj, fc1 and fc2 are one call where that is what they hold, else the layers' own calls on it"""
+    torch = pytest.importorskip("torch")
+    from paper_2305_10727_amd import gpusq, pipeline
+    calls = _Recorder()
+    monkeypatch.setattr(pipeline, "_call", calls)
+    M, D, H = 32, 64, 256
+    block = pipeline.EncoderBlockLinears(M, D, H, {k: torch.ones(1) for k in ("x", "qkv", "attn", "h", "g")}, device="cpu")
+    proj, fc1, fc2 = block.proj, block.fc1, block.fc2
+    if change == "fc2.Xq":
+        fc2.Xq = fc1.Y.clone()
+    elif change == "fc2.act_scale":
+        fc2.act_scale = torch.ones(1)
+    elif change == "scales":
+        block.scales = dict(block.scales, g=torch.ones(1))
+    elif change == "fc1.epilogue":
+        fc1.epilogue = gpusq.EPI_BIAS
+    elif change in ("proj.epilogue", "fc2.epilogue"):
+        (proj if change[0] == "p" else fc2).epilogue = 0
+    elif change == "fc2.out_dtype":
+        fc2.out_dtype = torch.int32
+    elif change == "rows":
+        proj.M = fc1.M = M - 1
+    elif change == "hidden":
+        fc2.K = H - 64
+    biases = [torch.zeros(n) for n in (3 * D, D, H, D)]
+    y = block.forward(torch.zeros((M, D), dtype=torch.float16), biases, lambda qkv, out: None)
+    assert y is fc2.Y
+    got = calls.met[1:]  # (behind qkv)
+    if change is None:
+        assert [n for n, _ in got] == ["gpusq_block_mlp_int8"]
+        return
+    assert [n for n, _ in got] == ["gpusq_spgemm_int8_codes", "gpusq_spgemm_int8", "gpusq_spgemm_int8"]
+    dt = gpusq._TORCH_DT
+    expected = [(proj.Xq, proj.packed, proj.act_scale, proj.w_scale, biases[1], proj.Y, fc1.Xq, fc1.act_scale, proj.M, D, D, proj.epilogue),
+                (fc1.Xq, fc1.packed, fc1.act_scale, fc1.w_scale, biases[2], fc1.Y, dt[torch.int8], block.scales["g"], fc1.M, H, D, fc1.epilogue),
+                (fc2.Xq, fc2.packed, fc2.act_scale, fc2.w_scale, biases[3], fc2.Y, dt[fc2.out_dtype], None, fc2.M, D, fc2.K, fc2.epilogue)]
+    for (_, a), e in zip(got, expected):
+        assert len(a) == len(e) and all(x is y if isinstance(y, torch.Tensor) else x == y for x, y in zip(a, e))
+
+
 @pytest.mark.parametrize("M,K,N,takes", [(197, 768, 768, True), (2047, 256, 64, True), (2048, 256, 64, True), (4096, 256, 64, True), (4097, 256, 128, False),
                                          (8192, 256, 64, True), (8193, 256, 64, False), (12608, 768, 768, False), (7029, 1152, 256, False)])
 def test_layers_whose_gemm_takes_fp16_activations(M, K, N, takes):
