@@ -162,6 +162,11 @@ class SparsePatchEmbed:
         Wflat[:, :self.K] = Wc.reshape(self.D, self.K)
         self.linear.prepare_weights(Wflat, fused=self.K_pad * 4 <= 64 * 1024)
 
+    def _linear_as_made(self):
+        """Whether the layer has the sizes and the output type that this object gave it (else its own call honours what it has now)"""
+        lin = self.linear
+        return lin.M == self.M and lin.K == self.K_pad and lin.N == self.D and lin.out_dtype is torch.float16
+
     def forward(self, img, bias):
         """img [B,C,H,W] fp16 (or fp32 on the int8 path)"""
         B, C, H, W = self.shape
@@ -170,7 +175,8 @@ class SparsePatchEmbed:
             _call.gpusq_patch_embed16_images(img, G._TORCH_DT[img.dtype], lin.packed, lin.act_scale, lin.w_scale, bias, lin.Y, self.img_q, self.workspace,
                                              B, C, H, W, self.D, lin.epilogue & G.EPI_BIAS)
             return lin.Y
-        if self.precision == "int8" and self.one_call:
+        one_call = self.one_call and self._linear_as_made()
+        if self.precision == "int8" and one_call:
             lin = self.linear
             lin.Xq = self.X
             _call.gpusq_patch_embed_int8(img, G._TORCH_DT[img.dtype], lin.packed, lin.act_scale, lin.w_scale, bias, lin.Y, self.img_q, self.X, self.workspace,
@@ -186,7 +192,7 @@ class SparsePatchEmbed:
             lin = self.linear
             _call.gpusq_patch_embed16_fp16(src, lin.packed, bias, lin.Y, B, C, H, W, self.D, lin.epilogue & G.EPI_BIAS)
             return lin.Y
-        if self.one_call:
+        if one_call:
             lin = self.linear
             _call.gpusq_patch_embed_fp16(src, lin.packed, bias, lin.Y, self.X, B, C, H, W, self.P, self.K_pad, self.D, lin.epilogue)
             return lin.Y

@@ -499,6 +499,35 @@ def test_a_block_honours_its_layers_attributes(monkeypatch, change):
         assert len(a) == len(e) and all(x is y if isinstance(y, torch.Tensor) else x == y for x, y in zip(a, e))
 
 
+@pytest.mark.parametrize("precision", ["int8", "fp16"])
+@pytest.mark.parametrize("change", [None, "out_dtype", "rows", "channels"])
+def test_a_patch_embedding_honours_its_layers_attributes(monkeypatch, precision, change):
+    torch = pytest.importorskip("torch")
+    from paper_2305_10727_amd import gpusq, pipeline
+    calls = _Recorder()
+    monkeypatch.setattr(pipeline, "_call", calls)
+    B, C, H, W, P, D = 2, 3, 28, 28, 14, 64
+    embed = pipeline.SparsePatchEmbed(B, C, H, W, P, D, precision, device="cpu")
+    lin = embed.linear
+    if change == "out_dtype":
+        lin.out_dtype = torch.int32
+    elif change == "rows":
+        lin.M = 4
+    elif change == "channels":
+        lin.N = 32
+    img, bias = torch.zeros((B, C, H, W), dtype=torch.float16), torch.zeros(D)
+    assert embed.forward(img, bias) is lin.Y
+    names = [n for n, _ in calls.met]
+    if change is None or (precision, change) == ("fp16", "out_dtype"):  # (the fp16 product has no other output: either way)
+        assert change is not None or names == ["gpusq_patch_embed_" + precision]
+        return
+    assert names == (["gpusq_quantize_int8"] if precision == "int8" else []) + ["gpusq_im2col_patches", "gpusq_spgemm_" + precision]
+    if precision == "int8":
+        assert calls.met[-1][1][6:] == (gpusq._TORCH_DT[lin.out_dtype], None, lin.M, lin.N, embed.K_pad, lin.epilogue)
+    else:
+        assert calls.met[-1][1][4:] == (lin.M, lin.N, embed.K_pad, lin.epilogue)
+
+
 @pytest.mark.parametrize("M,K,N,takes", [(197, 768, 768, True), (2047, 256, 64, True), (2048, 256, 64, True), (4096, 256, 64, True), (4097, 256, 128, False),
                                          (8192, 256, 64, True), (8193, 256, 64, False), (12608, 768, 768, False), (7029, 1152, 256, False)])
 def test_layers_whose_gemm_takes_fp16_activations(M, K, N, takes):
