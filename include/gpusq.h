@@ -271,7 +271,7 @@ gpusq_status gpusq_im2col_patches(const void* img, void* X, gpusq_dtype dt, int6
                                   int64_t P, int64_t K_pad, void* stream);
 
 /* The fp16 layer from images to tokens in one call: what gpusq_im2col_patches and gpusq_spgemm_fp16 give, in one launch that cuts the patches in
- * LDS where that is ahead (even P other than 16, D % 64 == 0, many patches), else by these two.
+ * LDS where that is ahead (even P other than 16, up to four channels of the images, D % 64 == 0, many patches), else by these two.
  *   img, X [B*(H/P)*(W/P)][K_pad], sizes and errors as there, epilogue and Y [B*(H/P)*(W/P)][D] as for gpusq_spgemm_fp16.  X is
  *   scratch: it holds the flattened patches afterwards where there were two launches, and is left as it is otherwise. */
 gpusq_status gpusq_patch_embed_fp16(const void* img, const void* Wpacked, const float* bias, void* Y, void* X, int64_t B, int64_t C,

@@ -332,24 +332,38 @@ static gpusq_status launch_patches(GemmArgs a, const PatchPlan& p, const void* i
 }
 
 // The plan of one launch; chunks == 0: flattened patches in memory and the GEMM.  Every workgroup reads all weights, so it takes patches enough for them and LDS for
-// at least two slabs.  Of 540 sizes timed (650 to 66000 patches of 2 x 2 to 28 x 28, 1 to 4 channels, 128 to 1408 channels out, calls in turn on three buffers) these are 1.5
-// times as fast in one launch (8192 x 588 -> 192 14.1 / 8.9 us, 2048 x 588 -> 768 12.6 / 11.8, 16384 x 588 -> 1280 33.2 / 25.7), 2 of 226 slower by 3 %; of the others 1105 x 588
-// -> 1280 12.7 / 15.1, 8192 x 588 -> 3072 35.7 / 38.4, with two slabs (972 to 1280 values) 2160 x 1200 -> 1152 24.0 / 24.7, with one 42390 x 1600 -> 448 124 / 137.  16 x 16 patches, whose
-// 16-byte pieces need no cutting, have gpusq_patch_embed16_fp16 (25088 x 768 -> 768 28.3, here 43.1) or, few of them, the two launches (832 x 768 -> 256 7.8, here 8.1).
-// int8: two launches instead of four, so for fewer patches too (98 x 588 -> 256 15.6 / 10.6, 896 x 588 -> 1088 20.9 / 16.2; 672 x 588 -> 1024 14.2 / 14.9); of 190 sizes of
-// 14 x 14 patches (24 to 62000, 128 to 1408 channels) 1.35 times as fast, none slower by more than 3 %.  Patches of more than 14 rows are 28 rows of work (4464 x 972 -> 896 24.0 / 30.4).
+// at least two slabs (8192 x 588 -> 192 14.1 / 8.9 us, 2048 x 588 -> 768 12.6 / 11.8, 16384 x 588 -> 1280 33.2 / 25.7; slower 1105 x 588 -> 1280 12.7 / 15.1, 8192 x 588 -> 3072 35.7 / 38.4,
+// with one slab 42390 x 1600 -> 448 124 / 137).  What it costs is not the patches' values but their rows: a patch is cut in batches of 7 or 14 rows of one channel of the image, full
+// or not, so many channels of few rows are slow, 2420 x 1280 -> 64 of 320 channels of 2 x 2 12.0 / 212.9, 9000 x 512 of 32 channels of 4 x 4 three times as slow; up to four channels are taken.
+// Of 10538 sizes timed (600 to 80000 patches of 2 x 2 to 28 x 28, 1 to 320 channels, 64 to 3072 channels out, calls in turn on three buffers) it takes 6551, 1.48 times as fast in one
+// launch, 10 of them slower by 3 to 8 %.  16 x 16 patches, whose 16-byte pieces need no cutting, have gpusq_patch_embed16_fp16 (25088 x 768 -> 768 28.3, here 43.1) or, few of them, the
+// two launches (832 x 768 -> 256 7.8, here 8.1).
+static bool patch_f16_ahead(int64_t M, int64_t C, int64_t P, int64_t ksteps, int64_t D, const PatchPlan& p, int resident) {
+  const int fit = patch_slabs(ksteps);
+  if (P == 16 || C > 4 || fit < 2) return false;
+  // workgroups just past what `n` of them fill: the CUs wait for the few that are left (two slabs, 16720 x 972 -> 384 29.1 / 34.6)
+  auto just_past = [&](int64_t n) { return p.chunks > n && 4 * (int64_t)p.chunks <= 5 * n; };
+  if (fit == 2) return M >= 2048 && D <= 512 && !just_past(resident / 2) && !just_past(resident) && !just_past(2 * (int64_t)resident);
+  if (D <= 512) return M >= 640;
+  // three slabs at the most: all of them (5244 x 648 -> 1152 with two 17.4 / 21.1, 1008 x 800 -> 576 with one 9.7 / 11.2)
+  if (fit == 3) return p.slabs == 3 && D <= 1408 && !just_past(2 * (int64_t)resident);
+  if (D <= 1408) return M >= 12 * (D - 512) + 512;  // (760 x 576 -> 576 7.0 / 8.2, 1280 x 256 -> 640 7.1 / 7.6)
+  // more channels out: a K of 8 steps, else the output decides (34632 x 64 -> 2752 41.2 / 54.0)
+  return ksteps >= 8 && M >= 10 * (D - 512) && !just_past(2 * (int64_t)resident);
+}
+// int8: two launches instead of four, so for fewer patches too (98 x 588 -> 256 15.6 / 10.6, 896 x 588 -> 1088 20.9 / 16.2; 672 x 588 -> 1024 14.2 / 14.9), but the codes move two at a time, so
+// up to three channels.  Patches of more than 14 rows are 28 rows of work (4464 x 972 -> 896 24.0 / 30.4).
+static bool patch_i8_ahead(int64_t M, int64_t P, int64_t ksteps, int64_t D) {
+  return P <= 14 && patch_slabs(ksteps) >= 3 && M >= (D <= 1408 ? 2 : 6) * (D - 512);
+}
 static PatchPlan patch_plan_where_ahead(bool is_i8, int x_bytes, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t ksteps, int64_t D, int epilogue, int resident) {
   const int forced = forced_kernel();
   if ((forced >= 0 && forced < 5) || (epilogue & GPUSQ_EPI_GELU) || !patch_takes_sizes(x_bytes, B, C, H, W, P, ksteps, D)) return PatchPlan{};
   const int64_t M = B * (H / P) * (W / P);
   if (M > INT32_MAX) return PatchPlan{};
-  if (forced != 6) {
-    const int slabs = patch_slabs(ksteps);
-    if (is_i8 ? P > 14 || slabs < 3 || M < (D <= 1408 ? 2 : 6) * (D - 512)
-              : P == 16 || slabs < 2 || (slabs == 2 ? M < 2048 || D > 512 : M < 640 || M < 6 * (D - 512)))
-      return PatchPlan{};
-  }
-  return patch_plan(M, ksteps, D, resident);
+  const PatchPlan p = patch_plan(M, ksteps, D, resident);
+  if (forced == 6 || (is_i8 ? patch_i8_ahead(M, P, ksteps, D) : patch_f16_ahead(M, C, P, ksteps, D, p, resident))) return p;
+  return PatchPlan{};
 }
 
 int patch_embed_f16_launches(int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t K_pad, int64_t D, int epilogue, int cus) {

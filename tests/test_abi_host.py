@@ -344,6 +344,19 @@ def test_patch_embedding_launches(sizes, launches):
     assert gpusq.lib().gpusq_patch_embed_fp16_launches(*sizes, 256) == launches
 
 
+# sizes that were timed slower in one launch, and neighbours that were timed faster
+@pytest.mark.parametrize("sizes,launches", [
+    ((11, 320, 44, 20, 2, 1280, 64, 1), 2), ((9, 32, 128, 128, 4, 512, 192, 1), 2), ((10, 8, 300, 300, 10, 832, 512, 1), 2),  # many channels
+    ((9, 3, 128, 128, 4, 64, 192, 1), 1), ((10, 4, 300, 300, 10, 448, 512, 1), 1),
+    ((39, 1, 192, 296, 8, 64, 2752, 1), 2), ((64, 3, 224, 224, 14, 640, 2176, 1), 2),                       # many channels out
+    ((19, 2, 288, 306, 18, 704, 1152, 1), 2), ((1, 2, 640, 640, 20, 832, 576, 1), 2), ((32, 2, 288, 324, 18, 704, 1152, 1), 1),  # LDS for three slabs, with fewer and with them
+    ((1, 1, 672, 672, 24, 576, 576, 1), 2), ((4, 1, 672, 672, 24, 576, 576, 1), 1),                         # few patches
+    ((19, 3, 396, 720, 18, 1024, 384, 1), 2), ((15, 3, 396, 720, 18, 1024, 384, 1), 1), ((24, 3, 396, 720, 18, 1024, 384, 1), 1)])  # two slabs: workgroups just past a round, fewer, more
+def test_patch_embeddings_timed_slower_in_one_launch_are_two(sizes, launches):
+    from paper_2305_10727_amd import gpusq
+    assert gpusq.lib().gpusq_patch_embed_fp16_launches(*sizes, 256) == launches
+
+
 @pytest.mark.parametrize("sizes,launches", [
     ((256, 3, 224, 224, 14, 640, 1280, 1), 2), ((1, 3, 14, 14, 14, 592, 512, 0), 2), ((2, 3, 56, 56, 8, 192, 256, 1), 2),
     ((4, 3, 224, 224, 14, 640, 1088, 1), 4),    # too few for the weights: 1024 patches, 1088 channels
