@@ -282,7 +282,7 @@ int gpusq_patch_embed_fp16_launches(int64_t B, int64_t C, int64_t H, int64_t W, 
 
 /* The int8 layer likewise, from fp16 or fp32 images (dt): bit-identical, the codes in img_q [B][C][H][W] and the scale in act_scale[0] included, to
  * gpusq_quantize_int8(GPUSQ_PER_TENSOR) on the images (workspace as there), gpusq_im2col_patches and gpusq_spgemm_int8 to fp16; behind the range pass one
- * launch where that is ahead (the conditions above, P <= 14; or P = 16 and few patches, on the kernel for whole rows of gpusq_linear_int8), else these.  X is
+ * launch where that is ahead (the conditions above, up to three channels, P <= 14; or P = 16 and few patches, on the kernel for whole rows of gpusq_linear_int8), else these.  X is
  * scratch as above.  Launches: 2 or 4. */
 gpusq_status gpusq_patch_embed_int8(const void* img, gpusq_dtype dt, const void* Wpacked, float* act_scale, const float* w_scale, const float* bias,
                                     void* Y, int8_t* img_q, void* X, void* workspace, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P,

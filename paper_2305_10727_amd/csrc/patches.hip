@@ -351,10 +351,17 @@ static bool patch_f16_ahead(int64_t M, int64_t C, int64_t P, int64_t ksteps, int
   // more channels out: a K of 8 steps, else the output decides (34632 x 64 -> 2752 41.2 / 54.0)
   return ksteps >= 8 && M >= 10 * (D - 512) && !just_past(2 * (int64_t)resident);
 }
-// int8: two launches instead of four, so for fewer patches too (98 x 588 -> 256 15.6 / 10.6, 896 x 588 -> 1088 20.9 / 16.2; 672 x 588 -> 1024 14.2 / 14.9), but the codes move two at a time, so
-// up to three channels.  Patches of more than 14 rows are 28 rows of work (4464 x 972 -> 896 24.0 / 30.4).
-static bool patch_i8_ahead(int64_t M, int64_t P, int64_t ksteps, int64_t D) {
-  return P <= 14 && patch_slabs(ksteps) >= 3 && M >= (D <= 1408 ? 2 : 6) * (D - 512);
+// int8: two launches instead of four, so for fewer patches too (98 x 588 -> 256 15.6 / 10.6, 896 x 588 -> 1088 20.9 / 16.2; 672 x 588 -> 1024 14.2 / 14.9); from fp32 images, which cost more
+// registers and loads, four times as many (1000 x 192 -> 960 12.0 / 13.2).  Codes move two at a time, so up to three channels (3 us of 12 behind with a fourth and few patches), and where
+// a workgroup has more than two slabs, rows of 2, 4 or 8 pixels, which leave half of a batch of 7 empty, only with one or two batches (50160 x 192 -> 256 fp32 29.9 / 36.6, 75776 x 48 -> 192
+// fp32 23.7 / 27.6); 14 rows leave nothing empty, the others are behind just past a round of workgroups (33120 x 300 -> 1088 40.5 / 45.3).  Patches of more than 14 rows are 28 rows of work
+// (4464 x 972 -> 896 24.0 / 30.4).  Of 21715 sizes timed (16 to 80000 patches of 2 x 2 to 14 x 14, 1 to 320 channels, 64 to 3072 channels out, fp16 and fp32) it takes 13337, 1.42 times as fast,
+// 8 of them slower by more than 3 %.
+static bool patch_i8_ahead(int64_t M, int64_t C, int64_t P, int64_t ksteps, int64_t D, bool fp32, const PatchPlan& p, int resident) {
+  if (P > 14 || C > 3 || patch_slabs(ksteps) < 3 || D > 1408 || M < (fp32 ? 8 : 2) * (D - 512)) return false;
+  if (p.slabs <= 2 || P == 14) return true;
+  if ((P <= 4 || P == 8) && (fp32 || C * ceil_div(P, 7) > 2)) return false;
+  return p.chunks <= 2 * (int64_t)resident || 4 * (int64_t)p.chunks > 5 * 2 * (int64_t)resident;
 }
 static PatchPlan patch_plan_where_ahead(bool is_i8, int x_bytes, int64_t B, int64_t C, int64_t H, int64_t W, int64_t P, int64_t ksteps, int64_t D, int epilogue, int resident) {
   const int forced = forced_kernel();
@@ -362,7 +369,7 @@ static PatchPlan patch_plan_where_ahead(bool is_i8, int x_bytes, int64_t B, int6
   const int64_t M = B * (H / P) * (W / P);
   if (M > INT32_MAX) return PatchPlan{};
   const PatchPlan p = patch_plan(M, ksteps, D, resident);
-  if (forced == 6 || (is_i8 ? patch_i8_ahead(M, P, ksteps, D) : patch_f16_ahead(M, C, P, ksteps, D, p, resident))) return p;
+  if (forced == 6 || (is_i8 ? patch_i8_ahead(M, C, P, ksteps, D, x_bytes == 4, p, resident) : patch_f16_ahead(M, C, P, ksteps, D, p, resident))) return p;
   return PatchPlan{};
 }
 

@@ -377,6 +377,21 @@ def test_int8_patch_embedding_launches(sizes, launches):
     assert gpusq.lib().gpusq_patch_embed_int8_launches(gpusq.F32, 1, 3, 19600, 19600, 14, 640, 768, 1, 256) == 4
 
 
+# sizes that were timed slower behind the range pass, and neighbours that were timed faster: both types, or (fp32, fp16)
+@pytest.mark.parametrize("sizes,launches", [
+    ((3, 320, 8, 14, 2, 1280, 64, 1), 4), ((5, 64, 64, 72, 4, 1024, 128, 1), 4), ((1, 4, 420, 420, 14, 896, 832, 1), 4), ((1, 3, 420, 420, 14, 640, 576, 1), 2),  # channels
+    ((30, 3, 320, 320, 8, 256, 256, 1), 4), ((30, 1, 320, 320, 8, 128, 256, 1), (4, 2)), ((4, 3, 320, 320, 8, 256, 256, 1), 2),  # 8 rows: many patches, few
+    ((30, 3, 200, 200, 4, 128, 192, 1), 4), ((30, 2, 200, 200, 4, 128, 192, 1), (4, 2)), ((2, 3, 200, 200, 4, 128, 192, 1), 2),
+    ((10, 3, 80, 80, 8, 256, 960, 1), (4, 2)),                                                                                   # few patches for the weights
+    ((64, 3, 224, 224, 14, 640, 1472, 1), 4),                                                                                    # channels out
+    ((53, 3, 250, 250, 10, 384, 1088, 1), 4), ((51, 3, 250, 250, 10, 384, 1088, 1), 2), ((66, 3, 250, 250, 10, 384, 1088, 1), 2),  # just past a round, in it, beyond
+    ((130, 3, 224, 224, 14, 640, 1088, 1), 2)])                                                                                  # (14 rows: there as well)
+def test_int8_patch_embeddings_timed_slower_behind_the_range_pass_are_four(sizes, launches):
+    from paper_2305_10727_amd import gpusq
+    both = launches if isinstance(launches, tuple) else (launches, launches)
+    assert tuple(gpusq.lib().gpusq_patch_embed_int8_launches(dt, *sizes, 256) for dt in (gpusq.F32, gpusq.F16)) == both
+
+
 def test_patch_embedding_argument_checks(lib):
     ERR_NULL, ERR_SHAPE, ERR_ALIGN, ERR_UNSUPPORTED = 1, 2, 3, 4
     vp, i64, ci = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int
