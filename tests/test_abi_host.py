@@ -410,11 +410,24 @@ def test_patch_embedding_argument_checks(lib):
         img, dt, W, sa, sw, bias, Y, q, X, ws, B, C, H, Wd, P, K_pad, D, epi, None)
     for missing in ("img", "W", "sa", "sw", "bias", "Y", "q", "X", "ws"):
         assert call8(**{missing: None}) == ERR_NULL
-        assert missing == "sa" or call8(**{missing: 24}) == ERR_ALIGN  # (the weights' scales as well, as gpusq_spgemm_int8 refuses them)
+        assert missing in ("sa", "sw") or call8(**{missing: 24}) == ERR_ALIGN
     for wrong in (dict(B=0), dict(H=27), dict(P=0), dict(K_pad=576), dict(D=0), dict(H=28 * 1400, Wd=28 * 1400)):
         assert call8(**wrong) == ERR_SHAPE
     for wrong in (dict(epi=4), dict(K_pad=596), dict(D=66), dict(dt=2), dict(dt=3)):
         assert call8(**wrong) == ERR_UNSUPPORTED
+
+
+def test_patch_embedding_refuses_weight_scales_as_the_product_does(lib):
+    """gpusq_patch_embed_int8 reads w_scale by 16 bytes, as gpusq_spgemm_int8: from an address that is not aligned to them neither does"""
+    ERR_ALIGN = 3
+    vp, i64, ci = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int
+    lib.gpusq_spgemm_int8.argtypes = [vp, vp, vp, vp, vp, vp, ci, vp, i64, i64, i64, ci, vp]
+    lib.gpusq_patch_embed_int8.argtypes = [vp, ci] + [vp] * 8 + [i64] * 7 + [ci, vp]
+    for sw in (20, 24, 28):
+        assert lib.gpusq_spgemm_int8(16, 16, 16, sw, 16, 16, 1, None, 4, 64, 592, 1, None) == ERR_ALIGN
+        for dt in (0, 1):
+            for P, H, K_pad in ((14, 28, 592), (16, 32, 768), (28, 28, 2352)):  # in LDS, on whole rows, apart
+                assert lib.gpusq_patch_embed_int8(16, dt, 16, 16, sw, 16, 16, 16, 16, 16, 1, 3, H, H, P, K_pad, 64, 1, None) == ERR_ALIGN
 
 
 def test_empty_of_the_extension_module_is_torch_empty():
