@@ -3,7 +3,9 @@ the oracle elsewhere: tokens, codes of the images and scale bit for bit."""
 import numpy as np
 import pytest
 
-from test_gpu_parity import force_kernel, g  # noqa: F401
+import oracle
+from test_gpu_parity import dev, force_kernel, g, host  # noqa: F401
+from test_gpu_wide_rows import _refined
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -81,6 +83,31 @@ def test_ranges(g, force_kernel, dtype, what):
         one, _ = _one(g, img, w, None, P, K_pad, D)
         force_kernel(None)
         _same(one, _three(g, img, w, None, P, K_pad, D))
+
+
+# ranges whose scale no reciprocal decides all codes of, and pixels on the boundaries between codes; one, two and three slabs to a workgroup
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+@pytest.mark.parametrize("B,H,W", [(3, 56, 42), (20, 224, 224), (33, 224, 224)])
+def test_ranges_whose_reciprocals_are_off(g, force_kernel, B, H, W, dtype):
+    C, P, K_pad, D = 3, 14, 592, 64
+    tops = [v for v in np.arange(0x3C00, 0x4000, dtype=np.uint16).view(np.float16) if _refined(np.float32(v) / np.float32(127))]
+    assert len(tops) == 7
+    rng = np.random.default_rng(B)
+    r = torch.Generator(device="cuda").manual_seed(B)
+    w = g.prepare_weights(torch.randn((D, K_pad), generator=r, device="cuda") * 0.05, torch.int8)
+    for top in tops[:: 3]:
+        boundaries = (top / np.float32(127) * (np.arange(128, dtype=np.float32) - np.float32(0.5))).astype(np.float16)
+        img = np.clip(rng.standard_normal((B, C, H, W), dtype=np.float32).astype(np.float16), -top, top)
+        at = rng.choice(img.size, 2048, replace=False)
+        img.reshape(-1)[at] = np.concatenate([boundaries, -boundaries] * 8)
+        img[0, 0, 0, 0] = top
+        x = dev(img).to(dtype)
+        force_kernel(6)
+        one, _ = _one(g, x, w, None, P, K_pad, D)
+        force_kernel(None)
+        _same(one, _three(g, x, w, None, P, K_pad, D))
+        codes, scale = oracle.quantize_tensor_int8(img.reshape(1, -1).astype(np.float32))
+        assert host(one[2])[0] == np.float32(scale) and np.array_equal(host(one[1]).reshape(1, -1), codes)
 
 
 def test_overlaps_are_the_three(g, force_kernel):
