@@ -61,6 +61,12 @@ def test_one_launch_is_the_three(g, force_kernel, M, D, H):
     assert _same(one, three)
 
 
+# the pairs of K steps and slabs (of the highest chunk, on 256 CUs) that no size above has: 1 step and 2, 3 slabs, 2 and 3, 4, 3 and 2, 4
+@pytest.mark.parametrize("M,D,H", [(4097, 128, 256), (8193, 128, 512), (8193, 256, 1024), (12601, 192, 768), (6304, 384, 1536), (12608, 384, 1536)])
+def test_one_launch_is_the_three_at_every_height(g, force_kernel, M, D, H):
+    test_one_launch_is_the_three(g, force_kernel, M, D, H)
+
+
 @pytest.mark.parametrize("scales", [(0.0, 0.03, 0.02), (0.02, 0.0, 0.02), (0.02, 0.03, 0.0), (float("inf"), 0.03, 0.02), (0.02, float("nan"), 0.02), (0.02, 0.03, float("inf")),
                                     (-0.02, -0.03, -0.02), (0.02, 1e-40, 0.02), (0.02, 0.03, 1e-40), (1e30, 0.03, 0.02), (0.02, 1e-6, 1e-6)])
 @pytest.mark.parametrize("M,D,H", [(100, 192, 768), (70, 448, 448)])
