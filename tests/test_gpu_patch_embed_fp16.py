@@ -57,6 +57,12 @@ def test_one_launch_matches_the_oracle_and_the_two(g, force_kernel, B, C, H, W, 
     assert (np.abs(host(Y)[:rows].astype(np.float64) - (expected + host(bias)[None].astype(np.float64))) <= tol + 2.0 ** -10 * np.abs(host(bias))[None]).all()
 
 
+# two slabs to a workgroup (on 256 CUs): 320 slabs of patches; 307 of them where LDS holds no more, the last workgroup with four patches
+@pytest.mark.parametrize("B,C,H,W,P,K_pad,D", [(20, 3, 224, 224, 14, 592, 64), (25, 3, 252, 252, 18, 976, 64)])
+def test_two_slabs(g, force_kernel, B, C, H, W, P, K_pad, D):
+    test_one_launch_matches_the_oracle_and_the_two(g, force_kernel, B, C, H, W, P, K_pad, D)
+
+
 @pytest.mark.parametrize("W", [14, 98, 126, 210, 224])  # (tails of patches in the last workgroup)
 def test_every_patch_and_pixel_is_met_once(g, force_kernel, W):
     """Weights that pick single pixels: Y holds the images, bit for bit"""
