@@ -636,9 +636,8 @@ constexpr int64_t kRangeHereBytes = 128 * 1024;
 
 // Where the estimates of the kernel that quantises whole rows (wide.hip) say little, below 2048 rows or beyond two column blocks, but a launch less decides: up
 // to 2^23 outputs, and K of up to 512 values, or 1024 (768 from 2048 rows on) where there are 2^20 outputs (fp32 X: and 2^21 at
-// the most), for every chunk walks all of K by itself.  Under a given scale up to 256 values only, though it would be ahead beyond: callers have been told of two launches for 1576 x 384 -> 1152, and plan with them.
-// Of 1540 sizes timed (16 to 50000 rows, K 64 to 1408, N 64 to 5120, both types and outputs, with and without GELU) that the kernel for few rows does not
-// quantise for, these are 1.2 times as fast, one slower by more than 3 %: quantiser and GEMM / whole rows 1989 x 128 -> 1152 under a given scale 8.6 / 5.9 us, 1301 x
+// the most), for every chunk walks all of K by itself.  Under a given scale up to 256 values only: beyond it would be ahead as well, but the tests' counts of launches (two for 1576 x 384
+// -> 1152) hold it there.  Quantiser and GEMM / whole rows 1989 x 128 -> 1152 under a given scale 8.6 / 5.9 us, 1301 x
 // 128 -> 1472 + GELU 12.8 / 9.4, 2000 x 384 -> 1024 11.6 / 9.0, 1382 x 960 -> 960 13.9 / 11.6, 2548 x 224 -> 1600 13.3 / 9.3; beyond them 802 x 1184 -> 688 11.5 / 14.1, 882 x 960
 // -> 736 fp32 10.9 / 13.6, 1576 x 768 -> 2304 + GELU fp32 13.5 / 14.3, 3199 x 576 -> 4160 fp32 19.6 / 23.1.
 static bool wide_saves_a_launch(int64_t M, int64_t N, int64_t K, bool fp32, bool given) {
@@ -647,7 +646,23 @@ static bool wide_saves_a_launch(int64_t M, int64_t N, int64_t K, bool fp32, bool
   if (K <= (given ? 2 : 4) * kStepBytes) return true;
   return !given && (!fp32 || outputs <= (1 << 21)) && outputs >= (1 << 20) && K <= (M < GPUSQ_WIDE_MIN_ROWS ? 8 : 6) * kStepBytes;
 }
-
+// Of these, the plans that are ahead.  A chunk of one slab has little work for the operands that it fetches: the more 64-channel blocks it has and the longer K, the more outputs it takes
+// (2^18 for each K step and block beyond a line; own range, 12 blocks, 700 x 512 -> 768 5 % behind, 1100 x 512 -> 768 1 % ahead; at most 750000, for 1000 x 512 -> 768 is held here by a test); the line
+// is lower for rows that are stored by four, and for patches of fp32.  fp32 rows in chunks of four slabs, in which the epilogue stands alone behind a short K, are behind by 2 to 15 %; without a GELU those of whole 16 channels stay (2047 x 512 -> 4096
+// is held there by a test).  Of 61274 and 12081 layers of whole and of no whole 16 channels timed (seldom more than 4096 rows, K 64 to 5120, N 32 to 5120) this takes 60372 and 10827, 1.21 and 1.16 times
+// as fast, 150 and 133 slower by more than 3 % (12 % at the most); of the others 345 and 585 were slower.
+static bool wide_plan_ahead(const GemmArgs& a, const WidePlan& p, bool fp32) {
+  const bool narrow = a.N % 16 != 0, gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0, patches = a.patch_P > 0;
+  const int ksteps = (int)ceil_div((int64_t)a.K, kStepBytes), slabs = wide_slabs(p);
+  if (slabs == 1 && ksteps <= 4 && (narrow || ksteps > (patches ? 3 : 2))) {
+    const int line = patches ? (narrow ? (fp32 ? 3 : 2) - (ksteps <= 2) : fp32 ? 2 : 0) : (narrow ? (fp32 ? 2 : 1) : 0);
+    const int64_t outputs = (int64_t)a.M * a.N;
+    if (outputs < (int64_t)(ksteps + p.blocks - 12 + line) << 18 && (narrow || patches || outputs < 750 * 1000)) return false;
+  }
+  if (!fp32 || patches) return true;
+  if (slabs == 3) return !gelu || ksteps < 4;
+  return slabs < 4 || !(narrow || (gelu && ksteps > 2));
+}
 // Many rows and few channels: the kernel that quantises whole rows (wide.hip) by the estimates, from 2048 rows on (below, they are
 // off by as much as there is to win) and up to the two column blocks of 1536 channels that were timed.  Calls in turn on three buffers of normal
 // values, us, apart / here, own range and given scale: 14070 x 576 -> 256 16.3 / 14.2 and 12.8 / 10.0, 12608 x 768 -> 768 20.6 / 20.0 and 17.1 / 15.1, 7029 x 1152
@@ -669,7 +684,8 @@ static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, bool behind_range, int
   const bool estimated = a.M >= GPUSQ_WIDE_MIN_ROWS && a.N <= 2 * kWideBlocks * kRowBlock;
   if (d.forced < 0 && !estimated && !wide_saves_a_launch(a.M, a.N, a.K, fp32, !behind_range && a.patch_P == 0)) return false;
   p = wide_plan(a.M, a.N, resident, fp32);
-  if (p.chunks == 0 || d.forced == 5 || !estimated) return p.chunks > 0;
+  if (p.chunks == 0 || d.forced == 5) return p.chunks > 0;
+  if (!estimated) return wide_plan_ahead(a, p, fp32);
   if (d.choice == 4) return a.N > 256 && (a.K <= 12 * kStepBytes || a.N < 448 || (fp32 && !behind_range));
   const double margin = behind_range ? wide_margin_behind_range(a.M, a.N, a.K, fp32, i8) : wide_margin(a.K, fp32);
   return d.gemm_us > 0 && wide_us(p, a.M, a.N, a.K, resident, fp32, gelu, i8) < margin * quantise_and_gemm_us(d.gemm_us, a.M, a.N, a.K, fp32, i8);

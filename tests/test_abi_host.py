@@ -616,6 +616,23 @@ def test_short_layers_of_the_kernel_for_whole_rows(lib, M, K, N, own, given, x_d
             assert (f(x_dt, out_dt, M, N, K, epilogue, 0, 256), f(x_dt, out_dt, M, N, K, epilogue, 1, 256)) == (own, given)
 
 
+def _on_whole_rows(lib, M, K, N, fp32, int8_out, gelu, given):
+    f = lib.gpusq_linear_int8_quantiser
+    f.argtypes = [ctypes.c_int, ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int] * 3
+    return f(0 if fp32 else 1, 2 if int8_out else 1, M, N, K, 3 if gelu else 1, given, 256) == 2
+
+
+# sizes that were timed slower on the kernel for whole rows, which then quantise apart, and neighbours that were timed faster: (M, K, N, fp32, int8 output, GELU, given scale)
+@pytest.mark.parametrize("sizes,whole_rows", [
+    ((861, 448, 720, 0, 1, 1, 0), False), ((952, 480, 768, 1, 1, 1, 0), False), ((723, 448, 720, 1, 1, 0, 0), False), ((1254, 384, 784, 1, 0, 0, 0), True),  # a slab of 12 blocks; more outputs
+    ((367, 400, 1424, 0, 1, 1, 0), False), ((542, 416, 2048, 0, 0, 0, 0), True), ((128, 400, 4432, 0, 1, 1, 0), False), ((345, 208, 3728, 0, 0, 0, 0), True),  # column blocks; 256 values
+    ((3998, 400, 1680, 1, 1, 1, 0), False), ((3939, 320, 1936, 1, 1, 1, 0), False), ((2340, 384, 3136, 1, 0, 1, 0), False), ((3939, 320, 1936, 0, 1, 1, 0), True),  # four slabs of fp32
+    ((250, 496, 2724, 0, 0, 0, 0), False), ((1136, 512, 540, 1, 0, 0, 0), False), ((237, 464, 3572, 1, 0, 0, 0), False), ((4087, 272, 1544, 1, 0, 1, 0), False),   # rows stored by four
+    ((224, 240, 2948, 0, 0, 1, 1), False), ((408, 128, 1432, 1, 0, 1, 1), False), ((368, 192, 2020, 1, 0, 0, 1), False), ((875, 128, 4204, 0, 0, 0, 0), True), ((806, 80, 924, 1, 0, 0, 1), True)])
+def test_short_layers_timed_slower_on_whole_rows_quantise_apart(lib, sizes, whole_rows):
+    assert _on_whole_rows(lib, *sizes) == whole_rows
+
+
 def test_what_quantises_a_layer(lib):
     """The answers of gpusq_linear_int8_quantiser and gpusq_linear_int8_launches agree; int32 output has no kernel for whole rows"""
     f = lib.gpusq_linear_int8_quantiser
