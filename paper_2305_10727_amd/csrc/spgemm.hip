@@ -663,6 +663,21 @@ static bool wide_plan_ahead(const GemmArgs& a, const WidePlan& p, bool fp32) {
   if (slabs == 3) return !gelu || ksteps < 4;
   return slabs < 4 || !(narrow || (gelu && ksteps > 2));
 }
+// Rows of Y of no whole 16 channels, stored by four, where the estimates, which are of whole pieces, take them: of 34505 sizes timed (M 2048 ... 66000, K 64 ... 5120, N 32 ... 1532) 33018 stay
+// with whole rows, 1.15 times as fast, 527 slower by more than 3 % (14 % at the most); the 1487 given back are as fast either way, 513 were slower.  The conditions are one block of channels with int8 or GELU
+// output and X up to 28.5 MB (32000 x 256 -> 60, int8 output, 10.4 / 11.1), two of a short K and many rows, int8 output without GELU of many outputs (29916 x 128 -> 1176 fp32 under a given scale 27.8 / 29.8), and fp32 rows
+// behind a range pass, 36 to 96 of them to a CU.  Patches of four channels or more in fp32: in chunks of more than a slab.
+static bool wide_narrow_ahead(const GemmArgs& a, const WidePlan& p, bool fp32, bool i8, bool own) {
+  const int64_t M = a.M, N = a.N, x_bytes = M * a.K * (fp32 ? 4 : 2);
+  const bool gelu = (a.epilogue & GPUSQ_EPI_GELU) != 0;
+  const int ksteps = (int)ceil_div((int64_t)a.K, kStepBytes);
+  if (a.patch_P > 0) return !fp32 || ksteps < 8 || wide_slabs(p) > 1;
+  if (N <= 64) return x_bytes > 28500000 || !(i8 ? x_bytes > 8000000 : gelu);
+  if (N <= 128 && (fp32 ? own && ksteps == 1 && M > 32768 : !own && ((ksteps == 1 && M > 49152) || (ksteps == 2 && M > 32768)))) return false;
+  if (i8 && !gelu && (N > 1024 ? M > 8192 : N > 512 && M > 16384 && fp32 && own && ksteps <= 4)) return false;
+  return !(fp32 && own && N <= 192 && ksteps > 2 && ksteps <= 5 && M > 9216 && M < 24576);
+}
+
 // Many rows and few channels: the kernel that quantises whole rows (wide.hip) by the estimates, from 2048 rows on (below, they are
 // off by as much as there is to win) and up to the two column blocks of 1536 channels that were timed.  Calls in turn on three buffers of normal
 // values, us, apart / here, own range and given scale: 14070 x 576 -> 256 16.3 / 14.2 and 12.8 / 10.0, 12608 x 768 -> 768 20.6 / 20.0 and 17.1 / 15.1, 7029 x 1152
@@ -673,8 +688,7 @@ static bool wide_plan_ahead(const GemmArgs& a, const WidePlan& p, bool fp32) {
 // 20022 sizes so timed (M 2048 ... 65792, K 64 ... 5120, N 32 ... 1536, both types and outputs, with and without GELU) it takes 68 % of the fp16 ones with an
 // own range, 1.15 times as fast there, and 70 % under a given scale, 1.22 times; 49 and 58 % of the fp32 ones, 1.08 and 1.20 times.  2 % of those with an own range
 // and 0.7 % of the others are slower by more than 5 % (8094 x 4608 -> 768 + GELU, int8 output, 59.3 / 66.5; 52052 x 640 -> 1440 under a given scale 67.5 / 79.3).
-// Rows of Y that are no whole 16 channels are stored by four, and the rules are the same: of 218 such sizes they take 1.15 times as fast, 4 slower by more than 3 %
-// (12608 x 768 -> 772 27.6 / 23.7, 50000 x 384 -> 388 38.6 / 33.5, 1576 x 384 -> 1148 11.5 / 8.9; 29916 x 128 -> 1176 fp32, int8 output, under a given scale 27.8 / 29.8).
+// Rows of Y that are no whole 16 channels are stored by four (12608 x 768 -> 772 27.6 / 23.7, 50000 x 384 -> 388 38.6 / 33.5, 1576 x 384 -> 1148 11.5 / 8.9; wide_narrow_ahead).
 // Where the product goes to the kernel for few rows (those have no estimate here) it is ahead beyond 256 channels: 1.1 to 1.3 times up to 12 K steps, 1.1 with
 // more of them up to 447 channels, from there on level or behind but for fp32 under a given scale (2085 x 3920 -> 640 24.7 / 27.8).
 static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, bool behind_range, int resident, const Decision& d, WidePlan& p) {
@@ -686,6 +700,7 @@ static bool wide_takes(const GemmArgs& a, gpusq_dtype dt, bool behind_range, int
   p = wide_plan(a.M, a.N, resident, fp32);
   if (p.chunks == 0 || d.forced == 5) return p.chunks > 0;
   if (!estimated) return wide_plan_ahead(a, p, fp32);
+  if (a.N % 16 != 0 && !wide_narrow_ahead(a, p, fp32, i8, behind_range)) return false;
   if (d.choice == 4) return a.N > 256 && (a.K <= 12 * kStepBytes || a.N < 448 || (fp32 && !behind_range));
   const double margin = behind_range ? wide_margin_behind_range(a.M, a.N, a.K, fp32, i8) : wide_margin(a.K, fp32);
   return d.gemm_us > 0 && wide_us(p, a.M, a.N, a.K, resident, fp32, gelu, i8) < margin * quantise_and_gemm_us(d.gemm_us, a.M, a.N, a.K, fp32, i8);

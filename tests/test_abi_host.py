@@ -633,6 +633,16 @@ def test_short_layers_timed_slower_on_whole_rows_quantise_apart(lib, sizes, whol
     assert _on_whole_rows(lib, *sizes) == whole_rows
 
 
+# rows of Y of no whole 16 channels, of layers that the estimates take: timed slower on whole rows, and neighbours timed faster
+@pytest.mark.parametrize("sizes,whole_rows", [
+    ((43513, 208, 60, 0, 1, 0, 1), False), ((18400, 448, 56, 0, 1, 1, 1), False), ((28812, 144, 40, 0, 0, 1, 1), False), ((25599, 64, 52, 0, 0, 0, 0), True),      # one block of channels
+    ((58500, 176, 88, 0, 0, 0, 1), False), ((55151, 128, 72, 0, 1, 1, 1), False), ((64607, 80, 124, 1, 0, 1, 0), False),                                          # two
+    ((39060, 64, 1080, 0, 1, 0, 0), False), ((29916, 128, 1176, 1, 1, 0, 1), False), ((29308, 160, 696, 1, 1, 0, 0), False), ((16695, 288, 1416, 0, 0, 0, 0), True),  # int8 output of many channels
+    ((9464, 384, 124, 1, 1, 0, 0), False), ((7352, 80, 856, 0, 1, 0, 1), True), ((53665, 2288, 748, 0, 0, 1, 1), True), ((7070, 448, 364, 1, 1, 0, 1), True)])
+def test_narrow_rows_timed_slower_on_whole_rows_quantise_apart(lib, sizes, whole_rows):
+    assert _on_whole_rows(lib, *sizes) == whole_rows
+
+
 def test_what_quantises_a_layer(lib):
     """The answers of gpusq_linear_int8_quantiser and gpusq_linear_int8_launches agree; int32 output has no kernel for whole rows"""
     f = lib.gpusq_linear_int8_quantiser
