@@ -771,11 +771,11 @@ static gpusq_status launch_wide_patches(GemmArgs a, gpusq_dtype dt, int8_t* img_
 }
 
 // Patches of 16 x 16 too few for the kernels that gather them (launch_patch_embed_int8): two launches instead of quantiser, flattened patches and GEMM, four. Of
-// 63 sizes timed (24 to 840 patches of one to four channels, 128 to 1216 channels out, fp16 and fp32) 1.46 times as fast, none less than 1.19: 150 x 768 -> 640 13.8 / 10.3 us, 700 x 1024 -> 192
-// 14.9 / 12.3; more than 1024 values were not timed.
+// 22830 sizes timed (1 to 2000 patches of one to four channels, 32 to 1600 channels out, fp16 and fp32) 1.40 times as fast in the 22158 that it takes, none slower by more than 3 %: 150 x 768 -> 640
+// 13.8 / 10.3 us.  Of four channels, 1024 values, up to 512 patches and 160 K outputs: beyond 351 x 1024 -> 648 fp32 11.8 / 13.3, 756 x 1024 -> 228 11.9 / 12.6; more values were not timed.
 static bool few_patches_take_whole_rows(int64_t M, int64_t N, int64_t K, int epilogue, gpusq_dtype dt, int resident, WidePlan& p) {
   const int forced = forced_kernel();
-  if ((forced >= 0 && forced < 5) || (epilogue & GPUSQ_EPI_GELU) || M * N > 256 * 1024 || K > 8 * kStepBytes || M * K * dtype_bytes(dt) >= ((int64_t)1 << 32)) return false;
+  if ((forced >= 0 && forced < 5) || (epilogue & GPUSQ_EPI_GELU) || M * N > 256 * 1024 || K > 8 * kStepBytes || (K > 6 * kStepBytes && (M * N > 160 * 1024 || M > 512)) || M * K * dtype_bytes(dt) >= ((int64_t)1 << 32)) return false;
   p = wide_plan(M, N, resident, dt == GPUSQ_F32);
   return p.chunks > 0;
 }

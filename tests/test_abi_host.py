@@ -377,6 +377,15 @@ def test_int8_patch_embedding_launches(sizes, launches):
     assert gpusq.lib().gpusq_patch_embed_int8_launches(gpusq.F32, 1, 3, 19600, 19600, 14, 640, 768, 1, 256) == 4
 
 
+# 16 x 16 patches of four channels, timed slower on the kernel for whole rows beyond 512 patches or 160 K outputs, and neighbours that were timed faster
+@pytest.mark.parametrize("sizes,launches", [
+    ((3, 4, 208, 144, 16, 1024, 648, 1), 4), ((6, 4, 128, 112, 16, 1024, 768, 1), 4), ((2, 4, 368, 320, 16, 1024, 204, 1), 4), ((6, 4, 208, 144, 16, 1024, 200, 1), 4),
+    ((6, 3, 128, 112, 16, 768, 768, 1), 2), ((8, 4, 48, 240, 16, 1024, 372, 1), 2), ((6, 4, 32, 144, 16, 1024, 1152, 1), 2)])
+def test_few_patches_timed_slower_on_whole_rows_are_four_launches(sizes, launches):
+    from paper_2305_10727_amd import gpusq
+    assert all(gpusq.lib().gpusq_patch_embed_int8_launches(dt, *sizes, 256) == launches for dt in (gpusq.F32, gpusq.F16))
+
+
 # sizes that were timed slower behind the range pass, and neighbours that were timed faster: both types, or (fp32, fp16)
 @pytest.mark.parametrize("sizes,launches", [
     ((3, 320, 8, 14, 2, 1280, 64, 1), 4), ((5, 64, 64, 72, 4, 1024, 128, 1), 4), ((1, 4, 420, 420, 14, 896, 832, 1), 4), ((1, 3, 420, 420, 14, 640, 576, 1), 2),  # channels
