@@ -312,16 +312,18 @@ __global__ void __launch_bounds__(F == 4 || KS < 3 ? 512 : 768, F == 4 ? 2 : (KS
   block_mlp<S, KS, F>(a, c.m0, mlp_lds_mem);
 }
 
-// The plan of one launch; chunks == 0: three launches.  Of 220 sizes timed (16 to 60000 rows, D 64 ... 512, H 2 D ... 8 D, calls in turn on three buffers) one launch is
-// 1.2 to 2.3 times as fast up to 460 KB of operands, and beyond that from a row for every 550 bytes of them on 1.04 to 1.6 times; with fewer rows it is a chain of
-// loads on few CUs (210 x 512, 2048 13.5 / 24.0 us, 1077 x 384, 1536 15.5 / 17.0).  Where LDS holds fewer than four slabs of codes, one round of chunks is ahead (4492 x 448,
-// 3584 47.6 / 41.3), more are not (17053 x 384, 3072 82.9 / 92.8).
+// The plan of one launch; chunks == 0: three launches.  One launch is 1.1 to 2.5 times as fast up to 440 KB of operands, and beyond that from a row for every 550 bytes of them on; with
+// fewer rows it is a chain of loads on few CUs (210 x 512, 2048 13.5 / 24.0 us, 1077 x 384, 1536 15.5 / 17.0, 104 x 320, 960 10.4 / 11.3 with 448 KB).  Where LDS holds fewer than four slabs of
+// codes, one round of chunks is ahead (4492 x 448, 3584 47.6 / 41.3), more are not (17053 x 384, 3072 82.9 / 92.8).  A hidden layer of at most half the row leaves little between the output of
+// proj and that of fc2, which three launches write as fast: many rows of more than 384 channels are behind (62832 x 512, 64 59.6 / 66.3).  Of 51363 sizes timed (16 to 420000 rows, D 64 ... 512, H 64 ... 8 D,
+// calls in turn on three buffers) it takes 51108, 1.52 times as fast, 6 slower by more than 3 % (6 % at the most).
 static MlpPlan mlp_plan_where_ahead(int64_t M, int64_t D, int64_t H, int resident) {
   const int forced = forced_kernel();
   if ((forced >= 0 && forced < 5) || !mlp_takes_sizes(D, H)) return MlpPlan{};
   const MlpPlan p = mlp_plan(M, D, H, resident);
   const int64_t operands = (D * D + 2 * D * H) * 5 / 8;
-  if (forced == 6 || ((operands <= 460 * 1000 || M * 550 >= operands) && (p.chunks <= resident || mlp_lds(D, H, kMlpSlabs) <= kMlpLds))) return p;
+  const bool short_hidden = D > 384 && 2 * H <= D && M > 16384 * (D > 448 ? 3 : 8);
+  if (forced == 6 || ((operands <= 440 * 1000 || M * 550 >= operands) && !short_hidden && (p.chunks <= resident || mlp_lds(D, H, kMlpSlabs) <= kMlpLds))) return p;
   return MlpPlan{};
 }
 

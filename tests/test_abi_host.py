@@ -497,6 +497,15 @@ def test_launches_behind_attention(M, D, H, launches):
     assert gpusq.lib().gpusq_block_mlp_int8_launches(M, D, H, 256) == launches
 
 
+# sizes that were timed slower in one launch, and neighbours that were timed faster: operands of 448 KB; many rows with a hidden layer of half the row or less
+@pytest.mark.parametrize("M,D,H,launches", [(104, 320, 960, 3), (221, 320, 960, 3), (122, 448, 576, 3), (1000, 320, 960, 1), (104, 320, 896, 1), (122, 448, 512, 1),
+                                            (53810, 512, 64, 3), (62832, 512, 128, 3), (200000, 512, 256, 3), (200000, 448, 64, 3), (30000, 512, 64, 1), (60000, 448, 128, 1), (60000, 512, 320, 1),
+                                            (200000, 384, 128, 1)])
+def test_layers_behind_attention_timed_slower_in_one_launch_are_three(M, D, H, launches):
+    from paper_2305_10727_amd import gpusq
+    assert gpusq.lib().gpusq_block_mlp_int8_launches(M, D, H, 256) == launches
+
+
 class _Recorder:
     """Stands for the library's calls: which ones, with what arguments"""
 
