@@ -344,7 +344,7 @@ static bool patch_f16_ahead(int64_t M, int64_t C, int64_t P, int64_t ksteps, int
   // workgroups just past what `n` of them fill: the CUs wait for the few that are left (two slabs, 16720 x 972 -> 384 29.1 / 34.6)
   auto just_past = [&](int64_t n) { return p.chunks > n && 4 * (int64_t)p.chunks <= 5 * n; };
   if (fit == 2) return M >= 2048 && D <= 512 && !just_past(resident / 2) && !just_past(resident) && !just_past(2 * (int64_t)resident);
-  if (D <= 512) return M >= 640;
+  if (D <= 512) return M >= (C == 4 && D > 256 ? 800 : 640);  // (660 x 256 -> 384 of four channels 5.7 / 6.5)
   // three slabs at the most: all of them (5244 x 648 -> 1152 with two 17.4 / 21.1, 1008 x 800 -> 576 with one 9.7 / 11.2)
   if (fit == 3) return p.slabs == 3 && D <= 1408 && !just_past(2 * (int64_t)resident);
   if (D <= 1408) return M >= 12 * (D - 512) + 512;  // (760 x 576 -> 576 7.0 / 8.2, 1280 x 256 -> 640 7.1 / 7.6)

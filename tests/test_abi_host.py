@@ -357,6 +357,14 @@ def test_patch_embeddings_timed_slower_in_one_launch_are_two(sizes, launches):
     assert gpusq.lib().gpusq_patch_embed_fp16_launches(*sizes, 256) == launches
 
 
+# four channels of the images and more than 256 out: from 800 patches on
+@pytest.mark.parametrize("sizes,launches", [((3, 4, 160, 88, 8, 256, 384, 1), 2), ((25, 4, 210, 28, 14, 832, 320, 1), 2), ((3, 4, 160, 88, 8, 256, 256, 1), 1), ((3, 3, 160, 88, 8, 192, 384, 1), 1),
+                                            ((4, 4, 160, 88, 8, 256, 384, 1), 1)])
+def test_patch_embeddings_of_four_channels_timed_slower_in_one_launch_are_two(sizes, launches):
+    from paper_2305_10727_amd import gpusq
+    assert gpusq.lib().gpusq_patch_embed_fp16_launches(*sizes, 256) == launches
+
+
 @pytest.mark.parametrize("sizes,launches", [
     ((256, 3, 224, 224, 14, 640, 1280, 1), 2), ((1, 3, 14, 14, 14, 592, 512, 0), 2), ((2, 3, 56, 56, 8, 192, 256, 1), 2),
     ((4, 3, 224, 224, 14, 640, 1088, 1), 4),    # too few for the weights: 1024 patches, 1088 channels
