@@ -275,9 +275,9 @@ def main():
                                                                                 r["t_sparse"] / 1e3, r["t_dense"] / 1e3, r["t_dense"] / r["t_sparse"],
                                                                                 r["ops"] / r["t_sparse"] / 1e6))
             print(lines[-1], flush=True)
-    lines += ["", "Patch embedding (a convolution with kernel = stride = P, run as quantise + im2col + sparse GEMM; images N(0,1) fp16, "
-              "hot buffers):", "", "| model | images | P | M | K | N | path | quantise us | im2col us | sparse GEMM us | whole layer us | whole layer, patches "
-              "gathered by the GEMM (P = 16) us |", "|---|---|---|---|---|---|---|---|---|---|---|---|"]
+    lines += ["", "Patch embedding (a convolution with kernel = stride = P; images N(0,1) fp16, hot buffers), as quantise + im2col + sparse GEMM (fused=False), and as "
+              "SparsePatchEmbed runs it by default (P = 16: patches gathered by the product; others: cut in LDS where the sizes favour it):", "", "| model | images | P | M | K | N | path | quantise us | im2col us | sparse GEMM us | whole layer so us | whole layer "
+              "by default us |", "|---|---|---|---|---|---|---|---|---|---|---|---|"]
     dev = torch.device("cuda")
     for model, B, HW, P, D in [] if a.only_blocks or a.only_int4 else [("ViT-B/16, batch 64", 64, 224, 16, 768), ("ViT-L/16, batch 256", 256, 224, 16, 1024),
                                                       ("ViT-H/14, batch 256", 256, 224, 14, 1280)]:
@@ -285,12 +285,10 @@ def main():
         Wc = torch.randn(D, 3, P, P, device=dev) * 0.02
         bias = torch.randn(D, device=dev) * 0.01
         for prec in ("int8", "fp16"):
-            t_fused = None
-            if P == 16:
-                pf = SparsePatchEmbed(B, 3, HW, HW, P, D, prec, fused=True)
-                pf.prepare_weights(Wc)
-                t_fused = _time([lambda: pf.forward(img, bias)], a.iters)
-                del pf
+            pf = SparsePatchEmbed(B, 3, HW, HW, P, D, prec)
+            pf.prepare_weights(Wc)
+            t_default = _time([lambda: pf.forward(img, bias)], a.iters)
+            del pf
             pe = SparsePatchEmbed(B, 3, HW, HW, P, D, prec, fused=False)
             pe.prepare_weights(Wc)
             pe.forward(img, bias)
@@ -299,18 +297,19 @@ def main():
             src = pe.img_q if prec == "int8" else img
             t_i2c = _time([lambda: G.im2col_patches(src, P, pe.K_pad)], a.iters)
             t_q = _time([lambda: G.quantize_int8(img.reshape(1, -1), G.PER_TENSOR)], a.iters) if prec == "int8" else 0.0
-            lines.append("| %s | %dx3x%dx%d | %d | %d | %d | %d | %s | %.1f | %.1f | %.1f | %.1f | %s |" % (
-                model, B, HW, HW, P, pe.M, pe.K_pad, D, prec, t_q, t_i2c, t_gemm, t_all, "%.1f" % t_fused if t_fused else "-"))
+            lines.append("| %s | %dx3x%dx%d | %d | %d | %d | %d | %s | %.1f | %.1f | %.1f | %.1f | %.1f |" % (
+                model, B, HW, HW, P, pe.M, pe.K_pad, D, prec, t_q, t_i2c, t_gemm, t_all, t_default))
             print(lines[-1], flush=True)
             del pe
             torch.cuda.empty_cache()
     lines += ["", "Linear layers of one encoder block on the INT8 path (qkv, proj, fc1 + GELU, fc2; attention and normalisation left out: "
               "proj and fc1 read buffers that nothing refreshes), us per block, hot buffers.  Unchained: every layer writes fp16 and the next "
               "one quantises it with a dynamic per-tensor scale (12 launches at the most).  Chained: static scales, the re-quantisation fused into the "
-              "producer's epilogue (5 launches, 4 where qkv quantises its rows itself), launched one by one or replayed as one HIP graph:", "",
-              "| model | M | D | hidden | unchained us | chained us | chained, HIP graph us |", "|---|---|---|---|---|---|---|"]
+              "producer's epilogue, no norm in front of fc1 (column `launches`: quantise, qkv, proj, fc1, fc2; one less where qkv quantises its rows itself, two less where proj, fc1 and "
+              "fc2 are one), launched one by one or replayed as one HIP graph:", "",
+              "| model | M | D | hidden | launches | unchained us | chained us | chained, HIP graph us |", "|---|---|---|---|---|---|---|---|"]
     for model, M, D, hidden in [] if a.only_int4 else [("DeiT-Tiny, batch 1", 197, 192, 768), ("DeiT-Small, batch 1", 197, 384, 1536), ("ViT-B/16, batch 1", 197, 768, 3072),
-                                ("ViT-B/16, batch 8", 1576, 768, 3072), ("ViT-B/16, batch 64", 12608, 768, 3072)]:
+                                ("ViT-B/16, batch 8", 1576, 768, 3072), ("ViT-B/16, batch 64", 12608, 768, 3072), ("Swin-B stage 3, batch 64", 12544, 512, 2048)]:
         shapes = [(3 * D, D), (D, D), (hidden, D), (D, hidden)]
         Ws = [torch.randn(n, k, device=dev) * 0.02 for n, k in shapes]
         bs = [torch.randn(n, device=dev) * 0.01 for n, k in shapes]
@@ -333,7 +332,9 @@ def main():
             h = lins[2].forward(xin[2], bs[2])
             lins[3].forward(h, bs[3])
         t_un = _time([unchained], a.iters)
-        lines.append("| %s | %d | %d | %d | %.1f | %.1f | %.1f |" % (model, M, D, hidden, t_un, t_chain, t_graph))
+        own = 1 if blk.fold_quantise else G.lib().gpusq_linear_int8_launches(G.F16, M, 3 * D, D, G.EPI_BIAS, 1, 0)
+        launches = own + G.lib().gpusq_block_mlp_int8_launches(M, D, hidden, 0)
+        lines.append("| %s | %d | %d | %d | %d | %.1f | %.1f | %.1f |" % (model, M, D, hidden, launches, t_un, t_chain, t_graph))
         print(lines[-1], flush=True)
         del blk, lins
         torch.cuda.empty_cache()
