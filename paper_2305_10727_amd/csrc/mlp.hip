@@ -11,7 +11,7 @@
 //   - Chunks of whole slabs of 16 rows, at most one slab apart: 12544 rows on 256 CUs as 240 chunks of 48 and 16 of 64 take 41.7 us, as 256 chunks of 49 rows, each as
 //     much work as 64, 46.0.
 // What bounds it: fc1's GELU and codes in the vector units, 20 of 32 us where few CUs are at work (12544 x 512, 2048 with 64 rows in each; start-up 3, proj 4.6, fc2
-// 5), and the board's power limit beyond.  Three launches / one, us: 12544 x 512, 2048 54.8 / 41.7, 3136 x 512, 2048 28.9 / 23.1, 12608 x 192, 768 29.0 / 17.3, 197 x 192, 768
+// 5); on all CUs the clock falls as well, to 2.0 to 2.1 GHz at 1.2 of the board's 1.4 kW.  Three launches / one, us: 12544 x 512, 2048 54.8 / 41.7, 3136 x 512, 2048 28.9 / 23.1, 12608 x 192, 768 29.0 / 17.3, 197 x 192, 768
 // 12.2 / 7.8, 25000 x 256, 1024 44.9 / 30.2, 50176 x 512, 2048 158.7 / 150.0.
 // (All operands touched ahead, a share of them by each workgroup of an XCD, so that the L2 has them: level.  B fragments read one slab ahead: level.)
 #include "mlp_plan.h"

@@ -8,9 +8,9 @@
 //     ahead (three, 0 to 2 % slower); B fragments one step ahead (82.6 us, read in the step itself 89.1).
 //   - Two workgroups of four wavefronts to a CU: one cuts or stores while the other multiplies.  One of 128 patches and eight wavefronts reads the weights half as often,
 //     but nothing runs beside its cutting: 93.8.
-// What bounds it: the matrix instructions at the board's power limit, 38 us of 82 for 65536 x 588 -> 1280, with their weights from the L2 (64 bytes a clock and CU) 50, the
-// 168 MB of output 34 alone, the images 15.  Flattened patches and GEMM / here, us: 65536 x 588 -> 1280 113 / 82, 44000 x 588 -> 768 61 / 42.7, 16384 x 588 -> 768 25.4 / 18.1, 4096 x 588
-// -> 320 13.2 / 9.9, 36936 x 144 -> 320 21.1 / 14.2.  (Output through the L2 instead of past it: 101 us.)
+// What bounds it: the board's power limit (1.39 of 1.4 kW, 1.85 GHz); of 82 us for 65536 x 588 -> 1280 the matrix instructions alone are 38 (their pipes are 31 % busy), with their
+// weights from the L2 (64 bytes a clock and CU) 50, the 168 MB of output 34 alone, the images 15.  Flattened patches and GEMM / here, us: 65536 x 588 -> 1280 113 / 82, 44000 x 588 -> 768
+// 61 / 42.7, 16384 x 588 -> 768 25.4 / 18.1, 4096 x 588 -> 320 13.2 / 9.9, 36936 x 144 -> 320 21.1 / 14.2.  (Output through the L2 instead of past it: 101 us.)
 // int8, quantiser's two launches, flattened patches and GEMM / range pass and here: 62400 x 588 -> 576 89.5 / 63.2, 16200 x 588 -> 192 28.4 / 18.0, 2048 x 588 -> 192 15.7 / 11.0, from
 // fp32 images 57600 x 588 -> 1216 126.6 / 107.5.  What bounds that: the codes go to the images' and to LDS two at a time, 74 stores of each for a thread and 64 patches.
 #include "patches_plan.h"
@@ -336,7 +336,7 @@ static gpusq_status launch_patches(GemmArgs a, const PatchPlan& p, const void* i
 // with one slab 42390 x 1600 -> 448 124 / 137).  What it costs is not the patches' values but their rows: a patch is cut in batches of 7 or 14 rows of one channel of the image, full
 // or not, so many channels of few rows are slow, 2420 x 1280 -> 64 of 320 channels of 2 x 2 12.0 / 212.9, 9000 x 512 of 32 channels of 4 x 4 three times as slow; up to four channels are taken.
 // Of 10538 sizes timed (600 to 80000 patches of 2 x 2 to 28 x 28, 1 to 320 channels, 64 to 3072 channels out, calls in turn on three buffers) it takes 6551, 1.48 times as fast in one
-// launch, 10 of them slower by 3 to 8 %.  16 x 16 patches, whose 16-byte pieces need no cutting, have gpusq_patch_embed16_fp16 (25088 x 768 -> 768 28.3, here 43.1) or, few of them, the
+// launch, 10 of them slower by 3 to 8 %; of 46400 others that it takes, up to 400000 patches, 1.76 times, 147 slower by more than 3 % (17 % at the most).  16 x 16 patches, whose 16-byte pieces need no cutting, have gpusq_patch_embed16_fp16 (25088 x 768 -> 768 28.3, here 43.1) or, few of them, the
 // two launches (832 x 768 -> 256 7.8, here 8.1).
 static bool patch_f16_ahead(int64_t M, int64_t C, int64_t P, int64_t ksteps, int64_t D, const PatchPlan& p, int resident) {
   const int fit = patch_slabs(ksteps);
@@ -356,7 +356,7 @@ static bool patch_f16_ahead(int64_t M, int64_t C, int64_t P, int64_t ksteps, int
 // a workgroup has more than two slabs, rows of 2, 4 or 8 pixels, which leave half of a batch of 7 empty, only with one or two batches (50160 x 192 -> 256 fp32 29.9 / 36.6, 75776 x 48 -> 192
 // fp32 23.7 / 27.6); 14 rows leave nothing empty, the others are behind just past a round of workgroups (33120 x 300 -> 1088 40.5 / 45.3).  Patches of more than 14 rows are 28 rows of work
 // (4464 x 972 -> 896 24.0 / 30.4).  Of 21715 sizes timed (16 to 80000 patches of 2 x 2 to 14 x 14, 1 to 320 channels, 64 to 3072 channels out, fp16 and fp32) it takes 13337, 1.42 times as fast,
-// 8 of them slower by more than 3 %.
+// 8 of them slower by more than 3 %; of 51691 others that it takes, up to 400000 patches, 1.41 times, 194 slower (17 % at the most).
 static bool patch_i8_ahead(int64_t M, int64_t C, int64_t P, int64_t ksteps, int64_t D, bool fp32, const PatchPlan& p, int resident) {
   if (P > 14 || C > 3 || patch_slabs(ksteps) < 3 || D > 1408 || M < (fp32 ? 8 : 2) * (D - 512)) return false;
   if (p.slabs <= 2 || P == 14) return true;

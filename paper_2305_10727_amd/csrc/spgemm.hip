@@ -793,7 +793,8 @@ bool few_patches_take_whole_rows(int64_t M, int64_t N, int64_t K, int epilogue, 
 // range pass does come first, but the kernels that gather patches take longer than a layer's, which makes up for it.  Of 403 sizes timed (72 to
 // 576 patches an image, 256 to 1024 values each, 192 to 1536 channels) it takes 238 of fp16, 1.19 times as fast, none slower, and 101 of fp32, 1.06 times, 8 %
 // slower at the most (29120 x 256 -> 1088; apart / here 62 images of 304 x 304 -> 704 41.2 / 37.4).  Below 2048 patches the line for a layer with an own range is theirs
-// as well (1536 x 768 -> 832 13.4 / 10.3, 560 x 256 -> 640 10.9 / 8.4, 704 x 768 -> 640 fp32 10.9 / 12.1; 53 sizes 1.2 times as fast, none slower).
+// as well (1536 x 768 -> 832 13.4 / 10.3, 560 x 256 -> 640 10.9 / 8.4, 704 x 768 -> 640 fp32 10.9 / 12.1; of 21035 sizes, 18008
+// of them of fewer than 2048 patches, 77 are slower by more than 3 %, 11 % at the most).
 gpusq_status launch_patch_embed_int8(GemmArgs a, gpusq_dtype dt, int8_t* img_q, float* scale, void* workspace, hipStream_t s) {
   const int resident = num_cus();
   const int choice = decide(true, a.M, a.N, a.K, false, resident, true).choice;

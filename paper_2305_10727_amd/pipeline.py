@@ -206,11 +206,11 @@ class EncoderBlockLinears:
     """The four linear layers of one encoder block (qkv, proj, fc1, fc2) on the INT8 path with static, calibrated
     activation scales, the deployment form with quantise / dequantise nodes around every linear layer: the
     re-quantisation of a layer's output with the next layer's input scale is fused into its epilogue (qkv -> int8,
-    fc1 -> GELU -> int8, which fc2 reads directly), and without a norm in between proj writes fc1's codes beside its fp16 output, so one block is
-    five launches of the library, with a norm six:
-        quantise x, qkv, [attention], proj, [residual + norm, quantise h], fc1 (GELU), fc2;
-    with few rows (problems of the latency kernel) qkv, and fc1 behind a norm, quantise their fp16 input on the way in, each where its sizes
-    favour it: a launch less for each; and without a norm proj, fc1 and fc2 are one launch up to 512 channels (gpusq_block_mlp_int8).
+    fc1 -> GELU -> int8, which fc2 reads directly).  With a norm one block is six launches of the library:
+        quantise x, qkv, [attention], proj, [residual + norm], quantise h, fc1 (GELU), fc2;
+    without one proj writes fc1's codes beside its fp16 output, which is a launch less, and up to 512 channels proj, fc1 and fc2 are one launch where that
+    is ahead (gpusq_block_mlp_int8), two less again.  qkv, and fc1 behind a norm, quantise their fp16 input on the way in where their sizes favour it: a launch
+    less for each.
     Attention and the normalisation are not part of the library: `attention(qkv_int8 [M,3D], out_int8 [M,D])` and
     `norm(proj_fp16 [M,D]) -> fp16 [M,D]` are the caller's (stubs in the tests and the report).  capture() records the
     whole sequence into a HIP graph, which takes the host out of the loop.
