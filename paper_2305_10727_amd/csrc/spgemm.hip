@@ -647,7 +647,7 @@ static bool wide_saves_a_launch(int64_t M, int64_t N, int64_t K, bool fp32, bool
   return !given && (!fp32 || outputs <= (1 << 21)) && outputs >= (1 << 20) && K <= (M < GPUSQ_WIDE_MIN_ROWS ? 8 : 6) * kStepBytes;
 }
 // Of these, the plans that are ahead.  A chunk of one slab has little work for the operands that it fetches: the more 64-channel blocks it has and the longer K, the more outputs it takes
-// (2^18 for each K step and block beyond a line; own range, 12 blocks, 700 x 512 -> 768 5 % behind, 1100 x 512 -> 768 1 % ahead; at most 750000, for 1000 x 512 -> 768 is held here by a test); the line
+// (2^18 for each K step and block beyond a line; own range, 12 blocks, fp32 753 x 512 -> 736 9.0 / 9.6, 1472 x 480 -> 752 11.0 / 10.2; at most 750000, for 1000 x 512 -> 768, 7 % behind in fp32, is held here by a test); the line
 // is lower for rows that are stored by four, and for patches of fp32.  fp32 rows in chunks of four slabs, in which the epilogue stands alone behind a short K, are behind by 2 to 15 %; without a GELU those of whole 16 channels stay (2047 x 512 -> 4096
 // is held there by a test).  Of 61274 and 12081 layers of whole and of no whole 16 channels timed (seldom more than 4096 rows, K 64 to 5120, N 32 to 5120) this takes 60372 and 10827, 1.21 and 1.16 times
 // as fast, 150 and 133 slower by more than 3 % (12 % at the most); of the others 345 and 585 were slower.

@@ -4,7 +4,8 @@ import numpy as np
 import pytest
 
 import oracle
-from test_gpu_parity import dev, force_kernel, g, host  # noqa: F401
+from test_gpu_parity import force_kernel, g  # noqa: F401
+from test_gpu_parity import dev, host
 from test_gpu_wide_rows import _refined
 
 torch = pytest.importorskip("torch")
